@@ -17,7 +17,7 @@
 namespace csgs {
 
 
-// Block b of the grid: row block b / slots (four tiles of TR consecutive output rows, one per wavefront) and
+// Block b of the grid: row block b / slots (four tiles of tr consecutive output rows, one per wavefront) and
 // feature slice b % slots (G * V features; slots = the slice count rounded up to a multiple of 8 when there is more
 // than one slice, blocks beyond the slice count leave at once).  The hardware deals consecutive blocks
 // round-robin to the 8 XCDs, so all blocks of slice s run on XCD s mod 8: that XCD's L2 sees only slice s of the
@@ -34,14 +34,13 @@ __global__ __launch_bounds__(AGG_BLOCK) void aggregate_k(const int32_t *__restri
                                                          const int32_t *__restrict__ src_row, int32_t F,
                                                          float *__restrict__ Z, int64_t ldz,
                                                          const float *__restrict__ mask, int64_t ldm,
-                                                         int32_t n_slices, int32_t slots, CompStride cs)
+                                                         int32_t n_slices, int32_t slots, int32_t tr, CompStride cs)
 {
-    constexpr int TR = tile_rows(G);
-    __shared__ WaveStage<TR> stage[AGG_WAVES];
+    __shared__ WaveStage<tile_rows(G)> stage[AGG_WAVES];
     __shared__ double heads[AGG_WAVES][WAVE * V], carries[AGG_WAVES][2 * G * V];
     const int32_t slice = (int32_t)(blockIdx.x % (unsigned)slots);
     if (slice >= n_slices) return;
-    const int64_t block_row0 = (int64_t)(blockIdx.x / (unsigned)slots) * (AGG_WAVES * TR);
+    const int64_t block_row0 = (int64_t)(blockIdx.x / (unsigned)slots) * (AGG_WAVES * tr);
     adj_rowptr = inst_ptr(adj_rowptr, cs.adj); adj_col = inst_ptr(adj_col, cs.adj); adj_val = inst_ptr(adj_val, cs.adj);
     nS_dev = inst_ptr(nS_dev, cs.adj); n_cols_p = inst_ptr(n_cols_p, cs.adj); src_row = inst_ptr(src_row, cs.adj);
     Xl = inst_ptr(Xl, cs.x); Xr = inst_ptr(Xr, cs.xr); Z = inst_ptr(Z, cs.out);
@@ -57,11 +56,11 @@ __global__ __launch_bounds__(AGG_BLOCK) void aggregate_k(const int32_t *__restri
     const int32_t slice0 = slice * G * V;
     const int32_t f = slice0 + (tid % G) * V;
     const bool active = f < F;  // F is a multiple of V (checked on the host)
-    const bool is_long = aggregate_tile<T, V, G, RELU>(stage[wave], heads[wave], carries[wave], block_row0 + (int64_t)wave * TR, 0, slice0, f,
+    const bool is_long = aggregate_tile<T, V, G, RELU>(stage[wave], tr, heads[wave], carries[wave], block_row0 + (int64_t)wave * tr, 0, slice0, f,
                                                        active, adj_rowptr, adj_col, adj_val, nS_bound, nS, n_cols, Xl, ldl, rows_l,
                                                        Xr, ldr, rows_r, src_row, Z, ldz, mask, ldm);
     if (__syncthreads_or(is_long ? 1 : 0))
-        aggregate_long_rows<T, V, G, RELU>(&heads[0][0], block_row0, 0, is_long, f, active, adj_rowptr, adj_col, adj_val, n_cols, Xl, ldl,
+        aggregate_long_rows<T, V, G, RELU>(&heads[0][0], tr, block_row0, 0, is_long, f, active, adj_rowptr, adj_col, adj_val, n_cols, Xl, ldl,
                                            rows_l, Xr, ldr, rows_r, src_row, Z, ldz, mask, ldm);
 }
 
@@ -70,15 +69,24 @@ static int launch_agg(const int32_t *rp, const int32_t *col, const float *val, i
                       int64_t ldl, int64_t rl, const void *Xr, int64_t ldr, int64_t rr, const int32_t *src_row, int32_t F, int relu, float *Z, int64_t ldz,
                       const float *mask, int64_t ldm, int kid, hipStream_t st, const CompInst &ci = CompInst{})
 {
-    constexpr int BLOCK_ROWS = AGG_WAVES * tile_rows(G);
-    const int64_t row_blocks = ((int64_t)nS + BLOCK_ROWS - 1) / BLOCK_ROWS;
     const int64_t n_slices = (F + G * V - 1) / (G * V);
     const int64_t slots = n_slices > 1 ? (n_slices + 7) / 8 * 8 : 1;
+    // Rows per wavefront.  A full tile (8 rows per lane group) shares the cost of its set-up among the most rows, but a
+    // launch for one mini-batch then has too few wavefronts: each walks through its tile's edges alone.  Tiles are
+    // halved until the launch has 512 blocks, two per compute unit (us per launch, full / this rule, one mini-batch:
+    // 2048 rows of 27 edges, F = 256, 81 / 24; 8192 x 2.8, F = 256, 21 / 17; 4096 x 1.6, F = 512, 13 / 9; 256 x 2,
+    // F = 64, 12 / 7).  Not further: at 1024 blocks the set-up dominates (8192 x 2.8: 22; 4096 x 1.6: 13), as it does
+    // with less than half a row per lane group (1024 x 2.2, F = 256: 4 rows per wavefront 8.6, 8 rows 7.6).
+    int tr = tile_rows(G);
+    constexpr int tr_min = WAVE / G / 2 > 2 ? WAVE / G / 2 : 2;
+    auto blocks_of = [&](int r) { return ((int64_t)nS + AGG_WAVES * r - 1) / (AGG_WAVES * r); };
+    while (tr > tr_min && blocks_of(tr) * n_slices * ci.n < 512) tr >>= 1;
+    const int64_t row_blocks = blocks_of(tr);
     if (row_blocks * slots > 0x7FFFFFFFll) return CSGS_EUNSUPPORTED;
     const dim3 grid((unsigned)(row_blocks * slots), 1, (unsigned)ci.n);
 #define CSGS_AGG_LAUNCH(RELU)                                                                                                     \
     CSGS_LAUNCH_ID(kid, (aggregate_k<T, V, G, RELU>), grid, dim3(AGG_BLOCK), st, rp, col, val, nS, nsd, ncp, (const T *)Xl, ldl, rl, \
-                   (const T *)Xr, ldr, rr, src_row, F, Z, ldz, mask, ldm, (int32_t)n_slices, (int32_t)slots, ci.cs)
+                   (const T *)Xr, ldr, rr, src_row, F, Z, ldz, mask, ldm, (int32_t)n_slices, (int32_t)slots, (int32_t)tr, ci.cs)
     if (relu) CSGS_AGG_LAUNCH(true); else CSGS_AGG_LAUNCH(false);
 #undef CSGS_AGG_LAUNCH
     CSGS_LAUNCH_CHECK();

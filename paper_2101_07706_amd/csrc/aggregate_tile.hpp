@@ -206,7 +206,7 @@ struct __align__(16) StagedEdge {
 // (G lanes each, spread over the slice's features) then take equal shares of the staged edges, whatever rows
 // they belong to, and stream through them; a row whose edges fall into several shares is put together from the
 // groups' partial sums afterwards, in group order.
-template <int TR, int PL = POOL>
+template <int TR /* most rows of a tile */, int PL = POOL>
 struct WaveStage {
     StagedEdge pool[PL + 1];     // [PL]: the edge that does not count (zeros, weight 0, ends no row)
     int32_t beg[TR];             // first edge of the row
@@ -220,16 +220,16 @@ enum { HEAD_NONE = 0,    // the share begins with the first edge of a row
        HEAD_CLOSED = 1,  // it begins inside a row, and that row's last edge is in the share: head = the row's edges in the share
        HEAD_OPEN = 2 };  // every edge of the share (possibly none) belongs to a row that began earlier and goes on: head = all of them
 
-constexpr int tile_rows(int G) { return (WAVE / G) * 8 < WAVE ? (WAVE / G) * 8 : WAVE; }   // about 8 rows per lane group
-constexpr int ilog2(int n) { return n <= 1 ? 0 : 1 + ilog2(n / 2); }
+constexpr int tile_rows(int G) { return (WAVE / G) * 8 < WAVE ? (WAVE / G) * 8 : WAVE; }   // about 8 rows per lane group: the most a tile holds
 
-// One wavefront, one tile of TR output rows, one slice of G * V features starting at feature `slice0`.
+// One wavefront, one tile of `tr` output rows (a power of two, at most tile_rows(G)), one slice of G * V features starting
+// at feature `slice0`.
 // head: LDS, WAVE * V doubles; carry: LDS, 2 * G * V doubles.
 // Row r of the call is stored at Z + (r - out_row0) * ldz.  ZLDS: Z is a tile in LDS.  PL: edges staged at a time.
 // WHOLE (G = 64: the wavefront is one lane group): the sum of a row that goes on beyond the staged edges stays in
 // the registers, and neither `head` nor `carry` is used (null).
 template <typename T, int V, int G, bool RELU, int PL = POOL, bool ZLDS = false, bool WHOLE = false>
-__device__ inline bool aggregate_tile(WaveStage<tile_rows(G), PL> &st, double *__restrict__ head, double *__restrict__ carry, int64_t row0, int64_t out_row0,
+__device__ inline bool aggregate_tile(WaveStage<tile_rows(G), PL> &st, int tr, double *__restrict__ head, double *__restrict__ carry, int64_t row0, int64_t out_row0,
                                       int32_t slice0, int32_t f, bool active, const int32_t *__restrict__ adj_rowptr,
                                       const int32_t *__restrict__ adj_col, const float *__restrict__ adj_val, int32_t nS_bound,
                                       int32_t nS, int64_t n_cols, const T *__restrict__ Xl, int64_t ldl, int64_t rows_l,
@@ -237,21 +237,20 @@ __device__ inline bool aggregate_tile(WaveStage<tile_rows(G), PL> &st, double *_
                                       float *__restrict__ Z, int64_t ldz, const float *__restrict__ mask, int64_t ldm)
 {
     constexpr int NG = WAVE / G;   // lane groups per wavefront
-    constexpr int TR = tile_rows(G);
     constexpr int UNR = unr<V>();
     static_assert(!WHOLE || G == WAVE, "whole rows: one lane group per wavefront");
     constexpr int ROUNDS = PL >= 2 * WAVE ? 2 : 1;   // staging rounds whose loads are asked for together
     const int lane = lane_id();
-    // ---- lane l < TR looks at row l of the tile
+    // ---- lane l < tr looks at row l of the tile
     const int64_t row = row0 + lane;
     const int64_t row_c = row < nS_bound ? row : (int64_t)nS_bound - 1;   // the row pointers have nS_bound + 1 entries
     const int32_t rbeg = adj_rowptr[row_c], rend = adj_rowptr[row_c + 1];
-    const bool in_call = lane < TR && row < nS;
+    const bool in_call = lane < tr && row < nS;
     const int32_t full_len = in_call ? rend - rbeg : 0;
     const bool is_long = full_len > LONG_ROW;
     const int32_t len = (is_long || full_len < 0) ? 0 : full_len;
     const int32_t incl = wave_inclusive_scan(len);
-    if (lane < TR) {
+    if (lane < tr) {
         st.beg[lane] = rbeg;
         st.len[lane] = len;
         st.xs[lane + 1] = incl;
@@ -268,7 +267,7 @@ __device__ inline bool aggregate_tile(WaveStage<tile_rows(G), PL> &st, double *_
     const uint32_t lane_off = active ? (uint32_t)((lane % G) * V * (int)sizeof(T)) : 0u;   // a lane past the last feature reads the slice's start and stores nothing
     __builtin_amdgcn_wave_barrier();
     // ---- rows without kept edges are zero rows
-    for (int rr = grp; rr < TR; rr += NG) {
+    for (int rr = grp; rr < tr; rr += NG) {
         if (st.ordinary[rr] && st.len[rr] == 0 && active) {
             double zero[V];
 #pragma unroll
@@ -299,9 +298,8 @@ __device__ inline bool aggregate_tile(WaveStage<tile_rows(G), PL> &st, double *_
             for (int k = 0; k < ROUNDS; ++k) {
                 const int32_t s = s0 + k * WAVE + lane;
                 const int32_t sa = cb + (s < S ? s : S - 1);   // a lane beyond the end repeats the last edge and stores nothing
-                int lo = 0, hi = TR;   // the row r with xs[r] <= sa < xs[r + 1]
-#pragma unroll
-                for (int step = 0; step < ilog2(TR); ++step) {
+                int lo = 0, hi = tr;   // the row r with xs[r] <= sa < xs[r + 1]
+                for (int span = tr; span > 1; span >>= 1) {
                     const int m = (lo + hi) >> 1;
                     if (st.xs[m] <= sa) lo = m; else hi = m;
                 }
@@ -461,7 +459,7 @@ __device__ inline bool aggregate_tile(WaveStage<tile_rows(G), PL> &st, double *_
 // a time, each of its 256 / G lane groups takes a contiguous share of the row's edges, and the groups' sums are
 // added in group order through LDS (fixed order: the result does not depend on timing).
 template <typename T, int V, int G, bool RELU, bool ZLDS = false>
-__device__ inline void aggregate_long_rows(double *__restrict__ part /* LDS, AGG_BLOCK * V */, int64_t block_row0, int64_t out_row0, bool is_long, int32_t f,
+__device__ inline void aggregate_long_rows(double *__restrict__ part /* LDS, AGG_BLOCK * V */, int tr, int64_t block_row0, int64_t out_row0, bool is_long, int32_t f,
                                            bool active, const int32_t *__restrict__ adj_rowptr, const int32_t *__restrict__ adj_col,
                                            const float *__restrict__ adj_val, int64_t n_cols, const T *__restrict__ Xl,
                                            int64_t ldl, int64_t rows_l, const T *__restrict__ Xr, int64_t ldr, int64_t rows_r,
@@ -469,8 +467,7 @@ __device__ inline void aggregate_long_rows(double *__restrict__ part /* LDS, AGG
                                            const float *__restrict__ mask, int64_t ldm)
 {
     constexpr int UNITS = AGG_BLOCK / G;
-    constexpr int TR = tile_rows(G);
-    __shared__ int32_t long_rows[AGG_WAVES * TR];   // row in the block, in row order
+    __shared__ int32_t long_rows[AGG_WAVES * tile_rows(G)];   // row in the block, in row order
     __shared__ int32_t wave_cnt[AGG_WAVES];
     const int tid = (int)threadIdx.x;
     const int lane = tid & (WAVE - 1), wave = tid >> 6;
@@ -482,7 +479,7 @@ __device__ inline void aggregate_long_rows(double *__restrict__ part /* LDS, AGG
         if (w2 < wave) base += wave_cnt[w2];
         cnt += wave_cnt[w2];
     }
-    if (is_long) long_rows[base + __popcll(m & ((1ull << lane) - 1ull))] = wave * TR + lane;
+    if (is_long) long_rows[base + __popcll(m & ((1ull << lane) - 1ull))] = wave * tr + lane;
     __syncthreads();
     const int unit = tid / G, g = tid % G;
     const int gbase = lane & ~(G - 1);
