@@ -32,8 +32,8 @@
  *   - `ws` describes scratch memory (see csgs_workspace), prepared once with
  *     csgs_workspace_init().  Every call leaves it ready for the next.  Calls that share one
  *     workspace must be ordered on one stream.  Calls on DIFFERENT workspaces may run side by
- *     side on different streams; at most four such call sequences per device at a time (two
- *     kernels hold all their blocks resident while they wait for each other, and four of them
+ *     side on different streams; at most four such call sequences per device at a time (one
+ *     kernel holds all its blocks resident while they wait for each other, and four of them
  *     fit a compute unit together; a sequence that processes several instances per call, see
  *     csgs_workspace, counts once: its instances are dispatched one after the other).
  *   - Replay.  Nothing a kernel needs to tell one call from the next is fixed at launch time

@@ -24,13 +24,15 @@ __host__ __device__ inline size_t align_up(size_t x, size_t a) { return (x + a -
 constexpr int CAND_TILE = 1024;   // node ids per block in the candidate scan
 constexpr int EDGE_TILE = 1024;   // edges per chunk in the flat edge passes
 constexpr int EDGE_GRID = 512;    // chunk blocks of the weight scan (grid-stride over chunks, they wait for nobody): two per compute unit
-constexpr int HIT_TILE_WORDS = 256;   // 64-position bitmap words per block in the hit compaction
+constexpr int HIT_MIN_WORDS = 16;     // fewest 64-position bitmap words a block of the hit compaction takes
+constexpr int HIT_GRID = 512;         // most blocks of it (they wait for nobody)
 constexpr int ROW_TILE = 1024;    // rows of S per block in the degree prefix
 // Weight scan through owners: edges that end in the local id range are handed, chunk by chunk, to
 // blocks that each own SUB_IDS consecutive local ids and add them up in LDS.
 constexpr int SUB_IDS = 2048;                     // ids per owner block (16 KB of 64-bit sums)
 constexpr int SUB_MAX = 128;                      // most owner blocks: local ranges up to SUB_IDS * SUB_MAX ids
 constexpr int64_t STAGE_EDGES_MAX = 8ll << 20;    // most edges of a call that are handed over this way
+constexpr int EPOCH_WORDS = 8;        // counters on the device (lookback.hpp)
 constexpr int META_WORDS = 4;
 constexpr int META_ROWS = 0;          // rows the latest row_prefix covered (the count behind eoff / rowstart)
 constexpr int META_EDGES = 1;         // eoff[rows]: edges of those rows (0 when above the workspace's capacity)
@@ -57,7 +59,6 @@ struct Workspace {
     uint64_t *wtable;    // [n_nodes]  per-node fixed-point weight accumulator
     uint8_t *tileflag;   // [8 * ceil(n_nodes/64)] byte g = 1: some node of ids 8g .. 8g+7 was touched (read 8 at a time: one 64-id word)
     uint32_t *hit;       // [n_nodes]  draws per candidate position
-    uint64_t *cbitmap;   // [ceil(n_nodes/64)] bit set = candidate position was drawn
     // persistent: zeroed once, then never cleared; an entry counts only if it carries the tag of
     // the current call
     uint64_t *rank;      // [n_nodes]  (tag << 32) | (position in S_next + 1)
@@ -65,8 +66,9 @@ struct Workspace {
     uint64_t *partial;   // [4 * n_tiles] per-tile candidate counts and weight sums
     uint64_t *gtot;      // [4 * ceil(n_tiles / 64)] the same per group of 64 tiles
     uint64_t *cand_flag; // [n_tiles] tag of the call whose partial sums a tile holds
-    uint64_t *epoch;     // [4] call counter and draw tag (see lookback.hpp); advanced on the device
-    uint64_t *hit_ts;    // scan state of the hit tiles (1 sum per tile)
+    uint64_t *epoch;     // [EPOCH_WORDS] call counter and draw tag (see lookback.hpp); advanced on the device
+    uint64_t *cbitmap[2]; // [ceil(n_nodes/64)] bit set = candidate position was drawn.  Draws take turns: the compaction of one
+                         // clears what the one before set
     // per call.  The row offsets exist twice: while the adjacency pass of one layer reads one set,
     // its spare blocks prepare the other for the next layer (rows = the node set just sampled).
     RowOffsets rows[2];
@@ -80,7 +82,7 @@ struct Workspace {
     uint64_t *stage_done;// [stage_chunks] persistent: tag of the call whose hand-over of this chunk is complete
     int64_t stage_chunks;
     int64_t chunk_cap;   // chunks of EDGE_TILE edges the adjacency scan can describe
-    int64_t n_tiles, hit_tiles, rp_tiles;
+    int64_t n_tiles, rp_tiles;
     size_t clean_bytes;  // size of the clean part
     size_t bytes;        // size of one instance's workspace (a multiple of 256)
     int32_t n_inst;      // instances a call on this workspace processes (set by open_workspace)
@@ -141,21 +143,19 @@ __host__ inline Workspace carve(void *base, int64_t n_nodes, int64_t nS_max, int
     };
     const size_t words = (size_t)(n_nodes + 63) / 64;
     w.n_tiles = (n_nodes + CAND_TILE - 1) / CAND_TILE;
-    w.hit_tiles = ((int64_t)words + HIT_TILE_WORDS - 1) / HIT_TILE_WORDS;
     w.chunk_cap = (edges_max + EDGE_TILE - 1) / EDGE_TILE;
     if (w.chunk_cap < 1) w.chunk_cap = 1;
     w.wtable = (uint64_t *)take((size_t)n_nodes * 8);
     w.tileflag = (uint8_t *)take(words * 8);
     w.hit = (uint32_t *)take((size_t)n_nodes * 4);
-    w.cbitmap = (uint64_t *)take(words * 8);
     w.clean_bytes = off;
     w.rank = (uint64_t *)take((size_t)n_nodes * 8);
     w.member = (uint64_t *)take((size_t)((n_nodes + 31) / 32) * 8);
     w.partial = (uint64_t *)take((size_t)w.n_tiles * 4 * 8);
     w.gtot = (uint64_t *)take((size_t)((w.n_tiles + 63) / 64) * 4 * 8);
     w.cand_flag = (uint64_t *)take((size_t)w.n_tiles * 8);
-    w.epoch = (uint64_t *)take(4 * 8);
-    w.hit_ts = (uint64_t *)take(scan_state_words(w.hit_tiles, 1) * 8);
+    w.epoch = (uint64_t *)take(EPOCH_WORDS * 8);
+    for (int b = 0; b < 2; ++b) w.cbitmap[b] = (uint64_t *)take(words * 8);
     w.adj_ts = (uint64_t *)take(scan_state_words(w.chunk_cap, 1) * 8);
     w.rp_tiles = (nS_max + ROW_TILE - 1) / ROW_TILE;
     w.rp_ts = (uint64_t *)take(scan_state_words(w.rp_tiles, 1) * 8);
@@ -200,9 +200,9 @@ __host__ inline InstStride inst_stride(const Workspace &w) { return InstStride{(
 // must have all its blocks resident at once.  Alone on the device that is certain (registers and
 // LDS allow several times as many).  Beside kernels of other streams it still holds as long as the
 // waiting kernels in flight fit together, because every other kernel drains by itself: the
-// compaction of drawn positions (33 KB of LDS) runs 1 block per unit and the adjacency filter
-// (13 KB) 2, so four call sequences on four workspaces can be in flight on one device within the
-// 2048 threads and 160 KB of a compute unit.  That is the documented limit.
+// adjacency filter (17 KB of LDS) runs 2 blocks per unit, so four call sequences on four workspaces
+// can be in flight on one device within the 2048 threads and 160 KB of a compute unit.  That is the
+// documented limit.
 // With several instances per call (blockIdx.z) the grid is that many times as large, but blocks
 // wait only for blocks of their own instance and the hardware hands out a grid's blocks in
 // ascending x, then y, then z: an instance is dispatched completely before the next one starts, a

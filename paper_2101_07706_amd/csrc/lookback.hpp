@@ -49,8 +49,13 @@ constexpr int LOOKBACK_SPIN_LIMIT = 1 << 22;
 constexpr int EPOCH_CALLS = 0;   // library calls completed on this workspace
 constexpr int EPOCH_DRAW = 1;    // value of (calls + 1) during the latest draw: tags the rank table
 constexpr int EPOCH_WAIT = 2;    // 0, or 1 + the number of polls a wait may take (set through csgs_workspace_wait_limit)
+// Which of the two position bitmaps a draw uses.  A word is advanced only by a kernel that does not read it (its blocks
+// run in any order): the draw reads NEXT and leaves CUR and the bitmap's extent, the compaction reads those and sets NEXT.
+constexpr int EPOCH_BITMAP_NEXT = 3, EPOCH_BITMAP_CUR = 4;
+constexpr int EPOCH_BITMAP_USED = 5;   // [2] words of each bitmap that its latest draw may have set
+static_assert(EPOCH_BITMAP_USED + 2 <= EPOCH_WORDS, "epoch words");
 // one tag space per scan-state region, so the kernels of one call never mistake each other's flags
-enum TagSlot { SLOT_ROWS = 1, SLOT_CAND = 2, SLOT_HITS = 3, SLOT_ADJ = 4, SLOT_ROWS_NEXT = 5, SLOT_STAGE = 6 };
+enum TagSlot { SLOT_ROWS = 1, SLOT_CAND = 2, SLOT_ADJ = 4, SLOT_ROWS_NEXT = 5, SLOT_STAGE = 6 };
 
 __device__ inline int wait_limit(const uint64_t *epoch)
 {

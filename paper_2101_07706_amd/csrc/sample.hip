@@ -10,11 +10,9 @@
 //                 CDF staged in LDS, the rest is an 8-ary search on the global array (seven
 //                 independent probes per round).  Hits are counted per candidate position with
 //                 integer atomics; first hits set a position bitmap.
-//   hits_fused    single pass over the position bitmap (tiles of 256 words): ordered list of
-//                 the tile's hits in LDS, prefix over earlier tiles by the single-pass scan
-//                 across blocks, then one thread per distinct hit: S_next ascending, mult,
-//                 p_incl, node -> rank table.  Everything but the output position is fetched
-//                 and computed while the prefix is being resolved.
+//   hits          every block takes a range of the position bitmap, counts the bits before it
+//                 itself, lists its own hits in LDS, then one thread per distinct hit: S_next
+//                 ascending, mult, p_incl, node -> rank table.
 //   adj_fused     flat over the edges of S (same chunking as the weight scan), single pass: keep
 //                 = the target was sampled; the kept edges in flat order ARE the CSR of P~ (rows
 //                 in the order of S, columns ascending), so position = prefix of the chunk +
@@ -55,13 +53,13 @@ __global__ __launch_bounds__(DRAW_BLOCK) void draw(const uint64_t *__restrict__ 
                                                    const csgs_prob_stats *__restrict__ stats, int64_t cand_cap,
                                                    int32_t B, uint32_t seed_lo, uint32_t seed_hi, uint64_t iter,
                                                    const uint64_t *__restrict__ iter_dev, uint32_t layer,
-                                                   uint32_t *__restrict__ hit, uint64_t *__restrict__ cbitmap,
-                                                   const uint64_t *__restrict__ epoch, uint64_t *__restrict__ rank,
+                                                   uint32_t *__restrict__ hit, uint64_t *cbitmap0, uint64_t *cbitmap1,
+                                                   uint64_t *__restrict__ epoch, uint64_t *__restrict__ rank,
                                                    uint64_t *__restrict__ member, int64_t n_nodes, InstStride is)
 {
     __shared__ uint64_t top[TOP];
     cdf = inst_ptr(cdf, is.buf); stats = inst_ptr(stats, is.buf);
-    hit = inst_ptr(hit, is.ws); cbitmap = inst_ptr(cbitmap, is.ws); epoch = inst_ptr(epoch, is.ws); rank = inst_ptr(rank, is.ws);
+    hit = inst_ptr(hit, is.ws); cbitmap0 = inst_ptr(cbitmap0, is.ws); cbitmap1 = inst_ptr(cbitmap1, is.ws); epoch = inst_ptr(epoch, is.ws); rank = inst_ptr(rank, is.ws);
     member = inst_ptr(member, is.ws);
     // rank entries and membership words carry the low 32 bits of the call number; when those wrap, stale
     // entries could look current, so both tables are wiped once every 2^32 calls (the compaction kernel that
@@ -77,6 +75,13 @@ __global__ __launch_bounds__(DRAW_BLOCK) void draw(const uint64_t *__restrict__ 
     const uint32_t iter_lo = (uint32_t)iter, iter_hi = (uint32_t)(iter >> 32);
     int64_t n = stats->n_cand;
     if (n > cand_cap) n = cand_cap;
+    const uint64_t turn = epoch[EPOCH_BITMAP_NEXT] & 1ull;
+    uint64_t *__restrict__ cbitmap = turn ? cbitmap1 : cbitmap0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {   // (nobody reads these words in this kernel)
+        epoch[EPOCH_DRAW] = call_number(epoch);
+        epoch[EPOCH_BITMAP_CUR] = turn;
+        epoch[EPOCH_BITMAP_USED + turn] = (uint64_t)(n > 0 ? (n + 63) / 64 : 0);
+    }
     if (n <= 0) return;
     const uint64_t total = stats->total;   // = cdf[n - 1], without waiting for a second dependent load
     if (total == 0) return;
@@ -166,129 +171,115 @@ __device__ inline void mark_members(uint64_t *__restrict__ member, int32_t id, u
     }
 }
 
-__global__ __launch_bounds__(256) void hits_fused(const int32_t *__restrict__ cand_id,
-                                                  const uint64_t *__restrict__ cdf,
-                                                  const csgs_prob_stats *__restrict__ stats, int64_t cand_cap,
-                                                  int64_t n_nodes, int32_t B, uint64_t *__restrict__ epoch,
-                                                  uint64_t *__restrict__ ts_mem, int64_t ts_tiles,
-                                                  uint32_t *__restrict__ hit, uint64_t *__restrict__ cbitmap,
-                                                  uint64_t *__restrict__ rank, uint64_t *__restrict__ member,
-                                                  int32_t *__restrict__ S_next,
-                                                  int32_t *__restrict__ mult, float *__restrict__ p_incl,
-                                                  double *__restrict__ pdbl, int32_t *__restrict__ n_next,
-                                                  int32_t *__restrict__ status, InstStride is)
+// The distinct drawn positions in order.  Every block takes `wpb` consecutive words of the position bitmap and counts
+// the bits of all words before them itself: the bitmap of n_c positions is n_c / 8 bytes (20 KB for 163 K candidates),
+// which a block reads from the L2s in one or two load latencies, where the prefix by waiting for other blocks took
+// three.  Nobody waits, so there may be as many blocks as the hits can use: bound by the dependent loads of a hit (bit,
+// counter, CDF, id), then by the double-precision logarithm and exponential, which more blocks share.  One mini-batch
+// of 8192 draws from 163 K candidates: 16 -> 6 us; 131072 from 650 K: 73 -> 11 us (blocks of 16384 positions with a
+// prefix across blocks before).
+__global__ __launch_bounds__(256) void hits(const int32_t *__restrict__ cand_id, const uint64_t *__restrict__ cdf,
+                                            const csgs_prob_stats *__restrict__ stats, int64_t cand_cap, int64_t n_nodes,
+                                            int32_t B, uint64_t *__restrict__ epoch, uint32_t *__restrict__ hit,
+                                            uint64_t *cbitmap0, uint64_t *cbitmap1, uint64_t *__restrict__ rank,
+                                            uint64_t *__restrict__ member, int32_t *__restrict__ S_next,
+                                            int32_t *__restrict__ mult, float *__restrict__ p_incl,
+                                            double *__restrict__ pdbl, int32_t *__restrict__ n_next, InstStride is)
 {
-    __shared__ uint32_t lds[17];
+    constexpr int SUB = 64;   // words listed at a time: four threads of 16 bits each per word
+    __shared__ uint16_t s_list[SUB * 64];   // drawn positions of those words, ascending
+    __shared__ uint32_t s_cnt[4], s_before[4];
     member = inst_ptr(member, is.ws);
     cand_id = inst_ptr(cand_id, is.buf); cdf = inst_ptr(cdf, is.buf); stats = inst_ptr(stats, is.buf);
     S_next = inst_ptr(S_next, is.buf); mult = inst_ptr(mult, is.buf); p_incl = inst_ptr(p_incl, is.buf);
-    n_next = inst_ptr(n_next, is.buf); status = inst_ptr(status, is.buf);
-    epoch = inst_ptr(epoch, is.ws); ts_mem = inst_ptr(ts_mem, is.ws); hit = inst_ptr(hit, is.ws);
-    cbitmap = inst_ptr(cbitmap, is.ws); rank = inst_ptr(rank, is.ws); pdbl = inst_ptr(pdbl, is.ws);
-    __shared__ unsigned long long s_lb[1];
-    __shared__ uint16_t s_list[HIT_TILE_WORDS * 64];   // drawn positions of the tile, ascending
-    const TileState<1> ts(ts_mem, ts_tiles, wait_limit(epoch));
-    const unsigned long long call = call_number(epoch);
-    const unsigned long long tag = call_tag(call, SLOT_HITS);
+    n_next = inst_ptr(n_next, is.buf);
+    epoch = inst_ptr(epoch, is.ws); hit = inst_ptr(hit, is.ws); cbitmap0 = inst_ptr(cbitmap0, is.ws);
+    cbitmap1 = inst_ptr(cbitmap1, is.ws); rank = inst_ptr(rank, is.ws); pdbl = inst_ptr(pdbl, is.ws);
+    const int tid = (int)threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    const unsigned long long call = epoch[EPOCH_DRAW];   // left by the draw
+    const uint64_t turn = epoch[EPOCH_BITMAP_CUR];
+    const uint64_t *__restrict__ bits = turn ? cbitmap1 : cbitmap0;
+    uint64_t *__restrict__ old_bits = turn ? cbitmap0 : cbitmap1;
+    const int64_t old_words = (int64_t)epoch[EPOCH_BITMAP_USED + (turn ^ 1ull)];
     int64_t n = stats->n_cand;
     if (n > cand_cap) n = cand_cap;
     if (n < 0) n = 0;
-    const int64_t n_words = (n + 63) / 64;
-    const int64_t n_tiles = (n_words + HIT_TILE_WORDS - 1) / HIT_TILE_WORDS;
-    if (n_tiles == 0) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) {  // no candidates at all
-            *n_next = 0;
-            epoch[EPOCH_DRAW] = call;
-            epoch[EPOCH_CALLS] = call;
-        }
-        return;
-    }
     const double total = (double)stats->total;   // = cdf[n - 1]
+    const int64_t n_words = (n + 63) / 64;
+    if (blockIdx.x == 0 && tid == 0) {   // last kernel of the draw (nobody reads these words in this kernel)
+        epoch[EPOCH_CALLS] = call;
+        epoch[EPOCH_BITMAP_NEXT] = turn ^ 1ull;
+        if (n_words == 0) *n_next = 0;
+    }
+    for (int64_t i = (int64_t)blockIdx.x * 256 + tid; i < old_words; i += (int64_t)gridDim.x * 256) old_bits[i] = 0ull;
+    int64_t wpb = (n_words + gridDim.x - 1) / gridDim.x;
+    if (wpb < HIT_MIN_WORDS) wpb = HIT_MIN_WORDS;
+    const int64_t w0 = (int64_t)blockIdx.x * wpb, w1 = w0 + wpb < n_words ? w0 + wpb : n_words;
+    if (w0 >= n_words) return;
     const uint64_t rank_tag = (call & 0xFFFFFFFFull) << 32;
-    for (int64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
-        // one bitmap word per thread -> ordered list of the tile's drawn positions in LDS
-        const int64_t wi = t * HIT_TILE_WORDS + threadIdx.x;
-        uint64_t word = wi < n_words ? cbitmap[wi] : 0ull;
-        const uint32_t cnt = (uint32_t)__popcll(word);
-        uint32_t tile_total;
-        uint32_t ex = block_exclusive_scan<uint32_t>(cnt, lds, &tile_total);
-        if (word) cbitmap[wi] = 0ull;  // back to the clean state
-        while (word) {
-            const int bit = __ffsll((unsigned long long)word) - 1;
-            word &= word - 1;
-            s_list[ex++] = (uint16_t)(threadIdx.x * 64 + bit);
+    uint64_t word = w0 + (tid >> 2) < w1 ? bits[w0 + (tid >> 2)] : 0ull;
+    uint32_t before = 0;   // bits set before w0 (then before the words at hand)
+    {
+        uint32_t c = 0;
+        int64_t i = tid;
+        for (; i + 3 * 256 < w0; i += 4 * 256) {   // four loads on their way at a time
+            const uint64_t a = bits[i], b = bits[i + 256], d = bits[i + 512], e = bits[i + 768];
+            c += (uint32_t)(__popcll(a) + __popcll(b) + __popcll(d) + __popcll(e));
         }
-        unsigned long long local[1] = {tile_total}, excl[1];
-        lookback_publish<1>(ts, tag, t, local);
-        __syncthreads();  // s_list complete
-        // One thread per distinct hit.  Everything except the output position is ready before the
-        // prefix is: fetch and compute it now.  The tile's first hits go to the last threads, so
-        // that the arithmetic runs in other wavefronts than the one that does the hops.
-        const uint32_t i0 = (uint32_t)(blockDim.x - 1 - threadIdx.x);
-        int64_t kpos0 = 0;
-        uint32_t m0 = 0;
-        int32_t id0 = -1;
-        double pk0 = 0.0;
-        if (i0 < tile_total) {
-            kpos0 = t * (HIT_TILE_WORDS * 64) + s_list[i0];
-            m0 = hit[kpos0];
-            hit[kpos0] = 0u;
-            const uint64_t wk = cdf[kpos0] - (kpos0 ? cdf[kpos0 - 1] : 0ull);
-            const double qk = (double)wk / total;
-            pk0 = (qk >= 1.0) ? 1.0 : -expm1((double)B * log1p(-qk));
-            id0 = cand_id[kpos0];
+        for (; i < w0; i += 256) c += (uint32_t)__popcll(bits[i]);
+        c = wave_sum(c);
+        if (lane == 0) s_before[wave] = c;
+    }
+    for (int64_t ws = w0; ws < w1; ws += SUB) {
+        if (ws > w0) word = ws + (tid >> 2) < w1 ? bits[ws + (tid >> 2)] : 0ull;
+        uint32_t mine = (uint32_t)(word >> (16 * (tid & 3))) & 0xFFFFu;
+        const uint32_t cnt = (uint32_t)__popc(mine);
+        const uint32_t incl = wave_inclusive_scan(cnt);
+        if (lane == WAVE - 1) s_cnt[wave] = incl;
+        __syncthreads();
+        if (ws == w0) before = s_before[0] + s_before[1] + s_before[2] + s_before[3];
+        uint32_t at = incl - cnt, n_hits = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t c = s_cnt[k];
+            if (k < wave) at += c;
+            n_hits += c;
         }
-        lookback_resolve<1>(ts, tag, t, n_tiles, local, excl, s_lb, status);
-        int32_t member_id = -1;
-        if (i0 < tile_total) {
-            const uint64_t pos = excl[0] + i0;
-            if (pos < (uint64_t)B) {  // at most B distinct hits exist; the guard keeps stores in bounds regardless
-                S_next[pos] = id0;
-                mult[pos] = (int32_t)m0;
-                p_incl[pos] = (float)pk0;
-                pdbl[pos] = pk0;
-                if (id0 >= 0 && id0 < n_nodes) {
-                    rank[id0] = rank_tag | (pos + 1);
-                    member_id = id0;
-                }
-            }
+        while (mine) {
+            const int bit = __ffs((int)mine) - 1;
+            mine &= mine - 1;
+            s_list[at++] = (uint16_t)(tid * 16 + bit);
         }
-        mark_members(member, member_id, (uint32_t)(rank_tag >> 32));
-        for (uint32_t i_base = blockDim.x; i_base < tile_total; i_base += blockDim.x) {  // crowded tiles (every lane goes round together)
-            const uint32_t i = i_base + threadIdx.x;
-            int32_t marked = -1;
-            if (i < tile_total) {
-                const int64_t kpos = t * (HIT_TILE_WORDS * 64) + s_list[i];
-                const uint64_t pos = excl[0] + i;
+        __syncthreads();
+        for (uint32_t i0 = 0; i0 < n_hits; i0 += 256) {   // every lane goes round together (mark_members)
+            const uint32_t i = i0 + (uint32_t)tid;
+            int32_t member_id = -1;
+            if (i < n_hits) {
+                const int64_t kpos = ws * 64 + s_list[i];
                 const uint32_t m = hit[kpos];
-                hit[kpos] = 0u;
-                if (pos < (uint64_t)B) {
-                    const uint64_t wk = cdf[kpos] - (kpos ? cdf[kpos - 1] : 0ull);
-                    const double qk = (double)wk / total;
-                    const double pk = (qk >= 1.0) ? 1.0 : -expm1((double)B * log1p(-qk));
-                    const int32_t id = cand_id[kpos];
+                const uint64_t hi = cdf[kpos], lo = cdf[kpos > 0 ? kpos - 1 : 0];
+                const int32_t id = cand_id[kpos];
+                const double qk = (double)(kpos > 0 ? hi - lo : hi) / total;
+                const double pk = (qk >= 1.0) ? 1.0 : -expm1((double)B * log1p(-qk));
+                hit[kpos] = 0u;   // back to the clean state
+                const uint64_t pos = (uint64_t)before + i;
+                if (pos < (uint64_t)B) {  // at most B distinct hits exist; the guard keeps stores in bounds regardless
                     S_next[pos] = id;
                     mult[pos] = (int32_t)m;
                     p_incl[pos] = (float)pk;
                     pdbl[pos] = pk;
                     if (id >= 0 && id < n_nodes) {
                         rank[id] = rank_tag | (pos + 1);
-                        marked = id;
+                        member_id = id;
                     }
                 }
             }
-            mark_members(member, marked, (uint32_t)(rank_tag >> 32));
+            mark_members(member, member_id, (uint32_t)(rank_tag >> 32));
         }
-        if (t == n_tiles - 1 && threadIdx.x == 0) {
-            const uint64_t tot = excl[0] + tile_total;
-            *n_next = (int32_t)(tot < (uint64_t)B ? tot : (uint64_t)B);
-            // Last kernel of the draw: advance the call counter.  Every block that owns a tile has
-            // read it by now (this tile's prefix needed all their sums), the others never use it.
-            epoch[EPOCH_DRAW] = call;
-            epoch[EPOCH_CALLS] = call;
-        }
-        __syncthreads();  // s_list is reused by the next tile
+        before += n_hits;
+        __syncthreads();   // the list is written again
     }
+    if (w1 == n_words && tid == 0) *n_next = (int32_t)(before < (uint32_t)B ? before : (uint32_t)B);
 }
 
 // S_next ascends and the local partition is one id range, so the sampled remote nodes are the
@@ -570,14 +561,14 @@ extern "C" int csgs_draw_nodes(int64_t n_nodes, const int32_t *cand_id, const ui
     const unsigned nz = (unsigned)w.n_inst;
     const InstStride is = inst_stride(w);
     CSGS_LAUNCH(K_DRAW, draw, dim3((unsigned)((B + DRAW_BLOCK - 1) / DRAW_BLOCK), 1, nz), dim3(DRAW_BLOCK), st, cdf, stats,
-                cand_cap, B, (uint32_t)seed, (uint32_t)(seed >> 32), iter, iter_dev, layer, w.hit, w.cbitmap, w.epoch, w.rank, w.member,
-                n_nodes, is);
+                cand_cap, B, (uint32_t)seed, (uint32_t)(seed >> 32), iter, iter_dev, layer, w.hit, w.cbitmap[0], w.cbitmap[1], w.epoch, w.rank,
+                w.member, n_nodes, is);
     CSGS_LAUNCH_CHECK();
     const int64_t cap_words = (cand_cap + 63) / 64;
-    const int64_t hit_tiles = (cap_words + HIT_TILE_WORDS - 1) / HIT_TILE_WORDS;
-    const unsigned hit_blocks = (unsigned)(hit_tiles < resident_grid(1) ? hit_tiles : resident_grid(1));
-    CSGS_LAUNCH(K_HITS_FUSED, hits_fused, dim3(hit_blocks, 1, nz), dim3(256), st, cand_id, cdf, stats, cand_cap, n_nodes, B,
-                w.epoch, w.hit_ts, w.hit_tiles, w.hit, w.cbitmap, w.rank, w.member, S_next, mult, p_incl, w.pdbl, n_next, status, is);
+    const int64_t hit_blocks = (cap_words + HIT_MIN_WORDS - 1) / HIT_MIN_WORDS;
+    CSGS_LAUNCH(K_HITS_FUSED, hits, dim3((unsigned)(hit_blocks < HIT_GRID ? hit_blocks : HIT_GRID), 1, nz), dim3(256), st, cand_id,
+                cdf, stats, cand_cap, n_nodes, B, w.epoch, w.hit, w.cbitmap[0], w.cbitmap[1], w.rank, w.member, S_next, mult, p_incl,
+                w.pdbl, n_next, is);
     CSGS_LAUNCH_CHECK();
     ws->has_draw = 1;
     ws->draw_B = B;

@@ -51,3 +51,37 @@ def test_aggregate_rows_per_wavefront(dev, F, bf16, rows):
         torch.cuda.synchronize()
         chain.assert_close(Z[:n].cpu().numpy(), want, chain.RTOL, chain.ATOL, f"aggregate {n} rows F={F}")
         assert bool(torch.isnan(Z[n:]).all()), f"{n} rows: wrote past the last row"
+
+
+# Candidate counts at the ends of bitmap words, of a block's 16 words, and where the blocks (512, 16 words each) begin to take
+# more words and then more than 64 at a time; budgets from a few hits to every position drawn, several draws in a row on one
+# workspace (the position bitmap of one draw is cleared by the next)
+@pytest.mark.parametrize("n_nodes,cases", [(1, ((1, 5),)), (1100, ((64, 3), (1023, 900), (65, 4000), (1, 7), (1025, 256))),
+                                           (600_000, ((524_288, 3000), (524_289, 5000), (1025, 20_000), (600_000, 70_000))),
+                                           (2_200_000, ((2_097_153, 9000), (2_200_000, 1), (100, 100)))])
+def test_draws_by_candidate_count(dev, n_nodes, cases):
+    from types import SimpleNamespace
+    from paper_2101_07706_amd import csgs, pipeline
+    rng = np.random.default_rng(n_nodes)
+    B_max = max(B for _, B in cases)
+    ws = pipeline.Workspace(n_nodes, 1, B_max, 1, dev)
+    clean = chain.csgs_clean_words(n_nodes)
+    for it, (n_c, B) in enumerate(cases):
+        print(f"[draw] {n_c} candidates of {n_nodes} nodes, {B} draws", flush=True)
+        ids = np.sort(rng.choice(n_nodes, n_c, replace=False)).astype(np.int32)
+        cdf = np.cumsum(rng.integers(1, 1 << 30, n_c), dtype=np.uint64)
+        want = oracle.draw_nodes(SimpleNamespace(cand_id=ids, cdf=cdf), B, 99, it, 2)
+        stats = csgs.ProbStats(n_cand=n_c, total=int(cdf[-1]))
+        st = torch.frombuffer(bytearray(bytes(stats)), dtype=torch.int64).to(dev)
+        i32 = lambda n: torch.zeros(n, dtype=torch.int32, device=dev)
+        S_next, mult, n_next, status, p = i32(B), i32(B), i32(1), i32(1), torch.zeros(B, dtype=torch.float32, device=dev)
+        csgs.csgs_draw_nodes(n_nodes, torch.from_numpy(ids).to(dev), torch.from_numpy(cdf.view(np.int64)).to(dev), st, B, 99, it, 2, S_next, mult,
+                             p, n_next, ws.desc, status)
+        torch.cuda.synchronize()
+        m = want.n_next
+        assert int(n_next.item()) == m and int(status.item()) == 0
+        np.testing.assert_array_equal(S_next[:m].cpu().numpy(), want.S_next)
+        np.testing.assert_array_equal(mult[:m].cpu().numpy(), want.mult)
+        chain.assert_close(p[:m].cpu().numpy(), want.p_incl, chain.P_RTOL, 0.0, "p_incl")
+        assert int(torch.count_nonzero(S_next[m:]).item()) == 0, "wrote past the last hit"
+        assert int(torch.count_nonzero(ws.buf[:clean]).item()) == 0, "workspace not restored"
