@@ -46,8 +46,9 @@ def algorithmic_bytes(s, N):
         "cand_partials": N / 64 + 8 * nc,                   # flags, accumulators read
         "cand_emit": N / 64 + 8 * nc + 20 * nc,             # the same again, id + weight + cdf written
         "draw": 12 * B,                                     # cdf probes are cache traffic
-        "hits_fused": nc / 8 + 36 * n2,                     # position bitmap, per hit: count, 2 cdf, id, 4 outputs
-        "adj_fused": 4 * E + 16 * nS + 4 * nS + 20 * nnz,   # col per edge, row slices, row pointers, kept edges
+        "hits": nc / 8 + 36 * n2,                           # position bitmap, per hit: count, 2 cdf, id, 4 outputs
+        "adj_mark": 4 * E + 16 * nS + 4 * nS + 20 * nnz,    # col per edge, row slices, row pointers, kept edges
+        "adj_place": 16 * nnz + 8 * nS,                     # kept edges in and out, row pointers
         "remote_count": 12 * n2,
         "aggregate": agg,
         "layer_gemm": 4 * (nS * Fi + Fi * Fo + nS * Fo),
@@ -833,7 +834,7 @@ def main():
         cfg_s = dataclasses.replace(cfg, batch=cfg.batch * sc, samples=cfg.samples * sc)
         rs = mk(cfg_s, 8, 1).measure(6, 2)
         tr = load_traffic(f"{cfg.name}_x{sc}", 1)
-        shown = ("aggregate", "layer_gemm", "layer_forward", "scan_edges", "adj_fused", "cand_emit")
+        shown = ("aggregate", "layer_gemm", "layer_forward", "scan_edges", "adj_mark", "cand_emit")
         scaled = dict(workload=f"{cfg.name} x{sc}: batch {cfg_s.batch}, {cfg_s.samples} samples/layer",
                       ms_per_step=rs["ms_per_step"], one_stream_ms_per_step=rs["serial_ms_per_step"],
                       sampled_edges_per_s=rs["per_step"]["sampled_edges"] / (rs["ms_per_step"] * 1e-3),

@@ -49,7 +49,7 @@ struct RowOffsets {
     int64_t *eoff;       // [nS + 1] exclusive prefix of the degrees of the rows
     int64_t *rowstart;   // [nS + 1] rowptr[S[a]]
     int64_t *meta;       // [META_WORDS] resolved on the device: row count, edge count, true edge count
-    int2 *chunk_note;    // [chunk_cap] (first row, rows) of every edge chunk, left by the weight scan for the adjacency pass
+    int2 *chunk_note;    // [chunk_cap] (first row, rows) of every edge chunk, left by the weight scan for the adjacency passes
     int2 *bound_note;    // [chunk_cap + 2] for the edge position t * EDGE_TILE: (first row of a chunk that starts there, first row
                          // whose offset is at or beyond it), left by the row pass for the weight scan
 };
@@ -73,9 +73,11 @@ struct Workspace {
     // its spare blocks prepare the other for the next layer (rows = the node set just sampled).
     RowOffsets rows[2];
     uint64_t *adj_ts;    // scan state of the edge chunks (1 sum per chunk of 1024 edges)
+    uint32_t *adj_cnt;   // [chunk_cap] kept edges of every edge chunk | 1 << 31 when a row starts at the chunk's first edge
     uint64_t *rp_ts;     // scan state of the row tiles (1 sum per tile of ROW_TILE rows)
     double *pdbl;        // [B]      inclusion probabilities in double
-    // hand-over of local-range edges from the chunk blocks of the weight scan to the owner blocks
+    // hand-over of local-range edges from the chunk blocks of the weight scan to the owner blocks; stage_w also takes the
+    // kept edges of a chunk (column | value << 32) from the adjacency's marking pass to its placing pass
     uint64_t *stage_w;   // [stage_chunks * EDGE_TILE] fixed-point weight of a handed-over edge
     uint32_t *stage_c;   // [stage_chunks * EDGE_TILE] its target id; a chunk's edges lie grouped by owner
     uint32_t *stage_off; // [stage_chunks * SUB_MAX]   per chunk and owner: begin | end << 16 of its group
@@ -157,6 +159,7 @@ __host__ inline Workspace carve(void *base, int64_t n_nodes, int64_t nS_max, int
     w.epoch = (uint64_t *)take(EPOCH_WORDS * 8);
     for (int b = 0; b < 2; ++b) w.cbitmap[b] = (uint64_t *)take(words * 8);
     w.adj_ts = (uint64_t *)take(scan_state_words(w.chunk_cap, 1) * 8);
+    w.adj_cnt = (uint32_t *)take((size_t)w.chunk_cap * 4);
     w.rp_tiles = (nS_max + ROW_TILE - 1) / ROW_TILE;
     w.rp_ts = (uint64_t *)take(scan_state_words(w.rp_tiles, 1) * 8);
     for (int b = 0; b < 2; ++b) {
@@ -199,7 +202,7 @@ __host__ inline InstStride inst_stride(const Workspace &w) { return InstStride{(
 // the device: resident_grid(per_cu) blocks of 256 threads, per_cu per compute unit.  Such a kernel
 // must have all its blocks resident at once.  Alone on the device that is certain (registers and
 // LDS allow several times as many).  Beside kernels of other streams it still holds as long as the
-// waiting kernels in flight fit together, because every other kernel drains by itself: the
+// waiting kernels in flight fit together, because every other kernel drains by itself: the one-pass
 // adjacency filter (17 KB of LDS) runs 2 blocks per unit, so four call sequences on four workspaces
 // can be in flight on one device within the 2048 threads and 160 KB of a compute unit.  That is the
 // documented limit.
@@ -378,35 +381,64 @@ __device__ inline T block_exclusive_scan(T v, T *lds /*[17]*/, T *block_total)
     return incl - v + lds[wave];
 }
 
-// First index in [0, n) with a[idx] >= key, found by the whole wavefront: every round the 64 lanes
+// First indices in [0, n) with a[idx] >= key[i], found by the whole wavefront: every round the 64 lanes
 // probe the ends of 64 equal segments at once, so an array of 8192 entries takes 3 dependent loads
-// instead of 13.  All lanes must call it with the same arguments; all get the result.
+// instead of 13, and the searches for several keys go through their rounds together.  All lanes must call it
+// with the same arguments; all get the results.
+template <int K, typename T, typename I>
+__device__ inline void wave_lower_bounds(const T *__restrict__ a, I n, const T (&key)[K], I (&out)[K])
+{
+    const int lane = lane_id();
+    I lo[K], hi[K];
+    bool more = false;
+#pragma unroll
+    for (int i = 0; i < K; ++i) { lo[i] = 0; hi[i] = n; more = more || n > 0; }
+    while (more) {
+        T v[K];
+        I step[K];
+        bool probe[K];
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            const I len = hi[i] - lo[i];
+            step[i] = (len + WAVE - 1) / WAVE;
+            const I seg_end = lo[i] + ((lane + 1) * step[i] < len ? (lane + 1) * step[i] : len);  // exclusive
+            const I seg_beg = lo[i] + (lane * step[i] < len ? lane * step[i] : len);
+            probe[i] = seg_end > seg_beg;
+            v[i] = a[probe[i] ? seg_end - 1 : 0];
+        }
+        more = false;
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            if (hi[i] <= lo[i]) continue;   // found
+            const I len = hi[i] - lo[i];
+            // empty segments sit past the end: treat as "all remaining entries are >= key"
+            const uint64_t m = __ballot(probe[i] ? v[i] >= key[i] : true);
+            const int first = m ? __ffsll((unsigned long long)m) - 1 : WAVE;
+            const I fb = lo[i] + (first * step[i] < len ? first * step[i] : len);
+            const I fe = lo[i] + ((first + 1) * step[i] < len ? (first + 1) * step[i] : len);
+            if (fe <= fb) {             // no segment ends at or above key: every entry is below it
+                lo[i] = hi[i];
+            } else if (step[i] == 1) {  // segments are single entries: entry fb is the first >= key
+                lo[i] = fb;
+                hi[i] = fb;
+            } else {                    // a[fe - 1] >= key and everything before fb is below key
+                lo[i] = fb;
+                hi[i] = fe;
+            }
+            more = more || hi[i] > lo[i];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < K; ++i) out[i] = lo[i];
+}
+
 template <typename T, typename I>
 __device__ inline I wave_lower_bound(const T *__restrict__ a, I n, T key)
 {
-    const int lane = lane_id();
-    I lo = 0, hi = n;
-    while (hi > lo) {
-        const I len = hi - lo;
-        const I step = (len + WAVE - 1) / WAVE;
-        const I seg_end = lo + ((lane + 1) * step < len ? (lane + 1) * step : len);  // exclusive
-        const I seg_beg = lo + (lane * step < len ? lane * step : len);
-        bool ge = true;  // empty segments sit past the end: treat as "all remaining entries are >= key"
-        if (seg_end > seg_beg) ge = a[seg_end - 1] >= key;
-        const uint64_t m = __ballot(ge);
-        const int first = m ? __ffsll((unsigned long long)m) - 1 : WAVE;
-        const I fb = lo + (first * step < len ? first * step : len);
-        const I fe = lo + ((first + 1) * step < len ? (first + 1) * step : len);
-        if (fe <= fb) {          // no segment ends at or above key: every entry is below it
-            lo = hi;
-        } else if (step == 1) {  // segments are single entries: entry fb is the first >= key
-            return fb;
-        } else {                 // a[fe - 1] >= key and everything before fb is below key
-            lo = fb;
-            hi = fe;
-        }
-    }
-    return lo;
+    const T k[1] = {key};
+    I r[1];
+    wave_lower_bounds<1>(a, n, k, r);
+    return r[0];
 }
 
 // ---------------------------------------------------------------- flat edge chunks

@@ -21,8 +21,8 @@ static std::vector<Pair> g_pool;   // created once, reused
 static size_t g_used = 0;
 static const size_t kMaxPairs = 1 << 16;
 
-static const char *const kNames[K_COUNT] = {"row_prefix", "scan_edges", "cand_partials", "cand_emit", "draw", "hits_fused",
-                                            "adj_fused", "remote_count", "aggregate",
+static const char *const kNames[K_COUNT] = {"row_prefix", "scan_edges", "cand_partials", "cand_emit", "draw", "hits",
+                                            "adj_mark", "adj_place", "adj_once", "remote_count", "aggregate",
                                             "layer_gemm", "gather_rows", "gemm_grad_z", "gemm_grad_w", "gemm_grad_w_reduce",
                                             "adjT_count", "adjT_prefix", "adjT_fill", "adjT_order", "aggregate_grad", "fill_zero", "copy", "atomics", "mfma_f64", "lookups", "layer_forward"};
 

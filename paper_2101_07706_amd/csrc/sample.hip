@@ -13,12 +13,15 @@
 //   hits          every block takes a range of the position bitmap, counts the bits before it
 //                 itself, lists its own hits in LDS, then one thread per distinct hit: S_next
 //                 ascending, mult, p_incl, node -> rank table.
-//   adj_fused     flat over the edges of S (same chunking as the weight scan), single pass: keep
-//                 = the target was sampled; the kept edges in flat order ARE the CSR of P~ (rows
-//                 in the order of S, columns ascending), so position = prefix of the chunk +
-//                 popcount of earlier keep bits, and the row pointers are the positions at the
-//                 row starts.  The node -> rank table is never cleared: its entries carry the
-//                 tag of the draw that wrote them.
+//   adj_mark      flat over the edges of S (same chunking as the weight scan): keep = the target was
+//                 sampled.  Leaves every chunk's kept edges in order, their number, and the row
+//                 pointers relative to the chunk.  The node -> rank table is never cleared: its
+//                 entries carry the tag of the draw that wrote them.
+//   adj_place     the kept edges in flat order ARE the CSR of P~ (rows in the order of S, columns
+//                 ascending): adds up the counts of the chunks before and puts a chunk's kept edges
+//                 and row pointers where they belong
+//   adj_once      both in one pass, the prefix by the single-pass scan across blocks: for calls with
+//                 few chunks, where a launch costs more than the wait
 //   remote_count_k  S_next ascends and the local partition is one id range: two searches by a
 //                 whole wavefront place every element (see the kernel)
 #include <math.h>
@@ -285,7 +288,8 @@ __global__ __launch_bounds__(256) void hits(const int32_t *__restrict__ cand_id,
 // S_next ascends and the local partition is one id range, so the sampled remote nodes are the
 // entries before the first id >= lo and from the first id >= hi on: two searches give every
 // element its place, no scan needed.
-constexpr int REMOTE_BLOCKS = 64;
+// Blocks of 256 threads that cover a budget of B in one sweep; larger ones are strided over.
+static int remote_blocks(int64_t B) { return (int)(B < 256 ? 1 : (B < 256 * 256 ? (B + 255) / 256 : 256)); }
 
 struct RemoteArgs {
     const int32_t *S_next, *n_next;
@@ -307,8 +311,11 @@ __device__ inline void remote_count_body(const RemoteArgs &r_, int32_t block, in
     int32_t *__restrict__ src_row = r_.src_row, *__restrict__ remote_ids = r_.remote_ids;
     int32_t n = *r_.n_next;
     if (n < 0) n = 0;
-    const int32_t a = wave_lower_bound(S_next, n, lo);   // ids below the local range
-    const int32_t b = wave_lower_bound(S_next, n, hi);   // first id above it
+    // ids below the local range end at a, the first id above it is at b
+    int32_t ab[2];
+    const int32_t bounds[2] = {lo, hi};
+    wave_lower_bounds<2>(S_next, n, bounds, ab);
+    const int32_t a = ab[0], b = ab[1];
     const int32_t n_local = b - a;
     const int32_t tid = (int32_t)(block * blockDim.x + threadIdx.x);
     const int32_t stride = (int32_t)(n_blocks * blockDim.x);
@@ -329,16 +336,17 @@ __device__ inline void remote_count_body(const RemoteArgs &r_, int32_t block, in
     if (per_part) {
         const int32_t wave = tid >> 6, n_waves = stride >> 6;
         for (int32_t p = wave; p < P; p += n_waves) {
-            const int32_t c0 = wave_lower_bound(S_next, n, part_bounds[p]);
-            const int32_t c1 = wave_lower_bound(S_next, n, part_bounds[p + 1]);
-            if (lane_id() == 0) per_part[p] = (int64_t)(c1 > c0 ? c1 - c0 : 0);
+            const int32_t ends[2] = {part_bounds[p], part_bounds[p + 1]};
+            int32_t c[2];
+            wave_lower_bounds<2>(S_next, n, ends, c);
+            if (lane_id() == 0) per_part[p] = (int64_t)(c[1] > c[0] ? c[1] - c[0] : 0);
         }
     }
 }
 
 __global__ __launch_bounds__(256) void remote_count_k(RemoteArgs r) { remote_count_body(r, (int32_t)blockIdx.x, (int32_t)gridDim.x); }
 
-// Work of the adjacency kernel's second group of spare blocks: the row offsets of the node set just
+// Work of the marking pass's second group of spare blocks: the row offsets of the node set just
 // sampled, for a following csgs_build_probs on those rows (one tile of rows per block).
 struct NextRows {
     const int64_t *rowptr;
@@ -353,34 +361,116 @@ struct NextRows {
     int32_t blocks;       // 0 = none
 };
 
+// One chunk of edges: which of them are kept.  Called by all threads; wavefront w owns positions [w * 256, w * 256 + 256),
+// four 64-edge words.  Out: per lane and word the kept edge's rank (position in S_next + 1; 0 = not kept) and CSR
+// position; in LDS the keep bits of every word (mask) and the kept edges before it (pre).
+struct AdjChunk {
+    RowSlice slice;
+    uint64_t mask[EDGE_TILE / 64];
+    int32_t pre[EDGE_TILE / 64 + 1];
+};
+struct AdjGraph {
+    const int32_t *colidx;
+    const float *val;
+    int64_t n_nodes, nnz;
+    const int64_t *eoff, *rowstart;
+    const uint64_t *rank, *member;
+    const double *pdbl;
+};
 template <bool FROM_NOTE>
-__global__ __launch_bounds__(256) void adj_fused(const int32_t *__restrict__ colidx, const float *__restrict__ val,
-                                                 int64_t n_nodes, int64_t nnz, const int64_t *__restrict__ meta,
-                                                 const int64_t *__restrict__ eoff,
-                                                 const int64_t *__restrict__ rowstart,
-                                                 const uint64_t *__restrict__ rank, const uint64_t *__restrict__ member,
-                                                 const double *__restrict__ pdbl,
-                                                 uint64_t *__restrict__ epoch, uint64_t *__restrict__ ts_mem, int64_t chunk_cap,
-                                                 int2 *__restrict__ chunk_note, int32_t *__restrict__ adj_rowptr,
-                                                 int32_t *__restrict__ adj_col, float *__restrict__ adj_val,
-                                                 int64_t adj_cap, int64_t *__restrict__ adj_nnz,
-                                                 int32_t *__restrict__ status, RemoteArgs rem, NextRows nxt, InstStride is)
+__device__ inline void adj_chunk(AdjChunk &s, const AdjGraph &g, int32_t nS, int64_t c0, int64_t c1, uint64_t rank_tag, int2 *note,
+                                 int32_t (&rk)[4], int64_t (&ea)[4])
 {
-    status = inst_ptr(status, is.buf);
-    epoch = inst_ptr(epoch, is.ws);
-    // The leading rem.blocks blocks split the new node set into local and remote (what
-    // csgs_remote_count does: it needs only S_next / n_next, complete since the previous kernel) so
-    // that a layer step is one launch shorter; they wait for nobody and nobody waits for them.
+    const int lane = lane_id();
+    const int wave = (int)(threadIdx.x >> 6);
+    stage_slice<FROM_NOTE>(s.slice, g.eoff, g.rowstart, nS, c0, c1, note);
+    const int32_t len = (int32_t)(c1 - c0);
+    // A lane's four edges go through each step together, and no load sits under a condition (an edge that does
+    // not exist reads entry 0 and is dropped): the four columns travel at the same time, then the four table
+    // lookups, instead of eight trips one after the other.
+    bool live[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int32_t x = wave * 256 + k * 64 + lane;
+        ea[k] = 0;
+        live[k] = false;
+        if (x < len) {
+            int32_t r;
+            const int64_t a = edge_address(s.slice, g.eoff, g.rowstart, c0, x, &r);
+            if (a >= 0 && a < g.nnz) {   // (an address outside the graph can only follow a failed wait)
+                ea[k] = a;
+                live[k] = true;
+            }
+        }
+    }
+    int32_t ck[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) ck[k] = g.colidx[ea[k]];
+    // the membership word of every column first (a small table that stays in the L2s), then the rank entry, which
+    // only a member's lane reads from its own place (the others read entry 0)
+    uint64_t mw[4], re[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        live[k] = live[k] && ck[k] >= 0 && ck[k] < g.n_nodes;
+        mw[k] = g.member[live[k] ? ck[k] >> 5 : 0];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        live[k] = live[k] && (mw[k] & 0xFFFFFFFF00000000ull) == rank_tag && ((mw[k] >> (ck[k] & 31)) & 1ull);
+        re[k] = g.rank[live[k] ? ck[k] : 0];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        rk[k] = (live[k] && (re[k] & 0xFFFFFFFF00000000ull) == rank_tag) ? (int32_t)(re[k] & 0xFFFFFFFFull) : 0;
+        const uint64_t m = __ballot(rk[k] > 0);
+        if (lane == 0) s.mask[wave * 4 + k] = m;
+    }
+    __syncthreads();
+    if (wave == 0) {
+        const int32_t c = lane < EDGE_TILE / 64 ? __popcll(s.mask[lane]) : 0;
+        const int32_t incl = wave_inclusive_scan(c);
+        if (lane <= EDGE_TILE / 64) s.pre[lane] = incl - c;
+    }
+    __syncthreads();
+}
+// Value and place inside the chunk of a lane's kept edges (unconditional loads again)
+__device__ inline void adj_values(const AdjChunk &s, const AdjGraph &g, const int32_t (&rk)[4], const int64_t (&ea)[4], float (&pv)[4],
+                                  int32_t (&at)[4])
+{
+    const int lane = lane_id();
+    const int wave = (int)(threadIdx.x >> 6);
+    float vv[4];
+    double pp[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        vv[k] = g.val[ea[k]];
+        pp[k] = g.pdbl[rk[k] > 0 ? rk[k] - 1 : 0];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int32_t word = wave * 4 + k;
+        pv[k] = rk[k] > 0 ? (float)((double)vv[k] / pp[k]) : 0.f;
+        at[k] = s.pre[word] + __popcll(s.mask[word] & ((1ull << lane) - 1ull));
+    }
+}
+
+// The leading blocks of an adjacency kernel do two other things that need only the new node set, complete since the
+// previous kernel, so that a layer step is that many launches shorter.  Returns true for such a block.
+__device__ inline bool adj_leading_blocks(RemoteArgs &rem, NextRows &nxt, const uint64_t *__restrict__ epoch, int32_t *__restrict__ status,
+                                          const InstStride &is)
+{
+    // The first rem.blocks split the node set into local and remote (what csgs_remote_count does); they wait for nobody
+    // and nobody waits for them.
     if ((int32_t)blockIdx.x < rem.blocks) {
         rem.S_next = inst_ptr(rem.S_next, is.buf); rem.n_next = inst_ptr(rem.n_next, is.buf);
         rem.remote_total = inst_ptr(rem.remote_total, is.buf); rem.per_part = inst_ptr(rem.per_part, is.buf);
         rem.src_row = inst_ptr(rem.src_row, is.buf); rem.remote_ids = inst_ptr(rem.remote_ids, is.buf);
         remote_count_body(rem, (int32_t)blockIdx.x, rem.blocks);
-        return;
+        return true;
     }
-    // The next nxt.blocks blocks lay out the rows of the new node set.  They wait only for each other
-    // (lower tiles, dispatched before them); their flags are tagged with the draw's call number,
-    // which the previous kernel wrote, so the counter this kernel advances at its end does not matter.
+    // The next nxt.blocks lay out the rows of the new node set.  They wait only for each other (lower tiles, dispatched
+    // before them); their flags are tagged with the draw's call number, so the counter that a call's last kernel
+    // advances does not matter.
     if ((int32_t)blockIdx.x < rem.blocks + nxt.blocks) {
         nxt.S_next = inst_ptr(nxt.S_next, is.buf); nxt.n_next = inst_ptr(nxt.n_next, is.buf);
         nxt.ts_mem = inst_ptr(nxt.ts_mem, is.ws); nxt.eoff = inst_ptr(nxt.eoff, is.ws);
@@ -393,37 +483,213 @@ __global__ __launch_bounds__(256) void adj_fused(const int32_t *__restrict__ col
             row_prefix_tile(nxt.rowptr, nxt.n_nodes, nxt.S_next, n, t, n_tiles, rts, call_tag(epoch[EPOCH_DRAW], SLOT_ROWS_NEXT),
                             nxt.eoff, nxt.rowstart, nxt.meta, nxt.edge_cap, nxt.bound_note, nxt.edge_cap / EDGE_TILE, status);
         }
-        return;
+        return true;
     }
-    meta = inst_ptr(meta, is.ws); eoff = inst_ptr(eoff, is.ws); rowstart = inst_ptr(rowstart, is.ws);
-    rank = inst_ptr(rank, is.ws); member = inst_ptr(member, is.ws); pdbl = inst_ptr(pdbl, is.ws); ts_mem = inst_ptr(ts_mem, is.ws);
-    chunk_note = inst_ptr(chunk_note, is.ws);
-    adj_rowptr = inst_ptr(adj_rowptr, is.buf); adj_col = inst_ptr(adj_col, is.buf); adj_val = inst_ptr(adj_val, is.buf);
-    adj_nnz = inst_ptr(adj_nnz, is.buf);
+    return false;
+}
+
+// Two passes over the edges' chunks, neither of which waits: the first does everything that costs lookups, with as many
+// blocks as the device holds; the second only adds up 4 bytes per chunk and copies what was kept.  Against the one pass
+// below, whose 512 resident blocks wait for each other's counts once per round (us per layer): 6.6 M edges 84 / 139, 4.1 M
+// 54 / 90, eight mini-batches of 380 K 35 / 41, 957 K 15 / 22; level at 413 K (16 / 15).  The first pass is bound by
+// its random lookups in the membership words (100 G edges/s).
+// Most chunks (of all instances of a launch, as expected from the mean degree) for the one pass: 2 K edges 10.5 against 14
+// us, 52 K 10.1 / 13.8, 80 K 13.4 / 14.4; from 400 K on two passes are level or better.
+constexpr int ADJ_ONCE_MAX = 256;
+constexpr int ADJ_MARK_GRID = 2048;    // eight blocks per compute unit, by threads
+constexpr int ADJ_PLACE_GRID = 512;
+constexpr int ADJ_PLACE_MIN = 4;       // chunks a block of the placing pass takes at least: one per wavefront
+
+template <bool FROM_NOTE>
+__global__ __launch_bounds__(256) void adj_mark(AdjGraph g, const int64_t *__restrict__ meta, const uint64_t *__restrict__ epoch,
+                                                int64_t chunk_cap, int2 *__restrict__ chunk_note, uint32_t *__restrict__ chunk_cnt,
+                                                uint64_t *__restrict__ kept, int64_t kept_chunks, int32_t *__restrict__ adj_rowptr,
+                                                int32_t *__restrict__ status, RemoteArgs rem, NextRows nxt, InstStride is)
+{
+    epoch = inst_ptr(epoch, is.ws); status = inst_ptr(status, is.buf);
+    if (adj_leading_blocks(rem, nxt, epoch, status, is)) return;
+    meta = inst_ptr(meta, is.ws); g.eoff = inst_ptr(g.eoff, is.ws); g.rowstart = inst_ptr(g.rowstart, is.ws);
+    g.rank = inst_ptr(g.rank, is.ws); g.member = inst_ptr(g.member, is.ws); g.pdbl = inst_ptr(g.pdbl, is.ws);
+    chunk_note = inst_ptr(chunk_note, is.ws); chunk_cnt = inst_ptr(chunk_cnt, is.ws); kept = inst_ptr(kept, is.ws);
+    adj_rowptr = inst_ptr(adj_rowptr, is.buf);
     const int64_t bid = (int64_t)blockIdx.x - rem.blocks - nxt.blocks;
     const int64_t n_bids = (int64_t)gridDim.x - rem.blocks - nxt.blocks;
-    __shared__ RowSlice slice;
-    __shared__ uint64_t s_mask[EDGE_TILE / 64];
-    __shared__ int32_t s_pre[EDGE_TILE / 64 + 1];
-    __shared__ unsigned long long s_lb[1];
-    const int lane = lane_id();
-    const int wave = (int)(threadIdx.x >> 6);
-    const TileState<1> ts(ts_mem, chunk_cap, wait_limit(epoch));
-    const unsigned long long call = call_number(epoch);
-    const unsigned long long tag = call_tag(call, SLOT_ADJ);
+    __shared__ AdjChunk s;
     const uint64_t rank_tag = (epoch[EPOCH_DRAW] & 0xFFFFFFFFull) << 32;
+    const int32_t nS = (int32_t)meta[META_ROWS];
+    const int64_t E = meta[META_EDGES];
+    const int64_t n_chunks = (E + EDGE_TILE - 1) / EDGE_TILE;
+    if (n_chunks > chunk_cap) return;   // (adj_place reports it)
+    for (int64_t t = bid; t < n_chunks; t += n_bids) {
+        const int64_t c0 = t * EDGE_TILE;
+        const int64_t c1 = (c0 + EDGE_TILE < E) ? c0 + EDGE_TILE : E;
+        int32_t rk[4], at[4];
+        int64_t ea[4];
+        float pv[4];
+        adj_chunk<FROM_NOTE>(s, g, nS, c0, c1, rank_tag, chunk_note + t, rk, ea);
+        adj_values(s, g, rk, ea, pv, at);
+        if (threadIdx.x == 0) {
+            const int64_t off0 = s.slice.in_lds ? (int64_t)s.slice.off[0] : g.eoff[s.slice.a_first] - c0;
+            chunk_cnt[t] = (uint32_t)s.pre[EDGE_TILE / 64] | (off0 == 0 ? 0x80000000u : 0u);
+        }
+        // row pointers of the rows that start inside this chunk: kept edges of the chunk before the row start
+        const int32_t R = s.slice.R, len = (int32_t)(c1 - c0);
+        const int64_t a_first = s.slice.a_first;
+        for (int32_t r = threadIdx.x; r < R; r += blockDim.x) {
+            const int64_t off = s.slice.in_lds ? (int64_t)s.slice.off[r] : g.eoff[a_first + r] - c0;
+            if (off >= 0 && off < len) adj_rowptr[a_first + r] = s.pre[off >> 6] + __popcll(s.mask[off >> 6] & ((1ull << (off & 63)) - 1ull));
+        }
+        if (t < kept_chunks) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (rk[k] > 0) kept[t * EDGE_TILE + at[k]] = (uint64_t)(uint32_t)(rk[k] - 1) | ((uint64_t)__float_as_uint(pv[k]) << 32);
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void adj_place(AdjGraph g, const int64_t *__restrict__ meta, uint64_t *__restrict__ epoch,
+                                                 int64_t chunk_cap, int2 *__restrict__ chunk_note, const uint32_t *__restrict__ chunk_cnt,
+                                                 const uint64_t *__restrict__ kept, int64_t kept_chunks, int32_t *__restrict__ adj_rowptr,
+                                                 int32_t *__restrict__ adj_col, float *__restrict__ adj_val, int64_t adj_cap,
+                                                 int64_t *__restrict__ adj_nnz, int32_t *__restrict__ status, InstStride is)
+{
+    __shared__ uint32_t s_scan[17];
+    __shared__ uint32_t s_cnt[256], s_base[256];
+    __shared__ int2 s_note[256];
+    __shared__ uint64_t s_sum[4];
+    __shared__ AdjChunk s;   // only for chunks whose kept edges were not left (more than kept_chunks)
+    status = inst_ptr(status, is.buf); epoch = inst_ptr(epoch, is.ws);
+    meta = inst_ptr(meta, is.ws); g.eoff = inst_ptr(g.eoff, is.ws); g.rowstart = inst_ptr(g.rowstart, is.ws);
+    g.rank = inst_ptr(g.rank, is.ws); g.member = inst_ptr(g.member, is.ws); g.pdbl = inst_ptr(g.pdbl, is.ws);
+    chunk_note = inst_ptr(chunk_note, is.ws); chunk_cnt = inst_ptr(chunk_cnt, is.ws); kept = inst_ptr(kept, is.ws);
+    adj_rowptr = inst_ptr(adj_rowptr, is.buf); adj_col = inst_ptr(adj_col, is.buf); adj_val = inst_ptr(adj_val, is.buf);
+    adj_nnz = inst_ptr(adj_nnz, is.buf);
+    const int tid = (int)threadIdx.x, lane = lane_id(), wave = tid >> 6;
     const int32_t nS = (int32_t)meta[META_ROWS];
     // Row pointers never exceed what adj_col / adj_val can hold: when the kept edges overflow the
     // capacity (status bit), later kernels that walk the rows still stay inside the arrays.
     const int64_t ptr_max = adj_cap < 0x7FFFFFFFll ? adj_cap : 0x7FFFFFFFll;
     int64_t E = meta[META_EDGES];
     int64_t n_chunks = (E + EDGE_TILE - 1) / EDGE_TILE;
-    bool overflow = false;
-    if (n_chunks > chunk_cap) {  // the workspace cannot describe this many chunks: report, emit nothing
-        overflow = true;
-        E = 0;
-        n_chunks = 0;
+    const bool overflow = n_chunks > chunk_cap;   // the workspace cannot describe this many chunks: report, emit nothing
+    if (overflow) { E = 0; n_chunks = 0; }
+    if (blockIdx.x == 0 && tid == 0) {
+        epoch[EPOCH_CALLS] += 1ull;   // last kernel of the call; no block of this kernel or of the marking pass reads the counter
+        if (overflow) atomicOr(status, CSGS_ST_EDGE_OVERFLOW);
+        if (n_chunks == 0) *adj_nnz = 0;
     }
+    if (n_chunks == 0) {
+        if (blockIdx.x == 0)
+            for (int32_t a = tid; a <= nS; a += 256) adj_rowptr[a] = 0;
+        return;
+    }
+    int64_t per = (n_chunks + gridDim.x - 1) / gridDim.x;
+    if (per < ADJ_PLACE_MIN) per = ADJ_PLACE_MIN;
+    const int64_t t0 = (int64_t)blockIdx.x * per, t1 = t0 + per < n_chunks ? t0 + per : n_chunks;
+    if (t0 >= n_chunks) return;
+    constexpr uint32_t CNT = 0x7FFFFFFFu;
+    uint64_t base = 0;   // kept edges before chunk t0 (then before the chunks at hand)
+    {
+        uint64_t c = 0;
+        int64_t i = tid;
+        for (; i + 3 * 256 < t0; i += 4 * 256)
+            c += (uint64_t)(chunk_cnt[i] & CNT) + (chunk_cnt[i + 256] & CNT) + (chunk_cnt[i + 512] & CNT) + (chunk_cnt[i + 768] & CNT);
+        for (; i < t0; i += 256) c += chunk_cnt[i] & CNT;
+        c = wave_sum(c);
+        if (lane == 0) s_sum[wave] = c;
+    }
+    for (int64_t ts = t0; ts < t1; ts += 256) {
+        const int m = (int)(t1 - ts < 256 ? t1 - ts : 256);
+        const uint32_t raw = tid < m ? chunk_cnt[ts + tid] : 0u;
+        if (tid < m) s_note[tid] = chunk_note[ts + tid];
+        uint32_t sum;
+        const uint32_t ex = block_exclusive_scan<uint32_t>(raw & CNT, s_scan, &sum);   // (starts with a barrier: the arrays below are free)
+        s_cnt[tid] = raw;
+        s_base[tid] = ex;
+        if (ts == t0) base = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+        __syncthreads();
+        for (int k = wave; k < m; k += 4) {   // one wavefront per chunk
+            const int64_t t = ts + k;
+            const uint32_t cnt = s_cnt[k] & CNT;
+            const int64_t b = (int64_t)(base + s_base[k]);
+            int64_t a = s_note[k].x, a_end = a + s_note[k].y;   // (stay inside the row pointers whatever a broken prefix left)
+            if (!(s_cnt[k] >> 31)) ++a;                        // the chunk's first row began in an earlier chunk
+            if (a < 0) a = 0;
+            if (a_end > (int64_t)nS + 1) a_end = (int64_t)nS + 1;
+            for (int64_t r = a + lane; r < a_end; r += WAVE) {
+                const int64_t v = b + adj_rowptr[r];
+                adj_rowptr[r] = (int32_t)(v < ptr_max ? v : ptr_max);
+            }
+            if (t < kept_chunks)
+                for (uint32_t i = lane; i < cnt; i += WAVE) {
+                    const uint64_t e = kept[t * EDGE_TILE + i];
+                    if (b + i < adj_cap) {
+                        adj_col[b + i] = (int32_t)(uint32_t)e;
+                        adj_val[b + i] = __uint_as_float((uint32_t)(e >> 32));
+                    }
+                }
+        }
+        for (int64_t t = ts > kept_chunks ? ts : kept_chunks; t < ts + m; ++t) {   // not left by the marking pass: look them up again
+            const int64_t c0 = t * EDGE_TILE, c1 = (c0 + EDGE_TILE < E) ? c0 + EDGE_TILE : E;
+            int32_t rk[4], at[4];
+            int64_t ea[4];
+            float pv[4];
+            adj_chunk<true>(s, g, nS, c0, c1, (epoch[EPOCH_DRAW] & 0xFFFFFFFFull) << 32, chunk_note + t, rk, ea);
+            adj_values(s, g, rk, ea, pv, at);
+            const int64_t b = (int64_t)(base + s_base[t - ts]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (rk[k] > 0 && b + at[k] < adj_cap) {
+                    adj_col[b + at[k]] = rk[k] - 1;
+                    adj_val[b + at[k]] = pv[k];
+                }
+        }
+        base += sum;
+        __syncthreads();
+    }
+    if (t1 == n_chunks) {
+        // rows that start at or after the last edge (trailing empty rows, and the end pointer)
+        const int64_t total = (int64_t)base;
+        const int32_t clamp = (int32_t)(total < ptr_max ? total : ptr_max);
+        const int64_t first_tail = wave_lower_bound(g.eoff, (int64_t)nS + 1, E);
+        for (int64_t a = first_tail + tid; a <= nS; a += 256) adj_rowptr[a] = clamp;
+        if (tid == 0) {
+            *adj_nnz = total;
+            if (total > adj_cap || total > 0x7FFFFFFFll) atomicOr(status, CSGS_ST_ADJ_OVERFLOW);
+        }
+    }
+}
+
+// One pass: a block publishes its chunk's count and waits for the earlier chunks' before it places anything.  All blocks
+// are resident; block b takes chunks b, b + grid, ... in ascending order.
+template <bool FROM_NOTE>
+__global__ __launch_bounds__(256) void adj_once(AdjGraph g, const int64_t *__restrict__ meta, uint64_t *__restrict__ epoch,
+                                                uint64_t *__restrict__ ts_mem, int64_t chunk_cap, int2 *__restrict__ chunk_note,
+                                                int32_t *__restrict__ adj_rowptr, int32_t *__restrict__ adj_col,
+                                                float *__restrict__ adj_val, int64_t adj_cap, int64_t *__restrict__ adj_nnz,
+                                                int32_t *__restrict__ status, RemoteArgs rem, NextRows nxt, InstStride is)
+{
+    epoch = inst_ptr(epoch, is.ws); status = inst_ptr(status, is.buf);
+    if (adj_leading_blocks(rem, nxt, epoch, status, is)) return;
+    meta = inst_ptr(meta, is.ws); g.eoff = inst_ptr(g.eoff, is.ws); g.rowstart = inst_ptr(g.rowstart, is.ws);
+    g.rank = inst_ptr(g.rank, is.ws); g.member = inst_ptr(g.member, is.ws); g.pdbl = inst_ptr(g.pdbl, is.ws);
+    ts_mem = inst_ptr(ts_mem, is.ws); chunk_note = inst_ptr(chunk_note, is.ws);
+    adj_rowptr = inst_ptr(adj_rowptr, is.buf); adj_col = inst_ptr(adj_col, is.buf); adj_val = inst_ptr(adj_val, is.buf);
+    adj_nnz = inst_ptr(adj_nnz, is.buf);
+    const int64_t bid = (int64_t)blockIdx.x - rem.blocks - nxt.blocks;
+    const int64_t n_bids = (int64_t)gridDim.x - rem.blocks - nxt.blocks;
+    __shared__ AdjChunk s;
+    __shared__ unsigned long long s_lb[1];
+    const TileState<1> ts(ts_mem, chunk_cap, wait_limit(epoch));
+    const unsigned long long call = call_number(epoch);
+    const unsigned long long tag = call_tag(call, SLOT_ADJ);
+    const uint64_t rank_tag = (epoch[EPOCH_DRAW] & 0xFFFFFFFFull) << 32;
+    const int32_t nS = (int32_t)meta[META_ROWS];
+    const int64_t ptr_max = adj_cap < 0x7FFFFFFFll ? adj_cap : 0x7FFFFFFFll;   // (see adj_place)
+    int64_t E = meta[META_EDGES];
+    int64_t n_chunks = (E + EDGE_TILE - 1) / EDGE_TILE;
+    const bool overflow = n_chunks > chunk_cap;
+    if (overflow) { E = 0; n_chunks = 0; }
     if (n_chunks == 0) {
         if (bid == 0) {
             for (int32_t a = threadIdx.x; a <= nS; a += blockDim.x) adj_rowptr[a] = 0;
@@ -435,102 +701,40 @@ __global__ __launch_bounds__(256) void adj_fused(const int32_t *__restrict__ col
         }
         return;
     }
-    // all blocks are resident; block b takes chunks b, b + grid, ... in ascending order
     for (int64_t t = bid; t < n_chunks; t += n_bids) {
         const int64_t c0 = t * EDGE_TILE;
         const int64_t c1 = (c0 + EDGE_TILE < E) ? c0 + EDGE_TILE : E;
-        stage_slice<FROM_NOTE>(slice, eoff, rowstart, nS, c0, c1, FROM_NOTE ? chunk_note + t : nullptr);
-        const int32_t len = (int32_t)(c1 - c0);
-        // wave w owns positions [w * 256, w * 256 + 256): four 64-edge words
-        // A lane's four edges go through each step together, and no load sits under a condition (an edge that does
-        // not exist reads entry 0 and is dropped): the four columns travel at the same time, then the four table
-        // lookups, instead of eight trips one after the other.
-        int32_t rk[4];
+        int32_t rk[4], at[4];
         int64_t ea[4];
-        bool live[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int32_t x = wave * 256 + k * 64 + lane;
-            ea[k] = 0;
-            live[k] = false;
-            if (x < len) {
-                int32_t r;
-                const int64_t a = edge_address(slice, eoff, rowstart, c0, x, &r);
-                if (a >= 0 && a < nnz) {   // (an address outside the graph can only follow a failed wait)
-                    ea[k] = a;
-                    live[k] = true;
-                }
-            }
-        }
-        int32_t ck[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) ck[k] = colidx[ea[k]];
-        // the membership word of every column first (a small table that stays in the L2s), then the rank entry, which
-        // only a member's lane reads from its own place (the others read entry 0)
-        uint64_t mw[4], re[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            live[k] = live[k] && ck[k] >= 0 && ck[k] < n_nodes;
-            mw[k] = member[live[k] ? ck[k] >> 5 : 0];
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            live[k] = live[k] && (mw[k] & 0xFFFFFFFF00000000ull) == rank_tag && ((mw[k] >> (ck[k] & 31)) & 1ull);
-            re[k] = rank[live[k] ? ck[k] : 0];
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            rk[k] = (live[k] && (re[k] & 0xFFFFFFFF00000000ull) == rank_tag) ? (int32_t)(re[k] & 0xFFFFFFFFull) : 0;
-            const uint64_t m = __ballot(rk[k] > 0);
-            if (lane == 0) s_mask[wave * 4 + k] = m;
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int32_t acc = 0;
-            for (int i = 0; i < EDGE_TILE / 64; ++i) { s_pre[i] = acc; acc += __popcll(s_mask[i]); }
-            s_pre[EDGE_TILE / 64] = acc;
-        }
-        __syncthreads();
-        const int32_t tile_cnt = s_pre[EDGE_TILE / 64];
+        float pv[4];
+        adj_chunk<FROM_NOTE>(s, g, nS, c0, c1, rank_tag, FROM_NOTE ? chunk_note + t : nullptr, rk, ea);
+        const int32_t tile_cnt = s.pre[EDGE_TILE / 64];
         unsigned long long local[1] = {(unsigned long long)tile_cnt}, excl[1];
         lookback_publish<1>(ts, tag, t, local);
-        // values of the kept edges do not depend on the prefix: fetch and divide while it is resolved
-        float pv[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {   // (unconditional loads again: entry 0 stands in for an edge that was not kept)
-            const float vv = val[ea[k]];
-            const double pp = pdbl[rk[k] > 0 ? rk[k] - 1 : 0];
-            pv[k] = rk[k] > 0 ? (float)((double)vv / pp) : 0.f;
-        }
+        adj_values(s, g, rk, ea, pv, at);   // does not depend on the prefix: fetch and divide while it is resolved
         lookback_resolve<1>(ts, tag, t, n_chunks, local, excl, s_lb, status);
         const int64_t base = (int64_t)excl[0];
         // row pointers of the rows that start inside this chunk: kept edges before the row start
-        const int32_t R = slice.R;
-        const int64_t a_first = slice.a_first;
+        const int32_t R = s.slice.R, len = (int32_t)(c1 - c0);
+        const int64_t a_first = s.slice.a_first;
         for (int32_t r = threadIdx.x; r < R; r += blockDim.x) {
-            const int64_t off = slice.in_lds ? (int64_t)slice.off[r] : eoff[a_first + r] - c0;
+            const int64_t off = s.slice.in_lds ? (int64_t)s.slice.off[r] : g.eoff[a_first + r] - c0;
             if (off >= 0 && off < len) {
-                const int64_t v = base + s_pre[off >> 6] + __popcll(s_mask[off >> 6] & ((1ull << (off & 63)) - 1ull));
+                const int64_t v = base + s.pre[off >> 6] + __popcll(s.mask[off >> 6] & ((1ull << (off & 63)) - 1ull));
                 adj_rowptr[a_first + r] = (int32_t)(v < ptr_max ? v : ptr_max);
             }
         }
-        if (tile_cnt) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (rk[k] <= 0) continue;
-                const int32_t word = wave * 4 + k;
-                const int64_t pos = base + s_pre[word] + __popcll(s_mask[word] & ((1ull << lane) - 1ull));
-                if (pos < adj_cap) {
-                    adj_col[pos] = rk[k] - 1;
-                    adj_val[pos] = pv[k];
-                }
+        for (int k = 0; k < 4; ++k)
+            if (rk[k] > 0 && base + at[k] < adj_cap) {
+                adj_col[base + at[k]] = rk[k] - 1;
+                adj_val[base + at[k]] = pv[k];
             }
-        }
         if (t == n_chunks - 1) {
             // rows that start at or after the last edge (trailing empty rows, and the end pointer)
             const int64_t total = base + tile_cnt;
             const int32_t clamp = (int32_t)(total < ptr_max ? total : ptr_max);
-            const int64_t first_tail = wave_lower_bound(eoff, (int64_t)nS + 1, E);
+            const int64_t first_tail = wave_lower_bound(g.eoff, (int64_t)nS + 1, E);
             for (int64_t a = first_tail + threadIdx.x; a <= nS; a += blockDim.x) adj_rowptr[a] = clamp;
             if (threadIdx.x == 0) {
                 *adj_nnz = total;
@@ -566,7 +770,7 @@ extern "C" int csgs_draw_nodes(int64_t n_nodes, const int32_t *cand_id, const ui
     CSGS_LAUNCH_CHECK();
     const int64_t cap_words = (cand_cap + 63) / 64;
     const int64_t hit_blocks = (cap_words + HIT_MIN_WORDS - 1) / HIT_MIN_WORDS;
-    CSGS_LAUNCH(K_HITS_FUSED, hits, dim3((unsigned)(hit_blocks < HIT_GRID ? hit_blocks : HIT_GRID), 1, nz), dim3(256), st, cand_id,
+    CSGS_LAUNCH(K_HITS, hits, dim3((unsigned)(hit_blocks < HIT_GRID ? hit_blocks : HIT_GRID), 1, nz), dim3(256), st, cand_id,
                 cdf, stats, cand_cap, n_nodes, B, w.epoch, w.hit, w.cbitmap[0], w.cbitmap[1], w.rank, w.member, S_next, mult, p_incl,
                 w.pdbl, n_next, is);
     CSGS_LAUNCH_CHECK();
@@ -605,17 +809,39 @@ static int sampled_adjacency_impl(const csgs_graph *g, const int32_t *rows, int3
                        o.bound_note, w.chunk_cap * EDGE_TILE, (int32_t)((ws->draw_B + ROW_TILE - 1) / ROW_TILE)};
     }
     ws->has_next = nxt.blocks > 0;
-    // after csgs_build_probs on the same rows the weight scan has left every chunk's row slice in the workspace
-    const dim3 grid((unsigned)(resident_grid(2) + rem.blocks + nxt.blocks), 1, (unsigned)w.n_inst);
+    // Blocks for the chunks the rows may be expected to have: their number is only known on the device, but rows of the
+    // graph's mean degree are a fair guess, and blocks stride over what is more.
+    const double guess = (double)n_rows * ((double)g->nnz / (double)g->n_nodes) / EDGE_TILE * 1.25 + 16.0;
+    const int64_t chunks = guess < (double)w.chunk_cap ? (int64_t)guess : w.chunk_cap;
+    const unsigned nz = (unsigned)w.n_inst;
     const InstStride is = inst_stride(w);
+    const AdjGraph ag{g->colidx, g->val, g->n_nodes, g->nnz, cur.eoff, cur.rowstart, w.rank, w.member, w.pdbl};
+    // after csgs_build_probs on the same rows the weight scan has left every chunk's row slice in the workspace
+    if (chunks * w.n_inst <= ADJ_ONCE_MAX) {
+        const int64_t once = chunks < resident_grid(2) ? chunks : resident_grid(2);
+        const dim3 grid_once((unsigned)(once + rem.blocks + nxt.blocks), 1, nz);
+        if (reuse_offsets)
+            CSGS_LAUNCH(K_ADJ_ONCE, adj_once<true>, grid_once, dim3(256), st, ag, cur.meta, w.epoch, w.adj_ts, w.chunk_cap, cur.chunk_note,
+                        adj_rowptr, adj_col, adj_val, adj_cap, adj_nnz, status, rem, nxt, is);
+        else
+            CSGS_LAUNCH(K_ADJ_ONCE, adj_once<false>, grid_once, dim3(256), st, ag, cur.meta, w.epoch, w.adj_ts, w.chunk_cap, cur.chunk_note,
+                        adj_rowptr, adj_col, adj_val, adj_cap, adj_nnz, status, rem, nxt, is);
+        CSGS_LAUNCH_CHECK();
+        return CSGS_OK;
+    }
+    const unsigned mark = (unsigned)(chunks < ADJ_MARK_GRID ? chunks : ADJ_MARK_GRID);
+    const int64_t place_want = (chunks + ADJ_PLACE_MIN - 1) / ADJ_PLACE_MIN;
+    const unsigned place = (unsigned)(place_want < ADJ_PLACE_GRID ? place_want : ADJ_PLACE_GRID);
+    const dim3 grid(mark + (unsigned)(rem.blocks + nxt.blocks), 1, nz);
     if (reuse_offsets)
-        CSGS_LAUNCH(K_ADJ_FUSED, adj_fused<true>, grid, dim3(256), st, g->colidx, g->val, g->n_nodes,
-                    g->nnz, cur.meta, cur.eoff, cur.rowstart, w.rank, w.member, w.pdbl, w.epoch, w.adj_ts, w.chunk_cap, cur.chunk_note,
-                    adj_rowptr, adj_col, adj_val, adj_cap, adj_nnz, status, rem, nxt, is);
+        CSGS_LAUNCH(K_ADJ_MARK, adj_mark<true>, grid, dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.chunk_note, w.adj_cnt, w.stage_w,
+                    w.stage_chunks, adj_rowptr, status, rem, nxt, is);
     else
-        CSGS_LAUNCH(K_ADJ_FUSED, adj_fused<false>, grid, dim3(256), st, g->colidx, g->val, g->n_nodes,
-                    g->nnz, cur.meta, cur.eoff, cur.rowstart, w.rank, w.member, w.pdbl, w.epoch, w.adj_ts, w.chunk_cap, cur.chunk_note,
-                    adj_rowptr, adj_col, adj_val, adj_cap, adj_nnz, status, rem, nxt, is);
+        CSGS_LAUNCH(K_ADJ_MARK, adj_mark<false>, grid, dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.chunk_note, w.adj_cnt, w.stage_w,
+                    w.stage_chunks, adj_rowptr, status, rem, nxt, is);
+    CSGS_LAUNCH_CHECK();
+    CSGS_LAUNCH(K_ADJ_PLACE, adj_place, dim3(place, 1, nz), dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.chunk_note, w.adj_cnt,
+                w.stage_w, w.stage_chunks, adj_rowptr, adj_col, adj_val, adj_cap, adj_nnz, status, is);
     CSGS_LAUNCH_CHECK();
     return CSGS_OK;
 }
@@ -643,7 +869,7 @@ extern "C" int csgs_sample_layer(const csgs_graph *g, const int32_t *S, int32_t 
             return CSGS_EINVAL;
         rem = RemoteArgs{S_next, n_next, remote->local_lo, remote->local_hi, remote->part_bounds,
                          remote->per_part ? remote->P : 0, remote->remote_total, remote->per_part, remote->src_row,
-                         remote->remote_ids, REMOTE_BLOCKS};
+                         remote->remote_ids, remote_blocks(B)};
     }
     const int rc = csgs_draw_nodes(g->n_nodes, cand_id, cdf, cand_cap, stats, B, seed, iter, iter_dev, layer, S_next, mult, p_incl,
                                    n_next, ws, status, stream);
@@ -657,11 +883,10 @@ extern "C" int csgs_remote_count(const int32_t *S_next, const int32_t *n_next, i
 {
     if (!S_next || !n_next || local_lo > local_hi || !remote_total) return CSGS_EINVAL;
     if (per_part && (!part_bounds || P <= 0)) return CSGS_EINVAL;
-    // the element count is known only on the device; REMOTE_BLOCKS blocks of 256 cover the usual budgets
-    // in one sweep and stride over larger ones
+    // the element count is known only on the device: 64 blocks of 256 cover the usual budgets in one sweep
     const RemoteArgs rem{S_next, n_next, local_lo, local_hi, part_bounds, per_part ? P : 0, remote_total, per_part, src_row,
-                         remote_ids, REMOTE_BLOCKS};
-    CSGS_LAUNCH(K_REMOTE_COUNT, remote_count_k, dim3(REMOTE_BLOCKS), dim3(256), (hipStream_t)stream, rem);
+                         remote_ids, 64};
+    CSGS_LAUNCH(K_REMOTE_COUNT, remote_count_k, dim3(64), dim3(256), (hipStream_t)stream, rem);
     CSGS_LAUNCH_CHECK();
     return CSGS_OK;
 }

@@ -85,3 +85,45 @@ def test_draws_by_candidate_count(dev, n_nodes, cases):
         chain.assert_close(p[:m].cpu().numpy(), want.p_incl, chain.P_RTOL, 0.0, "p_incl")
         assert int(torch.count_nonzero(S_next[m:]).item()) == 0, "wrote past the last hit"
         assert int(torch.count_nonzero(ws.buf[:clean]).item()) == 0, "workspace not restored"
+
+
+# Calls whose edges exceed what the marking pass can leave for the placing pass (8 Mi edges), and the sizes around the
+# choice between one pass and two (256 expected chunks of 1024 edges), with rows that have no edges at both ends
+@pytest.mark.parametrize("n_nodes,degree,rows", [(70_000, 130, (70_000, 69_000, 1)), (20_000, 40, (0.29, 4000, 5300, 6500, 20_000))])
+def test_sampled_adjacency_sizes(dev, n_nodes, degree, rows):
+    from paper_2101_07706_amd import csgs, pipeline
+    rng = np.random.default_rng(n_nodes)
+    deg = rng.poisson(degree, n_nodes)
+    deg[[0, 1, 777, n_nodes - 2, n_nodes - 1]] = (0, 3000, 0, 1, 0)
+    rowptr = np.zeros(n_nodes + 1, np.int64)
+    np.cumsum(deg, out=rowptr[1:])
+    col = rng.integers(0, n_nodes, int(rowptr[-1])).astype(np.int32)
+    order = np.argsort(np.repeat(np.arange(n_nodes, dtype=np.int64), deg) * n_nodes + col, kind="stable")
+    g = synth.Graph(n_nodes, rowptr, col[order], rng.uniform(0.01, 0.2, len(col)).astype(np.float32), synth.partition_bounds(n_nodes, 4), 0, 100.0)
+    B = 900
+    n_c = n_nodes // 2
+    ids = np.sort(rng.choice(n_nodes, n_c, replace=False)).astype(np.int32)
+    cdf = np.cumsum(rng.integers(1, 1 << 20, n_c), dtype=np.uint64)
+    from types import SimpleNamespace
+    draw = oracle.draw_nodes(SimpleNamespace(cand_id=ids, cdf=cdf), B, 5, 1, 0)
+    dg = pipeline.DeviceGraph(g, dev)
+    ws = pipeline.Workspace(n_nodes, n_nodes, B, g.nnz, dev)
+    i32 = lambda n: torch.zeros(n, dtype=torch.int32, device=dev)
+    S_next, mult, n_next, status, p = i32(B), i32(B), i32(1), i32(1), torch.zeros(B, dtype=torch.float32, device=dev)
+    st = torch.frombuffer(bytearray(bytes(csgs.ProbStats(n_cand=n_c, total=int(cdf[-1])))), dtype=torch.int64).to(dev)
+    csgs.csgs_draw_nodes(n_nodes, torch.from_numpy(ids).to(dev), torch.from_numpy(cdf.view(np.int64)).to(dev), st, B, 5, 1, 0, S_next, mult, p, n_next,
+                         ws.desc, status)
+    for n_rows in rows:
+        # 0.29: rows without any edge
+        sel = np.array([0, 777, n_nodes - 1], np.int32) if n_rows == 0.29 else rng.permutation(n_nodes)[:n_rows].astype(np.int32)
+        print(f"[adjacency] {len(sel)} rows, {int(deg[sel].sum())} edges", flush=True)
+        want = oracle.sampled_adjacency(g, sel, draw)
+        cap = max(want.adj_nnz, 1) + 5
+        rp, ac, av, nnz = i32(len(sel) + 1), i32(cap), torch.zeros(cap, dtype=torch.float32, device=dev), torch.zeros(1, dtype=torch.int64, device=dev)
+        csgs.csgs_sampled_adjacency(dg.c, torch.from_numpy(sel).to(dev), rp, ac, av, nnz, ws.desc, status)
+        torch.cuda.synchronize()
+        assert int(status.item()) == 0 and int(nnz.item()) == want.adj_nnz
+        np.testing.assert_array_equal(rp.cpu().numpy(), want.adj_rowptr)
+        np.testing.assert_array_equal(ac[:want.adj_nnz].cpu().numpy(), want.adj_col)
+        chain.assert_close(av[:want.adj_nnz].cpu().numpy(), want.adj_val, chain.P_RTOL, 0.0, "adj_val")
+        assert int(torch.count_nonzero(ac[want.adj_nnz:]).item()) == 0, "wrote past the last kept edge"
