@@ -23,15 +23,16 @@ __host__ __device__ inline size_t align_up(size_t x, size_t a) { return (x + a -
 // last; how many edges they can hold follows from the size the caller passed.
 constexpr int CAND_TILE = 1024;   // node ids per block in the candidate scan
 constexpr int EDGE_TILE = 1024;   // edges per chunk in the flat edge passes
-constexpr int EDGE_GRID = 512;    // chunk blocks of the weight scan (grid-stride over chunks, they wait for nobody): two per compute unit
+constexpr int SCAN_GRID = 2048;   // most chunk blocks of the weight scan (grid-stride over chunks, they wait for nobody): more than the device holds at once
 constexpr int HIT_MIN_WORDS = 16;     // fewest 64-position bitmap words a block of the hit compaction takes
 constexpr int HIT_GRID = 512;         // most blocks of it (they wait for nobody)
 constexpr int ROW_TILE = 1024;    // rows of S per block in the degree prefix
-// Weight scan through owners: edges that end in the local id range are handed, chunk by chunk, to
-// blocks that each own SUB_IDS consecutive local ids and add them up in LDS.
-constexpr int SUB_IDS = 2048;                     // ids per owner block (16 KB of 64-bit sums)
-constexpr int SUB_MAX = 128;                      // most owner blocks: local ranges up to SUB_IDS * SUB_MAX ids
-constexpr int64_t STAGE_EDGES_MAX = 8ll << 20;    // most edges of a call that are handed over this way
+// Hand-over of the weight scan: edges that end in the local id range are left, chunk by chunk, for blocks that each add
+// up one tile of CAND_TILE ids in LDS.
+constexpr int SUB_MAX = 320;                      // most such tiles: local ranges up to 319 K ids
+constexpr int SUB_STRIDE = SUB_MAX + 32;          // entries per chunk of the groups' begins: SUB_MAX + 1, in whole 64-byte pieces
+constexpr int64_t SPLIT_BLOCKS = 512;             // most blocks of a launch over which the local tiles are split
+constexpr int64_t STAGE_EDGES_MAX = 8ll << 20;    // most edges of a call that are handed over this way (the others go through atomics)
 constexpr int EPOCH_WORDS = 8;        // counters on the device (lookback.hpp)
 constexpr int META_WORDS = 4;
 constexpr int META_ROWS = 0;          // rows the latest row_prefix covered (the count behind eoff / rowstart)
@@ -76,12 +77,13 @@ struct Workspace {
     uint32_t *adj_cnt;   // [chunk_cap] kept edges of every edge chunk | 1 << 31 when a row starts at the chunk's first edge
     uint64_t *rp_ts;     // scan state of the row tiles (1 sum per tile of ROW_TILE rows)
     double *pdbl;        // [B]      inclusion probabilities in double
-    // hand-over of local-range edges from the chunk blocks of the weight scan to the owner blocks; stage_w also takes the
-    // kept edges of a chunk (column | value << 32) from the adjacency's marking pass to its placing pass
-    uint64_t *stage_w;   // [stage_chunks * EDGE_TILE] fixed-point weight of a handed-over edge
-    uint32_t *stage_c;   // [stage_chunks * EDGE_TILE] its target id; a chunk's edges lie grouped by owner
-    uint32_t *stage_off; // [stage_chunks * SUB_MAX]   per chunk and owner: begin | end << 16 of its group
-    uint64_t *stage_done;// [stage_chunks] persistent: tag of the call whose hand-over of this chunk is complete
+    // hand-over of local-range edges from the weight scan to the candidate sums; `stage` also takes the kept edges of a
+    // chunk (column | value << 32) from the adjacency's marking pass to its placing pass
+    uint64_t *stage;     // [stage_chunks * EDGE_TILE] weight and id of a handed-over edge; a chunk's edges lie grouped by tile
+    uint16_t *stage_off; // [stage_chunks * SUB_STRIDE] per chunk and local tile: where its group begins (and the previous one ends)
+    uint64_t *split_sum; // [split_blocks * CAND_TILE] and tags: sums of the blocks that share a local tile
+    uint64_t *split_flag;// [split_blocks] persistent
+    int64_t split_blocks;
     int64_t stage_chunks;
     int64_t chunk_cap;   // chunks of EDGE_TILE edges the adjacency scan can describe
     int64_t n_tiles, rp_tiles;
@@ -171,10 +173,12 @@ __host__ inline Workspace carve(void *base, int64_t n_nodes, int64_t nS_max, int
     }
     w.pdbl = (double *)take((size_t)B_max * 8);
     w.stage_chunks = w.chunk_cap < STAGE_EDGES_MAX / EDGE_TILE ? w.chunk_cap : STAGE_EDGES_MAX / EDGE_TILE;
-    w.stage_w = (uint64_t *)take((size_t)w.stage_chunks * EDGE_TILE * 8);
-    w.stage_c = (uint32_t *)take((size_t)w.stage_chunks * EDGE_TILE * 4);
-    w.stage_off = (uint32_t *)take((size_t)w.stage_chunks * SUB_MAX * 4);
-    w.stage_done = (uint64_t *)take((size_t)w.stage_chunks * 8);
+    w.stage = (uint64_t *)take((size_t)w.stage_chunks * EDGE_TILE * 8);
+    w.stage_off = (uint16_t *)take((size_t)w.stage_chunks * SUB_STRIDE * 2);
+    w.split_blocks = w.n_tiles * (w.stage_chunks / 64 + 1);
+    if (w.split_blocks > SPLIT_BLOCKS) w.split_blocks = SPLIT_BLOCKS;
+    w.split_sum = (uint64_t *)take((size_t)w.split_blocks * CAND_TILE * 8);
+    w.split_flag = (uint64_t *)take((size_t)w.split_blocks * 8);
     w.bytes = off;
     w.n_inst = 1;
     w.buf_stride = 0;

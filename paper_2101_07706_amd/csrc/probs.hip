@@ -9,12 +9,12 @@
 //   scan_edges     flat over the edges of S (chunks of 1024, rows of a chunk staged in LDS, so
 //                  hub rows and short rows cost the same per edge): square each edge value
 //                  exactly, round to the fixed-point grid, add into a per-node 64-bit accumulator
-//                  -- remote targets with fire-and-forget integer atomics, targets in the local id
-//                  range (in launches large enough to be bound by the atomic rate) through owner
-//                  blocks that sum in LDS (see the kernel); flag the group of 8 node ids of the
+//                  -- remote targets with fire-and-forget integer atomics; targets in the local id
+//                  range (in launches with enough edges) are left grouped by tile for the next
+//                  kernel, which sums them in LDS; flag the group of 8 node ids of the
 //                  target (one 64-byte piece of the accumulator table) with a plain byte store, so
 //                  that the candidate kernels fetch only touched pieces
-//   cand_partials  per tile of 1024 node ids: candidate count, local count, local and remote
+//   cand_partials  sums of what the weight scan left for the local tiles; per tile of 1024 node ids: candidate count, local count, local and remote
 //                  weight sums of the flagged words (unskewed, so they do not depend on s); the
 //                  last tile of each group of 64 adds up its group (it waits for the other
 //                  tiles' flags)
@@ -55,36 +55,38 @@ __global__ __launch_bounds__(256) void row_prefix(const int64_t *__restrict__ ro
                     meta, edge_cap, bound_note, edge_cap / EDGE_TILE, status);
 }
 
-// Arguments of the hand-over inside the weight scan (see scan_edges).
+// Arguments of the hand-over from the weight scan to the candidate sums (see scan_edges).
 struct Stage {
-    uint64_t *w;
-    uint32_t *c, *off;
-    unsigned long long *done;
+    uint64_t *e;        // [chunks * EDGE_TILE] weight * CAND_TILE + target id % CAND_TILE; a chunk's edges lie grouped by tile
+    uint16_t *off;      // [chunks * SUB_STRIDE] per chunk and local tile: where its group begins (and the previous one ends)
     int64_t chunks;     // chunks the hand-over arrays can hold
     int32_t lo, hi;     // local id range
-    int32_t owners;     // owner blocks at the end of the grid (0: every edge goes through device-scope atomics)
-    int32_t mode;       // 0: hand over when the launch has enough chunks to be bound by the atomic rate; 1: never; 2: always
+    int32_t tiles;      // tiles of CAND_TILE ids that meet it (0: every edge goes through device-scope atomics)
+    int32_t split;      // blocks that share a tile, each taking an equal share of the chunks
+    unsigned long long *part;        // [tiles * split * CAND_TILE] sums of all but a tile's last block
+    unsigned long long *part_flag;   // [tiles * split] tag of the call that left them
 };
-// chunks (over all instances of the launch) from which the hand-over pays: below, the launch is
-// bound by latency and the owners' last round only adds to it
-constexpr int64_t STAGE_MIN_CHUNKS = 1024;
+constexpr unsigned long long HAND_OVER_WEIGHTS = 1ull << 54;   // a weight that an entry can hold beside the 10 bits of the id (larger ones go through atomics)
 
-// The weight scan.  Two kinds of blocks in one grid:
-//  * chunk blocks (the first gridDim.x - owners, grid-stride over chunks of EDGE_TILE edges): stage the
-//    rows of the chunk, fetch column and value of every edge, square and round.  An edge whose
-//    target lies outside the local id range is added to the per-node accumulator with a
-//    device-scope atomic.  The others -- most edges: the partition holds most neighbors -- are
-//    counting-sorted by owner inside the block and written to the chunk's piece of the hand-over
-//    arrays, then the chunk's flag is raised.  Scattered device-scope atomics run at about 23 G/s on
-//    this part whatever their scope or target range; LDS atomics are two orders faster.
-//  * owner blocks (the last `owners` of the grid): block r owns local ids [lo + r SUB_IDS, + SUB_IDS),
-//    sums in LDS what the chunks hand it (64 chunks at a time per wavefront, one per lane, as their
-//    flags come up), and stores the non-zero sums and their touch flags with plain stores: nobody
-//    else writes those entries.
-// Owners wait only for chunk blocks, which have lower block ids and wait for nobody.  Integer sums:
-// the result does not depend on which way an edge went or in what order.  The hand-over is used
-// when the call's edges fit its arrays and are many enough (see STAGE_MIN_CHUNKS); all blocks take
-// that decision from the same words.
+// Fixed-point weight of an edge value: exact square (24 x 24 bit product) times a power of two, then round to nearest even;
+// every candidate stays drawable.
+__device__ inline unsigned long long edge_weight(float v, double scale)
+{
+    const double sq = (double)v * (double)v;
+    const long long q = __double2ll_rn(sq * scale);
+    return q < 1 ? 1ull : (unsigned long long)q;
+}
+
+// The weight scan, grid-stride over chunks of EDGE_TILE edges: stage the rows of the chunk, fetch column and value of
+// every edge, square, round.  An edge whose target lies outside the local id range is added to the per-node accumulator
+// with a device-scope atomic.  The others -- most edges: the partition holds most neighbors -- are, in launches with
+// enough of them, counting-sorted by the tile of their target inside the block and written to the chunk's piece of the
+// hand-over array: the next kernel has blocks per local tile, which add its groups up in LDS.  Scattered device-scope
+// atomics run at about 23 G/s on this part whatever their scope or target range, and those of the remote edges are what
+// bounds a large scan.  Integer sums: the result does not depend on which way an edge went or in what order.
+// Nobody waits here, so there are as many blocks as the device holds (us, 512 blocks whose edges were summed by 2048-id
+// owner blocks of the same launch / this: 6.7 M edges 211 / 83, 3.4 M 104 / 42, 1.0 M 50 / 17, eight mini-batches of
+// 0.4 M 85 / 53; the sums then take 41, 26, 16 and 54 in cand_partials, which took 8 and, for the eight, 29).
 __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ colidx, const float *__restrict__ val,
                                                   int64_t n_nodes, int64_t nnz, int32_t shift_base,
                                                   const int64_t *__restrict__ meta, int64_t edge_cap,
@@ -92,119 +94,43 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
                                                   const int64_t *__restrict__ rowstart,
                                                   uint64_t *__restrict__ wtable, uint8_t *__restrict__ tileflag,
                                                   int2 *__restrict__ chunk_note, const int2 *__restrict__ bound_note,
-                                                  int32_t *__restrict__ status,
-                                                  const uint64_t *__restrict__ epoch, Stage stg, InstStride is)
+                                                  int32_t *__restrict__ status, Stage stg, InstStride is)
 {
+    constexpr int ITEMS = EDGE_TILE / 256;
+    constexpr int BINS = SUB_MAX / WAVE;          // groups per lane of the counting sort
+    static_assert(SUB_MAX % WAVE == 0 && EDGE_TILE <= 0xFFFF, "groups of a chunk");
     __shared__ RowSlice slice;
-    __shared__ unsigned long long acc[SUB_IDS];
+    __shared__ unsigned long long s_e[EDGE_TILE];
     __shared__ uint32_t hist[SUB_MAX + 1];
     meta = inst_ptr(meta, is.ws); eoff = inst_ptr(eoff, is.ws); rowstart = inst_ptr(rowstart, is.ws);
     wtable = inst_ptr(wtable, is.ws); tileflag = inst_ptr(tileflag, is.ws); chunk_note = inst_ptr(chunk_note, is.ws); bound_note = inst_ptr(bound_note, is.ws);
-    epoch = inst_ptr(epoch, is.ws);
-    stg.w = inst_ptr(stg.w, is.ws); stg.c = inst_ptr(stg.c, is.ws); stg.off = inst_ptr(stg.off, is.ws);
-    stg.done = inst_ptr(stg.done, is.ws);
+    stg.e = inst_ptr(stg.e, is.ws); stg.off = inst_ptr(stg.off, is.ws);
     status = inst_ptr(status, is.buf);
     const int32_t nS = (int32_t)meta[META_ROWS];
     const double scale = ldexp(1.0, shift_for_rows(shift_base, nS));
     const int64_t E = meta[META_EDGES];
     const int64_t n_chunks = (E + EDGE_TILE - 1) / EDGE_TILE;
-    const bool staged = stg.owners > 0 && n_chunks <= stg.chunks && stg.mode != 1 &&
-                        (stg.mode == 2 || n_chunks * (int64_t)gridDim.z >= STAGE_MIN_CHUNKS);
-    const unsigned long long tag = call_tag(call_number(epoch), SLOT_STAGE);
-    const int32_t chunk_blocks = (int32_t)gridDim.x - stg.owners;
+    const int32_t tile0 = stg.lo / CAND_TILE;
     const int lane = lane_id();
     const int wave = (int)(threadIdx.x >> 6);
 
-    if ((int32_t)blockIdx.x >= chunk_blocks) {   // ---------------- owner
-        if (!staged) return;
-        const int32_t r = (int32_t)blockIdx.x - chunk_blocks;
-        const int32_t base_id = stg.lo + r * SUB_IDS;
-        const int limit = wait_limit(epoch);
-        for (int i = threadIdx.x; i < SUB_IDS; i += blockDim.x) acc[i] = 0ull;
-        __syncthreads();
-        bool timed_out = false;
-        for (int64_t cb = (int64_t)wave * WAVE; cb < n_chunks; cb += (int64_t)(blockDim.x >> 6) * WAVE) {
-            // one chunk per lane: where my group lies in its piece
-            const int64_t c = cb + lane;
-            int32_t beg = 0, end = 0;
-            if (c < n_chunks) {
-                if (wait_tag(&stg.done[c], tag, limit)) {
-                    const uint32_t pr = ld_relaxed32(&stg.off[c * SUB_MAX + r]);
-                    beg = (int32_t)(pr & 0xFFFFu);
-                    end = (int32_t)(pr >> 16);
-                    if (end > EDGE_TILE || beg > end) beg = end = 0;   // (only after a failed wait elsewhere)
-                } else {
-                    timed_out = true;
-                }
-            }
-            // the 64 groups as one sequence, one entry per lane and step: entry j belongs to the first
-            // lane whose running count exceeds j
-            const int32_t n = end - beg;
-            const int32_t incl = wave_inclusive_scan<int32_t>(n);
-            const int32_t excl = incl - n;
-            const int32_t total = __builtin_amdgcn_readlane(incl, WAVE - 1);
-            for (int32_t j0 = 0; j0 < total; j0 += 4 * WAVE) {
-                unsigned long long wv[4];
-                uint32_t cv[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int32_t j = j0 + u * WAVE + lane;
-                    int lo_l = 0, hi_l = WAVE - 1;
-#pragma unroll
-                    for (int it = 0; it < 6; ++it) {
-                        const int mid = (lo_l + hi_l) >> 1;
-                        if (__shfl(incl, mid, WAVE) > j) hi_l = mid; else lo_l = mid + 1;
-                    }
-                    const int src = lo_l < WAVE ? lo_l : WAVE - 1;
-                    const int64_t pos = (cb + src) * EDGE_TILE + __shfl(beg, src, WAVE) + (j - __shfl(excl, src, WAVE));
-                    // unconditional (entry 0 stands in past the end and is dropped below), so that the four
-                    // steps' loads are on their way together
-                    const int64_t at = j < total ? pos : 0;
-                    wv[u] = ld_relaxed((const unsigned long long *)&stg.w[at]);
-                    cv[u] = ld_relaxed32(&stg.c[at]);
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int64_t x = (int64_t)cv[u] - base_id;
-                    if (j0 + u * WAVE + lane < total && x >= 0 && x < SUB_IDS) atomicAdd(&acc[x], wv[u]);
-                }
-            }
-        }
-        if (timed_out) atomicOr(status, CSGS_ST_INTERNAL);
-        __syncthreads();
-        for (int i = threadIdx.x; i < SUB_IDS; i += blockDim.x) {
-            const unsigned long long v = acc[i];
-            const int64_t id = (int64_t)base_id + i;
-            if (v && id < stg.hi && id < n_nodes) {
-                wtable[id] = v;
-                tileflag[id >> 3] = 1;
-            }
-        }
-        return;
-    }
-
-    // ---------------- chunk blocks
     if (blockIdx.x == 0 && threadIdx.x == 0 && meta[META_EDGES_TRUE] > edge_cap) atomicOr(status, CSGS_ST_EDGE_OVERFLOW);
     bool bad = false;
-    for (int64_t t = blockIdx.x; t < n_chunks; t += chunk_blocks) {
+    for (int64_t t = blockIdx.x; t < n_chunks; t += gridDim.x) {
         const int64_t c0 = t * EDGE_TILE;
         const int64_t c1 = (c0 + EDGE_TILE < E) ? c0 + EDGE_TILE : E;
-        stage_slice_bounds(slice, eoff, rowstart, nS, t, c0, c1, bound_note, chunk_note + t);   // (starts with a barrier)
-        if (staged) {
-            for (int i = threadIdx.x; i <= SUB_MAX; i += blockDim.x) hist[i] = 0u;
-            __syncthreads();
-        }
+        const bool staged = stg.tiles > 0 && t < stg.chunks;   // (chunks beyond the arrays go through atomics)
+        if (staged)
+            for (int i = threadIdx.x; i < SUB_MAX; i += blockDim.x) hist[i] = 0u;   // (its last readers are a barrier behind)
+        stage_slice_bounds(slice, eoff, rowstart, nS, t, c0, c1, bound_note, chunk_note + t);   // (starts and ends with a barrier)
         const int32_t len = (int32_t)(c1 - c0);
-        unsigned long long hq[EDGE_TILE / 256];
-        int32_t hc[EDGE_TILE / 256], hb[EDGE_TILE / 256];
-        uint32_t hr[EDGE_TILE / 256];
         // All of a thread's edges go through each step together -- their addresses, then their columns and
         // values with unconditional loads (an edge that does not exist reads entry 0 and is dropped) -- so
         // the loads of the four edges travel at the same time instead of one after the other.
-        int64_t ek[EDGE_TILE / 256];
-        bool live[EDGE_TILE / 256];
+        int64_t ek[ITEMS];
+        bool live[ITEMS];
 #pragma unroll
-        for (int k = 0; k < EDGE_TILE / 256; ++k) {
+        for (int k = 0; k < ITEMS; ++k) {
             const int32_t x = (int32_t)threadIdx.x + k * 256;
             ek[k] = 0;
             live[k] = x < len;
@@ -218,90 +144,83 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
                 }
             }
         }
-        int32_t ck[EDGE_TILE / 256];
-        float vk[EDGE_TILE / 256];
+        int32_t ck[ITEMS];
+        float vk[ITEMS];
 #pragma unroll
-        for (int k = 0; k < EDGE_TILE / 256; ++k) {
+        for (int k = 0; k < ITEMS; ++k) {
             ck[k] = colidx[ek[k]];
             vk[k] = val[ek[k]];
         }
-        // Everything that reads a loaded value comes before the first update: an update issued between two
-        // such reads would have to be acknowledged before the second value counts as arrived.
-        long long qk[EDGE_TILE / 256];
+        unsigned long long qk[ITEMS];
+        int32_t hb[ITEMS];    // tile of an edge that is handed over; -1: no edge, -2: device-scope atomic
+        uint32_t hr[ITEMS];   // its place inside the group (any order)
 #pragma unroll
-        for (int k = 0; k < EDGE_TILE / 256; ++k) {
+        for (int k = 0; k < ITEMS; ++k) {
             const bool sound = isfinite(vk[k]) && ck[k] >= 0 && ck[k] < n_nodes;
             if (live[k] && !sound) bad = true;
-            live[k] = live[k] && sound;
-            const double sq = (double)vk[k] * (double)vk[k];   // exact: 24 x 24 bit product
-            qk[k] = live[k] ? __double2ll_rn(sq * scale) : 0;  // scale is a power of two: exact, then RNE
-            if (qk[k] < 1) qk[k] = 1;                          // every candidate stays drawable
-        }
-#pragma unroll
-        for (int k = 0; k < EDGE_TILE / 256; ++k) {
             hb[k] = -1;
-            hq[k] = 0ull; hc[k] = 0; hr[k] = 0u;
-            if (!live[k]) continue;
-            const int32_t c = ck[k];
-            if (staged && c >= stg.lo && c < stg.hi) {
-                hb[k] = (c - stg.lo) / SUB_IDS;           // < owners <= SUB_MAX
-                hq[k] = (unsigned long long)qk[k];
-                hc[k] = c;
-                hr[k] = atomicAdd(&hist[hb[k]], 1u);      // place inside the owner's group (any order)
-            } else {
-                hb[k] = -2;   // goes through a device-scope atomic, issued after the chunk's hand-over (below)
+            hr[k] = 0u;
+            qk[k] = 0ull;
+            if (!live[k] || !sound) continue;
+            hb[k] = -2;
+            qk[k] = edge_weight(vk[k], scale);
+            if (staged && ck[k] >= stg.lo && ck[k] < stg.hi && qk[k] < HAND_OVER_WEIGHTS) {
+                hb[k] = ck[k] / CAND_TILE - tile0;            // < stg.tiles <= SUB_MAX
+                hr[k] = atomicAdd(&hist[hb[k]], 1u);
             }
         }
         if (staged) {
             __syncthreads();
-            if (wave == 0) {   // counts -> begin of every owner's group; two owners per lane
-                const uint32_t a = hist[2 * lane], b = (2 * lane + 1 <= SUB_MAX) ? hist[2 * lane + 1] : 0u;
-                const uint32_t incl = wave_inclusive_scan<uint32_t>(a + b);
-                const uint32_t ex = incl - (a + b);
-                hist[2 * lane] = ex;
-                hist[2 * lane + 1] = ex + a;
-                if (lane == WAVE - 1) hist[SUB_MAX] = incl;   // edges handed over by this chunk
-                // begin | end << 16 for the owners' lookups
-                st_relaxed32(&stg.off[t * SUB_MAX + 2 * lane], ex | ((ex + a) << 16));
-                st_relaxed32(&stg.off[t * SUB_MAX + 2 * lane + 1], (ex + a) | ((ex + a + b) << 16));
+            if (wave == 0) {   // counts -> begin of every group
+                uint32_t cnt[BINS], sum = 0;
+#pragma unroll
+                for (int i = 0; i < BINS; ++i) {
+                    cnt[i] = hist[lane * BINS + i];
+                    sum += cnt[i];
+                }
+                const uint32_t incl = wave_inclusive_scan<uint32_t>(sum);
+                uint32_t ex = incl - sum;
+#pragma unroll
+                for (int i = 0; i < BINS; ++i) {
+                    hist[lane * BINS + i] = ex;
+                    if (lane * BINS + i <= stg.tiles) stg.off[t * SUB_STRIDE + lane * BINS + i] = (uint16_t)ex;
+                    ex += cnt[i];
+                }
+                if (lane == WAVE - 1) {   // edges handed over by this chunk
+                    hist[SUB_MAX] = incl;
+                    if (stg.tiles == SUB_MAX) stg.off[t * SUB_STRIDE + SUB_MAX] = (uint16_t)incl;
+                }
             }
             __syncthreads();
-            // grouped by owner in LDS first (the owner blocks' sum array is free here), then out in
-            // order: full 64-byte pieces instead of one scattered store per edge
-            static_assert(SUB_IDS * 8 >= EDGE_TILE * 12, "the sort buffer lives in the owners' sum array");
-            unsigned long long *s_w = acc;                                           // [EDGE_TILE]
-            uint32_t *s_c = reinterpret_cast<uint32_t *>(acc + EDGE_TILE);           // [EDGE_TILE]
+            // grouped in LDS first, then out in order: full 64-byte pieces instead of one scattered store per edge
 #pragma unroll
-            for (int k = 0; k < EDGE_TILE / 256; ++k) {
-                if (hb[k] < 0) continue;
-                const uint32_t slot = hist[hb[k]] + hr[k];    // < EDGE_TILE: the groups partition the chunk's local edges
-                s_w[slot] = hq[k];
-                s_c[slot] = (uint32_t)hc[k];
-            }
+            for (int k = 0; k < ITEMS; ++k)
+                if (hb[k] >= 0) s_e[hist[hb[k]] + hr[k]] = qk[k] * CAND_TILE + (unsigned)(ck[k] % CAND_TILE);   // < EDGE_TILE: the groups partition the chunk's local edges
             __syncthreads();
             const uint32_t n_handed = hist[SUB_MAX];
-            for (uint32_t i = threadIdx.x; i < n_handed; i += blockDim.x) {
-                st_relaxed((unsigned long long *)&stg.w[t * EDGE_TILE + i], s_w[i]);
-                st_relaxed32(&stg.c[t * EDGE_TILE + i], s_c[i]);
-            }
-            wait_memory_ops();     // this wavefront's hand-over stores have been acknowledged
-            __syncthreads();
-            if (threadIdx.x == 0) st_flag(&stg.done[t], tag);
+            for (uint32_t i = threadIdx.x; i < n_handed; i += blockDim.x) stg.e[t * EDGE_TILE + i] = s_e[i];
         }
-        // The edges that end outside the local range (all edges without the hand-over).  After the flag: the wait above
-        // would otherwise include these updates, which take far longer to be acknowledged than the stores, and the
-        // owners would start that much later.
 #pragma unroll
-        for (int k = 0; k < EDGE_TILE / 256; ++k) {
+        for (int k = 0; k < ITEMS; ++k) {
             if (hb[k] != -2) continue;
             const int32_t c = ck[k];
-            (void)__hip_atomic_fetch_add((unsigned long long *)&wtable[c], (unsigned long long)qk[k], __ATOMIC_RELAXED,
+            (void)__hip_atomic_fetch_add((unsigned long long *)&wtable[c], qk[k], __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT);
             tileflag[c >> 3] = 1;  // same value from every writer
         }
     }
     if (bad) atomicOr(status, CSGS_ST_BAD_EDGE_VALUE);
 }
+
+// The hand-over is taken from this many chunks on (of all instances of a launch, as expected from the mean degree): below,
+// the atomics hide in the scan's latency (scan + candidate sums, atomics / hand-over: 75 chunks 18 / 19 us, 1004 chunks
+// 56 / 33, 426 chunks 36 / 24).
+constexpr double HAND_OVER_MIN_CHUNKS = 160.0;
+// A tile's sums are split over several blocks while each block has this many edges left and the launch has SPLIT_BLOCKS
+// of them at most, two per compute unit: a narrow local range has few tiles (29 tiles, 1 M edges: 31 us with a block
+// per tile, 16 split by 7), and 150 tiles leave compute units idle (5.4 M edges: 49 / 40 us).  Shares below that only
+// add the hop between the blocks (150 tiles, 0.35 M edges: 11 us with a block per tile, 14 split by 3).
+constexpr double SPLIT_MIN_EDGES = 4096.0;
 
 // Skew policy, resolved on the device once the candidate counts are known.
 struct SkewPolicy {
@@ -338,73 +257,194 @@ constexpr int CAND_WORDS = CAND_TILE / WAVE;  // 16 words per tile, 4 per wave
 // Tile sums, and -- by the last tile of every group of 64 -- the group's sums.  That tile waits
 // for the flags of the (at most 63) lower tiles of its group, which were dispatched before it
 // (ascending block ids) or belong to its own block and are published before the wait, and which
-// wait for nobody, so the wait ends.  A block takes CAND_PART_TILES consecutive tiles and asks for
-// the flags of all their words, then for all their pieces of the table: two load latencies per block.
-constexpr int CAND_PART_TILES = 2;
-__global__ __launch_bounds__(256) void cand_partials(const uint64_t *__restrict__ wtable,
-                                                     const uint8_t *__restrict__ tileflag, int64_t n_words,
+// wait for nobody, so the wait ends.  Two kinds of blocks:
+//  * a block of four tiles asks for the flags of all their words, then for their pieces of the table: two load latencies.
+//  * when the weight scan has handed the local edges over, every tile that meets the local range has a block of its own,
+//    which first adds up in LDS what the chunks left for it (64 chunks at a time per wavefront, one per lane) and stores the
+//    sums and their touch flags: nobody else writes the local entries.  Bound by the latency of those reads; eight
+//    wavefronts per tile.
+constexpr int CAND_PART_BLOCK = 512, CAND_PART_TILES = 4;
+constexpr int CAND_PART_WORDS = CAND_PART_TILES * CAND_WORDS / (CAND_PART_BLOCK / WAVE);   // words per wavefront
+
+// Sums of the edges that chunks [c_first, n_chunks) handed over for local tile `tile` into acc[CAND_TILE] (LDS, zeroed here).  A wavefront takes up to 64
+// chunks at a time, one per lane, and walks through their groups as one sequence.  Called by all threads; ends with a barrier.
+__device__ inline void sum_handed_over(unsigned long long *acc, const Stage &stg, int32_t tile, int64_t c_first, int64_t n_chunks)
+{
+    constexpr int U = 8;   // entries on their way per lane
+    const int lane = lane_id();
+    const int wave = (int)(threadIdx.x >> 6);
+    for (int i = threadIdx.x; i < CAND_TILE; i += CAND_PART_BLOCK) acc[i] = 0ull;
+    __syncthreads();
+    const uint16_t *__restrict__ off = stg.off + tile;
+    const uint64_t *__restrict__ e = stg.e;
+    uint16_t beg, end;
+    auto extents = [&](int64_t cb) {   // where my chunk's group lies in its piece
+        const int64_t c = cb + lane;
+        const uint16_t *p = off + (c < n_chunks ? c : n_chunks - 1) * SUB_STRIDE;
+        beg = p[0];
+        end = p[1];
+    };
+    constexpr int WAVES = CAND_PART_BLOCK / WAVE;
+    const int64_t want = (n_chunks - c_first + WAVES - 1) / WAVES;
+    const int32_t per = want < WAVE ? (int32_t)want : WAVE;   // chunks per wavefront at a time
+    int64_t cb = c_first + (int64_t)wave * per;
+    extents(cb);
+    for (; cb < n_chunks; cb += WAVES * per) {
+        // entry j of the sequence belongs to the first lane whose running count exceeds j
+        const int32_t n = (lane < per && cb + lane < n_chunks && beg <= end && end <= EDGE_TILE) ? (int32_t)end - (int32_t)beg : 0;
+        const int32_t incl = wave_inclusive_scan<int32_t>(n);
+        const int32_t first = (int32_t)beg - (incl - n) + lane * EDGE_TILE;   // it is entry first + j of the 64 chunks' pieces
+        const int32_t total = __builtin_amdgcn_readlane(incl, WAVE - 1);
+        const uint64_t *__restrict__ piece = e + cb * EDGE_TILE;
+        extents(cb + WAVES * per);   // of the next chunks
+        for (int32_t j0 = 0; j0 < total; j0 += U * WAVE) {
+            uint64_t v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int32_t j = j0 + u * WAVE + lane;
+                int lo_l = 0, hi_l = WAVE - 1;
+#pragma unroll
+                for (int it = 0; it < 6; ++it) {
+                    const int mid = (lo_l + hi_l) >> 1;
+                    if (__shfl(incl, mid, WAVE) > j) hi_l = mid; else lo_l = mid + 1;
+                }
+                const int32_t pos = __shfl(first, lo_l, WAVE) + j;
+                // unconditional (entry 0 stands in past the end and is dropped below), so that the steps' loads are on
+                // their way together
+                v[u] = piece[j < total ? pos : 0];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (j0 + u * WAVE + lane < total) atomicAdd(&acc[v[u] % CAND_TILE], (unsigned long long)(v[u] / CAND_TILE));
+        }
+    }
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(CAND_PART_BLOCK) void cand_partials(uint64_t *__restrict__ wtable,
+                                                     uint8_t *__restrict__ tileflag, int64_t n_words,
                                                      int64_t n_nodes, int64_t n_tiles, int32_t lo, int32_t hi,
-                                                     const uint64_t *__restrict__ epoch, unsigned long long *__restrict__ cand_flag,
+                                                     const int64_t *__restrict__ meta, Stage stg,
+                                                     int64_t blocks_below, const uint64_t *__restrict__ epoch, unsigned long long *__restrict__ cand_flag,
                                                      unsigned long long *__restrict__ partial,
                                                      uint64_t *__restrict__ gtot, int32_t *__restrict__ status, InstStride is)
 {
-    constexpr int TPB = CAND_PART_TILES, W = CAND_WORDS / 4;   // tiles per block, words per wavefront and tile
-    __shared__ uint64_t lds[TPB][4][3];
+    constexpr int W = CAND_PART_WORDS, WAVES = CAND_PART_BLOCK / WAVE;
+    __shared__ uint64_t lds[WAVES][3];
+    __shared__ unsigned long long acc[CAND_TILE];
     wtable = inst_ptr(wtable, is.ws); tileflag = inst_ptr(tileflag, is.ws); epoch = inst_ptr(epoch, is.ws);
     cand_flag = inst_ptr(cand_flag, is.ws); partial = inst_ptr(partial, is.ws); gtot = inst_ptr(gtot, is.ws);
-    status = inst_ptr(status, is.buf);
+    status = inst_ptr(status, is.buf); meta = inst_ptr(meta, is.ws);
+    stg.e = inst_ptr(stg.e, is.ws); stg.off = inst_ptr(stg.off, is.ws);
+    stg.part = inst_ptr(stg.part, is.ws); stg.part_flag = inst_ptr(stg.part_flag, is.ws);
     const int lane = lane_id();
     const int wave = (int)(threadIdx.x >> 6);
-    const int64_t t0 = (int64_t)blockIdx.x * TPB;
     const unsigned long long tag = call_tag(call_number(epoch), SLOT_CAND);
-    uint64_t f8[TPB][W], w[TPB][W];
-#pragma unroll
-    for (int h = 0; h < TPB; ++h)
-#pragma unroll
-        for (int k = 0; k < W; ++k) {
-            const int64_t word_idx = (t0 + h) * CAND_WORDS + wave * W + k;
-            f8[h][k] = word_idx < n_words ? reinterpret_cast<const uint64_t *>(tileflag)[word_idx] : 0ull;   // the word's eight group flags
-        }
-#pragma unroll
-    for (int h = 0; h < TPB; ++h)
-#pragma unroll
-        for (int k = 0; k < W; ++k) {
-            const uint32_t id = ((uint32_t)(t0 + h) * CAND_WORDS + wave * W + k) * 64u + lane;   // below 2^31 + 1024
-            // only the touched groups of 8 ids (one 64-byte piece of the table each) are fetched
-            w[h][k] = (((f8[h][k] >> (8 * (lane >> 3))) & 0xFFull) && id < (uint32_t)n_nodes) ? wtable[id] : 0ull;
-        }
+    // blocks in the order of their tiles: blocks_below of four tiles, one per tile that meets the local range, four again
+    const int64_t tile0 = stg.lo / CAND_TILE;
+    int64_t t0, t1;
+    const int64_t b = (int64_t)blockIdx.x - blocks_below;
+    const int64_t own_blocks = (int64_t)stg.tiles * stg.split;
+    const bool own = b >= 0 && b < own_blocks;
+    if (b < 0) {
+        t0 = (int64_t)blockIdx.x * CAND_PART_TILES;
+        t1 = t0 + CAND_PART_TILES;
+        if (stg.tiles > 0 && t1 > tile0) t1 = tile0;
+    } else if (own) {
+        t0 = tile0 + b / stg.split;
+        t1 = t0 + 1;
+    } else {   // from the block of four that the last local tile belongs to
+        const int64_t end = tile0 + stg.tiles, q = end / CAND_PART_TILES + (b - own_blocks);
+        t0 = q * CAND_PART_TILES;
+        t1 = t0 + CAND_PART_TILES;
+        if (t0 < end) t0 = end;
+    }
+    if (t1 > n_tiles) t1 = n_tiles;
+    if (t0 >= t1) return;   // the whole block
+    const int64_t E = meta[META_EDGES], all_chunks = (E + EDGE_TILE - 1) / EDGE_TILE;
+    const int64_t n_chunks = all_chunks < stg.chunks ? all_chunks : stg.chunks;   // that have handed over
+    const bool sums = own && n_chunks > 0;
+    const int share = own ? (int)(b % stg.split) : 0;
+    if (own && share != stg.split - 1) {   // a share of a tile's sums: left for the block of the last share
+        if (!sums) return;
+        sum_handed_over(acc, stg, (int32_t)(t0 - tile0), n_chunks * share / stg.split, n_chunks * (share + 1) / stg.split);
+        for (int i = threadIdx.x; i < CAND_TILE; i += CAND_PART_BLOCK) st_relaxed(&stg.part[b * CAND_TILE + i], acc[i]);
+        wait_memory_ops();
+        __syncthreads();
+        if (threadIdx.x == 0) st_relaxed(&stg.part_flag[b], tag);
+        return;
+    }
+    const int waves_per_tile = own ? WAVES : WAVES / CAND_PART_TILES;
+    const int64_t tile = own ? t0 : (t0 / CAND_PART_TILES) * CAND_PART_TILES + wave / waves_per_tile;   // of this wavefront
+    const bool in_block = tile >= t0 && tile < t1;
+    const int w_used = own ? CAND_WORDS / WAVES : W;   // words of this wavefront
+    const int64_t word0 = tile * CAND_WORDS + (wave % waves_per_tile) * w_used;
     const uint32_t lo_u = lo > 0 ? (uint32_t)lo : 0u, hi_u = hi > 0 ? (uint32_t)hi : 0u;
+    uint64_t f8[W], w[W];
 #pragma unroll
-    for (int h = 0; h < TPB; ++h) {
+    for (int k = 0; k < W; ++k) {
+        const bool have = in_block && k < w_used && word0 + k < n_words;
+        f8[k] = have ? reinterpret_cast<const uint64_t *>(tileflag)[word0 + k] : 0ull;   // the word's eight group flags
+    }
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+        const uint32_t id = (uint32_t)(word0 + k) * 64u + lane;   // below 2^31 + 1024
+        // only the touched groups of 8 ids (one 64-byte piece of the table each) are fetched
+        w[k] = (((f8[k] >> (8 * (lane >> 3))) & 0xFFull) && id < (uint32_t)n_nodes) ? wtable[id] : 0ull;
+    }
+    if (sums) {   // (what did not fit an entry, and ids of the tile outside the local range, have come through the table)
+        sum_handed_over(acc, stg, (int32_t)(t0 - tile0), n_chunks * share / stg.split, n_chunks);
+        if (stg.split > 1) {   // (the other shares' blocks were dispatched before and wait for nobody)
+            const int64_t first = b - share;
+            bool ok = true;
+            if (threadIdx.x < (unsigned)share) ok = wait_tag(&stg.part_flag[first + threadIdx.x], tag, wait_limit(epoch));
+            if (!ok) atomicOr(status, CSGS_ST_INTERNAL);
+            __syncthreads();
+            for (int i = threadIdx.x; i < CAND_TILE; i += CAND_PART_BLOCK) {
+                unsigned long long v = acc[i];
+                for (int k = 0; k < share; ++k) v += ld_relaxed(&stg.part[(first + k) * CAND_TILE + i]);
+                acc[i] = v;
+            }
+            __syncthreads();
+        }
+#pragma unroll
+        for (int k = 0; k < CAND_WORDS / WAVES; ++k) {
+            const uint32_t id = (uint32_t)(word0 + k) * 64u + lane;
+            const unsigned long long v = acc[id - (uint32_t)(t0 * CAND_TILE)];
+            if (v && id < hi_u) {
+                w[k] += v;
+                wtable[id] = w[k];
+                tileflag[id >> 3] = 1;
+            }
+        }
+    }
+    {
         // counts from the ballots (scalar work), weights as the sum over everything and over the local ids: two
-        // wave-wide 64-bit sums per tile instead of three
+        // wave-wide 64-bit sums instead of three
         uint64_t cn = 0, wl = 0, wa = 0;   // cn packs (candidates << 32) | local candidates
 #pragma unroll
         for (int k = 0; k < W; ++k) {
-            const uint32_t id = ((uint32_t)(t0 + h) * CAND_WORDS + wave * W + k) * 64u + lane;
+            const uint32_t id = (uint32_t)(word0 + k) * 64u + lane;
             const bool local = id >= lo_u && id < hi_u;
-            cn += ((uint64_t)__popcll(__ballot(w[h][k] != 0)) << 32) | (uint64_t)__popcll(__ballot(w[h][k] != 0 && local));
-            wa += w[h][k];
-            wl += local ? w[h][k] : 0ull;
+            cn += ((uint64_t)__popcll(__ballot(w[k] != 0)) << 32) | (uint64_t)__popcll(__ballot(w[k] != 0 && local));
+            wa += w[k];
+            wl += local ? w[k] : 0ull;
         }
         wl = wave_sum(wl); wa = wave_sum(wa);
-        if (lane == 0) { lds[h][wave][0] = cn; lds[h][wave][1] = wl; lds[h][wave][2] = wa - wl; }
+        if (lane == 0) { lds[wave][0] = cn; lds[wave][1] = wl; lds[wave][2] = wa - wl; }
     }
     __syncthreads();
-    if (wave != 0) return;
-    // packed count halves cannot carry: each is at most 1024 per tile
-    unsigned long long mine = 0ull;   // of the block's last tile
-    int64_t t = t0;
-#pragma unroll
-    for (int h = 0; h < TPB; ++h) {
-        if (t0 + h >= n_tiles) break;
-        t = t0 + h;
-        mine = lane < 3 ? lds[h][0][lane] + lds[h][1][lane] + lds[h][2][lane] + lds[h][3][lane] : 0ull;
-        if (lane < 3) st_relaxed(&partial[t * 4 + lane], mine);
-        if (lane == 0) st_flag(&cand_flag[t], tag);   // after the wavefront's value stores have been acknowledged
-    }
-    // the last tile of a group (and the last tile of all) is odd-numbered or the last: always a block's last tile
-    static_assert(LB_GROUP % CAND_PART_TILES == 0, "a group's last tile must be a block's last tile");
+    // one wavefront publishes each tile; the block's last tile is the last wavefront's.
+    // (packed count halves cannot carry: each is at most 1024 per tile)
+    const int64_t t = t0 + wave;
+    if (t >= t1) return;
+    const int w0 = own ? 0 : (int)(t % CAND_PART_TILES) * waves_per_tile;
+    unsigned long long mine = 0ull;
+    if (lane < 3)
+        for (int i = 0; i < waves_per_tile; ++i) mine += lds[w0 + i][lane];
+    if (lane < 3) st_relaxed(&partial[t * 4 + lane], mine);
+    if (lane == 0) st_flag(&cand_flag[t], tag);   // after the wavefront's value stores have been acknowledged
+    // A wavefront waits only for tiles below its own, and every tile's wavefront publishes before it waits.
     const int r = (int)(t % LB_GROUP);
     if (r != LB_GROUP - 1 && t != n_tiles - 1) return;
     const int64_t g = t / LB_GROUP;
@@ -413,8 +453,8 @@ __global__ __launch_bounds__(256) void cand_partials(const uint64_t *__restrict_
     unsigned long long sum[3];
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-        const unsigned long long own = __shfl(mine, i, WAVE);
-        sum[i] = own + wave_sum((lane < r && ok) ? ld_relaxed(&partial[(g * LB_GROUP + lane) * 4 + i]) : 0ull);
+        const unsigned long long own_sum = __shfl(mine, i, WAVE);
+        sum[i] = own_sum + wave_sum((lane < r && ok) ? ld_relaxed(&partial[(g * LB_GROUP + lane) * 4 + i]) : 0ull);
     }
     if (__ballot(!ok) && lane == 0) atomicOr(status, CSGS_ST_INTERNAL);
     if (lane < 3) gtot[g * 4 + lane] = lane == 0 ? sum[0] : (lane == 1 ? sum[1] : sum[2]);
@@ -723,19 +763,35 @@ static int build_probs_impl(const csgs_graph *g, const int32_t *S, int32_t nS, c
     const RowOffsets &rows = w.rows[ws->rows_buf & 1];
     const unsigned nz = (unsigned)w.n_inst;
     const InstStride is = inst_stride(w);
-    // owner blocks for the local id range, when it is one the hand-over can cover
-    const int64_t n_local = (int64_t)g->local_hi - (int64_t)g->local_lo;
-    const int32_t owners = (n_local > 0 && n_local <= (int64_t)SUB_IDS * SUB_MAX && g->local_lo >= 0 && g->local_hi <= g->n_nodes)
-                               ? (int32_t)((n_local + SUB_IDS - 1) / SUB_IDS) : 0;
-    const Stage stg{w.stage_w, w.stage_c, w.stage_off, (unsigned long long *)w.stage_done, w.stage_chunks, g->local_lo,
-                    g->local_hi, owners, ws->scan_mode};
-    CSGS_LAUNCH(K_SCAN_EDGES, scan_edges, dim3((unsigned)(EDGE_GRID + owners), 1, nz), dim3(256), st, g->colidx, g->val,
+    // The number of edges is known on the device only; rows of the graph's mean degree are a fair guess.
+    const double guess = (double)nS * ((double)g->nnz / (double)g->n_nodes) / EDGE_TILE;
+    const int64_t chunks = guess * 1.25 + 16.0 < (double)w.chunk_cap ? (int64_t)(guess * 1.25 + 16.0) : w.chunk_cap;
+    // tiles that meet the local id range, when the hand-over can cover them and is wanted
+    const bool range_ok = g->local_hi > g->local_lo && g->local_lo >= 0 && g->local_hi <= g->n_nodes;
+    const int64_t tile0 = range_ok ? g->local_lo / CAND_TILE : 0, tile1 = range_ok ? ((int64_t)g->local_hi - 1) / CAND_TILE + 1 : 0;
+    const bool hand = ws->scan_mode == 2 || (ws->scan_mode == 0 && guess * (double)w.n_inst >= HAND_OVER_MIN_CHUNKS);
+    const int32_t tiles = (hand && tile1 - tile0 <= SUB_MAX) ? (int32_t)(tile1 - tile0) : 0;
+    int64_t split = 1;
+    if (tiles) {
+        split = SPLIT_BLOCKS / ((int64_t)tiles * w.n_inst);
+        const int64_t most = (int64_t)(guess * EDGE_TILE / tiles / SPLIT_MIN_EDGES);
+        if (split > most) split = most;
+        if (split > w.split_blocks / tiles) split = w.split_blocks / tiles;
+        if (split > WAVE) split = WAVE;
+        if (split < 1) split = 1;
+    }
+    const Stage stg{w.stage, w.stage_off, w.stage_chunks, range_ok ? g->local_lo : 0, range_ok ? g->local_hi : 0, tiles, (int32_t)split,
+                    (unsigned long long *)w.split_sum, (unsigned long long *)w.split_flag};
+    CSGS_LAUNCH(K_SCAN_EDGES, scan_edges, dim3((unsigned)(chunks < SCAN_GRID ? chunks : SCAN_GRID), 1, nz), dim3(256), st, g->colidx, g->val,
                 g->n_nodes, g->nnz, shift_base, rows.meta, w.chunk_cap * EDGE_TILE, rows.eoff, rows.rowstart, w.wtable,
-                w.tileflag, rows.chunk_note, rows.bound_note, status, w.epoch, stg, is);
+                w.tileflag, rows.chunk_note, rows.bound_note, status, stg, is);
     CSGS_LAUNCH_CHECK();
-    CSGS_LAUNCH(K_CAND_PARTIALS, cand_partials, dim3((unsigned)((w.n_tiles + CAND_PART_TILES - 1) / CAND_PART_TILES), 1, nz), dim3(256), st, w.wtable, w.tileflag, n_words,
-                g->n_nodes, w.n_tiles, g->local_lo, g->local_hi, w.epoch, (unsigned long long *)w.cand_flag,
-                (unsigned long long *)w.partial, w.gtot, status, is);
+    const int64_t below = tiles ? (tile0 + CAND_PART_TILES - 1) / CAND_PART_TILES : 0;
+    const int64_t part_blocks = tiles ? below + tiles * split + (w.n_tiles + CAND_PART_TILES - 1) / CAND_PART_TILES - tile1 / CAND_PART_TILES
+                                      : (w.n_tiles + CAND_PART_TILES - 1) / CAND_PART_TILES;
+    CSGS_LAUNCH(K_CAND_PARTIALS, cand_partials, dim3((unsigned)part_blocks, 1, nz), dim3(CAND_PART_BLOCK), st, w.wtable, w.tileflag, n_words,
+                g->n_nodes, w.n_tiles, g->local_lo, g->local_hi, rows.meta, stg, tiles ? below : part_blocks, w.epoch,
+                (unsigned long long *)w.cand_flag, (unsigned long long *)w.partial, w.gtot, status, is);
     CSGS_LAUNCH_CHECK();
     CSGS_LAUNCH(K_CAND_EMIT, cand_emit, dim3((unsigned)w.n_tiles, 1, nz), dim3(256), st, w.wtable, w.tileflag, n_words,
                 g->n_nodes, w.n_tiles, g->local_lo, g->local_hi, pol, w.partial, w.gtot, rows.meta, shift_base, w.epoch, stats, status, cand_id,

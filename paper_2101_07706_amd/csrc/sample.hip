@@ -834,14 +834,14 @@ static int sampled_adjacency_impl(const csgs_graph *g, const int32_t *rows, int3
     const unsigned place = (unsigned)(place_want < ADJ_PLACE_GRID ? place_want : ADJ_PLACE_GRID);
     const dim3 grid(mark + (unsigned)(rem.blocks + nxt.blocks), 1, nz);
     if (reuse_offsets)
-        CSGS_LAUNCH(K_ADJ_MARK, adj_mark<true>, grid, dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.chunk_note, w.adj_cnt, w.stage_w,
+        CSGS_LAUNCH(K_ADJ_MARK, adj_mark<true>, grid, dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.chunk_note, w.adj_cnt, w.stage,
                     w.stage_chunks, adj_rowptr, status, rem, nxt, is);
     else
-        CSGS_LAUNCH(K_ADJ_MARK, adj_mark<false>, grid, dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.chunk_note, w.adj_cnt, w.stage_w,
+        CSGS_LAUNCH(K_ADJ_MARK, adj_mark<false>, grid, dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.chunk_note, w.adj_cnt, w.stage,
                     w.stage_chunks, adj_rowptr, status, rem, nxt, is);
     CSGS_LAUNCH_CHECK();
     CSGS_LAUNCH(K_ADJ_PLACE, adj_place, dim3(place, 1, nz), dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.chunk_note, w.adj_cnt,
-                w.stage_w, w.stage_chunks, adj_rowptr, adj_col, adj_val, adj_cap, adj_nnz, status, is);
+                w.stage, w.stage_chunks, adj_rowptr, adj_col, adj_val, adj_cap, adj_nnz, status, is);
     CSGS_LAUNCH_CHECK();
     return CSGS_OK;
 }

@@ -127,3 +127,49 @@ def test_sampled_adjacency_sizes(dev, n_nodes, degree, rows):
         np.testing.assert_array_equal(ac[:want.adj_nnz].cpu().numpy(), want.adj_col)
         chain.assert_close(av[:want.adj_nnz].cpu().numpy(), want.adj_val, chain.P_RTOL, 0.0, "adj_val")
         assert int(torch.count_nonzero(ac[want.adj_nnz:]).item()) == 0, "wrote past the last kept edge"
+
+
+# The weight scan's hand-over: local ranges that begin and end inside tiles of 1024 ids (one tile, many, the most it
+# takes and one more), a tile's sums split over several blocks, weights too large for a handed-over entry (2^54; four rows
+# whose norm is one edge's), more edges than it takes (8 Mi), and hardly any edge; by every form of the scan
+@pytest.mark.parametrize("n_nodes,degree,n_rows,lo,hi,skew", [
+    (6000, 60, 5000, 1000, 2050, 2.0),         # three tiles, blocks of several shares each
+    (6000, 60, 5000, 1023, 1025, 8.0), (6000, 1.5, 4, 0, 6000, 1.0), (700, 0.01, 700, 5, 690, 1.0),
+    (400_000, 3, 60_000, 1, 327_681, 2.0), (400_000, 3, 60_000, 1023, 327_681, 2.0),   # 321 and 320 tiles
+    (70_000, 130, 70_000, 511, 30_001, 2.0),
+])
+def test_weight_scan_hand_over(dev, n_nodes, degree, n_rows, lo, hi, skew):
+    from paper_2101_07706_amd import csgs, pipeline
+    rng = np.random.default_rng(n_nodes + hi)
+    deg = rng.poisson(degree, n_nodes)
+    rowptr = np.zeros(n_nodes + 1, np.int64)
+    np.cumsum(deg, out=rowptr[1:])
+    col = np.where(rng.random(int(rowptr[-1])) < 0.5, rng.integers(0, n_nodes, int(rowptr[-1])), rng.integers(lo, hi, int(rowptr[-1])))
+    order = np.argsort(np.repeat(np.arange(n_nodes, dtype=np.int64), deg) * n_nodes + col, kind="stable")
+    val = rng.uniform(0.01, 1.0, len(col)).astype(np.float32)
+    if n_rows == 4:
+        val[::2] = 33.0
+    bounds = np.array(sorted({0, lo, hi, n_nodes}), np.int32)
+    g = synth.Graph(n_nodes, rowptr, col[order].astype(np.int32), val, bounds, int(np.flatnonzero(bounds == lo)[0]))
+    S = rng.permutation(n_nodes)[:n_rows].astype(np.int32)
+    if n_rows == 4:
+        S = np.flatnonzero(deg == 1)[:4].astype(np.int32)
+    g.rownorm2_max = max(float(np.square(val[rowptr[i]:rowptr[i + 1]], dtype=np.float64).sum()) for i in S) * 1.001
+    assert (g.local_lo, g.local_hi) == (lo, hi)
+    dg = pipeline.DeviceGraph(g, dev)
+    print(f"[hand-over] {n_rows} rows, {int(deg[S].sum())} edges, local [{lo}, {hi})", flush=True)
+    want = oracle.build_probs(g, S, skew)
+    if n_rows == 4:
+        assert int(want.cand_w.max()) >= 1 << 54, "no weight beyond an entry of the hand-over"
+    for mode in (0, 1, 2):
+        ws = pipeline.Workspace(n_nodes, n_rows, 1, max(g.nnz, 1), dev, scan_mode=mode)
+        lb = pipeline.LayerBuffers(n_rows, 1, n_nodes, 1, 1, dev)
+        for again in range(2):
+            csgs.csgs_build_probs(dg.c, torch.from_numpy(S).to(dev), skew, lb.cand_id, lb.cand_w, lb.cdf, None, lb.stats, ws.desc, lb.status)
+        torch.cuda.synchronize()
+        n_c = len(want.cand_id)
+        assert int(lb.stats_host().n_cand) == n_c and int(lb.status.item()) == (0 if n_c else csgs.ST_EMPTY_CANDIDATES)
+        np.testing.assert_array_equal(lb.cand_id[:n_c].cpu().numpy(), want.cand_id)
+        np.testing.assert_array_equal(lb.cand_w[:n_c].cpu().numpy().view(np.uint64), want.cand_w)
+        np.testing.assert_array_equal(lb.cdf[:n_c].cpu().numpy().view(np.uint64), want.cdf)
+        assert int(torch.count_nonzero(ws.buf[:chain.csgs_clean_words(n_nodes)]).item()) == 0, "workspace not restored"
