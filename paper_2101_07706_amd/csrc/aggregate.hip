@@ -17,12 +17,10 @@
 namespace csgs {
 
 
-// Block b of the grid: row block b / slots (four tiles of tr consecutive output rows, one per wavefront) and
-// feature slice b % slots (G * V features; slots = the slice count rounded up to a multiple of 8 when there is more
-// than one slice, blocks beyond the slice count leave at once).  The hardware deals consecutive blocks
-// round-robin to the 8 XCDs, so all blocks of slice s run on XCD s mod 8: that XCD's L2 sees only slice s of the
-// gathered table, an eighth of it for rows of 1 KB, and a row that several output rows refer to is fetched
-// from memory once.
+// Block b of the grid: row block b / n_slices (four tiles of tr consecutive output rows, one per wavefront) and
+// feature slice b % n_slices (G * V features).  The hardware deals consecutive blocks round-robin to the 8 XCDs, so with 2, 4
+// or 8 slices all blocks of slice s run on XCDs s, s + n_slices, ...: such an XCD's L2 sees only slice s of the gathered
+// table, a quarter of it for rows of 1 KB, and a row that several output rows refer to is fetched from memory less often.
 template <typename T, int V, int G, bool RELU>
 __global__ __launch_bounds__(AGG_BLOCK) void aggregate_k(const int32_t *__restrict__ adj_rowptr,
                                                          const int32_t *__restrict__ adj_col,
@@ -34,13 +32,12 @@ __global__ __launch_bounds__(AGG_BLOCK) void aggregate_k(const int32_t *__restri
                                                          const int32_t *__restrict__ src_row, int32_t F,
                                                          float *__restrict__ Z, int64_t ldz,
                                                          const float *__restrict__ mask, int64_t ldm,
-                                                         int32_t n_slices, int32_t slots, int32_t tr, CompStride cs)
+                                                         int32_t n_slices, int32_t tr, CompStride cs)
 {
     __shared__ WaveStage<tile_rows(G)> stage[AGG_WAVES];
     __shared__ double heads[AGG_WAVES][WAVE * V], carries[AGG_WAVES][2 * G * V];
-    const int32_t slice = (int32_t)(blockIdx.x % (unsigned)slots);
-    if (slice >= n_slices) return;
-    const int64_t block_row0 = (int64_t)(blockIdx.x / (unsigned)slots) * (AGG_WAVES * tr);
+    const int32_t slice = (int32_t)(blockIdx.x % (unsigned)n_slices);
+    const int64_t block_row0 = (int64_t)(blockIdx.x / (unsigned)n_slices) * (AGG_WAVES * tr);
     adj_rowptr = inst_ptr(adj_rowptr, cs.adj); adj_col = inst_ptr(adj_col, cs.adj); adj_val = inst_ptr(adj_val, cs.adj);
     nS_dev = inst_ptr(nS_dev, cs.adj); n_cols_p = inst_ptr(n_cols_p, cs.adj); src_row = inst_ptr(src_row, cs.adj);
     Xl = inst_ptr(Xl, cs.x); Xr = inst_ptr(Xr, cs.xr); Z = inst_ptr(Z, cs.out);
@@ -70,7 +67,6 @@ static int launch_agg(const int32_t *rp, const int32_t *col, const float *val, i
                       const float *mask, int64_t ldm, int kid, hipStream_t st, const CompInst &ci = CompInst{})
 {
     const int64_t n_slices = (F + G * V - 1) / (G * V);
-    const int64_t slots = n_slices > 1 ? (n_slices + 7) / 8 * 8 : 1;
     // Rows per wavefront.  A full tile (8 rows per lane group) shares the cost of its set-up among the most rows, but a
     // launch for one mini-batch then has too few wavefronts: each walks through its tile's edges alone.  Tiles are
     // halved until the launch has 512 blocks, two per compute unit (us per launch, full / this rule, one mini-batch:
@@ -82,26 +78,29 @@ static int launch_agg(const int32_t *rp, const int32_t *col, const float *val, i
     auto blocks_of = [&](int r) { return ((int64_t)nS + AGG_WAVES * r - 1) / (AGG_WAVES * r); };
     while (tr > tr_min && blocks_of(tr) * n_slices * ci.n < 512) tr >>= 1;
     const int64_t row_blocks = blocks_of(tr);
-    if (row_blocks * slots > 0x7FFFFFFFll) return CSGS_EUNSUPPORTED;
-    const dim3 grid((unsigned)(row_blocks * slots), 1, (unsigned)ci.n);
+    if (row_blocks * n_slices > 0x7FFFFFFFll) return CSGS_EUNSUPPORTED;
+    const dim3 grid((unsigned)(row_blocks * n_slices), 1, (unsigned)ci.n);
 #define CSGS_AGG_LAUNCH(RELU)                                                                                                     \
     CSGS_LAUNCH_ID(kid, (aggregate_k<T, V, G, RELU>), grid, dim3(AGG_BLOCK), st, rp, col, val, nS, nsd, ncp, (const T *)Xl, ldl, rl, \
-                   (const T *)Xr, ldr, rr, src_row, F, Z, ldz, mask, ldm, (int32_t)n_slices, (int32_t)slots, (int32_t)tr, ci.cs)
+                   (const T *)Xr, ldr, rr, src_row, F, Z, ldz, mask, ldm, (int32_t)n_slices, (int32_t)tr, ci.cs)
     if (relu) CSGS_AGG_LAUNCH(true); else CSGS_AGG_LAUNCH(false);
 #undef CSGS_AGG_LAUNCH
     CSGS_LAUNCH_CHECK();
     return CSGS_OK;
 }
 
-// Lanes per row and slice.  Rows of 1 KB and more are cut into (about) eight slices, one per XCD; shorter rows
-// are taken whole by the smallest group of lanes that covers them.
+// Lanes per row and slice.  Rows of 1 KB and more are cut into (about) four slices; shorter rows are taken whole by the
+// smallest group of lanes that covers them.  Eight slices, one per XCD, keep more of the table in the L2s but stage every edge
+// eight times and end a row every few steps, and the kernel is bound by vector instructions where rows are many (us, eight /
+// four / two slices, F = 256: 83 K rows of 21 kept edges 228 / 200 / 207, 131 K of 22 353 / 305 / 321, 2048 of 26 22 / 19 /
+// 18, 7.3 K of 2.9 17 / 14 / 16, eight of those 51 / 53 / 51).
 template <typename T, int V>
 static int pick_group(const int32_t *rp, const int32_t *col, const float *val, int32_t nS, const int32_t *nsd, const int32_t *ncp, const void *Xl,
                       int64_t ldl, int64_t rl, const void *Xr, int64_t ldr, int64_t rr, const int32_t *src_row, int32_t F, int relu, float *Z, int64_t ldz,
                       const float *mask, int64_t ldm, int kid, hipStream_t st, const CompInst &ci = CompInst{})
 {
     const int64_t vecs = (F + V - 1) / V;
-    const int64_t want = (int64_t)F * (int64_t)sizeof(T) >= 1024 ? (vecs + 7) / 8 : vecs;
+    const int64_t want = (int64_t)F * (int64_t)sizeof(T) >= 1024 ? (vecs + 3) / 4 : vecs;
 #define CSGS_AGG_G(GG) launch_agg<T, V, GG>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci)
     if (want <= 4) return CSGS_AGG_G(4);
     if (want <= 8) return CSGS_AGG_G(8);

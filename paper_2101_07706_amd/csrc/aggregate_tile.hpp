@@ -73,7 +73,12 @@ __device__ inline Vec<8> load_row<uint16_t, 8>(const uint16_t *p)
                    __uint_as_float(v.w << 16), __uint_as_float(v.w & 0xFFFF0000u)}};
 }
 
-constexpr int LONG_ROW = 256;   // rows with more kept edges than this are taken by the whole block, after its tiles
+// Rows with more kept edges than this are taken by the whole block, after its tiles.  A wavefront with one or two lane groups
+// walks through a long row nearly alone (us, 256 everywhere / this: F = 100 bf16, 7283 rows, 32 lanes a row, 19 / 15; eight
+// of those 32 / 25; F = 602, 2048 rows of 26 edges, 64 lanes, 40 / 35; layers in one kernel 117 + 194 + 80 / 104 + 182 + 71);
+// half of that again is level.
+template <int G>
+constexpr int long_row() { return G >= 64 ? 64 : (G >= 32 ? 128 : 256); }
 template <int V>
 constexpr int unr() { return V >= 8 ? 2 : 4; }   // gathered row pieces asked for at a time per lane (and as many again before those are used): 64 bytes
 constexpr int AGG_BLOCK = 256;  // threads per block.  Small blocks on purpose: beside kernels of other streams a 1024-thread
@@ -85,59 +90,39 @@ constexpr int POOL = 256;       // edges a wavefront stages at a time
 // the edges has ended) go here: zeros, so that they add 0 * 0 without a test.  At least 64 lanes x 8 floats.
 static __device__ __align__(256) uint32_t g_zero_row[512];
 
-// Resolves edge e to (source row pointer, weight); a null pointer marks an edge that must not be read.
-template <typename T>
-__device__ inline void resolve_edge(int32_t e, const int32_t *__restrict__ adj_col, const float *__restrict__ adj_val,
-                                    int64_t n_cols, const int32_t *__restrict__ src_row, const T *__restrict__ Xl,
-                                    int64_t ldl, int64_t rows_l, const T *__restrict__ Xr, int64_t ldr, int64_t rows_r,
-                                    const T **src, float *w)
+// The gathered value in double, after ReLU.  The maximum is taken in double: a widened value needs no separate
+// instruction that makes it canonical first.
+template <bool RELU>
+__device__ inline double widen(float x)
 {
-    *src = nullptr;
-    *w = 0.f;
-    const int32_t c = adj_col[e];
-    const float val = adj_val[e];   // asked for together with the column: one load latency, not two
-    // a column or source row outside the tables contributes nothing (keeps every load in bounds)
-    if (c >= 0 && c < n_cols) {
-        const int64_t sr = src_row ? (int64_t)src_row[c] : (int64_t)c;
-        if (sr >= 0 && sr < rows_l) {
-            *src = Xl + sr * ldl;
-            *w = val;
-        } else if (sr < 0 && -1 - sr < rows_r) {
-            *src = Xr + (-1 - sr) * ldr;
-            *w = val;
-        }
-    }
+    const double d = (double)x;
+    return RELU ? fmax(d, 0.0) : d;
 }
 
 // acc += sum over the n_max staged edges (held one per lane, group base lane `gbase`) of w * x[f..f+V).
 // Loads are issued UNR at a time so that a row with many edges is not a chain of load latencies.
-template <typename T, int V, bool RELU>
-__device__ inline void accumulate_staged(double (&acc)[V], const T *src, float w, int gbase, int32_t n_here,
-                                         int32_t n_max, bool active, int32_t f)
+template <typename T, int V, int G, bool RELU>
+__device__ inline void accumulate_staged(double (&acc)[V], const T *src, float w, int gbase, int32_t n_max, bool active, int32_t f)
 {
-    constexpr int UNR = unr<V>();
+    constexpr int UNR = 64 / V < G ? (64 / V < 16 ? 64 / V : 16) : (G < 16 ? G : 16);   // 64 registers of gathered values
+    const uint64_t p = src ? (uint64_t)(uintptr_t)(src + (f - (lane_id() % G) * V)) : (uint64_t)(uintptr_t)g_zero_row;
+    const uint32_t lane_off = active ? (uint32_t)((lane_id() % G) * V * (int)sizeof(T)) : 0u;
+    if (!src) w = 0.f;
     for (int32_t j0 = 0; j0 < n_max; j0 += UNR) {
         Vec<V> x[UNR];
         float wj[UNR];
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
-            const int srcl = gbase + ((j0 + u) & (WAVE - 1));
-            const uint64_t pj = __shfl((uint64_t)(uintptr_t)src, srcl, WAVE);
+            // (no load under a condition: an edge that must not count reads the zero row with weight 0, and the compiler
+            // keeps exact count of the loads in flight; UNR divides G: no lane of another group is read)
+            const int srcl = gbase + j0 + u;
             wj[u] = __shfl(w, srcl, WAVE);
-            // (no load under a condition: what must not count reads the zero row with weight 0, and the compiler
-            // keeps exact count of the loads in flight)
-            const bool ok = active && (j0 + u) < n_here && pj != 0;
-            if (!ok) wj[u] = 0.f;
-            x[u] = load_row<T, V>(ok ? reinterpret_cast<const T *>((uintptr_t)pj) + f : reinterpret_cast<const T *>(g_zero_row));
+            x[u] = load_row<T, V>(reinterpret_cast<const T *>((uintptr_t)(__shfl(p, srcl, WAVE) + lane_off)));
         }
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
 #pragma unroll
-            for (int v = 0; v < V; ++v) {
-                float xv = x[u].x[v];
-                if (RELU) xv = xv > 0.f ? xv : 0.f;
-                acc[v] = fma((double)wj[u], (double)xv, acc[v]);
-            }
+            for (int v = 0; v < V; ++v) acc[v] = fma((double)wj[u], widen<RELU>(x[u].x[v]), acc[v]);
         }
     }
 }
@@ -171,6 +156,16 @@ __device__ inline void store_untracked(float *p, f32x2 v)
 __device__ inline void store_untracked(float *p, f32x4 v)
 {
     asm volatile("global_store_dwordx4 %0, %1, off" : : "v"(p), "v"(v) : "memory");
+}
+
+// r * ld for a row of a tile (r < 64).  A row ends in most steps of the streaming loop, for one lane group or another, and a
+// 64-bit product is four instructions at a quarter of the rate: the 24-bit one wherever the stride allows.
+__device__ inline int64_t row_offset(int r, int64_t ld)
+{
+    if (__builtin_expect((ld >> 24) == 0, 1)) return (int64_t)(uint32_t)__umul24((uint32_t)r, (uint32_t)ld);
+    int64_t o = (int64_t)r * ld;
+    asm volatile("" : "+v"(o));   // stays behind the (uniform) branch
+    return o;
 }
 
 template <int V, bool ZLDS = false>
@@ -247,7 +242,7 @@ __device__ inline bool aggregate_tile(WaveStage<tile_rows(G), PL> &st, int tr, d
     const int32_t rbeg = adj_rowptr[row_c], rend = adj_rowptr[row_c + 1];
     const bool in_call = lane < tr && row < nS;
     const int32_t full_len = in_call ? rend - rbeg : 0;
-    const bool is_long = full_len > LONG_ROW;
+    const bool is_long = full_len > long_row<G>();
     const int32_t len = (is_long || full_len < 0) ? 0 : full_len;
     const int32_t incl = wave_inclusive_scan(len);
     if (lane < tr) {
@@ -275,11 +270,12 @@ __device__ inline bool aggregate_tile(WaveStage<tile_rows(G), PL> &st, int tr, d
             store_row<V, ZLDS>(Z + (row0 - out_row0 + rr) * ldz + f, zero);
         }
     }
+    float *const z_tile = Z + (row0 - out_row0) * ldz + f;
+    const float *const m_tile = mask ? mask + row0 * ldm + f : nullptr;
     auto finish_row = [&](double (&sum)[V], int r) {   // rounds and stores row r of the tile
-        const int64_t out = row0 + r;
         if (active) {
-            if (mask) apply_mask<V>(sum, mask + out * ldm + f);
-            store_row<V, ZLDS>(Z + (out - out_row0) * ldz + f, sum);
+            if (mask) apply_mask<V>(sum, m_tile + row_offset(r, ldm));
+            store_row<V, ZLDS>(z_tile + row_offset(r, ldz), sum);
         }
     };
     double acc[V];
@@ -373,11 +369,7 @@ __device__ inline bool aggregate_tile(WaveStage<tile_rows(G), PL> &st, int tr, d
 #pragma unroll
             for (int u = 0; u < UNR; ++u) {
 #pragma unroll
-                for (int v = 0; v < V; ++v) {
-                    float xv = bt.x[u].x[v];
-                    if (RELU) xv = xv > 0.f ? xv : 0.f;
-                    acc[v] = fma((double)bt.w[u], (double)xv, acc[v]);
-                }
+                for (int v = 0; v < V; ++v) acc[v] = fma((double)bt.w[u], widen<RELU>(bt.x[u].x[v]), acc[v]);
                 if (bt.tg[u] & 1u) {         // the row ends here
                     if (in_head) {           // its beginning lies in an earlier share: leave my part for whoever holds that
 #pragma unroll
@@ -455,9 +447,11 @@ __device__ inline bool aggregate_tile(WaveStage<tile_rows(G), PL> &st, int tr, d
     return is_long;
 }
 
-// Rows with more than LONG_ROW kept edges (hubs among the rows of S): the whole block works on one such row at
+// Rows with more than long_row<G>() kept edges (hubs among the rows of S): the whole block works on one such row at
 // a time, each of its 256 / G lane groups takes a contiguous share of the row's edges, and the groups' sums are
-// added in group order through LDS (fixed order: the result does not depend on timing).
+// added in a fixed order by lane exchanges and through LDS (the result does not depend on timing).  The edges come one per
+// lane, their columns and values asked for two rounds ahead and the source rows one, so that a round of 256 edges waits for
+// the gathered rows only.
 template <typename T, int V, int G, bool RELU, bool ZLDS = false>
 __device__ inline void aggregate_long_rows(double *__restrict__ part /* LDS, AGG_BLOCK * V */, int tr, int64_t block_row0, int64_t out_row0, bool is_long, int32_t f,
                                            bool active, const int32_t *__restrict__ adj_rowptr, const int32_t *__restrict__ adj_col,
@@ -492,25 +486,41 @@ __device__ inline void aggregate_long_rows(double *__restrict__ part /* LDS, AGG
         double acc[V];
 #pragma unroll
         for (int v = 0; v < V; ++v) acc[v] = 0.0;
+        auto edge_at = [&](int32_t k0) { return ub + k0 + g < ue ? ub + k0 + g : end - 1; };   // the row's last edge stands in
+        auto col_ok = [&](int32_t c) { return c >= 0 && c < n_cols; };
+        int32_t c0 = adj_col[edge_at(0)], c1 = adj_col[edge_at(G)];
+        float w0 = adj_val[edge_at(0)], w1 = adj_val[edge_at(G)];
+        int32_t s0 = src_row ? src_row[col_ok(c0) ? c0 : 0] : c0;
         for (int32_t k0 = 0; k0 < share; k0 += G) {   // the same trip count for every group of the block
-            const int32_t e = ub + k0 + g;
-            const T *src = nullptr;
-            float w = 0.f;
-            if (e < ue) resolve_edge<T>(e, adj_col, adj_val, n_cols, src_row, Xl, ldl, rows_l, Xr, ldr, rows_r, &src, &w);
-            const int32_t left = ue - (ub + k0);
-            const int32_t n_here = left < 0 ? 0 : (left < G ? left : G);
-            const int32_t n_max = (share - k0) < G ? (share - k0) : G;
-            accumulate_staged<T, V, RELU>(acc, src, w, gbase, n_here, n_max, active, f);
+            const int32_t s1 = src_row ? src_row[col_ok(c1) ? c1 : 0] : c1;
+            const int32_t c2 = adj_col[edge_at(k0 + 2 * G)];
+            const float w2 = adj_val[edge_at(k0 + 2 * G)];
+            const T *src = nullptr;   // a column or source row outside the tables contributes nothing (keeps every load in bounds)
+            if (ub + k0 + g < ue && col_ok(c0)) {
+                if (s0 >= 0 && s0 < rows_l) src = Xl + (int64_t)s0 * ldl;
+                else if (s0 < 0 && -1 - (int64_t)s0 < rows_r) src = Xr + (-1 - (int64_t)s0) * ldr;
+            }
+            accumulate_staged<T, V, G, RELU>(acc, src, w0, gbase, (share - k0) < G ? (share - k0) : G, active, f);
+            c0 = c1; w0 = w1; s0 = s1;
+            c1 = c2; w1 = w2;
         }
-        __syncthreads();  // part[] of the previous row has been read
+        // the lane groups of a wavefront, then the four wavefronts
 #pragma unroll
-        for (int v = 0; v < V; ++v) part[tid * V + v] = acc[v];
+        for (int d = G; d < WAVE; d <<= 1)
+#pragma unroll
+            for (int v = 0; v < V; ++v) acc[v] += __shfl_xor(acc[v], d, WAVE);
+        __syncthreads();  // part[] of the previous row has been read
+        if (lane < G) {
+#pragma unroll
+            for (int v = 0; v < V; ++v) part[(wave * G + lane) * V + v] = acc[v];
+        }
         __syncthreads();
         if (tid < G && active) {
             double sum[V];
 #pragma unroll
-            for (int v = 0; v < V; ++v) sum[v] = 0.0;
-            for (int u = 0; u < UNITS; ++u) {
+            for (int v = 0; v < V; ++v) sum[v] = part[tid * V + v];
+#pragma unroll
+            for (int u = 1; u < AGG_WAVES; ++u) {
 #pragma unroll
                 for (int v = 0; v < V; ++v) sum[v] += part[(u * G + tid) * V + v];
             }

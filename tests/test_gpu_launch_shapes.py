@@ -53,6 +53,31 @@ def test_aggregate_rows_per_wavefront(dev, F, bf16, rows):
         assert bool(torch.isnan(Z[n:]).all()), f"{n} rows: wrote past the last row"
 
 
+# Rows around the lengths from which a block takes them together (64, 128 or 256 by the lanes per row) and around its rounds
+# of 256 edges, in 1, 2, 3 and 5 feature slices; columns outside the table; output rows closer and further apart than 2^24
+@pytest.mark.parametrize("F,bf16,ld", [(256, False, 0), (300, False, 0), (602, False, 0), (100, True, 0), (640, True, 0), (64, False, (1 << 24) + 8),
+                                       (64, False, (1 << 24) - 8)])
+def test_aggregate_long_rows(dev, F, bf16, ld):
+    from paper_2101_07706_amd import csgs
+    rng = np.random.default_rng(F + ld)
+    n_cols = 900
+    X = rng.standard_normal((n_cols, F)).astype(np.float32)
+    Xh = synth.to_bf16_bits(X) if bf16 else X
+    Xd = torch.from_numpy(Xh.view(np.int16) if bf16 else Xh).to(dev)
+    lens = np.array([64, 65, 0, 128, 129, 255, 256, 257, 1, 63, 511, 513, 5000])
+    print(f"[aggregate] long rows, F={F} bf16={bf16} ld={ld}", flush=True)
+    rowptr, col, val = _csr(rng, lens, n_cols)
+    out = rng.random(len(col)) < 0.1                             # edges that must not count
+    want = oracle.aggregate(rowptr, col, np.where(out, 0, val).astype(np.float32), Xh, relu_on_input=True)
+    col[out] = rng.choice([-1, n_cols, 2**31 - 1], int(out.sum()))
+    ld = ld or F
+    Z = torch.as_strided(torch.full((len(lens) * ld,), float("nan"), dtype=torch.float32, device=dev), (len(lens), F), (ld, 1))
+    t = lambda a: torch.from_numpy(a).to(dev)
+    csgs.csgs_aggregate(t(rowptr), t(col), t(val), None, Xd, None, None, True, Z)
+    torch.cuda.synchronize()
+    chain.assert_close(Z.cpu().numpy(), want, chain.RTOL, chain.ATOL, f"long rows F={F}")
+
+
 # Candidate counts at the ends of bitmap words, of a block's 16 words, and where the blocks (512, 16 words each) begin to take
 # more words and then more than 64 at a time; budgets from a few hits to every position drawn, several draws in a row on one
 # workspace (the position bitmap of one draw is cleared by the next)
