@@ -198,3 +198,34 @@ def test_weight_scan_hand_over(dev, n_nodes, degree, n_rows, lo, hi, skew):
         np.testing.assert_array_equal(lb.cand_w[:n_c].cpu().numpy().view(np.uint64), want.cand_w)
         np.testing.assert_array_equal(lb.cdf[:n_c].cpu().numpy().view(np.uint64), want.cdf)
         assert int(torch.count_nonzero(ws.buf[:chain.csgs_clean_words(n_nodes)]).item()) == 0, "workspace not restored"
+
+
+# Column counts around what one block of the transpose orders (16), what one takes of its prefix (2048) and several of those;
+# fewer columns on the device than the bound; columns around the 64 entries that one wavefront orders
+@pytest.mark.parametrize("bound,n_cols", [(15, 15), (17, 16), (17, 17), (2047, 2047), (2049, 2048), (2049, 2049), (10_300, 10_241), (9000, 100), (50, 0)])
+def test_aggregate_gradient_columns(dev, bound, n_cols):
+    from paper_2101_07706_amd import csgs
+    rng = np.random.default_rng(bound + n_cols)
+    nS, F = 700, 20
+    print(f"[aggregate grad] {n_cols} of {bound} columns", flush=True)
+    dense = rng.random((nS, n_cols)) < 2.0 / max(n_cols, 4)
+    for c, k in zip(rng.permutation(n_cols)[:5], (63, 64, 65, 257, 700)):
+        dense[:, c] = False
+        dense[rng.choice(nS, k, replace=False), c] = True
+    rows, col = np.nonzero(dense)
+    rp = np.zeros(nS + 1, np.int32)
+    np.cumsum(np.bincount(rows, minlength=nS), out=rp[1:])
+    val = rng.standard_normal(len(col)).astype(np.float32)
+    dZ, Hp = rng.standard_normal((nS, F)).astype(np.float32), rng.standard_normal((bound, F)).astype(np.float32)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+    cap = len(col) + 3
+    cold, vald = torch.zeros(cap, dtype=torch.int32, device=dev), torch.zeros(cap, dtype=torch.float32, device=dev)
+    cold[:len(col)], vald[:len(col)] = t(col.astype(np.int32)), t(val)
+    dH = torch.full((bound, F), float("nan"), dtype=torch.float32, device=dev)
+    nbytes = csgs.csgs_aggregate_grad_scratch_bytes(bound, cap)
+    scratch = torch.full((nbytes // 8 + 32,), -1, dtype=torch.int64, device=dev)
+    csgs.csgs_aggregate_grad(t(rp), cold, vald, torch.tensor([n_cols], dtype=torch.int32, device=dev), t(dZ), t(Hp), dH, scratch)
+    torch.cuda.synchronize()
+    want = oracle.aggregate_grad(rp, col.astype(np.int32), val, n_cols, dZ, Hp[:n_cols])
+    chain.assert_close(dH[:n_cols].cpu().numpy(), want, chain.RTOL, chain.ATOL, "dH_prev")
+    assert bool(torch.isnan(dH[n_cols:]).all()), "wrote past the last column"
