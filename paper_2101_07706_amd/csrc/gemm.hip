@@ -49,6 +49,8 @@ __global__ __launch_bounds__(256, (MODE == MODE_FWD && BM_ == 128 && BN == 64) ?
     constexpr int RT = BM_ / 64;  // 16-row MFMA tiles per wavefront: the four wavefronts are stacked along M
     static_assert(BM_ == 128 || BM_ == 64, "block tiles of 128 or 64 rows");
     constexpr bool A_KMAJOR = MODE != MODE_DW, B_KMAJOR = MODE == MODE_DZ;
+    constexpr bool A_BLOCKS = MODE == MODE_DW && V == 4;
+    static_assert(!A_BLOCKS || BM_ == 128, "one block of 4 x 4 per thread");
     __shared__ __attribute__((aligned(16))) float As[2][BM_ * LDS_STRIDE];
     // The B tile of the forward product's 128 x 64 blocks is swizzled instead of padded: 52-53 KB of LDS per block
     // instead of 54, which lets a third block onto a compute unit (the launch bound asks the compiler for the
@@ -91,13 +93,15 @@ __global__ __launch_bounds__(256, (MODE == MODE_FWD && BM_ == 128 && BN == 64) ?
     bool k_whole = false;   // of the chunk in the registers
     auto fetch = [&](int k0) {
         k_whole = k0 + BK <= k_end;
-        if (A_KMAJOR) fetch_kmajor<BM_, V, FULL>(A, lda, M_bound, k_end, m0, k0, tid, ra, oka);
+        if constexpr (A_KMAJOR) fetch_kmajor<BM_, V, FULL>(A, lda, M_bound, k_end, m0, k0, tid, ra, oka);
+        else if constexpr (A_BLOCKS) fetch_rmajor_blocks(A, lda, M_bound, k_end, m0, k0, tid, ra, oka);
         else fetch_rmajor<BM_, FULL>(A, lda, M_bound, k_end, m0, k0, tid, ra, oka);
         if (B_KMAJOR) fetch_kmajor<BN, V, FULL>(Bm, ldb, N, k_end, n0, k0, tid, rb, okb);
         else fetch_rmajor<BN, FULL>(Bm, ldb, N, k_end, n0, k0, tid, rb, okb);
     };
     auto stash = [&](int buf) {
-        stash_tile<BM_, A_KMAJOR, FULL>(As[buf], tid, ra, oka, a_whole && k_whole);
+        if constexpr (A_BLOCKS) stash_blocks(As[buf], tid, ra, oka, a_whole && k_whole);
+        else stash_tile<BM_, A_KMAJOR, FULL>(As[buf], tid, ra, oka, a_whole && k_whole);
         stash_tile<BN, B_KMAJOR, FULL, SWZ>(Bs[buf], tid, rb, okb, b_whole && k_whole);
     };
     if (n_chunks > 0) fetch(k_begin);
@@ -384,8 +388,12 @@ static int grad_w_launch(const float *Z, int64_t ldz, const float *G, int64_t ld
     dw_split(M, n_tiles, &parts, &ks);
     const dim3 grid((unsigned)(((n_tiles + 7) / 8) * 8), (unsigned)parts);
     float *none = nullptr;
-    CSGS_LAUNCH(K_GEMM_DW, (gemm_f32_k<32, MODE_DW, 1, false>), grid, dim3(256), st, Z, ldz, G, ldg, none, (int64_t)0,
-                parts_buf, K, Nout, M, M_dev, tn, n_tiles, ks, CompStride{0, 0, 0, 0});
+    if (widest(Z, ldz, K) == 4)
+        CSGS_LAUNCH(K_GEMM_DW, (gemm_f32_k<32, MODE_DW, 4, false>), grid, dim3(256), st, Z, ldz, G, ldg, none, (int64_t)0,
+                    parts_buf, K, Nout, M, M_dev, tn, n_tiles, ks, CompStride{0, 0, 0, 0});
+    else
+        CSGS_LAUNCH(K_GEMM_DW, (gemm_f32_k<32, MODE_DW, 1, false>), grid, dim3(256), st, Z, ldz, G, ldg, none, (int64_t)0,
+                    parts_buf, K, Nout, M, M_dev, tn, n_tiles, ks, CompStride{0, 0, 0, 0});
     CSGS_LAUNCH_CHECK();
     const int64_t count = (int64_t)K * Nout;
     CSGS_LAUNCH(K_GEMM_DW_REDUCE, gemm_reduce_parts, dim3((unsigned)((count + 255) / 256)), dim3(256), st,

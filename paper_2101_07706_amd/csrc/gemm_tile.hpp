@@ -103,6 +103,40 @@ __device__ inline void fetch_rmajor(const float *__restrict__ P, int64_t ld, int
     }
 }
 
+// The same tile of 128 rows where the rows come in whole aligned pieces of four (the host checks): a thread takes a block of
+// 4 r x 4 k as four 16-byte loads -- eight lanes side by side read 128 bytes -- and turns it round on the way to LDS: a
+// fifth of the loads and address arithmetic of the form above, beside which the MFMAs waited (dW, 512 x 512 from 4096 rows 63 ->
+// 55 us, 300 x 512 49 -> 43, 256 x 256 from 8192 34 -> 30).  Bit j of `ok` belongs to k + j.
+__device__ inline void fetch_rmajor_blocks(const float *__restrict__ P, int64_t ld, int R, int K, int64_t r0, int k0, int tid,
+                                           float4 (&reg)[4], uint32_t &ok)
+{
+    const int64_t gr = r0 + (tid >> 3) * 4;
+    const int gk = k0 + (tid & 7) * 4;
+    const bool r_ok = gr < R;
+    const float *col = P + (r_ok ? gr : (int64_t)R - 4);   // the nearest real piece stands in
+    ok = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const bool k_ok = gk + j < K;
+        reg[j] = *reinterpret_cast<const float4 *>(col + (int64_t)(k_ok ? gk + j : K - 1) * ld);
+        if (r_ok && k_ok) ok |= 1u << j;
+    }
+}
+__device__ inline void stash_blocks(float *S, int tid, const float4 (&reg)[4], uint32_t ok, bool whole)
+{
+    float4 t[4] = {reg[0], reg[1], reg[2], reg[3]};
+    if (!whole) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (!((ok >> j) & 1u)) t[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    float *p = &S[(tid >> 3) * 4 * LDS_STRIDE + (tid & 7) * 4];
+    *reinterpret_cast<float4 *>(p) = make_float4(t[0].x, t[1].x, t[2].x, t[3].x);
+    *reinterpret_cast<float4 *>(p + LDS_STRIDE) = make_float4(t[0].y, t[1].y, t[2].y, t[3].y);
+    *reinterpret_cast<float4 *>(p + 2 * LDS_STRIDE) = make_float4(t[0].z, t[1].z, t[2].z, t[3].z);
+    *reinterpret_cast<float4 *>(p + 3 * LDS_STRIDE) = make_float4(t[0].w, t[1].w, t[2].w, t[3].w);
+}
+
 // Registers -> LDS tile [ROWS][LDS_STRIDE], with the (r, k) of each group as the fetch above had it;
 // values whose bit in `ok` is clear become zeros.
 // SWZ: rows of 32 words without padding; the 16-byte column c of row r sits at column c ^ ((r >> 1) & 7), which

@@ -229,3 +229,24 @@ def test_aggregate_gradient_columns(dev, bound, n_cols):
     want = oracle.aggregate_grad(rp, col.astype(np.int32), val, n_cols, dZ, Hp[:n_cols])
     chain.assert_close(dH[:n_cols].cpu().numpy(), want, chain.RTOL, chain.ATOL, "dH_prev")
     assert bool(torch.isnan(dH[n_cols:]).all()), "wrote past the last column"
+
+
+# The weight gradient's two ways of loading Z: whole aligned pieces of four columns, or not (odd widths, strides, addresses);
+# rows and columns around its tiles (128 x 32) and chunks (32 rows), fewer rows on the device than the bound
+@pytest.mark.parametrize("M,m,K,N,pad", [(1, 1, 4, 1, 0), (31, 31, 124, 5, 0), (33, 20, 128, 32, 0), (1000, 970, 132, 33, 0), (4096, 4096, 300, 100, 0),
+                                         (64, 64, 260, 64, 4), (500, 499, 128, 40, 1), (500, 500, 130, 31, 2), (40, 0, 8, 8, 0)])
+def test_weight_gradient_loads(dev, M, m, K, N, pad):
+    from paper_2101_07706_amd import csgs
+    rng = np.random.default_rng(M + K + N)
+    print(f"[dW] {m} of {M} rows, {K} x {N}, pad {pad}", flush=True)
+    Z, G = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((M, N)).astype(np.float32)
+    Zd = torch.full((M, K + pad), float("nan"), dtype=torch.float32, device=dev)[:, :K]
+    Zd.copy_(torch.from_numpy(Z))
+    Gd = torch.from_numpy(G).to(dev)
+    Zd[m:], Gd[m:] = float("nan"), float("inf")                  # rows beyond the count are never summed
+    dW = torch.zeros((K, N), dtype=torch.float32, device=dev)
+    scratch = torch.zeros(csgs.csgs_layer_gemm_grad_w_scratch_bytes(M, K, N) // 8 + 32, dtype=torch.int64, device=dev)
+    csgs.csgs_layer_gemm_grad_w(Zd, Gd, dW, scratch, M_dev=torch.tensor([m], dtype=torch.int32, device=dev))
+    torch.cuda.synchronize()
+    want = oracle.layer_gemm_grad_w(Z[:m], G[:m]) if m else np.zeros((K, N), np.float32)
+    chain.assert_close(dW.cpu().numpy(), want, chain.RTOL, chain.ATOL, "dW")
