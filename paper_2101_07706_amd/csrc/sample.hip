@@ -49,8 +49,11 @@ __device__ inline uint64_t philox_word(uint32_t c0, uint32_t c1, uint32_t c2, ui
     return (uint64_t)c0 | ((uint64_t)c1 << 32);
 }
 
-constexpr int DRAW_BLOCK = 256;
-constexpr int TOP = 2048;  // CDF samples staged in LDS per block (16 KB)
+// Blocks of two wavefronts and few samples: the search is bound by the scattered loads of one compute unit, and every sample
+// is a line of its own (us for one mini-batch of 8192 draws from 163 K candidates / eight of them / 131 K draws from 650 K: 256
+// threads and 2048 samples 10.0 / 16.4 / 26, 128 and 256 7.2 / 15.4 / 24, 64 and 512 8.4 / 16.3 / 26, 1024 and 2048 19 / 24 / 26).
+constexpr int DRAW_BLOCK = 128;
+constexpr int TOP = 256;   // CDF samples staged in LDS per block
 
 __global__ __launch_bounds__(DRAW_BLOCK) void draw(const uint64_t *__restrict__ cdf,
                                                    const csgs_prob_stats *__restrict__ stats, int64_t cand_cap,
