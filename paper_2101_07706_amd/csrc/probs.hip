@@ -280,7 +280,7 @@ __device__ inline void sum_handed_over(unsigned long long *acc, const Stage &stg
     uint16_t beg, end;
     auto extents = [&](int64_t cb) {   // where my chunk's group lies in its piece
         const int64_t c = cb + lane;
-        const uint16_t *p = off + (c < n_chunks ? c : n_chunks - 1) * SUB_STRIDE;
+        const uint16_t *p = off + (c < n_chunks ? c : 0) * SUB_STRIDE;   // (a share may hold no chunk at all)
         beg = p[0];
         end = p[1];
     };

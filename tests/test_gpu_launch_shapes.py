@@ -186,21 +186,24 @@ def test_weight_scan_hand_over(dev, n_nodes, degree, n_rows, lo, hi, skew):
     assert (g.local_lo, g.local_hi) == (lo, hi)
     dg = pipeline.DeviceGraph(g, dev)
     print(f"[hand-over] {n_rows} rows, {int(deg[S].sum())} edges, local [{lo}, {hi})", flush=True)
-    want = oracle.build_probs(g, S, skew)
+    S = S[np.argsort(deg[S] == 0, kind="stable")]   # rows with edges first
+    few = max(1, min(n_rows // 2, 3))   # so few rows on the device that most shares of a tile hold no chunk
+    wants = [(n_rows, oracle.build_probs(g, S, skew)), (few, oracle.build_probs(g, S[:few], skew))]
     if n_rows == 4:
-        assert int(want.cand_w.max()) >= 1 << 54, "no weight beyond an entry of the hand-over"
+        assert int(wants[0][1].cand_w.max()) >= 1 << 54, "no weight beyond an entry of the hand-over"
     for mode in (0, 1, 2):
         ws = pipeline.Workspace(n_nodes, n_rows, 1, max(g.nnz, 1), dev, scan_mode=mode)
-        lb = pipeline.LayerBuffers(n_rows, 1, n_nodes, 1, 1, dev)
-        for again in range(2):
-            csgs.csgs_build_probs(dg.c, torch.from_numpy(S).to(dev), skew, lb.cand_id, lb.cand_w, lb.cdf, None, lb.stats, ws.desc, lb.status)
-        torch.cuda.synchronize()
-        n_c = len(want.cand_id)
-        assert int(lb.stats_host().n_cand) == n_c and int(lb.status.item()) == (0 if n_c else csgs.ST_EMPTY_CANDIDATES)
-        np.testing.assert_array_equal(lb.cand_id[:n_c].cpu().numpy(), want.cand_id)
-        np.testing.assert_array_equal(lb.cand_w[:n_c].cpu().numpy().view(np.uint64), want.cand_w)
-        np.testing.assert_array_equal(lb.cdf[:n_c].cpu().numpy().view(np.uint64), want.cdf)
-        assert int(torch.count_nonzero(ws.buf[:chain.csgs_clean_words(n_nodes)]).item()) == 0, "workspace not restored"
+        for rows, want in wants + wants[:1]:
+            lb = pipeline.LayerBuffers(n_rows, 1, n_nodes, 1, 1, dev)
+            csgs.csgs_build_probs(dg.c, torch.from_numpy(S).to(dev), skew, lb.cand_id, lb.cand_w, lb.cdf, None, lb.stats, ws.desc, lb.status,
+                                  nS_dev=torch.tensor([rows], dtype=torch.int32, device=dev))
+            torch.cuda.synchronize()
+            n_c = len(want.cand_id)
+            assert int(lb.stats_host().n_cand) == n_c and int(lb.status.item()) == (0 if n_c else csgs.ST_EMPTY_CANDIDATES)
+            np.testing.assert_array_equal(lb.cand_id[:n_c].cpu().numpy(), want.cand_id)
+            np.testing.assert_array_equal(lb.cand_w[:n_c].cpu().numpy().view(np.uint64), want.cand_w)
+            np.testing.assert_array_equal(lb.cdf[:n_c].cpu().numpy().view(np.uint64), want.cdf)
+            assert int(torch.count_nonzero(ws.buf[:chain.csgs_clean_words(n_nodes)]).item()) == 0, "workspace not restored"
 
 
 # Column counts around what one block of the transpose orders (16), what one takes of its prefix (2048) and several of those;
