@@ -1,13 +1,11 @@
 // csgs_aggregate: Z = P~ sigma?(X)  (Section 3, Eq. 1 with the sampled operator P~).
 //
-// A group of G lanes (16, 32 or 64) owns one output row and spreads over the feature dimension
-// with V-element vector loads, so every gathered source row is read as one contiguous burst.
-// The row's edges (column, value, resolved source pointer) are fetched G at a time, one edge per
-// lane, and broadcast lane-to-lane.  Products are accumulated in double, in ascending edge order,
-// and rounded to float once: sampled rows carry 1/p_j discounts of 10^2..10^3, so near-cancelling
-// outputs would lose the 1e-5 absolute tolerance with a float accumulator; the kernel is bound
-// by memory traffic, so the wider adds are free.  Rows with many kept edges (hubs) are taken by
-// all wavefronts of the block that owns them, after its ordinary rows.
+// A wavefront takes a tile of output rows, resolves their edges into LDS, and its groups of G lanes (4 .. 64, spread over the
+// features of a slice with V-element vector loads) stream through equal shares of them.  Products are accumulated in double,
+// in ascending edge order, and rounded to float once: sampled rows carry 1/p_j discounts of 10^2..10^3, so near-cancelling
+// outputs would lose the 1e-5 absolute tolerance with a float accumulator.  Bound by vector instructions where rows are
+// many (a widening and a double add per element, the staging per slice, a row's end in most steps), by latency where they are
+// few.  Rows with many kept edges (hubs) are taken by all wavefronts of the block that owns them, after its ordinary rows.
 //
 // Also here: csgs_gather_rows (staging of the sampled remote feature rows) and csgs_aggregate_grad
 // (dH_prev = (P~^T dZ) .* [H_prev > 0]: the same kernel on a per-call transpose of P~).
