@@ -144,7 +144,9 @@ __device__ inline void apply_mask(double (&acc)[V], const float *__restrict__ m)
 // compiler waits for everything before it uses any loaded value, so a row's store inside a loop that keeps the next
 // loads in flight would drain them at every turn.  A store it does not see leaves its count of the loads exact, and
 // the extra outstanding operation only makes a wait for "all but the last n" longer, never shorter.  Only for memory
-// that the kernel itself never reads again.
+// that the kernel itself never reads again.  A store of more than 64 bits reads its data registers late: a vector
+// instruction may write them two wait states after it at the earliest, and the compiler, which puts these in after its
+// own stores, does not look inside an asm statement, hence the s_nop behind the 16-byte form.
 __device__ inline void store_untracked(float *p, float v)
 {
     asm volatile("global_store_dword %0, %1, off" : : "v"(p), "v"(v) : "memory");
@@ -155,7 +157,7 @@ __device__ inline void store_untracked(float *p, f32x2 v)
 }
 __device__ inline void store_untracked(float *p, f32x4 v)
 {
-    asm volatile("global_store_dwordx4 %0, %1, off" : : "v"(p), "v"(v) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
 }
 
 // r * ld for a row of a tile (r < 64).  A row ends in most steps of the streaming loop, for one lane group or another, and a

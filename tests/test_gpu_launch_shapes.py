@@ -31,7 +31,8 @@ def _csr(rng, lens, n_cols):
 # 2, 4, ..., 64 rows: 512 blocks of 4 wavefronts over all feature slices
 @pytest.mark.parametrize("F,bf16,rows", [(256, False, (1, 9, 2016, 2017, 4033, 8065, 16128, 16129)), (64, False, (1, 33, 16352, 16353, 65409)),
                                          (128, False, (7, 4088, 4089, 65409)), (100, True, (3, 8176, 8177, 32705)),
-                                         (75, False, (1, 2045, 4089, 16369))])
+                                         (75, False, (1, 2045, 4089, 16369)),
+                                         (264, True, (1, 5, 8176, 8177, 16352, 16353)), (504, True, (700, 16353))])
 def test_aggregate_rows_per_wavefront(dev, F, bf16, rows):
     from paper_2101_07706_amd import csgs
     rng = np.random.default_rng(31 * F)
@@ -55,7 +56,8 @@ def test_aggregate_rows_per_wavefront(dev, F, bf16, rows):
 
 # Rows around the lengths from which a block takes them together (64, 128 or 256 by the lanes per row) and around its rounds
 # of 256 edges, in 1, 2, 3 and 5 feature slices; columns outside the table; output rows closer and further apart than 2^24
-@pytest.mark.parametrize("F,bf16,ld", [(256, False, 0), (300, False, 0), (602, False, 0), (100, True, 0), (640, True, 0), (64, False, (1 << 24) + 8),
+@pytest.mark.parametrize("F,bf16,ld", [(256, False, 0), (300, False, 0), (602, False, 0), (100, True, 0), (640, True, 0), (264, True, 0), (504, True, 0),
+                                       (64, False, (1 << 24) + 8),
                                        (64, False, (1 << 24) - 8)])
 def test_aggregate_long_rows(dev, F, bf16, ld):
     from paper_2101_07706_amd import csgs

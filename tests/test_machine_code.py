@@ -1,0 +1,112 @@
+"""What the built library's own gfx950 code must keep to where the compiler does not see an instruction (inline assembly)."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+from paper_2101_07706_amd import build
+
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+WIDE_STORE = re.compile(r"(global|flat|scratch|buffer)_store_(dwordx[34]|b96|b128)$")
+REG = re.compile(r"^([va])(?:(\d+)|\[(\d+):(\d+)\])$")
+
+
+def _code_objects():
+    """The gfx950 ELF images of the bundles inside the shared library."""
+    with open(build.LIB, "rb") as f:
+        blob = f.read()
+    magic = b"__CLANG_OFFLOAD_BUNDLE__"
+    at, out = blob.find(magic), []
+    while at >= 0:
+        p = at + len(magic)
+        n, = struct.unpack_from("<Q", blob, p)
+        p += 8
+        for _ in range(n):
+            off, size, id_len = struct.unpack_from("<QQQ", blob, p)
+            p += 24
+            if b"gfx950" in blob[p:p + id_len] and size:
+                out.append(blob[at + off:at + off + size])
+            p += id_len
+        at = blob.find(magic, at + 1)
+    return out
+
+
+def _regs(operand):
+    m = REG.match(operand.strip())
+    if not m:
+        return set()
+    lo = int(m.group(2) or m.group(3))
+    return {(m.group(1), r) for r in range(lo, int(m.group(2) or m.group(4)) + 1)}
+
+
+def _functions(obj_path):
+    """(name, [(address, mnemonic, operands, branch target or None)]) of every function."""
+    text = subprocess.run([OBJDUMP, "-d", "--mcpu=gfx950", obj_path], stdout=subprocess.PIPE, text=True, check=True).stdout
+    name, ins = None, []
+    for line in text.splitlines():
+        head = re.match(r"^([0-9a-f]+) <(.*)>:$", line)
+        if head:
+            if ins:
+                yield name, ins
+            name, start, ins = head.group(2), int(head.group(1), 16), []
+            continue
+        body, _, tail = line.partition("//")
+        f = body.split(None, 1)
+        addr = re.match(r"\s*([0-9A-Fa-f]+):", tail)
+        if not f or not addr:
+            continue
+        target = re.search(r"<.*\+0x([0-9a-f]+)>\s*$", tail)
+        ins.append((int(addr.group(1), 16), f[0], f[1] if len(f) > 1 else "", start + int(target.group(1), 16) if target else None))
+    if ins:
+        yield name, ins
+
+
+def _overwritten(ins, i, data):
+    """The instruction within two wait states of instruction i that writes `data`, on any way through the code."""
+    at = {a: k for k, (a, _, _, _) in enumerate(ins)}
+    todo = [(i + 1, 0)]
+    while todo:
+        k, passed = todo.pop()
+        if k >= len(ins) or passed >= 2:
+            continue
+        _, op, args, target = ins[k]
+        if op.startswith("v_") and _regs(args.split(",")[0]) & data:
+            return f"{op} {args.strip()}"
+        if op == "s_endpgm":
+            continue
+        step = int(args.split()[0], 0) + 1 if op == "s_nop" else 1
+        if op.startswith(("s_branch", "s_cbranch")) and target in at:
+            todo.append((at[target], passed + step))
+        if op != "s_branch":
+            todo.append((k + 1, passed + step))
+    return None
+
+
+# A store of more than 64 bits reads its data registers late: a vector instruction may write them two wait states after it
+# at the earliest.  The compiler sees to that for its own stores, not for those written as inline assembly.
+def test_wide_stores_keep_their_data(tmp_path):
+    if not os.path.exists(build.LIB):
+        build.build_library()
+    if not os.path.exists(OBJDUMP):
+        pytest.skip("no llvm-objdump")
+    objects = _code_objects()
+    assert len(objects) == len(build.SOURCES)
+    n_stores, bad = 0, []
+    for j, obj in enumerate(objects):
+        path = tmp_path / f"{j}.elf"
+        path.write_bytes(obj)
+        for name, ins in _functions(str(path)):
+            for i, (addr, op, args, _) in enumerate(ins):
+                if not WIDE_STORE.match(op):
+                    continue
+                n_stores += 1
+                operands = args.split(",")
+                data = _regs(operands[0 if op.startswith("buffer") else 1])
+                assert data, f"{name}: {op} {args}"
+                hit = _overwritten(ins, i, data)
+                if hit:
+                    bad.append(f"{name} {addr:#x}: {op} {args.strip()} -> {hit}")
+    assert n_stores > 100
+    assert not bad, f"{len(bad)} stores lose their data registers:\n" + "\n".join(bad[:20])
