@@ -63,8 +63,8 @@ def _functions(obj_path):
         yield name, ins
 
 
-def _overwritten(ins, i, data):
-    """The instruction within two wait states of instruction i that writes `data`, on any way through the code."""
+def _within_two_wait_states(ins, i, is_hit):
+    """The first instruction less than two wait states after instruction i that is_hit(op, args), on any way through the code."""
     at = {a: k for k, (a, _, _, _) in enumerate(ins)}
     todo = [(i + 1, 0)]
     while todo:
@@ -72,7 +72,7 @@ def _overwritten(ins, i, data):
         if k >= len(ins) or passed >= 2:
             continue
         _, op, args, target = ins[k]
-        if op.startswith("v_") and _regs(args.split(",")[0]) & data:
+        if is_hit(op, args):
             return f"{op} {args.strip()}"
         if op == "s_endpgm":
             continue
@@ -84,29 +84,63 @@ def _overwritten(ins, i, data):
     return None
 
 
-# A store of more than 64 bits reads its data registers late: a vector instruction may write them two wait states after it
-# at the earliest.  The compiler sees to that for its own stores, not for those written as inline assembly.
-def test_wide_stores_keep_their_data(tmp_path):
+@pytest.fixture(scope="module")
+def functions(tmp_path_factory):
     if not os.path.exists(build.LIB):
         build.build_library()
     if not os.path.exists(OBJDUMP):
         pytest.skip("no llvm-objdump")
     objects = _code_objects()
     assert len(objects) == len(build.SOURCES)
-    n_stores, bad = 0, []
+    out = []
     for j, obj in enumerate(objects):
-        path = tmp_path / f"{j}.elf"
+        path = tmp_path_factory.mktemp("code") / f"{j}.elf"
         path.write_bytes(obj)
-        for name, ins in _functions(str(path)):
-            for i, (addr, op, args, _) in enumerate(ins):
-                if not WIDE_STORE.match(op):
-                    continue
-                n_stores += 1
-                operands = args.split(",")
-                data = _regs(operands[0 if op.startswith("buffer") else 1])
-                assert data, f"{name}: {op} {args}"
-                hit = _overwritten(ins, i, data)
-                if hit:
-                    bad.append(f"{name} {addr:#x}: {op} {args.strip()} -> {hit}")
+        out += list(_functions(str(path)))
+    return out
+
+
+# A store of more than 64 bits reads its data registers late: a vector instruction may write them two wait states after it
+# at the earliest.  The compiler sees to that for its own stores, not for those written as inline assembly.
+def test_wide_stores_keep_their_data(functions):
+    n_stores, bad = 0, []
+    for name, ins in functions:
+        for i, (addr, op, args, _) in enumerate(ins):
+            if not WIDE_STORE.match(op):
+                continue
+            n_stores += 1
+            data = _regs(args.split(",")[0 if op.startswith("buffer") else 1])
+            assert data, f"{name}: {op} {args}"
+            hit = _within_two_wait_states(ins, i, lambda o, a: o.startswith("v_") and _regs(a.split(",")[0]) & data)
+            if hit:
+                bad.append(f"{name} {addr:#x}: {op} {args.strip()} -> {hit}")
     assert n_stores > 100
     assert not bad, f"{len(bad)} stores lose their data registers:\n" + "\n".join(bad[:20])
+
+
+# VCC written by a vector instruction may be read by one two wait states later at the earliest (the carry of a 64-bit
+# addition, a select); a register may be read through a lane exchange (DPP) that far behind its writing.
+def test_carries_and_lane_exchanges_wait(functions):
+    n_carries, bad = 0, []
+    for name, ins in functions:
+        for i, (addr, op, args, _) in enumerate(ins):
+            if not op.startswith("v_") or op == "v_nop":
+                continue
+            dst = args.split(",")[:2]
+            writes_vcc = "vcc" in [d.strip() for d in (dst if "_co_" in op or op.startswith("v_div_scale") else dst[:1])]
+            n_carries += writes_vcc
+            if not writes_vcc and not any("_dpp" in o for _, o, _, _ in ins[i + 1:i + 3]):
+                continue
+            regs = _regs(dst[0])
+
+            def hit(o, a):
+                if not o.startswith("v_"):
+                    return False
+                f = [x.strip() for x in a.split(",")]
+                reads_vcc = any(re.match(r"vcc\b", x) for x in f[2 if "_co_" in o or o.startswith("v_div_scale") else 1:])
+                return (writes_vcc and reads_vcc) or ("_dpp" in o and any(_regs(x.split()[0]) & regs for x in f[1:]))
+            h = _within_two_wait_states(ins, i, hit)
+            if h:
+                bad.append(f"{name} {addr:#x}: {op} {args.strip()} -> {h}")
+    assert n_carries > 100
+    assert not bad, f"{len(bad)} reads too early:\n" + "\n".join(bad[:20])
