@@ -10,7 +10,7 @@
 //                  hub rows and short rows cost the same per edge): square each edge value
 //                  exactly, round to the fixed-point grid, add into a per-node 64-bit accumulator
 //                  -- remote targets with fire-and-forget integer atomics; targets in the local id
-//                  range (in launches with enough edges) are left grouped by tile for the next
+//                  range (in calls with enough edges) are left grouped by tile for the next
 //                  kernel, which sums them in LDS; flag the group of 8 node ids of the
 //                  target (one 64-byte piece of the accumulator table) with a plain byte store, so
 //                  that the candidate kernels fetch only touched pieces
@@ -62,10 +62,18 @@ struct Stage {
     int64_t chunks;     // chunks the hand-over arrays can hold
     int32_t lo, hi;     // local id range
     int32_t tiles;      // tiles of CAND_TILE ids that meet it (0: every edge goes through device-scope atomics)
-    int32_t split;      // blocks that share a tile, each taking an equal share of the chunks
-    unsigned long long *part;        // [tiles * split * CAND_TILE] sums of all but a tile's last block
-    unsigned long long *part_flag;   // [tiles * split] tag of the call that left them
+    int32_t max_split;  // blocks launched per tile
+    int64_t min_chunks; // chunks from which edges are handed over
+    unsigned long long *part;        // [tiles * max_split * CAND_TILE] sums of all but a tile's last block
+    unsigned long long *part_flag;   // [tiles * max_split] tag of the call that left them
 };
+// Chunks of a call that hand their local edges over.  Decided from the chunks there are, by the scan and by the candidate
+// sums alike: the rows' degrees may be anything, whatever the graph's mean.
+__device__ inline int64_t handed_chunks(const Stage &stg, int64_t n_chunks)
+{
+    if (stg.tiles <= 0 || n_chunks < stg.min_chunks) return 0;
+    return n_chunks < stg.chunks ? n_chunks : stg.chunks;   // (chunks beyond the arrays go through atomics)
+}
 constexpr unsigned long long HAND_OVER_WEIGHTS = 1ull << 54;   // a weight that an entry can hold beside the 10 bits of the id (larger ones go through atomics)
 
 // Fixed-point weight of an edge value: exact square (24 x 24 bit product) times a power of two, then round to nearest even;
@@ -79,8 +87,8 @@ __device__ inline unsigned long long edge_weight(float v, double scale)
 
 // The weight scan, grid-stride over chunks of EDGE_TILE edges: stage the rows of the chunk, fetch column and value of
 // every edge, square, round.  An edge whose target lies outside the local id range is added to the per-node accumulator
-// with a device-scope atomic.  The others -- most edges: the partition holds most neighbors -- are, in launches with
-// enough of them, counting-sorted by the tile of their target inside the block and written to the chunk's piece of the
+// with a device-scope atomic.  The others -- most edges: the partition holds most neighbors -- are, in calls with
+// enough edges, counting-sorted by the tile of their target inside the block and written to the chunk's piece of the
 // hand-over array: the next kernel has blocks per local tile, which add its groups up in LDS.  Scattered device-scope
 // atomics run at about 23 G/s on this part whatever their scope or target range, and those of the remote edges are what
 // bounds a large scan.  Integer sums: the result does not depend on which way an edge went or in what order.
@@ -110,6 +118,7 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
     const double scale = ldexp(1.0, shift_for_rows(shift_base, nS));
     const int64_t E = meta[META_EDGES];
     const int64_t n_chunks = (E + EDGE_TILE - 1) / EDGE_TILE;
+    const int64_t n_handed_chunks = handed_chunks(stg, n_chunks);
     const int32_t tile0 = stg.lo / CAND_TILE;
     const int lane = lane_id();
     const int wave = (int)(threadIdx.x >> 6);
@@ -119,7 +128,7 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
     for (int64_t t = blockIdx.x; t < n_chunks; t += gridDim.x) {
         const int64_t c0 = t * EDGE_TILE;
         const int64_t c1 = (c0 + EDGE_TILE < E) ? c0 + EDGE_TILE : E;
-        const bool staged = stg.tiles > 0 && t < stg.chunks;   // (chunks beyond the arrays go through atomics)
+        const bool staged = t < n_handed_chunks;
         if (staged)
             for (int i = threadIdx.x; i < SUB_MAX; i += blockDim.x) hist[i] = 0u;   // (its last readers are a barrier behind)
         stage_slice_bounds(slice, eoff, rowstart, nS, t, c0, c1, bound_note, chunk_note + t);   // (starts and ends with a barrier)
@@ -212,15 +221,15 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
     if (bad) atomicOr(status, CSGS_ST_BAD_EDGE_VALUE);
 }
 
-// The hand-over is taken from this many chunks on (of all instances of a launch, as expected from the mean degree): below,
-// the atomics hide in the scan's latency (scan + candidate sums, atomics / hand-over: 75 chunks 18 / 19 us, 1004 chunks
+// The hand-over is taken from this many chunks on (over all instances of a launch, each taken to have as many as the one at
+// hand): below, the atomics hide in the scan's latency (scan + candidate sums, atomics / hand-over: 75 chunks 18 / 19 us, 1004 chunks
 // 56 / 33, 426 chunks 36 / 24).
-constexpr double HAND_OVER_MIN_CHUNKS = 160.0;
+constexpr int64_t HAND_OVER_MIN_CHUNKS = 160;
 // A tile's sums are split over several blocks while each block has this many edges left and the launch has SPLIT_BLOCKS
 // of them at most, two per compute unit: a narrow local range has few tiles (29 tiles, 1 M edges: 31 us with a block
 // per tile, 16 split by 7), and 150 tiles leave compute units idle (5.4 M edges: 49 / 40 us).  Shares below that only
 // add the hop between the blocks (150 tiles, 0.35 M edges: 11 us with a block per tile, 14 split by 3).
-constexpr double SPLIT_MIN_EDGES = 4096.0;
+constexpr int64_t SPLIT_MIN_EDGES = 4096;
 
 // Skew policy, resolved on the device once the candidate counts are known.
 struct SkewPolicy {
@@ -259,10 +268,11 @@ constexpr int CAND_WORDS = CAND_TILE / WAVE;  // 16 words per tile, 4 per wave
 // (ascending block ids) or belong to its own block and are published before the wait, and which
 // wait for nobody, so the wait ends.  Two kinds of blocks:
 //  * a block of four tiles asks for the flags of all their words, then for their pieces of the table: two load latencies.
-//  * when the weight scan has handed the local edges over, every tile that meets the local range has a block of its own,
-//    which first adds up in LDS what the chunks left for it (64 chunks at a time per wavefront, one per lane) and stores the
-//    sums and their touch flags: nobody else writes the local entries.  Bound by the latency of those reads; eight
-//    wavefronts per tile.
+//  * where the weight scan may hand local edges over, every tile that meets the local range has blocks of its own.  If it
+//    has done so, they first add up in LDS what the chunks left for the tile (64 chunks at a time per wavefront, one per
+//    lane; each of the tile's blocks a share of the chunks, the last one all shares) and the last one stores the sums and
+//    their touch flags: nobody else writes the local entries.  Bound by the latency of those reads; eight wavefronts per
+//    block.
 constexpr int CAND_PART_BLOCK = 512, CAND_PART_TILES = 4;
 constexpr int CAND_PART_WORDS = CAND_PART_TILES * CAND_WORDS / (CAND_PART_BLOCK / WAVE);   // words per wavefront
 
@@ -325,7 +335,7 @@ __global__ __launch_bounds__(CAND_PART_BLOCK) void cand_partials(uint64_t *__res
                                                      uint8_t *__restrict__ tileflag, int64_t n_words,
                                                      int64_t n_nodes, int64_t n_tiles, int32_t lo, int32_t hi,
                                                      const int64_t *__restrict__ meta, Stage stg,
-                                                     int64_t blocks_below, const uint64_t *__restrict__ epoch, unsigned long long *__restrict__ cand_flag,
+                                                     int32_t blocks_below, const uint64_t *__restrict__ epoch, unsigned long long *__restrict__ cand_flag,
                                                      unsigned long long *__restrict__ partial,
                                                      uint64_t *__restrict__ gtot, int32_t *__restrict__ status, InstStride is)
 {
@@ -340,18 +350,20 @@ __global__ __launch_bounds__(CAND_PART_BLOCK) void cand_partials(uint64_t *__res
     const int lane = lane_id();
     const int wave = (int)(threadIdx.x >> 6);
     const unsigned long long tag = call_tag(call_number(epoch), SLOT_CAND);
-    // blocks in the order of their tiles: blocks_below of four tiles, one per tile that meets the local range, four again
+    // blocks in the order of their tiles: blocks_below of four tiles, max_split per tile that meets the local range, four again
     const int64_t tile0 = stg.lo / CAND_TILE;
     int64_t t0, t1;
-    const int64_t b = (int64_t)blockIdx.x - blocks_below;
-    const int64_t own_blocks = (int64_t)stg.tiles * stg.split;
+    const int32_t b = (int32_t)blockIdx.x - blocks_below;
+    const int32_t own_blocks = stg.tiles * stg.max_split;   // at most SPLIT_BLOCKS
     const bool own = b >= 0 && b < own_blocks;
+    // one block of every tile after the other, so that those that leave are no more of one XCD's than of another's
+    const uint32_t round_own = own ? (uint32_t)b / (uint32_t)stg.tiles : 0u, tile_own = own ? (uint32_t)b % (uint32_t)stg.tiles : 0u;
     if (b < 0) {
         t0 = (int64_t)blockIdx.x * CAND_PART_TILES;
         t1 = t0 + CAND_PART_TILES;
         if (stg.tiles > 0 && t1 > tile0) t1 = tile0;
     } else if (own) {
-        t0 = tile0 + b / stg.split;
+        t0 = tile0 + tile_own;
         t1 = t0 + 1;
     } else {   // from the block of four that the last local tile belongs to
         const int64_t end = tile0 + stg.tiles, q = end / CAND_PART_TILES + (b - own_blocks);
@@ -361,14 +373,20 @@ __global__ __launch_bounds__(CAND_PART_BLOCK) void cand_partials(uint64_t *__res
     }
     if (t1 > n_tiles) t1 = n_tiles;
     if (t0 >= t1) return;   // the whole block
-    const int64_t E = meta[META_EDGES], all_chunks = (E + EDGE_TILE - 1) / EDGE_TILE;
-    const int64_t n_chunks = all_chunks < stg.chunks ? all_chunks : stg.chunks;   // that have handed over
-    const bool sums = own && n_chunks > 0;
-    const int share = own ? (int)(b % stg.split) : 0;
-    if (own && share != stg.split - 1) {   // a share of a tile's sums: left for the block of the last share
-        if (!sums) return;
-        sum_handed_over(acc, stg, (int32_t)(t0 - tile0), n_chunks * share / stg.split, n_chunks * (share + 1) / stg.split);
-        for (int i = threadIdx.x; i < CAND_TILE; i += CAND_PART_BLOCK) st_relaxed(&stg.part[b * CAND_TILE + i], acc[i]);
+    const uint32_t n_chunks = own ? (uint32_t)handed_chunks(stg, (meta[META_EDGES] + EDGE_TILE - 1) / EDGE_TILE) : 0u;   // at most STAGE_EDGES_MAX / EDGE_TILE
+    const bool sums = n_chunks > 0;
+    // The last `split` of a tile's blocks share its sums, the others leave (all but the last where nothing was handed over).
+    uint32_t split = 1;
+    if (sums) {
+        split = n_chunks / (uint32_t)(SPLIT_MIN_EDGES / EDGE_TILE) / (uint32_t)stg.tiles;
+        if (split > (uint32_t)stg.max_split) split = (uint32_t)stg.max_split;
+        if (split < 1u) split = 1u;
+    }
+    const int share = own ? (int)round_own - (stg.max_split - (int)split) : 0;
+    if (share < 0) return;
+    if (own && share != (int)split - 1) {   // a share of a tile's sums: left for the block of the last share
+        sum_handed_over(acc, stg, (int32_t)tile_own, n_chunks * share / split, n_chunks * (share + 1) / split);
+        for (int i = threadIdx.x; i < CAND_TILE; i += CAND_PART_BLOCK) st_relaxed(&stg.part[(int64_t)b * CAND_TILE + i], acc[i]);
         wait_memory_ops();
         __syncthreads();
         if (threadIdx.x == 0) st_relaxed(&stg.part_flag[b], tag);
@@ -393,16 +411,16 @@ __global__ __launch_bounds__(CAND_PART_BLOCK) void cand_partials(uint64_t *__res
         w[k] = (((f8[k] >> (8 * (lane >> 3))) & 0xFFull) && id < (uint32_t)n_nodes) ? wtable[id] : 0ull;
     }
     if (sums) {   // (what did not fit an entry, and ids of the tile outside the local range, have come through the table)
-        sum_handed_over(acc, stg, (int32_t)(t0 - tile0), n_chunks * share / stg.split, n_chunks);
-        if (stg.split > 1) {   // (the other shares' blocks were dispatched before and wait for nobody)
-            const int64_t first = b - share;
+        sum_handed_over(acc, stg, (int32_t)tile_own, n_chunks * share / split, n_chunks);
+        if (split > 1) {   // (the other shares' blocks were dispatched before and wait for nobody)
+            const int64_t first = b - (int64_t)share * stg.tiles;
             bool ok = true;
-            if (threadIdx.x < (unsigned)share) ok = wait_tag(&stg.part_flag[first + threadIdx.x], tag, wait_limit(epoch));
+            if (threadIdx.x < (unsigned)share) ok = wait_tag(&stg.part_flag[first + (int64_t)threadIdx.x * stg.tiles], tag, wait_limit(epoch));
             if (!ok) atomicOr(status, CSGS_ST_INTERNAL);
             __syncthreads();
             for (int i = threadIdx.x; i < CAND_TILE; i += CAND_PART_BLOCK) {
                 unsigned long long v = acc[i];
-                for (int k = 0; k < share; ++k) v += ld_relaxed(&stg.part[(first + k) * CAND_TILE + i]);
+                for (int k = 0; k < share; ++k) v += ld_relaxed(&stg.part[(first + (int64_t)k * stg.tiles) * CAND_TILE + i]);
                 acc[i] = v;
             }
             __syncthreads();
@@ -763,26 +781,37 @@ static int build_probs_impl(const csgs_graph *g, const int32_t *S, int32_t nS, c
     const RowOffsets &rows = w.rows[ws->rows_buf & 1];
     const unsigned nz = (unsigned)w.n_inst;
     const InstStride is = inst_stride(w);
-    // The number of edges is known on the device only; rows of the graph's mean degree are a fair guess.
-    const double guess = (double)nS * ((double)g->nnz / (double)g->n_nodes) / EDGE_TILE;
-    const int64_t chunks = guess * 1.25 + 16.0 < (double)w.chunk_cap ? (int64_t)(guess * 1.25 + 16.0) : w.chunk_cap;
+    // The number of edges is known on the device only: rows of the graph's mean degree are a guess that hubs can exceed many
+    // times over.  What depends on the number is decided on the device, and there are never fewer blocks over all
+    // instances than the device holds (those without a chunk leave at once) unless the workspace describes fewer chunks.
+    // (us for scan and sums, grid and hand-over by the mean degree / as here: 256 rows of 5000 edges, mean degree 8, 270 / 68;
+    // the 1024 rows of most edges in 2.4 M, 6.4 M edges of them, 336 / 282.)
+    const double guess = (double)nS * ((double)g->nnz / (double)g->n_nodes) / EDGE_TILE * 1.25 + 16.0;
+    int64_t chunks = guess < (double)SCAN_GRID ? (int64_t)guess : SCAN_GRID;
+    if (chunks < SCAN_GRID / w.n_inst) chunks = SCAN_GRID / w.n_inst;
+    if (chunks > w.chunk_cap) chunks = w.chunk_cap;
     // tiles that meet the local id range, when the hand-over can cover them and is wanted
     const bool range_ok = g->local_hi > g->local_lo && g->local_lo >= 0 && g->local_hi <= g->n_nodes;
     const int64_t tile0 = range_ok ? g->local_lo / CAND_TILE : 0, tile1 = range_ok ? ((int64_t)g->local_hi - 1) / CAND_TILE + 1 : 0;
-    const bool hand = ws->scan_mode == 2 || (ws->scan_mode == 0 && guess * (double)w.n_inst >= HAND_OVER_MIN_CHUNKS);
+    const int64_t min_chunks = ws->scan_mode == 2 ? 0 : (HAND_OVER_MIN_CHUNKS + w.n_inst - 1) / w.n_inst;
+    const bool hand = ws->scan_mode != 1 && w.chunk_cap >= min_chunks;
     const int32_t tiles = (hand && tile1 - tile0 <= SUB_MAX) ? (int32_t)(tile1 - tile0) : 0;
+    // Blocks per tile: what the expected chunks can use, at least two and a block per compute unit in all, in case the rows hold
+    // more.  (Not as many as there might ever be use for: idle ones cost a launch a few tenths of a us.)
     int64_t split = 1;
     if (tiles) {
-        split = SPLIT_BLOCKS / ((int64_t)tiles * w.n_inst);
-        const int64_t most = (int64_t)(guess * EDGE_TILE / tiles / SPLIT_MIN_EDGES);
-        if (split > most) split = most;
+        const int64_t each = (int64_t)tiles * w.n_inst;
+        split = (int64_t)fmin(guess, (double)w.stage_chunks) * EDGE_TILE / tiles / SPLIT_MIN_EDGES;
+        if (split < SPLIT_BLOCKS / 2 / each) split = SPLIT_BLOCKS / 2 / each;
+        if (split < 2) split = 2;
+        if (split > SPLIT_BLOCKS / each) split = SPLIT_BLOCKS / each;
         if (split > w.split_blocks / tiles) split = w.split_blocks / tiles;
         if (split > WAVE) split = WAVE;
         if (split < 1) split = 1;
     }
     const Stage stg{w.stage, w.stage_off, w.stage_chunks, range_ok ? g->local_lo : 0, range_ok ? g->local_hi : 0, tiles, (int32_t)split,
-                    (unsigned long long *)w.split_sum, (unsigned long long *)w.split_flag};
-    CSGS_LAUNCH(K_SCAN_EDGES, scan_edges, dim3((unsigned)(chunks < SCAN_GRID ? chunks : SCAN_GRID), 1, nz), dim3(256), st, g->colidx, g->val,
+                    min_chunks, (unsigned long long *)w.split_sum, (unsigned long long *)w.split_flag};
+    CSGS_LAUNCH(K_SCAN_EDGES, scan_edges, dim3((unsigned)chunks, 1, nz), dim3(256), st, g->colidx, g->val,
                 g->n_nodes, g->nnz, shift_base, rows.meta, w.chunk_cap * EDGE_TILE, rows.eoff, rows.rowstart, w.wtable,
                 w.tileflag, rows.chunk_note, rows.bound_note, status, stg, is);
     CSGS_LAUNCH_CHECK();
@@ -790,7 +819,7 @@ static int build_probs_impl(const csgs_graph *g, const int32_t *S, int32_t nS, c
     const int64_t part_blocks = tiles ? below + tiles * split + (w.n_tiles + CAND_PART_TILES - 1) / CAND_PART_TILES - tile1 / CAND_PART_TILES
                                       : (w.n_tiles + CAND_PART_TILES - 1) / CAND_PART_TILES;
     CSGS_LAUNCH(K_CAND_PARTIALS, cand_partials, dim3((unsigned)part_blocks, 1, nz), dim3(CAND_PART_BLOCK), st, w.wtable, w.tileflag, n_words,
-                g->n_nodes, w.n_tiles, g->local_lo, g->local_hi, rows.meta, stg, tiles ? below : part_blocks, w.epoch,
+                g->n_nodes, w.n_tiles, g->local_lo, g->local_hi, rows.meta, stg, (int32_t)(tiles ? below : part_blocks), w.epoch,
                 (unsigned long long *)w.cand_flag, (unsigned long long *)w.partial, w.gtot, status, is);
     CSGS_LAUNCH_CHECK();
     CSGS_LAUNCH(K_CAND_EMIT, cand_emit, dim3((unsigned)w.n_tiles, 1, nz), dim3(256), st, w.wtable, w.tileflag, n_words,

@@ -1,0 +1,74 @@
+"""Calls whose time follows from what they are given, whatever a graph's mean degree or a tuned size would suggest: kernel
+durations (least of several) of two calls beside each other, with results against the CPU oracle."""
+import numpy as np
+import pytest
+
+import chain
+import oracle
+from paper_2101_07706_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2101_07706_amd import csgs
+    csgs.lib()
+    return torch.device("cuda:0")
+
+
+def _least_us(call, kernels, reps=10):
+    """Sum over `kernels` of the least duration of a launch, in us."""
+    from paper_2101_07706_amd import csgs
+    call()
+    torch.cuda.synchronize()
+    csgs.csgs_profile_enable(True)
+    for _ in range(reps):
+        call()
+    torch.cuda.synchronize()
+    samples = csgs.csgs_profile_samples()
+    csgs.csgs_profile_collect()
+    csgs.csgs_profile_enable(False)
+    return sum(min(samples[k]) for k in kernels if k in samples) * 1e3
+
+
+def _hub_graph(rng, n, mean, hubs, hub_degree):
+    """A graph whose rows have `mean` edges, but for `hubs` of them."""
+    deg = np.full(n, mean)
+    hub_rows = np.sort(rng.choice(n, hubs, replace=False)).astype(np.int32)
+    deg[hub_rows] = hub_degree
+    rowptr = np.zeros(n + 1, np.int64)
+    np.cumsum(deg, out=rowptr[1:])
+    step = np.repeat(n // deg, deg)
+    col = (np.arange(rowptr[-1]) - np.repeat(rowptr[:-1], deg)) * step + (rng.random(int(rowptr[-1])) * step).astype(np.int64)
+    val = (1.0 / np.repeat(deg, deg)).astype(np.float32)
+    return synth.Graph(n, rowptr, col.astype(np.int32), val, synth.partition_bounds(n, 8), 0, 1.0), hub_rows
+
+
+# A million edges in a few rows of a sparse graph against the same number in ordinary rows.
+def test_weight_scan_of_hub_rows(dev):
+    from paper_2101_07706_amd import csgs, pipeline
+    rng = np.random.default_rng(11)
+    n, mean, hubs, hub_degree = 200_000, 8, 256, 4000
+    g, hub_rows = _hub_graph(rng, n, mean, hubs, hub_degree)
+    ordinary = np.sort(rng.choice(np.setdiff1d(np.arange(n), hub_rows), hubs * hub_degree // mean, replace=False)).astype(np.int32)
+    dg = pipeline.DeviceGraph(g, dev)
+    us = []
+    for S in (ordinary, hub_rows):
+        print(f"[scan] {len(S)} rows", flush=True)
+        ws = pipeline.Workspace(n, len(S), 1, g.nnz, dev)
+        lb = pipeline.LayerBuffers(len(S), 1, n, 1, 8, dev)
+        Sd = torch.from_numpy(S).to(dev)
+        us.append(_least_us(lambda: csgs.csgs_build_probs(dg.c, Sd, 4.0, lb.cand_id, lb.cand_w, lb.cdf, None, lb.stats, ws.desc, lb.status),
+                            ("scan_edges", "cand_partials")))
+        want = oracle.build_probs(g, S, 4.0)
+        n_c = len(want.cand_id)
+        assert int(lb.status.item()) == 0 and int(lb.stats_host().n_cand) == n_c
+        np.testing.assert_array_equal(lb.cand_id[:n_c].cpu().numpy(), want.cand_id)
+        np.testing.assert_array_equal(lb.cdf[:n_c].cpu().numpy().view(np.uint64), want.cdf)
+    print(f"[scan] ordinary {us[0]:.1f} us, hubs {us[1]:.1f} us")
+    assert us[1] < 2.0 * us[0]
