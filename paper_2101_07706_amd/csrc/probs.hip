@@ -267,14 +267,18 @@ constexpr int CAND_WORDS = CAND_TILE / WAVE;  // 16 words per tile, 4 per wave
 // for the flags of the (at most 63) lower tiles of its group, which were dispatched before it
 // (ascending block ids) or belong to its own block and are published before the wait, and which
 // wait for nobody, so the wait ends.  Two kinds of blocks:
-//  * a block of four tiles asks for the flags of all their words, then for their pieces of the table: two load latencies.
+//  * a block of TILES tiles asks for the flags of all their words, then for their pieces of the table: two load latencies.
 //  * where the weight scan may hand local edges over, every tile that meets the local range has blocks of its own.  If it
 //    has done so, they first add up in LDS what the chunks left for the tile (64 chunks at a time per wavefront, one per
 //    lane; each of the tile's blocks a share of the chunks, the last one all shares) and the last one stores the sums and
 //    their touch flags: nobody else writes the local entries.  Bound by the latency of those reads; eight wavefronts per
 //    block.
-constexpr int CAND_PART_BLOCK = 512, CAND_PART_TILES = 4;
-constexpr int CAND_PART_WORDS = CAND_PART_TILES * CAND_WORDS / (CAND_PART_BLOCK / WAVE);   // words per wavefront
+constexpr int CAND_PART_BLOCK = 512;
+// Tiles per block of the first kind.  While all blocks with one tile each are on the device together, they are quickest
+// (us per launch, four tiles / one: 4 tiles 6.6 / 5.2, 98 tiles 6.9 / 6.0, 256 tiles 7.5 / 5.6, 700 tiles 7.7 / 7.2); beyond
+// that their number costs more than it gives (2392 tiles 10.6 / 14.1, eight times that 51 / 84; two tiles 11.8 and 62).
+constexpr int CAND_PART_TILES = 4;
+constexpr int64_t CAND_PART_ONE = 1024;
 
 // Sums of the edges that chunks [c_first, n_chunks) handed over for local tile `tile` into acc[CAND_TILE] (LDS, zeroed here).  A wavefront takes up to 64
 // chunks at a time, one per lane, and walks through their groups as one sequence.  Called by all threads; ends with a barrier.
@@ -331,6 +335,7 @@ __device__ inline void sum_handed_over(unsigned long long *acc, const Stage &stg
     __syncthreads();
 }
 
+template <int TILES>
 __global__ __launch_bounds__(CAND_PART_BLOCK) void cand_partials(uint64_t *__restrict__ wtable,
                                                      uint8_t *__restrict__ tileflag, int64_t n_words,
                                                      int64_t n_nodes, int64_t n_tiles, int32_t lo, int32_t hi,
@@ -339,7 +344,7 @@ __global__ __launch_bounds__(CAND_PART_BLOCK) void cand_partials(uint64_t *__res
                                                      unsigned long long *__restrict__ partial,
                                                      uint64_t *__restrict__ gtot, int32_t *__restrict__ status, InstStride is)
 {
-    constexpr int W = CAND_PART_WORDS, WAVES = CAND_PART_BLOCK / WAVE;
+    constexpr int WAVES = CAND_PART_BLOCK / WAVE, W = TILES * CAND_WORDS / WAVES;   // words per wavefront
     __shared__ uint64_t lds[WAVES][3];
     __shared__ unsigned long long acc[CAND_TILE];
     wtable = inst_ptr(wtable, is.ws); tileflag = inst_ptr(tileflag, is.ws); epoch = inst_ptr(epoch, is.ws);
@@ -350,7 +355,7 @@ __global__ __launch_bounds__(CAND_PART_BLOCK) void cand_partials(uint64_t *__res
     const int lane = lane_id();
     const int wave = (int)(threadIdx.x >> 6);
     const unsigned long long tag = call_tag(call_number(epoch), SLOT_CAND);
-    // blocks in the order of their tiles: blocks_below of four tiles, max_split per tile that meets the local range, four again
+    // blocks in the order of their tiles: blocks_below of TILES tiles, max_split per tile that meets the local range, TILES again
     const int64_t tile0 = stg.lo / CAND_TILE;
     int64_t t0, t1;
     const int32_t b = (int32_t)blockIdx.x - blocks_below;
@@ -359,16 +364,16 @@ __global__ __launch_bounds__(CAND_PART_BLOCK) void cand_partials(uint64_t *__res
     // one block of every tile after the other, so that those that leave are no more of one XCD's than of another's
     const uint32_t round_own = own ? (uint32_t)b / (uint32_t)stg.tiles : 0u, tile_own = own ? (uint32_t)b % (uint32_t)stg.tiles : 0u;
     if (b < 0) {
-        t0 = (int64_t)blockIdx.x * CAND_PART_TILES;
-        t1 = t0 + CAND_PART_TILES;
+        t0 = (int64_t)blockIdx.x * TILES;
+        t1 = t0 + TILES;
         if (stg.tiles > 0 && t1 > tile0) t1 = tile0;
     } else if (own) {
         t0 = tile0 + tile_own;
         t1 = t0 + 1;
-    } else {   // from the block of four that the last local tile belongs to
-        const int64_t end = tile0 + stg.tiles, q = end / CAND_PART_TILES + (b - own_blocks);
-        t0 = q * CAND_PART_TILES;
-        t1 = t0 + CAND_PART_TILES;
+    } else {   // from the block that the last local tile belongs to
+        const int64_t end = tile0 + stg.tiles, q = end / TILES + (b - own_blocks);
+        t0 = q * TILES;
+        t1 = t0 + TILES;
         if (t0 < end) t0 = end;
     }
     if (t1 > n_tiles) t1 = n_tiles;
@@ -392,8 +397,8 @@ __global__ __launch_bounds__(CAND_PART_BLOCK) void cand_partials(uint64_t *__res
         if (threadIdx.x == 0) st_relaxed(&stg.part_flag[b], tag);
         return;
     }
-    const int waves_per_tile = own ? WAVES : WAVES / CAND_PART_TILES;
-    const int64_t tile = own ? t0 : (t0 / CAND_PART_TILES) * CAND_PART_TILES + wave / waves_per_tile;   // of this wavefront
+    const int waves_per_tile = own ? WAVES : WAVES / TILES;
+    const int64_t tile = own ? t0 : (t0 / TILES) * TILES + wave / waves_per_tile;   // of this wavefront
     const bool in_block = tile >= t0 && tile < t1;
     const int w_used = own ? CAND_WORDS / WAVES : W;   // words of this wavefront
     const int64_t word0 = tile * CAND_WORDS + (wave % waves_per_tile) * w_used;
@@ -456,7 +461,7 @@ __global__ __launch_bounds__(CAND_PART_BLOCK) void cand_partials(uint64_t *__res
     // (packed count halves cannot carry: each is at most 1024 per tile)
     const int64_t t = t0 + wave;
     if (t >= t1) return;
-    const int w0 = own ? 0 : (int)(t % CAND_PART_TILES) * waves_per_tile;
+    const int w0 = own ? 0 : (int)(t % TILES) * waves_per_tile;
     unsigned long long mine = 0ull;
     if (lane < 3)
         for (int i = 0; i < waves_per_tile; ++i) mine += lds[w0 + i][lane];
@@ -815,12 +820,16 @@ static int build_probs_impl(const csgs_graph *g, const int32_t *S, int32_t nS, c
                 g->n_nodes, g->nnz, shift_base, rows.meta, w.chunk_cap * EDGE_TILE, rows.eoff, rows.rowstart, w.wtable,
                 w.tileflag, rows.chunk_note, rows.bound_note, status, stg, is);
     CSGS_LAUNCH_CHECK();
-    const int64_t below = tiles ? (tile0 + CAND_PART_TILES - 1) / CAND_PART_TILES : 0;
-    const int64_t part_blocks = tiles ? below + tiles * split + (w.n_tiles + CAND_PART_TILES - 1) / CAND_PART_TILES - tile1 / CAND_PART_TILES
-                                      : (w.n_tiles + CAND_PART_TILES - 1) / CAND_PART_TILES;
-    CSGS_LAUNCH(K_CAND_PARTIALS, cand_partials, dim3((unsigned)part_blocks, 1, nz), dim3(CAND_PART_BLOCK), st, w.wtable, w.tileflag, n_words,
-                g->n_nodes, w.n_tiles, g->local_lo, g->local_hi, rows.meta, stg, (int32_t)(tiles ? below : part_blocks), w.epoch,
-                (unsigned long long *)w.cand_flag, (unsigned long long *)w.partial, w.gtot, status, is);
+    const int64_t per = w.n_tiles * w.n_inst <= CAND_PART_ONE ? 1 : CAND_PART_TILES;
+    const int64_t below = tiles ? (tile0 + per - 1) / per : 0;
+    const int64_t part_blocks = tiles ? below + tiles * split + (w.n_tiles + per - 1) / per - tile1 / per : (w.n_tiles + per - 1) / per;
+    const dim3 part_grid((unsigned)part_blocks, 1, nz);
+#define CSGS_CAND_PARTIALS(TILES)                                                                                                       \
+    CSGS_LAUNCH(K_CAND_PARTIALS, cand_partials<TILES>, part_grid, dim3(CAND_PART_BLOCK), st, w.wtable, w.tileflag, n_words, g->n_nodes, \
+                w.n_tiles, g->local_lo, g->local_hi, rows.meta, stg, (int32_t)(tiles ? below : part_blocks), w.epoch,                   \
+                (unsigned long long *)w.cand_flag, (unsigned long long *)w.partial, w.gtot, status, is)
+    if (per == 1) CSGS_CAND_PARTIALS(1); else CSGS_CAND_PARTIALS(CAND_PART_TILES);
+#undef CSGS_CAND_PARTIALS
     CSGS_LAUNCH_CHECK();
     CSGS_LAUNCH(K_CAND_EMIT, cand_emit, dim3((unsigned)w.n_tiles, 1, nz), dim3(256), st, w.wtable, w.tileflag, n_words,
                 g->n_nodes, w.n_tiles, g->local_lo, g->local_hi, pol, w.partial, w.gtot, rows.meta, shift_base, w.epoch, stats, status, cand_id,

@@ -167,6 +167,7 @@ def test_sampled_adjacency_sizes(dev, n_nodes, degree, rows):
     (6000, 60, 5000, 1023, 1025, 8.0), (6000, 1.5, 4, 0, 6000, 1.0), (700, 0.01, 700, 5, 690, 1.0),
     (400_000, 3, 60_000, 1, 327_681, 2.0), (400_000, 3, 60_000, 1023, 327_681, 2.0),   # 321 and 320 tiles
     (70_000, 130, 70_000, 511, 30_001, 2.0),
+    (1_048_576, 3, 40_000, 6500, 300_001, 2.0), (1_048_577, 3, 70_000, 6500, 300_001, 2.0), (1_048_577, 3, 70_000, 4096, 8192, 4.0),   # one and four tiles per block
 ])
 def test_weight_scan_hand_over(dev, n_nodes, degree, n_rows, lo, hi, skew):
     from paper_2101_07706_amd import csgs, pipeline
