@@ -812,16 +812,24 @@ static int sampled_adjacency_impl(const csgs_graph *g, const int32_t *rows, int3
                        o.bound_note, w.chunk_cap * EDGE_TILE, (int32_t)((ws->draw_B + ROW_TILE - 1) / ROW_TILE)};
     }
     ws->has_next = nxt.blocks > 0;
-    // Blocks for the chunks the rows may be expected to have: their number is only known on the device, but rows of the
-    // graph's mean degree are a fair guess, and blocks stride over what is more.
+    // The number of chunks is known on the device only.  Rows of the graph's mean degree are a guess that hubs can exceed
+    // many times over: it picks the path, and may ask for more blocks than the device holds over all instances but not for
+    // fewer (those without a chunk leave at once) unless the workspace describes fewer chunks.  (us, grid by the mean degree / as
+    // here: 256 rows of 5000 edges, mean degree 8, one pass 317 / 26; the 8192 rows of most edges in 2.4 M, 21 M edges of them,
+    // two passes 638 / 245.)
     const double guess = (double)n_rows * ((double)g->nnz / (double)g->n_nodes) / EDGE_TILE * 1.25 + 16.0;
-    const int64_t chunks = guess < (double)w.chunk_cap ? (int64_t)guess : w.chunk_cap;
+    const int64_t expected = guess < (double)w.chunk_cap ? (int64_t)guess : w.chunk_cap;
+    auto blocks = [&](int64_t grid, int64_t chunks_each) {
+        const int64_t least = grid / w.n_inst, want = (expected + chunks_each - 1) / chunks_each, cap = (w.chunk_cap + chunks_each - 1) / chunks_each;
+        const int64_t n = want < least ? least : (want < grid ? want : grid);
+        return (unsigned)(n < cap ? n : cap);
+    };
     const unsigned nz = (unsigned)w.n_inst;
     const InstStride is = inst_stride(w);
     const AdjGraph ag{g->colidx, g->val, g->n_nodes, g->nnz, cur.eoff, cur.rowstart, w.rank, w.member, w.pdbl};
     // after csgs_build_probs on the same rows the weight scan has left every chunk's row slice in the workspace
-    if (chunks * w.n_inst <= ADJ_ONCE_MAX) {
-        const int64_t once = chunks < resident_grid(2) ? chunks : resident_grid(2);
+    if (expected * w.n_inst <= ADJ_ONCE_MAX) {
+        const int64_t once = w.chunk_cap < resident_grid(2) ? w.chunk_cap : resident_grid(2);
         const dim3 grid_once((unsigned)(once + rem.blocks + nxt.blocks), 1, nz);
         if (reuse_offsets)
             CSGS_LAUNCH(K_ADJ_ONCE, adj_once<true>, grid_once, dim3(256), st, ag, cur.meta, w.epoch, w.adj_ts, w.chunk_cap, cur.chunk_note,
@@ -832,9 +840,7 @@ static int sampled_adjacency_impl(const csgs_graph *g, const int32_t *rows, int3
         CSGS_LAUNCH_CHECK();
         return CSGS_OK;
     }
-    const unsigned mark = (unsigned)(chunks < ADJ_MARK_GRID ? chunks : ADJ_MARK_GRID);
-    const int64_t place_want = (chunks + ADJ_PLACE_MIN - 1) / ADJ_PLACE_MIN;
-    const unsigned place = (unsigned)(place_want < ADJ_PLACE_GRID ? place_want : ADJ_PLACE_GRID);
+    const unsigned mark = blocks(ADJ_MARK_GRID, 1), place = blocks(ADJ_PLACE_GRID, ADJ_PLACE_MIN);
     const dim3 grid(mark + (unsigned)(rem.blocks + nxt.blocks), 1, nz);
     if (reuse_offsets)
         CSGS_LAUNCH(K_ADJ_MARK, adj_mark<true>, grid, dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.chunk_note, w.adj_cnt, w.stage,

@@ -72,3 +72,37 @@ def test_weight_scan_of_hub_rows(dev):
         np.testing.assert_array_equal(lb.cdf[:n_c].cpu().numpy().view(np.uint64), want.cdf)
     print(f"[scan] ordinary {us[0]:.1f} us, hubs {us[1]:.1f} us")
     assert us[1] < 2.0 * us[0]
+
+
+# The sampled adjacency of the same two sets of rows.
+def test_sampled_adjacency_of_hub_rows(dev):
+    from types import SimpleNamespace
+    from paper_2101_07706_amd import csgs, pipeline
+    rng = np.random.default_rng(12)
+    n, mean, hubs, hub_degree, B = 200_000, 8, 256, 4000, 1000
+    g, hub_rows = _hub_graph(rng, n, mean, hubs, hub_degree)
+    ordinary = np.sort(rng.choice(np.setdiff1d(np.arange(n), hub_rows), hubs * hub_degree // mean, replace=False)).astype(np.int32)
+    dg = pipeline.DeviceGraph(g, dev)
+    ids = np.arange(n, dtype=np.int32)
+    cdf = np.cumsum(rng.integers(1, 1 << 20, n), dtype=np.uint64)
+    draw = oracle.draw_nodes(SimpleNamespace(cand_id=ids, cdf=cdf), B, 5, 1, 0)
+    ws = pipeline.Workspace(n, len(ordinary), B, g.nnz, dev)
+    i32 = lambda k: torch.zeros(k, dtype=torch.int32, device=dev)
+    S_next, mult, n_next, status, p = i32(B), i32(B), i32(1), i32(1), torch.zeros(B, dtype=torch.float32, device=dev)
+    st = torch.frombuffer(bytearray(bytes(csgs.ProbStats(n_cand=n, total=int(cdf[-1])))), dtype=torch.int64).to(dev)
+    csgs.csgs_draw_nodes(n, torch.from_numpy(ids).to(dev), torch.from_numpy(cdf.view(np.int64)).to(dev), st, B, 5, 1, 0, S_next, mult, p, n_next,
+                         ws.desc, status)
+    us = []
+    for S in (ordinary, hub_rows):
+        print(f"[adjacency] {len(S)} rows", flush=True)
+        want = oracle.sampled_adjacency(g, S, draw)
+        cap = want.adj_nnz + 5
+        rp, ac, av, nnz = i32(len(S) + 1), i32(cap), torch.zeros(cap, dtype=torch.float32, device=dev), torch.zeros(1, dtype=torch.int64, device=dev)
+        Sd = torch.from_numpy(S).to(dev)
+        us.append(_least_us(lambda: csgs.csgs_sampled_adjacency(dg.c, Sd, rp, ac, av, nnz, ws.desc, status), ("adj_once", "adj_mark", "adj_place")))
+        assert int(status.item()) == 0 and int(nnz.item()) == want.adj_nnz
+        np.testing.assert_array_equal(rp.cpu().numpy(), want.adj_rowptr)
+        np.testing.assert_array_equal(ac[:want.adj_nnz].cpu().numpy(), want.adj_col)
+        chain.assert_close(av[:want.adj_nnz].cpu().numpy(), want.adj_val, chain.P_RTOL, 0.0, "adj_val")
+    print(f"[adjacency] ordinary {us[0]:.1f} us, hubs {us[1]:.1f} us")
+    assert us[1] < 2.0 * us[0]
