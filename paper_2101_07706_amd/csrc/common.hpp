@@ -25,7 +25,8 @@ constexpr int CAND_TILE = 1024;   // node ids per block in the candidate scan
 constexpr int EDGE_TILE = 1024;   // edges per chunk in the flat edge passes
 constexpr int SCAN_GRID = 2048;   // most chunk blocks of the weight scan (grid-stride over chunks, they wait for nobody): more than the device holds at once
 constexpr int HIT_MIN_WORDS = 16;     // fewest 64-position bitmap words a block of the hit compaction takes
-constexpr int HIT_GRID = 512;         // most blocks of it (they wait for nobody)
+constexpr int HIT_GRID = 512;         // most blocks of it
+constexpr int64_t HIT_COUNT_WORDS = 49152;   // most bitmap words of which every block counts those before its own itself
 constexpr int ROW_TILE = 1024;    // rows of S per block in the degree prefix
 // Hand-over of the weight scan: edges that end in the local id range are left, chunk by chunk, for blocks that each add
 // up one tile of CAND_TILE ids in LDS.
@@ -73,6 +74,7 @@ struct Workspace {
     // per call.  The row offsets exist twice: while the adjacency pass of one layer reads one set,
     // its spare blocks prepare the other for the next layer (rows = the node set just sampled).
     RowOffsets rows[2];
+    uint64_t *hit_ts;    // scan state of the hit compaction's blocks (long position bitmaps)
     uint64_t *adj_ts;    // scan state of the edge chunks (1 sum per chunk of 1024 edges)
     uint32_t *adj_cnt;   // [chunk_cap] kept edges of every edge chunk | 1 << 31 when a row starts at the chunk's first edge
     uint64_t *rp_ts;     // scan state of the row tiles (1 sum per tile of ROW_TILE rows)
@@ -160,6 +162,7 @@ __host__ inline Workspace carve(void *base, int64_t n_nodes, int64_t nS_max, int
     w.cand_flag = (uint64_t *)take((size_t)w.n_tiles * 8);
     w.epoch = (uint64_t *)take(EPOCH_WORDS * 8);
     for (int b = 0; b < 2; ++b) w.cbitmap[b] = (uint64_t *)take(words * 8);
+    w.hit_ts = (uint64_t *)take(scan_state_words(HIT_GRID, 1) * 8);
     w.adj_ts = (uint64_t *)take(scan_state_words(w.chunk_cap, 1) * 8);
     w.adj_cnt = (uint32_t *)take((size_t)w.chunk_cap * 4);
     w.rp_tiles = (nS_max + ROW_TILE - 1) / ROW_TILE;

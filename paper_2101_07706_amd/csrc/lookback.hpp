@@ -55,7 +55,7 @@ constexpr int EPOCH_BITMAP_NEXT = 3, EPOCH_BITMAP_CUR = 4;
 constexpr int EPOCH_BITMAP_USED = 5;   // [2] words of each bitmap that its latest draw may have set
 static_assert(EPOCH_BITMAP_USED + 2 <= EPOCH_WORDS, "epoch words");
 // one tag space per scan-state region, so the kernels of one call never mistake each other's flags
-enum TagSlot { SLOT_ROWS = 1, SLOT_CAND = 2, SLOT_ADJ = 4, SLOT_ROWS_NEXT = 5 };
+enum TagSlot { SLOT_ROWS = 1, SLOT_CAND = 2, SLOT_HITS = 3, SLOT_ADJ = 4, SLOT_ROWS_NEXT = 5 };
 
 __device__ inline int wait_limit(const uint64_t *epoch)
 {

@@ -11,7 +11,7 @@
 //                 independent probes per round).  Hits are counted per candidate position with
 //                 integer atomics; first hits set a position bitmap.
 //   hits          every block takes a range of the position bitmap, counts the bits before it
-//                 itself, lists its own hits in LDS, then one thread per distinct hit: S_next
+//                 itself (or, in a long bitmap, takes them from the scan across blocks), lists its own hits in LDS, then one thread per distinct hit: S_next
 //                 ascending, mult, p_incl, node -> rank table.
 //   adj_mark      flat over the edges of S (same chunking as the weight scan): keep = the target was
 //                 sampled.  Leaves every chunk's kept edges in order, their number, and the row
@@ -184,23 +184,29 @@ __device__ inline void mark_members(uint64_t *__restrict__ member, int32_t id, u
 // counter, CDF, id), then by the double-precision logarithm and exponential, which more blocks share.  One mini-batch
 // of 8192 draws from 163 K candidates: 16 -> 6 us; 131072 from 650 K: 73 -> 11 us (blocks of 16384 positions with a
 // prefix across blocks before).
+// A long bitmap is too much for every block to read: beyond HIT_COUNT_WORDS the blocks count their own words and take the
+// prefix from the scan across blocks (a block waits for lower ones only, which were dispatched before it).  us, reading all /
+// scan, 8192 draws: 1.8 M candidates 10.2 / 11.4, 2.4 M 12.3 / 13.9, 16 M 50 / 26, 256 M 572 / 109.
 __global__ __launch_bounds__(256) void hits(const int32_t *__restrict__ cand_id, const uint64_t *__restrict__ cdf,
                                             const csgs_prob_stats *__restrict__ stats, int64_t cand_cap, int64_t n_nodes,
                                             int32_t B, uint64_t *__restrict__ epoch, uint32_t *__restrict__ hit,
                                             uint64_t *cbitmap0, uint64_t *cbitmap1, uint64_t *__restrict__ rank,
                                             uint64_t *__restrict__ member, int32_t *__restrict__ S_next,
                                             int32_t *__restrict__ mult, float *__restrict__ p_incl,
-                                            double *__restrict__ pdbl, int32_t *__restrict__ n_next, InstStride is)
+                                            double *__restrict__ pdbl, int32_t *__restrict__ n_next,
+                                            uint64_t *__restrict__ ts_mem, int32_t *__restrict__ status, InstStride is)
 {
     constexpr int SUB = 64;   // words listed at a time: four threads of 16 bits each per word
     __shared__ uint16_t s_list[SUB * 64];   // drawn positions of those words, ascending
     __shared__ uint32_t s_cnt[4], s_before[4];
+    __shared__ unsigned long long s_lb[1];
     member = inst_ptr(member, is.ws);
     cand_id = inst_ptr(cand_id, is.buf); cdf = inst_ptr(cdf, is.buf); stats = inst_ptr(stats, is.buf);
     S_next = inst_ptr(S_next, is.buf); mult = inst_ptr(mult, is.buf); p_incl = inst_ptr(p_incl, is.buf);
     n_next = inst_ptr(n_next, is.buf);
     epoch = inst_ptr(epoch, is.ws); hit = inst_ptr(hit, is.ws); cbitmap0 = inst_ptr(cbitmap0, is.ws);
     cbitmap1 = inst_ptr(cbitmap1, is.ws); rank = inst_ptr(rank, is.ws); pdbl = inst_ptr(pdbl, is.ws);
+    ts_mem = inst_ptr(ts_mem, is.ws); status = inst_ptr(status, is.buf);
     const int tid = (int)threadIdx.x, lane = lane_id(), wave = tid >> 6;
     const unsigned long long call = epoch[EPOCH_DRAW];   // left by the draw
     const uint64_t turn = epoch[EPOCH_BITMAP_CUR];
@@ -218,23 +224,38 @@ __global__ __launch_bounds__(256) void hits(const int32_t *__restrict__ cand_id,
         if (n_words == 0) *n_next = 0;
     }
     for (int64_t i = (int64_t)blockIdx.x * 256 + tid; i < old_words; i += (int64_t)gridDim.x * 256) old_bits[i] = 0ull;
-    int64_t wpb = (n_words + gridDim.x - 1) / gridDim.x;
+    int64_t wpb = ((n_words + gridDim.x - 1) / gridDim.x + 1) / 2 * 2;   // even
     if (wpb < HIT_MIN_WORDS) wpb = HIT_MIN_WORDS;
     const int64_t w0 = (int64_t)blockIdx.x * wpb, w1 = w0 + wpb < n_words ? w0 + wpb : n_words;
     if (w0 >= n_words) return;
     const uint64_t rank_tag = (call & 0xFFFFFFFFull) << 32;
     uint64_t word = w0 + (tid >> 2) < w1 ? bits[w0 + (tid >> 2)] : 0ull;
     uint32_t before = 0;   // bits set before w0 (then before the words at hand)
+    const bool chained = n_words > HIT_COUNT_WORDS;
     {
+        // pairs of words (w0 is even; behind an odd last word lies a zero), eight loads per thread on their way at a time
+        const ulonglong2 *__restrict__ pairs = reinterpret_cast<const ulonglong2 *>(bits);
+        const int64_t end = ((chained ? w1 : w0) + 1) / 2;
         uint32_t c = 0;
-        int64_t i = tid;
-        for (; i + 3 * 256 < w0; i += 4 * 256) {   // four loads on their way at a time
-            const uint64_t a = bits[i], b = bits[i + 256], d = bits[i + 512], e = bits[i + 768];
-            c += (uint32_t)(__popcll(a) + __popcll(b) + __popcll(d) + __popcll(e));
+        for (int64_t i = (chained ? w0 / 2 : 0) + tid; i < end; i += 8 * 256) {
+            ulonglong2 v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = pairs[i + k * 256 < end ? i + k * 256 : i];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) c += i + k * 256 < end ? (uint32_t)(__popcll(v[k].x) + __popcll(v[k].y)) : 0u;
         }
-        for (; i < w0; i += 256) c += (uint32_t)__popcll(bits[i]);
         c = wave_sum(c);
         if (lane == 0) s_before[wave] = c;
+    }
+    if (chained) {
+        const TileState<1> ts(ts_mem, HIT_GRID, wait_limit(epoch));
+        const unsigned long long tag = call_tag(call, SLOT_HITS);
+        __syncthreads();
+        const unsigned long long local[1] = {(unsigned long long)s_before[0] + s_before[1] + s_before[2] + s_before[3]};
+        unsigned long long excl[1];
+        lookback_publish<1>(ts, tag, blockIdx.x, local);
+        lookback_resolve<1>(ts, tag, blockIdx.x, (n_words + wpb - 1) / wpb, local, excl, s_lb, status);
+        before = (uint32_t)excl[0];
     }
     for (int64_t ws = w0; ws < w1; ws += SUB) {
         if (ws > w0) word = ws + (tid >> 2) < w1 ? bits[ws + (tid >> 2)] : 0ull;
@@ -243,7 +264,7 @@ __global__ __launch_bounds__(256) void hits(const int32_t *__restrict__ cand_id,
         const uint32_t incl = wave_inclusive_scan(cnt);
         if (lane == WAVE - 1) s_cnt[wave] = incl;
         __syncthreads();
-        if (ws == w0) before = s_before[0] + s_before[1] + s_before[2] + s_before[3];
+        if (ws == w0 && !chained) before = s_before[0] + s_before[1] + s_before[2] + s_before[3];
         uint32_t at = incl - cnt, n_hits = 0;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -775,7 +796,7 @@ extern "C" int csgs_draw_nodes(int64_t n_nodes, const int32_t *cand_id, const ui
     const int64_t hit_blocks = (cap_words + HIT_MIN_WORDS - 1) / HIT_MIN_WORDS;
     CSGS_LAUNCH(K_HITS, hits, dim3((unsigned)(hit_blocks < HIT_GRID ? hit_blocks : HIT_GRID), 1, nz), dim3(256), st, cand_id,
                 cdf, stats, cand_cap, n_nodes, B, w.epoch, w.hit, w.cbitmap[0], w.cbitmap[1], w.rank, w.member, S_next, mult, p_incl,
-                w.pdbl, n_next, is);
+                w.pdbl, n_next, w.hit_ts, status, is);
     CSGS_LAUNCH_CHECK();
     ws->has_draw = 1;
     ws->draw_B = B;

@@ -86,6 +86,8 @@ def test_aggregate_long_rows(dev, F, bf16, ld):
 @pytest.mark.parametrize("n_nodes,cases", [(1, ((1, 5),)), (1100, ((64, 3), (1023, 900), (65, 4000), (1, 7), (1025, 256))),
                                            (600_000, ((524_288, 3000), (524_289, 5000), (1025, 20_000), (600_000, 70_000))),
                                            (2_200_000, ((2_097_153, 9000), (2_200_000, 1), (100, 100))),
+                                           # ... and where the prefix comes from the scan across blocks (beyond 49152 words)
+                                           (3_300_000, ((3_145_728, 9000), (3_145_729, 9000), (1000, 500), (3_300_000, 100_000), (3_200_001, 1))),
                                            # ... and around the 256 samples of the CDF and the 128 draws of a block
                                            (1100, ((255, 127), (256, 128), (257, 129), (511, 300), (512, 300), (513, 300))),
                                            (70_000, ((2047, 4000), (2049, 4000), (16_641, 4000), (65_537, 4000)))])

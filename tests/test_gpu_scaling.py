@@ -106,3 +106,24 @@ def test_sampled_adjacency_of_hub_rows(dev):
         chain.assert_close(av[:want.adj_nnz].cpu().numpy(), want.adj_val, chain.P_RTOL, 0.0, "adj_val")
     print(f"[adjacency] ordinary {us[0]:.1f} us, hubs {us[1]:.1f} us")
     assert us[1] < 2.0 * us[0]
+
+
+# The compaction of the drawn positions reads a bitmap of one bit per candidate: sixteen times the candidates, sixteen times
+# the bits at most.
+def test_draw_from_many_candidates(dev):
+    from paper_2101_07706_amd import csgs, pipeline
+    B, us = 8192, []
+    for n_c in (16_000_000, 256_000_000):
+        print(f"[draw] {n_c} candidates", flush=True)
+        ws = pipeline.Workspace(n_c, 1, B, 1, dev)
+        ids = torch.arange(n_c, dtype=torch.int32, device=dev)
+        cdf = torch.arange(1, n_c + 1, dtype=torch.int64, device=dev) * 1000003
+        st = torch.frombuffer(bytearray(bytes(csgs.ProbStats(n_cand=n_c, total=n_c * 1000003))), dtype=torch.int64).to(dev)
+        i32 = lambda k: torch.zeros(k, dtype=torch.int32, device=dev)
+        S_next, mult, n_next, status, p = i32(B), i32(B), i32(1), i32(1), torch.zeros(B, dtype=torch.float32, device=dev)
+        us.append(_least_us(lambda: csgs.csgs_draw_nodes(n_c, ids, cdf, st, B, 5, 1, 0, S_next, mult, p, n_next, ws.desc, status), ("hits",)))
+        m = int(n_next.item())
+        assert int(status.item()) == 0 and int(mult[:m].sum().item()) == B and bool((S_next[1:m] > S_next[:m - 1]).all())
+        del ws, ids, cdf
+    print(f"[draw] {us[0]:.1f} us, {us[1]:.1f} us")
+    assert us[1] < 8.0 * us[0]
