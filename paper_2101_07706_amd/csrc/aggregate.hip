@@ -159,17 +159,20 @@ __global__ __launch_bounds__(256) void adjT_count(const int32_t *__restrict__ ad
     }
 }
 
-// colptr = exclusive prefix of counts.  A block takes PREFIX_COLS columns and adds up all counts before them itself (4 bytes
-// per column, from the L2s): nobody waits, and 7.4 K columns are four blocks instead of one that goes round by 8192 (11 -> 6 us).
+// colptr = exclusive prefix of counts.  A block takes `rounds` times PREFIX_COLS columns and adds up all counts before them
+// itself (4 bytes per column, from the L2s): nobody waits, and 4 K columns are two blocks instead of one that goes round by 8192
+// (7.2 -> 4.2 us; 131 K columns 167 -> 18).  Blocks re-read what lies before them, so there are PREFIX_GRID of them at most and
+// each takes several rounds (64 M columns, one block / a block per 2048 columns / this: 88 / 551 / 13 ms).
 constexpr int PREFIX_COLS = 2048;
+constexpr int64_t PREFIX_GRID = 512;
 __global__ __launch_bounds__(256) void adjT_prefix(const int32_t *__restrict__ counts, int32_t n_cols_bound,
-                                                   const int32_t *__restrict__ n_cols_dev, int32_t *__restrict__ colptr)
+                                                   const int32_t *__restrict__ n_cols_dev, int32_t *__restrict__ colptr, int32_t rounds)
 {
     __shared__ int32_t lds[17];
     __shared__ int32_t s_before[4];
     const int32_t n_cols = resolve_count(n_cols_bound, n_cols_dev);
     const int tid = (int)threadIdx.x;
-    const int64_t first = (int64_t)blockIdx.x * PREFIX_COLS;
+    const int64_t first = (int64_t)blockIdx.x * rounds * PREFIX_COLS;
     if (first >= n_cols) {
         if (first == 0 && tid == 0) colptr[0] = 0;
         return;
@@ -188,38 +191,43 @@ __global__ __launch_bounds__(256) void adjT_prefix(const int32_t *__restrict__ c
             sum_before += p.x + p.y + p.z + p.w;
         }
     }
-    const int64_t c0 = first + tid * 8;
-    int32_t v[8], sum = 0;
-    if (c0 + 8 <= n_cols) {
-        const int4 p = *reinterpret_cast<const int4 *>(counts + c0), q = *reinterpret_cast<const int4 *>(counts + c0 + 4);
-        v[0] = p.x; v[1] = p.y; v[2] = p.z; v[3] = p.w;
-        v[4] = q.x; v[5] = q.y; v[6] = q.z; v[7] = q.w;
-    } else {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = c0 + k < n_cols ? counts[c0 + k] : 0;
-    }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) sum += v[k];
     sum_before = wave_sum(sum_before);
     if ((tid & (WAVE - 1)) == 0) s_before[tid >> 6] = sum_before;
-    int32_t total;
-    int32_t ex = block_exclusive_scan<int32_t>(sum, lds, &total);
-    __syncthreads();
-    ex += s_before[0] + s_before[1] + s_before[2] + s_before[3];
-    if (c0 + 8 <= n_cols) {
-        int32_t o[8];
+    int32_t base = 0;   // of the round's first column
+    for (int32_t round = 0; round < rounds; ++round) {
+        const int64_t c0 = first + (int64_t)round * PREFIX_COLS + tid * 8;
+        if (c0 - tid * 8 >= n_cols) break;   // the whole block
+        int32_t v[8], sum = 0;
+        if (c0 + 8 <= n_cols) {
+            const int4 p = *reinterpret_cast<const int4 *>(counts + c0), q = *reinterpret_cast<const int4 *>(counts + c0 + 4);
+            v[0] = p.x; v[1] = p.y; v[2] = p.z; v[3] = p.w;
+            v[4] = q.x; v[5] = q.y; v[6] = q.z; v[7] = q.w;
+        } else {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) { o[k] = ex; ex += v[k]; }
-        *reinterpret_cast<int4 *>(colptr + c0) = make_int4(o[0], o[1], o[2], o[3]);
-        *reinterpret_cast<int4 *>(colptr + c0 + 4) = make_int4(o[4], o[5], o[6], o[7]);
-    } else {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            if (c0 + k < n_cols) colptr[c0 + k] = ex;
-            ex += v[k];
+            for (int k = 0; k < 8; ++k) v[k] = c0 + k < n_cols ? counts[c0 + k] : 0;
         }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) sum += v[k];
+        int32_t total;
+        int32_t ex = block_exclusive_scan<int32_t>(sum, lds, &total);   // (its barriers are behind the stores of s_before)
+        if (round == 0) base = s_before[0] + s_before[1] + s_before[2] + s_before[3];
+        ex += base;
+        base += total;
+        if (c0 + 8 <= n_cols) {
+            int32_t o[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) { o[k] = ex; ex += v[k]; }
+            *reinterpret_cast<int4 *>(colptr + c0) = make_int4(o[0], o[1], o[2], o[3]);
+            *reinterpret_cast<int4 *>(colptr + c0 + 4) = make_int4(o[4], o[5], o[6], o[7]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                if (c0 + k < n_cols) colptr[c0 + k] = ex;
+                ex += v[k];
+            }
+        }
+        if (c0 < n_cols && c0 + 8 >= n_cols) colptr[n_cols] = ex;   // the thread of the last column
     }
-    if (c0 < n_cols && c0 + 8 >= n_cols) colptr[n_cols] = ex;   // the thread of the last column
 }
 
 // one wavefront per row of P~: entry (r, c, v) goes to slot colptr[c] + --left[c] of the unordered list
@@ -504,7 +512,9 @@ extern "C" int csgs_aggregate_grad(const int32_t *adj_rowptr, const int32_t *adj
     const unsigned rb = (unsigned)(((int64_t)nS + 3) / 4 < 4096 ? ((int64_t)nS + 3) / 4 : 4096);   // 4 rows (wavefronts) per block
     CSGS_LAUNCH(K_ADJT_COUNT, adjT_count, dim3(rb), dim3(256), st, adj_rowptr, adj_col, nS, nS_dev, n_cols, n_cols_dev, adj_cap, g.counts);
     CSGS_LAUNCH_CHECK();
-    CSGS_LAUNCH(K_ADJT_PREFIX, adjT_prefix, dim3((unsigned)(((int64_t)n_cols + PREFIX_COLS - 1) / PREFIX_COLS)), dim3(256), st, (const int32_t *)g.counts, n_cols, n_cols_dev, g.colptr);
+    const int64_t pieces = ((int64_t)n_cols + PREFIX_COLS - 1) / PREFIX_COLS, rounds = (pieces + PREFIX_GRID - 1) / PREFIX_GRID;
+    CSGS_LAUNCH(K_ADJT_PREFIX, adjT_prefix, dim3((unsigned)((pieces + rounds - 1) / rounds)), dim3(256), st, (const int32_t *)g.counts, n_cols, n_cols_dev,
+                g.colptr, (int32_t)rounds);
     CSGS_LAUNCH_CHECK();
     CSGS_LAUNCH(K_ADJT_FILL, adjT_fill, dim3(rb), dim3(256), st, adj_rowptr, adj_col, adj_val, nS, nS_dev, n_cols, n_cols_dev,
                 (const int32_t *)g.colptr, g.counts, g.unordered, adj_cap);

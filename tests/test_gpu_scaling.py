@@ -127,3 +127,24 @@ def test_draw_from_many_candidates(dev):
         del ws, ids, cdf
     print(f"[draw] {us[0]:.1f} us, {us[1]:.1f} us")
     assert us[1] < 8.0 * us[0]
+
+
+# The transpose of the aggregation gradient reads its columns' counts a bounded number of times.
+def test_gradient_with_many_columns(dev):
+    from paper_2101_07706_amd import csgs
+    nS, F, us = 4096, 8, []
+    gen = torch.Generator(device=dev).manual_seed(7)
+    for n_cols in (4_000_000, 64_000_000):
+        print(f"[aggregate grad] {n_cols} columns", flush=True)
+        rp = (torch.arange(nS + 1, device=dev) * 4).to(torch.int32)
+        col = torch.randperm(n_cols, generator=gen, device=dev)[:nS * 4].view(nS, 4).sort(1)[0].reshape(-1)   # a column of its own for every entry
+        val = torch.rand(nS * 4, generator=gen, device=dev)
+        dZ, dH = torch.randn((nS, F), generator=gen, device=dev), torch.full((n_cols, F), float("nan"), device=dev)
+        scratch = torch.empty(csgs.csgs_aggregate_grad_scratch_bytes(n_cols, nS * 4) // 8 + 32, dtype=torch.int64, device=dev)
+        c32 = col.to(torch.int32)
+        us.append(_least_us(lambda: csgs.csgs_aggregate_grad(rp, c32, val, None, dZ, None, dH, scratch), ("adjT_prefix",), 3))
+        want = (val[:, None].double() * dZ.double().repeat_interleave(4, 0)).float()
+        assert bool((dH[col] == want).all()) and int(torch.count_nonzero(dH).item()) == int(torch.count_nonzero(want).item())
+        del dH, scratch
+    print(f"[aggregate grad] {us[0]:.1f} us, {us[1]:.1f} us")
+    assert us[1] < 60.0 * us[0]
