@@ -73,12 +73,17 @@ __device__ inline Vec<8> load_row<uint16_t, 8>(const uint16_t *p)
                    __uint_as_float(v.w << 16), __uint_as_float(v.w & 0xFFFF0000u)}};
 }
 
-// Rows with more kept edges than this are taken by the whole block, after its tiles.  A wavefront with one or two lane groups
-// walks through a long row nearly alone (us, 256 everywhere / this: F = 100 bf16, 7283 rows, 32 lanes a row, 19 / 15; eight
-// of those 32 / 25; F = 602, 2048 rows of 26 edges, 64 lanes, 40 / 35; layers in one kernel 117 + 194 + 80 / 104 + 182 + 71);
-// half of that again is level.
+// Rows with more kept edges than LONG_ROW are taken by the whole block, after its tiles.  With 32 or 64 lanes per row, where a
+// wavefront walks through a long row nearly alone, so are rows of more than long_row<G>() (us, 256 everywhere / this: F = 100
+// bf16, 7283 rows, 32 lanes a row, 19 / 15; eight of those 32 / 25; F = 602, 2048 rows of 26 edges, 64 lanes, 40 / 35; layers in
+// one kernel 117 + 194 + 80 / 104 + 182 + 71; half of that again is level) -- in tiles of more than LONG_TILE rows only if they
+// hold more than LONG_SKEW times what the tile's other rows do on average: where all rows are long, each wavefront has enough
+// rows to walk through, and a block that takes them one after the other only adds its barriers (us, any such row / this: rows
+// of 65 edges, one-kernel layer, F = 128, 2048 rows 107 / 64; F = 100 bf16, 65536 rows 417 / 270; F = 504 bf16, 65536 rows
+// 727 / 641; 130 edges, F = 100 bf16, 65536 rows 477 / 347).
+constexpr int LONG_ROW = 256, LONG_SKEW = 3, LONG_TILE = 4;
 template <int G>
-constexpr int long_row() { return G >= 64 ? 64 : (G >= 32 ? 128 : 256); }
+constexpr int long_row() { return G >= 64 ? 64 : (G >= 32 ? 128 : LONG_ROW); }
 template <int V>
 constexpr int unr() { return V >= 8 ? 2 : 4; }   // gathered row pieces asked for at a time per lane (and as many again before those are used): 64 bytes
 constexpr int AGG_BLOCK = 256;  // threads per block.  Small blocks on purpose: beside kernels of other streams a 1024-thread
@@ -244,7 +249,16 @@ __device__ inline bool aggregate_tile(WaveStage<tile_rows(G), PL> &st, int tr, d
     const int32_t rbeg = adj_rowptr[row_c], rend = adj_rowptr[row_c + 1];
     const bool in_call = lane < tr && row < nS;
     const int32_t full_len = in_call ? rend - rbeg : 0;
-    const bool is_long = full_len > long_row<G>();
+    bool is_long = full_len > LONG_ROW;
+    if (long_row<G>() < LONG_ROW) {
+        bool skewed = true;
+        if (tr > LONG_TILE) {
+            const int32_t counted = full_len < 0 ? 0 : (full_len < 2 * LONG_ROW ? full_len : 2 * LONG_ROW);   // (its sum stays small)
+            const int32_t rest = wave_sum(counted) - counted, others = (int32_t)__popcll(__ballot(in_call)) - 1;
+            skewed = counted * others > LONG_SKEW * rest;
+        }
+        is_long = is_long || (full_len > long_row<G>() && skewed);
+    }
     const int32_t len = (is_long || full_len < 0) ? 0 : full_len;
     const int32_t incl = wave_inclusive_scan(len);
     if (lane < tr) {
@@ -449,7 +463,7 @@ __device__ inline bool aggregate_tile(WaveStage<tile_rows(G), PL> &st, int tr, d
     return is_long;
 }
 
-// Rows with more than long_row<G>() kept edges (hubs among the rows of S): the whole block works on one such row at
+// Long rows (hubs among the rows of S): the whole block works on one such row at
 // a time, each of its 256 / G lane groups takes a contiguous share of the row's edges, and the groups' sums are
 // added in a fixed order by lane exchanges and through LDS (the result does not depend on timing).  The edges come one per
 // lane, their columns and values asked for two rounds ahead and the source rows one, so that a round of 256 edges waits for

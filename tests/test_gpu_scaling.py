@@ -148,3 +148,32 @@ def test_gradient_with_many_columns(dev):
         del dH, scratch
     print(f"[aggregate grad] {us[0]:.1f} us, {us[1]:.1f} us")
     assert us[1] < 60.0 * us[0]
+
+
+# Rows a little longer than those that a wavefront walks through: a tenth more edges, not half as much time again.
+@pytest.mark.parametrize("fused,F,bf16,n_rows,short,longer", [(True, 128, False, 2048, 60, 66), (True, 128, False, 16_384, 60, 66), (False, 100, True, 65_536, 120, 132),
+                                                              (False, 504, True, 65_536, 60, 66)])
+def test_rows_of_equal_length(dev, fused, F, bf16, n_rows, short, longer):
+    from paper_2101_07706_amd import csgs
+    rng = np.random.default_rng(F)
+    n_cols, us = 100_000, []
+    X = rng.standard_normal((n_cols, F)).astype(np.float32)
+    Xh = synth.to_bf16_bits(X) if bf16 else X
+    Xd = torch.from_numpy(Xh.view(np.int16) if bf16 else Xh).to(dev)
+    W = rng.standard_normal((F, 64)).astype(np.float32)
+    Wd, t = torch.from_numpy(W).to(dev), lambda a: torch.from_numpy(a).to(dev)
+    for length in (short, longer):
+        print(f"[rows] {n_rows} of {length} edges, F={F} bf16={bf16} fused={fused}", flush=True)
+        rowptr = (np.arange(n_rows + 1) * length).astype(np.int32)
+        col, val = rng.integers(0, n_cols, n_rows * length).astype(np.int32), rng.standard_normal(n_rows * length).astype(np.float32)
+        rp, cd, vd = t(rowptr), t(col), t(val)
+        Z, H = torch.zeros((n_rows, F), device=dev), torch.zeros((n_rows, 64), device=dev)
+        if fused:
+            us.append(_least_us(lambda: csgs.csgs_layer_forward(rp, cd, vd, None, Xd, None, None, True, Wd, H, Z), ("layer_forward",)))
+        else:
+            us.append(_least_us(lambda: csgs.csgs_aggregate(rp, cd, vd, None, Xd, None, None, True, Z), ("aggregate",)))
+        few = 500
+        want = oracle.aggregate(rowptr[:few + 1], col[:few * length], val[:few * length], Xh, relu_on_input=True)
+        chain.assert_close(Z[:few].cpu().numpy(), want, chain.RTOL, chain.ATOL, f"{length} edges")
+    print(f"[rows] {us[0]:.1f} us, {us[1]:.1f} us")
+    assert us[1] < 1.3 * us[0]
