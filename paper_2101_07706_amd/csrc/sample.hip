@@ -312,8 +312,14 @@ __global__ __launch_bounds__(256) void hits(const int32_t *__restrict__ cand_id,
 // S_next ascends and the local partition is one id range, so the sampled remote nodes are the
 // entries before the first id >= lo and from the first id >= hi on: two searches give every
 // element its place, no scan needed.
-// Blocks of 256 threads that cover a budget of B in one sweep; larger ones are strided over.
-static int remote_blocks(int64_t B) { return (int)(B < 256 ? 1 : (B < 256 * 256 ? (B + 255) / 256 : 256)); }
+// Blocks of 256 threads that cover a budget of B and, a partition per wavefront, the P partitions in one sweep; more are
+// strided over.  (us of the one-pass adjacency, blocks by B alone / this: 200 draws, 1024 partitions 206 / 10, 256 partitions
+// 53 / 10.)
+static int remote_blocks(int64_t B, int64_t P)
+{
+    const int64_t n = (B + 255) / 256 > (P + 3) / 4 ? (B + 255) / 256 : (P + 3) / 4;
+    return (int)(n < 1 ? 1 : (n < 256 ? n : 256));
+}
 
 struct RemoteArgs {
     const int32_t *S_next, *n_next;
@@ -899,7 +905,7 @@ extern "C" int csgs_sample_layer(const csgs_graph *g, const int32_t *S, int32_t 
             return CSGS_EINVAL;
         rem = RemoteArgs{S_next, n_next, remote->local_lo, remote->local_hi, remote->part_bounds,
                          remote->per_part ? remote->P : 0, remote->remote_total, remote->per_part, remote->src_row,
-                         remote->remote_ids, remote_blocks(B)};
+                         remote->remote_ids, remote_blocks(B, remote->per_part ? remote->P : 0)};
     }
     const int rc = csgs_draw_nodes(g->n_nodes, cand_id, cdf, cand_cap, stats, B, seed, iter, iter_dev, layer, S_next, mult, p_incl,
                                    n_next, ws, status, stream);

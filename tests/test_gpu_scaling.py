@@ -177,3 +177,26 @@ def test_rows_of_equal_length(dev, fused, F, bf16, n_rows, short, longer):
         chain.assert_close(Z[:few].cpu().numpy(), want, chain.RTOL, chain.ATOL, f"{length} edges")
     print(f"[rows] {us[0]:.1f} us, {us[1]:.1f} us")
     assert us[1] < 1.3 * us[0]
+
+
+# The split of the node set just sampled, with as many partitions as nodes sampled and more: level with a few partitions.
+def test_remote_split_over_many_partitions(dev):
+    from paper_2101_07706_amd import csgs, pipeline
+    rng = np.random.default_rng(13)
+    n, B, us = 100_000, 200, []
+    g, _ = _hub_graph(rng, n, 10, 1, 10)
+    S = np.sort(rng.choice(n, B, replace=False)).astype(np.int32)
+    for P in (8, 1024, 1500):
+        print(f"[remote split] {P} partitions", flush=True)
+        g.part_bounds = synth.partition_bounds(n, P)
+        dg = pipeline.DeviceGraph(g, dev)
+        ws, lb = pipeline.Workspace(n, B, B, g.nnz, dev), pipeline.LayerBuffers(B, B, n, 64 * B, P, dev)
+        Sd = torch.from_numpy(S).to(dev)
+        us.append(_least_us(lambda: pipeline.sample_step(dg, ws, Sd, 4.0, B, 5, 3, 0, lb), ("adj_once",)))
+        m = int(lb.n_next.item())
+        want = oracle.remote_count(lb.S_next[:m].cpu().numpy(), g.local_lo, g.local_hi, g.part_bounds)
+        assert int(lb.status.item()) == 0 and int(lb.remote_total.item()) == want.remote_total
+        np.testing.assert_array_equal(lb.per_part[:P].cpu().numpy(), want.per_part)
+        np.testing.assert_array_equal(lb.src_row[:m].cpu().numpy(), want.src_row)
+    print("[remote split] " + ", ".join(f"{u:.1f} us" for u in us))
+    assert max(us[1:]) < 3.0 * us[0]
