@@ -121,7 +121,7 @@ typedef struct csgs_workspace {
     /* several instances per call, set by the caller (see below); 0 or 1 = one instance */
     int32_t n_inst;
     int32_t scan_mode;   /* how csgs_build_probs adds up the weights of local candidates: 0 = the library
-                            chooses (in LDS, tile by tile, when a call scans 160 K edges or more over its
+                            chooses (in LDS, tile by tile, where there are 128 K local edges or more over a call's
                             instances, else with device-scope atomics like the remote ones), 1 = always atomics,
                             2 = in LDS whenever the local range allows.  Same results. */
     int64_t inst_stride; /* bytes between consecutive instances' arrays; a multiple of 256 */

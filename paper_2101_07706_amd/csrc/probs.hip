@@ -63,16 +63,20 @@ struct Stage {
     int32_t lo, hi;     // local id range
     int32_t tiles;      // tiles of CAND_TILE ids that meet it (0: every edge goes through device-scope atomics)
     int32_t max_split;  // blocks launched per tile
-    int64_t min_chunks; // chunks from which edges are handed over
+    int32_t n_inst;     // instances of the launch
+    int32_t min_edges;  // local edges over all instances from which they are handed over
     unsigned long long *part;        // [tiles * max_split * CAND_TILE] sums of all but a tile's last block
     unsigned long long *part_flag;   // [tiles * max_split] tag of the call that left them
 };
-// Chunks of a call that hand their local edges over.  Decided from the chunks there are, by the scan and by the candidate
-// sums alike: the rows' degrees may be anything, whatever the graph's mean.
-__device__ inline int64_t handed_chunks(const Stage &stg, int64_t n_chunks)
+// A chunk hands its local edges over when a call whose chunks all had as many would have stg.min_edges of them: decided
+// chunk by chunk from what there is, as the rows' degrees and the share of local targets may be anything, whatever the
+// graph's mean and its partition.  Returns the local edges that a chunk must have (more than EDGE_TILE: no chunk).
+__device__ inline uint32_t hand_over_from(const Stage &stg, int64_t n_chunks)
 {
-    if (stg.tiles <= 0 || n_chunks < stg.min_chunks) return 0;
-    return n_chunks < stg.chunks ? n_chunks : stg.chunks;   // (chunks beyond the arrays go through atomics)
+    if (stg.tiles <= 0) return EDGE_TILE + 1;
+    const int64_t all = n_chunks * stg.n_inst;
+    if (all >= stg.min_edges) return stg.min_edges ? 1u : 0u;
+    return all > 0 ? ((uint32_t)stg.min_edges + (uint32_t)all - 1u) / (uint32_t)all : EDGE_TILE + 1;
 }
 constexpr unsigned long long HAND_OVER_WEIGHTS = 1ull << 54;   // a weight that an entry can hold beside the 10 bits of the id (larger ones go through atomics)
 
@@ -87,8 +91,8 @@ __device__ inline unsigned long long edge_weight(float v, double scale)
 
 // The weight scan, grid-stride over chunks of EDGE_TILE edges: stage the rows of the chunk, fetch column and value of
 // every edge, square, round.  An edge whose target lies outside the local id range is added to the per-node accumulator
-// with a device-scope atomic.  The others -- most edges: the partition holds most neighbors -- are, in calls with
-// enough edges, counting-sorted by the tile of their target inside the block and written to the chunk's piece of the
+// with a device-scope atomic.  The others -- most edges: the partition holds most neighbors -- are counting-sorted by the
+// tile of their target inside the block and, where there are enough of them, written to the chunk's piece of the
 // hand-over array: the next kernel has blocks per local tile, which add its groups up in LDS.  Scattered device-scope
 // atomics run at about 23 G/s on this part whatever their scope or target range, and those of the remote edges are what
 // bounds a large scan.  Integer sums: the result does not depend on which way an edge went or in what order.
@@ -102,7 +106,7 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
                                                   const int64_t *__restrict__ rowstart,
                                                   uint64_t *__restrict__ wtable, uint8_t *__restrict__ tileflag,
                                                   int2 *__restrict__ chunk_note, const int2 *__restrict__ bound_note,
-                                                  int32_t *__restrict__ status, Stage stg, InstStride is)
+                                                  uint64_t *__restrict__ epoch, int32_t *__restrict__ status, Stage stg, InstStride is)
 {
     constexpr int ITEMS = EDGE_TILE / 256;
     constexpr int BINS = SUB_MAX / WAVE;          // groups per lane of the counting sort
@@ -113,12 +117,14 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
     meta = inst_ptr(meta, is.ws); eoff = inst_ptr(eoff, is.ws); rowstart = inst_ptr(rowstart, is.ws);
     wtable = inst_ptr(wtable, is.ws); tileflag = inst_ptr(tileflag, is.ws); chunk_note = inst_ptr(chunk_note, is.ws); bound_note = inst_ptr(bound_note, is.ws);
     stg.e = inst_ptr(stg.e, is.ws); stg.off = inst_ptr(stg.off, is.ws);
-    status = inst_ptr(status, is.buf);
+    status = inst_ptr(status, is.buf); epoch = inst_ptr(epoch, is.ws);
     const int32_t nS = (int32_t)meta[META_ROWS];
     const double scale = ldexp(1.0, shift_for_rows(shift_base, nS));
     const int64_t E = meta[META_EDGES];
     const int64_t n_chunks = (E + EDGE_TILE - 1) / EDGE_TILE;
-    const int64_t n_handed_chunks = handed_chunks(stg, n_chunks);
+    const uint32_t from = hand_over_from(stg, n_chunks);
+    const int64_t n_staged = from <= EDGE_TILE ? stg.chunks : 0;   // (chunks beyond the arrays go through atomics)
+    const unsigned long long call = call_number(epoch);
     const int32_t tile0 = stg.lo / CAND_TILE;
     const int lane = lane_id();
     const int wave = (int)(threadIdx.x >> 6);
@@ -128,7 +134,7 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
     for (int64_t t = blockIdx.x; t < n_chunks; t += gridDim.x) {
         const int64_t c0 = t * EDGE_TILE;
         const int64_t c1 = (c0 + EDGE_TILE < E) ? c0 + EDGE_TILE : E;
-        const bool staged = t < n_handed_chunks;
+        const bool staged = t < n_staged;
         if (staged)
             for (int i = threadIdx.x; i < SUB_MAX; i += blockDim.x) hist[i] = 0u;   // (its last readers are a barrier behind)
         stage_slice_bounds(slice, eoff, rowstart, nS, t, c0, c1, bound_note, chunk_note + t);   // (starts and ends with a barrier)
@@ -188,26 +194,35 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
                     sum += cnt[i];
                 }
                 const uint32_t incl = wave_inclusive_scan<uint32_t>(sum);
+                const uint32_t n_local = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1);
+                const bool take = n_local >= from;
                 uint32_t ex = incl - sum;
 #pragma unroll
                 for (int i = 0; i < BINS; ++i) {
                     hist[lane * BINS + i] = ex;
-                    if (lane * BINS + i <= stg.tiles) stg.off[t * SUB_STRIDE + lane * BINS + i] = (uint16_t)ex;
+                    if (lane * BINS + i <= stg.tiles) stg.off[t * SUB_STRIDE + lane * BINS + i] = (uint16_t)(take ? ex : 0u);
                     ex += cnt[i];
                 }
                 if (lane == WAVE - 1) {   // edges handed over by this chunk
-                    hist[SUB_MAX] = incl;
-                    if (stg.tiles == SUB_MAX) stg.off[t * SUB_STRIDE + SUB_MAX] = (uint16_t)incl;
+                    hist[SUB_MAX] = take ? n_local : 0u;
+                    if (stg.tiles == SUB_MAX) stg.off[t * SUB_STRIDE + SUB_MAX] = (uint16_t)(take ? n_local : 0u);
+                    if (take && n_local) epoch[EPOCH_HANDED] = call;   // same value from every writer
                 }
             }
             __syncthreads();
-            // grouped in LDS first, then out in order: full 64-byte pieces instead of one scattered store per edge
-#pragma unroll
-            for (int k = 0; k < ITEMS; ++k)
-                if (hb[k] >= 0) s_e[hist[hb[k]] + hr[k]] = qk[k] * CAND_TILE + (unsigned)(ck[k] % CAND_TILE);   // < EDGE_TILE: the groups partition the chunk's local edges
-            __syncthreads();
             const uint32_t n_handed = hist[SUB_MAX];
-            for (uint32_t i = threadIdx.x; i < n_handed; i += blockDim.x) stg.e[t * EDGE_TILE + i] = s_e[i];
+            if (n_handed) {
+                // grouped in LDS first, then out in order: full 64-byte pieces instead of one scattered store per edge
+#pragma unroll
+                for (int k = 0; k < ITEMS; ++k)
+                    if (hb[k] >= 0) s_e[hist[hb[k]] + hr[k]] = qk[k] * CAND_TILE + (unsigned)(ck[k] % CAND_TILE);   // < EDGE_TILE: the groups partition the chunk's local edges
+                __syncthreads();
+                for (uint32_t i = threadIdx.x; i < n_handed; i += blockDim.x) stg.e[t * EDGE_TILE + i] = s_e[i];
+            } else {
+#pragma unroll
+                for (int k = 0; k < ITEMS; ++k)
+                    if (hb[k] >= 0) hb[k] = -2;
+            }
         }
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
@@ -221,10 +236,11 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
     if (bad) atomicOr(status, CSGS_ST_BAD_EDGE_VALUE);
 }
 
-// The hand-over is taken from this many chunks on (over all instances of a launch, each taken to have as many as the one at
-// hand): below, the atomics hide in the scan's latency (scan + candidate sums, atomics / hand-over: 75 chunks 18 / 19 us, 1004 chunks
-// 56 / 33, 426 chunks 36 / 24).
-constexpr int64_t HAND_OVER_MIN_CHUNKS = 160;
+// Fewer local edges than this over all instances of a launch hide their atomics in the scan's latency, and the sums of what was
+// handed over cost more (us for scan + candidate sums, atomics / hand-over, four edges in five local: 75 chunks 18 / 19, 426
+// chunks 36 / 24, 1004 chunks 56 / 33; one in two: 200 chunks 20 / 21, 400 chunks 30 / 27; one in eight: 200 chunks 21 / 24, 800
+// chunks 50 / 53; one in 64: 800 chunks 50 / 68).
+constexpr int32_t HAND_OVER_MIN_EDGES = 128 * EDGE_TILE;
 // A tile's sums are split over several blocks while each block has this many edges left and the launch has SPLIT_BLOCKS
 // of them at most, two per compute unit: a narrow local range has few tiles (29 tiles, 1 M edges: 31 us with a block
 // per tile, 16 split by 7), and 150 tiles leave compute units idle (5.4 M edges: 49 / 40 us).  Shares below that only
@@ -378,7 +394,11 @@ __global__ __launch_bounds__(CAND_PART_BLOCK) void cand_partials(uint64_t *__res
     }
     if (t1 > n_tiles) t1 = n_tiles;
     if (t0 >= t1) return;   // the whole block
-    const uint32_t n_chunks = own ? (uint32_t)handed_chunks(stg, (meta[META_EDGES] + EDGE_TILE - 1) / EDGE_TILE) : 0u;   // at most STAGE_EDGES_MAX / EDGE_TILE
+    uint32_t n_chunks = 0;   // that may have handed edges over
+    if (own && epoch[EPOCH_HANDED] == call_number(epoch)) {
+        const int64_t all = (meta[META_EDGES] + EDGE_TILE - 1) / EDGE_TILE;
+        n_chunks = (uint32_t)(all < stg.chunks ? all : stg.chunks);   // at most STAGE_EDGES_MAX / EDGE_TILE
+    }
     const bool sums = n_chunks > 0;
     // The last `split` of a tile's blocks share its sums, the others leave (all but the last where nothing was handed over).
     uint32_t split = 1;
@@ -798,8 +818,8 @@ static int build_probs_impl(const csgs_graph *g, const int32_t *S, int32_t nS, c
     // tiles that meet the local id range, when the hand-over can cover them and is wanted
     const bool range_ok = g->local_hi > g->local_lo && g->local_lo >= 0 && g->local_hi <= g->n_nodes;
     const int64_t tile0 = range_ok ? g->local_lo / CAND_TILE : 0, tile1 = range_ok ? ((int64_t)g->local_hi - 1) / CAND_TILE + 1 : 0;
-    const int64_t min_chunks = ws->scan_mode == 2 ? 0 : (HAND_OVER_MIN_CHUNKS + w.n_inst - 1) / w.n_inst;
-    const bool hand = ws->scan_mode != 1 && w.chunk_cap >= min_chunks;
+    const int32_t min_edges = ws->scan_mode == 2 ? 0 : HAND_OVER_MIN_EDGES;
+    const bool hand = ws->scan_mode != 1 && w.chunk_cap * EDGE_TILE * w.n_inst >= min_edges;
     const int32_t tiles = (hand && tile1 - tile0 <= SUB_MAX) ? (int32_t)(tile1 - tile0) : 0;
     // Blocks per tile: what the expected chunks can use, at least two and a block per compute unit in all, in case the rows hold
     // more.  (Not as many as there might ever be use for: idle ones cost a launch a few tenths of a us.)
@@ -815,10 +835,10 @@ static int build_probs_impl(const csgs_graph *g, const int32_t *S, int32_t nS, c
         if (split < 1) split = 1;
     }
     const Stage stg{w.stage, w.stage_off, w.stage_chunks, range_ok ? g->local_lo : 0, range_ok ? g->local_hi : 0, tiles, (int32_t)split,
-                    min_chunks, (unsigned long long *)w.split_sum, (unsigned long long *)w.split_flag};
+                    w.n_inst, min_edges, (unsigned long long *)w.split_sum, (unsigned long long *)w.split_flag};
     CSGS_LAUNCH(K_SCAN_EDGES, scan_edges, dim3((unsigned)chunks, 1, nz), dim3(256), st, g->colidx, g->val,
                 g->n_nodes, g->nnz, shift_base, rows.meta, w.chunk_cap * EDGE_TILE, rows.eoff, rows.rowstart, w.wtable,
-                w.tileflag, rows.chunk_note, rows.bound_note, status, stg, is);
+                w.tileflag, rows.chunk_note, rows.bound_note, w.epoch, status, stg, is);
     CSGS_LAUNCH_CHECK();
     const int64_t per = w.n_tiles * w.n_inst <= CAND_PART_ONE ? 1 : CAND_PART_TILES;
     const int64_t below = tiles ? (tile0 + per - 1) / per : 0;

@@ -200,3 +200,43 @@ def test_remote_split_over_many_partitions(dev):
         np.testing.assert_array_equal(lb.src_row[:m].cpu().numpy(), want.src_row)
     print("[remote split] " + ", ".join(f"{u:.1f} us" for u in us))
     assert max(us[1:]) < 3.0 * us[0]
+
+
+def _rows_by_target(rng, n, P, n_rows, degree, local_share):
+    """`n_rows` rows of `degree` edges, row i with local_share[i] of them in the local range [0, n / P); the other rows are empty."""
+    deg = np.zeros(n, np.int64)
+    S = np.sort(rng.choice(n, n_rows, replace=False)).astype(np.int32)
+    deg[S] = degree
+    rowptr = np.zeros(n + 1, np.int64)
+    np.cumsum(deg, out=rowptr[1:])
+    local = rng.random((n_rows, degree)) < np.asarray(local_share)[:, None]
+    col = np.where(local, rng.integers(0, n // P, (n_rows, degree)), rng.integers(n // P, n, (n_rows, degree)))
+    col.sort(axis=1)
+    return synth.Graph(n, rowptr, col.reshape(-1).astype(np.int32), np.full(n_rows * degree, 1.0 / degree, np.float32), synth.partition_bounds(n, P), 0, 1.0), S
+
+
+# Few local targets: what the library chooses is level with atomics for all.  Chunks with local targets only beside chunks
+# with hardly any: a call in which some chunks hand theirs over.
+@pytest.mark.parametrize("P,n_rows,shares,timed", [(64, 16_000, (1 / 64, 1 / 64), True), (8, 4000, (1 / 8, 1 / 8), False), (2, 4000, (1.0, 0.02), False),
+                                                   (2, 4000, (0.66, 0.64), False)])
+def test_weight_scan_by_local_share(dev, P, n_rows, shares, timed):
+    from paper_2101_07706_amd import csgs, pipeline
+    rng = np.random.default_rng(P + n_rows)
+    n = 400_000
+    g, S = _rows_by_target(rng, n, P, n_rows, 50, np.repeat(shares, n_rows // 2))
+    dg, Sd = pipeline.DeviceGraph(g, dev), torch.from_numpy(S).to(dev)
+    want = oracle.build_probs(g, S, 4.0)
+    n_c, us = len(want.cand_id), {}
+    for mode in (0, 1, 2):
+        print(f"[scan] {n_rows} rows, local shares {shares}, mode {mode}", flush=True)
+        ws, lb = pipeline.Workspace(n, n_rows, 1, g.nnz, dev, scan_mode=mode), pipeline.LayerBuffers(n_rows, 1, n, 1, 8, dev)
+        us[mode] = _least_us(lambda: csgs.csgs_build_probs(dg.c, Sd, 4.0, lb.cand_id, lb.cand_w, lb.cdf, None, lb.stats, ws.desc, lb.status),
+                             ("scan_edges", "cand_partials"))
+        assert int(lb.status.item()) == 0 and int(lb.stats_host().n_cand) == n_c
+        np.testing.assert_array_equal(lb.cand_id[:n_c].cpu().numpy(), want.cand_id)
+        np.testing.assert_array_equal(lb.cand_w[:n_c].cpu().numpy().view(np.uint64), want.cand_w)
+        np.testing.assert_array_equal(lb.cdf[:n_c].cpu().numpy().view(np.uint64), want.cdf)
+        assert int(torch.count_nonzero(ws.buf[:chain.csgs_clean_words(n)]).item()) == 0, "workspace not restored"
+    print("[scan] " + ", ".join(f"mode {m} {u:.1f} us" for m, u in us.items()))
+    if timed:
+        assert us[0] < 1.2 * us[1]
