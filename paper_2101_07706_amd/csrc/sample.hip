@@ -840,15 +840,18 @@ static int sampled_adjacency_impl(const csgs_graph *g, const int32_t *rows, int3
     }
     ws->has_next = nxt.blocks > 0;
     // The number of chunks is known on the device only.  Rows of the graph's mean degree are a guess that hubs can exceed
-    // many times over: it picks the path, and may ask for more blocks than the device holds over all instances but not for
-    // fewer (those without a chunk leave at once) unless the workspace describes fewer chunks.  (us, grid by the mean degree / as
-    // here: 256 rows of 5000 edges, mean degree 8, one pass 317 / 26; the 8192 rows of most edges in 2.4 M, 21 M edges of them,
-    // two passes 638 / 245.)
+    // many times over: it picks the path, and may ask for more blocks but not for fewer than the device holds (those without a
+    // chunk leave at once; two per compute unit over several instances, where they are not free) unless the workspace
+    // describes fewer chunks.  (us, grid by the mean degree / as here: 256 rows of 5000 edges, mean degree 8, one pass 317 / 26,
+    // eight instances of that 324 / 122; the 8192 rows of most edges in 2.4 M, 21 M edges of them, two passes 638 / 245.)
     const double guess = (double)n_rows * ((double)g->nnz / (double)g->n_nodes) / EDGE_TILE * 1.25 + 16.0;
     const int64_t expected = guess < (double)w.chunk_cap ? (int64_t)guess : w.chunk_cap;
-    auto blocks = [&](int64_t grid, int64_t chunks_each) {
-        const int64_t least = grid / w.n_inst, want = (expected + chunks_each - 1) / chunks_each, cap = (w.chunk_cap + chunks_each - 1) / chunks_each;
-        const int64_t n = want < least ? least : (want < grid ? want : grid);
+    auto blocks = [&](int64_t grid, int64_t chunks_each) {   // at most `grid`
+        const int64_t least = w.n_inst == 1 ? grid : 512 / w.n_inst;
+        int64_t n = (expected + chunks_each - 1) / chunks_each;
+        if (n < least) n = least;
+        if (n > grid) n = grid;
+        const int64_t cap = (w.chunk_cap + chunks_each - 1) / chunks_each;
         return (unsigned)(n < cap ? n : cap);
     };
     const unsigned nz = (unsigned)w.n_inst;
@@ -856,8 +859,7 @@ static int sampled_adjacency_impl(const csgs_graph *g, const int32_t *rows, int3
     const AdjGraph ag{g->colidx, g->val, g->n_nodes, g->nnz, cur.eoff, cur.rowstart, w.rank, w.member, w.pdbl};
     // after csgs_build_probs on the same rows the weight scan has left every chunk's row slice in the workspace
     if (expected * w.n_inst <= ADJ_ONCE_MAX) {
-        const int64_t once = w.chunk_cap < resident_grid(2) ? w.chunk_cap : resident_grid(2);
-        const dim3 grid_once((unsigned)(once + rem.blocks + nxt.blocks), 1, nz);
+        const dim3 grid_once(blocks(resident_grid(2), 1) + (unsigned)(rem.blocks + nxt.blocks), 1, nz);
         if (reuse_offsets)
             CSGS_LAUNCH(K_ADJ_ONCE, adj_once<true>, grid_once, dim3(256), st, ag, cur.meta, w.epoch, w.adj_ts, w.chunk_cap, cur.chunk_note,
                         adj_rowptr, adj_col, adj_val, adj_cap, adj_nnz, status, rem, nxt, is);
