@@ -121,8 +121,8 @@ typedef struct csgs_workspace {
     /* several instances per call, set by the caller (see below); 0 or 1 = one instance */
     int32_t n_inst;
     int32_t scan_mode;   /* how csgs_build_probs adds up the weights of local candidates: 0 = the library
-                            chooses (in LDS, tile by tile, where there are 128 K local edges or more over a call's
-                            instances, else with device-scope atomics like the remote ones), 1 = always atomics,
+                            chooses (in LDS, tile by tile, when a launch scans 160 K edges or more and enough of
+                            them are local, else with device-scope atomics like the remote ones), 1 = always atomics,
                             2 = in LDS whenever the local range allows.  Same results. */
     int64_t inst_stride; /* bytes between consecutive instances' arrays; a multiple of 256 */
 } csgs_workspace;
@@ -144,7 +144,7 @@ typedef struct csgs_workspace {
 size_t csgs_workspace_bytes(int64_t n_nodes, int32_t nS_max, int32_t B_max, int64_t edges_max);
 
 /* Size of the leading part of the workspace that is all-zero whenever no call is in flight
- * (accumulators, flags, bitmaps, rank table).  For tests and debugging. */
+ * (accumulators, flags, draw counters).  For tests and debugging. */
 size_t csgs_workspace_clean_bytes(int64_t n_nodes);
 
 /* Zero-fills the buffer of `ws` (a fill kernel, safe under graph capture).  Call once before the

@@ -63,20 +63,24 @@ struct Stage {
     int32_t lo, hi;     // local id range
     int32_t tiles;      // tiles of CAND_TILE ids that meet it (0: every edge goes through device-scope atomics)
     int32_t max_split;  // blocks launched per tile
+    int32_t adjacent;   // 1: a tile's blocks lie side by side (else one block of every tile after the other)
     int32_t n_inst;     // instances of the launch
-    int32_t min_edges;  // local edges over all instances from which they are handed over
+    int32_t min_chunks; // chunks over all instances from which edges are handed over (0: whatever a chunk holds)
     unsigned long long *part;        // [tiles * max_split * CAND_TILE] sums of all but a tile's last block
     unsigned long long *part_flag;   // [tiles * max_split] tag of the call that left them
 };
-// A chunk hands its local edges over when a call whose chunks all had as many would have stg.min_edges of them: decided
-// chunk by chunk from what there is, as the rows' degrees and the share of local targets may be anything, whatever the
-// graph's mean and its partition.  Returns the local edges that a chunk must have (more than EDGE_TILE: no chunk).
+// Local edges that a chunk must have to hand them over (more than EDGE_TILE: no chunk does).  Decided chunk by chunk from
+// what there is, as the rows' degrees and the share of local targets may be anything, whatever the graph's mean and its
+// partition.  What the hand-over saves grows with the local edges (their atomics, 23 G/s); what it costs is the sums' latency and
+// a piece for every chunk: about 2.4 us and 6 ns a chunk, which an eighth of the edges does not bring in and half of them
+// do from 160 chunks on.
 __device__ inline uint32_t hand_over_from(const Stage &stg, int64_t n_chunks)
 {
     if (stg.tiles <= 0) return EDGE_TILE + 1;
-    const int64_t all = n_chunks * stg.n_inst;
-    if (all >= stg.min_edges) return stg.min_edges ? 1u : 0u;
-    return all > 0 ? ((uint32_t)stg.min_edges + (uint32_t)all - 1u) / (uint32_t)all : EDGE_TILE + 1;
+    if (stg.min_chunks == 0) return 0u;
+    const int64_t all = n_chunks * stg.n_inst;   // every instance taken to have as many as the one at hand
+    if (all < stg.min_chunks) return EDGE_TILE + 1;
+    return EDGE_TILE / 7 + (all < 56 * EDGE_TILE ? 56u * EDGE_TILE / (uint32_t)all : 0u);
 }
 constexpr unsigned long long HAND_OVER_WEIGHTS = 1ull << 54;   // a weight that an entry can hold beside the 10 bits of the id (larger ones go through atomics)
 
@@ -236,11 +240,10 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
     if (bad) atomicOr(status, CSGS_ST_BAD_EDGE_VALUE);
 }
 
-// Fewer local edges than this over all instances of a launch hide their atomics in the scan's latency, and the sums of what was
-// handed over cost more (us for scan + candidate sums, atomics / hand-over, four edges in five local: 75 chunks 18 / 19, 426
-// chunks 36 / 24, 1004 chunks 56 / 33; one in two: 200 chunks 20 / 21, 400 chunks 30 / 27; one in eight: 200 chunks 21 / 24, 800
-// chunks 50 / 53; one in 64: 800 chunks 50 / 68).
-constexpr int32_t HAND_OVER_MIN_EDGES = 128 * EDGE_TILE;
+// Below this many chunks over all instances of a launch the atomics hide in the scan's latency (us for scan + candidate sums,
+// atomics / hand-over, four edges in five local: 75 chunks 18 / 19, 426 chunks 36 / 24, 1004 chunks 56 / 33; one in two: 200
+// chunks 20 / 21, 400 chunks 30 / 27; one in eight: 200 chunks 21 / 24, 800 chunks 50 / 53; one in 64: 800 chunks 50 / 68).
+constexpr int32_t HAND_OVER_MIN_CHUNKS = 160;
 // A tile's sums are split over several blocks while each block has this many edges left and the launch has SPLIT_BLOCKS
 // of them at most, two per compute unit: a narrow local range has few tiles (29 tiles, 1 M edges: 31 us with a block
 // per tile, 16 split by 7), and 150 tiles leave compute units idle (5.4 M edges: 49 / 40 us).  Shares below that only
@@ -292,7 +295,8 @@ constexpr int CAND_WORDS = CAND_TILE / WAVE;  // 16 words per tile, 4 per wave
 constexpr int CAND_PART_BLOCK = 512;
 // Tiles per block of the first kind.  While all blocks with one tile each are on the device together, they are quickest
 // (us per launch, four tiles / one: 4 tiles 6.6 / 5.2, 98 tiles 6.9 / 6.0, 256 tiles 7.5 / 5.6, 700 tiles 7.7 / 7.2); beyond
-// that their number costs more than it gives (2392 tiles 10.6 / 14.1, eight times that 51 / 84; two tiles 11.8 and 62).
+// that their number costs more than it gives (2392 tiles 10.6 / 14.1, eight times that 51 / 84; two tiles 11.8 and 62), and so
+// it does with several instances (64 of 4 tiles 6.3 / 11).
 constexpr int CAND_PART_TILES = 4;
 constexpr int64_t CAND_PART_ONE = 1024;
 
@@ -377,8 +381,9 @@ __global__ __launch_bounds__(CAND_PART_BLOCK) void cand_partials(uint64_t *__res
     const int32_t b = (int32_t)blockIdx.x - blocks_below;
     const int32_t own_blocks = stg.tiles * stg.max_split;   // at most SPLIT_BLOCKS
     const bool own = b >= 0 && b < own_blocks;
-    // one block of every tile after the other, so that those that leave are no more of one XCD's than of another's
-    const uint32_t round_own = own ? (uint32_t)b / (uint32_t)stg.tiles : 0u, tile_own = own ? (uint32_t)b % (uint32_t)stg.tiles : 0u;
+    const uint32_t per_step = stg.adjacent ? (uint32_t)stg.max_split : (uint32_t)stg.tiles;
+    const uint32_t step_own = own ? (uint32_t)b / per_step : 0u, rest_own = own ? (uint32_t)b % per_step : 0u;
+    const uint32_t tile_own = stg.adjacent ? step_own : rest_own, round_own = stg.adjacent ? rest_own : step_own;
     if (b < 0) {
         t0 = (int64_t)blockIdx.x * TILES;
         t1 = t0 + TILES;
@@ -438,14 +443,14 @@ __global__ __launch_bounds__(CAND_PART_BLOCK) void cand_partials(uint64_t *__res
     if (sums) {   // (what did not fit an entry, and ids of the tile outside the local range, have come through the table)
         sum_handed_over(acc, stg, (int32_t)tile_own, n_chunks * share / split, n_chunks);
         if (split > 1) {   // (the other shares' blocks were dispatched before and wait for nobody)
-            const int64_t first = b - (int64_t)share * stg.tiles;
+            const int64_t next = stg.adjacent ? 1 : stg.tiles, first = b - share * next;
             bool ok = true;
-            if (threadIdx.x < (unsigned)share) ok = wait_tag(&stg.part_flag[first + (int64_t)threadIdx.x * stg.tiles], tag, wait_limit(epoch));
+            if (threadIdx.x < (unsigned)share) ok = wait_tag(&stg.part_flag[first + threadIdx.x * next], tag, wait_limit(epoch));
             if (!ok) atomicOr(status, CSGS_ST_INTERNAL);
             __syncthreads();
             for (int i = threadIdx.x; i < CAND_TILE; i += CAND_PART_BLOCK) {
                 unsigned long long v = acc[i];
-                for (int k = 0; k < share; ++k) v += ld_relaxed(&stg.part[(first + (int64_t)k * stg.tiles) * CAND_TILE + i]);
+                for (int k = 0; k < share; ++k) v += ld_relaxed(&stg.part[(first + k * next) * CAND_TILE + i]);
                 acc[i] = v;
             }
             __syncthreads();
@@ -807,40 +812,50 @@ static int build_probs_impl(const csgs_graph *g, const int32_t *S, int32_t nS, c
     const unsigned nz = (unsigned)w.n_inst;
     const InstStride is = inst_stride(w);
     // The number of edges is known on the device only: rows of the graph's mean degree are a guess that hubs can exceed many
-    // times over.  What depends on the number is decided on the device, and there are never fewer blocks over all
-    // instances than the device holds (those without a chunk leave at once) unless the workspace describes fewer chunks.
+    // times over.  What depends on the number is decided on the device, and there are never fewer blocks than the device
+    // holds (those without a chunk leave at once) unless the workspace describes fewer chunks.  With several instances the
+    // least is a block per compute unit over all of them: there, blocks that leave are not free (eight instances of 14
+    // chunks, 32 blocks each 12 us, 64 blocks 14, 256 blocks 28).
     // (us for scan and sums, grid and hand-over by the mean degree / as here: 256 rows of 5000 edges, mean degree 8, 270 / 68;
     // the 1024 rows of most edges in 2.4 M, 6.4 M edges of them, 336 / 282.)
-    const double guess = (double)nS * ((double)g->nnz / (double)g->n_nodes) / EDGE_TILE * 1.25 + 16.0;
+    const double mean = (double)nS * ((double)g->nnz / (double)g->n_nodes) / EDGE_TILE, guess = mean * 1.25 + 16.0;
     int64_t chunks = guess < (double)SCAN_GRID ? (int64_t)guess : SCAN_GRID;
-    if (chunks < SCAN_GRID / w.n_inst) chunks = SCAN_GRID / w.n_inst;
+    const int64_t least = w.n_inst == 1 ? SCAN_GRID : SCAN_GRID / 8 / w.n_inst;
+    if (chunks < least) chunks = least;
     if (chunks > w.chunk_cap) chunks = w.chunk_cap;
     // tiles that meet the local id range, when the hand-over can cover them and is wanted
     const bool range_ok = g->local_hi > g->local_lo && g->local_lo >= 0 && g->local_hi <= g->n_nodes;
     const int64_t tile0 = range_ok ? g->local_lo / CAND_TILE : 0, tile1 = range_ok ? ((int64_t)g->local_hi - 1) / CAND_TILE + 1 : 0;
-    const int32_t min_edges = ws->scan_mode == 2 ? 0 : HAND_OVER_MIN_EDGES;
-    const bool hand = ws->scan_mode != 1 && w.chunk_cap * EDGE_TILE * w.n_inst >= min_edges;
+    const int32_t min_chunks = ws->scan_mode == 2 ? 0 : HAND_OVER_MIN_CHUNKS;
+    // With several instances the blocks that a hand-over needs are launched only where it is to be expected (eight instances of
+    // 13 chunks and 114 local tiles, the sums without / with them 14.4 / 16.6 us); rows that hold more go through atomics there.
+    const bool hand = ws->scan_mode != 1 && (w.n_inst == 1 ? (double)w.chunk_cap : mean * w.n_inst) >= (double)min_chunks;
     const int32_t tiles = (hand && tile1 - tile0 <= SUB_MAX) ? (int32_t)(tile1 - tile0) : 0;
-    // Blocks per tile: what the expected chunks can use, at least two and a block per compute unit in all, in case the rows hold
-    // more.  (Not as many as there might ever be use for: idle ones cost a launch a few tenths of a us.)
+    // Blocks per tile: what the expected chunks can use, and in case the rows hold more, a block per compute unit in all with
+    // one instance.  (Not as many as there might ever be use for: 150 idle ones cost a launch 1 us.)  Blocks of a tile that all
+    // have work lie side by side, an XCD taking the same chunks of all tiles (6.8 K chunks, 64 tiles 28 us, else 32); those of
+    // which some may leave do not, as the ones that stay would be on a few XCDs only.
     int64_t split = 1;
+    bool adjacent = true;
     if (tiles) {
         const int64_t each = (int64_t)tiles * w.n_inst;
-        split = (int64_t)fmin(guess, (double)w.stage_chunks) * EDGE_TILE / tiles / SPLIT_MIN_EDGES;
-        if (split < SPLIT_BLOCKS / 2 / each) split = SPLIT_BLOCKS / 2 / each;
-        if (split < 2) split = 2;
+        split = (int64_t)fmin(mean, (double)w.stage_chunks) * EDGE_TILE / tiles / SPLIT_MIN_EDGES;
+        if (w.n_inst == 1 && split < SPLIT_BLOCKS / 2 / tiles) {
+            split = SPLIT_BLOCKS / 2 / tiles;
+            adjacent = false;
+        }
         if (split > SPLIT_BLOCKS / each) split = SPLIT_BLOCKS / each;
         if (split > w.split_blocks / tiles) split = w.split_blocks / tiles;
         if (split > WAVE) split = WAVE;
         if (split < 1) split = 1;
     }
     const Stage stg{w.stage, w.stage_off, w.stage_chunks, range_ok ? g->local_lo : 0, range_ok ? g->local_hi : 0, tiles, (int32_t)split,
-                    w.n_inst, min_edges, (unsigned long long *)w.split_sum, (unsigned long long *)w.split_flag};
+                    adjacent ? 1 : 0, w.n_inst, min_chunks, (unsigned long long *)w.split_sum, (unsigned long long *)w.split_flag};
     CSGS_LAUNCH(K_SCAN_EDGES, scan_edges, dim3((unsigned)chunks, 1, nz), dim3(256), st, g->colidx, g->val,
                 g->n_nodes, g->nnz, shift_base, rows.meta, w.chunk_cap * EDGE_TILE, rows.eoff, rows.rowstart, w.wtable,
                 w.tileflag, rows.chunk_note, rows.bound_note, w.epoch, status, stg, is);
     CSGS_LAUNCH_CHECK();
-    const int64_t per = w.n_tiles * w.n_inst <= CAND_PART_ONE ? 1 : CAND_PART_TILES;
+    const int64_t per = w.n_inst == 1 && w.n_tiles <= CAND_PART_ONE ? 1 : CAND_PART_TILES;
     const int64_t below = tiles ? (tile0 + per - 1) / per : 0;
     const int64_t part_blocks = tiles ? below + tiles * split + (w.n_tiles + per - 1) / per - tile1 / per : (w.n_tiles + per - 1) / per;
     const dim3 part_grid((unsigned)part_blocks, 1, nz);

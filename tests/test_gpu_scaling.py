@@ -218,7 +218,7 @@ def _rows_by_target(rng, n, P, n_rows, degree, local_share):
 # Few local targets: what the library chooses is level with atomics for all.  Chunks with local targets only beside chunks
 # with hardly any: a call in which some chunks hand theirs over.
 @pytest.mark.parametrize("P,n_rows,shares,timed", [(64, 16_000, (1 / 64, 1 / 64), True), (8, 4000, (1 / 8, 1 / 8), False), (2, 4000, (1.0, 0.02), False),
-                                                   (2, 4000, (0.66, 0.64), False)])
+                                                   (2, 4000, (0.45, 0.41), False)])
 def test_weight_scan_by_local_share(dev, P, n_rows, shares, timed):
     from paper_2101_07706_amd import csgs, pipeline
     rng = np.random.default_rng(P + n_rows)
