@@ -77,11 +77,11 @@ __device__ inline Vec<8> load_row<uint16_t, 8>(const uint16_t *p)
 // wavefront walks through a long row nearly alone, so are rows of more than long_row<G>() (us, 256 everywhere / this: F = 100
 // bf16, 7283 rows, 32 lanes a row, 19 / 15; eight of those 32 / 25; F = 602, 2048 rows of 26 edges, 64 lanes, 40 / 35; layers in
 // one kernel 117 + 194 + 80 / 104 + 182 + 71; half of that again is level) -- in tiles of more than LONG_TILE rows only if they
-// hold more than LONG_SKEW times what the tile's other rows do on average: where all rows are long, each wavefront has enough
-// rows to walk through, and a block that takes them one after the other only adds its barriers (us, any such row / this: rows
-// of 65 edges, one-kernel layer, F = 128, 2048 rows 107 / 64; F = 100 bf16, 65536 rows 417 / 270; F = 504 bf16, 65536 rows
-// 727 / 641; 130 edges, F = 100 bf16, 65536 rows 477 / 347).
-constexpr int LONG_ROW = 256, LONG_SKEW = 3, LONG_TILE = 4;
+// hold more than LONG_SKEW times what the tile's rows that are not as long do on average: where all rows are long, each
+// wavefront has enough to walk through, and a block that takes them one after the other only adds its barriers (us, any
+// such row / this: rows of 65 edges, one-kernel layer, F = 128, 2048 rows 107 / 64; F = 100 bf16, 65536 rows 417 / 270; F = 504
+// bf16, 65536 rows 727 / 641; 130 edges, F = 100 bf16, 65536 rows 477 / 347).
+constexpr int LONG_ROW = 256, LONG_SKEW = 2, LONG_TILE = 4;
 template <int G>
 constexpr int long_row() { return G >= 64 ? 64 : (G >= 32 ? 128 : LONG_ROW); }
 template <int V>
@@ -253,9 +253,9 @@ __device__ inline bool aggregate_tile(WaveStage<tile_rows(G), PL> &st, int tr, d
     if (long_row<G>() < LONG_ROW) {
         bool skewed = true;
         if (tr > LONG_TILE) {
-            const int32_t counted = full_len < 0 ? 0 : (full_len < 2 * LONG_ROW ? full_len : 2 * LONG_ROW);   // (its sum stays small)
-            const int32_t rest = wave_sum(counted) - counted, others = (int32_t)__popcll(__ballot(in_call)) - 1;
-            skewed = counted * others > LONG_SKEW * rest;
+            const bool is_short = in_call && full_len <= long_row<G>();
+            const int32_t edges = wave_sum((is_short && full_len > 0) ? full_len : 0), rows = (int32_t)__popcll(__ballot(is_short));
+            skewed = (full_len < LONG_ROW ? full_len : LONG_ROW) * rows > LONG_SKEW * edges;
         }
         is_long = is_long || (full_len > long_row<G>() && skewed);
     }
