@@ -42,10 +42,11 @@ constexpr int META_EDGES_TRUE = 2;    // their true number
 
 // Words of workspace a single-pass scan over at most `tiles` tiles with nv sums per tile needs
 // (one tag word and nv sums per tile, and twice that per group of 64 tiles).
-__host__ __device__ inline size_t scan_state_words(int64_t tiles, int nv)
+__host__ __device__ constexpr size_t scan_state_words(int64_t tiles, int nv)
 {
     return (size_t)(1 + nv) * (size_t)(tiles + 2 * (tiles / 64 + 2));
 }
+static_assert(HIT_COUNT_WORDS * 64 / CAND_TILE >= (int64_t)scan_state_words(HIT_GRID, 1), "the hit compaction's scan state in cand_flag");
 
 struct RowOffsets {
     int64_t *eoff;       // [nS + 1] exclusive prefix of the degrees of the rows
@@ -67,14 +68,14 @@ struct Workspace {
     uint64_t *member;    // [(n_nodes + 31) / 32]  (tag << 32) | one bit per id of the word's 32: in S_next of the draw with that tag
     uint64_t *partial;   // [4 * n_tiles] per-tile candidate counts and weight sums
     uint64_t *gtot;      // [4 * ceil(n_tiles / 64)] the same per group of 64 tiles
-    uint64_t *cand_flag; // [n_tiles] tag of the call whose partial sums a tile holds
+    uint64_t *cand_flag; // [n_tiles] tag of the call whose partial sums a tile holds; in a draw with a long position bitmap the
+                         // scan state of the hit compaction (which keeps its sums apart from any tag)
     uint64_t *epoch;     // [EPOCH_WORDS] call counter and draw tag (see lookback.hpp); advanced on the device
     uint64_t *cbitmap[2]; // [ceil(n_nodes/64)] bit set = candidate position was drawn.  Draws take turns: the compaction of one
                          // clears what the one before set
     // per call.  The row offsets exist twice: while the adjacency pass of one layer reads one set,
     // its spare blocks prepare the other for the next layer (rows = the node set just sampled).
     RowOffsets rows[2];
-    uint64_t *hit_ts;    // scan state of the hit compaction's blocks (long position bitmaps)
     uint64_t *adj_ts;    // scan state of the edge chunks (1 sum per chunk of 1024 edges)
     uint32_t *adj_cnt;   // [chunk_cap] kept edges of every edge chunk | 1 << 31 when a row starts at the chunk's first edge
     uint64_t *rp_ts;     // scan state of the row tiles (1 sum per tile of ROW_TILE rows)
@@ -162,7 +163,6 @@ __host__ inline Workspace carve(void *base, int64_t n_nodes, int64_t nS_max, int
     w.cand_flag = (uint64_t *)take((size_t)w.n_tiles * 8);
     w.epoch = (uint64_t *)take(EPOCH_WORDS * 8);
     for (int b = 0; b < 2; ++b) w.cbitmap[b] = (uint64_t *)take(words * 8);
-    w.hit_ts = (uint64_t *)take(scan_state_words(HIT_GRID, 1) * 8);
     w.adj_ts = (uint64_t *)take(scan_state_words(w.chunk_cap, 1) * 8);
     w.adj_cnt = (uint32_t *)take((size_t)w.chunk_cap * 4);
     w.rp_tiles = (nS_max + ROW_TILE - 1) / ROW_TILE;

@@ -251,11 +251,12 @@ __global__ __launch_bounds__(256) void hits(const int32_t *__restrict__ cand_id,
         const TileState<1> ts(ts_mem, HIT_GRID, wait_limit(epoch));
         const unsigned long long tag = call_tag(call, SLOT_HITS);
         __syncthreads();
-        const unsigned long long local[1] = {(unsigned long long)s_before[0] + s_before[1] + s_before[2] + s_before[3]};
+        // (a count and one in the bits above it, so that no sum of these is ever taken for a tag)
+        const unsigned long long local[1] = {(1ull << 52) + s_before[0] + s_before[1] + s_before[2] + s_before[3]};
         unsigned long long excl[1];
         lookback_publish<1>(ts, tag, blockIdx.x, local);
         lookback_resolve<1>(ts, tag, blockIdx.x, (n_words + wpb - 1) / wpb, local, excl, s_lb, status);
-        before = (uint32_t)excl[0];
+        before = (uint32_t)excl[0];   // (positions: below 2^31)
     }
     for (int64_t ws = w0; ws < w1; ws += SUB) {
         if (ws > w0) word = ws + (tid >> 2) < w1 ? bits[ws + (tid >> 2)] : 0ull;
@@ -802,7 +803,7 @@ extern "C" int csgs_draw_nodes(int64_t n_nodes, const int32_t *cand_id, const ui
     const int64_t hit_blocks = (cap_words + HIT_MIN_WORDS - 1) / HIT_MIN_WORDS;
     CSGS_LAUNCH(K_HITS, hits, dim3((unsigned)(hit_blocks < HIT_GRID ? hit_blocks : HIT_GRID), 1, nz), dim3(256), st, cand_id,
                 cdf, stats, cand_cap, n_nodes, B, w.epoch, w.hit, w.cbitmap[0], w.cbitmap[1], w.rank, w.member, S_next, mult, p_incl,
-                w.pdbl, n_next, w.hit_ts, status, is);
+                w.pdbl, n_next, w.cand_flag, status, is);
     CSGS_LAUNCH_CHECK();
     ws->has_draw = 1;
     ws->draw_B = B;
