@@ -27,20 +27,29 @@ def _csr(rng, lens, n_cols):
     return rowptr, rng.integers(0, n_cols, int(rowptr[-1])).astype(np.int32), rng.standard_normal(int(rowptr[-1])).astype(np.float32)
 
 
-# F picks the lanes per row (4, 8, 16, 32, 64); the row counts lie at the ends of the ranges in which a wavefront takes
-# 2, 4, ..., 64 rows: 512 blocks of 4 wavefronts over all feature slices
-@pytest.mark.parametrize("F,bf16,rows", [(256, False, (1, 9, 2016, 2017, 4033, 8065, 16128, 16129)), (64, False, (1, 33, 16352, 16353, 65409)),
-                                         (128, False, (7, 4088, 4089, 65409)), (100, True, (3, 8176, 8177, 32705)),
-                                         (75, False, (1, 2045, 4089, 16369)),
-                                         (264, True, (1, 5, 8176, 8177, 16352, 16353)), (504, True, (700, 16353))])
-def test_aggregate_rows_per_wavefront(dev, F, bf16, rows):
+# F, its type and its slices pick the lanes per row (4, 8, 16, 32, 64).  A wavefront takes 8 rows per lane group (at most 64),
+# half as many until the launch has 512 blocks of four wavefronts: the row counts on both sides of every halving.
+def _rows_around_halvings(lanes, slices):
+    most, least = min(64 // lanes * 8, 64), max(64 // lanes // 2, 2)
+    edges, tr = [], most
+    while tr > least:
+        last = 4 * tr * ((512 + slices - 1) // slices - 1)     # rows with which `tr` rows a wavefront are too few blocks still
+        edges += [last, last + 1]
+        tr //= 2
+    return edges
+
+
+@pytest.mark.parametrize("F,bf16,lanes,slices,rows", [(32, False, 4, 1, (1, 65, 700)), (64, False, 8, 1, (1, 33)), (256, False, 8, 4, (1, 9)),
+                                                      (128, False, 16, 1, (7,)), (100, True, 32, 1, (3,)), (75, False, 64, 2, (1,)),
+                                                      (264, True, 64, 1, (1, 5)), (504, True, 64, 1, (700,))])
+def test_aggregate_rows_per_wavefront(dev, F, bf16, lanes, slices, rows):
     from paper_2101_07706_amd import csgs
     rng = np.random.default_rng(31 * F)
     n_cols = 3000
     X = rng.standard_normal((n_cols, F)).astype(np.float32)
     Xh = synth.to_bf16_bits(X) if bf16 else X
     Xd = torch.from_numpy(Xh.view(np.int16) if bf16 else Xh).to(dev)
-    for n in rows:
+    for n in rows + tuple(_rows_around_halvings(lanes, slices)):
         print(f"[aggregate] {n} rows, F={F} bf16={bf16}", flush=True)
         lens = rng.poisson(2, n)
         lens[rng.integers(0, n, 4)] = (0, 300, 257, 90)       # the block-wide path, and rows longer than a share
@@ -54,8 +63,8 @@ def test_aggregate_rows_per_wavefront(dev, F, bf16, rows):
         assert bool(torch.isnan(Z[n:]).all()), f"{n} rows: wrote past the last row"
 
 
-# Rows around the lengths from which a block takes them together (64, 128 or 256 by the lanes per row) and around its rounds
-# of 256 edges, in 1, 2, 3 and 5 feature slices; columns outside the table; output rows closer and further apart than 2^24
+# Rows around the lengths from which a block takes them together (256, and from 64 or 128 on by the lanes per row where the
+# tile's other rows are shorter) and around its rounds of 256 edges, in 1, 3, 4 and 5 feature slices; columns outside the table; output rows closer and further apart than 2^24
 @pytest.mark.parametrize("F,bf16,ld", [(256, False, 0), (300, False, 0), (602, False, 0), (100, True, 0), (640, True, 0), (264, True, 0), (504, True, 0),
                                        (64, False, (1 << 24) + 8),
                                        (64, False, (1 << 24) - 8)])

@@ -110,7 +110,7 @@ def run_instances(name, K, chained, batched):
 def test_dense_config_skew_sweep(dev, monkeypatch):
     """Dense-neighborhood config at full size (114 M edges), every output element by element, over
     the skew sweep; the bottom layer's remote count must fall as the skew grows.  Once more with the
-    weight scan forced through owner blocks (left to itself the library scans these sizes with atomics)."""
+    hand-over of local edges forced whatever a chunk holds (left to itself the library chooses it here chunk by chunk)."""
     from paper_2101_07706_amd import pipeline
     cfg = synth.CONFIGS["dense"]
     remote = []
@@ -198,10 +198,10 @@ def test_small_graphs(dev, n, avg_deg, nS, B, skew, lo, hi):
     chain.compare_chain(osteps, gsteps)
 
 
-# ---------------------------------------------------------------- weight scan through owner blocks
+# ---------------------------------------------------------------- weight scan with the hand-over forced
 @pytest.fixture
 def owner_scan(monkeypatch):
-    """Workspaces made during the test ask for the owner-block form of the weight scan whatever the size
+    """Workspaces made during the test ask for the hand-over of local edges to the candidate sums whatever the size
     (left to itself the library takes it only for launches of a million edges or more)."""
     from paper_2101_07706_amd import pipeline
     monkeypatch.setattr(pipeline, "DEFAULT_SCAN_MODE", 2)
@@ -210,7 +210,7 @@ def owner_scan(monkeypatch):
 @pytest.mark.parametrize("n,avg_deg,nS,B,skew,lo,hi", [
     (1, 0, 1, 1, 1.0, 0, 1), (70, 3, 1, 5, 2.0, 10, 40), (70, 3, 70, 500, 16.0, 0, 70), (1000, 8, 65, 64, 4.0, 300, 600),
     (5000, 40, 333, 257, 8.0, 0, 1250), (5000, 2, 1023, 1025, 2.5, 4000, 5000), (3000, 5, 17, 4100, 1.0, 1000, 1000),
-    (9000, 30, 2000, 700, 4.0, 100, 8900),     # several owner blocks, the last one partly outside the range
+    (9000, 30, 2000, 700, 4.0, 100, 8900),     # several local tiles, the first and the last one partly outside the range
 ])
 def test_small_graphs_owner_scan(dev, owner_scan, n, avg_deg, nS, B, skew, lo, hi):
     test_small_graphs(dev, n, avg_deg, nS, B, skew, lo, hi)
@@ -223,7 +223,7 @@ def test_configs_owner_scan(dev, owner_scan, name):
 
 
 def test_weight_scan_modes_agree_and_bad_mode_is_rejected(dev):
-    """The same call with scan_mode 1 (atomics) and 2 (owner blocks) writes identical candidates, weights and CDF."""
+    """The same call with scan_mode 1 (atomics) and 2 (hand-over) writes identical candidates, weights and CDF."""
     from paper_2101_07706_amd import csgs, pipeline
     cfg, g, X, Ws, S0 = chain.config_inputs("medium", 3)
     dg = pipeline.DeviceGraph(g, dev)
@@ -760,8 +760,8 @@ def test_layer_forward_instances_and_unsupported_widths(dev):
 
 @pytest.mark.parametrize("mean_len,device_count", [(2, False), (2, True), (24, False), (24, True)])
 def test_aggregate_many_rows(dev, mean_len, device_count):
-    """Calls with tens of thousands of rows: the kernel itself decides, by the mean number of kept edges per
-    row, whether leading blocks or the owning blocks take the long rows.  Both outcomes, rows of 0 to 400 edges."""
+    """Calls with tens of thousands of rows of 0 to 400 edges: short rows by their wavefront, those beyond the limit
+    by the whole block, among few and among many edges."""
     from paper_2101_07706_amd import csgs
     rng = np.random.default_rng(1000 + mean_len)
     n_rows, n_cols, F = 40000, 6000, 64
@@ -1450,8 +1450,8 @@ def test_failed_waits_end_normally_and_are_reported(dev, scan_mode):
     """Timeout path of the waits between blocks, forced from the host: with a poll limit of zero a
     wait that is not satisfied at once gives up.  Every kernel must still end (no hang, all accesses
     in bounds), the status word must say so, and after csgs_workspace_init the same workspace must
-    give exact results again.  Both forms of the weight scan (the owner blocks of the second wait for
-    the chunk blocks)."""
+    give exact results again.  Both forms of the weight scan (in the second a tile's last block waits for
+    the blocks that share its sums)."""
     from paper_2101_07706_amd import csgs, pipeline
     cfg, g, X, Ws, S0 = chain.config_inputs("medium")
     dg = pipeline.DeviceGraph(g, dev)
