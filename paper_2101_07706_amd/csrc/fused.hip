@@ -4,8 +4,8 @@
 //
 // A block of four wavefronts owns 32 consecutive rows of the sampled layer.
 //   1. Aggregation: each wavefront takes 8 of the rows, all 64 lanes spread over the (at most 256) input features
-//      of one gathered row at a time; sums in double in edge order, one rounding to float into the LDS tile.  Rows
-//      with more than 256 kept edges are taken by the whole block afterwards.  This is the code of csgs_aggregate
+//      of one gathered row at a time; sums in double in edge order, one rounding to float into the LDS tile.  Long
+//      rows (LONG_ROW, long_row<64>()) are taken by the whole block afterwards.  This is the code of csgs_aggregate
 //      with one lane group per wavefront.
 //   2. Product: wavefront w computes the 16-column tiles w, w + 4, ... of H for all 32 rows.  A comes from the LDS
 //      tile (two 128-bit reads per 16 rows and K chunk of 32, the k order permuted as in csgs_layer_gemm: lane group

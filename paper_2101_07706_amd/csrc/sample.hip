@@ -522,8 +522,9 @@ __device__ inline bool adj_leading_blocks(RemoteArgs &rem, NextRows &nxt, const 
 // Two passes over the edges' chunks, neither of which waits: the first does everything that costs lookups, with as many
 // blocks as the device holds; the second only adds up 4 bytes per chunk and copies what was kept.  Against the one pass
 // below, whose 512 resident blocks wait for each other's counts once per round (us per layer): 6.6 M edges 84 / 139, 4.1 M
-// 54 / 90, eight mini-batches of 380 K 35 / 41, 957 K 15 / 22; level at 413 K (16 / 15).  The first pass is bound by
-// its random lookups in the membership words (100 G edges/s).
+// 54 / 90, eight mini-batches of 380 K 35 / 41, 957 K 15 / 22; level at 413 K (16 / 15); beyond the 8 Mi edges whose kept ones
+// the first pass can leave, where the second looks up the rest again: 16.7 M 300 / 340, 33 M 645 / 720, 125 M 2310 / 3500.  The first
+// pass is bound by its random lookups in the membership words (100 G edges/s).
 // Most chunks (of all instances of a launch, as expected from the mean degree) for the one pass: 2 K edges 10.5 against 14
 // us, 52 K 10.1 / 13.8, 80 K 13.4 / 14.4; from 400 K on two passes are level or better.
 constexpr int ADJ_ONCE_MAX = 256;
