@@ -559,20 +559,34 @@ def roofline_of(kernels, name, traffic, k_inst):
     return r
 
 
-def load_traffic(workload, k_inst, one_kernel=False):
+def kernel_sources_hash(csrc=os.path.join(ROOT, "paper_2101_07706_amd", "csrc")):
+    """Twelve hex digits over the kernels' sources, without comments and white space: what a counter summary was taken on."""
+    import hashlib
+    import re
+    h = hashlib.sha256()
+    for name in sorted(os.listdir(csrc)):
+        code = re.sub(r"//[^\n]*|/\*.*?\*/", "", open(os.path.join(csrc, name)).read(), flags=re.S)
+        h.update((name + re.sub(r"\s+", "", code)).encode())
+    return h.hexdigest()[:12]
+
+
+def load_traffic(workload, k_inst, one_kernel=False, folder=os.path.join(ROOT, "profiles")):
     """HBM bytes per launch and kernel from the committed counter summary profiles/<workload>_step_hbm_traffic.txt
     (<workload>_step_layer_forward_hbm_traffic.txt for the schedule with csgs_layer_forward), if that summary was
-    taken with the same number of mini-batches per launch; else (None, why)."""
-    path = os.path.join(ROOT, "profiles", f"{workload}_step_{'layer_forward_' if one_kernel else ''}hbm_traffic.txt")
+    taken on these kernels and with the same number of mini-batches per launch; else (None, why)."""
+    import re
+    path = os.path.join(folder, f"{workload}_step_{'layer_forward_' if one_kernel else ''}hbm_traffic.txt")
     if not os.path.exists(path):
         return None, f"no counter summary for workload {workload} under profiles/"
     lines = open(path).read().splitlines()
-    import re
     m = re.search(r"(\d+) mini-batch(?:es)? per launch", lines[0]) if lines else None
     if not m:
         return None, f"{os.path.basename(path)} does not state its mini-batches per launch"
     if int(m.group(1)) != k_inst:
         return None, f"{os.path.basename(path)} was taken with {m.group(1)} mini-batches per launch, this run uses {k_inst}"
+    src = re.search(r"source hash of the kernels: ([0-9a-f]+)", "\n".join(lines))
+    if not src or src.group(1) != kernel_sources_hash():
+        return None, f"{os.path.basename(path)} was taken on other kernels ({src.group(1) if src else 'not stated'}, these are {kernel_sources_hash()})"
     table, in_table = {}, False
     for ln in lines:
         f = ln.split()
