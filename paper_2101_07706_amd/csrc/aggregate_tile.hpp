@@ -109,25 +109,26 @@ __device__ inline double widen(float x)
 template <typename T, int V, int G, bool RELU>
 __device__ inline void accumulate_staged(double (&acc)[V], const T *src, float w, int gbase, int32_t n_max, bool active, int32_t f)
 {
-    constexpr int UNR = 64 / V < G ? (64 / V < 16 ? 64 / V : 16) : (G < 16 ? G : 16);   // 64 registers of gathered values
+    // Eight pieces on their way per lane, and the weights fetched from their lanes when used: with sixteen of them for narrow
+    // vectors the kernel's registers held it to four blocks per compute unit instead of six, in launches without a long row
+    // too (us, sixteen / eight, F = 481, 68536 rows of 4.5 edges 149 / 123; F = 333 bf16, 95553 rows of 0.6 104 / 82; rows of
+    // 600 edges among 2000 of 5, F = 250, 19 / 21).
+    constexpr int UNR = G < 8 ? G : 8;
     const uint64_t p = src ? (uint64_t)(uintptr_t)(src + (f - (lane_id() % G) * V)) : (uint64_t)(uintptr_t)g_zero_row;
     const uint32_t lane_off = active ? (uint32_t)((lane_id() % G) * V * (int)sizeof(T)) : 0u;
     if (!src) w = 0.f;
     for (int32_t j0 = 0; j0 < n_max; j0 += UNR) {
         Vec<V> x[UNR];
-        float wj[UNR];
+        // (no load under a condition: an edge that must not count reads the zero row with weight 0, and the compiler
+        // keeps exact count of the loads in flight; UNR divides G: no lane of another group is read)
+#pragma unroll
+        for (int u = 0; u < UNR; ++u)
+            x[u] = load_row<T, V>(reinterpret_cast<const T *>((uintptr_t)(__shfl(p, gbase + j0 + u, WAVE) + lane_off)));
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
-            // (no load under a condition: an edge that must not count reads the zero row with weight 0, and the compiler
-            // keeps exact count of the loads in flight; UNR divides G: no lane of another group is read)
-            const int srcl = gbase + j0 + u;
-            wj[u] = __shfl(w, srcl, WAVE);
-            x[u] = load_row<T, V>(reinterpret_cast<const T *>((uintptr_t)(__shfl(p, srcl, WAVE) + lane_off)));
-        }
+            const float wj = __shfl(w, gbase + j0 + u, WAVE);
 #pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-#pragma unroll
-            for (int v = 0; v < V; ++v) acc[v] = fma((double)wj[u], widen<RELU>(x[u].x[v]), acc[v]);
+            for (int v = 0; v < V; ++v) acc[v] = fma((double)wj, widen<RELU>(x[u].x[v]), acc[v]);
         }
     }
 }

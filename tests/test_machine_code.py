@@ -9,6 +9,7 @@ import pytest
 from paper_2101_07706_amd import build
 
 OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+READELF = "/opt/rocm/llvm/bin/llvm-readelf"
 WIDE_STORE = re.compile(r"(global|flat|scratch|buffer)_store_(dwordx[34]|b96|b128)$")
 REG = re.compile(r"^([va])(?:(\d+)|\[(\d+):(\d+)\])$")
 
@@ -144,3 +145,23 @@ def test_carries_and_lane_exchanges_wait(functions):
                 bad.append(f"{name} {addr:#x}: {op} {args.strip()} -> {h}")
     assert n_carries > 100
     assert not bad, f"{len(bad)} reads too early:\n" + "\n".join(bad[:20])
+
+
+# Aggregations with one or two features a lane and 32 or 64 lanes a row: the registers leave room for the blocks that the LDS
+# holds (a block puts one wavefront on each of a compute unit's four units; 512 registers a lane in pieces of 8, 160 KB of LDS).
+def test_narrow_aggregations_fill_the_lds(functions, tmp_path):
+    if not os.path.exists(READELF):
+        pytest.skip("no llvm-readelf")
+    seen = 0
+    for j, obj in enumerate(_code_objects()):
+        path = tmp_path / f"{j}.elf"
+        path.write_bytes(obj)
+        notes = subprocess.run([READELF, "--notes", str(path)], stdout=subprocess.PIPE, text=True, check=True).stdout
+        for kernel in re.split(r"\n  - \.", notes):
+            name = re.search(r"\.name: +(\S+)", kernel)
+            if not name or not re.search(r"11aggregate_kI[ft]Li[12]ELi(32|64)E", name.group(1)):
+                continue
+            lds, regs = (int(re.search(rf"\.{key}: +(\d+)", kernel).group(1)) for key in ("group_segment_fixed_size", "vgpr_count"))
+            seen += 1
+            assert 512 // (-(-regs // 8) * 8) >= (160 << 10) // lds, f"{name.group(1)}: {regs} registers, {lds} bytes of LDS"
+    assert seen == 16
