@@ -80,8 +80,10 @@ __device__ inline Vec<8> load_row<uint16_t, 8>(const uint16_t *p)
 // hold more than LONG_SKEW times what the tile's rows that are not as long do on average: where all rows are long, each
 // wavefront has enough to walk through, and a block that takes them one after the other only adds its barriers (us, any
 // such row / this: rows of 65 edges, one-kernel layer, F = 128, 2048 rows 107 / 64; F = 100 bf16, 65536 rows 417 / 270; F = 504
-// bf16, 65536 rows 727 / 641; 130 edges, F = 100 bf16, 65536 rows 477 / 347).
-constexpr int LONG_ROW = 256, LONG_SKEW = 2, LONG_TILE = 4;
+// bf16, 65536 rows 727 / 641; 130 edges, F = 100 bf16, 65536 rows 477 / 347).  Tiles of LONG_TILE rows are made only where the
+// launch would not fill the compute units otherwise, and walking them leaves most of those idle; tiles of four rows do fill
+// them (us, any such row / this: 10000 rows of 66, F = 47, 55 / 30; 2000 of 66, F = 481, 68 / 52).
+constexpr int LONG_ROW = 256, LONG_SKEW = 2, LONG_TILE = 2;
 template <int G>
 constexpr int long_row() { return G >= 64 ? 64 : (G >= 32 ? 128 : LONG_ROW); }
 template <int V>
