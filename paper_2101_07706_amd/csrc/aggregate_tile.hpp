@@ -82,7 +82,9 @@ __device__ inline Vec<8> load_row<uint16_t, 8>(const uint16_t *p)
 // such row / this: rows of 65 edges, one-kernel layer, F = 128, 2048 rows 107 / 64; F = 100 bf16, 65536 rows 417 / 270; F = 504
 // bf16, 65536 rows 727 / 641; 130 edges, F = 100 bf16, 65536 rows 477 / 347).  Tiles of LONG_TILE rows are made only where the
 // launch would not fill the compute units otherwise, and walking them leaves most of those idle; tiles of four rows do fill
-// them (us, any such row / this: 10000 rows of 66, F = 47, 55 / 30; 2000 of 66, F = 481, 68 / 52).
+// them (us, any such row / this: 10000 rows of 66, F = 47, 55 / 30; 2000 of 66, F = 481, 68 / 52).  Nor does the mean decide in
+// a block of which no more than 5/6 are rows of the call: there the wavefronts without rows help (one-kernel layer, F = 128,
+// compared / this: 8 rows of 120 edges 85 / 26, 20 rows 90 / 55; a full block of such rows is level either way).
 constexpr int LONG_ROW = 256, LONG_SKEW = 2, LONG_TILE = 2;
 template <int G>
 constexpr int long_row() { return G >= 64 ? 64 : (G >= 32 ? 128 : LONG_ROW); }
@@ -255,7 +257,8 @@ __device__ inline bool aggregate_tile(WaveStage<tile_rows(G), PL> &st, int tr, d
     bool is_long = full_len > LONG_ROW;
     if (long_row<G>() < LONG_ROW) {
         bool skewed = true;
-        if (tr > LONG_TILE) {
+        const int64_t block_row0 = row0 - (int64_t)(threadIdx.x / WAVE) * tr;
+        if (tr > LONG_TILE && (nS - block_row0) * 6 > 5 * AGG_WAVES * tr) {
             const bool is_short = in_call && full_len <= long_row<G>();
             const int32_t edges = wave_sum((is_short && full_len > 0) ? full_len : 0), rows = (int32_t)__popcll(__ballot(is_short));
             skewed = (full_len < LONG_ROW ? full_len : LONG_ROW) * rows > LONG_SKEW * edges;

@@ -151,9 +151,9 @@ def test_gradient_with_many_columns(dev):
 
 
 # Rows a little longer than those that a wavefront walks through: a tenth more edges, not half as much time again.  (2000 rows with
-# F = 481: four rows a tile.)
+# F = 481: four rows a tile.)  A block of few rows: twice the edges in no more time, since all its wavefronts take part.
 @pytest.mark.parametrize("fused,F,bf16,n_rows,short,longer", [(True, 128, False, 2048, 60, 66), (True, 128, False, 16_384, 60, 66), (False, 100, True, 65_536, 120, 132),
-                                                              (False, 504, True, 65_536, 60, 66), (False, 481, False, 2000, 60, 66)])
+                                                              (False, 504, True, 65_536, 60, 66), (False, 481, False, 2000, 60, 66), (True, 128, False, 15, 60, 120)])
 def test_rows_of_equal_length(dev, fused, F, bf16, n_rows, short, longer):
     from paper_2101_07706_amd import csgs
     rng = np.random.default_rng(F)
