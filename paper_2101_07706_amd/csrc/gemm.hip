@@ -1,27 +1,31 @@
-// csgs_layer_gemm: H = Z W (Section 3, Eq. 1), fp32 in, fp32 out, fp64 matrix-core accumulation.
+// csgs_layer_gemm: H = Z W (Section 3, Eq. 1), fp32 in, fp32 out, fp64 matrix-core accumulation, and the two gradient
+// products of a layer.
 //
 // Why double: sampled rows carry 1/p_j discounts that compound over the layers, so the products
 // z*w of a near-cancelling output reach magnitude 10 and more while the tolerance is 1e-5
 // absolute.  fp32 MFMA with double master accumulators over runs of 32 k was measured to miss it
 // (5.9e-5 against 3.5e-5 allowed on one output of the largest configuration).  The operands are
-// widened to double after the LDS read (exact), products of two 24-bit mantissas are exact in
+// widened to double (exact), products of two 24-bit mantissas are exact in
 // double, and v_mfma_f64_16x16x4_f64 accumulates in double, so the only rounding is the final
 // conversion to float.
 //
-// Block tile BM (128, or 64 where that would leave too few blocks) x BN (64 or 32), K chunks of 32,
-// four wavefronts stacked along M, each owning a BM/4 x BN strip = BM/64 x BN/16 MFMA tiles of
-// 16 x 16.  Global -> register -> LDS with the next chunk's loads in flight during the current
-// chunk's MFMAs (two LDS buffers).  Every load of a tile is unconditional (a piece that does not
-// exist reads a clamped address and becomes zero on the way to LDS); a row count that lives on the
-// device gates only the early exit and the stores.
-//
-// LDS layout (fp32): A row-major [BM][36], B transposed [BN][36] (k contiguous, 16-byte aligned
-// rows whose stride of 36 words spreads 16 lanes' 128-bit reads over all 64 banks); in the
-// 128 x 64 blocks of the forward product B has rows of 32 words with the 16-byte columns swizzled
-// instead, which brings a block to 52-53 KB and three blocks onto a compute unit.  The k order
-// inside a chunk is permuted -- the lane group l / 16 = g feeds k = 8 g + s at step s, for both
-// operands alike, which leaves the sum unchanged -- so that every lane fetches the 8 values it
-// needs per operand row with two 128-bit LDS reads.
+// What bounds it, and why it has this form: v_mfma_f64_16x16x4_f64 occupies a SIMD for 29 ns (72 TFLOP/s over the device), and
+// the vector ALU stands still meanwhile: every vector instruction, of any wavefront, adds its own 1.8 ns (measured with adds,
+// conversions and FMAs beside the MFMAs, one and two wavefronts per SIMD).  So what counts is vector instructions per MFMA,
+// and the time until all SIMDs multiply.
+//  * A wavefront works for itself on a tile of 16 RT x 16 NT outputs: no LDS, no barrier.  Its operands come straight
+//    from L1 / L2 (16 bytes a cycle and compute unit), the next 32 k on their way while the current ones are multiplied.
+//  * The lane group l / 16 = g feeds k = 8 g + s at step s, for both operands alike, which leaves the sum unchanged.  A
+//    lane then needs 8 consecutive k of a row where the k lie side by side (two 16-byte loads), and NT (RT for Z^T)
+//    consecutive columns of 8 rows where the columns do (8 loads of up to 16 bytes); its NT results of a row go out in one store.
+//  * All addresses are an offset that a lane keeps from the start plus scalar arithmetic, so the only vector instructions in the loop are
+//    the conversions: RT + NT per RT * NT MFMAs.
+//  * Rows and columns that do not exist read the nearest ones that do and are not stored, so no operand needs a mask; a K that is no
+//    multiple of 32 takes its last k first, in steps of four.
+// With blocks of four wavefronts that staged 64 or 128 x 64 tiles in LDS (conversions by every wavefront, addresses in vector
+// registers, a barrier per 32 k) before: 4096 x 512 x 512 46 -> 37 us, 4096 x 300 x 512 36 -> 25, 4500 x 512 x 100 29 -> 13,
+// 8192 x 256 x 256 25 -> 20, 8192 x 256 x 47 12.2 -> 7.7, 2048 x 602 x 256 27 -> 15.5, 1024 x 256 x 256 9.5 -> 5.9,
+// 131072 x 256 x 256 278 -> 262, odd sizes (20000 x 301 x 201) 85 -> 53.
 //
 // Block ids are remapped so that consecutive tiles (same rows of Z, neighbouring column tiles)
 // land on the same XCD and share its L2.
@@ -32,208 +36,298 @@
 
 namespace csgs {
 
-// TAIL (forward product only, K = 32 n + 1 .. 4 with n >= 1): the last 1 .. 4 k do not get a chunk of
-// their own, whose loads, barrier and LDS reads would cost as much as a full one (100 input features
-// are three chunks and four k).  They are loaded once, before the first barrier, into the four padding
-// words of the rows of the LDS buffer that will hold the last chunk, and take one MFMA step after it,
-// in which lane group g feeds k = 32 n + g.
-template <int BN, int MODE, int V, bool FULL, bool TAIL = false, int BM_ = 128>
-__global__ __launch_bounds__(256, (MODE == MODE_FWD && BM_ == 128 && BN == 64) ? 3 : 2) void gemm_f32_k(const float *__restrict__ A, int64_t lda,
-                                                  const float *__restrict__ Bm, int64_t ldb, float *__restrict__ C,
-                                                  int64_t ldc, double *__restrict__ partial, int M_bound, int N,
-                                                  int K_bound, const int32_t *__restrict__ rows_dev, int n_tiles_n,
-                                                  int n_tiles, int k_split, CompStride cs)
+// The same kernel serves the layer's forward product and its two gradient products; they differ in
+// how the operands lie in memory and in where the result goes:
+//   FWD  H  = Z W        A(m,k) = Z[m][k]           B(k,n) = W[k][n]      C float [M x N]
+//   DZ   dZ = G W^T      A(m,k) = G[m][k]           B(k,n) = W[n][k]      C float [M x N]
+//   DW   dW = Z^T G      A(m,k) = Z[k][m]           B(k,n) = G[k][n]      the reduction dimension (the rows of the
+//        sampled layer) is dealt to the four wavefronts of a block, whose sums are added in LDS, and over blockIdx.y; the
+//        parts go out in double and a second kernel adds them in a fixed order (one part: float, no second kernel).
+enum { MODE_FWD = 0, MODE_DZ = 1, MODE_DW = 2 };
+
+// MFMA steps (of four k) that a kernel has for the K % 32 k behind the whole chunks
+enum { TAIL_NONE = 0, TAIL_8 = 2, TAIL_32 = 8 };
+
+// N consecutive floats at a byte offset from an address the whole wavefront shares.  Four bytes of alignment are
+// enough for any width of global load on this part.
+template <int N, typename OFF>
+__device__ inline void load_floats(const char *base, OFF off, float *out)
 {
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+    typedef float f2 __attribute__((ext_vector_type(2), aligned(4)));
+    const char *p = base + off;
+    if constexpr (N == 4) {
+        const f4 x = *reinterpret_cast<const f4 *>(p);
+        out[0] = x[0]; out[1] = x[1]; out[2] = x[2]; out[3] = x[3];
+    } else if constexpr (N >= 2) {
+        const f2 x = *reinterpret_cast<const f2 *>(p);
+        out[0] = x[0]; out[1] = x[1];
+        if constexpr (N == 3) out[2] = *reinterpret_cast<const float *>(p + 8);
+    } else {
+        out[0] = *reinterpret_cast<const float *>(p);
+    }
+}
+template <int N>
+__device__ inline void store_floats(float *p, const float *v)
+{
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+    typedef float f2 __attribute__((ext_vector_type(2), aligned(4)));
+    if constexpr (N == 4) {
+        *reinterpret_cast<f4 *>(p) = f4{v[0], v[1], v[2], v[3]};
+    } else if constexpr (N >= 2) {
+        *reinterpret_cast<f2 *>(p) = f2{v[0], v[1]};
+        if constexpr (N == 3) p[2] = v[2];
+    } else {
+        *p = v[0];
+    }
+}
+
+// OFF: a lane's byte offsets; 64 bits only where rows lie 2^24 floats apart or more.
+// Registers: two sets of operands (16 (RT + NT) in all) and 8 RT NT of sums; 230 for 2 x 4, 135 for 2 x 2.
+template <int MODE, int RT, int NT, int TAIL, typename OFF>
+__global__ __launch_bounds__(256, RT * NT >= 6 ? 2 : (RT * NT >= 4 ? 3 : 4)) void gemm_wave_k(
+    const float *__restrict__ A, int64_t lda, const float *__restrict__ Bm, int64_t ldb, float *__restrict__ C, int64_t ldc,
+    double *__restrict__ partial, int M_bound, int N, int K_bound, const int32_t *__restrict__ rows_dev, int tiles_n, int n_tiles,
+    int n_blocks, CompStride cs)
+{
+    constexpr bool DW = MODE == MODE_DW, B_KMAJOR = MODE == MODE_DZ;
+    constexpr int BM = 16 * RT, BN = 16 * NT;
     A = inst_ptr(A, cs.x); C = inst_ptr(C, cs.out); rows_dev = inst_ptr(rows_dev, cs.adj);   // B (the weights) is shared
-    constexpr int NT = BN / 16;   // 16-column MFMA tiles per wavefront
-    constexpr int RT = BM_ / 64;  // 16-row MFMA tiles per wavefront: the four wavefronts are stacked along M
-    static_assert(BM_ == 128 || BM_ == 64, "block tiles of 128 or 64 rows");
-    constexpr bool A_KMAJOR = MODE != MODE_DW, B_KMAJOR = MODE == MODE_DZ;
-    constexpr bool A_BLOCKS = MODE == MODE_DW && V == 4;
-    static_assert(!A_BLOCKS || BM_ == 128, "one block of 4 x 4 per thread");
-    __shared__ __attribute__((aligned(16))) float As[2][BM_ * LDS_STRIDE];
-    // The B tile of the forward product's 128 x 64 blocks is swizzled instead of padded: 52-53 KB of LDS per block
-    // instead of 54, which lets a third block onto a compute unit (the launch bound asks the compiler for the
-    // 168 registers that go with it)
-    constexpr bool SWZ = MODE == MODE_FWD && BM_ == 128 && BN == 64;
-    constexpr int B_STRIDE = SWZ ? BK : LDS_STRIDE;
-    __shared__ __attribute__((aligned(16))) float Bs[2][BN * B_STRIDE];
-    __shared__ float Bt[(TAIL && SWZ) ? BN * 4 : 1];   // the K tail of B where its rows have no padding
-    const int tid = (int)threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = (int)(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int grp = lane >> 4, l16 = lane & 15;
     // XCD-aware tile order: hardware deals consecutive block ids round-robin to the 8 XCDs
     const int bid = (int)blockIdx.x;
-    const int per_xcd = (n_tiles + 7) / 8;
+    const int per_xcd = (n_blocks + 7) / 8;
     // (rotated by the instance: the row tiles beyond a mini-batch's row count are the last ones, and with the
     // same order for every instance they would all fall to the same XCD, which then idles)
-    const int tile = (((bid & 7) + (int)blockIdx.z) & 7) * per_xcd + (bid >> 3);
-    if (tile >= n_tiles) return;
-    const int64_t m0 = (int64_t)(tile / n_tiles_n) * BM_, n0 = (int64_t)(tile % n_tiles_n) * BN;
-    // the row count of the sampled layer may live on the device: it bounds M, or K for dW.  As a bound
-    // of M it is only needed once the first chunk's loads are on their way (see below)
-    const int m_dev = (MODE != MODE_DW && rows_dev) ? *rows_dev : M_bound;
-    const int K = MODE == MODE_DW ? resolve_count(K_bound, rows_dev) : K_bound;
-    const int k_begin = MODE == MODE_DW ? (int)blockIdx.y * k_split : 0;
-    const int k_end = MODE == MODE_DW ? (k_begin + k_split < K ? k_begin + k_split : K) : K;
-    static_assert(!TAIL || MODE == MODE_FWD, "the folded tail is for forward products");
-    const int n_chunks = TAIL ? (k_end - k_begin) / BK : (k_end > k_begin ? (k_end - k_begin + BK - 1) / BK : 0);
+    const int blk = (((bid & 7) + (int)blockIdx.z) & 7) * per_xcd + (bid >> 3);
+    const int tile = DW ? blk : blk * 4 + wave;
+    if (blk >= n_blocks || tile >= n_tiles) return;   // for dW the whole block
+    const int m0 = (tile / tiles_n) * BM, n0 = (tile % tiles_n) * BN;
+    const int m_dev = (!DW && rows_dev) ? *rows_dev : M_bound;
+    const int K = DW ? __builtin_amdgcn_readfirstlane(resolve_count(K_bound, rows_dev)) : K_bound;
 
+    // ---- where this lane's operands lie: bytes from addresses that the whole wavefront shares
+    OFF offa[DW ? 1 : RT], offb[B_KMAJOR ? NT : 1];
+    const char *pa, *pb;
+    if constexpr (DW) {
+        const int m = m0 + RT * l16 < M_bound - RT ? m0 + RT * l16 : M_bound - RT;
+        offa[0] = (OFF)(8 * grp) * (OFF)(lda * 4) + (OFF)m * 4;
+        pa = reinterpret_cast<const char *>(A);
+    } else {
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            const int row = m0 + 16 * r + l16 < M_bound ? 16 * r + l16 : M_bound - 1 - m0;
+            offa[r] = (OFF)row * (OFF)(lda * 4) + (OFF)(32 * grp);
+        }
+        pa = reinterpret_cast<const char *>(A + (int64_t)m0 * lda);
+    }
+    const int col0 = n0 + NT * l16 < N - NT ? n0 + NT * l16 : N - NT;   // this lane's first column
+    if constexpr (B_KMAJOR) {
+        const int nb = n0 < N - NT ? n0 : N - NT;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) offb[t] = (OFF)(col0 - nb + t) * (OFF)(ldb * 4) + (OFF)(32 * grp);
+        pb = reinterpret_cast<const char *>(Bm + (int64_t)nb * ldb);
+    } else {
+        offb[0] = (OFF)(8 * grp) * (OFF)(ldb * 4) + (OFF)col0 * 4;
+        pb = reinterpret_cast<const char *>(Bm);
+    }
+
+    struct Set {
+        float a[8][RT], b[8][NT];
+    };
+    const int64_t lda4 = lda * 4, ldb4 = ldb * 4;
+    // the chunk whose first k stands at ca, cb
+    auto load = [&](Set &x, const char *ca, const char *cb) {
+        // (the offsets are kept apart from the shared address by hand: left alone the compiler adds the two in every lane)
+#pragma unroll
+        for (auto &o : offa) asm volatile("" : "+v"(o));
+#pragma unroll
+        for (auto &o : offb) asm volatile("" : "+v"(o));
+        if constexpr (DW) {
+#pragma unroll
+            for (int s = 0; s < 8; ++s, ca += lda4) load_floats<RT>(ca, offa[0], x.a[s]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < RT; ++r) {
+                float v[8];
+                load_floats<4>(ca, offa[r], v);
+                load_floats<4>(ca + 16, offa[r], v + 4);
+#pragma unroll
+                for (int s = 0; s < 8; ++s) x.a[s][r] = v[s];
+            }
+        }
+        if constexpr (B_KMAJOR) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                float v[8];
+                load_floats<4>(cb, offb[t], v);
+                load_floats<4>(cb + 16, offb[t], v + 4);
+#pragma unroll
+                for (int s = 0; s < 8; ++s) x.b[s][t] = v[s];
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < 8; ++s, cb += ldb4) load_floats<NT>(cb, offb[0], x.b[s]);
+        }
+    };
     doublex4 acc[RT][NT];
 #pragma unroll
     for (int r = 0; r < RT; ++r)
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[r][t] = doublex4{0.0, 0.0, 0.0, 0.0};
-    float4 ra[BM_ / 32], rb[BN / 32];
-    uint32_t oka = 0, okb = 0;
-    // Rows of A up to M_bound are the caller's memory whatever the device count says, and a row of A
-    // only reaches its own row of C, which is not stored beyond the count: so the count never masks a
-    // load, and the first chunk's loads need not wait for it.
-    const bool a_whole = m0 + BM_ <= M_bound, b_whole = n0 + BN <= N;
-    bool k_whole = false;   // of the chunk in the registers
-    auto fetch = [&](int k0) {
-        k_whole = k0 + BK <= k_end;
-        if constexpr (A_KMAJOR) fetch_kmajor<BM_, V, FULL>(A, lda, M_bound, k_end, m0, k0, tid, ra, oka);
-        else if constexpr (A_BLOCKS) fetch_rmajor_blocks(A, lda, M_bound, k_end, m0, k0, tid, ra, oka);
-        else fetch_rmajor<BM_, FULL>(A, lda, M_bound, k_end, m0, k0, tid, ra, oka);
-        if (B_KMAJOR) fetch_kmajor<BN, V, FULL>(Bm, ldb, N, k_end, n0, k0, tid, rb, okb);
-        else fetch_rmajor<BN, FULL>(Bm, ldb, N, k_end, n0, k0, tid, rb, okb);
-    };
-    auto stash = [&](int buf) {
-        if constexpr (A_BLOCKS) stash_blocks(As[buf], tid, ra, oka, a_whole && k_whole);
-        else stash_tile<BM_, A_KMAJOR, FULL>(As[buf], tid, ra, oka, a_whole && k_whole);
-        stash_tile<BN, B_KMAJOR, FULL, SWZ>(Bs[buf], tid, rb, okb, b_whole && k_whole);
-    };
-    if (n_chunks > 0) fetch(k_begin);
-    // the K tail's loads travel with the first chunk's (unconditional, clamped addresses; threads beyond the
-    // tail's extent read a stand-in and store nothing): one load latency before the first barrier, not two
-    float ta0 = 0.f, ta1 = 0.f, tb = 0.f;
-    const int kt = k_begin + n_chunks * BK, tail = k_end - kt;
-    const int tr = (tid >> 1) < BM_ ? (tid >> 1) : BM_ - 1, tj0 = (tid & 1) * 2;   // A: BM_ rows x 4 k, two floats per thread
-    const int tn = tid % BN, tj = (tid / BN) & 3;                                  // B: 4 k x BN columns, one float per thread
-    if (TAIL) {
-        const int64_t gr = m0 + tr;
-        const float *row = A + (gr < M_bound ? gr : (int64_t)M_bound - 1) * lda;
-        ta0 = row[tj0 < tail ? kt + tj0 : k_end - 1];
-        ta1 = row[tj0 + 1 < tail ? kt + tj0 + 1 : k_end - 1];
-        const int64_t gn = n0 + tn;
-        tb = Bm[(int64_t)(tj < tail ? kt + tj : k_end - 1) * ldb + (gn < N ? gn : (int64_t)N - 1)];
-    }
-    const int M = m_dev < 0 ? 0 : (m_dev < M_bound ? m_dev : M_bound);
-    if (m0 >= M) return;  // the whole block leaves together, before any barrier
-    if (n_chunks > 0) stash(0);
-    if (TAIL) {
-        const int last = (n_chunks - 1) & 1;
-        if (tid < BM_ * 2) {
-            const bool row_ok = m0 + tr < M_bound;
-            As[last][tr * LDS_STRIDE + BK + tj0] = (row_ok && tj0 < tail) ? ta0 : 0.f;
-            As[last][tr * LDS_STRIDE + BK + tj0 + 1] = (row_ok && tj0 + 1 < tail) ? ta1 : 0.f;
-        }
-        if (tid < BN * 4) {
-            const bool ok = n0 + tn < N && tj < tail;
-            if (SWZ) Bt[tn * 4 + tj] = ok ? tb : 0.f;
-            else Bs[last][tn * LDS_STRIDE + BK + tj] = ok ? tb : 0.f;
-        }
-    }
-    __syncthreads();
-    const int a_off = (wave * (BM_ / 4) + l16) * LDS_STRIDE + 8 * grp;
-    const int b_off = l16 * LDS_STRIDE + 8 * grp;
-    const int bx_off = l16 * BK + (((2 * grp) ^ ((l16 >> 1) & 7)) << 2), by_off = l16 * BK + (((2 * grp + 1) ^ ((l16 >> 1) & 7)) << 2);
-    // 16-column MFMA tiles of this block that hold any real column (47 output classes fill 3 of 4), and
-    // k steps of the last chunk that hold any real k (lane group g feeds k = 8 g + s at step s, so with
-    // k_left <= 8 only the first k_left steps of group 0 are not padding): the rest would multiply zeros
-    // (a regular shape has neither: then nothing in the chunk loop sits under a condition, and the compiler is free to
-    // order the conversions, the MFMAs and the next chunk's loads)
-    const int nt_valid = FULL ? NT : (int)(N - n0 >= BN ? NT : (N - n0 + 15) / 16);
-    const int k_left = n_chunks > 0 ? (k_end - k_begin) - (n_chunks - 1) * BK : 0;
-    const int s_last = (FULL || k_left >= 8) ? 8 : k_left;
-    for (int c = 0; c < n_chunks; ++c) {
-        const int cur = c & 1;
-        if (c + 1 < n_chunks) fetch(k_begin + (c + 1) * BK);
-        float av[RT][8], bv[NT][8];
+    auto step = [&](const float *av, const float *bv) {
+        double a[RT], b[NT];
 #pragma unroll
-        for (int r = 0; r < RT; ++r) {
-            const float *ap = &As[cur][a_off + r * 16 * LDS_STRIDE];
-            const float4 x = *reinterpret_cast<const float4 *>(ap), y = *reinterpret_cast<const float4 *>(ap + 4);
-            av[r][0] = x.x; av[r][1] = x.y; av[r][2] = x.z; av[r][3] = x.w;
-            av[r][4] = y.x; av[r][5] = y.y; av[r][6] = y.z; av[r][7] = y.w;
-        }
+        for (int r = 0; r < RT; ++r) a[r] = (double)av[r];
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            float4 x, y;
-            if (SWZ) {   // row 16 t + l16: its swizzle (row >> 1) & 7 does not depend on t
-                x = *reinterpret_cast<const float4 *>(&Bs[cur][bx_off + t * 16 * BK]);
-                y = *reinterpret_cast<const float4 *>(&Bs[cur][by_off + t * 16 * BK]);
+        for (int t = 0; t < NT; ++t) b[t] = (double)bv[t];
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int r = 0; r < RT; ++r) acc[r][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[r], b[t], acc[r][t], 0, 0, 0);
+    };
+    auto multiply = [&](const Set &x) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) step(x.a[s], x.b[s]);
+    };
+    // the last K % 32 k: lane group g feeds k = kt + 4 s + g, so no step multiplies more than three k that do not exist
+    constexpr int TS = DW ? TAIL_32 : TAIL;
+    struct Tail {
+        float a[TS > 0 ? TS : 1][RT], b[TS > 0 ? TS : 1][NT];
+    };
+    const int kt = K & ~31, tail = K & 31;
+    auto load_tail = [&](Tail &x) {
+        const char *ta = pa + (DW ? kt * lda4 : (int64_t)kt * 4), *tb = pb + (B_KMAJOR ? (int64_t)kt * 4 : kt * ldb4);
+#pragma unroll
+        for (int s = 0; s < TS; ++s) {
+            const int kb = 4 * s < tail - 1 ? 4 * s : (tail > 0 ? tail - 1 : -1);   // (without a tail the last k stands in)
+            const int g = kb + grp < tail - 1 ? grp : tail - 1 - kb;
+            if constexpr (DW) {
+                load_floats<RT>(ta + kb * lda4, offa[0] - (OFF)(8 * grp) * (OFF)lda4 + (OFF)g * (OFF)lda4, x.a[s]);
             } else {
-                const float *bp = &Bs[cur][b_off + t * 16 * LDS_STRIDE];
-                x = *reinterpret_cast<const float4 *>(bp);
-                y = *reinterpret_cast<const float4 *>(bp + 4);
+#pragma unroll
+                for (int r = 0; r < RT; ++r) load_floats<1>(ta + kb * 4, offa[r] - (OFF)(32 * grp) + (OFF)(4 * g), &x.a[s][r]);
             }
-            bv[t][0] = x.x; bv[t][1] = x.y; bv[t][2] = x.z; bv[t][3] = x.w;
-            bv[t][4] = y.x; bv[t][5] = y.y; bv[t][6] = y.z; bv[t][7] = y.w;
-        }
-        const int s_end = (FULL || c + 1 < n_chunks) ? 8 : s_last;
+            if constexpr (B_KMAJOR) {
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            if (FULL || s < s_end) {
-                double a[RT];
-#pragma unroll
-                for (int r = 0; r < RT; ++r) a[r] = (double)av[r][s];
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    if (FULL || t < nt_valid) {
-                        const double b = (double)bv[t][s];
-#pragma unroll
-                        for (int r = 0; r < RT; ++r) acc[r][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[r], b, acc[r][t], 0, 0, 0);
-                    }
-                }
+                for (int t = 0; t < NT; ++t) load_floats<1>(tb + kb * 4, offb[t] - (OFF)(32 * grp) + (OFF)(4 * g), &x.b[s][t]);
+            } else {
+                load_floats<NT>(tb + kb * ldb4, (OFF)g * (OFF)ldb4 + (OFF)col0 * 4, x.b[s]);
             }
         }
-        if (c + 1 < n_chunks) {
-            stash(cur ^ 1);
-            __syncthreads();
+    };
+    auto multiply_tail = [&](Tail &x) {
+#pragma unroll
+        for (int s = 0; s < TS; ++s) {
+            if (4 * s >= tail) break;
+            if (4 * s + 4 > tail) {
+                const bool ok = 4 * s + grp < tail;
+#pragma unroll
+                for (int r = 0; r < RT; ++r) x.a[s][r] = ok ? x.a[s][r] : 0.f;
+#pragma unroll
+                for (int t = 0; t < NT; ++t) x.b[s][t] = ok ? x.b[s][t] : 0.f;
+            }
+            step(x.a[s], x.b[s]);
+        }
+    };
+
+    // ---- chunks of 32 k, `stride` apart: lane group g feeds k = 8 g + s at step s
+    int c0 = 0, n_chunks = K >> 5;
+    int64_t sa = 128, sb = B_KMAJOR ? 128 : 32 * ldb4;   // bytes from one chunk of this wavefront to its next
+    bool own_tail = true;
+    if constexpr (DW) {   // this block's chunks, dealt to its four wavefronts in turn
+        const int all = (K + 31) >> 5, per = (all + (int)gridDim.y - 1) / (int)gridDim.y;
+        const int first = (int)blockIdx.y * per + wave, end = first - wave + per < all ? first - wave + per : all;
+        const int whole_end = end < n_chunks ? end : n_chunks;
+        own_tail = tail && end == all && first < all && ((all - 1 - first) & 3) == 0 && first <= all - 1;
+        c0 = first * 32;
+        sa = 128 * lda4;
+        sb = 128 * ldb4;
+        n_chunks = whole_end > first ? (whole_end - first + 3) >> 2 : 0;
+    }
+    Set s0, s1;
+    Tail tl;
+    if constexpr (!DW && TAIL != TAIL_NONE) load_tail(tl);
+    const char *ca = pa, *cb = pb;
+    if constexpr (DW) {
+        ca += c0 * lda4;
+        cb += c0 * ldb4;
+    }
+    if (n_chunks > 0) load(s0, ca, cb);
+    if constexpr (!DW) {
+        // a row count on the device is needed only now that loads are on their way
+        if (m0 >= (m_dev < M_bound ? m_dev : M_bound)) return;
+        if constexpr (TAIL != TAIL_NONE) multiply_tail(tl);
+    }
+    if (n_chunks > 0) {
+        // The next chunk is asked for before this one is multiplied, and no load sits under a condition of its own: the
+        // compiler then waits for exactly the chunk it needs
+        int c = 0;
+        for (; c + 2 < n_chunks; c += 2) {
+            load(s1, ca += sa, cb += sb);
+            multiply(s0);
+            load(s0, ca += sa, cb += sb);
+            multiply(s1);
+        }
+        if (c + 2 == n_chunks) {
+            load(s1, ca += sa, cb += sb);
+            multiply(s0);
+            multiply(s1);
+        } else {
+            multiply(s0);
         }
     }
-    if (TAIL) {
-        const int last = (n_chunks - 1) & 1;
-        double a[RT];
-#pragma unroll
-        for (int r = 0; r < RT; ++r) a[r] = (double)As[last][(wave * (BM_ / 4) + r * 16 + l16) * LDS_STRIDE + BK + grp];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            if (FULL || t < nt_valid) {
-                const double b = (double)(SWZ ? Bt[(t * 16 + l16) * 4 + grp] : Bs[last][(t * 16 + l16) * LDS_STRIDE + BK + grp]);
-#pragma unroll
-                for (int r = 0; r < RT; ++r) acc[r][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[r], b, acc[r][t], 0, 0, 0);
-            }
+    if constexpr (DW) {
+        if (own_tail) {
+            load_tail(tl);
+            multiply_tail(tl);
         }
     }
-    // accumulator element i of lane l holds row l / 16 + 4 * i, column l % 16 of its 16 x 16 tile
-    auto store = [&](auto whole) {
-        constexpr bool WHOLE = decltype(whole)::value;
+
+    // ---- accumulator element i of lane (g, l) belongs to row g + 4 i of operand A's 16 and to column l of B's
+    const bool col_ok = n0 + NT * l16 < N;
+    if constexpr (!DW) {
+        const int M = m_dev < M_bound ? m_dev : M_bound;
 #pragma unroll
         for (int r = 0; r < RT; ++r)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int64_t row = m0 + wave * (BM_ / 4) + r * 16 + grp + 4 * i;
-                if (WHOLE || row < M) {
+                const int row = m0 + 16 * r + grp + 4 * i;
+                float v[NT];
 #pragma unroll
-                    for (int t = 0; t < NT; ++t) {
-                        const int64_t col = n0 + t * 16 + l16;
-                        if (WHOLE || col < N) {
-                            if (MODE == MODE_DW)
-                                partial[((int64_t)blockIdx.y * M_bound + row) * N + col] = acc[r][t][i];
-                            else
-                                C[row * ldc + col] = (float)acc[r][t][i];
-                        }
-                    }
+                for (int t = 0; t < NT; ++t) v[t] = (float)acc[r][t][i];
+                if (row < M && col_ok) store_floats<NT>(C + (int64_t)row * ldc + col0, v);
+            }
+    } else {
+        // the four wavefronts' sums, added in wavefront order
+        constexpr int E = RT * NT * 4;
+        __shared__ double red[4][E][64];
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) red[wave][(r * 4 + i) * NT + t][lane] = acc[r][t][i];
+        __syncthreads();
+        static_assert(E % (4 * NT) == 0 && (E / 4) % NT == 0, "whole rows per wavefront");
+#pragma unroll
+        for (int j = 0; j < RT; ++j) {
+            const int ri = wave * RT + j, r = ri >> 2, i = ri & 3;
+            const int ma = m0 + RT * (grp + 4 * i);
+            const int row = (ma < M_bound - RT ? ma : M_bound - RT) + r;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const int e = ri * NT + t;
+                const double s = ((red[0][e][lane] + red[1][e][lane]) + red[2][e][lane]) + red[3][e][lane];
+                if (ma < M_bound && col_ok) {
+                    if (C) C[(int64_t)row * ldc + col0 + t] = (float)s;   // the only part
+                    else partial[((int64_t)blockIdx.y * M_bound + row) * N + col0 + t] = s;
                 }
             }
-    };
-    if (m0 + BM_ <= M && (FULL || n0 + BN <= N)) store(std::true_type{});
-    else store(std::false_type{});
+        }
+    }
 }
-
 // dW[i] = sum over the K parts, in ascending part order (fixed: the result does not depend on timing)
 __global__ __launch_bounds__(256) void gemm_reduce_parts(const double *__restrict__ partial, int parts, int64_t count,
                                                          int N, float *__restrict__ C, int64_t ldc)
@@ -253,72 +347,113 @@ __global__ __launch_bounds__(256) void gemm_reduce_parts(const double *__restric
     C[(i / N) * ldc + (i % N)] = (float)s;
 }
 
-// Widest vector (in floats) that loads rows of `k` floats, `ld` apart, in whole pieces
-static int widest(const float *p, int64_t ld, int k)
+// What one MFMA of a tile shape costs beside one of the largest shape (conversions per MFMA, tiles per
+// wavefront slot), measured on 4096 .. 131072 rows
+struct Shape {
+    int rt, nt;
+    double cost;
+};
+static const Shape kShapes[] = {{2, 4, 1.0}, {2, 3, 1.01}, {2, 2, 1.05}, {1, 4, 1.06}, {1, 3, 1.1}, {2, 1, 1.2}, {1, 2, 1.2}, {1, 1, 1.35}};
+constexpr int CUS = 256;   // compute units; a block has a wavefront for each SIMD
+
+// The shape whose slowest compute unit is done first: blocks per unit, rounded up, times what a block takes.  The larger shapes waste fewer
+// conversions, the smaller ones waste fewer columns and leave fewer units idle (4500 x 512 x 100, us: 2x4 33.4, 2x2 19.4, 2x1 14.3, 1x1
+// 13.1; 8192 x 256 x 256: 19.9, 20.5, 23.3, 24.6).
+static Shape pick_shape(int64_t M, int64_t N, int64_t n_inst)
 {
-    if (ld % 4 == 0 && k % 4 == 0 && ((uintptr_t)p & 15) == 0) return 4;
-    if (ld % 2 == 0 && k % 2 == 0 && ((uintptr_t)p & 7) == 0) return 2;
-    return 1;
+    Shape best = kShapes[7];
+    double least = 1e300;
+    for (const Shape &s : kShapes) {
+        if (s.nt > N) continue;   // a lane's NT columns exist
+        const int64_t tiles = ((M + 16 * s.rt - 1) / (16 * s.rt)) * ((N + 16 * s.nt - 1) / (16 * s.nt));
+        const int64_t per_cu = ((tiles + 3) / 4 * n_inst + CUS - 1) / CUS;
+        const double c = (double)per_cu * s.rt * s.nt * s.cost;
+        if (c < least) { least = c; best = s; }
+    }
+    return best;
 }
 
-template <int BMF, int BN>
-static void launch_fwd(const float *Z, int64_t ldz, int M, const int32_t *M_dev, int K, const float *W, int64_t ldw, int N, float *H,
-                       int64_t ldh, hipStream_t st, const CompInst &ci)
+// A row of a matrix this long could put a lane's offset beyond 32 bits
+static bool far_apart(int64_t lda, int64_t ldb) { return lda >= (1 << 24) || ldb >= (1 << 24); }
+
+template <int MODE>
+static void launch_product(const float *A, int64_t lda, const float *B, int64_t ldb, float *C, int64_t ldc, int M, int N, int K,
+                           const int32_t *M_dev, hipStream_t st, const CompInst &ci)
 {
-    const int tm = (M + BMF - 1) / BMF, tn = (N + BN - 1) / BN;
-    const int n_tiles = tm * tn;
-    const dim3 grid((unsigned)(((n_tiles + 7) / 8) * 8), 1, (unsigned)ci.n);
-    const int va = widest(Z, ldz, K);
-    const bool fold = K > BK && K % BK >= 1 && K % BK <= 4;   // see TAIL
-    // regular shape (of the bounds: a device count only gates the stores); a folded tail leaves whole chunks
-    const bool full = M % BMF == 0 && N % BN == 0 && (K % BK == 0 || fold) && va == 4;
+    const bool far = far_apart(lda, ldb);
+    const Shape s = far ? Shape{1, 1, 0.0} : pick_shape(M, N, ci.n);
+    const int tm = (int)(((int64_t)M + 16 * s.rt - 1) / (16 * s.rt)), tn = (int)(((int64_t)N + 16 * s.nt - 1) / (16 * s.nt));
+    const int n_tiles = tm * tn, n_blocks = (n_tiles + 3) / 4;
+    const dim3 grid((unsigned)((n_blocks + 7) / 8 * 8), 1, (unsigned)ci.n);
     double *none = nullptr;
-#define CSGS_GEMM_FWD(V, FULL, TAIL) \
-    CSGS_LAUNCH(K_GEMM, (gemm_f32_k<BN, MODE_FWD, V, FULL, TAIL, BMF>), grid, dim3(256), st, Z, ldz, W, ldw, H, ldh, none, M, N, K, M_dev, tn, n_tiles, 0, ci.cs)
-    if (full && fold) CSGS_GEMM_FWD(4, true, true);
-    else if (full) CSGS_GEMM_FWD(4, true, false);
-    else if (fold && va == 4) CSGS_GEMM_FWD(4, false, true);
-    else if (fold && va == 2) CSGS_GEMM_FWD(2, false, true);
-    else if (fold) CSGS_GEMM_FWD(1, false, true);
-    else if (va == 4) CSGS_GEMM_FWD(4, false, false);
-    else if (va == 2) CSGS_GEMM_FWD(2, false, false);
-    else CSGS_GEMM_FWD(1, false, false);
-#undef CSGS_GEMM_FWD
+    constexpr int STAGE = MODE;   // (names the launch in the profile)
+#define CSGS_PRODUCT(RT, NT, TAIL, OFF)                                                                                                       \
+    do {                                                                                                                                      \
+        if (STAGE == MODE_FWD)                                                                                                                \
+            CSGS_LAUNCH(K_GEMM, (gemm_wave_k<MODE, RT, NT, TAIL, OFF>), grid, dim3(256), st, A, lda, B, ldb, C, ldc, none, M, N, K, M_dev,    \
+                        tn, n_tiles, n_blocks, ci.cs);                                                                                        \
+        else                                                                                                                                  \
+            CSGS_LAUNCH(K_GEMM_DZ, (gemm_wave_k<MODE, RT, NT, TAIL, OFF>), grid, dim3(256), st, A, lda, B, ldb, C, ldc, none, M, N, K, M_dev, \
+                        tn, n_tiles, n_blocks, ci.cs);                                                                                        \
+    } while (0)
+#define CSGS_SHAPE(RT, NT)                                                  \
+    if (s.rt == RT && s.nt == NT) {                                         \
+        if (K % 32 == 0) CSGS_PRODUCT(RT, NT, TAIL_NONE, uint32_t);         \
+        else if (K % 32 <= 8) CSGS_PRODUCT(RT, NT, TAIL_8, uint32_t);       \
+        else CSGS_PRODUCT(RT, NT, TAIL_32, uint32_t);                       \
+    }
+    if (far) {
+        CSGS_PRODUCT(1, 1, TAIL_32, uint64_t);
+        return;
+    }
+    CSGS_SHAPE(2, 4) CSGS_SHAPE(2, 3) CSGS_SHAPE(2, 2) CSGS_SHAPE(2, 1) CSGS_SHAPE(1, 4) CSGS_SHAPE(1, 3) CSGS_SHAPE(1, 2) CSGS_SHAPE(1, 1)
+#undef CSGS_SHAPE
+#undef CSGS_PRODUCT
 }
 
-template <int BN>
-static void launch_dz(const float *G, int64_t ldg, int M, const int32_t *M_dev, int K, const float *W, int64_t ldw, int N, float *dZ,
-                      int64_t lddz, hipStream_t st)
+// Parts of the reduction dimension for dW = Z^T G with `rows` rows that the caller's scratch has room for
+static int dw_max_parts(int rows, int64_t K, int64_t N)
 {
-    const int tm = (M + BM - 1) / BM, tn = (N + BN - 1) / BN;
-    const int n_tiles = tm * tn;
-    const dim3 grid((unsigned)(((n_tiles + 7) / 8) * 8));
-    const int v = widest(G, ldg, K) == 4 && widest(W, ldw, K) == 4 ? 4 : 1;
-    double *none = nullptr;
-    if (v == 4)
-        CSGS_LAUNCH(K_GEMM_DZ, (gemm_f32_k<BN, MODE_DZ, 4, false>), grid, dim3(256), st, G, ldg, W, ldw, dZ, lddz, none, M, N, K, M_dev, tn, n_tiles, 0, CompStride{0, 0, 0, 0});
-    else
-        CSGS_LAUNCH(K_GEMM_DZ, (gemm_f32_k<BN, MODE_DZ, 1, false>), grid, dim3(256), st, G, ldg, W, ldw, dZ, lddz, none, M, N, K, M_dev, tn, n_tiles, 0, CompStride{0, 0, 0, 0});
-}
-
-// Parts of the reduction dimension for dW = Z^T G with `rows` rows: enough blocks to fill the device,
-// each part a multiple of the K chunk.
-static void dw_split(int rows, int tiles, int *parts, int *k_split)
-{
-    int want = (512 + tiles - 1) / tiles;
-    const int max_parts = (rows + BK - 1) / BK;
-    if (want > max_parts) want = max_parts;
+    const int64_t tiles = ((K + 127) / 128) * ((N + 31) / 32);
+    int64_t want = (512 + tiles - 1) / tiles;
+    const int64_t chunks = ((int64_t)rows + 31) / 32;
+    if (want > chunks) want = chunks;
     if (want < 1) want = 1;
-    int ks = ((rows + want - 1) / want + BK - 1) / BK * BK;
-    if (ks < BK) ks = BK;
-    *k_split = ks;
-    *parts = (rows + ks - 1) / ks;
-    if (*parts < 1) *parts = 1;
+    int64_t ks = ((rows + want - 1) / want + 31) / 32 * 32;
+    if (ks < 32) ks = 32;
+    const int64_t parts = (rows + ks - 1) / ks;
+    return (int)(parts < 1 ? 1 : parts);
+}
+
+// Shape and parts for dW: as pick_shape, with a block per tile and part; parts fill idle compute units and cost their way through memory
+// (16 bytes per output and part at about 4 TB/s) and the kernel that adds them (3.5 us).  Measured, us: 4096 rows, 512 x 512: one
+// part of 2x2 tiles 37, two of 2x4 40; 8192 rows, 256 x 256: 2x2 in 1 / 2 / 4 / 8 / 16 parts 72 / 40 / 24 / 24 / 26, 256 x 47: 2x3 in 8 / 16 / 32 18 / 14 / 11.5.
+static void dw_split(int rows, int64_t K, int64_t N, Shape *shape, int *parts)
+{
+    static const Shape shapes[] = {{2, 4, 1.0}, {2, 3, 1.01}, {2, 2, 1.05}, {1, 1, 1.35}};
+    const int64_t chunks = ((int64_t)rows + 31) / 32;
+    const int max_parts = dw_max_parts(rows, K, N);
+    double least = 1e300;
+    *shape = shapes[3];
+    *parts = 1;
+    for (const Shape &s : shapes) {
+        if (s.nt > N || s.rt > K) continue;
+        const int64_t tiles = ((K + 16 * s.rt - 1) / (16 * s.rt)) * ((N + 16 * s.nt - 1) / (16 * s.nt));
+        for (const int64_t fill : {(int64_t)0, (int64_t)CUS, (int64_t)2 * CUS}) {
+            int64_t p = fill / tiles;
+            p = p < 1 ? 1 : (p > max_parts ? max_parts : p);
+            const int64_t per_cu = (tiles * p + CUS - 1) / CUS, mine = (chunks + 4 * p - 1) / (4 * p);
+            const double c = (double)per_cu * (double)mine * (8 * 0.029) * s.rt * s.nt * s.cost + (p > 1 ? 3.5 + (double)(p * K * N) * (16 / 4e6) : 0.0);
+            if (c < least) { least = c; *shape = s; *parts = (int)p; }
+        }
+    }
 }
 
 }  // namespace csgs
 
 using namespace csgs;
+
+static bool too_many_tiles(int64_t M, int64_t N) { return ((M + 127) / 128) * ((N + 31) / 32) > 0x3FFFFFFF; }
 
 extern "C" int csgs_layer_gemm(const float *Z, int64_t ldz, int32_t M, const int32_t *M_dev, int32_t K, const float *W, int64_t ldw,
                                int32_t Nout, float *H, int64_t ldh, void *stream)
@@ -332,21 +467,8 @@ extern "C" int csgs_layer_gemm_n(const csgs_inst_strides *inst, const float *Z, 
     if (!Z || !W || !H || M <= 0 || K <= 0 || Nout <= 0 || ldz < K || ldw < Nout || ldh < Nout) return CSGS_EINVAL;
     CompInst ci;
     if (open_instances(inst, &ci) != CSGS_OK) return CSGS_EINVAL;
-    const int64_t tm = ((int64_t)M + BM - 1) / BM;
-    if (tm * (((int64_t)Nout + 31) / 32) > 0x3FFFFFFF) return CSGS_EUNSUPPORTED;
-    hipStream_t st = (hipStream_t)stream;
-    // Tiles of 128 x 64 where they give at least two blocks per compute unit; else 64 rows (twice the
-    // blocks: 18 against 20 us per launch for one mini-batch of the named configuration; with 512 tiles
-    // of 128 rows, the narrow output layer of 8 mini-batches, 64-row tiles are 2 us slower); narrow column
-    // tiles when even those would leave fewer than two blocks per compute unit
-    const int64_t wide_tiles = tm * (((int64_t)Nout + 63) / 64);
-    const int64_t tm64 = ((int64_t)M + 63) / 64;
-    if (wide_tiles * ci.n >= 512 && Nout > 32)
-        launch_fwd<128, 64>(Z, ldz, M, M_dev, K, W, ldw, Nout, H, ldh, st, ci);
-    else if (tm64 * (((int64_t)Nout + 63) / 64) * ci.n >= 512 && Nout > 32)
-        launch_fwd<64, 64>(Z, ldz, M, M_dev, K, W, ldw, Nout, H, ldh, st, ci);
-    else
-        launch_fwd<64, 32>(Z, ldz, M, M_dev, K, W, ldw, Nout, H, ldh, st, ci);
+    if (too_many_tiles(M, Nout)) return CSGS_EUNSUPPORTED;
+    launch_product<MODE_FWD>(Z, ldz, W, ldw, H, ldh, M, Nout, K, M_dev, (hipStream_t)stream, ci);
     CSGS_LAUNCH_CHECK();
     return CSGS_OK;
 }
@@ -355,15 +477,9 @@ extern "C" int csgs_layer_gemm_grad_z(const float *G, int64_t ldg, int32_t M, co
                                       int64_t ldw, int32_t K, float *dZ, int64_t lddz, void *stream)
 {
     if (!G || !W || !dZ || M <= 0 || K <= 0 || Nout <= 0 || ldg < Nout || ldw < Nout || lddz < K) return CSGS_EINVAL;
-    const int64_t tm = ((int64_t)M + BM - 1) / BM;
-    if (tm * (((int64_t)K + 31) / 32) > 0x3FFFFFFF) return CSGS_EUNSUPPORTED;
-    hipStream_t st = (hipStream_t)stream;
+    if (too_many_tiles(M, K)) return CSGS_EUNSUPPORTED;
     // output [M x K]; the reduction runs over the Nout columns of G
-    const int64_t wide_tiles = tm * (((int64_t)K + 63) / 64);
-    if (wide_tiles >= 512 && K > 32)
-        launch_dz<64>(G, ldg, M, M_dev, Nout, W, ldw, K, dZ, lddz, st);
-    else
-        launch_dz<32>(G, ldg, M, M_dev, Nout, W, ldw, K, dZ, lddz, st);
+    launch_product<MODE_DZ>(G, ldg, W, ldw, dZ, lddz, M, K, Nout, M_dev, (hipStream_t)stream, CompInst{});
     CSGS_LAUNCH_CHECK();
     return CSGS_OK;
 }
@@ -371,10 +487,7 @@ extern "C" int csgs_layer_gemm_grad_z(const float *G, int64_t ldg, int32_t M, co
 extern "C" size_t csgs_layer_gemm_grad_w_scratch_bytes(int32_t M, int32_t K, int32_t Nout)
 {
     if (M <= 0 || K <= 0 || Nout <= 0) return 0;
-    const int tiles = ((K + BM - 1) / BM) * ((Nout + 31) / 32);
-    int parts, ks;
-    dw_split(M, tiles, &parts, &ks);
-    return (size_t)parts * (size_t)K * (size_t)Nout * sizeof(double);
+    return (size_t)dw_max_parts(M, K, Nout) * (size_t)K * (size_t)Nout * sizeof(double);
 }
 
 // dW = Z^T G with the partial sums in `parts` (device, at least csgs_layer_gemm_grad_w_scratch_bytes bytes)
@@ -382,19 +495,26 @@ static int grad_w_launch(const float *Z, int64_t ldz, const float *G, int64_t ld
                          int32_t Nout, float *dW, int64_t lddw, double *parts_buf, hipStream_t st)
 {
     // kernel terms: output [K x Nout], reduction over the M rows (their count may live on the device)
-    const int tm = (K + BM - 1) / BM, tn = (Nout + 31) / 32;
+    Shape s;
+    int parts;
+    dw_split(M, K, Nout, &s, &parts);
+    const bool far = far_apart(ldz, ldg);
+    if (far) s = Shape{1, 1, 0.0};
+    const int tm = (int)(((int64_t)K + 16 * s.rt - 1) / (16 * s.rt)), tn = (int)(((int64_t)Nout + 16 * s.nt - 1) / (16 * s.nt));
     const int n_tiles = tm * tn;
-    int parts, ks;
-    dw_split(M, n_tiles, &parts, &ks);
-    const dim3 grid((unsigned)(((n_tiles + 7) / 8) * 8), (unsigned)parts);
-    float *none = nullptr;
-    if (widest(Z, ldz, K) == 4)
-        CSGS_LAUNCH(K_GEMM_DW, (gemm_f32_k<32, MODE_DW, 4, false>), grid, dim3(256), st, Z, ldz, G, ldg, none, (int64_t)0,
-                    parts_buf, K, Nout, M, M_dev, tn, n_tiles, ks, CompStride{0, 0, 0, 0});
-    else
-        CSGS_LAUNCH(K_GEMM_DW, (gemm_f32_k<32, MODE_DW, 1, false>), grid, dim3(256), st, Z, ldz, G, ldg, none, (int64_t)0,
-                    parts_buf, K, Nout, M, M_dev, tn, n_tiles, ks, CompStride{0, 0, 0, 0});
+    const dim3 grid((unsigned)((n_tiles + 7) / 8 * 8), (unsigned)parts);
+    float *out = parts == 1 ? dW : nullptr;
+#define CSGS_DW(RT, NT, OFF)                                                                                                                \
+    CSGS_LAUNCH(K_GEMM_DW, (gemm_wave_k<MODE_DW, RT, NT, TAIL_32, OFF>), grid, dim3(256), st, Z, ldz, G, ldg, out, lddw, parts_buf, K, Nout, \
+                M, M_dev, tn, n_tiles, n_tiles, CompStride{0, 0, 0, 0})
+    if (far) CSGS_DW(1, 1, uint64_t);
+    else if (s.nt == 4) CSGS_DW(2, 4, uint32_t);
+    else if (s.nt == 3) CSGS_DW(2, 3, uint32_t);
+    else if (s.nt == 2) CSGS_DW(2, 2, uint32_t);
+    else CSGS_DW(1, 1, uint32_t);
+#undef CSGS_DW
     CSGS_LAUNCH_CHECK();
+    if (parts == 1) return CSGS_OK;
     const int64_t count = (int64_t)K * Nout;
     CSGS_LAUNCH(K_GEMM_DW_REDUCE, gemm_reduce_parts, dim3((unsigned)((count + 255) / 256)), dim3(256), st,
                 (const double *)parts_buf, parts, count, Nout, dW, lddw);

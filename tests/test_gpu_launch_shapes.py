@@ -270,3 +270,32 @@ def test_weight_gradient_loads(dev, M, m, K, N, pad):
     torch.cuda.synchronize()
     want = oracle.layer_gemm_grad_w(Z[:m], G[:m]) if m else np.zeros((K, N), np.float32)
     chain.assert_close(dW.cpu().numpy(), want, chain.RTOL, chain.ATOL, "dW")
+
+
+# The products' wavefront tiles: 16 or 32 rows by 16, 32, 48 or 64 columns, by what fills the device; K in chunks of 32 and what is left of
+# them (in steps of four, room for 8 or 32); rows whose floats start anywhere; rows 2^24 floats apart (offsets of 64 bits)
+@pytest.mark.parametrize("M,K,N,pad", [(1, 1, 1, 0), (15, 31, 2, 1), (17, 32, 3, 0), (16, 33, 16, 3), (33, 36, 17, 0), (1023, 40, 7, 2), (1024, 64, 256, 0),
+                                       (2048, 41, 250, 1), (4095, 63, 100, 0), (4096, 96, 512, 0), (4097, 34, 511, 1), (20001, 9, 201, 0), (65530, 8, 47, 1),
+                                       (65537, 4, 130, 2), (3, 37, 5, 1 << 24)])
+def test_product_tiles(dev, M, K, N, pad):
+    from paper_2101_07706_amd import csgs
+    rng = np.random.default_rng(7 * M + K + N)
+    print(f"[products] {M} x {K} x {N}, pad {pad}", flush=True)
+
+    def padded(a):
+        t = torch.full((a.shape[0], a.shape[1] + pad), float("nan"), dtype=torch.float32, device=dev)[:, :a.shape[1]]
+        t.copy_(torch.from_numpy(a))
+        return t
+    Z, W, G = (rng.standard_normal(s).astype(np.float32) for s in ((M, K), (K, N), (M, N)))
+    Zd, Wd, Gd = padded(Z), padded(W), padded(G)
+    out = lambda r, c: torch.full((r + 1, c + 3), float("nan"), dtype=torch.float32, device=dev)
+    H, dZ, dW = out(M, N), out(M, K), out(K, N)
+    csgs.csgs_layer_gemm(Zd, Wd, H[:M, :N])
+    csgs.csgs_layer_gemm_grad_z(Gd, Wd, dZ[:M, :K])
+    scratch = torch.full((csgs.csgs_layer_gemm_grad_w_scratch_bytes(M, K, N) // 8,), -1, dtype=torch.int64, device=dev)
+    csgs.csgs_layer_gemm_grad_w(Zd, Gd, dW[:K, :N], scratch)
+    torch.cuda.synchronize()
+    for got, want, what in ((H, oracle.layer_gemm(Z, W), "H"), (dZ, oracle.layer_gemm_grad_z(G, W), "dZ"), (dW, oracle.layer_gemm_grad_w(Z, G), "dW")):
+        r, c = want.shape
+        chain.assert_close(got[:r, :c].cpu().numpy(), want, chain.RTOL, chain.ATOL, what)
+        assert bool(torch.isnan(got[r:]).all()) and bool(torch.isnan(got[:, c:]).all()), f"{what}: wrote outside"
