@@ -48,14 +48,17 @@ __global__ __launch_bounds__(AGG_BLOCK) void aggregate_k(const int32_t *__restri
     if (block_row0 >= nS) return;
     const int tid = (int)threadIdx.x;
     const int wave = tid >> 6;
-    const int32_t slice0 = slice * G * V;
-    const int32_t f = slice0 + (tid % G) * V;
-    const bool active = f < F;  // F is a multiple of V (checked on the host)
+    // V is at most F, and where F is no multiple of it the last V features of a row are taken together: those among them that
+    // another lane (or slice) has too are written twice, the same.  Lanes past the row repeat them and store nothing
+    const int32_t slice0 = slice * G * V < F - V ? slice * G * V : F - V;
+    const int32_t lane_f = slice0 + (tid % G) * V;
+    const int32_t f = lane_f < F - V ? lane_f : F - V;
+    const bool active = lane_f < F;
     const bool is_long = aggregate_tile<T, V, G, RELU>(stage[wave], tr, heads[wave], carries[wave], block_row0 + (int64_t)wave * tr, 0, slice0, f,
                                                        active, adj_rowptr, adj_col, adj_val, nS_bound, nS, n_cols, Xl, ldl, rows_l,
                                                        Xr, ldr, rows_r, src_row, Z, ldz, mask, ldm);
     if (__syncthreads_or(is_long ? 1 : 0))
-        aggregate_long_rows<T, V, G, RELU>(&heads[0][0], tr, block_row0, 0, is_long, f, active, adj_rowptr, adj_col, adj_val, n_cols, Xl, ldl,
+        aggregate_long_rows<T, V, G, RELU>(&heads[0][0], tr, block_row0, 0, is_long, slice0, f, active, adj_rowptr, adj_col, adj_val, n_cols, Xl, ldl,
                                            rows_l, Xr, ldr, rows_r, src_row, Z, ldz, mask, ldm);
 }
 
@@ -99,6 +102,7 @@ static int pick_group(const int32_t *rp, const int32_t *col, const float *val, i
 {
     const int64_t vecs = (F + V - 1) / V;
     const int64_t want = (int64_t)F * (int64_t)sizeof(T) >= 1024 ? (vecs + 3) / 4 : vecs;
+    static_assert(V >= 4, "narrow rows take four lanes");
 #define CSGS_AGG_G(GG) launch_agg<T, V, GG>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci)
     if (want <= 4) return CSGS_AGG_G(4);
     if (want <= 8) return CSGS_AGG_G(8);
@@ -108,24 +112,45 @@ static int pick_group(const int32_t *rp, const int32_t *col, const float *val, i
 #undef CSGS_AGG_G
 }
 
+// Tables whose rows start anywhere, or whose rows are no whole number of four-element pieces: the same wide loads, which take any
+// address, the last V features of a row together (they overlap the lane's before).  A piece then lies across two cache lines more
+// often and a slice's edge in the middle of one, so slices are fewer and wider here: of 256 features, of 64 in rows of up to 128.
+// (us, an element or a pair per lane and four slices / this: 2048 rows of 27 edges, F = 602, 36 / 25; 20000 of 6, F = 481, 54 / 47,
+// bf16 56 / 37, F = 201 31 / 24; 3000 of 8, F = 333, 19 / 14, bf16 18 / 15; 68536 of 4.5, F = 481, 146 / 111; 12000 of 26, F = 318,
+// 75 / 68; 60000 of 12, F = 410, 200 / 200, bf16 155 / 137; 2048 of 27, F = 47, 19 / 14.)
+constexpr int32_t ODD_NARROW = 128;
+template <typename T>
+static int pick_odd(const int32_t *rp, const int32_t *col, const float *val, int32_t nS, const int32_t *nsd, const int32_t *ncp, const void *Xl,
+                    int64_t ldl, int64_t rl, const void *Xr, int64_t ldr, int64_t rr, const int32_t *src_row, int32_t F, int relu, float *Z, int64_t ldz,
+                    const float *mask, int64_t ldm, int kid, hipStream_t st, const CompInst &ci)
+{
+#define CSGS_AGG_VG(V, G) launch_agg<T, V, G>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci)
+    if (F > ODD_NARROW) return CSGS_AGG_VG(8, 32);
+    if (F > 32) return CSGS_AGG_VG(4, 16);
+    if (F > 16) return CSGS_AGG_VG(4, 8);
+    if (F >= 4) return CSGS_AGG_VG(4, 4);
+    if (F >= 2) return CSGS_AGG_VG(2, 4);
+    return CSGS_AGG_VG(1, 4);
+#undef CSGS_AGG_VG
+}
+
 template <typename T>
 static int pick_vec(const int32_t *rp, const int32_t *col, const float *val, int32_t nS, const int32_t *nsd, const int32_t *ncp, const void *Xl,
                     int64_t ldl, int64_t rl, const void *Xr, int64_t ldr, int64_t rr, const int32_t *src_row, int32_t F, int relu, float *Z, int64_t ldz,
                     const float *mask, int64_t ldm, int kid, hipStream_t st, const CompInst &ci = CompInst{})
 {
-    // widest vector for which every row start and F are aligned (8 floats are read as two pieces of 4)
-    auto ok = [&](int v) {
+    // rows of whole pieces that every row starts on a multiple of (8 floats are read as two pieces of 4)
+    auto whole = [&](int v) {
         const int piece = (v == 8 && sizeof(T) == 4) ? 4 : v;
         const uintptr_t bytes = (uintptr_t)piece * sizeof(T);
         const int zpiece = v == 8 ? 4 : v;
         return F % v == 0 && (!Xl || (ldl % piece == 0 && ((uintptr_t)Xl % bytes) == 0)) &&
                (!Xr || (ldr % piece == 0 && ((uintptr_t)Xr % bytes) == 0)) && ldz % zpiece == 0 &&
-               ((uintptr_t)Z % ((uintptr_t)zpiece * sizeof(float))) == 0 && (!mask || ldm % 1 == 0);
+               ((uintptr_t)Z % ((uintptr_t)zpiece * sizeof(float))) == 0;
     };
-    if (ok(8)) return pick_group<T, 8>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci);
-    if (ok(4)) return pick_group<T, 4>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci);
-    if (ok(2)) return pick_group<T, 2>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci);
-    return pick_group<T, 1>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci);
+    if (whole(8)) return pick_group<T, 8>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci);
+    if (whole(4)) return pick_group<T, 4>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci);
+    return pick_odd<T>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci);
 }
 
 // ------------------------------------------------------------------ gradient of the aggregation
@@ -390,14 +415,15 @@ __host__ inline GradScratch carve_grad(void *base, int32_t n_cols_cap, int64_t a
     return g;
 }
 
-// out[k, :] = X[ids[k], :] in units of U (the widest type every row start is aligned to); one
-// wavefront per row, rows strided over the grid.  An id outside the table gives a zero row.
+// out[k, :] = X[ids[k], :] in pieces of U, from any address; one wavefront per row, rows strided over the grid.  Rows of `row_b` bytes, at least
+// one piece: the last piece ends with the row and may overlap the one before.  An id outside the table gives a zero row.
 template <typename U>
-__global__ __launch_bounds__(256) void gather_rows_k(const U *__restrict__ X, int64_t ld_u, int64_t rows, int32_t row_u,
+__global__ __launch_bounds__(256) void gather_rows_k(const char *__restrict__ X, int64_t ld_b, int64_t rows, int64_t row_b,
                                                      const int32_t *__restrict__ ids, int64_t cap,
-                                                     const int64_t *__restrict__ n_dev, U *__restrict__ out,
-                                                     int64_t ldo_u, CompStride cs)
+                                                     const int64_t *__restrict__ n_dev, char *__restrict__ out,
+                                                     int64_t ldo_b, CompStride cs)
 {
+    constexpr int32_t SIZE = (int32_t)sizeof(U);
     X = inst_ptr(X, cs.x); ids = inst_ptr(ids, cs.adj); n_dev = inst_ptr(n_dev, cs.adj); out = inst_ptr(out, cs.out);
     int64_t n = cap;
     if (n_dev) {
@@ -410,7 +436,10 @@ __global__ __launch_bounds__(256) void gather_rows_k(const U *__restrict__ X, in
     for (int64_t k = wave; k < n; k += n_waves) {
         const int64_t id = ids[k];
         const bool ok = id >= 0 && id < rows;
-        for (int32_t f = lane; f < row_u; f += WAVE) out[k * ldo_u + f] = ok ? X[id * ld_u + f] : U{};
+        for (int64_t f = lane * SIZE; f < row_b; f += WAVE * SIZE) {
+            const int64_t at = f < row_b - SIZE ? f : row_b - SIZE;
+            *reinterpret_cast<U *>(out + k * ldo_b + at) = ok ? *reinterpret_cast<const U *>(X + id * ld_b + at) : U{};
+        }
     }
 }
 
@@ -420,9 +449,8 @@ static void launch_gather(const void *X, int64_t ld_b, int64_t rows, int64_t row
 {
     const int64_t waves = cap < 8192 ? cap : 8192;
     const unsigned blocks = (unsigned)((waves + 3) / 4);
-    CSGS_LAUNCH(K_GATHER_ROWS, gather_rows_k<U>, dim3(blocks, 1, (unsigned)ci.n), dim3(256), st, (const U *)X,
-                ld_b / (int64_t)sizeof(U), rows, (int32_t)(row_b / (int64_t)sizeof(U)), ids, cap, n_dev, (U *)out,
-                ldo_b / (int64_t)sizeof(U), ci.cs);
+    CSGS_LAUNCH(K_GATHER_ROWS, gather_rows_k<U>, dim3(blocks, 1, (unsigned)ci.n), dim3(256), st, (const char *)X, ld_b, rows, row_b, ids, cap,
+                n_dev, (char *)out, ldo_b, ci.cs);
 }
 
 }  // namespace csgs
@@ -439,13 +467,8 @@ extern "C" int csgs_gather_rows_n(const csgs_inst_strides *inst, const void *X, 
     const int64_t elt = dtype == CSGS_F32 ? 4 : 2;
     const int64_t row_b = (int64_t)F * elt, ld_b = ld * elt, ldo_b = ldo * elt;
     hipStream_t st = (hipStream_t)stream;
-    auto aligned = [&](int64_t a) {
-        return row_b % a == 0 && ld_b % a == 0 && ldo_b % a == 0 && ((uintptr_t)X % (uintptr_t)a) == 0 &&
-               ((uintptr_t)out % (uintptr_t)a) == 0;
-    };
-    if (aligned(16)) launch_gather<uint4>(X, ld_b, rows, row_b, ids, cap, n_dev, out, ldo_b, st, ci);
-    else if (aligned(8)) launch_gather<uint2>(X, ld_b, rows, row_b, ids, cap, n_dev, out, ldo_b, st, ci);
-    else if (aligned(4)) launch_gather<uint32_t>(X, ld_b, rows, row_b, ids, cap, n_dev, out, ldo_b, st, ci);
+    // (131 K rows of 333 bf16 values, an element per lane 43 us, this 31; of 333 floats, 20 K rows, 11.5 / 10.2; whole pieces: level)
+    if (row_b >= 16) launch_gather<u32x4_any>(X, ld_b, rows, row_b, ids, cap, n_dev, out, ldo_b, st, ci);
     else launch_gather<uint16_t>(X, ld_b, rows, row_b, ids, cap, n_dev, out, ldo_b, st, ci);
     CSGS_LAUNCH_CHECK();
     return CSGS_OK;

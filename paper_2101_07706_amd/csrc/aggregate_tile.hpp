@@ -17,8 +17,12 @@ struct Vec {
 #define CSGS_GLOBAL __attribute__((address_space(1)))
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// ... as they lie in a table whose rows start on any element: global loads of any width take any address on this part
+typedef float f32x2_any __attribute__((ext_vector_type(2), aligned(4)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32_any __attribute__((aligned(2)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
 template <typename U>
 __device__ inline U load_global(const void *p)
 {
@@ -33,19 +37,19 @@ __device__ inline Vec<1> load_row<float, 1>(const float *p) { return Vec<1>{{loa
 template <>
 __device__ inline Vec<2> load_row<float, 2>(const float *p)
 {
-    const f32x2 v = load_global<f32x2>(p);
+    const f32x2 v = load_global<f32x2_any>(p);
     return Vec<2>{{v.x, v.y}};
 }
 template <>
 __device__ inline Vec<4> load_row<float, 4>(const float *p)
 {
-    const f32x4 v = load_global<f32x4>(p);
+    const f32x4 v = load_global<f32x4_any>(p);
     return Vec<4>{{v.x, v.y, v.z, v.w}};
 }
 template <>
 __device__ inline Vec<8> load_row<float, 8>(const float *p)   // two 16-byte loads
 {
-    const f32x4 a = load_global<f32x4>(p), b = load_global<f32x4>(p + 4);
+    const f32x4 a = load_global<f32x4_any>(p), b = load_global<f32x4_any>(p + 4);
     return Vec<8>{{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w}};
 }
 // bfloat16 bit patterns: widening is a 16-bit left shift
@@ -54,20 +58,20 @@ __device__ inline Vec<1> load_row<uint16_t, 1>(const uint16_t *p) { return Vec<1
 template <>
 __device__ inline Vec<2> load_row<uint16_t, 2>(const uint16_t *p)
 {
-    const uint32_t v = load_global<uint32_t>(p);
+    const uint32_t v = load_global<u32_any>(p);
     return Vec<2>{{__uint_as_float(v << 16), __uint_as_float(v & 0xFFFF0000u)}};
 }
 template <>
 __device__ inline Vec<4> load_row<uint16_t, 4>(const uint16_t *p)
 {
-    const u32x2 v = load_global<u32x2>(p);
+    const u32x2_any v = load_global<u32x2_any>(p);
     return Vec<4>{{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16),
                    __uint_as_float(v.y & 0xFFFF0000u)}};
 }
 template <>
 __device__ inline Vec<8> load_row<uint16_t, 8>(const uint16_t *p)
 {
-    const u32x4 v = load_global<u32x4>(p);
+    const u32x4_any v = load_global<u32x4_any>(p);
     return Vec<8>{{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16),
                    __uint_as_float(v.y & 0xFFFF0000u), __uint_as_float(v.z << 16), __uint_as_float(v.z & 0xFFFF0000u),
                    __uint_as_float(v.w << 16), __uint_as_float(v.w & 0xFFFF0000u)}};
@@ -85,6 +89,7 @@ __device__ inline Vec<8> load_row<uint16_t, 8>(const uint16_t *p)
 // them (us, any such row / this: 10000 rows of 66, F = 47, 55 / 30; 2000 of 66, F = 481, 68 / 52).  Nor does the mean decide in
 // a block of which no more than 5/6 are rows of the call: there the wavefronts without rows help (one-kernel layer, F = 128,
 // compared / this: 8 rows of 120 edges 85 / 26, 20 rows 90 / 55; a full block of such rows is level either way).
+// (The figures of odd F are from when such rows had an element or a pair per lane, 64 lanes a row.)
 constexpr int LONG_ROW = 256, LONG_SKEW = 2, LONG_TILE = 2;
 template <int G>
 constexpr int long_row() { return G >= 64 ? 64 : (G >= 32 ? 128 : LONG_ROW); }
@@ -111,15 +116,15 @@ __device__ inline double widen(float x)
 // acc += sum over the n_max staged edges (held one per lane, group base lane `gbase`) of w * x[f..f+V).
 // Loads are issued UNR at a time so that a row with many edges is not a chain of load latencies.
 template <typename T, int V, int G, bool RELU>
-__device__ inline void accumulate_staged(double (&acc)[V], const T *src, float w, int gbase, int32_t n_max, bool active, int32_t f)
+__device__ inline void accumulate_staged(double (&acc)[V], const T *src, float w, int gbase, int32_t n_max, bool active, int32_t slice0, int32_t f)
 {
     // Eight pieces on their way per lane, and the weights fetched from their lanes when used: with sixteen of them for narrow
     // vectors the kernel's registers held it to four blocks per compute unit instead of six, in launches without a long row
     // too (us, sixteen / eight, F = 481, 68536 rows of 4.5 edges 149 / 123; F = 333 bf16, 95553 rows of 0.6 104 / 82; rows of
     // 600 edges among 2000 of 5, F = 250, 19 / 21).
     constexpr int UNR = G < 8 ? G : 8;
-    const uint64_t p = src ? (uint64_t)(uintptr_t)(src + (f - (lane_id() % G) * V)) : (uint64_t)(uintptr_t)g_zero_row;
-    const uint32_t lane_off = active ? (uint32_t)((lane_id() % G) * V * (int)sizeof(T)) : 0u;
+    const uint64_t p = src ? (uint64_t)(uintptr_t)(src + slice0) : (uint64_t)(uintptr_t)g_zero_row;
+    const uint32_t lane_off = active ? (uint32_t)((f - slice0) * (int)sizeof(T)) : 0u;
     if (!src) w = 0.f;
     for (int32_t j0 = 0; j0 < n_max; j0 += UNR) {
         Vec<V> x[UNR];
@@ -230,7 +235,7 @@ enum { HEAD_NONE = 0,    // the share begins with the first edge of a row
 constexpr int tile_rows(int G) { return (WAVE / G) * 8 < WAVE ? (WAVE / G) * 8 : WAVE; }   // about 8 rows per lane group: the most a tile holds
 
 // One wavefront, one tile of `tr` output rows (a power of two, at most tile_rows(G)), one slice of G * V features starting
-// at feature `slice0`.
+// at feature `slice0`; this lane's V features start at f, at most G * V - V beyond.
 // head: LDS, WAVE * V doubles; carry: LDS, 2 * G * V doubles.
 // Row r of the call is stored at Z + (r - out_row0) * ldz.  ZLDS: Z is a tile in LDS.  PL: edges staged at a time.
 // WHOLE (G = 64: the wavefront is one lane group): the sum of a row that goes on beyond the staged edges stays in
@@ -281,7 +286,7 @@ __device__ inline bool aggregate_tile(WaveStage<tile_rows(G), PL> &st, int tr, d
     const int32_t total = __builtin_amdgcn_readlane(incl, WAVE - 1);
     const int grp = lane / G;
     int par = 0;   // which half of `carry` the next round reads
-    const uint32_t lane_off = active ? (uint32_t)((lane % G) * V * (int)sizeof(T)) : 0u;   // a lane past the last feature reads the slice's start and stores nothing
+    const uint32_t lane_off = active ? (uint32_t)((f - slice0) * (int)sizeof(T)) : 0u;   // a lane past the last feature reads the slice's start and stores nothing
     __builtin_amdgcn_wave_barrier();
     // ---- rows without kept edges are zero rows
     for (int rr = grp; rr < tr; rr += NG) {
@@ -475,7 +480,7 @@ __device__ inline bool aggregate_tile(WaveStage<tile_rows(G), PL> &st, int tr, d
 // lane, their columns and values asked for two rounds ahead and the source rows one, so that a round of 256 edges waits for
 // the gathered rows only.
 template <typename T, int V, int G, bool RELU, bool ZLDS = false>
-__device__ inline void aggregate_long_rows(double *__restrict__ part /* LDS, AGG_BLOCK * V */, int tr, int64_t block_row0, int64_t out_row0, bool is_long, int32_t f,
+__device__ inline void aggregate_long_rows(double *__restrict__ part /* LDS, AGG_BLOCK * V */, int tr, int64_t block_row0, int64_t out_row0, bool is_long, int32_t slice0, int32_t f,
                                            bool active, const int32_t *__restrict__ adj_rowptr, const int32_t *__restrict__ adj_col,
                                            const float *__restrict__ adj_val, int64_t n_cols, const T *__restrict__ Xl,
                                            int64_t ldl, int64_t rows_l, const T *__restrict__ Xr, int64_t ldr, int64_t rows_r,
@@ -522,7 +527,7 @@ __device__ inline void aggregate_long_rows(double *__restrict__ part /* LDS, AGG
                 if (s0 >= 0 && s0 < rows_l) src = Xl + (int64_t)s0 * ldl;
                 else if (s0 < 0 && -1 - (int64_t)s0 < rows_r) src = Xr + (-1 - (int64_t)s0) * ldr;
             }
-            accumulate_staged<T, V, G, RELU>(acc, src, w0, gbase, (share - k0) < G ? (share - k0) : G, active, f);
+            accumulate_staged<T, V, G, RELU>(acc, src, w0, gbase, (share - k0) < G ? (share - k0) : G, active, slice0, f);
             c0 = c1; w0 = w1; s0 = s1;
             c1 = c2; w1 = w2;
         }

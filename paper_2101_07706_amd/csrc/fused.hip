@@ -77,7 +77,7 @@ __global__ __launch_bounds__(AGG_BLOCK, 3) void layer_forward_k(const int32_t *_
         stage[wave], TR, nullptr, nullptr, block_row0 + (int64_t)wave * TR, block_row0, 0, f, active, adj_rowptr, adj_col, adj_val, nS_bound, nS,
         n_cols, Xl, ldl, rows_l, Xr, ldr, rows_r, src_row, Zt, ZS, nullptr, 0);
     if (__syncthreads_or(is_long ? 1 : 0))
-        aggregate_long_rows<T, V, G, RELU, true>(part, TR, block_row0, block_row0, is_long, f, active, adj_rowptr, adj_col, adj_val, n_cols, Xl,
+        aggregate_long_rows<T, V, G, RELU, true>(part, TR, block_row0, block_row0, is_long, 0, f, active, adj_rowptr, adj_col, adj_val, n_cols, Xl,
                                                  ldl, rows_l, Xr, ldr, rows_r, src_row, Zt, ZS, nullptr, 0);
 
     // ---- 2. the product.  Tile t of 16 columns, chunk c of 32 k; this wavefront takes the tiles wave, wave + 4, ...

@@ -299,3 +299,55 @@ def test_product_tiles(dev, M, K, N, pad):
         r, c = want.shape
         chain.assert_close(got[:r, :c].cpu().numpy(), want, chain.RTOL, chain.ATOL, what)
         assert bool(torch.isnan(got[r:]).all()) and bool(torch.isnan(got[:, c:]).all()), f"{what}: wrote outside"
+
+
+# Rows that start anywhere: widths around the vectors' (2, 4, 8), the slices' (64 and 256 features) and the narrow rows' limits, tables and
+# outputs that begin an element late with odd distances between rows, both types; nothing beside a row is written
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("F", [1, 2, 3, 4, 5, 8, 16, 17, 33, 65, 127, 128, 129, 200, 257, 264, 515])
+def test_rows_that_start_anywhere(dev, F, bf16):
+    from paper_2101_07706_amd import csgs
+    rng = np.random.default_rng(F)
+    n, n_local, n_remote = 300, 500, 90
+    print(f"[odd rows] F={F} bf16={bf16}", flush=True)
+
+    def late(a, fill):   # the same values, one element late in rows that are longer by an odd number
+        t = torch.full((a.shape[0], a.shape[1] + 3 - a.shape[1] % 2), fill, dtype=torch.int16 if a.dtype == np.int16 else torch.float32, device=dev)
+        t[:, 1:1 + a.shape[1]] = torch.from_numpy(a).to(dev)
+        return t[:, 1:1 + a.shape[1]]
+    X = rng.standard_normal((n_local + n_remote, F)).astype(np.float32)
+    Xh = synth.to_bf16_bits(X) if bf16 else X
+    bits = Xh.view(np.int16) if bf16 else Xh
+    Xl, Xr = late(bits[:n_local], -1 if bf16 else float("nan")), late(bits[n_local:], -1 if bf16 else float("nan"))
+    n_cols = n_local + n_remote
+    lens = rng.poisson(3, n)
+    lens[rng.integers(0, n, 6)] = (0, 1, 300, 257, 90, 140)
+    rowptr, col, val = _csr(rng, lens, n_cols)
+    src = rng.permutation(n_cols).astype(np.int32)                 # column -> row of X
+    src_row = np.where(src < n_local, src, n_local - 1 - src).astype(np.int32)
+    want = oracle.aggregate(rowptr, src[col].astype(np.int32), val, Xh, relu_on_input=True)
+    Zbuf = torch.full((n, F + 2 + F % 2), float("nan"), dtype=torch.float32, device=dev)
+    t = lambda a: torch.from_numpy(a).to(dev)
+    csgs.csgs_aggregate(t(rowptr), t(col), t(val), torch.tensor([n_cols], dtype=torch.int32, device=dev), Xl, Xr, t(src_row), True, Zbuf[:, 1:1 + F])
+    ids = rng.integers(0, n_local, 70).astype(np.int32)
+    out = torch.full((71, F + 2 + F % 2), 7, dtype=Xl.dtype, device=dev)
+    csgs.csgs_gather_rows(Xl, t(ids), None, out[:70, 1:1 + F])
+    torch.cuda.synchronize()
+    chain.assert_close(Zbuf[:, 1:1 + F].cpu().numpy(), want, chain.RTOL, chain.ATOL, "Z")
+    assert bool(torch.isnan(Zbuf[:, 0]).all()) and bool(torch.isnan(Zbuf[:, 1 + F:]).all()), "wrote beside a row"
+    assert np.array_equal(out[:70, 1:1 + F].cpu().numpy(), bits[ids])
+    assert bool((out[:, 0] == 7).all()) and bool((out[:, 1 + F:] == 7).all()) and bool((out[70] == 7).all()), "gathered beside a row"
+    if not bf16:   # the gradient through the same kernel: output mask and table in odd places
+        H = rng.standard_normal((n_cols, F)).astype(np.float32)
+        dense = np.unique(np.stack([rng.integers(0, n, 900), rng.integers(0, n_cols, 900)], 1), axis=0)
+        rp = np.zeros(n + 1, np.int32)
+        np.cumsum(np.bincount(dense[:, 0], minlength=n), out=rp[1:])
+        gcol, gval = dense[:, 1].astype(np.int32), rng.standard_normal(len(dense)).astype(np.float32)
+        dZ = rng.standard_normal((n, F)).astype(np.float32)
+        dH = torch.full((n_cols, F + 2 + F % 2), float("nan"), dtype=torch.float32, device=dev)
+        scratch = torch.full((csgs.csgs_aggregate_grad_scratch_bytes(n_cols, len(gcol)) // 8 + 32,), -1, dtype=torch.int64, device=dev)
+        csgs.csgs_aggregate_grad(t(rp), t(gcol), t(gval), torch.tensor([n_cols], dtype=torch.int32, device=dev), late(dZ, float("nan")),
+                                 late(H, float("nan")), dH[:, 1:1 + F], scratch)
+        torch.cuda.synchronize()
+        chain.assert_close(dH[:, 1:1 + F].cpu().numpy(), oracle.aggregate_grad(rp, gcol, gval, n_cols, dZ, H), chain.RTOL, chain.ATOL, "dH")
+        assert bool(torch.isnan(dH[:, 0]).all()) and bool(torch.isnan(dH[:, 1 + F:]).all()), "wrote beside a row"
