@@ -60,7 +60,7 @@ struct RowOffsets {
 struct Workspace {
     // clean: all-zero whenever no call is in flight
     uint64_t *wtable;    // [n_nodes]  per-node fixed-point weight accumulator
-    uint8_t *tileflag;   // [8 * ceil(n_nodes/64)] byte g = 1: some node of ids 8g .. 8g+7 was touched (read 8 at a time: one 64-id word)
+    uint8_t *tileflag;   // [8 * ceil(n_nodes/64)] byte g = 1: some node of ids 8g .. 8g+7 was touched (read 8 at a time: one 64-id word; between the two candidate kernels of a packed call: a bit per id)
     uint32_t *hit;       // [n_nodes]  draws per candidate position
     // persistent: zeroed once, then never cleared; an entry counts only if it carries the tag of
     // the current call

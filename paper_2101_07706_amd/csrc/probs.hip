@@ -22,7 +22,8 @@
 //                  group (plain loads: the producers are earlier kernels); the skew multiplier is
 //                  fixed by the caller, or taken from the grand totals by the rule of Theorem 1
 //                  (Eq. 12), or zero for remote nodes ("Local" version of Section 5.1); the
-//                  tile's candidates are packed into LDS in id order (ballot popcount), then the
+//                  tile's candidates are packed into LDS in id order (ballot popcount; of many tiles,
+//                  four at a time, from the packed form that cand_partials leaves), then the
 //                  packed list gets its skewed weights, their inclusive running sum and q, and goes
 //                  out as contiguous runs of cand_id / cand_w / cdf / q; restores accumulator and
 //                  flags to zero; the last tile writes the stats
@@ -355,8 +356,10 @@ __device__ inline void sum_handed_over(unsigned long long *acc, const Stage &stg
     __syncthreads();
 }
 
-template <int TILES>
-__global__ __launch_bounds__(CAND_PART_BLOCK) void cand_partials(uint64_t *__restrict__ wtable,
+// PACK: the tiles are also put into the form that the packing kind of cand_emit reads, each tile's weights side by side at the start of its piece
+// of the table and a bit per id in place of the groups' flags.
+template <int TILES, bool PACK>
+__global__ __launch_bounds__(CAND_PART_BLOCK, PACK ? 8 : 1) void cand_partials(uint64_t *__restrict__ wtable,
                                                      uint8_t *__restrict__ tileflag, int64_t n_words,
                                                      int64_t n_nodes, int64_t n_tiles, int32_t lo, int32_t hi,
                                                      const int64_t *__restrict__ meta, Stage stg,
@@ -367,6 +370,7 @@ __global__ __launch_bounds__(CAND_PART_BLOCK) void cand_partials(uint64_t *__res
     constexpr int WAVES = CAND_PART_BLOCK / WAVE, W = TILES * CAND_WORDS / WAVES;   // words per wavefront
     __shared__ uint64_t lds[WAVES][3];
     __shared__ unsigned long long acc[CAND_TILE];
+    __shared__ __attribute__((aligned(8))) uint8_t s_bits[PACK ? WAVES : 1][W * 8];   // a wavefront's groups: a bit per id
     wtable = inst_ptr(wtable, is.ws); tileflag = inst_ptr(tileflag, is.ws); epoch = inst_ptr(epoch, is.ws);
     cand_flag = inst_ptr(cand_flag, is.ws); partial = inst_ptr(partial, is.ws); gtot = inst_ptr(gtot, is.ws);
     status = inst_ptr(status, is.buf); meta = inst_ptr(meta, is.ws);
@@ -426,19 +430,53 @@ __global__ __launch_bounds__(CAND_PART_BLOCK) void cand_partials(uint64_t *__res
     const int64_t tile = own ? t0 : (t0 / TILES) * TILES + wave / waves_per_tile;   // of this wavefront
     const bool in_block = tile >= t0 && tile < t1;
     const int w_used = own ? CAND_WORDS / WAVES : W;   // words of this wavefront
-    const int64_t word0 = tile * CAND_WORDS + (wave % waves_per_tile) * w_used;
+    const uint32_t first_word = (uint32_t)((wave % waves_per_tile) * w_used);   // in the tile
+    const int64_t word0 = tile * CAND_WORDS + first_word;
+    const uint32_t tile_id = (uint32_t)tile * CAND_TILE;                         // below 2^31 + 1024
     const uint32_t lo_u = lo > 0 ? (uint32_t)lo : 0u, hi_u = hi > 0 ? (uint32_t)hi : 0u;
-    uint64_t f8[W], w[W];
+    uint64_t w[W];     // a lane's weights, ids ascending with (step, lane)
+    uint32_t at[W];    // PACK: their ids' places in the tile,
+    bool full[W];      // and whether that entry of the table goes back to zero
+    int steps = w_used;
+    if (!PACK || own) {
+        uint64_t f8[W];
 #pragma unroll
-    for (int k = 0; k < W; ++k) {
-        const bool have = in_block && k < w_used && word0 + k < n_words;
-        f8[k] = have ? reinterpret_cast<const uint64_t *>(tileflag)[word0 + k] : 0ull;   // the word's eight group flags
-    }
+        for (int k = 0; k < W; ++k) {
+            const bool have = in_block && k < w_used && word0 + k < n_words;
+            f8[k] = have ? reinterpret_cast<const uint64_t *>(tileflag)[word0 + k] : 0ull;   // the word's eight group flags
+        }
 #pragma unroll
-    for (int k = 0; k < W; ++k) {
-        const uint32_t id = (uint32_t)(word0 + k) * 64u + lane;   // below 2^31 + 1024
-        // only the touched groups of 8 ids (one 64-byte piece of the table each) are fetched
-        w[k] = (((f8[k] >> (8 * (lane >> 3))) & 0xFFull) && id < (uint32_t)n_nodes) ? wtable[id] : 0ull;
+        for (int k = 0; k < W; ++k) {
+            if (PACK) at[k] = (first_word + k) * WAVE + lane;
+            const uint32_t id = (uint32_t)(word0 + k) * 64u + lane;   // below 2^31 + 1024
+            // only the touched groups of 8 ids (one 64-byte piece of the table each) are fetched
+            w[k] = (((f8[k] >> (8 * (lane >> 3))) & 0xFFull) && id < (uint32_t)n_nodes) ? wtable[id] : 0ull;
+        }
+#pragma unroll
+        for (int k = 0; k < W; ++k) full[k] = w[k] != 0;
+    } else {
+        // Lane l looks at the flag of the wavefront's l-th group of 8 ids; the touched ones, a quarter to a half of them in a
+        // sparse neighbourhood, are then taken eight at a time, a lane per id.
+        static_assert(!PACK || W * 8 == WAVE, "a lane per group");
+        const int64_t group = word0 * 8 + lane;
+        const bool touched = in_block && group < n_words * 8 && tileflag[in_block && group < n_words * 8 ? group : 0];
+        const uint64_t mask = __ballot(touched), below = (1ull << lane) - 1ull;
+        const int n_groups = __popcll(mask);
+        const int to = touched ? __popcll(mask & below) : n_groups + __popcll(~mask & below);
+        const int list = __builtin_amdgcn_ds_permute(to * 4, lane);   // lane r: the r-th touched group
+        steps = (n_groups + 7) >> 3;
+        // (no load under a condition: past the last touched group the first one is read again and dropped)
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+            const int r = k * 8 + (lane >> 3);
+            at[k] = (first_word * 8 + (uint32_t)__shfl(list, r < n_groups ? r : 0, WAVE)) * 8 + (lane & 7);
+            const uint32_t id = tile_id + at[k];
+            full[k] = r < n_groups && id < (uint32_t)n_nodes;
+            w[k] = wtable[id < (uint32_t)n_nodes ? id : (uint32_t)n_nodes - 1u];
+        }
+#pragma unroll
+        for (int k = 0; k < W; ++k)
+            if (!full[k]) w[k] = 0ull;   // (whole pieces go back to zero)
     }
     if (sums) {   // (what did not fit an entry, and ids of the tile outside the local range, have come through the table)
         sum_handed_over(acc, stg, (int32_t)tile_own, n_chunks * share / split, n_chunks);
@@ -461,18 +499,22 @@ __global__ __launch_bounds__(CAND_PART_BLOCK) void cand_partials(uint64_t *__res
             const unsigned long long v = acc[id - (uint32_t)(t0 * CAND_TILE)];
             if (v && id < hi_u) {
                 w[k] += v;
-                wtable[id] = w[k];
-                tileflag[id >> 3] = 1;
+                if (!PACK) {
+                    wtable[id] = w[k];
+                    tileflag[id >> 3] = 1;
+                }
             }
         }
     }
+    if (PACK && lane < W) *reinterpret_cast<uint64_t *>(&s_bits[PACK ? wave : 0][lane * 8]) = 0ull;
     {
         // counts from the ballots (scalar work), weights as the sum over everything and over the local ids: two
         // wave-wide 64-bit sums instead of three
         uint64_t cn = 0, wl = 0, wa = 0;   // cn packs (candidates << 32) | local candidates
 #pragma unroll
         for (int k = 0; k < W; ++k) {
-            const uint32_t id = (uint32_t)(word0 + k) * 64u + lane;
+            if (PACK && k >= steps) continue;
+            const uint32_t id = PACK ? tile_id + at[k] : (uint32_t)(word0 + k) * 64u + lane;
             const bool local = id >= lo_u && id < hi_u;
             cn += ((uint64_t)__popcll(__ballot(w[k] != 0)) << 32) | (uint64_t)__popcll(__ballot(w[k] != 0 && local));
             wa += w[k];
@@ -485,29 +527,64 @@ __global__ __launch_bounds__(CAND_PART_BLOCK) void cand_partials(uint64_t *__res
     // one wavefront publishes each tile; the block's last tile is the last wavefront's.
     // (packed count halves cannot carry: each is at most 1024 per tile)
     const int64_t t = t0 + wave;
-    if (t >= t1) return;
-    const int w0 = own ? 0 : (int)(t % TILES) * waves_per_tile;
-    unsigned long long mine = 0ull;
-    if (lane < 3)
-        for (int i = 0; i < waves_per_tile; ++i) mine += lds[w0 + i][lane];
-    if (lane < 3) st_relaxed(&partial[t * 4 + lane], mine);
-    if (lane == 0) st_flag(&cand_flag[t], tag);   // after the wavefront's value stores have been acknowledged
-    // A wavefront waits only for tiles below its own, and every tile's wavefront publishes before it waits.
-    const int r = (int)(t % LB_GROUP);
-    if (r != LB_GROUP - 1 && t != n_tiles - 1) return;
-    const int64_t g = t / LB_GROUP;
-    bool ok = true;
-    if (lane < r) ok = wait_tag(&cand_flag[g * LB_GROUP + lane], tag, wait_limit(epoch));
-    unsigned long long sum[3];
+    if (!PACK && t >= t1) return;
+    if (t < t1) {
+        const int w0 = own ? 0 : (int)(t % TILES) * waves_per_tile;
+        unsigned long long mine = 0ull;
+        if (lane < 3)
+            for (int i = 0; i < waves_per_tile; ++i) mine += lds[w0 + i][lane];
+        if (lane < 3) st_relaxed(&partial[t * 4 + lane], mine);
+        if (lane == 0) st_flag(&cand_flag[t], tag);   // after the wavefront's value stores have been acknowledged
+        // A wavefront waits only for tiles below its own, and every tile's wavefront publishes before it waits.
+        const int r = (int)(t % LB_GROUP);
+        if (!PACK && r != LB_GROUP - 1 && t != n_tiles - 1) return;
+        if (r == LB_GROUP - 1 || t == n_tiles - 1) {
+            const int64_t g = t / LB_GROUP;
+            bool ok = true;
+            if (lane < r) ok = wait_tag(&cand_flag[g * LB_GROUP + lane], tag, wait_limit(epoch));
+            unsigned long long sum[3];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        const unsigned long long own_sum = __shfl(mine, i, WAVE);
-        sum[i] = own_sum + wave_sum((lane < r && ok) ? ld_relaxed(&partial[(g * LB_GROUP + lane) * 4 + i]) : 0ull);
+            for (int i = 0; i < 3; ++i) {
+                const unsigned long long own_sum = __shfl(mine, i, WAVE);
+                sum[i] = own_sum + wave_sum((lane < r && ok) ? ld_relaxed(&partial[(g * LB_GROUP + lane) * 4 + i]) : 0ull);
+            }
+            if (__ballot(!ok) && lane == 0) atomicOr(status, CSGS_ST_INTERNAL);
+            if (lane < 3) gtot[g * 4 + lane] = lane == 0 ? sum[0] : (lane == 1 ? sum[1] : sum[2]);
+        }
     }
-    if (__ballot(!ok) && lane == 0) atomicOr(status, CSGS_ST_INTERNAL);
-    if (lane < 3) gtot[g * 4 + lane] = lane == 0 ? sum[0] : (lane == 1 ? sum[1] : sum[2]);
+    if (!PACK || !in_block) return;
+    // All of the tile's loads lie before the barrier above, and every entry of the table is written once: up to n_t by the weight
+    // that belongs there, from there on by the lane that has read it.
+    const int first_wave = wave - wave % waves_per_tile;
+    uint32_t put = 0, n_t = 0;   // candidates before this wavefront's, and in the tile
+    for (int i = 0; i < waves_per_tile; ++i) {
+        const uint32_t n = (uint32_t)(lds[first_wave + i][0] >> 32);
+        if (first_wave + i < wave) put += n;
+        n_t += n;
+    }
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+        if (k >= steps) continue;
+        const uint64_t word = __ballot(w[k] != 0);
+        if (word) {
+            if (w[k] != 0) wtable[tile_id + put + (uint32_t)__popcll(word & ((1ull << lane) - 1ull))] = w[k];
+            const uint32_t bits = (uint32_t)(word >> (lane & ~7)) & 0xFFu;
+            if ((lane & 7) == 0 && bits) s_bits[PACK ? wave : 0][(at[k] >> 3) - first_word * 8] = (uint8_t)bits;
+            put += (uint32_t)__popcll(word);
+        }
+        if (full[k] && at[k] >= n_t) wtable[tile_id + at[k]] = 0ull;
+    }
+    if (lane < w_used && word0 + lane < n_words)
+        reinterpret_cast<uint64_t *>(tileflag)[word0 + lane] = *reinterpret_cast<const uint64_t *>(&s_bits[PACK ? wave : 0][lane * 8]);
 }
 
+// Two kinds.  With PACKED a block takes four tiles that cand_partials has packed: where there are many tiles (several instances) the kernel is bound by
+// vector instructions, and what they cost for the sums before a block, for the totals and for every 64-id word is then spent
+// once for four tiles and on the candidates alone (us per launch of 8 x 2392 tiles with 67 candidates each, cand_partials and this kernel,
+// words / packed: 51 + 45 / 53 + 22).  With few tiles the packing only makes cand_partials' blocks last longer (2392 tiles 10.5 + 10.8 / 11.3 +
+// 8.2 with a block per tile, with 450 candidates each 29 + 13 / 31 + 10.3, 701 tiles 6.5 + 6.2 / 8 + 5), so there a block takes one tile, word by word.
+constexpr int64_t CAND_PACKED_FROM = 8192;   // tiles over all instances
+template <bool PACKED>
 __global__ __launch_bounds__(256) void cand_emit(uint64_t *__restrict__ wtable, uint8_t *__restrict__ tileflag,
                                                  int64_t n_words, int64_t n_nodes, int64_t n_tiles, int32_t lo,
                                                  int32_t hi, SkewPolicy pol, const uint64_t *__restrict__ partial,
@@ -519,8 +596,10 @@ __global__ __launch_bounds__(256) void cand_emit(uint64_t *__restrict__ wtable, 
                                                  uint64_t *__restrict__ cdf, float *__restrict__ q, int64_t cap, InstStride is)
 {
     __shared__ uint32_t s_cnt[4];
-    __shared__ uint32_t s_id[4][CAND_TILE / 4];    // the tile's candidates, packed: ids ...
-    __shared__ uint64_t s_wt[4][CAND_TILE / 4];    // ... and fixed-point weights, per wavefront in id order
+    constexpr int TILES = PACKED ? 4 : 1, WORDS = CAND_WORDS / 4;
+    __shared__ uint32_t s_id[4][PACKED ? 1 : CAND_TILE / 4];    // the tile's candidates, packed: ids ...
+    __shared__ uint64_t s_wt[4][PACKED ? 1 : CAND_TILE / 4];    // ... and fixed-point weights, per wavefront in id order
+    __shared__ uint16_t s_at[4][PACKED ? CAND_TILE : 1];        // PACKED: places of a tile's candidates in it, in id order
     wtable = inst_ptr(wtable, is.ws); tileflag = inst_ptr(tileflag, is.ws); partial = inst_ptr(partial, is.ws);
     gtot = inst_ptr(gtot, is.ws); meta = inst_ptr(meta, is.ws); epoch = inst_ptr(epoch, is.ws);
     stats = inst_ptr(stats, is.buf); status = inst_ptr(status, is.buf); cand_id = inst_ptr(cand_id, is.buf);
@@ -529,15 +608,21 @@ __global__ __launch_bounds__(256) void cand_emit(uint64_t *__restrict__ wtable, 
     __shared__ uint64_t s_red[4][6];
     const int lane = lane_id();
     const int wave = (int)(threadIdx.x >> 6);
-    const int64_t t = blockIdx.x;
+    const int64_t t = (int64_t)blockIdx.x * TILES;   // the block's first tile
     const int64_t g = t / 64, n_groups = (n_tiles + 63) / 64;
     // Loads are issued in the order flags, prefix inputs, accumulators, and consumed only after
     // all are in flight, so the tile's own data travels while the prefix is being summed.
-    uint64_t flagged[CAND_WORDS / 4];   // the eight group flags of each 64-id word (one byte per 8 ids)
+    uint64_t flagged[WORDS];   // the eight group flags of each 64-id word (one byte per 8 ids)
+    const int64_t bits_at = t * (CAND_TILE / 16) + threadIdx.x;   // PACKED: a lane holds the bits of 16 ids
+    uint32_t bits = 0;
+    if (PACKED) {
+        if (bits_at < n_words * 4) bits = reinterpret_cast<const uint16_t *>(tileflag)[bits_at];
+    } else {
 #pragma unroll
-    for (int k = 0; k < CAND_WORDS / 4; ++k) {
-        const int64_t word_idx = t * CAND_WORDS + wave * (CAND_WORDS / 4) + k;
-        flagged[k] = word_idx < n_words ? reinterpret_cast<const uint64_t *>(tileflag)[word_idx] : 0ull;
+        for (int k = 0; k < WORDS; ++k) {
+            const int64_t word_idx = t * CAND_WORDS + wave * WORDS + k;
+            flagged[k] = word_idx < n_words ? reinterpret_cast<const uint64_t *>(tileflag)[word_idx] : 0ull;
+        }
     }
     // sums over everything (tot) and over what lies before this tile (pre): group sums before my
     // group, then tile sums before me inside my group
@@ -553,12 +638,20 @@ __global__ __launch_bounds__(256) void cand_emit(uint64_t *__restrict__ wtable, 
             for (int i = 0; i < 3; ++i) pv[i] = partial[j * 4 + i];
         }
     }
-    uint64_t w[CAND_WORDS / 4];
+    uint64_t w[WORDS];
+    if (PACKED) {
+        if (bits) reinterpret_cast<uint16_t *>(tileflag)[bits_at] = 0;   // back to the clean state
+        const uint32_t n = (uint32_t)__popc(bits), incl = wave_inclusive_scan<uint32_t>(n);
+        if (lane == WAVE - 1) s_cnt[wave] = incl;
+        uint16_t *list = s_at[wave] + (incl - n);
+        for (; bits; bits &= bits - 1u) *list++ = (uint16_t)(lane * 16 + __ffs(bits) - 1);
+    } else {
 #pragma unroll
-    for (int k = 0; k < CAND_WORDS / 4; ++k) {
-        // node ids are below 2^31 and a tile adds at most 1023: 32-bit arithmetic, half the instructions
-        const uint32_t id = ((uint32_t)t * CAND_WORDS + wave * (CAND_WORDS / 4) + k) * 64u + lane;
-        w[k] = (((flagged[k] >> (8 * (lane >> 3))) & 0xFFull) && id < (uint32_t)n_nodes) ? wtable[id] : 0ull;
+        for (int k = 0; k < WORDS; ++k) {
+            // node ids are below 2^31 and a tile adds at most 1023: 32-bit arithmetic, half the instructions
+            const uint32_t id = ((uint32_t)t * CAND_WORDS + wave * WORDS + k) * 64u + lane;
+            w[k] = (((flagged[k] >> (8 * (lane >> 3))) & 0xFFull) && id < (uint32_t)n_nodes) ? wtable[id] : 0ull;
+        }
     }
     uint64_t tot[3], pre[3];
 #pragma unroll
@@ -585,6 +678,32 @@ __global__ __launch_bounds__(256) void cand_emit(uint64_t *__restrict__ wtable, 
         for (int i = 0; i < 3; ++i) { s_red[wave][i] = tot[i]; s_red[wave][3 + i] = pre[i]; }
     }
     __syncthreads();
+    uint32_t c0 = 0, c1 = 0, c2 = 0, n_t = 0;   // candidates of the first wavefront's piece, of the first two, ..., of the block
+    auto counts = [&]() {
+        c0 = s_cnt[0];
+        c1 = c0 + s_cnt[1];
+        c2 = c1 + s_cnt[2];
+        n_t = c2 + s_cnt[3];
+    };
+    uint32_t id = 0;
+    uint64_t wi = 0;
+    auto fetch = [&](uint32_t i) {   // candidate i < n_t of the block
+        const int src = i < c0 ? 0 : (i < c1 ? 1 : (i < c2 ? 2 : 3));
+        const uint32_t k = i - (src == 0 ? 0u : (src == 1 ? c0 : (src == 2 ? c1 : c2)));
+        if (PACKED) {
+            const uint32_t first = ((uint32_t)t + src) * CAND_TILE;
+            id = first + s_at[src][k];
+            wi = wtable[first + k];
+            wtable[first + k] = 0ull;   // back to the clean state
+        } else {
+            id = s_id[src][k];
+            wi = s_wt[src][k];
+        }
+    };
+    if (PACKED) {   // the first pass' weights are asked for before the sums are put together
+        counts();
+        if (threadIdx.x < n_t) fetch(threadIdx.x);
+    }
     {   // lanes 0 .. 5 add up one of the six sums each; the others get them by lane broadcast (not every lane all 24 terms)
         const uint64_t mine = lane < 6 ? s_red[0][lane] + s_red[1][lane] + s_red[2][lane] + s_red[3][lane] : 0ull;
 #pragma unroll
@@ -603,41 +722,37 @@ __global__ __launch_bounds__(256) void cand_emit(uint64_t *__restrict__ wtable, 
     // wavefront its own four words in id order, the accumulators and flags going back to their clean state on the way.
     // Everything that costs instructions per candidate -- the skewed weight, the 64-bit running sum, q, the five
     // stores -- is then done on the packed list, by as many wavefronts as it fills, with contiguous stores.
-    uint32_t my_cnt = 0;
+    if (!PACKED) {
+        uint32_t my_cnt = 0;
 #pragma unroll
-    for (int k = 0; k < CAND_WORDS / 4; ++k) {
-        const int slot = wave * (CAND_WORDS / 4) + k;
-        const uint32_t id = ((uint32_t)t * CAND_WORDS + slot) * 64u + lane;
-        const uint64_t word = __ballot(w[k] != 0);
-        if (w[k] != 0) {
-            const uint32_t at = my_cnt + (uint32_t)__popcll(word & ((1ull << lane) - 1ull));
-            s_id[wave][at] = id;
-            s_wt[wave][at] = w[k];
-            wtable[id] = 0ull;  // back to the clean state
+        for (int k = 0; k < WORDS; ++k) {
+            const int slot = wave * (WORDS) + k;
+            const uint32_t my_id = ((uint32_t)t * CAND_WORDS + slot) * 64u + lane;
+            const uint64_t word = __ballot(w[k] != 0);
+            if (w[k] != 0) {
+                const uint32_t at = my_cnt + (uint32_t)__popcll(word & ((1ull << lane) - 1ull));
+                s_id[wave][at] = my_id;
+                s_wt[wave][at] = w[k];
+                wtable[my_id] = 0ull;  // back to the clean state
+            }
+            my_cnt += (uint32_t)__popcll(word);
+            if (flagged[k] && lane == 0) reinterpret_cast<uint64_t *>(tileflag)[t * CAND_WORDS + slot] = 0ull;  // back to the clean state
         }
-        my_cnt += (uint32_t)__popcll(word);
-        if (flagged[k] && lane == 0) reinterpret_cast<uint64_t *>(tileflag)[t * CAND_WORDS + slot] = 0ull;  // back to the clean state
+        if (lane == 0) s_cnt[wave] = my_cnt;
+        __syncthreads();
+        counts();
     }
-    if (lane == 0) s_cnt[wave] = my_cnt;
-    __syncthreads();
-    const uint32_t c0 = s_cnt[0], c1 = c0 + s_cnt[1], c2 = c1 + s_cnt[2], n_t = c2 + s_cnt[3];
     const uint32_t lo_u = lo > 0 ? (uint32_t)lo : 0u, hi_u = hi > 0 ? (uint32_t)hi : 0u;
     const int64_t base_cnt = (int64_t)(pre[0] >> 32);
     uint64_t run_w = pre[1] * m_local + pre[2] * m_remote;   // skewed weight before the packed candidate at pass_base
-    for (uint32_t pass_base = 0; pass_base < n_t; pass_base += 256u) {   // one pass unless the tile holds more than 256 candidates
+    for (uint32_t pass_base = 0; pass_base < n_t; pass_base += 256u) {
         const uint32_t i = pass_base + threadIdx.x;
         const bool have = i < n_t;
         const bool wave_has = pass_base + (uint32_t)wave * WAVE < n_t;   // the same for the whole wavefront
-        uint32_t id = 0;
-        uint64_t wi = 0, wsk = 0, incl = 0;
+        uint64_t wsk = 0, incl = 0;
+        if (have && (!PACKED || pass_base)) fetch(i);
         if (wave_has) {
-            if (have) {
-                const int src = i < c0 ? 0 : (i < c1 ? 1 : (i < c2 ? 2 : 3));
-                const uint32_t at = i - (src == 0 ? 0u : (src == 1 ? c0 : (src == 2 ? c1 : c2)));
-                id = s_id[src][at];
-                wi = s_wt[src][at];
-                wsk = wi * ((id >= lo_u && id < hi_u) ? m_local : m_remote);
-            }
+            if (have) wsk = wi * ((id >= lo_u && id < hi_u) ? m_local : m_remote);
             incl = wave_inclusive_scan(wsk);
             if (lane == WAVE - 1) s_w[wave] = incl;
         } else if (lane == WAVE - 1) {
@@ -658,7 +773,7 @@ __global__ __launch_bounds__(256) void cand_emit(uint64_t *__restrict__ wtable, 
         run_w += s_w[0] + s_w[1] + s_w[2] + s_w[3];
         __syncthreads();   // s_w is written again in the next pass
     }
-    if (t == n_tiles - 1 && threadIdx.x == 0) {
+    if (t + TILES >= n_tiles && threadIdx.x == 0) {
         stats->n_cand = (int64_t)n_cand;
         stats->n_local = (int64_t)n_local;
         stats->n_remote = (int64_t)(n_cand - n_local);
@@ -859,16 +974,22 @@ static int build_probs_impl(const csgs_graph *g, const int32_t *S, int32_t nS, c
     const int64_t below = tiles ? (tile0 + per - 1) / per : 0;
     const int64_t part_blocks = tiles ? below + tiles * split + (w.n_tiles + per - 1) / per - tile1 / per : (w.n_tiles + per - 1) / per;
     const dim3 part_grid((unsigned)part_blocks, 1, nz);
-#define CSGS_CAND_PARTIALS(TILES)                                                                                                       \
-    CSGS_LAUNCH(K_CAND_PARTIALS, cand_partials<TILES>, part_grid, dim3(CAND_PART_BLOCK), st, w.wtable, w.tileflag, n_words, g->n_nodes, \
+#define CSGS_CAND_PARTIALS(TILES, PACK)                                                                                                       \
+    CSGS_LAUNCH(K_CAND_PARTIALS, (cand_partials<TILES, PACK>), part_grid, dim3(CAND_PART_BLOCK), st, w.wtable, w.tileflag, n_words, g->n_nodes, \
                 w.n_tiles, g->local_lo, g->local_hi, rows.meta, stg, (int32_t)(tiles ? below : part_blocks), w.epoch,                   \
                 (unsigned long long *)w.cand_flag, (unsigned long long *)w.partial, w.gtot, status, is)
-    if (per == 1) CSGS_CAND_PARTIALS(1); else CSGS_CAND_PARTIALS(CAND_PART_TILES);
+    const bool packed = w.n_tiles * w.n_inst >= CAND_PACKED_FROM;   // (then `per` is CAND_PART_TILES)
+    if (packed) CSGS_CAND_PARTIALS(CAND_PART_TILES, true);
+    else if (per == 1) CSGS_CAND_PARTIALS(1, false);
+    else CSGS_CAND_PARTIALS(CAND_PART_TILES, false);
 #undef CSGS_CAND_PARTIALS
     CSGS_LAUNCH_CHECK();
-    CSGS_LAUNCH(K_CAND_EMIT, cand_emit, dim3((unsigned)w.n_tiles, 1, nz), dim3(256), st, w.wtable, w.tileflag, n_words,
-                g->n_nodes, w.n_tiles, g->local_lo, g->local_hi, pol, w.partial, w.gtot, rows.meta, shift_base, w.epoch, stats, status, cand_id,
-                cand_w, cdf, q, cap, is);
+#define CSGS_CAND_EMIT(PACKED)                                                                                                              \
+    CSGS_LAUNCH(K_CAND_EMIT, cand_emit<PACKED>, dim3((unsigned)(PACKED ? (w.n_tiles + 3) / 4 : w.n_tiles), 1, nz), dim3(256), st, w.wtable, \
+                w.tileflag, n_words, g->n_nodes, w.n_tiles, g->local_lo, g->local_hi, pol, w.partial, w.gtot, rows.meta, shift_base, w.epoch, \
+                stats, status, cand_id, cand_w, cdf, q, cap, is)
+    if (packed) CSGS_CAND_EMIT(true); else CSGS_CAND_EMIT(false);
+#undef CSGS_CAND_EMIT
     CSGS_LAUNCH_CHECK();
     return CSGS_OK;
 }

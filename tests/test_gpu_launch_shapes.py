@@ -351,3 +351,45 @@ def test_rows_that_start_anywhere(dev, F, bf16):
         torch.cuda.synchronize()
         chain.assert_close(dH[:, 1:1 + F].cpu().numpy(), oracle.aggregate_grad(rp, gcol, gval, n_cols, dZ, H), chain.RTOL, chain.ATOL, "dH")
         assert bool(torch.isnan(dH[:, 0]).all()) and bool(torch.isnan(dH[:, 1 + F:]).all()), "wrote beside a row"
+
+
+# From 8192 tiles of 1024 ids on, over all instances, the candidate sums pack their tiles: tiles with all ids, with one, without any, the last,
+# shorter one, tiles of the local range with and without a hand-over, one instance and several; the workspace is left clean
+@pytest.mark.parametrize("n,n_inst", [(8192 * 1024 + 37, 1), (1366 * 1024 - 5, 6)])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_packed_candidate_tiles(dev, n, n_inst, mode):
+    from paper_2101_07706_amd import csgs, pipeline
+    from test_gpu_scaling import _rows_by_target
+    rng = np.random.default_rng(n_inst)
+    P, n_rows, degree = 16, 4000, 50
+    g, S = _rows_by_target(rng, n, P, n_rows, degree, np.full(n_rows, 0.7))
+    cols = g.colidx.reshape(n_rows, degree)
+    for first, row in ((9 * 1024, 0), ((n // P // 1024 + 40) * 1024, 21)):      # a local tile and a remote one, every id of them
+        ids = np.arange(first, first + 21 * degree) % n
+        cols[row:row + 21] = ids.reshape(21, degree)
+    cols[42] = np.arange(n - degree, n)
+    edge = (n // P) - degree // 2
+    cols[43] = np.arange(edge, edge + degree)                                    # across the end of the local range
+    print(f"[packed tiles] n={n} n_inst={n_inst} mode={mode}", flush=True)
+    K, skew = n_inst, 4.0
+    lb = pipeline.LayerBuffers(n_rows, 1, n, 1, P, dev, n_inst=K)
+    ws = pipeline.Workspace(n, n_rows, 1, g.nnz, dev, n_inst=K, inst_stride=lb.stride, scan_mode=mode)
+    dg = pipeline.DeviceGraph(g, dev)
+    rows = [np.sort(rng.permutation(S)[:n_rows - 700 * k]).astype(np.int32) for k in range(K)]
+    for k in range(K):
+        lb.inst(k).S0[:n_rows].zero_()
+        lb.inst(k).S0[:len(rows[k])].copy_(torch.from_numpy(rows[k]))
+        lb.inst(k).n_next.fill_(len(rows[k]))
+    for _ in range(2):                                                           # the second call finds what the first left
+        csgs.csgs_build_probs(dg.c, lb.S0[:n_rows], skew, lb.cand_id, lb.cand_w, lb.cdf, lb.q, lb.stats, ws.desc, lb.status, nS_dev=lb.n_next)
+    torch.cuda.synchronize()
+    for k in range(K):
+        one, want = lb.inst(k), oracle.build_probs(g, rows[k], skew)
+        n_c = len(want.cand_id)
+        assert int(one.status.item()) == 0 and int(one.stats_host().n_cand) == n_c
+        np.testing.assert_array_equal(one.cand_id[:n_c].cpu().numpy(), want.cand_id)
+        np.testing.assert_array_equal(one.cand_w[:n_c].cpu().numpy().view(np.uint64), want.cand_w)
+        np.testing.assert_array_equal(one.cdf[:n_c].cpu().numpy().view(np.uint64), want.cdf)
+        np.testing.assert_array_equal(one.q[:n_c].cpu().numpy(), want.q)
+        at = k * ws.bytes_per_inst // 8
+        assert int(torch.count_nonzero(ws.buf[at:at + chain.csgs_clean_words(n)]).item()) == 0, "workspace not restored"
