@@ -102,7 +102,6 @@ static int pick_group(const int32_t *rp, const int32_t *col, const float *val, i
 {
     const int64_t vecs = (F + V - 1) / V;
     const int64_t want = (int64_t)F * (int64_t)sizeof(T) >= 1024 ? (vecs + 3) / 4 : vecs;
-    static_assert(V >= 4, "narrow rows take four lanes");
 #define CSGS_AGG_G(GG) launch_agg<T, V, GG>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci)
     if (want <= 4) return CSGS_AGG_G(4);
     if (want <= 8) return CSGS_AGG_G(8);
@@ -117,8 +116,11 @@ static int pick_group(const int32_t *rp, const int32_t *col, const float *val, i
 // often and a slice's edge in the middle of one, so slices are fewer and wider here: of 256 features, of 64 in rows of up to 128.
 // (us, an element or a pair per lane and four slices / this: 2048 rows of 27 edges, F = 602, 36 / 25; 20000 of 6, F = 481, 54 / 47,
 // bf16 56 / 37, F = 201 31 / 24; 3000 of 8, F = 333, 19 / 14, bf16 18 / 15; 68536 of 4.5, F = 481, 146 / 111; 12000 of 26, F = 318,
-// 75 / 68; 60000 of 12, F = 410, 200 / 200, bf16 155 / 137; 2048 of 27, F = 47, 19 / 14.)
-constexpr int32_t ODD_NARROW = 128;
+// 75 / 68; 60000 of 12, F = 410, 200 / 200, bf16 155 / 137; 2048 of 27, F = 47, 19 / 14.)  Rows of 65 to 128 features are taken whole
+// where there are many (two slices / one: 131 K rows of 13, F = 65, 129 / 95, F = 127 176 / 157; 2048 of 26 16.4 / 16.9, 512 of 3 5.7 / 6.1).
+// A handful of rows keeps an element or a pair per lane and a row per wavefront, which has no shares to put together (16 rows of 3,
+// F = 31, 4.9 against 5.4, F = 63 4.9 / 5.2; 64 of 3 5.3 / 5.6, 5.1 / 5.5; 256 of 3 5.8 / 5.7).
+constexpr int32_t ODD_NARROW = 128, ODD_FEW_ROWS = 64, ODD_WHOLE_ROWS = 4096;
 template <typename T>
 static int pick_odd(const int32_t *rp, const int32_t *col, const float *val, int32_t nS, const int32_t *nsd, const int32_t *ncp, const void *Xl,
                     int64_t ldl, int64_t rl, const void *Xr, int64_t ldr, int64_t rr, const int32_t *src_row, int32_t F, int relu, float *Z, int64_t ldz,
@@ -126,6 +128,7 @@ static int pick_odd(const int32_t *rp, const int32_t *col, const float *val, int
 {
 #define CSGS_AGG_VG(V, G) launch_agg<T, V, G>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci)
     if (F > ODD_NARROW) return CSGS_AGG_VG(8, 32);
+    if (F > 64 && (int64_t)nS * ci.n > ODD_WHOLE_ROWS) return CSGS_AGG_VG(4, 32);
     if (F > 32) return CSGS_AGG_VG(4, 16);
     if (F > 16) return CSGS_AGG_VG(4, 8);
     if (F >= 4) return CSGS_AGG_VG(4, 4);
@@ -150,6 +153,10 @@ static int pick_vec(const int32_t *rp, const int32_t *col, const float *val, int
     };
     if (whole(8)) return pick_group<T, 8>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci);
     if (whole(4)) return pick_group<T, 4>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci);
+    if ((int64_t)nS * ci.n <= ODD_FEW_ROWS) {
+        if (whole(2)) return pick_group<T, 2>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci);
+        return pick_group<T, 1>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci);
+    }
     return pick_odd<T>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci);
 }
 

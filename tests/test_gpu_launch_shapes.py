@@ -308,7 +308,7 @@ def test_product_tiles(dev, M, K, N, pad):
 def test_rows_that_start_anywhere(dev, F, bf16):
     from paper_2101_07706_amd import csgs
     rng = np.random.default_rng(F)
-    n, n_local, n_remote = 300, 500, 90
+    n, n_local, n_remote = 5000 if 64 < F <= 128 else 300, 500, 90   # (narrow rows are cut by how many there are)
     print(f"[odd rows] F={F} bf16={bf16}", flush=True)
 
     def late(a, fill):   # the same values, one element late in rows that are longer by an odd number
@@ -329,11 +329,15 @@ def test_rows_that_start_anywhere(dev, F, bf16):
     Zbuf = torch.full((n, F + 2 + F % 2), float("nan"), dtype=torch.float32, device=dev)
     t = lambda a: torch.from_numpy(a).to(dev)
     csgs.csgs_aggregate(t(rowptr), t(col), t(val), torch.tensor([n_cols], dtype=torch.int32, device=dev), Xl, Xr, t(src_row), True, Zbuf[:, 1:1 + F])
+    few = torch.full((61, F), float("nan"), dtype=torch.float32, device=dev)   # a handful of rows
+    csgs.csgs_aggregate(t(rowptr[:61]), t(col), t(val), torch.tensor([n_cols], dtype=torch.int32, device=dev), Xl, Xr, t(src_row), True, few[:60])
     ids = rng.integers(0, n_local, 70).astype(np.int32)
     out = torch.full((71, F + 2 + F % 2), 7, dtype=Xl.dtype, device=dev)
     csgs.csgs_gather_rows(Xl, t(ids), None, out[:70, 1:1 + F])
     torch.cuda.synchronize()
     chain.assert_close(Zbuf[:, 1:1 + F].cpu().numpy(), want, chain.RTOL, chain.ATOL, "Z")
+    chain.assert_close(few[:60].cpu().numpy(), want[:60], chain.RTOL, chain.ATOL, "Z of few rows")
+    assert bool(torch.isnan(few[60]).all()), "wrote past the last row"
     assert bool(torch.isnan(Zbuf[:, 0]).all()) and bool(torch.isnan(Zbuf[:, 1 + F:]).all()), "wrote beside a row"
     assert np.array_equal(out[:70, 1:1 + F].cpu().numpy(), bits[ids])
     assert bool((out[:, 0] == 7).all()) and bool((out[:, 1 + F:] == 7).all()) and bool((out[70] == 7).all()), "gathered beside a row"
