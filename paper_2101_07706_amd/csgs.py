@@ -139,16 +139,28 @@ def strerror(code: int) -> str:
     return lib().csgs_strerror(code).decode()
 
 
+# A step of a small mini-batch is as long as the host takes to issue it (two-layer steps of 1024 and 777 rows through the helpers of
+# pipeline.py, us: 133 and 138 with a ctypes object per pointer, a Stream object per call and a view of the row pointers per
+# layer, 119 and 114 -- about the device's time -- without).  Declared argument types turn plain integers into pointers.
 def _ptr(t):
-    """Device pointer of a tensor; ctypes objects (a caller's mutable pointer box) pass through."""
-    if t is None or isinstance(t, C._SimpleCData):
+    """Device address of a tensor; ctypes objects (a caller's mutable pointer box) pass through."""
+    if t is None:
+        return None
+    if isinstance(t, C._SimpleCData):
         return t
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+_raw_stream, _device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    """Handle of a stream; None: the current device's current stream."""
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _chk(rc, where):
@@ -313,19 +325,23 @@ def _inst(inst):
 
 
 def csgs_aggregate(adj_rowptr, adj_col, adj_val, n_next, X_local, X_remote, src_row, relu_on_input, Z,
-                   stream=None, nS_dev=None, inst=None):
+                   stream=None, nS_dev=None, inst=None, nS=None):
     """X_* are 2-D float32 tensors or int16/uint16/bfloat16 tensors holding bfloat16 rows.
-    inst (InstStrides): several instances per launch; the tensors are instance 0's."""
+    inst (InstStrides): several instances per launch; the tensors are instance 0's.
+    nS: row capacity, where adj_rowptr holds more than nS + 1 entries."""
     suffix, lead = _inst(inst)
     dtype = F32 if X_local.dtype == torch.float32 else BF16
-    F = X_local.shape[1]
+    rows_l, F = X_local.shape
     rows_r = 0 if X_remote is None else X_remote.shape[0]
     ld_r = 0 if X_remote is None else X_remote.stride(0)
     if X_remote is not None and rows_r == 0:
         X_remote = None
-    Xl_ptr = _ptr(X_local) if X_local.shape[0] > 0 else None
-    _call("csgs_aggregate" + suffix, *lead, _ptr(adj_rowptr), _ptr(adj_col), _ptr(adj_val), adj_rowptr.numel() - 1,
-                              _ptr(nS_dev), _ptr(n_next), Xl_ptr, X_local.stride(0), X_local.shape[0], _ptr(X_remote),
+    Xl_ptr = _ptr(X_local) if rows_l > 0 else None
+    rows = adj_rowptr.numel() - 1
+    if nS is not None and nS < rows:
+        rows = nS
+    _call("csgs_aggregate" + suffix, *lead, _ptr(adj_rowptr), _ptr(adj_col), _ptr(adj_val), rows,
+                              _ptr(nS_dev), _ptr(n_next), Xl_ptr, X_local.stride(0), rows_l, _ptr(X_remote),
                               ld_r, rows_r, _ptr(src_row), F, dtype, 1 if relu_on_input else 0, _ptr(Z),
                               Z.stride(0), _stream(stream))
 

@@ -117,7 +117,7 @@ def sample_step(dg, ws, S, skew, B, seed, it, layer, lb, stream=None, want_q=Tru
         lb.remote = csgs.make_remote_out(dg.local_lo, dg.local_hi, dg.part_bounds, lb.remote_total, lb.per_part, lb.src_row,
                                          lb.remote_ids)
     csgs.csgs_sample_layer(dg.c, S, lb.cand_id, lb.cdf, lb.stats, B, seed, it, layer, lb.S_next, lb.mult,
-                           lb.p_incl, lb.n_next, lb.adj_rowptr[:nS + 1], lb.adj_col, lb.adj_val, lb.adj_nnz,
+                           lb.p_incl, lb.n_next, lb.adj_rowptr, lb.adj_col, lb.adj_val, lb.adj_nnz,
                            ws.desc, lb.status, stream, iter_dev=iter_dev, remote=lb.remote if fuse_remote else None, nS=nS)
     if not fuse_remote:
         csgs.csgs_remote_count(lb.S_next, lb.n_next, dg.local_lo, dg.local_hi, dg.part_bounds, lb.remote_total,
@@ -153,8 +153,8 @@ def compute_step(lb, nS, X_local, X_remote, use_src_row, relu, W, Z, H, stream=N
     if strides is not None:
         x, xr, z, h = strides
         agg, gemm = instance_strides(lb, x, xr, z, n_inst), instance_strides(lb, z, 0, h, n_inst)
-    csgs.csgs_aggregate(lb.adj_rowptr[:nS + 1], lb.adj_col, lb.adj_val, lb.n_next, X_local, X_remote,
-                        lb.src_row if use_src_row else None, relu, Z, stream, nS_dev=nS_dev, inst=agg)
+    csgs.csgs_aggregate(lb.adj_rowptr, lb.adj_col, lb.adj_val, lb.n_next, X_local, X_remote,
+                        lb.src_row if use_src_row else None, relu, Z, stream, nS_dev=nS_dev, inst=agg, nS=nS)
     csgs.csgs_layer_gemm(Z, W, H, stream, M_dev=nS_dev, inst=gemm)
     return False
 
