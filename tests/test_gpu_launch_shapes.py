@@ -301,6 +301,26 @@ def test_product_tiles(dev, M, K, N, pad):
         assert bool(torch.isnan(got[r:]).all()) and bool(torch.isnan(got[:, c:]).all()), f"{what}: wrote outside"
 
 
+# The weight gradient's tiles and parts: each shape of its rule (2x2, 2x4, 2x3, 1x4, 1x2, 2x1, 1x1), one part and several, columns beside their
+# edges, rows that are no multiple of a part's chunks
+@pytest.mark.parametrize("M,K,N", [(65, 64, 2), (7135, 47, 1), (63, 193, 322), (2400, 17, 66), (2433, 130, 306), (10847, 175, 1), (18817, 175, 17),
+                                   (12287, 161, 33), (12033, 66, 318)])
+def test_weight_gradient_tiles(dev, M, K, N):
+    from paper_2101_07706_amd import csgs
+    rng = np.random.default_rng(3 * M + K + N)
+    print(f"[dW tiles] {M} rows, {K} x {N}", flush=True)
+    Z, G = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((M, N)).astype(np.float32)
+    dW = torch.full((K + 1, N + 3), float("nan"), dtype=torch.float32, device=dev)
+    scratch = torch.full((csgs.csgs_layer_gemm_grad_w_scratch_bytes(M, K, N) // 8,), -1, dtype=torch.int64, device=dev)
+    csgs.csgs_layer_gemm_grad_w(torch.from_numpy(Z).to(dev), torch.from_numpy(G).to(dev), dW[:K, :N], scratch)
+    torch.cuda.synchronize()
+    # one rounding to float of a sum held in double: half a unit in the last place, and what 2^-53 leaves of the summands
+    want = Z.T.astype(np.float64) @ G.astype(np.float64)
+    bound = 2.0 ** -24 * np.abs(want) + M * 2.0 ** -52 * (np.abs(Z).T.astype(np.float64) @ np.abs(G).astype(np.float64))
+    assert (np.abs(dW[:K, :N].cpu().numpy() - want) <= bound).all()
+    assert torch.isnan(dW[K]).all() and torch.isnan(dW[:, N:]).all()
+
+
 # Rows that start anywhere: widths around the vectors' (2, 4, 8), the slices' (64 and 256 features) and the narrow rows' limits, tables and
 # outputs that begin an element late with odd distances between rows, both types; nothing beside a row is written
 @pytest.mark.parametrize("bf16", [False, True])
