@@ -445,7 +445,7 @@ __global__ __launch_bounds__(256) void gather_rows_k(const char *__restrict__ X,
         const bool ok = id >= 0 && id < rows;
         for (int64_t f = lane * SIZE; f < row_b; f += WAVE * SIZE) {
             const int64_t at = f < row_b - SIZE ? f : row_b - SIZE;
-            *reinterpret_cast<U *>(out + k * ldo_b + at) = ok ? *reinterpret_cast<const U *>(X + id * ld_b + at) : U{};
+            store_global<U, 2>(out + k * ldo_b + at, ok ? load_global<U, 2>(X + id * ld_b + at) : U{});
         }
     }
 }
@@ -475,7 +475,7 @@ extern "C" int csgs_gather_rows_n(const csgs_inst_strides *inst, const void *X, 
     const int64_t row_b = (int64_t)F * elt, ld_b = ld * elt, ldo_b = ldo * elt;
     hipStream_t st = (hipStream_t)stream;
     // (131 K rows of 333 bf16 values, an element per lane 43 us, this 31; of 333 floats, 20 K rows, 11.5 / 10.2; whole pieces: level)
-    if (row_b >= 16) launch_gather<u32x4_any>(X, ld_b, rows, row_b, ids, cap, n_dev, out, ldo_b, st, ci);
+    if (row_b >= 16) launch_gather<u32x4>(X, ld_b, rows, row_b, ids, cap, n_dev, out, ldo_b, st, ci);
     else launch_gather<uint16_t>(X, ld_b, rows, row_b, ids, cap, n_dev, out, ldo_b, st, ci);
     CSGS_LAUNCH_CHECK();
     return CSGS_OK;

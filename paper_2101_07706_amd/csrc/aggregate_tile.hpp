@@ -17,16 +17,26 @@ struct Vec {
 #define CSGS_GLOBAL __attribute__((address_space(1)))
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-// ... as they lie in a table whose rows start on any element: global loads of any width take any address on this part
-typedef float f32x2_any __attribute__((ext_vector_type(2), aligned(4)));
-typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-typedef uint32_t u32_any __attribute__((aligned(2)));
-typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
-typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
-template <typename U>
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// A value in a table whose rows start on any element of ALIGN bytes: global loads and stores of any width take any address on this
+// part, but the compiler has to know that they are asked to.  (A struct, whose alignment is part of the type: that of a typedef is
+// dropped where it is a template argument, and the access then claims the vector's own.)
+template <typename U, int ALIGN>
+struct __attribute__((packed, aligned(ALIGN))) Piece {
+    U v;
+};
+template <typename U, int ALIGN = (int)alignof(U)>
 __device__ inline U load_global(const void *p)
 {
-    return *reinterpret_cast<const CSGS_GLOBAL U *>((uintptr_t)p);
+    static_assert(alignof(Piece<U, ALIGN>) == ALIGN && sizeof(Piece<U, ALIGN>) == sizeof(U), "the claim on the address");
+    return reinterpret_cast<const CSGS_GLOBAL Piece<U, ALIGN> *>((uintptr_t)p)->v;
+}
+template <typename U, int ALIGN = (int)alignof(U)>
+__device__ inline void store_global(void *p, U v)
+{
+    static_assert(alignof(Piece<U, ALIGN>) == ALIGN && sizeof(Piece<U, ALIGN>) == sizeof(U), "the claim on the address");
+    reinterpret_cast<CSGS_GLOBAL Piece<U, ALIGN> *>((uintptr_t)p)->v = v;
 }
 
 template <typename T, int V>
@@ -37,19 +47,19 @@ __device__ inline Vec<1> load_row<float, 1>(const float *p) { return Vec<1>{{loa
 template <>
 __device__ inline Vec<2> load_row<float, 2>(const float *p)
 {
-    const f32x2 v = load_global<f32x2_any>(p);
+    const f32x2 v = load_global<f32x2, 4>(p);
     return Vec<2>{{v.x, v.y}};
 }
 template <>
 __device__ inline Vec<4> load_row<float, 4>(const float *p)
 {
-    const f32x4 v = load_global<f32x4_any>(p);
+    const f32x4 v = load_global<f32x4, 4>(p);
     return Vec<4>{{v.x, v.y, v.z, v.w}};
 }
 template <>
 __device__ inline Vec<8> load_row<float, 8>(const float *p)   // two 16-byte loads
 {
-    const f32x4 a = load_global<f32x4_any>(p), b = load_global<f32x4_any>(p + 4);
+    const f32x4 a = load_global<f32x4, 4>(p), b = load_global<f32x4, 4>(p + 4);
     return Vec<8>{{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w}};
 }
 // bfloat16 bit patterns: widening is a 16-bit left shift
@@ -58,20 +68,20 @@ __device__ inline Vec<1> load_row<uint16_t, 1>(const uint16_t *p) { return Vec<1
 template <>
 __device__ inline Vec<2> load_row<uint16_t, 2>(const uint16_t *p)
 {
-    const uint32_t v = load_global<u32_any>(p);
+    const uint32_t v = load_global<uint32_t, 2>(p);
     return Vec<2>{{__uint_as_float(v << 16), __uint_as_float(v & 0xFFFF0000u)}};
 }
 template <>
 __device__ inline Vec<4> load_row<uint16_t, 4>(const uint16_t *p)
 {
-    const u32x2_any v = load_global<u32x2_any>(p);
+    const u32x2 v = load_global<u32x2, 2>(p);
     return Vec<4>{{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16),
                    __uint_as_float(v.y & 0xFFFF0000u)}};
 }
 template <>
 __device__ inline Vec<8> load_row<uint16_t, 8>(const uint16_t *p)
 {
-    const u32x4_any v = load_global<u32x4_any>(p);
+    const u32x4 v = load_global<u32x4, 2>(p);
     return Vec<8>{{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16),
                    __uint_as_float(v.y & 0xFFFF0000u), __uint_as_float(v.z << 16), __uint_as_float(v.z & 0xFFFF0000u),
                    __uint_as_float(v.w << 16), __uint_as_float(v.w & 0xFFFF0000u)}};

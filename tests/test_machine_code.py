@@ -165,3 +165,42 @@ def test_narrow_aggregations_fill_the_lds(functions, tmp_path):
             seen += 1
             assert 512 // (-(-regs // 8) * 8) >= (160 << 10) // lds, f"{name.group(1)}: {regs} registers, {lds} bytes of LDS"
     assert seen == 16
+
+
+# Rows that start on any element: what the compiler is told of a piece's address is the alignment of an element and no more,
+# in every load and store of a feature row (a typedef's own alignment, for one, is lost where it is a template argument).
+ROW_PIECES = """
+#include "aggregate_tile.hpp"
+using namespace csgs;
+template <typename T, int V>
+__device__ inline void row(const T *x, float *out)
+{
+    const Vec<V> v = load_row<T, V>(x + threadIdx.x);
+    for (int i = 0; i < V; ++i) out[i * 64 + threadIdx.x] = v.x[i];
+}
+#define ROW(T, V) extern "C" __global__ void row_##T##_##V(const T *x, float *out) { row<T, V>(x, out); }
+ROW(float, 1) ROW(float, 2) ROW(float, 4) ROW(float, 8)
+ROW(uint16_t, 1) ROW(uint16_t, 2) ROW(uint16_t, 4) ROW(uint16_t, 8)
+extern "C" __global__ void piece_uint16_t(const char *x, char *out)
+{
+    store_global<u32x4, 2>(out + 2 * threadIdx.x, load_global<u32x4, 2>(x + 2 * threadIdx.x));
+}
+"""
+
+
+def test_rows_claim_no_more_than_an_element(tmp_path):
+    src = tmp_path / "pieces.hip"
+    src.write_text(ROW_PIECES)
+    ir = subprocess.run(["hipcc", "--offload-arch=gfx950", "--cuda-device-only", "-O3", "-std=c++17", "-S", "-emit-llvm", "-o", "-",
+                         "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC, str(src)], stdout=subprocess.PIPE, text=True, check=True).stdout
+    seen = {}
+    for name, body in re.findall(r"^define [^\n]*@((?:row|piece)_\w+)\([^\n]*\{\n(.*?)^\}", ir, re.M | re.S):
+        element = 4 if "float" in name else 2
+        loads = [(line.strip(), int(align)) for line, align in re.findall(r"(= load (?:<|i|float|half)[^\n]*addrspace\(1\)[^\n]*?align (\d+)[^\n]*)", body)]
+        stores = [(line.strip(), int(align)) for line, align in re.findall(r"(store <[^\n]*addrspace\(1\)[^\n]*?align (\d+)[^\n]*)", body)]
+        assert loads, name
+        assert name[0] == "r" or stores, name
+        for line, align in loads + stores:
+            assert align <= element, f"{name}: {line}"
+        seen[name] = len(loads)
+    assert len(seen) == 9, seen
