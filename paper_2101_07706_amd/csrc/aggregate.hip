@@ -422,13 +422,14 @@ __host__ inline GradScratch carve_grad(void *base, int32_t n_cols_cap, int64_t a
     return g;
 }
 
-// out[k, :] = X[ids[k], :] in pieces of U, from any address; one wavefront per row, rows strided over the grid.  Rows of `row_b` bytes, at least
-// one piece: the last piece ends with the row and may overlap the one before.  An id outside the table gives a zero row.
-template <typename U>
-__global__ __launch_bounds__(256) void gather_rows_k(const char *__restrict__ X, int64_t ld_b, int64_t rows, int64_t row_b,
+// out[k, :] = X[ids[k], :]; one wavefront per row, rows strided over the grid.  An id outside the table gives a zero row.
+// WHOLE: rows of whole pieces of U that start on a multiple of it, everything counted in pieces.  Else everything is counted in bytes, the
+// pieces are taken from any address, and the last one of a row (of at least one piece) ends with it and may overlap the one before.
+template <typename U, bool WHOLE>
+__global__ __launch_bounds__(256) void gather_rows_k(const U *__restrict__ X, int64_t ld, int64_t rows, int64_t row,
                                                      const int32_t *__restrict__ ids, int64_t cap,
-                                                     const int64_t *__restrict__ n_dev, char *__restrict__ out,
-                                                     int64_t ldo_b, CompStride cs)
+                                                     const int64_t *__restrict__ n_dev, U *__restrict__ out,
+                                                     int64_t ldo, CompStride cs)
 {
     constexpr int32_t SIZE = (int32_t)sizeof(U);
     X = inst_ptr(X, cs.x); ids = inst_ptr(ids, cs.adj); n_dev = inst_ptr(n_dev, cs.adj); out = inst_ptr(out, cs.out);
@@ -443,21 +444,26 @@ __global__ __launch_bounds__(256) void gather_rows_k(const char *__restrict__ X,
     for (int64_t k = wave; k < n; k += n_waves) {
         const int64_t id = ids[k];
         const bool ok = id >= 0 && id < rows;
-        for (int64_t f = lane * SIZE; f < row_b; f += WAVE * SIZE) {
-            const int64_t at = f < row_b - SIZE ? f : row_b - SIZE;
-            store_global<U, 2>(out + k * ldo_b + at, ok ? load_global<U, 2>(X + id * ld_b + at) : U{});
+        if constexpr (WHOLE) {
+            for (int32_t f = lane; f < (int32_t)row; f += WAVE) out[k * ldo + f] = ok ? X[id * ld + f] : U{};
+        } else {
+            for (int64_t f = lane * SIZE; f < row; f += WAVE * SIZE) {
+                const int64_t at = f < row - SIZE ? f : row - SIZE;
+                store_global<U, 2>((char *)out + k * ldo + at, ok ? load_global<U, 2>((const char *)X + id * ld + at) : U{});
+            }
         }
     }
 }
 
-template <typename U>
+template <typename U, bool WHOLE>
 static void launch_gather(const void *X, int64_t ld_b, int64_t rows, int64_t row_b, const int32_t *ids, int64_t cap,
                           const int64_t *n_dev, void *out, int64_t ldo_b, hipStream_t st, const CompInst &ci)
 {
     const int64_t waves = cap < 8192 ? cap : 8192;
     const unsigned blocks = (unsigned)((waves + 3) / 4);
-    CSGS_LAUNCH(K_GATHER_ROWS, gather_rows_k<U>, dim3(blocks, 1, (unsigned)ci.n), dim3(256), st, (const char *)X, ld_b, rows, row_b, ids, cap,
-                n_dev, (char *)out, ldo_b, ci.cs);
+    constexpr int64_t UNIT = WHOLE ? (int64_t)sizeof(U) : 1;
+    CSGS_LAUNCH(K_GATHER_ROWS, (gather_rows_k<U, WHOLE>), dim3(blocks, 1, (unsigned)ci.n), dim3(256), st, (const U *)X, ld_b / UNIT, rows,
+                row_b / UNIT, ids, cap, n_dev, (U *)out, ldo_b / UNIT, ci.cs);
 }
 
 }  // namespace csgs
@@ -474,9 +480,19 @@ extern "C" int csgs_gather_rows_n(const csgs_inst_strides *inst, const void *X, 
     const int64_t elt = dtype == CSGS_F32 ? 4 : 2;
     const int64_t row_b = (int64_t)F * elt, ld_b = ld * elt, ldo_b = ldo * elt;
     hipStream_t st = (hipStream_t)stream;
-    // (131 K rows of 333 bf16 values, an element per lane 43 us, this 31; of 333 floats, 20 K rows, 11.5 / 10.2; whole pieces: level)
-    if (row_b >= 16) launch_gather<u32x4>(X, ld_b, rows, row_b, ids, cap, n_dev, out, ldo_b, st, ci);
-    else launch_gather<uint16_t>(X, ld_b, rows, row_b, ids, cap, n_dev, out, ldo_b, st, ci);
+    auto whole = [&](int64_t a) {
+        return row_b % a == 0 && ld_b % a == 0 && ldo_b % a == 0 && ((uintptr_t)X % (uintptr_t)a) == 0 &&
+               ((uintptr_t)out % (uintptr_t)a) == 0;
+    };
+    const int64_t piece = whole(16) ? 16 : (whole(4) ? 4 : 2);
+    // Rows that the wavefront's lanes cover at once go in whole pieces; longer ones that are no whole 16-byte pieces in 16 bytes from any
+    // address (us, 131 K rows, 16 bytes from any address / whole pieces: 9 bf16 values 14.1 / 10.3, 5 floats 12.9 / 10.8, 31 floats 16.2 /
+    // 15.7, 133 floats 22.7 / 28.1, 333 bf16 values 26.9 / 42.7; 75 bf16 values 16.5 / 20.8, of 30 K rows 5.7 / 5.3).  No pieces of 8: the same
+    // in pieces of 4 is quicker (12 bf16 values 13.5 / 12.0, 2 floats 11.9 / 9.4).
+    if (piece == 16) launch_gather<u32x4, true>(X, ld_b, rows, row_b, ids, cap, n_dev, out, ldo_b, st, ci);
+    else if (row_b > WAVE * piece) launch_gather<u32x4, false>(X, ld_b, rows, row_b, ids, cap, n_dev, out, ldo_b, st, ci);
+    else if (piece == 4) launch_gather<uint32_t, true>(X, ld_b, rows, row_b, ids, cap, n_dev, out, ldo_b, st, ci);
+    else launch_gather<uint16_t, true>(X, ld_b, rows, row_b, ids, cap, n_dev, out, ldo_b, st, ci);
     CSGS_LAUNCH_CHECK();
     return CSGS_OK;
 }

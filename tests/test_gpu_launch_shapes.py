@@ -417,3 +417,29 @@ def test_packed_candidate_tiles(dev, n, n_inst, mode):
         np.testing.assert_array_equal(one.q[:n_c].cpu().numpy(), want.q)
         at = k * ws.bytes_per_inst // 8
         assert int(torch.count_nonzero(ws.buf[at:at + chain.csgs_clean_words(n)]).item()) == 0, "workspace not restored"
+
+
+# Staged rows in whole pieces of 2, 4 and 16 bytes while 64 lanes cover them at once, beyond in 16 bytes from any address: widths around the
+# pieces and the limits (128 and 256 bytes), tables and outputs that begin on a piece and one element late; ids outside the table
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("F", [1, 2, 3, 4, 5, 7, 8, 9, 10, 12, 62, 63, 64, 65, 66, 127, 128, 129, 130, 132, 200, 333])
+def test_gathered_row_pieces(dev, F, bf16):
+    from paper_2101_07706_amd import csgs
+    rng = np.random.default_rng(F)
+    rows, cap, n = 300, 77, 70
+    dtype = np.int16 if bf16 else np.float32
+    X = rng.integers(-30000, 30000, (rows, F)).astype(dtype)
+    ids = rng.integers(0, rows, cap).astype(np.int32)
+    ids[3], ids[4] = -1, rows
+    want = np.where(((ids >= 0) & (ids < rows))[:, None], X[np.clip(ids, 0, rows - 1)], 0)[:n].astype(dtype)
+    for late in (0, 1):
+        print(f"[gathered rows] F={F} bf16={bf16} late={late}", flush=True)
+        place = lambda r, fill: torch.full((r, (F + 15) // 8 * 8 + late), fill, dtype=torch.from_numpy(X).dtype, device=dev)
+        table, out = place(rows, 5), place(cap, 7)
+        table[:, late:late + F] = torch.from_numpy(X).to(dev)
+        csgs.csgs_gather_rows(table[:, late:late + F], torch.from_numpy(ids).to(dev), torch.tensor([n], dtype=torch.int64, device=dev),
+                              out[:, late:late + F])
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(out[:n, late:late + F].cpu().numpy(), want)
+        out[:n, late:late + F] = 7
+        assert bool((out == 7).all()), "wrote beside the rows"
