@@ -113,27 +113,37 @@ static int pick_group(const int32_t *rp, const int32_t *col, const float *val, i
 
 // Tables whose rows start anywhere, or whose rows are no whole number of four-element pieces: the same wide loads, which take any
 // address, the last V features of a row together (they overlap the lane's before).  A piece then lies across two cache lines more
-// often and a slice's edge in the middle of one, so slices are fewer and wider here: of 256 features, of 64 in rows of up to 128.
-// (us, an element or a pair per lane and four slices / this: 2048 rows of 27 edges, F = 602, 36 / 25; 20000 of 6, F = 481, 54 / 47,
-// bf16 56 / 37, F = 201 31 / 24; 3000 of 8, F = 333, 19 / 14, bf16 18 / 15; 68536 of 4.5, F = 481, 146 / 111; 12000 of 26, F = 318,
-// 75 / 68; 60000 of 12, F = 410, 200 / 200, bf16 155 / 137; 2048 of 27, F = 47, 19 / 14.)  Rows of 65 to 128 features are taken whole
-// where there are many (two slices / one: 131 K rows of 13, F = 65, 129 / 95, F = 127 176 / 157; 2048 of 26 16.4 / 16.9, 512 of 3 5.7 / 6.1).
-// A handful of rows keeps an element or a pair per lane and a row per wavefront, which has no shares to put together (16 rows of 3,
-// F = 31, 4.9 against 5.4, F = 63 4.9 / 5.2; 64 of 3 5.3 / 5.6, 5.1 / 5.5; 256 of 3 5.8 / 5.7).
-constexpr int32_t ODD_NARROW = 128, ODD_FEW_ROWS = 64, ODD_WHOLE_ROWS = 4096;
+// often and a slice's edge in the middle of one, so slices are fewer and wider here, of 256 features (us, an element or a pair per lane
+// and four slices / this: 2048 rows of 27 edges, F = 602, 36 / 25; 20000 of 6, F = 481, 54 / 47, bf16 56 / 37, F = 201 31 / 24; 3000 of 8,
+// F = 333, 19 / 14, bf16 18 / 15; 68536 of 4.5, F = 481, 146 / 111).  Up to 128 features by how many rows there are:
+//  * 65 .. 128: many rows are taken whole (two slices / one: 131 K rows of 13, F = 65, 129 / 95, F = 127 176 / 157), from ODD_WIDE_ROWS on by
+//    16 lanes with eight features each (3000 rows of 0.6 edges, F = 82, 7.0 / 6.2, of 27, F = 127, 9.5 / 9.0; 777 rows of 100, F = 127, 12.2 / 13.4).
+//  * 33 .. 64: 16 lanes with four each.  What rows of an edge or two pay for the share of a row that every group may hold (777 rows of 0.6,
+//    F = 63, an element per lane 5.2, this 5.9; 3000, 5.5 / 6.4) longer ones get back (777 of 27, F = 65, 10.2 / 7.6, of 100, F = 63, 21.6 / 12.0).
+//  * 17 .. 32: 16 lanes with a pair each (32 with an element / eight with four / this: 100 rows of 100, F = 17, 14.0 / 14.8 / 10.1; 2048 of 27,
+//    F = 31, 8.5 / 8.3 / 7.1), beyond ODD_GROUPS_FROM rows, which fill the device with fewer lanes each, eight with four (20000 of 27, F = 31, 20.6 / 15.1 / 15.9).
+//  * 9 .. 16, between ODD_GROUPS_FROM and ODD_GROUPS_TO rows: eight lanes with a pair (16 with an element / this: 60000 of 27, F = 15, 27.9 / 24.5).
+// The others keep an element per lane, or a pair where rows begin on one and hold whole pairs:
+//  * fewer features: four lanes with four each let a tile be twice as many rows that a wavefront walks through alone (100 rows of 100,
+//    F = 15, 9.9 / 23.4; 2048 of 100, F = 5, 14.1 / 23.8; 12000 of 27, F = 5, 8.8 / 11.7; 131072 of 13, F = 15, 41 / 45);
+//  * float rows of 257 to 320 features in pairs, where a second slice of 256 is nearly empty, if they are many (pairs / two slices: F = 258, 8192 rows of
+//    27, 37.9 / 44.3, of 0.6, F = 270, 9.2 / 9.8; 60000 of 13, F = 262, 156 / 189; 2048 of 100, F = 258, 35.8 / 29.7);
+//  * a handful of rows, a row per wavefront, which has no shares to put together (16 rows of 3, F = 31, 4.9 / 5.4, F = 63 4.9 / 5.2; 64 of
+//    3 5.3 / 5.6, 5.1 / 5.5).
+constexpr int32_t ODD_FEW_ROWS = 64, ODD_WIDE_ROWS = 1024, ODD_WHOLE_ROWS = 4096, ODD_GROUPS_FROM = 8192, ODD_GROUPS_TO = 65536, ODD_PAIRS = 320;
 template <typename T>
 static int pick_odd(const int32_t *rp, const int32_t *col, const float *val, int32_t nS, const int32_t *nsd, const int32_t *ncp, const void *Xl,
                     int64_t ldl, int64_t rl, const void *Xr, int64_t ldr, int64_t rr, const int32_t *src_row, int32_t F, int relu, float *Z, int64_t ldz,
                     const float *mask, int64_t ldm, int kid, hipStream_t st, const CompInst &ci)
 {
 #define CSGS_AGG_VG(V, G) launch_agg<T, V, G>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci)
-    if (F > ODD_NARROW) return CSGS_AGG_VG(8, 32);
-    if (F > 64 && (int64_t)nS * ci.n > ODD_WHOLE_ROWS) return CSGS_AGG_VG(4, 32);
+    const int64_t rows = (int64_t)nS * ci.n;
+    if (F > 128) return CSGS_AGG_VG(8, 32);
+    if (F > 64 && rows > ODD_WHOLE_ROWS) return CSGS_AGG_VG(4, 32);
+    if (F > 64 && rows > ODD_WIDE_ROWS) return CSGS_AGG_VG(8, 16);
     if (F > 32) return CSGS_AGG_VG(4, 16);
-    if (F > 16) return CSGS_AGG_VG(4, 8);
-    if (F >= 4) return CSGS_AGG_VG(4, 4);
-    if (F >= 2) return CSGS_AGG_VG(2, 4);
-    return CSGS_AGG_VG(1, 4);
+    if (F > 16) return rows > ODD_GROUPS_FROM ? CSGS_AGG_VG(4, 8) : CSGS_AGG_VG(2, 16);
+    return CSGS_AGG_VG(2, 8);
 #undef CSGS_AGG_VG
 }
 
@@ -153,7 +163,10 @@ static int pick_vec(const int32_t *rp, const int32_t *col, const float *val, int
     };
     if (whole(8)) return pick_group<T, 8>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci);
     if (whole(4)) return pick_group<T, 4>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci);
-    if ((int64_t)nS * ci.n <= ODD_FEW_ROWS) {
+    const int64_t rows = (int64_t)nS * ci.n;
+    const bool narrow = F <= 8 || (F <= 16 && (rows <= ODD_GROUPS_FROM || rows > ODD_GROUPS_TO));
+    const bool pairs = sizeof(T) == 4 && F > 256 && F <= ODD_PAIRS && rows > ODD_WHOLE_ROWS && whole(2);
+    if (narrow || pairs || rows <= ODD_FEW_ROWS) {
         if (whole(2)) return pick_group<T, 2>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci);
         return pick_group<T, 1>(rp, col, val, nS, nsd, ncp, Xl, ldl, rl, Xr, ldr, rr, src_row, F, relu, Z, ldz, mask, ldm, kid, st, ci);
     }
@@ -488,7 +501,7 @@ extern "C" int csgs_gather_rows_n(const csgs_inst_strides *inst, const void *X, 
     // Rows that the wavefront's lanes cover at once go in whole pieces; longer ones that are no whole 16-byte pieces in 16 bytes from any
     // address (us, 131 K rows, 16 bytes from any address / whole pieces: 9 bf16 values 14.1 / 10.3, 5 floats 12.9 / 10.8, 31 floats 16.2 /
     // 15.7, 133 floats 22.7 / 28.1, 333 bf16 values 26.9 / 42.7; 75 bf16 values 16.5 / 20.8, of 30 K rows 5.7 / 5.3).  No pieces of 8: the same
-    // in pieces of 4 is quicker (12 bf16 values 13.5 / 12.0, 2 floats 11.9 / 9.4).
+    // in pieces of 4 is quicker (12 bf16 values 13.5 / 12.0, 2 floats 11.8 / 9.1).
     if (piece == 16) launch_gather<u32x4, true>(X, ld_b, rows, row_b, ids, cap, n_dev, out, ldo_b, st, ci);
     else if (row_b > WAVE * piece) launch_gather<u32x4, false>(X, ld_b, rows, row_b, ids, cap, n_dev, out, ldo_b, st, ci);
     else if (piece == 4) launch_gather<uint32_t, true>(X, ld_b, rows, row_b, ids, cap, n_dev, out, ldo_b, st, ci);

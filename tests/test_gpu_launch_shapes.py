@@ -443,3 +443,32 @@ def test_gathered_row_pieces(dev, F, bf16):
         np.testing.assert_array_equal(out[:n, late:late + F].cpu().numpy(), want)
         out[:n, late:late + F] = 7
         assert bool((out == 7).all()), "wrote beside the rows"
+
+
+# Odd widths on either side of the row counts at which the lanes per row change (64, 1024, 4096, 8192 and 65536 rows), tables that begin on a
+# pair (float rows of 258 to 320 features are then read in pairs) and one element late; rows without edges and long ones among them
+@pytest.mark.parametrize("n,F", [(64, 15), (65, 15), (8192, 15), (8193, 9), (8193, 15), (65536, 11), (65537, 11), (8192, 17), (8193, 17), (8193, 31),
+                                 (1024, 65), (1025, 65), (1025, 127), (4096, 127), (4097, 127), (4096, 258), (4097, 257), (4097, 258), (4097, 320), (4097, 322)])
+def test_odd_widths_by_rows(dev, n, F):
+    from paper_2101_07706_amd import csgs
+    rng = np.random.default_rng(n + F)
+    n_cols = 700
+    lens = rng.poisson(1.5, n)
+    lens[rng.integers(0, n, 4)] = (0, 70, 140, 300)
+    rowptr, col, val = _csr(rng, lens, n_cols)
+    X = rng.standard_normal((n_cols, F)).astype(np.float32)
+    t = lambda a: torch.from_numpy(a).to(dev)
+    adj, cols = [t(a) for a in (rowptr, col, val)], torch.tensor([n_cols], dtype=torch.int32, device=dev)
+    for bf16 in (False, True):
+        Xh = synth.to_bf16_bits(X) if bf16 else X
+        want = oracle.aggregate(rowptr, col, val, Xh, relu_on_input=False)
+        for late in (0, 1):
+            print(f"[odd widths] {n} rows F={F} bf16={bf16} late={late}", flush=True)
+            bits = Xh.view(np.int16) if bf16 else Xh
+            table = torch.full((n_cols, F + F % 2 + late), -1 if bf16 else float("nan"), dtype=torch.int16 if bf16 else torch.float32, device=dev)
+            table[:, late:late + F] = t(bits)
+            Z = torch.full((n, F + F % 2 + late), float("nan"), dtype=torch.float32, device=dev)
+            csgs.csgs_aggregate(*adj, cols, table[:, late:late + F], None, None, False, Z[:, late:late + F])
+            torch.cuda.synchronize()
+            chain.assert_close(Z[:, late:late + F].cpu().numpy(), want, chain.RTOL, chain.ATOL, "Z")
+            assert bool(torch.isnan(Z[:, :late]).all()) and bool(torch.isnan(Z[:, late + F:]).all()), "wrote beside a row"
