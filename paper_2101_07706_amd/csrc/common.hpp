@@ -11,6 +11,8 @@ namespace csgs {
 
 constexpr int WAVE = 64;
 
+typedef double doublex4 __attribute__((ext_vector_type(4)));   // what a lane holds of a 16 x 16 tile of sums
+
 #define CSGS_LAUNCH_CHECK()                                   \
     do {                                                      \
         if (hipGetLastError() != hipSuccess) return CSGS_ELAUNCH; \

@@ -17,10 +17,10 @@
 // Blocks of one compute unit are at different points of their life, so one block's gathers overlap another's MFMAs.
 #include "common.hpp"
 #include "aggregate_tile.hpp"
-#include "gemm_tile.hpp"
 
 namespace csgs {
 
+constexpr int BK = 32;           // k per chunk
 constexpr int FUSED_ROWS = 32;   // rows of Z per block: one 8-row tile per wavefront
 constexpr int FUSED_POOL = 64;   // edges a wavefront stages at a time (8 rows hold a few dozen)
 

@@ -29,11 +29,10 @@
 //
 // Block ids are remapped so that consecutive tiles (same rows of Z, neighbouring column tiles)
 // land on the same XCD and share its L2.
-#include <algorithm>
 #include <type_traits>
 #include "common.hpp"
 
-#include "gemm_tile.hpp"
+#include "gemm_rules.hpp"
 
 namespace csgs {
 
@@ -348,38 +347,6 @@ __global__ __launch_bounds__(256) void gemm_reduce_parts(const double *__restric
     C[(i / N) * ldc + (i % N)] = (float)s;
 }
 
-// What one MFMA of a tile shape costs beside one of the largest shape (conversions per MFMA, tiles per
-// wavefront slot), measured on 4096 .. 131072 rows
-struct Shape {
-    int rt, nt;
-    double cost;
-};
-static const Shape kShapes[] = {{2, 4, 1.0}, {2, 3, 1.01}, {2, 2, 1.05}, {1, 4, 1.06}, {1, 3, 1.1}, {1, 2, 1.17}, {2, 1, 1.22}, {1, 1, 1.33}};
-constexpr int CUS = 256;   // compute units; a block has a wavefront for each SIMD
-
-// The shape whose slowest compute unit is done first: blocks per unit, rounded up, times what a block takes.  The larger shapes waste fewer
-// conversions, the smaller ones waste fewer columns and leave fewer units idle (4500 x 512 x 100, us: 2x4 33.1, 2x2 19.7, 2x1 14.5, 1x1
-// 12.9; 8192 x 256 x 256: 19.8, 20.4, 22.8, 23.1).  Of the two shapes of two instructions a step 1x2 is the quicker where a lane's columns of B
-// come in one load (1x2 against 2x1 at 20000 x 481 x 100 46 and 49, 2048 x 602 x 256 14.8 and 17, 4500 x 300 x 512 31 and 33.5), 2x1 for
-// dZ, whose B is read along k (5367 x 48 x 460 19.9 and 19.0).
-static Shape pick_shape(int64_t M, int64_t N, int64_t n_inst, bool b_kmajor)
-{
-    Shape best = kShapes[7];
-    double least = 1e300;
-    for (const Shape &s : kShapes) {
-        if (s.nt > N) continue;   // a lane's NT columns exist
-        const int64_t tiles = ((M + 16 * s.rt - 1) / (16 * s.rt)) * ((N + 16 * s.nt - 1) / (16 * s.nt));
-        const int64_t per_cu = ((tiles + 3) / 4 * n_inst + CUS - 1) / CUS;
-        const double cost = b_kmajor && s.rt == 1 && s.nt == 2 ? 1.25 : s.cost;
-        const double c = (double)per_cu * s.rt * s.nt * cost;
-        if (c < least) { least = c; best = s; }
-    }
-    return best;
-}
-
-// A row of a matrix this long could put a lane's offset beyond 32 bits
-static bool far_apart(int64_t lda, int64_t ldb) { return lda >= (1 << 24) || ldb >= (1 << 24); }
-
 template <int MODE>
 static void launch_product(const float *A, int64_t lda, const float *B, int64_t ldb, float *C, int64_t ldc, int M, int N, int K,
                            const int32_t *M_dev, hipStream_t st, const CompInst &ci)
@@ -413,59 +380,6 @@ static void launch_product(const float *A, int64_t lda, const float *B, int64_t 
     CSGS_SHAPE(2, 4) CSGS_SHAPE(2, 3) CSGS_SHAPE(2, 2) CSGS_SHAPE(2, 1) CSGS_SHAPE(1, 4) CSGS_SHAPE(1, 3) CSGS_SHAPE(1, 2) CSGS_SHAPE(1, 1)
 #undef CSGS_SHAPE
 #undef CSGS_PRODUCT
-}
-
-// Parts of the reduction dimension for dW = Z^T G with `rows` rows that the caller's scratch has room for
-static int dw_max_parts(int rows, int64_t K, int64_t N)
-{
-    const int64_t tiles = ((K + 127) / 128) * ((N + 31) / 32);
-    int64_t want = (512 + tiles - 1) / tiles;
-    const int64_t chunks = ((int64_t)rows + 31) / 32;
-    if (want > chunks) want = chunks;
-    if (want < 1) want = 1;
-    int64_t ks = ((rows + want - 1) / want + 31) / 32 * 32;
-    if (ks < 32) ks = 32;
-    const int64_t parts = (rows + ks - 1) / ks;
-    return (int)(parts < 1 ? 1 : parts);
-}
-
-// Shape and parts for dW, a block per tile and part: the fewest microseconds by
-//  * 29 ns per MFMA for the blocks of the fullest compute unit (28 tiles in 9 parts are 36 blocks for the 32 units of seven XCDs and twice the
-//    time of 8 parts), times what the shape costs beside it;
-//  * or 0.5 us per chunk of a wavefront where its unit holds too few blocks to multiply meanwhile (the chunk's loads take that long: one
-//    block of 1x1 tiles per unit, 8192 rows, 256 x 256, 43 us);
-//  * or what the XCDs fetch at 5.6 TB/s: each holds consecutive tiles and reads their columns of Z and G once (65536 rows, 100 x 256, 1x4 in 8
-//    parts: seven XCDs read all of G, 97 us; 2x2 in 16 72);
-//  * 3.5 us for the kernel that adds several parts and what these take through memory (16 bytes per output and part at about 4 TB/s).
-// Measured against that, us: 8192 rows, 256 x 256: 2x2 in 4 / 8 parts 24.4 / 23.9 (24 / 25 expected), 1x2 in 4 24.8 (25), 2x3 in 16 28.6 (28),
-// 256 x 47: 1x2 in 8 10.6 (11.2); 4096 rows, 512 x 512: one part of 2x2 37.6 (36), four of 2x4 41 (41), 512 x 100: 1x2 in 2 14.9 (15.6).
-static void dw_split(int rows, int64_t K, int64_t N, Shape *shape, int *parts)
-{
-    static const Shape shapes[] = {{2, 2, 1.1}, {2, 4, 1.03}, {2, 3, 1.06}, {1, 4, 1.1}, {1, 2, 1.17}, {2, 1, 1.3}, {1, 1, 1.5}};
-    constexpr double MFMA_US = 0.029, CHUNK_US = 0.5, FETCH_BYTES_PER_US = 5.6e6, REDUCE_US = 3.5;
-    constexpr int64_t RESIDENT = 3;   // blocks that a compute unit holds at once
-    const int64_t chunks = ((int64_t)rows + 31) / 32;
-    const int max_parts = dw_max_parts(rows, K, N);
-    double least = 1e300;
-    *shape = shapes[6];
-    *parts = 1;
-    for (const Shape &s : shapes) {
-        if (s.nt > N || s.rt > K) continue;
-        const int64_t tn = (N + 16 * s.nt - 1) / (16 * s.nt), tiles = ((K + 16 * s.rt - 1) / (16 * s.rt)) * tn;
-        const int64_t xcd_tiles = (tiles + 7) / 8;   // every part deals its tiles to the XCDs anew
-        const int64_t cols_z = (xcd_tiles + tn - 1) / tn * 16 * s.rt, cols_g = (xcd_tiles < tn ? xcd_tiles : tn) * 16 * s.nt;
-        const int64_t cols = (tiles + xcd_tiles - 1) / xcd_tiles * ((cols_z < K ? cols_z : K) + (cols_g < N ? cols_g : N));
-        const double fetch = (double)cols * rows * 4 / FETCH_BYTES_PER_US;
-        for (const int64_t fill : {(int64_t)0, (int64_t)CUS, (int64_t)2 * CUS, (int64_t)4 * CUS}) {
-            int64_t p = fill / 8 / xcd_tiles;
-            p = p < 1 ? 1 : (p > max_parts ? max_parts : p);
-            const int64_t per_cu = (xcd_tiles * p + CUS / 8 - 1) / (CUS / 8), mine = (chunks + 4 * p - 1) / (4 * p);
-            const double multiply = (double)(per_cu * mine) * (8 * MFMA_US) * s.rt * s.nt * s.cost;
-            const double load = (double)((per_cu + RESIDENT - 1) / RESIDENT * mine) * CHUNK_US;
-            const double c = std::max(std::max(multiply, load), fetch) + (p > 1 ? REDUCE_US + (double)(p * K * N) * (16 / 4e6) : 0.0);
-            if (c < least) { least = c; *shape = s; *parts = (int)p; }
-        }
-    }
 }
 
 }  // namespace csgs
