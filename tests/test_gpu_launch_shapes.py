@@ -251,8 +251,8 @@ def test_aggregate_gradient_columns(dev, bound, n_cols):
     assert bool(torch.isnan(dH[n_cols:]).all()), "wrote past the last column"
 
 
-# The weight gradient's two ways of loading Z: whole aligned pieces of four columns, or not (odd widths, strides, addresses);
-# rows and columns around its tiles (128 x 32) and chunks (32 rows), fewer rows on the device than the bound
+# The weight gradient with widths that are whole pieces of four columns and odd ones, odd strides and addresses; rows and columns around
+# multiples of 128 and 32, fewer rows on the device than the bound
 @pytest.mark.parametrize("M,m,K,N,pad", [(1, 1, 4, 1, 0), (31, 31, 124, 5, 0), (33, 20, 128, 32, 0), (1000, 970, 132, 33, 0), (4096, 4096, 300, 100, 0),
                                          (64, 64, 260, 64, 4), (500, 499, 128, 40, 1), (500, 500, 130, 31, 2), (40, 0, 8, 8, 0)])
 def test_weight_gradient_loads(dev, M, m, K, N, pad):
@@ -272,8 +272,9 @@ def test_weight_gradient_loads(dev, M, m, K, N, pad):
     chain.assert_close(dW.cpu().numpy(), want, chain.RTOL, chain.ATOL, "dW")
 
 
-# The products' wavefront tiles: 16 or 32 rows by 16, 32, 48 or 64 columns, by what fills the device; K in chunks of 32 and what is left of
-# them (in steps of four, room for 8 or 32); rows whose floats start anywhere; rows 2^24 floats apart (offsets of 64 bits)
+# The products around a wavefront's tiles of 16 rows and columns: K in chunks of 32 and what is left of them (in steps of four, room for 8 or 32), rows
+# whose floats start anywhere.  (Most of these sizes are taken in tiles of 16 x 16: each larger one in test_product_shapes.  The last size takes the
+# kernel for rows 2^24 floats apart and more; offsets that need its 64 bits in test_products_of_distant_rows.)
 @pytest.mark.parametrize("M,K,N,pad", [(1, 1, 1, 0), (15, 31, 2, 1), (17, 32, 3, 0), (16, 33, 16, 3), (33, 36, 17, 0), (1023, 40, 7, 2), (1024, 64, 256, 0),
                                        (2048, 41, 250, 1), (4095, 63, 100, 0), (4096, 96, 512, 0), (4097, 34, 511, 1), (20001, 9, 201, 0), (65530, 8, 47, 1),
                                        (65537, 4, 130, 2), (3, 37, 5, 1 << 24)])
@@ -301,10 +302,76 @@ def test_product_tiles(dev, M, K, N, pad):
         assert bool(torch.isnan(got[r:]).all()) and bool(torch.isnan(got[:, c:]).all()), f"{what}: wrote outside"
 
 
+# Every tile of the two products that go over the rows with every length of their last chunk (test_product_rules.py asks the rule whether these
+# sizes take them): outputs that are no whole tiles in either direction, columns that are no multiple of a lane's
+PRODUCT_SHAPES = [  # product, 16-row tiles, columns a lane, room for the last K % 32 k; M, K, N
+    ("H", 2, 4, 0, 14088, 96, 97), ("H", 2, 4, 8, 14094, 66, 97), ("H", 2, 4, 32, 14089, 41, 103),
+    ("H", 2, 3, 0, 13124, 96, 65), ("H", 2, 3, 8, 13191, 66, 65), ("H", 2, 3, 32, 13333, 42, 65),
+    ("H", 2, 2, 0, 12290, 96, 49), ("H", 2, 2, 8, 12452, 65, 49), ("H", 2, 2, 32, 12692, 41, 49),
+    ("H", 1, 4, 0, 5448, 96, 173), ("H", 1, 4, 8, 5446, 65, 163), ("H", 1, 4, 32, 5442, 42, 167),
+    ("H", 1, 3, 0, 10939, 96, 35), ("H", 1, 3, 8, 10985, 65, 35), ("H", 1, 3, 32, 11022, 41, 35),
+    ("H", 1, 2, 0, 8197, 96, 17), ("H", 1, 2, 8, 8223, 65, 17), ("H", 1, 2, 32, 8327, 41, 17),
+    ("H", 2, 1, 0, 16397, 96, 5), ("H", 2, 1, 8, 16392, 65, 5), ("H", 2, 1, 32, 16625, 41, 5),
+    ("H", 1, 1, 0, 17, 96, 5), ("H", 1, 1, 8, 17, 65, 5), ("H", 1, 1, 32, 17, 41, 5),
+    ("dZ", 2, 4, 0, 14088, 97, 96), ("dZ", 2, 4, 8, 14094, 97, 66), ("dZ", 2, 4, 32, 14089, 103, 41),
+    ("dZ", 2, 3, 0, 13124, 65, 96), ("dZ", 2, 3, 8, 13191, 65, 66), ("dZ", 2, 3, 32, 13333, 65, 42),
+    ("dZ", 2, 2, 0, 12290, 49, 96), ("dZ", 2, 2, 8, 12452, 49, 65), ("dZ", 2, 2, 32, 12692, 49, 41),
+    ("dZ", 1, 4, 0, 5448, 173, 96), ("dZ", 1, 4, 8, 5446, 163, 65), ("dZ", 1, 4, 32, 5442, 167, 42),
+    ("dZ", 1, 3, 0, 10939, 35, 96), ("dZ", 1, 3, 8, 10985, 35, 65), ("dZ", 1, 3, 32, 11022, 35, 41),
+    ("dZ", 1, 2, 0, 5453, 83, 96), ("dZ", 1, 2, 8, 841, 595, 65), ("dZ", 1, 2, 32, 1163, 439, 41),
+    ("dZ", 2, 1, 0, 16397, 5, 96), ("dZ", 2, 1, 8, 16392, 5, 65), ("dZ", 2, 1, 32, 16625, 5, 41),
+    ("dZ", 1, 1, 0, 17, 5, 96), ("dZ", 1, 1, 8, 17, 5, 65), ("dZ", 1, 1, 32, 17, 5, 41)]
+
+
+@pytest.mark.parametrize("what,rt,nt,tail,M,K,N", PRODUCT_SHAPES)
+def test_product_shapes(dev, what, rt, nt, tail, M, K, N):
+    from paper_2101_07706_amd import csgs
+    rng = np.random.default_rng(M + K + N)
+    print(f"[products] {what} {M} x {K} x {N}: {16 * rt} x {16 * nt}, room for {tail}", flush=True)
+    a, b, width = (M, K), (K, N), N
+    if what == "dZ":
+        a, width = (M, N), K
+    A, W = rng.standard_normal(a).astype(np.float32), rng.standard_normal(b).astype(np.float32)
+    out = torch.full((M + 1, width + 3), float("nan"), dtype=torch.float32, device=dev)
+    call = csgs.csgs_layer_gemm if what == "H" else csgs.csgs_layer_gemm_grad_z
+    call(torch.from_numpy(A).to(dev), torch.from_numpy(W).to(dev), out[:M, :width])
+    torch.cuda.synchronize()
+    want = oracle.layer_gemm(A, W) if what == "H" else oracle.layer_gemm_grad_z(A, W)
+    chain.assert_close(out[:M, :width].cpu().numpy(), want, chain.RTOL, chain.ATOL, what)
+    assert bool(torch.isnan(out[M:]).all()) and bool(torch.isnan(out[:, width:]).all()), "wrote outside"
+
+
+# Rows so far apart that a lane's offset from its tile needs more than 32 bits, in each operand of the three products
+def test_products_of_distant_rows(dev):
+    from paper_2101_07706_amd import csgs
+    M, K, N, ld = 40, 34, 17, 5 << 24
+    assert 15 * ld * 4 > 1 << 32    # the last of a tile's rows from its first
+    rng = np.random.default_rng(11)
+    Z, W, G = (rng.standard_normal(s).astype(np.float32) for s in ((M, K), (K, N), (M, N)))
+    print(f"[products] rows {ld} floats apart", flush=True)
+    buf = torch.full((M, ld), float("nan"), dtype=torch.float32, device=dev)
+    Zd, Wd, Gd = buf[:, :K], buf[:K, 64:64 + N], buf[:, 128:128 + N]
+    for d, a in ((Zd, Z), (Wd, W), (Gd, G)):
+        d.copy_(torch.from_numpy(a))
+    H, dZ, dW = (torch.empty(s, dtype=torch.float32, device=dev) for s in ((M, N), (M, K), (K, N)))
+    csgs.csgs_layer_gemm(Zd, Wd, H)
+    csgs.csgs_layer_gemm_grad_z(Gd, Wd, dZ)
+    scratch = torch.full((csgs.csgs_layer_gemm_grad_w_scratch_bytes(M, K, N) // 8,), -1, dtype=torch.int64, device=dev)
+    csgs.csgs_layer_gemm_grad_w(Zd, Gd, dW, scratch)
+    torch.cuda.synchronize()
+    for got, want, what in ((H, oracle.layer_gemm(Z, W), "H"), (dZ, oracle.layer_gemm_grad_z(G, W), "dZ"), (dW, oracle.layer_gemm_grad_w(Z, G), "dW")):
+        chain.assert_close(got.cpu().numpy(), want, chain.RTOL, chain.ATOL, what)
+    del buf, Zd, Wd, Gd
+    torch.cuda.empty_cache()
+
+
 # The weight gradient's tiles and parts: each shape of its rule (2x2, 2x4, 2x3, 1x4, 1x2, 2x1, 1x1), one part and several, columns beside their
 # edges, rows that are no multiple of a part's chunks
-@pytest.mark.parametrize("M,K,N", [(65, 64, 2), (7135, 47, 1), (63, 193, 322), (2400, 17, 66), (2433, 130, 306), (10847, 175, 1), (18817, 175, 17),
-                                   (12287, 161, 33), (12033, 66, 318)])
+GRAD_W_SIZES = [(65, 64, 2), (7135, 47, 1), (63, 193, 322), (2400, 17, 66), (2433, 130, 306), (10847, 175, 1), (18817, 175, 17), (12287, 161, 33),
+                (12033, 66, 318)]
+
+
+@pytest.mark.parametrize("M,K,N", GRAD_W_SIZES)
 def test_weight_gradient_tiles(dev, M, K, N):
     from paper_2101_07706_amd import csgs
     rng = np.random.default_rng(3 * M + K + N)
