@@ -49,7 +49,7 @@ __global__ __launch_bounds__(AGG_BLOCK) void aggregate_k(const int32_t *__restri
     const int tid = (int)threadIdx.x;
     const int wave = tid >> 6;
     // V is at most F, and where F is no multiple of it the last V features of a row are taken together: those among them that
-    // another lane (or slice) has too are written twice, the same.  Lanes past the row repeat them and store nothing
+    // another lane (or slice) has too are written twice, the same.  Lanes past the row read the slice's start and store nothing
     const int32_t slice0 = slice * G * V < F - V ? slice * G * V : F - V;
     const int32_t lane_f = slice0 + (tid % G) * V;
     const int32_t f = lane_f < F - V ? lane_f : F - V;

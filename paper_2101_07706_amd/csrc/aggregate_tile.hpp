@@ -89,17 +89,16 @@ __device__ inline Vec<8> load_row<uint16_t, 8>(const uint16_t *p)
 
 // Rows with more kept edges than LONG_ROW are taken by the whole block, after its tiles.  With 32 or 64 lanes per row, where a
 // wavefront walks through a long row nearly alone, so are rows of more than long_row<G>() (us, 256 everywhere / this: F = 100
-// bf16, 7283 rows, 32 lanes a row, 19 / 15; eight of those 32 / 25; F = 602, 2048 rows of 26 edges, 64 lanes, 40 / 35; layers in
-// one kernel 117 + 194 + 80 / 104 + 182 + 71; half of that again is level) -- in tiles of more than LONG_TILE rows only if they
-// hold more than LONG_SKEW times what the tile's rows that are not as long do on average: where all rows are long, each
-// wavefront has enough to walk through, and a block that takes them one after the other only adds its barriers (us, any
-// such row / this: rows of 65 edges, one-kernel layer, F = 128, 2048 rows 107 / 64; F = 100 bf16, 65536 rows 417 / 270; F = 504
-// bf16, 65536 rows 727 / 641; 130 edges, F = 100 bf16, 65536 rows 477 / 347).  Tiles of LONG_TILE rows are made only where the
-// launch would not fill the compute units otherwise, and walking them leaves most of those idle; tiles of four rows do fill
-// them (us, any such row / this: 10000 rows of 66, F = 47, 55 / 30; 2000 of 66, F = 481, 68 / 52).  Nor does the mean decide in
-// a block of which no more than 5/6 are rows of the call: there the wavefronts without rows help (one-kernel layer, F = 128,
-// compared / this: 8 rows of 120 edges 85 / 26, 20 rows 90 / 55; a full block of such rows is level either way).
-// (The figures of odd F are from when such rows had an element or a pair per lane, 64 lanes a row.)
+// bf16, 7283 rows, 32 lanes a row, 19 / 15; eight of those 32 / 25; layers in one kernel 117 + 194 + 80 / 104 + 182 + 71; half of
+// that again is level) -- in tiles of more than LONG_TILE rows only if they hold more than LONG_SKEW times what the tile's rows that
+// are not as long do on average: where all rows are long, each wavefront has enough to walk through, and a block that takes them one
+// after the other only adds its barriers (us, any such row / this: rows of 65 edges, one-kernel layer, F = 128, 2048 rows 107 / 64; F =
+// 100 bf16, 65536 rows 417 / 270; aggregation, F = 504 bf16, 65536 rows of 66 706 / 632; F = 100 bf16, 65536 of 130 366 / 297; F = 481
+// bf16, 10000 of 130 236 / 164).  Tiles of LONG_TILE rows are made only where the launch would not fill the compute units otherwise,
+// and walking them leaves most of those idle; tiles of four rows do fill them (us, any such row / this: F = 504 bf16, 10000 rows of 66
+// 143 / 107, of 130 215 / 197; F = 252, 10000 of 66 85 / 80).  Dearer for it: 23611 rows of 149, F = 456 bf16, 468 / 484; F = 252, 65536 of 66,
+// 626 / 646.  Nor does the mean decide in a block of which no more than 5/6 are rows of the call: there the wavefronts without rows help
+// (one-kernel layer, F = 128, compared / this: 8 rows of 120 edges 85 / 26, 20 rows 90 / 55; a full block of such rows is level either way).
 constexpr int LONG_ROW = 256, LONG_SKEW = 2, LONG_TILE = 2;
 template <int G>
 constexpr int long_row() { return G >= 64 ? 64 : (G >= 32 ? 128 : LONG_ROW); }
@@ -129,9 +128,9 @@ template <typename T, int V, int G, bool RELU>
 __device__ inline void accumulate_staged(double (&acc)[V], const T *src, float w, int gbase, int32_t n_max, bool active, int32_t slice0, int32_t f)
 {
     // Eight pieces on their way per lane, and the weights fetched from their lanes when used: with sixteen of them for narrow
-    // vectors the kernel's registers held it to four blocks per compute unit instead of six, in launches without a long row
-    // too (us, sixteen / eight, F = 481, 68536 rows of 4.5 edges 149 / 123; F = 333 bf16, 95553 rows of 0.6 104 / 82; rows of
-    // 600 edges among 2000 of 5, F = 250, 19 / 21).
+    // vectors the kernel's registers hold it to four blocks per compute unit instead of six, in launches without a long row
+    // too (us, sixteen / eight, float pairs, F = 258: 68536 rows of 4.5 edges 92 / 86, 95553 of 0.6 56 / 49; rows of 600 edges among
+    // 2000 of 5, F = 31, 10.3 / 9.6).
     constexpr int UNR = G < 8 ? G : 8;
     const uint64_t p = src ? (uint64_t)(uintptr_t)(src + slice0) : (uint64_t)(uintptr_t)g_zero_row;
     const uint32_t lane_off = active ? (uint32_t)((f - slice0) * (int)sizeof(T)) : 0u;

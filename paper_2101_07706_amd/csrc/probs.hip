@@ -580,9 +580,12 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, PACK ? 8 : 1) void cand_partials(u
 
 // Two kinds.  With PACKED a block takes four tiles that cand_partials has packed: where there are many tiles (several instances) the kernel is bound by
 // vector instructions, and what they cost for the sums before a block, for the totals and for every 64-id word is then spent
-// once for four tiles and on the candidates alone (us per launch of 8 x 2392 tiles with 67 candidates each, cand_partials and this kernel,
-// words / packed: 51 + 45 / 53 + 22).  With few tiles the packing only makes cand_partials' blocks last longer (2392 tiles 10.5 + 10.8 / 11.3 +
-// 8.2 with a block per tile, with 450 candidates each 29 + 13 / 31 + 10.3, 701 tiles 6.5 + 6.2 / 8 + 5), so there a block takes one tile, word by word.
+// once for four tiles and on the candidates alone, while cand_partials takes longer (us per launch, cand_partials + this kernel, words / packed: 8 x 2392
+// tiles with 65 candidates each 32 + 44 / 37 + 15, with 361 each 36 + 86 / 59 + 48; 1 x 9568 with 65 19 + 26 / 22 + 10, with 258 21 + 37 / 29 + 20; 8 x 1024
+// with 501 19 + 42 / 26 + 33).  Below the line that depends on how full the tiles are, which the host does not know: few candidates are the quicker
+// packed (1 x 2392 tiles with 65 each 8.1 + 11.2 / 9.7 + 5.4, 1 x 4784 12.9 + 15.5 / 15.2 + 7.2), many by words (1 x 2392 with 361 8.1 + 13.8 / 11.8 + 14.0,
+// 1 x 1100 6.8 + 10.1 / 9.1 + 12.8).  From the line on no call was found that words serve better.
+// (cand_partials at eight wavefronts per SIMD keeps two registers of the packing kind in scratch memory: its figures hold that.)
 constexpr int64_t CAND_PACKED_FROM = 8192;   // tiles over all instances
 template <bool PACKED>
 __global__ __launch_bounds__(256) void cand_emit(uint64_t *__restrict__ wtable, uint8_t *__restrict__ tileflag,

@@ -789,11 +789,11 @@ def test_aggregate_many_rows(dev, mean_len, device_count):
 @pytest.mark.parametrize("M,K,N", [(1, 1, 1), (33, 17, 5), (256, 64, 64), (1024, 128, 256), (2048, 602, 256),
                                    (2048, 256, 41), (4096, 300, 512), (4096, 512, 100), (8192, 100, 256),
                                    (8192, 256, 256), (8192, 256, 47), (100, 1000, 70),
-                                   # one to four k beyond whole chunks of 32: folded into the last chunk
+                                   # a few k beyond whole chunks of 32: one or two steps of four, before the chunks
                                    (300, 36, 70), (513, 68, 47), (1000, 33, 64), (257, 66, 33), (129, 99, 20),
                                    (4096, 132, 256), (640, 35, 300), (77, 34, 16), (128, 37, 64),
-                                   # 512 and more blocks of 128 x 64: the block shape of a launch for 8 mini-batches of the
-                                   # largest configuration (regular shape, with and without folded tail, ragged, narrow output)
+                                   # the sizes of a launch for 8 mini-batches of the largest configuration: whole tiles, with and
+                                   # without k beyond whole chunks, ragged rows, a narrow output
                                    (16384, 256, 256), (16384, 100, 256), (16500, 100, 256), (16421, 250, 256),
                                    (65536, 256, 47), (65541, 256, 47), (32768, 36, 128)])
 def test_layer_gemm_shapes(dev, M, K, N):
