@@ -20,6 +20,9 @@ constexpr int CUS = 256;   // compute units; a block has a wavefront for each SI
 // 12.9; 8192 x 256 x 256: 19.8, 20.4, 22.8, 23.1).  Of the two shapes of two instructions a step 1x2 is the quicker where a lane's columns of B
 // come in one load (1x2 against 2x1 at 20000 x 481 x 100 46 and 49, 2048 x 602 x 256 14.8 and 17, 4500 x 300 x 512 31 and 33.5), 2x1 for
 // dZ, whose B is read along k (5367 x 48 x 460 19.9 and 19.0).
+// M is the row bound.  Of a count on the device that lies far below it nothing is known here, and the tiles are then larger than they had best be: 1024
+// rows in 8 instances, 100 x 256, 11.9 us with all rows, 10.8 with half of them (blocks of 64 x 64 that staged in LDS 13.2 and 8.9); 8192 rows of
+// which 409 are there, 256 x 256, 19.3 (16.2).  Shapes for half the rows would cost the calls that have them all 5 %.
 inline Shape pick_shape(int64_t M, int64_t N, int64_t n_inst, bool b_kmajor)
 {
     Shape best = kShapes[7];
