@@ -54,9 +54,8 @@ struct RowOffsets {
     int64_t *eoff;       // [nS + 1] exclusive prefix of the degrees of the rows
     int64_t *rowstart;   // [nS + 1] rowptr[S[a]]
     int64_t *meta;       // [META_WORDS] resolved on the device: row count, edge count, true edge count
-    int2 *chunk_note;    // [chunk_cap] (first row, rows) of every edge chunk, left by the weight scan for the adjacency passes
     int2 *bound_note;    // [chunk_cap + 2] for the edge position t * EDGE_TILE: (first row of a chunk that starts there, first row
-                         // whose offset is at or beyond it), left by the row pass for the weight scan
+                         // whose offset is at or beyond it), left by the row pass for the edge passes
 };
 
 struct Workspace {
@@ -173,7 +172,6 @@ __host__ inline Workspace carve(void *base, int64_t n_nodes, int64_t nS_max, int
         w.rows[b].eoff = (int64_t *)take((size_t)(nS_max + 1) * 8);
         w.rows[b].rowstart = (int64_t *)take((size_t)(nS_max + 1) * 8);
         w.rows[b].meta = (int64_t *)take(META_WORDS * 8);
-        w.rows[b].chunk_note = (int2 *)take((size_t)w.chunk_cap * sizeof(int2));
         w.rows[b].bound_note = (int2 *)take((size_t)(w.chunk_cap + 2) * sizeof(int2));
     }
     w.pdbl = (double *)take((size_t)B_max * 8);
@@ -397,139 +395,108 @@ __device__ inline void wave_lower_bounds(const T *__restrict__ a, I n, const T (
     for (int i = 0; i < K; ++i) out[i] = lo[i];
 }
 
-template <typename T, typename I>
-__device__ inline I wave_lower_bound(const T *__restrict__ a, I n, T key)
-{
-    const T k[1] = {key};
-    I r[1];
-    wave_lower_bounds<1>(a, n, k, r);
-    return r[0];
-}
-
 // ---------------------------------------------------------------- flat edge chunks
 // The edges of the rows of S, concatenated in row order, form one sequence of E edges; position
 // e belongs to the row a with eoff[a] <= e < eoff[a+1] and sits at rowstart[a] + (e - eoff[a])
-// in the CSR arrays.  A block works on chunks of EDGE_TILE consecutive positions, so the work
-// per block does not depend on the degree distribution.  The rows that overlap a chunk are
-// staged in LDS once per chunk.
-constexpr int SLICE_MAX = EDGE_TILE + 2;
-
-struct RowSlice {
-    int32_t off[SLICE_MAX];     // eoff[a_first + r] - c0 (first entry may be negative)
-    int64_t start[SLICE_MAX];   // rowstart[a_first + r]
-    int32_t a_first;            // first staged row
-    int32_t R;                  // staged rows; rows [a_first, a_first + R) overlap or start in the chunk
-    bool in_lds;                // false: too many (empty) rows for LDS, read eoff / rowstart directly
+// in the CSR arrays.  A block works on chunks of consecutive positions, so the work per block does
+// not depend on the degree distribution.
+//
+// Which row a position belongs to: the rows that overlap a chunk set the bit of the position where they start (a row
+// that began before the chunk: position 0) and leave there what must be added to a position to get its CSR address.  A position's row is
+// the one of the last bit at or before it: the 64 positions of a word are a wavefront's lanes, so that is a mask and a count of leading
+// zeros, and the last bit before a word comes from one scan over the words.  Empty rows set no bit.  (us, a binary search per edge over
+// the rows staged in LDS / this: weight scan of 2.3 K edges 8.8 / 5.8, of 52 K 11 / 8.3, of eight times 380 K 52 / 47; marking pass of the adjacency
+// 28.7 / 26.0 for the eight, 65 / 59 for 6.7 M; its one-pass form 11.8 / 7.9 for 2.3 K and 10.3 / 8.0 for 52 K.)
+template <int TILE>
+struct EdgeMap {
+    static constexpr int WORDS = TILE / WAVE;
+    static_assert(WORDS <= WAVE, "a lane per word");
+    int64_t delta[TILE];          // at a row's first position: CSR address minus position
+    unsigned long long starts[WORDS];
 };
 
-// Second half of staging a chunk: rows [a_first, a_first + R) into LDS.  Called by all threads.
-__device__ inline void stage_rows(RowSlice &s, const int64_t *__restrict__ eoff, const int64_t *__restrict__ rowstart,
-                                  int32_t nS, int64_t c0, int64_t a_first, int64_t R)
+// What the row pass left for the chunk boundaries (see row_prefix_tile): the chunk of edge positions [t0 * EDGE_TILE, t1 * EDGE_TILE)
+// is covered by the rows [first, end).
+struct ChunkRows {
+    int32_t first, end;
+};
+__device__ inline ChunkRows chunk_rows(const int2 *__restrict__ bound, int64_t t0, int64_t t1)
 {
-    // A prefix broken by a failed wait, or a stale note (the caller skipped the scan that writes it),
-    // must not lead outside eoff / rowstart: rows [a_first, a_first + R) stay within [0, nS].
-    if (a_first < 0) a_first = 0;
-    if (a_first > nS) a_first = nS;
-    if (R < 0) R = 0;
-    if (R > (int64_t)nS + 1 - a_first) R = (int64_t)nS + 1 - a_first;
-    if (threadIdx.x == 0) {
-        s.a_first = (int32_t)a_first;
-        s.R = (int32_t)R;
-        s.in_lds = R <= SLICE_MAX;
-    }
-    if (R <= SLICE_MAX) {
-        for (int64_t r = threadIdx.x; r < R; r += blockDim.x) {
-            s.off[r] = (int32_t)(eoff[a_first + r] - c0);
-            s.start[r] = (a_first + r < nS) ? rowstart[a_first + r] : 0;
+    const ChunkRows r{bound[t0].x, bound[t1].y};
+    return ChunkRows{t0 == 0 ? 0 : r.first, r.end};
+}
+
+// Fills `m` for the edge positions [c0, c0 + len).  Called by all threads of the block.  Returns where row r.first + threadIdx.x starts, relative
+// to c0 (the caller's place for that row's pointer; INT32_MIN: no such row).
+template <int TILE>
+__device__ inline int32_t map_edges(EdgeMap<TILE> &m, const int64_t *__restrict__ eoff, const int64_t *__restrict__ rowstart, int32_t nS,
+                                    int64_t c0, int32_t len, ChunkRows &r)
+{
+    // A prefix broken by a failed wait must not lead outside eoff / rowstart.
+    if (r.first < 0) r.first = 0;
+    if (r.end > nS) r.end = nS;
+    __syncthreads();   // the previous chunk's readers are done
+    if (threadIdx.x < EdgeMap<TILE>::WORDS) m.starts[threadIdx.x] = 0ull;
+    if (threadIdx.x == 0) m.delta[0] = 0;
+    int32_t mine = INT32_MIN;
+    bool cleared = false;
+    for (int32_t a0 = r.first; a0 < r.end || !cleared; a0 += (int32_t)blockDim.x) {
+        const int32_t a = a0 + (int32_t)threadIdx.x;
+        const bool have = a < r.end;
+        int64_t beg = 0, end = 0, csr = 0;
+        if (have) {
+            beg = eoff[a] - c0;
+            end = eoff[a + 1] - c0;
+            csr = rowstart[a];
+        }
+        if (!cleared) {
+            if (have) mine = (int32_t)(beg < INT32_MIN + 1 ? INT32_MIN + 1 : beg);
+            __syncthreads();
+            cleared = true;
+        }
+        if (have && end > beg && end > 0 && beg < len) {
+            const int32_t p = beg > 0 ? (int32_t)beg : 0;
+            m.delta[p] = csr - beg;
+            atomicOr(&m.starts[p >> 6], 1ull << (p & 63));
         }
     }
     __syncthreads();
+    return mine;
 }
 
-// Called by all threads of the block (at least two wavefronts).  c0 < c1 <= eoff[nS].
-// `note` (nullable) points at this chunk's entry of the workspace's chunk table: with FROM_NOTE the
-// first row and row count are read from it (one load) instead of being searched for (four dependent
-// loads); otherwise they are searched for and, if `note` is given, left there for a later pass over
-// the same chunks.
-template <bool FROM_NOTE>
-__device__ inline void stage_slice(RowSlice &s, const int64_t *__restrict__ eoff, const int64_t *__restrict__ rowstart,
-                                   int32_t nS, int64_t c0, int64_t c1, int2 *note)
+// A lane's view of the words: their bits, and the last start at or before the end of each (lane l: word l).
+struct EdgeWords {
+    uint32_t lo, hi;
+    int32_t last;
+};
+template <int TILE>
+__device__ inline EdgeWords edge_words(const EdgeMap<TILE> &m)
 {
-    __syncthreads();  // previous chunk's readers are done
-    int64_t a_first, R;
-    if (FROM_NOTE) {
-        const int2 v = *note;
-        a_first = v.x;
-        R = v.y;
-    } else {
-        // the two searches run side by side, each by one whole wavefront (3 dependent loads for 8192
-        // rows where a per-thread binary search takes 14)
-        const int wave = (int)(threadIdx.x >> 6);
-        if (wave == 0) {
-            int64_t lb0 = wave_lower_bound(eoff, (int64_t)nS + 1, c0);
-            if (lb0 > nS) lb0 = nS;   // cannot happen with a sound prefix (c0 < eoff[nS])
-            if (lane_id() == 0) s.a_first = (int32_t)((eoff[lb0] == c0) ? lb0 : lb0 - 1);
-        } else if (wave == 1) {
-            const int64_t lb1 = wave_lower_bound(eoff, (int64_t)nS + 1, c1);
-            if (lane_id() == 0) s.R = (int32_t)lb1;  // turned into a count below
-        }
-        __syncthreads();
-        a_first = s.a_first;
-        R = (int64_t)s.R - a_first;
-        __syncthreads();  // everyone has read the end index before it is replaced by the count
-        if (note && threadIdx.x == 0) *note = make_int2((int)a_first, (int)R);
+    const int lane = lane_id();
+    const unsigned long long w = lane < EdgeMap<TILE>::WORDS ? m.starts[lane] : 0ull;
+    int32_t last = w ? lane * WAVE + 64 - __clzll((long long)w) : 0;   // one past the position; 0: none
+    // inclusive maximum over the lanes (zero fill does not change a maximum of counts)
+    auto step = [&](uint32_t v) { last = (int32_t)v > last ? (int32_t)v : last; };
+    step(dpp_move<0x111, 0xF>((uint32_t)last));
+    step(dpp_move<0x112, 0xF>((uint32_t)last));
+    step(dpp_move<0x114, 0xF>((uint32_t)last));
+    step(dpp_move<0x118, 0xF>((uint32_t)last));
+    if (EdgeMap<TILE>::WORDS > 16) {
+        step(dpp_move<0x142, 0xA>((uint32_t)last));
+        step(dpp_move<0x143, 0xC>((uint32_t)last));
     }
-    stage_rows(s, eoff, rowstart, nS, c0, a_first, R);
+    return EdgeWords{(uint32_t)w, (uint32_t)(w >> 32), last > 0 ? last - 1 : 0};
 }
-
-// The same from what the row pass left per chunk boundary (bound[t] belongs to edge position
-// t * EDGE_TILE): chunk t starts at bound[t].x (row 0 for t = 0) and ends before bound[t + 1].y -- two
-// independent loads instead of the searches.  The last chunk, when it ends short of a boundary, still
-// searches for its end.  Leaves (first row, rows) in `note` like the searching form.
-__device__ inline void stage_slice_bounds(RowSlice &s, const int64_t *__restrict__ eoff,
-                                          const int64_t *__restrict__ rowstart, int32_t nS, int64_t t, int64_t c0,
-                                          int64_t c1, const int2 *__restrict__ bound, int2 *note)
+// CSR address of position word * 64 + lane; `word` is the same for the whole wavefront.
+template <int TILE>
+__device__ inline int64_t edge_address(const EdgeMap<TILE> &m, const EdgeWords &e, int word)
 {
-    __syncthreads();  // previous chunk's readers are done
-    const bool ends_on_bound = c1 == c0 + EDGE_TILE;
-    const int64_t a_first = t == 0 ? 0 : (int64_t)bound[t].x;
-    int64_t lb1;
-    if (ends_on_bound) {
-        lb1 = bound[t + 1].y;
-    } else {
-        if (threadIdx.x < WAVE) {
-            const int64_t lb = wave_lower_bound(eoff, (int64_t)nS + 1, c1);
-            if (lane_id() == 0) s.R = (int32_t)lb;
-        }
-        __syncthreads();
-        lb1 = s.R;
-        __syncthreads();  // everyone has read the end index before it is replaced by the count
-    }
-    const int64_t R = lb1 - a_first;
-    if (note && threadIdx.x == 0) *note = make_int2((int)a_first, (int)R);
-    stage_rows(s, eoff, rowstart, nS, c0, a_first, R);
-}
-
-// CSR position of chunk-relative edge x (0 <= x < c1 - c0); *r_out = staged row index.
-__device__ inline int64_t edge_address(const RowSlice &s, const int64_t *__restrict__ eoff,
-                                       const int64_t *__restrict__ rowstart, int64_t c0, int32_t x, int32_t *r_out)
-{
-    int32_t lo = 0, hi = s.R;  // last r with off[r] <= x; off[0] <= 0 <= x always
-    if (s.in_lds) {
-        while (hi - lo > 1) {
-            const int32_t m = (lo + hi) >> 1;
-            if (s.off[m] <= x) lo = m; else hi = m;
-        }
-        *r_out = lo;
-        return s.start[lo] + (x - s.off[lo]);
-    }
-    const int64_t a0 = s.a_first;
-    while (hi - lo > 1) {
-        const int32_t m = (lo + hi) >> 1;
-        if (eoff[a0 + m] - c0 <= (int64_t)x) lo = m; else hi = m;
-    }
-    *r_out = lo;
-    return rowstart[a0 + lo] + ((int64_t)x - (eoff[a0 + lo] - c0));
+    const int lane = lane_id();
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)e.lo, word), hi = (uint32_t)__builtin_amdgcn_readlane((int)e.hi, word);
+    const int32_t before = word ? __builtin_amdgcn_readlane(e.last, word - 1) : 0;
+    const uint64_t upto = (((uint64_t)hi << 32) | lo) & (~0ull >> (63 - lane));
+    const int32_t p = upto ? word * WAVE + 63 - __clzll((long long)upto) : before;
+    return m.delta[p] + (word * WAVE + lane);
 }
 
 }  // namespace csgs

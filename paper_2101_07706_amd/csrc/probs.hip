@@ -6,7 +6,7 @@
 //                  numbering; tile offsets by the single-pass scan across blocks), CSR start of
 //                  every row; the last tile leaves the row count and the edge counts for
 //                  the kernels that follow
-//   scan_edges     flat over the edges of S (chunks of 1024, rows of a chunk staged in LDS, so
+//   scan_edges     flat over the edges of S (chunks of 1024, a chunk's rows mapped to its positions in LDS, so
 //                  hub rows and short rows cost the same per edge): square each edge value
 //                  exactly, round to the fixed-point grid, add into a per-node 64-bit accumulator
 //                  -- remote targets with fire-and-forget integer atomics; targets in the local id
@@ -94,7 +94,7 @@ __device__ inline unsigned long long edge_weight(float v, double scale)
     return q < 1 ? 1ull : (unsigned long long)q;
 }
 
-// The weight scan, grid-stride over chunks of EDGE_TILE edges: stage the rows of the chunk, fetch column and value of
+// The weight scan, grid-stride over chunks of EDGE_TILE edges: map the chunk's positions to rows, fetch column and value of
 // every edge, square, round.  An edge whose target lies outside the local id range is added to the per-node accumulator
 // with a device-scope atomic.  The others -- most edges: the partition holds most neighbors -- are counting-sorted by the
 // tile of their target inside the block and, where there are enough of them, written to the chunk's piece of the
@@ -110,19 +110,20 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
                                                   const int64_t *__restrict__ eoff,
                                                   const int64_t *__restrict__ rowstart,
                                                   uint64_t *__restrict__ wtable, uint8_t *__restrict__ tileflag,
-                                                  int2 *__restrict__ chunk_note, const int2 *__restrict__ bound_note,
+                                                  const int2 *__restrict__ bound_note,
                                                   uint64_t *__restrict__ epoch, int32_t *__restrict__ status, Stage stg, InstStride is)
 {
     constexpr int ITEMS = EDGE_TILE / 256;
     constexpr int BINS = SUB_MAX / WAVE;          // groups per lane of the counting sort
     static_assert(SUB_MAX % WAVE == 0 && EDGE_TILE <= 0xFFFF, "groups of a chunk");
-    __shared__ RowSlice slice;
+    __shared__ EdgeMap<EDGE_TILE> map;
     __shared__ unsigned long long s_e[EDGE_TILE];
     __shared__ uint32_t hist[SUB_MAX + 1];
     meta = inst_ptr(meta, is.ws); eoff = inst_ptr(eoff, is.ws); rowstart = inst_ptr(rowstart, is.ws);
-    wtable = inst_ptr(wtable, is.ws); tileflag = inst_ptr(tileflag, is.ws); chunk_note = inst_ptr(chunk_note, is.ws); bound_note = inst_ptr(bound_note, is.ws);
+    wtable = inst_ptr(wtable, is.ws); tileflag = inst_ptr(tileflag, is.ws); bound_note = inst_ptr(bound_note, is.ws);
     stg.e = inst_ptr(stg.e, is.ws); stg.off = inst_ptr(stg.off, is.ws);
     status = inst_ptr(status, is.buf); epoch = inst_ptr(epoch, is.ws);
+    ChunkRows rows = chunk_rows(bound_note, blockIdx.x, (int64_t)blockIdx.x + 1);   // (the grid stays within the notes; on its way beside the counts)
     const int32_t nS = (int32_t)meta[META_ROWS];
     const double scale = ldexp(1.0, shift_for_rows(shift_base, nS));
     const int64_t E = meta[META_EDGES];
@@ -142,8 +143,10 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
         const bool staged = t < n_staged;
         if (staged)
             for (int i = threadIdx.x; i < SUB_MAX; i += blockDim.x) hist[i] = 0u;   // (its last readers are a barrier behind)
-        stage_slice_bounds(slice, eoff, rowstart, nS, t, c0, c1, bound_note, chunk_note + t);   // (starts and ends with a barrier)
         const int32_t len = (int32_t)(c1 - c0);
+        if (t != blockIdx.x) rows = chunk_rows(bound_note, t, t + 1);
+        (void)map_edges(map, eoff, rowstart, nS, c0, len, rows);   // (starts and ends with a barrier)
+        const EdgeWords words = edge_words(map);
         // All of a thread's edges go through each step together -- their addresses, then their columns and
         // values with unconditional loads (an edge that does not exist reads entry 0 and is dropped) -- so
         // the loads of the four edges travel at the same time instead of one after the other.
@@ -154,9 +157,9 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
             const int32_t x = (int32_t)threadIdx.x + k * 256;
             ek[k] = 0;
             live[k] = x < len;
+            const int64_t at = edge_address(map, words, __builtin_amdgcn_readfirstlane(wave + k * 4));
             if (live[k]) {
-                int32_t r;
-                ek[k] = edge_address(slice, eoff, rowstart, c0, x, &r);
+                ek[k] = at;
                 if (ek[k] < 0 || ek[k] >= nnz) {   // only after a failed wait in the prefix kernel: stay inside the graph
                     bad = true;
                     ek[k] = 0;
@@ -971,7 +974,7 @@ static int build_probs_impl(const csgs_graph *g, const int32_t *S, int32_t nS, c
                     adjacent ? 1 : 0, w.n_inst, min_chunks, (unsigned long long *)w.split_sum, (unsigned long long *)w.split_flag};
     CSGS_LAUNCH(K_SCAN_EDGES, scan_edges, dim3((unsigned)chunks, 1, nz), dim3(256), st, g->colidx, g->val,
                 g->n_nodes, g->nnz, shift_base, rows.meta, w.chunk_cap * EDGE_TILE, rows.eoff, rows.rowstart, w.wtable,
-                w.tileflag, rows.chunk_note, rows.bound_note, w.epoch, status, stg, is);
+                w.tileflag, rows.bound_note, w.epoch, status, stg, is);
     CSGS_LAUNCH_CHECK();
     const int64_t per = w.n_inst == 1 && w.n_tiles <= CAND_PART_ONE ? 1 : CAND_PART_TILES;
     const int64_t below = tiles ? (tile0 + per - 1) / per : 0;

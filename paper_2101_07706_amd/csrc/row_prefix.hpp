@@ -12,7 +12,7 @@ static_assert(ROW_TILE == 256 * RP_ITEMS, "row tile");
 
 // Tile t of the rows S[0 .. nS).  Called by all 256 threads of a block; blocks with t >= number of
 // tiles must not call.  Leaves in `meta` (by the last tile): row count, edge count (0 when above
-// edge_cap: treated as empty), true edge count; in bound_note [chunk_cap + 2] what stage_slice_bounds() reads.
+// edge_cap: treated as empty), true edge count; in bound_note [chunk_cap + 2] what chunk_rows() reads.
 __device__ inline void row_prefix_tile(const int64_t *__restrict__ rowptr, int64_t n_nodes,
                                        const int32_t *__restrict__ S, int32_t nS, int64_t t, int64_t n_tiles,
                                        const TileState<1> &ts, unsigned long long tag, int64_t *__restrict__ eoff,
@@ -68,12 +68,17 @@ __device__ inline void row_prefix_tile(const int64_t *__restrict__ rowptr, int64
             const int64_t e1 = ex + d[k];
             for (int64_t tb = ex / EDGE_TILE + 1; tb <= e1 / EDGE_TILE && tb <= chunk_cap; ++tb)
                 bound_note[tb] = make_int2(e1 == tb * EDGE_TILE ? a + 1 : a, a + 1);
+            // a last chunk that ends short of a boundary ends with the last row that has edges
+            if (t == n_tiles - 1 && d[k] > 0 && e1 == (int64_t)excl[0] + tile_total && e1 % EDGE_TILE && e1 / EDGE_TILE <= chunk_cap)
+                bound_note[e1 / EDGE_TILE + 1].y = a + 1;
         }
         ex += d[k];
     }
     if (bad) atomicOr(status, CSGS_ST_BAD_NODE_ID);
     if (t == n_tiles - 1 && threadIdx.x == 0) {
         const int64_t total = (int64_t)excl[0] + tile_total;
+        // (none of this tile's rows has edges: somewhere before it, and the rows in between are empty)
+        if (tile_total == 0 && total % EDGE_TILE && total / EDGE_TILE <= chunk_cap) bound_note[total / EDGE_TILE + 1].y = r0;
         // an edge count the workspace cannot hold is treated as empty (the weight scan reports it)
         const int64_t usable = total > edge_cap ? 0 : total;
         eoff[nS] = usable;
@@ -94,8 +99,7 @@ __device__ inline int64_t row_tiles(int32_t nS)
 // 2^61 / (s_fx rmax); shift_base = 61 - ceil(log2 s_fx) - ceil(log2 rmax).
 __device__ inline int32_t shift_for_rows(int32_t shift_base, int64_t nS)
 {
-    int32_t lg = 0;
-    while (lg < 31 && (1ll << lg) < nS) ++lg;
+    const int32_t lg = nS > 1 ? 64 - __builtin_clzll((unsigned long long)(nS - 1)) : 0;   // ceil(log2 nS), nS below 2^31
     const int32_t shift = shift_base - lg;
     return shift > 52 ? 52 : shift;
 }

@@ -396,7 +396,7 @@ struct NextRows {
 // four 64-edge words.  Out: per lane and word the kept edge's rank (position in S_next + 1; 0 = not kept) and CSR
 // position; in LDS the keep bits of every word (mask) and the kept edges before it (pre).
 struct AdjChunk {
-    RowSlice slice;
+    EdgeMap<EDGE_TILE> map;
     uint64_t mask[EDGE_TILE / 64];
     int32_t pre[EDGE_TILE / 64 + 1];
 };
@@ -408,14 +408,15 @@ struct AdjGraph {
     const uint64_t *rank, *member;
     const double *pdbl;
 };
-template <bool FROM_NOTE>
-__device__ inline void adj_chunk(AdjChunk &s, const AdjGraph &g, int32_t nS, int64_t c0, int64_t c1, uint64_t rank_tag, int2 *note,
-                                 int32_t (&rk)[4], int64_t (&ea)[4])
+// Returns what map_edges() does.
+__device__ inline int32_t adj_chunk(AdjChunk &s, const AdjGraph &g, int32_t nS, int64_t c0, int64_t c1, uint64_t rank_tag, ChunkRows &rows,
+                                    int32_t (&rk)[4], int64_t (&ea)[4])
 {
     const int lane = lane_id();
     const int wave = (int)(threadIdx.x >> 6);
-    stage_slice<FROM_NOTE>(s.slice, g.eoff, g.rowstart, nS, c0, c1, note);
     const int32_t len = (int32_t)(c1 - c0);
+    const int32_t starts = map_edges(s.map, g.eoff, g.rowstart, nS, c0, len, rows);
+    const EdgeWords words = edge_words(s.map);
     // A lane's four edges go through each step together, and no load sits under a condition (an edge that does
     // not exist reads entry 0 and is dropped): the four columns travel at the same time, then the four table
     // lookups, instead of eight trips one after the other.
@@ -423,16 +424,9 @@ __device__ inline void adj_chunk(AdjChunk &s, const AdjGraph &g, int32_t nS, int
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const int32_t x = wave * 256 + k * 64 + lane;
-        ea[k] = 0;
-        live[k] = false;
-        if (x < len) {
-            int32_t r;
-            const int64_t a = edge_address(s.slice, g.eoff, g.rowstart, c0, x, &r);
-            if (a >= 0 && a < g.nnz) {   // (an address outside the graph can only follow a failed wait)
-                ea[k] = a;
-                live[k] = true;
-            }
-        }
+        const int64_t a = edge_address(s.map, words, __builtin_amdgcn_readfirstlane(wave * 4 + k));
+        live[k] = x < len && a >= 0 && a < g.nnz;   // (an address outside the graph can only follow a failed wait)
+        ea[k] = live[k] ? a : 0;
     }
     int32_t ck[4];
 #pragma unroll
@@ -463,6 +457,12 @@ __device__ inline void adj_chunk(AdjChunk &s, const AdjGraph &g, int32_t nS, int
         if (lane <= EDGE_TILE / 64) s.pre[lane] = incl - c;
     }
     __syncthreads();
+    return starts;
+}
+// Kept edges of the chunk before position `off` of it (0 <= off < its length)
+__device__ inline int32_t kept_before(const AdjChunk &s, int32_t off)
+{
+    return s.pre[off >> 6] + __popcll(s.mask[off >> 6] & ((1ull << (off & 63)) - 1ull));
 }
 // Value and place inside the chunk of a lane's kept edges (unconditional loads again)
 __device__ inline void adj_values(const AdjChunk &s, const AdjGraph &g, const int32_t (&rk)[4], const int64_t (&ea)[4], float (&pv)[4],
@@ -532,9 +532,8 @@ constexpr int ADJ_MARK_GRID = 2048;    // eight blocks per compute unit, by thre
 constexpr int ADJ_PLACE_GRID = 512;
 constexpr int ADJ_PLACE_MIN = 4;       // chunks a block of the placing pass takes at least: one per wavefront
 
-template <bool FROM_NOTE>
 __global__ __launch_bounds__(256) void adj_mark(AdjGraph g, const int64_t *__restrict__ meta, const uint64_t *__restrict__ epoch,
-                                                int64_t chunk_cap, int2 *__restrict__ chunk_note, uint32_t *__restrict__ chunk_cnt,
+                                                int64_t chunk_cap, const int2 *__restrict__ bound_note, uint32_t *__restrict__ chunk_cnt,
                                                 uint64_t *__restrict__ kept, int64_t kept_chunks, int32_t *__restrict__ adj_rowptr,
                                                 int32_t *__restrict__ status, RemoteArgs rem, NextRows nxt, InstStride is)
 {
@@ -542,10 +541,11 @@ __global__ __launch_bounds__(256) void adj_mark(AdjGraph g, const int64_t *__res
     if (adj_leading_blocks(rem, nxt, epoch, status, is)) return;
     meta = inst_ptr(meta, is.ws); g.eoff = inst_ptr(g.eoff, is.ws); g.rowstart = inst_ptr(g.rowstart, is.ws);
     g.rank = inst_ptr(g.rank, is.ws); g.member = inst_ptr(g.member, is.ws); g.pdbl = inst_ptr(g.pdbl, is.ws);
-    chunk_note = inst_ptr(chunk_note, is.ws); chunk_cnt = inst_ptr(chunk_cnt, is.ws); kept = inst_ptr(kept, is.ws);
+    bound_note = inst_ptr(bound_note, is.ws); chunk_cnt = inst_ptr(chunk_cnt, is.ws); kept = inst_ptr(kept, is.ws);
     adj_rowptr = inst_ptr(adj_rowptr, is.buf);
     const int64_t bid = (int64_t)blockIdx.x - rem.blocks - nxt.blocks;
     const int64_t n_bids = (int64_t)gridDim.x - rem.blocks - nxt.blocks;
+    ChunkRows rows = chunk_rows(bound_note, bid, bid + 1);   // (the grid stays within the notes; on its way beside the counts)
     __shared__ AdjChunk s;
     const uint64_t rank_tag = (epoch[EPOCH_DRAW] & 0xFFFFFFFFull) << 32;
     const int32_t nS = (int32_t)meta[META_ROWS];
@@ -558,18 +558,17 @@ __global__ __launch_bounds__(256) void adj_mark(AdjGraph g, const int64_t *__res
         int32_t rk[4], at[4];
         int64_t ea[4];
         float pv[4];
-        adj_chunk<FROM_NOTE>(s, g, nS, c0, c1, rank_tag, chunk_note + t, rk, ea);
+        if (t != bid) rows = chunk_rows(bound_note, t, t + 1);
+        int32_t off = adj_chunk(s, g, nS, c0, c1, rank_tag, rows, rk, ea);
         adj_values(s, g, rk, ea, pv, at);
-        if (threadIdx.x == 0) {
-            const int64_t off0 = s.slice.in_lds ? (int64_t)s.slice.off[0] : g.eoff[s.slice.a_first] - c0;
-            chunk_cnt[t] = (uint32_t)s.pre[EDGE_TILE / 64] | (off0 == 0 ? 0x80000000u : 0u);
-        }
-        // row pointers of the rows that start inside this chunk: kept edges of the chunk before the row start
-        const int32_t R = s.slice.R, len = (int32_t)(c1 - c0);
-        const int64_t a_first = s.slice.a_first;
-        for (int32_t r = threadIdx.x; r < R; r += blockDim.x) {
-            const int64_t off = s.slice.in_lds ? (int64_t)s.slice.off[r] : g.eoff[a_first + r] - c0;
-            if (off >= 0 && off < len) adj_rowptr[a_first + r] = s.pre[off >> 6] + __popcll(s.mask[off >> 6] & ((1ull << (off & 63)) - 1ull));
+        if (threadIdx.x == 0) chunk_cnt[t] = (uint32_t)s.pre[EDGE_TILE / 64] | (off == 0 ? 0x80000000u : 0u);
+        // row pointers of the rows that start inside this chunk (the last one's: or behind it): kept edges of the chunk before the row start
+        const int32_t len = (int32_t)(c1 - c0);
+        const bool last = t == n_chunks - 1;
+        for (int32_t a = rows.first + (int32_t)threadIdx.x; a < rows.end;) {
+            if (off >= 0 && (off < len || last)) adj_rowptr[a] = off < len ? kept_before(s, off) : s.pre[EDGE_TILE / 64];
+            a += (int32_t)blockDim.x;
+            if (a < rows.end) off = (int32_t)(g.eoff[a] - c0);   // (a row behind the first one starts inside the chunk or at its end)
         }
         if (t < kept_chunks) {
 #pragma unroll
@@ -580,20 +579,20 @@ __global__ __launch_bounds__(256) void adj_mark(AdjGraph g, const int64_t *__res
 }
 
 __global__ __launch_bounds__(256) void adj_place(AdjGraph g, const int64_t *__restrict__ meta, uint64_t *__restrict__ epoch,
-                                                 int64_t chunk_cap, int2 *__restrict__ chunk_note, const uint32_t *__restrict__ chunk_cnt,
+                                                 int64_t chunk_cap, const int2 *__restrict__ bound_note, const uint32_t *__restrict__ chunk_cnt,
                                                  const uint64_t *__restrict__ kept, int64_t kept_chunks, int32_t *__restrict__ adj_rowptr,
                                                  int32_t *__restrict__ adj_col, float *__restrict__ adj_val, int64_t adj_cap,
                                                  int64_t *__restrict__ adj_nnz, int32_t *__restrict__ status, InstStride is)
 {
     __shared__ uint32_t s_scan[17];
     __shared__ uint32_t s_cnt[256], s_base[256];
-    __shared__ int2 s_note[256];
+    __shared__ ChunkRows s_rows[256];
     __shared__ uint64_t s_sum[4];
     __shared__ AdjChunk s;   // only for chunks whose kept edges were not left (more than kept_chunks)
     status = inst_ptr(status, is.buf); epoch = inst_ptr(epoch, is.ws);
     meta = inst_ptr(meta, is.ws); g.eoff = inst_ptr(g.eoff, is.ws); g.rowstart = inst_ptr(g.rowstart, is.ws);
     g.rank = inst_ptr(g.rank, is.ws); g.member = inst_ptr(g.member, is.ws); g.pdbl = inst_ptr(g.pdbl, is.ws);
-    chunk_note = inst_ptr(chunk_note, is.ws); chunk_cnt = inst_ptr(chunk_cnt, is.ws); kept = inst_ptr(kept, is.ws);
+    bound_note = inst_ptr(bound_note, is.ws); chunk_cnt = inst_ptr(chunk_cnt, is.ws); kept = inst_ptr(kept, is.ws);
     adj_rowptr = inst_ptr(adj_rowptr, is.buf); adj_col = inst_ptr(adj_col, is.buf); adj_val = inst_ptr(adj_val, is.buf);
     adj_nnz = inst_ptr(adj_nnz, is.buf);
     const int tid = (int)threadIdx.x, lane = lane_id(), wave = tid >> 6;
@@ -633,7 +632,7 @@ __global__ __launch_bounds__(256) void adj_place(AdjGraph g, const int64_t *__re
     for (int64_t ts = t0; ts < t1; ts += 256) {
         const int m = (int)(t1 - ts < 256 ? t1 - ts : 256);
         const uint32_t raw = tid < m ? chunk_cnt[ts + tid] : 0u;
-        if (tid < m) s_note[tid] = chunk_note[ts + tid];
+        if (tid < m) s_rows[tid] = chunk_rows(bound_note, ts + tid, ts + tid + 1);
         uint32_t sum;
         const uint32_t ex = block_exclusive_scan<uint32_t>(raw & CNT, s_scan, &sum);   // (starts with a barrier: the arrays below are free)
         s_cnt[tid] = raw;
@@ -644,10 +643,10 @@ __global__ __launch_bounds__(256) void adj_place(AdjGraph g, const int64_t *__re
             const int64_t t = ts + k;
             const uint32_t cnt = s_cnt[k] & CNT;
             const int64_t b = (int64_t)(base + s_base[k]);
-            int64_t a = s_note[k].x, a_end = a + s_note[k].y;   // (stay inside the row pointers whatever a broken prefix left)
+            int64_t a = s_rows[k].first, a_end = s_rows[k].end;   // (stay inside the row pointers whatever a broken prefix left)
             if (!(s_cnt[k] >> 31)) ++a;                        // the chunk's first row began in an earlier chunk
             if (a < 0) a = 0;
-            if (a_end > (int64_t)nS + 1) a_end = (int64_t)nS + 1;
+            if (a_end > nS) a_end = nS;
             for (int64_t r = a + lane; r < a_end; r += WAVE) {
                 const int64_t v = b + adj_rowptr[r];
                 adj_rowptr[r] = (int32_t)(v < ptr_max ? v : ptr_max);
@@ -666,7 +665,8 @@ __global__ __launch_bounds__(256) void adj_place(AdjGraph g, const int64_t *__re
             int32_t rk[4], at[4];
             int64_t ea[4];
             float pv[4];
-            adj_chunk<true>(s, g, nS, c0, c1, (epoch[EPOCH_DRAW] & 0xFFFFFFFFull) << 32, chunk_note + t, rk, ea);
+            ChunkRows rows = chunk_rows(bound_note, t, t + 1);
+            adj_chunk(s, g, nS, c0, c1, (epoch[EPOCH_DRAW] & 0xFFFFFFFFull) << 32, rows, rk, ea);
             adj_values(s, g, rk, ea, pv, at);
             const int64_t b = (int64_t)(base + s_base[t - ts]);
 #pragma unroll
@@ -680,11 +680,11 @@ __global__ __launch_bounds__(256) void adj_place(AdjGraph g, const int64_t *__re
         __syncthreads();
     }
     if (t1 == n_chunks) {
-        // rows that start at or after the last edge (trailing empty rows, and the end pointer)
+        // rows behind the last one with edges, and the end pointer
         const int64_t total = (int64_t)base;
         const int32_t clamp = (int32_t)(total < ptr_max ? total : ptr_max);
-        const int64_t first_tail = wave_lower_bound(g.eoff, (int64_t)nS + 1, E);
-        for (int64_t a = first_tail + tid; a <= nS; a += 256) adj_rowptr[a] = clamp;
+        const int32_t end = chunk_rows(bound_note, n_chunks - 1, n_chunks).end;
+        for (int64_t a = (end < 0 ? 0 : end) + (int64_t)tid; a <= nS; a += 256) adj_rowptr[a] = clamp;
         if (tid == 0) {
             *adj_nnz = total;
             if (total > adj_cap || total > 0x7FFFFFFFll) atomicOr(status, CSGS_ST_ADJ_OVERFLOW);
@@ -694,9 +694,8 @@ __global__ __launch_bounds__(256) void adj_place(AdjGraph g, const int64_t *__re
 
 // One pass: a block publishes its chunk's count and waits for the earlier chunks' before it places anything.  All blocks
 // are resident; block b takes chunks b, b + grid, ... in ascending order.
-template <bool FROM_NOTE>
 __global__ __launch_bounds__(256) void adj_once(AdjGraph g, const int64_t *__restrict__ meta, uint64_t *__restrict__ epoch,
-                                                uint64_t *__restrict__ ts_mem, int64_t chunk_cap, int2 *__restrict__ chunk_note,
+                                                uint64_t *__restrict__ ts_mem, int64_t chunk_cap, const int2 *__restrict__ bound_note,
                                                 int32_t *__restrict__ adj_rowptr, int32_t *__restrict__ adj_col,
                                                 float *__restrict__ adj_val, int64_t adj_cap, int64_t *__restrict__ adj_nnz,
                                                 int32_t *__restrict__ status, RemoteArgs rem, NextRows nxt, InstStride is)
@@ -705,13 +704,14 @@ __global__ __launch_bounds__(256) void adj_once(AdjGraph g, const int64_t *__res
     if (adj_leading_blocks(rem, nxt, epoch, status, is)) return;
     meta = inst_ptr(meta, is.ws); g.eoff = inst_ptr(g.eoff, is.ws); g.rowstart = inst_ptr(g.rowstart, is.ws);
     g.rank = inst_ptr(g.rank, is.ws); g.member = inst_ptr(g.member, is.ws); g.pdbl = inst_ptr(g.pdbl, is.ws);
-    ts_mem = inst_ptr(ts_mem, is.ws); chunk_note = inst_ptr(chunk_note, is.ws);
+    ts_mem = inst_ptr(ts_mem, is.ws); bound_note = inst_ptr(bound_note, is.ws);
     adj_rowptr = inst_ptr(adj_rowptr, is.buf); adj_col = inst_ptr(adj_col, is.buf); adj_val = inst_ptr(adj_val, is.buf);
     adj_nnz = inst_ptr(adj_nnz, is.buf);
     const int64_t bid = (int64_t)blockIdx.x - rem.blocks - nxt.blocks;
     const int64_t n_bids = (int64_t)gridDim.x - rem.blocks - nxt.blocks;
     __shared__ AdjChunk s;
     __shared__ unsigned long long s_lb[1];
+    ChunkRows rows = chunk_rows(bound_note, bid, bid + 1);   // (the grid stays within the notes; on its way beside the counts)
     const TileState<1> ts(ts_mem, chunk_cap, wait_limit(epoch));
     const unsigned long long call = call_number(epoch);
     const unsigned long long tag = call_tag(call, SLOT_ADJ);
@@ -739,22 +739,24 @@ __global__ __launch_bounds__(256) void adj_once(AdjGraph g, const int64_t *__res
         int32_t rk[4], at[4];
         int64_t ea[4];
         float pv[4];
-        adj_chunk<FROM_NOTE>(s, g, nS, c0, c1, rank_tag, FROM_NOTE ? chunk_note + t : nullptr, rk, ea);
+        if (t != bid) rows = chunk_rows(bound_note, t, t + 1);
+        int32_t off = adj_chunk(s, g, nS, c0, c1, rank_tag, rows, rk, ea);
         const int32_t tile_cnt = s.pre[EDGE_TILE / 64];
         unsigned long long local[1] = {(unsigned long long)tile_cnt}, excl[1];
         lookback_publish<1>(ts, tag, t, local);
         adj_values(s, g, rk, ea, pv, at);   // does not depend on the prefix: fetch and divide while it is resolved
         lookback_resolve<1>(ts, tag, t, n_chunks, local, excl, s_lb, status);
         const int64_t base = (int64_t)excl[0];
-        // row pointers of the rows that start inside this chunk: kept edges before the row start
-        const int32_t R = s.slice.R, len = (int32_t)(c1 - c0);
-        const int64_t a_first = s.slice.a_first;
-        for (int32_t r = threadIdx.x; r < R; r += blockDim.x) {
-            const int64_t off = s.slice.in_lds ? (int64_t)s.slice.off[r] : g.eoff[a_first + r] - c0;
-            if (off >= 0 && off < len) {
-                const int64_t v = base + s.pre[off >> 6] + __popcll(s.mask[off >> 6] & ((1ull << (off & 63)) - 1ull));
-                adj_rowptr[a_first + r] = (int32_t)(v < ptr_max ? v : ptr_max);
+        // row pointers of the rows that start inside this chunk (the last one's: or behind it): kept edges before the row start
+        const int32_t len = (int32_t)(c1 - c0);
+        const bool last = t == n_chunks - 1;
+        for (int32_t a = rows.first + (int32_t)threadIdx.x; a < rows.end;) {
+            if (off >= 0 && (off < len || last)) {
+                const int64_t v = base + (off < len ? kept_before(s, off) : tile_cnt);
+                adj_rowptr[a] = (int32_t)(v < ptr_max ? v : ptr_max);
             }
+            a += (int32_t)blockDim.x;
+            if (a < rows.end) off = (int32_t)(g.eoff[a] - c0);   // (a row behind the first one starts inside the chunk or at its end)
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k)
@@ -762,12 +764,11 @@ __global__ __launch_bounds__(256) void adj_once(AdjGraph g, const int64_t *__res
                 adj_col[base + at[k]] = rk[k] - 1;
                 adj_val[base + at[k]] = pv[k];
             }
-        if (t == n_chunks - 1) {
-            // rows that start at or after the last edge (trailing empty rows, and the end pointer)
+        if (last) {
+            // rows behind the last one with edges, and the end pointer
             const int64_t total = base + tile_cnt;
             const int32_t clamp = (int32_t)(total < ptr_max ? total : ptr_max);
-            const int64_t first_tail = wave_lower_bound(g.eoff, (int64_t)nS + 1, E);
-            for (int64_t a = first_tail + threadIdx.x; a <= nS; a += blockDim.x) adj_rowptr[a] = clamp;
+            for (int64_t a = (rows.end < 0 ? 0 : rows.end) + (int64_t)threadIdx.x; a <= nS; a += blockDim.x) adj_rowptr[a] = clamp;
             if (threadIdx.x == 0) {
                 *adj_nnz = total;
                 if (total > adj_cap || total > 0x7FFFFFFFll) atomicOr(status, CSGS_ST_ADJ_OVERFLOW);
@@ -859,28 +860,19 @@ static int sampled_adjacency_impl(const csgs_graph *g, const int32_t *rows, int3
     const unsigned nz = (unsigned)w.n_inst;
     const InstStride is = inst_stride(w);
     const AdjGraph ag{g->colidx, g->val, g->n_nodes, g->nnz, cur.eoff, cur.rowstart, w.rank, w.member, w.pdbl};
-    // after csgs_build_probs on the same rows the weight scan has left every chunk's row slice in the workspace
     if (expected * w.n_inst <= ADJ_ONCE_MAX) {
         const dim3 grid_once(blocks(resident_grid(2), 1) + (unsigned)(rem.blocks + nxt.blocks), 1, nz);
-        if (reuse_offsets)
-            CSGS_LAUNCH(K_ADJ_ONCE, adj_once<true>, grid_once, dim3(256), st, ag, cur.meta, w.epoch, w.adj_ts, w.chunk_cap, cur.chunk_note,
-                        adj_rowptr, adj_col, adj_val, adj_cap, adj_nnz, status, rem, nxt, is);
-        else
-            CSGS_LAUNCH(K_ADJ_ONCE, adj_once<false>, grid_once, dim3(256), st, ag, cur.meta, w.epoch, w.adj_ts, w.chunk_cap, cur.chunk_note,
-                        adj_rowptr, adj_col, adj_val, adj_cap, adj_nnz, status, rem, nxt, is);
+        CSGS_LAUNCH(K_ADJ_ONCE, adj_once, grid_once, dim3(256), st, ag, cur.meta, w.epoch, w.adj_ts, w.chunk_cap, cur.bound_note,
+                    adj_rowptr, adj_col, adj_val, adj_cap, adj_nnz, status, rem, nxt, is);
         CSGS_LAUNCH_CHECK();
         return CSGS_OK;
     }
     const unsigned mark = blocks(ADJ_MARK_GRID, 1), place = blocks(ADJ_PLACE_GRID, ADJ_PLACE_MIN);
     const dim3 grid(mark + (unsigned)(rem.blocks + nxt.blocks), 1, nz);
-    if (reuse_offsets)
-        CSGS_LAUNCH(K_ADJ_MARK, adj_mark<true>, grid, dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.chunk_note, w.adj_cnt, w.stage,
-                    w.stage_chunks, adj_rowptr, status, rem, nxt, is);
-    else
-        CSGS_LAUNCH(K_ADJ_MARK, adj_mark<false>, grid, dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.chunk_note, w.adj_cnt, w.stage,
-                    w.stage_chunks, adj_rowptr, status, rem, nxt, is);
+    CSGS_LAUNCH(K_ADJ_MARK, adj_mark, grid, dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.bound_note, w.adj_cnt, w.stage,
+                w.stage_chunks, adj_rowptr, status, rem, nxt, is);
     CSGS_LAUNCH_CHECK();
-    CSGS_LAUNCH(K_ADJ_PLACE, adj_place, dim3(place, 1, nz), dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.chunk_note, w.adj_cnt,
+    CSGS_LAUNCH(K_ADJ_PLACE, adj_place, dim3(place, 1, nz), dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.bound_note, w.adj_cnt,
                 w.stage, w.stage_chunks, adj_rowptr, adj_col, adj_val, adj_cap, adj_nnz, status, is);
     CSGS_LAUNCH_CHECK();
     return CSGS_OK;
