@@ -36,7 +36,7 @@ constexpr int SUB_MAX = 320;                      // most such tiles: local rang
 constexpr int SUB_STRIDE = SUB_MAX + 32;          // entries per chunk of the groups' begins: SUB_MAX + 1, in whole 64-byte pieces
 constexpr int64_t SPLIT_BLOCKS = 512;             // most blocks of a launch over which the local tiles are split
 constexpr int64_t STAGE_EDGES_MAX = 8ll << 20;    // most edges of a call that are handed over this way (the others go through atomics)
-constexpr int EPOCH_WORDS = 8;        // counters on the device (lookback.hpp)
+constexpr int EPOCH_WORDS = 16;       // counters on the device (lookback.hpp)
 constexpr int META_WORDS = 4;
 constexpr int META_ROWS = 0;          // rows the latest row_prefix covered (the count behind eoff / rowstart)
 constexpr int META_EDGES = 1;         // eoff[rows]: edges of those rows (0 when above the workspace's capacity)
@@ -48,7 +48,7 @@ __host__ __device__ constexpr size_t scan_state_words(int64_t tiles, int nv)
 {
     return (size_t)(1 + nv) * (size_t)(tiles + 2 * (tiles / 64 + 2));
 }
-static_assert(HIT_COUNT_WORDS * 64 / CAND_TILE >= (int64_t)scan_state_words(HIT_GRID, 1), "the hit compaction's scan state in cand_flag");
+static_assert(HIT_COUNT_WORDS * 64 / CAND_TILE >= (int64_t)scan_state_words(HIT_GRID, 1), "the hit compaction's scan state in hit_ts");
 
 struct RowOffsets {
     int64_t *eoff;       // [nS + 1] exclusive prefix of the degrees of the rows
@@ -69,8 +69,7 @@ struct Workspace {
     uint64_t *member;    // [(n_nodes + 31) / 32]  (tag << 32) | one bit per id of the word's 32: in S_next of the draw with that tag
     uint64_t *partial;   // [4 * n_tiles] per-tile candidate counts and weight sums
     uint64_t *gtot;      // [4 * ceil(n_tiles / 64)] the same per group of 64 tiles
-    uint64_t *cand_flag; // [n_tiles] tag of the call whose partial sums a tile holds; in a draw with a long position bitmap the
-                         // scan state of the hit compaction (which keeps its sums apart from any tag)
+    uint64_t *hit_ts;    // [n_tiles] in a draw with a long position bitmap the scan state of the hit compaction
     uint64_t *epoch;     // [EPOCH_WORDS] call counter and draw tag (see lookback.hpp); advanced on the device
     uint64_t *cbitmap[2]; // [ceil(n_nodes/64)] bit set = candidate position was drawn.  Draws take turns: the compaction of one
                          // clears what the one before set
@@ -161,7 +160,7 @@ __host__ inline Workspace carve(void *base, int64_t n_nodes, int64_t nS_max, int
     w.member = (uint64_t *)take((size_t)((n_nodes + 31) / 32) * 8);
     w.partial = (uint64_t *)take((size_t)w.n_tiles * 4 * 8);
     w.gtot = (uint64_t *)take((size_t)((w.n_tiles + 63) / 64) * 4 * 8);
-    w.cand_flag = (uint64_t *)take((size_t)w.n_tiles * 8);
+    w.hit_ts = (uint64_t *)take((size_t)w.n_tiles * 8);
     w.epoch = (uint64_t *)take(EPOCH_WORDS * 8);
     for (int b = 0; b < 2; ++b) w.cbitmap[b] = (uint64_t *)take(words * 8);
     w.adj_ts = (uint64_t *)take(scan_state_words(w.chunk_cap, 1) * 8);
@@ -426,42 +425,47 @@ __device__ inline ChunkRows chunk_rows(const int2 *__restrict__ bound, int64_t t
     return ChunkRows{t0 == 0 ? 0 : r.first, r.end};
 }
 
-// Fills `m` for the edge positions [c0, c0 + len).  Called by all threads of the block.  Returns where row r.first + threadIdx.x starts, relative
-// to c0 (the caller's place for that row's pointer; INT32_MIN: no such row).
+// Row r.first + threadIdx.x: where its edges begin and end in the flat order, and in the CSR arrays.  (Loads without a condition: a row that
+// does not exist reads another one's.)  nS > 0.
+struct RowEdges {
+    int64_t beg, end, csr;
+};
+__device__ inline RowEdges row_edges(const int64_t *__restrict__ eoff, const int64_t *__restrict__ rowstart, int32_t nS, int64_t a)
+{
+    if (a > nS - 1) a = nS - 1;   // (also after a prefix broken by a failed wait)
+    if (a < 0) a = 0;
+    return RowEdges{eoff[a], eoff[a + 1], rowstart[a]};
+}
+__device__ inline RowEdges first_rows(const int64_t *__restrict__ eoff, const int64_t *__restrict__ rowstart, int32_t nS, const ChunkRows &r)
+{
+    return row_edges(eoff, rowstart, nS, (int64_t)r.first + threadIdx.x);
+}
+
+// Fills `m` for the edge positions [c0, c0 + len).  Called by all threads of the block, with its first_rows().  Returns where row
+// r.first + threadIdx.x starts, relative to c0 (the caller's place for that row's pointer).
 template <int TILE>
 __device__ inline int32_t map_edges(EdgeMap<TILE> &m, const int64_t *__restrict__ eoff, const int64_t *__restrict__ rowstart, int32_t nS,
-                                    int64_t c0, int32_t len, ChunkRows &r)
+                                    int64_t c0, int32_t len, ChunkRows &r, RowEdges row)
 {
-    // A prefix broken by a failed wait must not lead outside eoff / rowstart.
-    if (r.first < 0) r.first = 0;
+    if (r.first < 0) r.first = 0;   // (a prefix broken by a failed wait)
     if (r.end > nS) r.end = nS;
     __syncthreads();   // the previous chunk's readers are done
     if (threadIdx.x < EdgeMap<TILE>::WORDS) m.starts[threadIdx.x] = 0ull;
     if (threadIdx.x == 0) m.delta[0] = 0;
-    int32_t mine = INT32_MIN;
-    bool cleared = false;
-    for (int32_t a0 = r.first; a0 < r.end || !cleared; a0 += (int32_t)blockDim.x) {
-        const int32_t a = a0 + (int32_t)threadIdx.x;
-        const bool have = a < r.end;
-        int64_t beg = 0, end = 0, csr = 0;
-        if (have) {
-            beg = eoff[a] - c0;
-            end = eoff[a + 1] - c0;
-            csr = rowstart[a];
-        }
-        if (!cleared) {
-            if (have) mine = (int32_t)(beg < INT32_MIN + 1 ? INT32_MIN + 1 : beg);
-            __syncthreads();
-            cleared = true;
-        }
-        if (have && end > beg && end > 0 && beg < len) {
+    __syncthreads();
+    const int64_t off = row.beg - c0;
+    for (int32_t a = r.first + (int32_t)threadIdx.x; a < r.end;) {
+        const int64_t beg = row.beg - c0, end = row.end - c0;
+        if (end > beg && end > 0 && beg < len) {
             const int32_t p = beg > 0 ? (int32_t)beg : 0;
-            m.delta[p] = csr - beg;
+            m.delta[p] = row.csr - beg;
             atomicOr(&m.starts[p >> 6], 1ull << (p & 63));
         }
+        a += (int32_t)blockDim.x;
+        if (a < r.end) row = row_edges(eoff, rowstart, nS, a);
     }
     __syncthreads();
-    return mine;
+    return off < INT32_MIN ? INT32_MIN : (int32_t)off;
 }
 
 // A lane's view of the words: their bits, and the last start at or before the end of each (lane l: word l).

@@ -15,9 +15,10 @@
 //                  target (one 64-byte piece of the accumulator table) with a plain byte store, so
 //                  that the candidate kernels fetch only touched pieces
 //   cand_partials  sums of what the weight scan left for the local tiles; per tile of 1024 node ids: candidate count, local count, local and remote
-//                  weight sums of the flagged words (unskewed, so they do not depend on s); the
-//                  last tile of each group of 64 adds up its group (it waits for the other
-//                  tiles' flags)
+//                  weight sums of the flagged words (unskewed, so they do not depend on s), and their
+//                  sums per group of 64 tiles
+//   scan_wide, bin_sums   the two for launches with many edges: all edges, remote ones too, are sorted by
+//                  the block that sums their target and handed over; no scattered atomics
 //   cand_emit      per tile: prefix = group sums before my group + tile sums before me in my
 //                  group (plain loads: the producers are earlier kernels); the skew multiplier is
 //                  fixed by the caller, or taken from the grand totals by the rule of Theorem 1
@@ -67,9 +68,18 @@ struct Stage {
     int32_t adjacent;   // 1: a tile's blocks lie side by side (else one block of every tile after the other)
     int32_t n_inst;     // instances of the launch
     int32_t min_chunks; // chunks over all instances from which edges are handed over (0: whatever a chunk holds)
+    int32_t below, bins; // wide form (scan_wide): bins before the local tiles, bins in all
     unsigned long long *part;        // [tiles * max_split * CAND_TILE] sums of all but a tile's last block
     unsigned long long *part_flag;   // [tiles * max_split] tag of the call that left them
+    uint64_t *gtot;     // [gtot_words] sums per group of tiles: the scan clears them for the candidate sums
+    int64_t gtot_words;
 };
+// By the first block of a scan
+__device__ inline void clear_group_sums(const Stage &stg, int64_t ws_stride)
+{
+    uint64_t *__restrict__ g = inst_ptr(stg.gtot, ws_stride);
+    for (int64_t i = threadIdx.x; i < stg.gtot_words; i += blockDim.x) g[i] = 0ull;
+}
 // Local edges that a chunk must have to hand them over (more than EDGE_TILE: no chunk does).  Decided chunk by chunk from
 // what there is, as the rows' degrees and the share of local targets may be anything, whatever the graph's mean and its
 // partition.  What the hand-over saves grows with the local edges (their atomics, 23 G/s); what it costs is the sums' latency and
@@ -135,6 +145,7 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
     const int lane = lane_id();
     const int wave = (int)(threadIdx.x >> 6);
 
+    if (blockIdx.x == 0) clear_group_sums(stg, is.ws);
     if (blockIdx.x == 0 && threadIdx.x == 0 && meta[META_EDGES_TRUE] > edge_cap) atomicOr(status, CSGS_ST_EDGE_OVERFLOW);
     bool bad = false;
     for (int64_t t = blockIdx.x; t < n_chunks; t += gridDim.x) {
@@ -145,7 +156,7 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
             for (int i = threadIdx.x; i < SUB_MAX; i += blockDim.x) hist[i] = 0u;   // (its last readers are a barrier behind)
         const int32_t len = (int32_t)(c1 - c0);
         if (t != blockIdx.x) rows = chunk_rows(bound_note, t, t + 1);
-        (void)map_edges(map, eoff, rowstart, nS, c0, len, rows);   // (starts and ends with a barrier)
+        (void)map_edges(map, eoff, rowstart, nS, c0, len, rows, first_rows(eoff, rowstart, nS, rows));   // (starts and ends with a barrier)
         const EdgeWords words = edge_words(map);
         // All of a thread's edges go through each step together -- their addresses, then their columns and
         // values with unconditional loads (an edge that does not exist reads entry 0 and is dropped) -- so
@@ -244,10 +255,181 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
     if (bad) atomicOr(status, CSGS_ST_BAD_EDGE_VALUE);
 }
 
+// The weight scan of a launch with many edges: every edge is handed over, so that none costs a scattered atomic.  A block sorts
+// WIDE_EDGES edges at a time by the bin of their target -- the ids of one block of the candidate sums: a local tile, or four tiles
+// elsewhere -- by a counting sort in LDS, and writes them out as one run.  The more edges at a time, the longer a bin's group in the run,
+// which the sums read piece by piece.  What an entry does not hold (weights from WIDE_WEIGHTS on), bins outside the
+// local range that take more than WIDE_BIN_MAX of a run (their block would walk alone through what belongs to many), and runs
+// beyond the hand-over array go through the atomics.
+constexpr int WIDE_CHUNKS = 16;                            // chunks of EDGE_TILE edges a run holds
+constexpr int WIDE_EDGES = WIDE_CHUNKS * EDGE_TILE;
+constexpr int WIDE_BLOCK = WIDE_EDGES / 16;                // 16 edges per thread
+constexpr int WIDE_STEP = WIDE_BLOCK * 4;                  // mapped at a time
+constexpr int WIDE_BINS = 4096;
+constexpr int WIDE_STRIDE = WIDE_CHUNKS * SUB_STRIDE;      // entries per run of the groups' begins
+constexpr int WIDE_IDS = CAND_TILE * 4;                    // most ids of a bin
+constexpr unsigned long long WIDE_WEIGHTS = 1ull << 52;
+constexpr uint32_t WIDE_BIN_MAX = WIDE_EDGES / 8;
+static_assert(WIDE_BINS + 1 <= WIDE_STRIDE && WIDE_EDGES <= 0xFFFF && WIDE_STEP / WAVE <= WAVE, "runs of the wide form");
+
+__global__ __launch_bounds__(WIDE_BLOCK) void scan_wide(const int32_t *__restrict__ colidx, const float *__restrict__ val, int64_t n_nodes,
+                                                        int64_t nnz, int32_t shift_base, const int64_t *__restrict__ meta, int64_t edge_cap,
+                                                        const int64_t *__restrict__ eoff, const int64_t *__restrict__ rowstart,
+                                                        uint64_t *__restrict__ wtable, uint8_t *__restrict__ tileflag,
+                                                        const int2 *__restrict__ bound_note, uint64_t *__restrict__ epoch,
+                                                        int32_t *__restrict__ status, Stage stg, InstStride is)
+{
+    constexpr int STEPS = WIDE_EDGES / WIDE_STEP, BINS = WIDE_BINS / WIDE_BLOCK;   // bins per thread
+    __shared__ union {
+        EdgeMap<WIDE_STEP> map;
+        unsigned long long e[WIDE_EDGES];
+    } u;
+    __shared__ uint32_t hist[WIDE_BINS];
+    __shared__ uint32_t s_scan[17];
+    meta = inst_ptr(meta, is.ws); eoff = inst_ptr(eoff, is.ws); rowstart = inst_ptr(rowstart, is.ws);
+    wtable = inst_ptr(wtable, is.ws); tileflag = inst_ptr(tileflag, is.ws); bound_note = inst_ptr(bound_note, is.ws);
+    stg.e = inst_ptr(stg.e, is.ws); stg.off = inst_ptr(stg.off, is.ws);
+    status = inst_ptr(status, is.buf); epoch = inst_ptr(epoch, is.ws);
+    const int32_t nS = (int32_t)meta[META_ROWS];
+    const double scale = ldexp(1.0, shift_for_rows(shift_base, nS));
+    const int64_t E = meta[META_EDGES];
+    const int64_t n_chunks = (E + EDGE_TILE - 1) / EDGE_TILE, n_runs = (E + WIDE_EDGES - 1) / WIDE_EDGES;
+    const int64_t n_staged = stg.chunks / WIDE_CHUNKS;
+    const unsigned long long call = call_number(epoch);
+    const int32_t tile0 = stg.tiles ? stg.lo / CAND_TILE : 0x7FFFFFFF, tile1 = stg.tiles ? tile0 + stg.tiles : 0x7FFFFFFF;
+    const int32_t past = stg.below + stg.tiles - tile1 / 4;   // of a tile past the local ones: its bin minus a quarter of it
+    const int tid = (int)threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    auto add = [&](int32_t c, unsigned long long q) {
+        (void)__hip_atomic_fetch_add((unsigned long long *)&wtable[c], q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        tileflag[c >> 3] = 1;         // same values from every writer
+        epoch[EPOCH_ADDED] = call;
+    };
+    if (blockIdx.x == 0) clear_group_sums(stg, is.ws);
+    if (blockIdx.x == 0 && tid == 0 && meta[META_EDGES_TRUE] > edge_cap) atomicOr(status, CSGS_ST_EDGE_OVERFLOW);
+    bool bad = false;
+    for (int64_t run = blockIdx.x; run < n_runs; run += gridDim.x) {
+        const bool staged = run < n_staged;
+        for (int i = tid; i < stg.bins; i += WIDE_BLOCK) hist[i] = 0u;   // (its last readers are a barrier behind)
+        // Which rows, and where they start, is asked for for all steps at once; columns and values of a step travel while the next one
+        // is mapped.
+        ChunkRows rows[STEPS];
+        RowEdges mine[STEPS];
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) {
+            const int64_t t0 = run * WIDE_CHUNKS + s * (WIDE_STEP / EDGE_TILE), t1 = t0 + WIDE_STEP / EDGE_TILE;
+            rows[s] = t0 < n_chunks ? chunk_rows(bound_note, t0, t1 < n_chunks ? t1 : n_chunks) : ChunkRows{0, 0};
+        }
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) mine[s] = first_rows(eoff, rowstart, nS, rows[s]);
+        int32_t col[STEPS][4];
+        float v[STEPS][4];
+        uint32_t live = 0;
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) {
+            const int64_t c0 = run * WIDE_EDGES + (int64_t)s * WIDE_STEP, left = E - c0;
+            const int32_t len = left <= 0 ? 0 : (left < WIDE_STEP ? (int32_t)left : WIDE_STEP);
+            (void)map_edges(u.map, eoff, rowstart, nS, c0, len, rows[s], mine[s]);
+            const EdgeWords words = edge_words(u.map);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int word = __builtin_amdgcn_readfirstlane(wave * 4 + k);
+                const int64_t a = edge_address(u.map, words, word);
+                const bool have = word * WAVE + lane < len, inside = a >= 0 && a < nnz;   // (outside only after a failed wait in the row pass)
+                if (have && !inside) bad = true;
+                live |= (uint32_t)(have && inside) << (s * 4 + k);
+                const int64_t at = have && inside ? a : 0;
+                col[s][k] = colidx[at];
+                v[s][k] = val[at];
+            }
+        }
+        unsigned long long entry[STEPS][4];
+        uint32_t place[STEPS][4];   // bin << 16 | place inside its group (any order); all ones: nothing to hand over
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int32_t c = col[s][k];
+                const bool here = (live >> (s * 4 + k)) & 1u, sound = isfinite(v[s][k]) && c >= 0 && c < n_nodes;
+                if (here && !sound) bad = true;
+                place[s][k] = ~0u;
+                entry[s][k] = 0ull;
+                if (!here || !sound) continue;
+                const unsigned long long q = edge_weight(v[s][k], scale);
+                if (!staged || q >= WIDE_WEIGHTS) {
+                    add(c, q);
+                    continue;
+                }
+                const int32_t t = c / CAND_TILE;
+                const int32_t b = t < tile0 ? t >> 2 : (t < tile1 ? stg.below + (t - tile0) : (t >> 2) + past);   // < stg.bins
+                entry[s][k] = q * WIDE_IDS + (unsigned)(c % WIDE_IDS);
+                place[s][k] = (uint32_t)b << 16 | atomicAdd(&hist[b], 1u);
+            }
+        }
+        if (staged) {
+            __syncthreads();
+            // counts -> begin of every group; a bin with too many keeps an empty group and the top bit
+            uint32_t cnt[BINS], sum = 0;
+            bool heavy[BINS];
+#pragma unroll
+            for (int i = 0; i < BINS; ++i) {
+                const int b = tid * BINS + i;
+                const uint32_t n = b < stg.bins ? hist[b] : 0u;
+                heavy[i] = n > WIDE_BIN_MAX && (b < stg.below || b >= stg.below + stg.tiles);
+                cnt[i] = heavy[i] ? 0u : n;
+                sum += cnt[i];
+            }
+            uint32_t n_handed;
+            uint32_t ex = block_exclusive_scan<uint32_t>(sum, s_scan, &n_handed);
+#pragma unroll
+            for (int i = 0; i < BINS; ++i) {
+                const int b = tid * BINS + i;
+                if (b < stg.bins) {
+                    hist[b] = ex | (heavy[i] ? 0x80000000u : 0u);
+                    stg.off[run * WIDE_STRIDE + b] = (uint16_t)ex;
+                }
+                ex += cnt[i];
+            }
+            if (tid == 0) {
+                stg.off[run * WIDE_STRIDE + stg.bins] = (uint16_t)n_handed;
+                if (n_handed) epoch[EPOCH_HANDED] = call;   // same value from every writer
+            }
+            __syncthreads();
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if (place[s][k] == ~0u) continue;
+                    const int32_t b = (int32_t)(place[s][k] >> 16);
+                    const uint32_t begin = hist[b];
+                    if (begin >> 31) {   // (not a local bin)
+                        const int32_t first = (b < stg.below ? b : b - past) * WIDE_IDS;
+                        add(first + (int32_t)(entry[s][k] % WIDE_IDS), entry[s][k] / WIDE_IDS);
+                    } else {
+                        u.e[begin + (place[s][k] & 0xFFFFu)] = entry[s][k];   // < WIDE_EDGES: the groups partition what is handed over
+                    }
+                }
+            }
+            __syncthreads();
+            uint64_t *__restrict__ out = stg.e + run * WIDE_EDGES;
+            for (uint32_t i = tid * 2u; i < n_handed; i += WIDE_BLOCK * 2u)
+                *reinterpret_cast<ulonglong2 *>(&out[i]) = *reinterpret_cast<const ulonglong2 *>(&u.e[i]);   // (one past an odd end: inside the run)
+        }
+        __syncthreads();   // hist is cleared next
+    }
+    if (bad) atomicOr(status, CSGS_ST_BAD_EDGE_VALUE);
+}
+
 // Below this many chunks over all instances of a launch the atomics hide in the scan's latency (us for scan + candidate sums,
 // atomics / hand-over, four edges in five local: 75 chunks 18 / 19, 426 chunks 36 / 24, 1004 chunks 56 / 33; one in two: 200
 // chunks 20 / 21, 400 chunks 30 / 27; one in eight: 200 chunks 21 / 24, 800 chunks 50 / 53; one in 64: 800 chunks 50 / 68).
 constexpr int32_t HAND_OVER_MIN_CHUNKS = 160;
+// The wide form costs a sort of every edge and saves the scattered atomics and the sums' short reads (us of csgs_build_probs in the narrow / wide form; 2.4 M
+// nodes, 150 local tiles: 1664 chunks 64 / 67, 2496 chunks 74 / 69, eight instances of 208 chunks 95 / 88, of 312 chunks 105 / 93, of 372 chunks 124 / 90, one of 6.6 K
+// chunks 139 / 96; 200 K nodes: eight of 197 chunks 57 / 66, of 394 chunks 75 / 70).  Where the local range is too wide for the narrow form's hand-over, which then
+// sends every edge through atomics, it pays much earlier (2 M nodes, 489 local tiles: 605 chunks 60 / 59, 1210 chunks 87 / 70, 3632 chunks 198 / 101).  With
+// few bins their blocks leave compute units idle (30 K nodes, eight of 394 chunks: 73 / 82).
+constexpr int64_t WIDE_MIN_CHUNKS = 2400, WIDE_MIN_CHUNKS_NARROW_OFF = 700;   // expected, over all instances
+constexpr int64_t WIDE_MIN_BINS = 256;                                        // outside the local range, over all instances
 // A tile's sums are split over several blocks while each block has this many edges left and the launch has SPLIT_BLOCKS
 // of them at most, two per compute unit: a narrow local range has few tiles (29 tiles, 1 M edges: 31 us with a block
 // per tile, 16 split by 7), and 150 tiles leave compute units idle (5.4 M edges: 49 / 40 us).  Shares below that only
@@ -286,10 +468,7 @@ __device__ inline void resolve_skew(const SkewPolicy &pol, uint64_t n_cand, uint
 
 constexpr int CAND_WORDS = CAND_TILE / WAVE;  // 16 words per tile, 4 per wave
 
-// Tile sums, and -- by the last tile of every group of 64 -- the group's sums.  That tile waits
-// for the flags of the (at most 63) lower tiles of its group, which were dispatched before it
-// (ascending block ids) or belong to its own block and are published before the wait, and which
-// wait for nobody, so the wait ends.  Two kinds of blocks:
+// Tile sums and the sums of every group of 64 tiles.  Two kinds of blocks:
 //  * a block of TILES tiles asks for the flags of all their words, then for their pieces of the table: two load latencies.
 //  * where the weight scan may hand local edges over, every tile that meets the local range has blocks of its own.  If it
 //    has done so, they first add up in LDS what the chunks left for the tile (64 chunks at a time per wavefront, one per
@@ -359,6 +538,17 @@ __device__ inline void sum_handed_over(unsigned long long *acc, const Stage &stg
     __syncthreads();
 }
 
+// Lane i < 3 of a wavefront holds sum i of tile t in `mine`: left for cand_emit, and added to the sums of its group of 64 tiles, which the weight scan
+// has cleared.  Nobody waits (with a last tile that waited for the others' flags and added them up: 59 against 55 us for an earlier bin_sums over eight instances,
+// 1 % of the smallest step).
+__device__ inline void publish_tile(int64_t t, unsigned long long mine, unsigned long long *__restrict__ partial, uint64_t *__restrict__ gtot)
+{
+    const int lane = lane_id();
+    if (lane >= 3) return;
+    partial[t * 4 + lane] = mine;
+    if (mine) (void)__hip_atomic_fetch_add((unsigned long long *)&gtot[t / LB_GROUP * 4 + lane], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // PACK: the tiles are also put into the form that the packing kind of cand_emit reads, each tile's weights side by side at the start of its piece
 // of the table and a bit per id in place of the groups' flags.
 template <int TILES, bool PACK>
@@ -366,7 +556,7 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, PACK ? 8 : 1) void cand_partials(u
                                                      uint8_t *__restrict__ tileflag, int64_t n_words,
                                                      int64_t n_nodes, int64_t n_tiles, int32_t lo, int32_t hi,
                                                      const int64_t *__restrict__ meta, Stage stg,
-                                                     int32_t blocks_below, const uint64_t *__restrict__ epoch, unsigned long long *__restrict__ cand_flag,
+                                                     int32_t blocks_below, const uint64_t *__restrict__ epoch,
                                                      unsigned long long *__restrict__ partial,
                                                      uint64_t *__restrict__ gtot, int32_t *__restrict__ status, InstStride is)
 {
@@ -375,7 +565,7 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, PACK ? 8 : 1) void cand_partials(u
     __shared__ unsigned long long acc[CAND_TILE];
     __shared__ __attribute__((aligned(8))) uint8_t s_bits[PACK ? WAVES : 1][W * 8];   // a wavefront's groups: a bit per id
     wtable = inst_ptr(wtable, is.ws); tileflag = inst_ptr(tileflag, is.ws); epoch = inst_ptr(epoch, is.ws);
-    cand_flag = inst_ptr(cand_flag, is.ws); partial = inst_ptr(partial, is.ws); gtot = inst_ptr(gtot, is.ws);
+    partial = inst_ptr(partial, is.ws); gtot = inst_ptr(gtot, is.ws);
     status = inst_ptr(status, is.buf); meta = inst_ptr(meta, is.ws);
     stg.e = inst_ptr(stg.e, is.ws); stg.off = inst_ptr(stg.off, is.ws);
     stg.part = inst_ptr(stg.part, is.ws); stg.part_flag = inst_ptr(stg.part_flag, is.ws);
@@ -536,24 +726,7 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, PACK ? 8 : 1) void cand_partials(u
         unsigned long long mine = 0ull;
         if (lane < 3)
             for (int i = 0; i < waves_per_tile; ++i) mine += lds[w0 + i][lane];
-        if (lane < 3) st_relaxed(&partial[t * 4 + lane], mine);
-        if (lane == 0) st_flag(&cand_flag[t], tag);   // after the wavefront's value stores have been acknowledged
-        // A wavefront waits only for tiles below its own, and every tile's wavefront publishes before it waits.
-        const int r = (int)(t % LB_GROUP);
-        if (!PACK && r != LB_GROUP - 1 && t != n_tiles - 1) return;
-        if (r == LB_GROUP - 1 || t == n_tiles - 1) {
-            const int64_t g = t / LB_GROUP;
-            bool ok = true;
-            if (lane < r) ok = wait_tag(&cand_flag[g * LB_GROUP + lane], tag, wait_limit(epoch));
-            unsigned long long sum[3];
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const unsigned long long own_sum = __shfl(mine, i, WAVE);
-                sum[i] = own_sum + wave_sum((lane < r && ok) ? ld_relaxed(&partial[(g * LB_GROUP + lane) * 4 + i]) : 0ull);
-            }
-            if (__ballot(!ok) && lane == 0) atomicOr(status, CSGS_ST_INTERNAL);
-            if (lane < 3) gtot[g * 4 + lane] = lane == 0 ? sum[0] : (lane == 1 ? sum[1] : sum[2]);
-        }
+        publish_tile(t, mine, partial, gtot);
     }
     if (!PACK || !in_block) return;
     // All of the tile's loads lie before the barrier above, and every entry of the table is written once: up to n_t by the weight
@@ -579,6 +752,201 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, PACK ? 8 : 1) void cand_partials(u
     }
     if (lane < w_used && word0 + lane < n_words)
         reinterpret_cast<uint64_t *>(tileflag)[word0 + lane] = *reinterpret_cast<const uint64_t *>(&s_bits[PACK ? wave : 0][lane * 8]);
+}
+
+// The candidate sums after scan_wide, packed like cand_partials' packing kind: a block per bin (several for a local tile with many edges), whose groups
+// it adds up in LDS, 64 runs at a time per wavefront, one per lane.  Bound by the latency of its loads -- where the groups lie, then
+// the entries -- and by how many blocks a compute unit holds, so the first are asked for before anything else is known; before that, by vector
+// instructions: 55 us for eight instances of 380 K edges with all eight wavefronts looking at every id, 41 with a bit per touched id.  (cand_partials
+// after the narrow scan: 52; with the scan, 47 and 25.)
+__global__ __launch_bounds__(CAND_PART_BLOCK, 8) void bin_sums(uint64_t *__restrict__ wtable, uint8_t *__restrict__ tileflag, int64_t n_words, int64_t n_nodes,
+                                                               int64_t n_tiles, int32_t lo, int32_t hi, const int64_t *__restrict__ meta, Stage stg,
+                                                               const uint64_t *__restrict__ epoch, unsigned long long *__restrict__ partial, uint64_t *__restrict__ gtot,
+                                                               int32_t *__restrict__ status, InstStride is)
+{
+    constexpr int WAVES = CAND_PART_BLOCK / WAVE, U = 4;   // entries on their way per lane
+    __shared__ unsigned long long acc[WIDE_IDS];
+    __shared__ __attribute__((aligned(8))) uint32_t s_bits[WIDE_IDS / 32];   // ids with a weight
+    __shared__ uint64_t lds[WAVES][3];
+    wtable = inst_ptr(wtable, is.ws); tileflag = inst_ptr(tileflag, is.ws); epoch = inst_ptr(epoch, is.ws);
+    partial = inst_ptr(partial, is.ws); gtot = inst_ptr(gtot, is.ws);
+    status = inst_ptr(status, is.buf); meta = inst_ptr(meta, is.ws);
+    stg.e = inst_ptr(stg.e, is.ws); stg.off = inst_ptr(stg.off, is.ws);
+    stg.part = inst_ptr(stg.part, is.ws); stg.part_flag = inst_ptr(stg.part_flag, is.ws);
+    const int tid = (int)threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    // blocks in the order of their bins, max_split for each of the local tiles (see cand_partials)
+    const int32_t own_blocks = stg.tiles * stg.max_split;
+    const int32_t b = (int32_t)blockIdx.x - stg.below;
+    const bool own = b >= 0 && b < own_blocks;
+    const uint32_t per_step = stg.adjacent ? (uint32_t)stg.max_split : (uint32_t)stg.tiles;
+    const uint32_t step_own = own ? (uint32_t)b / per_step : 0u, rest_own = own ? (uint32_t)b % per_step : 0u;
+    const uint32_t tile_own = stg.adjacent ? step_own : rest_own, round_own = stg.adjacent ? rest_own : step_own;
+    const int32_t bin = b < 0 ? (int32_t)blockIdx.x : (own ? stg.below + (int32_t)tile_own : stg.below + stg.tiles + (b - own_blocks));
+    const int64_t most = stg.chunks / WIDE_CHUNKS;   // runs that the hand-over array holds, at least one
+    const uint16_t *__restrict__ off = stg.off + bin;
+    uint32_t beg, end;
+    auto extents = [&](int64_t run) {   // where the bin's group lies in a run
+        const uint16_t *p = off + (run < most ? run : 0) * WIDE_STRIDE;
+        beg = p[0];
+        end = p[1];
+    };
+    // share s takes the runs s, s + split, ...; of those, the first `readers` wavefronts one after the other (a bin's groups are
+    // short: where there are few runs, fewer wavefronts have fewer instructions to issue)
+    int readers = own ? WAVES : CAND_PART_TILES;
+    extents(lane * readers + wave);
+    const unsigned long long call = call_number(epoch), tag = call_tag(call, SLOT_CAND);
+    int64_t n_runs = 0;
+    if (epoch[EPOCH_HANDED] == call) {
+        n_runs = (meta[META_EDGES] + WIDE_EDGES - 1) / WIDE_EDGES;
+        if (n_runs > most) n_runs = most;
+    }
+    const bool table = epoch[EPOCH_ADDED] == call;   // something went through the table of accumulators
+    const int64_t tile0 = stg.lo / CAND_TILE, local_end = tile0 + stg.tiles;
+    int64_t t0, t1;
+    if (b < 0) {
+        t0 = (int64_t)blockIdx.x * CAND_PART_TILES;
+        t1 = t0 + CAND_PART_TILES;
+        if (stg.tiles > 0 && t1 > tile0) t1 = tile0;
+    } else if (own) {
+        t0 = tile0 + tile_own;
+        t1 = t0 + 1;
+    } else {
+        t0 = (local_end / CAND_PART_TILES + (b - own_blocks)) * CAND_PART_TILES;
+        t1 = t0 + CAND_PART_TILES;
+        if (t0 < local_end) t0 = local_end;
+    }
+    if (t1 > n_tiles) t1 = n_tiles;
+    // the last `split` of a local tile's blocks share its sums, the others leave
+    uint32_t split = 1;
+    if (own && n_runs) {
+        const int64_t want = n_runs * (WIDE_CHUNKS * EDGE_TILE / SPLIT_MIN_EDGES) / stg.tiles;
+        split = (uint32_t)(want < n_runs ? want : n_runs);
+        if (split > (uint32_t)stg.max_split) split = (uint32_t)stg.max_split;
+        if (split < 1u) split = 1u;
+    }
+    const int share = own ? (int)round_own - (stg.max_split - (int)split) : 0;
+    if (t0 >= t1 || share < 0) return;   // the whole block
+    const uint32_t ids = own ? CAND_TILE : WIDE_IDS;
+    for (uint32_t i = tid; i < ids; i += CAND_PART_BLOCK) acc[i] = 0ull;
+    for (uint32_t i = tid; i < ids / 32; i += CAND_PART_BLOCK) s_bits[i] = 0u;
+    __syncthreads();
+    const bool sparse = !own && n_runs <= CAND_PART_TILES * WAVE;   // few entries: their bits are set one by one, else from the sums
+    if (split > 1 || (!own && !sparse)) {
+        readers = WAVES;
+        extents((int64_t)(lane * readers + wave) * split + share);
+    }
+    for (int64_t r0 = 0; r0 * split + share < n_runs && wave < readers; r0 += readers * WAVE) {
+        const int64_t run = (r0 + lane * readers + wave) * split + share;
+        // entry j of the sequence belongs to the first lane whose running count exceeds j
+        const int32_t n = run < n_runs && beg <= end && end <= WIDE_EDGES ? (int32_t)(end - beg) : 0;
+        const int32_t incl = wave_inclusive_scan<int32_t>(n);
+        const int32_t total = __builtin_amdgcn_readlane(incl, WAVE - 1);
+        const int32_t first = (int32_t)(run * WIDE_EDGES) + (int32_t)beg - (incl - n);   // it is entry first + j (at most STAGE_EDGES_MAX)
+        extents((r0 + readers * WAVE + lane * readers + wave) * split + share);
+        auto entry = [&](int32_t j) {
+            int lo_l = 0, hi_l = WAVE - 1;
+#pragma unroll
+            for (int it = 0; it < 6; ++it) {
+                const int mid = (lo_l + hi_l) >> 1;
+                if (__shfl(incl, mid, WAVE) > j) hi_l = mid; else lo_l = mid + 1;
+            }
+            const int32_t pos = __shfl(first, lo_l, WAVE) + j;
+            return stg.e[j < total ? pos : 0];   // (unconditional; entry 0 stands in past the end)
+        };
+        auto take = [&](int32_t j, uint64_t v) {
+            if (j >= total) return;
+            const uint32_t at = (uint32_t)v & (ids - 1u);
+            atomicAdd(&acc[at], (unsigned long long)(v / WIDE_IDS));
+            if (sparse) atomicOr(&s_bits[at >> 5], 1u << (at & 31));
+        };
+        for (int32_t j0 = 0; j0 < total; j0 += U * WAVE) {
+            if (total - j0 <= WAVE) {
+                take(j0 + lane, entry(j0 + lane));
+                break;
+            }
+            uint64_t v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = entry(j0 + u * WAVE + lane);
+#pragma unroll
+            for (int u = 0; u < U; ++u) take(j0 + u * WAVE + lane, v[u]);
+        }
+    }
+    __syncthreads();
+    if (own && share != (int)split - 1) {   // left for the block of the last share
+        for (int i = tid; i < CAND_TILE; i += CAND_PART_BLOCK) st_relaxed(&stg.part[(int64_t)b * CAND_TILE + i], acc[i]);
+        wait_memory_ops();
+        __syncthreads();
+        if (tid == 0) st_relaxed(&stg.part_flag[b], tag);
+        return;
+    }
+    if (split > 1) {   // (the other shares' blocks were dispatched before and wait for nobody)
+        const int64_t next = stg.adjacent ? 1 : stg.tiles, first = b - share * next;
+        bool ok = true;
+        if (tid < share) ok = wait_tag(&stg.part_flag[first + tid * next], tag, wait_limit(epoch));
+        if (!ok) atomicOr(status, CSGS_ST_INTERNAL);
+        __syncthreads();
+        for (int i = tid; i < CAND_TILE; i += CAND_PART_BLOCK) {
+            unsigned long long v = acc[i];
+            for (int k = 0; k < share; ++k) v += ld_relaxed(&stg.part[(first + k * next) * CAND_TILE + i]);
+            acc[i] = v;
+        }
+        __syncthreads();
+    }
+    if (!sparse) {
+        for (uint32_t i = tid; i < ids; i += CAND_PART_BLOCK) {
+            const uint64_t word = __ballot(acc[i] != 0);
+            if (lane == 0) reinterpret_cast<uint64_t *>(s_bits)[i >> 6] = word;
+        }
+        __syncthreads();
+    }
+    if (table) {   // what came through the table joins the sums, and the table is clean
+        for (uint32_t i = tid; i < ids; i += CAND_PART_BLOCK) {
+            const int64_t id = (own ? t0 : t0 / CAND_PART_TILES * CAND_PART_TILES) * CAND_TILE + i;
+            if (id < t0 * CAND_TILE || id >= t1 * CAND_TILE || id >= n_nodes || !tileflag[id >> 3]) continue;
+            const uint64_t more = wtable[id];
+            if (!more) continue;
+            wtable[id] = 0ull;
+            acc[i] += more;
+            atomicOr(&s_bits[i >> 5], 1u << (i & 31));
+        }
+        __syncthreads();
+    }
+    // Lane l looks at 16 ids of the wavefront's tile; a local tile is shared by all wavefronts, eight lanes' ids each.  The tile's weights go side by
+    // side to the start of its piece of the table, and a bit per id in place of the groups' flags.
+    if (!own && wave >= CAND_PART_TILES) return;
+    const int64_t tile = own ? t0 : t0 / CAND_PART_TILES * CAND_PART_TILES + wave;
+    if (tile < t0 || tile >= t1) return;   // (the whole wavefront; of a local tile, none)
+    const uint32_t base = own ? 0u : (uint32_t)wave * CAND_TILE, tile_id = (uint32_t)tile * CAND_TILE;   // (ids: below 2^31 + 1024)
+    const uint32_t piece = reinterpret_cast<const uint16_t *>(s_bits)[base / 16 + lane];
+    const uint32_t cnt = (uint32_t)__popc(piece), incl = wave_inclusive_scan<uint32_t>(cnt), n_t = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1);
+    const bool mine = !own || lane >> 3 == wave;
+    const int64_t at16 = (int64_t)tile_id / 16 + lane;
+    if (mine && at16 < n_words * 4 && (piece || table)) reinterpret_cast<uint16_t *>(tileflag)[at16] = (uint16_t)piece;
+    const uint32_t id0 = tile_id + lane * 16;
+    uint32_t put = tile_id + incl - cnt, n_local = 0;
+    uint64_t wl = 0, wa = 0;
+    for (uint32_t bits = mine ? piece : 0u; bits; bits &= bits - 1u) {
+        const uint32_t k = (uint32_t)__ffs((int)bits) - 1u;
+        const uint64_t v = acc[base + lane * 16 + k];
+        wtable[put++] = v;
+        const bool local = (int64_t)(id0 + k) >= lo && (int64_t)(id0 + k) < hi;
+        wa += v;
+        wl += local ? v : 0ull;
+        n_local += local ? 1u : 0u;
+    }
+    wl = wave_sum(wl); wa = wave_sum(wa);
+    n_local = wave_sum(n_local);
+    if (own) {
+        if (lane == 0) { lds[wave][0] = n_local; lds[wave][1] = wl; lds[wave][2] = wa - wl; }
+        __syncthreads();   // (all wavefronts of a local tile's block come here)
+        if (wave) return;
+    }
+    unsigned long long sum = lane == 0 ? (uint64_t)n_t << 32 | (own ? 0u : n_local) : (lane == 1 ? wl : wa - wl);
+    if (own && lane < 3) {
+        sum = lane == 0 ? (uint64_t)n_t << 32 : 0ull;
+        for (int i = 0; i < WAVES; ++i) sum += lds[i][lane];
+    }
+    publish_tile(tile, sum, partial, gtot);
 }
 
 // Two kinds.  With PACKED a block takes four tiles that cand_partials has packed: where there are many tiles (several instances) the kernel is bound by
@@ -970,22 +1338,39 @@ static int build_probs_impl(const csgs_graph *g, const int32_t *S, int32_t nS, c
         if (split > WAVE) split = WAVE;
         if (split < 1) split = 1;
     }
-    const Stage stg{w.stage, w.stage_off, w.stage_chunks, range_ok ? g->local_lo : 0, range_ok ? g->local_hi : 0, tiles, (int32_t)split,
-                    adjacent ? 1 : 0, w.n_inst, min_chunks, (unsigned long long *)w.split_sum, (unsigned long long *)w.split_flag};
-    CSGS_LAUNCH(K_SCAN_EDGES, scan_edges, dim3((unsigned)chunks, 1, nz), dim3(256), st, g->colidx, g->val,
-                g->n_nodes, g->nnz, shift_base, rows.meta, w.chunk_cap * EDGE_TILE, rows.eoff, rows.rowstart, w.wtable,
-                w.tileflag, rows.bound_note, w.epoch, status, stg, is);
-    CSGS_LAUNCH_CHECK();
     const int64_t per = w.n_inst == 1 && w.n_tiles <= CAND_PART_ONE ? 1 : CAND_PART_TILES;
     const int64_t below = tiles ? (tile0 + per - 1) / per : 0;
-    const int64_t part_blocks = tiles ? below + tiles * split + (w.n_tiles + per - 1) / per - tile1 / per : (w.n_tiles + per - 1) / per;
+    const int64_t rest = tiles ? (w.n_tiles + per - 1) / per - tile1 / per : (w.n_tiles + per - 1) / per;   // blocks of `per` tiles past the local ones
+    const int64_t part_blocks = below + tiles * split + rest;
+    const bool wide = ws->scan_mode == 0 && per == CAND_PART_TILES && w.stage_chunks >= WIDE_CHUNKS && below + tiles + rest <= WIDE_BINS &&
+                      (below + rest) * w.n_inst >= WIDE_MIN_BINS &&
+                      fmin(mean, (double)w.chunk_cap) * w.n_inst >= (double)(tiles ? WIDE_MIN_CHUNKS : WIDE_MIN_CHUNKS_NARROW_OFF);
+    const Stage stg{w.stage, w.stage_off, w.stage_chunks, range_ok ? g->local_lo : 0, range_ok ? g->local_hi : 0, tiles, (int32_t)split,
+                    adjacent ? 1 : 0, w.n_inst, min_chunks, (int32_t)(tiles ? below : rest), (int32_t)(below + tiles + rest), (unsigned long long *)w.split_sum, (unsigned long long *)w.split_flag,
+                    w.gtot, (w.n_tiles + 63) / 64 * 4};
+    if (wide) {
+        int64_t runs = (int64_t)(guess < 1e9 ? guess : 1e9) / WIDE_CHUNKS + 1;
+        if (runs < 256 && w.n_inst == 1) runs = 256;
+        if (runs > SCAN_GRID / 4) runs = SCAN_GRID / 4;
+        if (runs > (w.chunk_cap + WIDE_CHUNKS - 1) / WIDE_CHUNKS) runs = (w.chunk_cap + WIDE_CHUNKS - 1) / WIDE_CHUNKS;
+        CSGS_LAUNCH(K_SCAN_EDGES, scan_wide, dim3((unsigned)runs, 1, nz), dim3(WIDE_BLOCK), st, g->colidx, g->val, g->n_nodes, g->nnz, shift_base,
+                    rows.meta, w.chunk_cap * EDGE_TILE, rows.eoff, rows.rowstart, w.wtable, w.tileflag, rows.bound_note, w.epoch, status, stg, is);
+    } else {
+        CSGS_LAUNCH(K_SCAN_EDGES, scan_edges, dim3((unsigned)chunks, 1, nz), dim3(256), st, g->colidx, g->val,
+                    g->n_nodes, g->nnz, shift_base, rows.meta, w.chunk_cap * EDGE_TILE, rows.eoff, rows.rowstart, w.wtable,
+                    w.tileflag, rows.bound_note, w.epoch, status, stg, is);
+    }
+    CSGS_LAUNCH_CHECK();
     const dim3 part_grid((unsigned)part_blocks, 1, nz);
 #define CSGS_CAND_PARTIALS(TILES, PACK)                                                                                                       \
     CSGS_LAUNCH(K_CAND_PARTIALS, (cand_partials<TILES, PACK>), part_grid, dim3(CAND_PART_BLOCK), st, w.wtable, w.tileflag, n_words, g->n_nodes, \
                 w.n_tiles, g->local_lo, g->local_hi, rows.meta, stg, (int32_t)(tiles ? below : part_blocks), w.epoch,                   \
-                (unsigned long long *)w.cand_flag, (unsigned long long *)w.partial, w.gtot, status, is)
-    const bool packed = w.n_tiles * w.n_inst >= CAND_PACKED_FROM;   // (then `per` is CAND_PART_TILES)
-    if (packed) CSGS_CAND_PARTIALS(CAND_PART_TILES, true);
+                (unsigned long long *)w.partial, w.gtot, status, is)
+    const bool packed = wide || w.n_tiles * w.n_inst >= CAND_PACKED_FROM;   // (then `per` is CAND_PART_TILES)
+    if (wide)
+        CSGS_LAUNCH(K_CAND_PARTIALS, bin_sums, part_grid, dim3(CAND_PART_BLOCK), st, w.wtable, w.tileflag, n_words, g->n_nodes, w.n_tiles, g->local_lo,
+                    g->local_hi, rows.meta, stg, w.epoch, (unsigned long long *)w.partial, w.gtot, status, is);
+    else if (packed) CSGS_CAND_PARTIALS(CAND_PART_TILES, true);
     else if (per == 1) CSGS_CAND_PARTIALS(1, false);
     else CSGS_CAND_PARTIALS(CAND_PART_TILES, false);
 #undef CSGS_CAND_PARTIALS

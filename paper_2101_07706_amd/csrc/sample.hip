@@ -415,7 +415,7 @@ __device__ inline int32_t adj_chunk(AdjChunk &s, const AdjGraph &g, int32_t nS, 
     const int lane = lane_id();
     const int wave = (int)(threadIdx.x >> 6);
     const int32_t len = (int32_t)(c1 - c0);
-    const int32_t starts = map_edges(s.map, g.eoff, g.rowstart, nS, c0, len, rows);
+    const int32_t starts = map_edges(s.map, g.eoff, g.rowstart, nS, c0, len, rows, first_rows(g.eoff, g.rowstart, nS, rows));
     const EdgeWords words = edge_words(s.map);
     // A lane's four edges go through each step together, and no load sits under a condition (an edge that does
     // not exist reads entry 0 and is dropped): the four columns travel at the same time, then the four table
@@ -805,7 +805,7 @@ extern "C" int csgs_draw_nodes(int64_t n_nodes, const int32_t *cand_id, const ui
     const int64_t hit_blocks = (cap_words + HIT_MIN_WORDS - 1) / HIT_MIN_WORDS;
     CSGS_LAUNCH(K_HITS, hits, dim3((unsigned)(hit_blocks < HIT_GRID ? hit_blocks : HIT_GRID), 1, nz), dim3(256), st, cand_id,
                 cdf, stats, cand_cap, n_nodes, B, w.epoch, w.hit, w.cbitmap[0], w.cbitmap[1], w.rank, w.member, S_next, mult, p_incl,
-                w.pdbl, n_next, w.cand_flag, status, is);
+                w.pdbl, n_next, w.hit_ts, status, is);
     CSGS_LAUNCH_CHECK();
     ws->has_draw = 1;
     ws->draw_B = B;

@@ -539,3 +539,42 @@ def test_odd_widths_by_rows(dev, n, F):
             torch.cuda.synchronize()
             chain.assert_close(Z[:, late:late + F].cpu().numpy(), want, chain.RTOL, chain.ATOL, "Z")
             assert bool(torch.isnan(Z[:, :late]).all()) and bool(torch.isnan(Z[:, late + F:]).all()), "wrote beside a row"
+
+
+# The weight scan of many edges: every edge sorted by the block that sums its target.  Local ranges at the start, in the middle (bins of fewer than four
+# tiles before and behind it), in the last partial tile, and too wide to have blocks of their own; a remote piece of 4096 ids that takes all remote edges (its
+# runs go through the atomics); rows whose count only the device knows, few enough that an edge's weight does not fit an entry.
+@pytest.mark.parametrize("n,lo,hi,n_rows,degree,remote_ids,count", [(300_001, 0, 37_500, 9000, 41, None, None), (300_001, 150_700, 190_001, 9000, 41, None, None),
+                                                                     (299_900, 270_000, 299_900, 9000, 41, None, None), (400_000, 10, 390_000, 9000, 41, None, None),
+                                                                     (300_001, 0, 37_500, 9000, 41, (204_800, 208_896), None), (300_001, 0, 37_500, 9000, 41, None, 5)])
+def test_weight_scan_of_many_edges(dev, n, lo, hi, n_rows, degree, remote_ids, count):
+    from paper_2101_07706_amd import csgs, pipeline
+    rng = np.random.default_rng(n + lo)
+    K = 8
+    remote = np.setdiff1d(np.arange(n), np.arange(lo, hi)) if remote_ids is None else np.arange(*remote_ids)
+    col = np.where(rng.random((n, degree)) < 0.7, rng.integers(lo, hi, (n, degree)), remote[rng.integers(0, len(remote), (n, degree))]).astype(np.int32)
+    col.sort(axis=1)
+    val = rng.random((n, degree)).astype(np.float32) / degree
+    if count is not None:
+        val[:] = np.eye(1, degree, dtype=np.float32)   # 1, 0, 0, ...
+    g = synth.Graph(n, np.arange(n + 1, dtype=np.int64) * degree, col.reshape(-1), val.reshape(-1), np.array([0, lo, hi, n], np.int32) if lo else np.array([0, hi, n], np.int32),
+                    1 if lo else 0, 1.0)
+    assert (g.local_lo, g.local_hi) == (lo, hi)
+    dg = pipeline.DeviceGraph(g, dev)
+    lb = pipeline.LayerBuffers(n_rows, 1, n, 1, dg.n_parts, dev, n_inst=K)
+    ws = pipeline.Workspace(n, n_rows, 1, g.nnz, dev, n_inst=K, inst_stride=lb.stride)
+    S = [np.sort(rng.choice(n, n_rows, replace=False)).astype(np.int32) for _ in range(K)]
+    for k in range(K):
+        lb.inst(k).S0.copy_(torch.from_numpy(S[k]).to(dev))
+        lb.inst(k).n_next.fill_(n_rows if count is None else count)
+    for again in range(2):   # the second call finds the workspace as the first has left it
+        csgs.csgs_build_probs(dg.c, lb.S0[:n_rows], 4.0, lb.cand_id, lb.cand_w, lb.cdf, lb.q, lb.stats, ws.desc, lb.status, nS_dev=None if count is None else lb.n_next)
+        torch.cuda.synchronize()
+        for k in (0, 3, K - 1):
+            want, b = oracle.build_probs(g, S[k] if count is None else S[k][:count], 4.0), lb.inst(k)
+            n_c = len(want.cand_id)
+            assert int(b.status.item()) == 0 and b.stats_host().n_cand == n_c and b.stats_host().n_local == int(((want.cand_id >= lo) & (want.cand_id < hi)).sum())
+            np.testing.assert_array_equal(b.cand_id[:n_c].cpu().numpy(), want.cand_id)
+            np.testing.assert_array_equal(b.cand_w[:n_c].cpu().numpy().view(np.uint64), want.cand_w)
+            np.testing.assert_array_equal(b.cdf[:n_c].cpu().numpy().view(np.uint64), want.cdf)
+    assert int(torch.count_nonzero(ws.buf.view(K, -1)[:, :csgs.csgs_workspace_clean_bytes(n) // 8]).item()) == 0
