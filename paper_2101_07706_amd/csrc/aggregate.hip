@@ -405,6 +405,171 @@ __global__ __launch_bounds__(256) void adjT_order(const int32_t *__restrict__ co
     }
 }
 
+// The same in one launch for few entries: a block owns consecutive columns and looks at the columns of all entries itself (4 bytes each, from the
+// L2s), so that nothing has to be cleared, counted with atomics or waited for between launches.  It keeps its columns' entries in LDS,
+// an entry's place being the number of earlier entries of its column (entries of a row ascend, so earlier ones have smaller rows), and
+// finds an entry's row in the row pointers.  Where a block's entries do not fit, it takes the entries LIST at a time.
+// (us, five launches / this: 4096 rows of 6.2 K entries 16 / 7, 8192 rows of 21 K entries with columns of up to 306 27 / 15; reading a column's entries one
+// after the other for the places made that 25.)
+constexpr int ONE_BLOCK = 1024, ONE_GRID = 256, ONE_LIST = 8192;
+constexpr int64_t ONE_ENTRIES = 1ll << 19;   // most (the caller's bound): every block reads them all
+constexpr int32_t ONE_COLS = 65536;          // most columns
+constexpr int ONE_OWN = ONE_COLS / ONE_GRID;
+static_assert(ONE_OWN <= 4 * WAVE, "columns of a block: four per lane");
+
+__global__ __launch_bounds__(ONE_BLOCK) void adjT_one(const int32_t *__restrict__ adj_rowptr, const int32_t *__restrict__ adj_col,
+                                                      const float *__restrict__ adj_val, int32_t nS_bound, const int32_t *__restrict__ nS_dev,
+                                                      int32_t n_cols_bound, const int32_t *__restrict__ n_cols_dev, int64_t cap,
+                                                      int32_t *__restrict__ colptr, int32_t *__restrict__ rowT, float *__restrict__ valT)
+{
+    constexpr int U = 8;   // entries on their way per thread
+    __shared__ int32_t l_e[ONE_LIST], g_e[ONE_LIST];   // entries of my columns, in any order; grouped by column
+    __shared__ uint16_t l_c[ONE_LIST];                 // their columns
+    __shared__ int32_t cnt[ONE_OWN], pre[ONE_OWN], fill[ONE_OWN], done[ONE_OWN];
+    __shared__ int32_t n_list, s_before[ONE_BLOCK / WAVE], s_base;
+    const int32_t nS = resolve_count(nS_bound, nS_dev), n_cols = resolve_count(n_cols_bound, n_cols_dev);
+    const int tid = (int)threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
+    const int32_t own = (n_cols + ONE_GRID - 1) / ONE_GRID;   // at most ONE_OWN
+    const int32_t c0 = (int32_t)blockIdx.x * own, c1 = c0 + own < n_cols ? c0 + own : n_cols;
+    if (c0 >= n_cols) {
+        if (n_cols == 0 && blockIdx.x == 0 && tid == 0) colptr[0] = 0;
+        return;
+    }
+    // entries of the rows (inside the arrays whatever the pointers say)
+    int32_t e_beg = nS > 0 ? adj_rowptr[0] : 0, e_end = nS > 0 ? adj_rowptr[nS] : 0;
+    if (e_beg < 0) e_beg = 0;
+    if (e_end > cap) e_end = (int32_t)cap;
+    for (int i = tid; i < ONE_OWN; i += ONE_BLOCK) { cnt[i] = 0; done[i] = 0; }
+    if (tid == 0) n_list = 0;
+    __syncthreads();
+    // counts of my columns, entries of the columns before them
+    int32_t before = 0;
+    for (int64_t e0 = (int64_t)e_beg + tid; e0 < e_end; e0 += U * ONE_BLOCK) {
+        int32_t c[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) c[u] = adj_col[e0 + u * ONE_BLOCK < e_end ? e0 + u * ONE_BLOCK : e0];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (e0 + u * ONE_BLOCK >= e_end || c[u] < 0) continue;
+            before += c[u] < c0 ? 1 : 0;
+            if (c[u] < c0 || c[u] >= c1) continue;
+            atomicAdd(&cnt[c[u] - c0], 1);
+            const int32_t at = atomicAdd(&n_list, 1);
+            if (at < ONE_LIST) {
+                l_e[at] = (int32_t)(e0 + u * ONE_BLOCK);
+                l_c[at] = (uint16_t)(c[u] - c0);
+            }
+        }
+    }
+    before = wave_sum(before);
+    if (lane == 0) s_before[wave] = before;
+    __syncthreads();
+    const int32_t n_own = n_list;   // entries of my columns
+    auto group = [&](bool first) {   // wavefront 0: pre = exclusive prefix of cnt (first: and the column offsets)
+        int32_t v[4], sum = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            v[k] = lane * 4 + k < ONE_OWN ? cnt[lane * 4 + k] : 0;
+            sum += v[k];
+        }
+        int32_t ex = wave_inclusive_scan<int32_t>(sum) - sum;
+        int32_t base = 0;
+        if (first) {
+            base = lane < ONE_BLOCK / WAVE ? s_before[lane] : 0;
+            base = wave_sum(base);
+            if (lane == 0) s_base = base;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int32_t i = lane * 4 + k;
+            if (i < ONE_OWN) {
+                pre[i] = ex;
+                fill[i] = 0;
+                if (first && c0 + i < c1) colptr[c0 + i] = base + ex;
+            }
+            ex += v[k];
+        }
+        if (first && c1 == n_cols && lane == WAVE - 1) colptr[n_cols] = base + ex;
+    };
+    if (wave == 0) group(true);
+    __syncthreads();
+    const int32_t base = s_base;
+    const bool fits = n_own <= ONE_LIST;
+    // where a column's entries begin in the lists (colptr again, for the windows below, whose counts replace cnt and pre)
+    int32_t *__restrict__ const first = fits ? pre : done;
+    if (!fits) {
+        for (int i = tid; i < ONE_OWN; i += ONE_BLOCK) done[i] = pre[i];
+        __syncthreads();
+    }
+    for (int64_t w0 = e_beg; w0 < e_end; w0 += ONE_LIST) {
+        int32_t n = n_own;
+        if (!fits) {   // the entries of my columns among the next ONE_LIST
+            for (int i = tid; i < ONE_OWN; i += ONE_BLOCK) cnt[i] = 0;
+            if (tid == 0) n_list = 0;
+            __syncthreads();
+            const int64_t w1 = w0 + ONE_LIST < e_end ? w0 + ONE_LIST : e_end;
+            for (int64_t e = w0 + tid; e < w1; e += ONE_BLOCK) {
+                const int32_t c = adj_col[e];
+                if (c < c0 || c >= c1) continue;
+                atomicAdd(&cnt[c - c0], 1);
+                const int32_t at = atomicAdd(&n_list, 1);   // < ONE_LIST
+                l_e[at] = (int32_t)e;
+                l_c[at] = (uint16_t)(c - c0);
+            }
+            __syncthreads();
+            n = n_list;
+            if (wave == 0) group(false);
+            __syncthreads();
+        }
+        for (int32_t i = tid; i < n; i += ONE_BLOCK) g_e[pre[l_c[i]] + atomicAdd(&fill[l_c[i]], 1)] = l_e[i];
+        __syncthreads();
+        for (int32_t i = tid; i < n; i += ONE_BLOCK) {
+            const int32_t e = l_e[i], c = l_c[i], beg = pre[c], len = cnt[c];
+            const float v = adj_val[e];
+            // the row: last r with adj_rowptr[r] <= e, by eighths
+            int32_t lo = 0, hi = nS;   // adj_rowptr[lo] <= e < adj_rowptr[hi]
+            while (hi - lo > 1) {
+                const int32_t span = hi - lo;
+                int32_t p[7];
+#pragma unroll
+                for (int k = 0; k < 7; ++k) p[k] = adj_rowptr[lo + (int32_t)((int64_t)span * (k + 1) / 8)];
+                int below = 0;
+#pragma unroll
+                for (int k = 0; k < 7; ++k) below += p[k] <= e ? 1 : 0;
+                const int32_t new_lo = lo + (int32_t)((int64_t)span * below / 8);
+                hi = below < 7 ? lo + (int32_t)((int64_t)span * (below + 1) / 8) : hi;
+                lo = new_lo;
+                if (hi <= lo) break;
+            }
+            int32_t place = 0;
+            int32_t k0 = 0;
+            for (; k0 + 16 <= len; k0 += 16) {   // sixteen reads on their way
+                int32_t o[16];
+#pragma unroll
+                for (int k = 0; k < 16; ++k) o[k] = g_e[beg + k0 + k];
+#pragma unroll
+                for (int k = 0; k < 16; ++k) place += o[k] < e ? 1 : 0;
+            }
+            for (; k0 < len; k0 += 4) {   // (past the column's end its last entry again, dropped)
+                int32_t o[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) o[k] = g_e[beg + (k0 + k < len ? k0 + k : len - 1)];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) place += k0 + k < len && o[k] < e ? 1 : 0;
+            }
+            const int64_t at = (int64_t)base + first[c] + place;
+            if (at < cap) {
+                rowT[at] = lo;
+                valT[at] = v;
+            }
+        }
+        if (fits) break;
+        __syncthreads();
+        for (int i = tid; i < ONE_OWN; i += ONE_BLOCK) done[i] += cnt[i];
+        __syncthreads();
+    }
+}
+
 __global__ void fill_zero_i32(int32_t *p, int64_t n)
 {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0;
@@ -565,23 +730,29 @@ extern "C" int csgs_aggregate_grad(const int32_t *adj_rowptr, const int32_t *adj
     const GradScratch g = carve_grad(scratch, n_cols, adj_cap);
     if (scratch_bytes < g.bytes) return CSGS_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
-    const unsigned zb = (unsigned)(((int64_t)n_cols + 255) / 256 < 1024 ? ((int64_t)n_cols + 255) / 256 : 1024);
-    CSGS_LAUNCH(K_FILL_ZERO, fill_zero_i32, dim3(zb), dim3(256), st, g.counts, (int64_t)n_cols);
-    CSGS_LAUNCH_CHECK();
-    const unsigned rb = (unsigned)(((int64_t)nS + 3) / 4 < 4096 ? ((int64_t)nS + 3) / 4 : 4096);   // 4 rows (wavefronts) per block
-    CSGS_LAUNCH(K_ADJT_COUNT, adjT_count, dim3(rb), dim3(256), st, adj_rowptr, adj_col, nS, nS_dev, n_cols, n_cols_dev, adj_cap, g.counts);
-    CSGS_LAUNCH_CHECK();
-    const int64_t pieces = ((int64_t)n_cols + PREFIX_COLS - 1) / PREFIX_COLS, rounds = (pieces + PREFIX_GRID - 1) / PREFIX_GRID;
-    CSGS_LAUNCH(K_ADJT_PREFIX, adjT_prefix, dim3((unsigned)((pieces + rounds - 1) / rounds)), dim3(256), st, (const int32_t *)g.counts, n_cols, n_cols_dev,
-                g.colptr, (int32_t)rounds);
-    CSGS_LAUNCH_CHECK();
-    CSGS_LAUNCH(K_ADJT_FILL, adjT_fill, dim3(rb), dim3(256), st, adj_rowptr, adj_col, adj_val, nS, nS_dev, n_cols, n_cols_dev,
-                (const int32_t *)g.colptr, g.counts, g.unordered, adj_cap);
-    CSGS_LAUNCH_CHECK();
-    const unsigned ob = (unsigned)(((int64_t)n_cols + ORD_COLS - 1) / ORD_COLS);
-    CSGS_LAUNCH(K_ADJT_ORDER, adjT_order, dim3(ob), dim3(AGG_BLOCK), st, (const int32_t *)g.colptr, n_cols, n_cols_dev, nS, nS_dev,
-                (const uint2 *)g.unordered, g.rowT, g.valT, adj_cap);
-    CSGS_LAUNCH_CHECK();
+    if (adj_cap <= ONE_ENTRIES && n_cols <= ONE_COLS) {
+        CSGS_LAUNCH(K_ADJT_ORDER, adjT_one, dim3(ONE_GRID), dim3(ONE_BLOCK), st, adj_rowptr, adj_col, adj_val, nS, nS_dev, n_cols, n_cols_dev, adj_cap,
+                    g.colptr, g.rowT, g.valT);
+        CSGS_LAUNCH_CHECK();
+    } else {
+        const unsigned zb = (unsigned)(((int64_t)n_cols + 255) / 256 < 1024 ? ((int64_t)n_cols + 255) / 256 : 1024);
+        CSGS_LAUNCH(K_FILL_ZERO, fill_zero_i32, dim3(zb), dim3(256), st, g.counts, (int64_t)n_cols);
+        CSGS_LAUNCH_CHECK();
+        const unsigned rb = (unsigned)(((int64_t)nS + 3) / 4 < 4096 ? ((int64_t)nS + 3) / 4 : 4096);   // 4 rows (wavefronts) per block
+        CSGS_LAUNCH(K_ADJT_COUNT, adjT_count, dim3(rb), dim3(256), st, adj_rowptr, adj_col, nS, nS_dev, n_cols, n_cols_dev, adj_cap, g.counts);
+        CSGS_LAUNCH_CHECK();
+        const int64_t pieces = ((int64_t)n_cols + PREFIX_COLS - 1) / PREFIX_COLS, rounds = (pieces + PREFIX_GRID - 1) / PREFIX_GRID;
+        CSGS_LAUNCH(K_ADJT_PREFIX, adjT_prefix, dim3((unsigned)((pieces + rounds - 1) / rounds)), dim3(256), st, (const int32_t *)g.counts, n_cols, n_cols_dev,
+                    g.colptr, (int32_t)rounds);
+        CSGS_LAUNCH_CHECK();
+        CSGS_LAUNCH(K_ADJT_FILL, adjT_fill, dim3(rb), dim3(256), st, adj_rowptr, adj_col, adj_val, nS, nS_dev, n_cols, n_cols_dev,
+                    (const int32_t *)g.colptr, g.counts, g.unordered, adj_cap);
+        CSGS_LAUNCH_CHECK();
+        const unsigned ob = (unsigned)(((int64_t)n_cols + ORD_COLS - 1) / ORD_COLS);
+        CSGS_LAUNCH(K_ADJT_ORDER, adjT_order, dim3(ob), dim3(AGG_BLOCK), st, (const int32_t *)g.colptr, n_cols, n_cols_dev, nS, nS_dev,
+                    (const uint2 *)g.unordered, g.rowT, g.valT, adj_cap);
+        CSGS_LAUNCH_CHECK();
+    }
     // the forward kernel on the transposed structure: rows = columns of P~, gathered table = dZ
     // (its rows are bounded by the row count of P~), output mask = [H_prev > 0]
     return pick_vec<float>(g.colptr, g.rowT, g.valT, n_cols, n_cols_dev, nS_dev, dZ, lddz, (int64_t)nS, nullptr, (int64_t)F, 0,

@@ -578,3 +578,29 @@ def test_weight_scan_of_many_edges(dev, n, lo, hi, n_rows, degree, remote_ids, c
             np.testing.assert_array_equal(b.cand_w[:n_c].cpu().numpy().view(np.uint64), want.cand_w)
             np.testing.assert_array_equal(b.cdf[:n_c].cpu().numpy().view(np.uint64), want.cdf)
     assert int(torch.count_nonzero(ws.buf.view(K, -1)[:, :csgs.csgs_workspace_clean_bytes(n) // 8]).item()) == 0
+
+
+# The transpose in one launch: a column that holds more entries than a block's lists, row pointers that start inside the arrays, empty rows, the most
+# columns it takes and one more (several launches), two calls bit for bit.
+@pytest.mark.parametrize("nS,n_cols,most,hub", [(20_000, 700, 6, True), (20_000, 65_536, 6, False), (20_000, 65_537, 6, False), (3, 1, 1, True), (700, 256, 300, True), (1, 257, 200, False)])
+def test_aggregate_gradient_one_launch(dev, nS, n_cols, most, hub):
+    from paper_2101_07706_amd import csgs
+    rng = np.random.default_rng(nS + n_cols)
+    F, skip = 12, 37
+    cols = [np.unique(np.concatenate([rng.integers(0, n_cols, rng.integers(0, most + 1)), [min(5, n_cols - 1)] if hub else []])).astype(np.int32) for _ in range(nS)]
+    rp = np.zeros(nS + 1, np.int32)
+    np.cumsum([len(c) for c in cols], out=rp[1:])
+    nnz = int(rp[-1])
+    col, val = np.concatenate(cols + [np.zeros(1, np.int32)])[:max(nnz, 1)], rng.standard_normal(max(nnz, 1)).astype(np.float32)
+    dZ, H = rng.standard_normal((nS, F)).astype(np.float32), rng.standard_normal((n_cols, F)).astype(np.float32)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+    pad = np.full(skip, 3 % n_cols, np.int32)   # entries before the first row's
+    cold, vald = t(np.concatenate([pad, col])), t(np.concatenate([pad.astype(np.float32), val]))
+    scratch = torch.full((csgs.csgs_aggregate_grad_scratch_bytes(n_cols, cold.numel()) // 8 + 32,), -1, dtype=torch.int64, device=dev)
+    got = []
+    for _ in range(2):
+        dH = torch.full((n_cols, F), float("nan"), dtype=torch.float32, device=dev)
+        csgs.csgs_aggregate_grad(t(rp + skip), cold, vald, None, t(dZ), t(H), dH, scratch)
+        got.append(dH.cpu().numpy())
+    chain.assert_close(got[0], oracle.aggregate_grad(rp, col, val, n_cols, dZ, H), chain.RTOL, chain.ATOL, "dH")
+    np.testing.assert_array_equal(got[0], got[1])
