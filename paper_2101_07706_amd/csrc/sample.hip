@@ -526,8 +526,9 @@ __device__ inline bool adj_leading_blocks(RemoteArgs &rem, NextRows &nxt, const 
 // the first pass can leave, where the second looks up the rest again: 16.7 M 300 / 340, 33 M 645 / 720, 125 M 2310 / 3500.  The first
 // pass is bound by its random lookups in the membership words (100 G edges/s).
 // Most chunks (of all instances of a launch, as expected from the mean degree) for the one pass: 2 K edges 10.5 against 14
-// us, 52 K 10.1 / 13.8, 80 K 13.4 / 14.4; from 400 K on two passes are level or better.
-constexpr int ADJ_ONCE_MAX = 256;
+// us, 52 K 10.1 / 13.8, 80 K 13.4 / 14.4 (with rows searched for edge by edge; without, a three-layer step of 8192 rows and 420 K edges a layer 271 / 276, a
+// two-layer step of 1 M edges a layer 212 / 204).  With several instances the line is where it was measured for them.
+constexpr int ADJ_ONCE_MAX = 640, ADJ_ONCE_MAX_EACH = 256;
 constexpr int ADJ_MARK_GRID = 2048;    // eight blocks per compute unit, by threads
 constexpr int ADJ_PLACE_GRID = 512;
 constexpr int ADJ_PLACE_MIN = 4;       // chunks a block of the placing pass takes at least: one per wavefront
@@ -860,7 +861,7 @@ static int sampled_adjacency_impl(const csgs_graph *g, const int32_t *rows, int3
     const unsigned nz = (unsigned)w.n_inst;
     const InstStride is = inst_stride(w);
     const AdjGraph ag{g->colidx, g->val, g->n_nodes, g->nnz, cur.eoff, cur.rowstart, w.rank, w.member, w.pdbl};
-    if (expected * w.n_inst <= ADJ_ONCE_MAX) {
+    if (expected * w.n_inst <= (w.n_inst == 1 ? ADJ_ONCE_MAX : ADJ_ONCE_MAX_EACH)) {
         const dim3 grid_once(blocks(resident_grid(2), 1) + (unsigned)(rem.blocks + nxt.blocks), 1, nz);
         CSGS_LAUNCH(K_ADJ_ONCE, adj_once, grid_once, dim3(256), st, ag, cur.meta, w.epoch, w.adj_ts, w.chunk_cap, cur.bound_note,
                     adj_rowptr, adj_col, adj_val, adj_cap, adj_nnz, status, rem, nxt, is);
