@@ -32,6 +32,7 @@ __global__ __launch_bounds__(AGG_BLOCK) void aggregate_k(const int32_t *__restri
                                                          const float *__restrict__ mask, int64_t ldm,
                                                          int32_t n_slices, int32_t tr, CompStride cs)
 {
+    cs = at_instance(cs);
     __shared__ WaveStage<tile_rows(G)> stage[AGG_WAVES];
     __shared__ double heads[AGG_WAVES][WAVE * V], carries[AGG_WAVES][2 * G * V];
     const int32_t slice = (int32_t)(blockIdx.x % (unsigned)n_slices);
@@ -609,6 +610,7 @@ __global__ __launch_bounds__(256) void gather_rows_k(const U *__restrict__ X, in
                                                      const int64_t *__restrict__ n_dev, U *__restrict__ out,
                                                      int64_t ldo, CompStride cs)
 {
+    cs = at_instance(cs);
     constexpr int32_t SIZE = (int32_t)sizeof(U);
     X = inst_ptr(X, cs.x); ids = inst_ptr(ids, cs.adj); n_dev = inst_ptr(n_dev, cs.adj); out = inst_ptr(out, cs.out);
     int64_t n = cap;

@@ -96,19 +96,32 @@ struct Workspace {
     int64_t buf_stride;  // bytes between consecutive instances' caller buffers
 };
 
-// Several independent instances of a call run in the same launches: blockIdx.z selects the
-// instance, and every per-instance pointer moves by that instance's stride in bytes -- `ws` for
-// what lives in the workspace (instance k's workspace follows instance k - 1's), `buf` for the
-// caller's arrays.  The graph is shared.  With one instance blockIdx.z is 0 and nothing moves.
+// Several independent instances of a call run in the same launches, and every per-instance pointer moves by that
+// instance's stride in bytes -- `ws` for what lives in the workspace (instance k's workspace follows instance
+// k - 1's), `buf` for the caller's arrays.  The graph is shared.  With one instance nothing moves.
+// Two orders of the blocks: instance after instance (n = 0: blockIdx.z selects it), or the instances in turn (n of them: block b
+// of instance k is blockIdx.x = b * n + k).  The hardware deals consecutive blocks round-robin to the 8 XCDs, so in turn an
+// instance's blocks stay on one XCD of eight instances, two of four, four of two, and so do the tables
+// they look things up in, which one L2 then holds (see inst_grid).
 struct InstStride {
     int64_t ws, buf;
+    int32_t n;
 };
+__device__ inline uint32_t inst_index(const InstStride &is) { return is.n ? blockIdx.x % (uint32_t)is.n : blockIdx.z; }
+__device__ inline uint32_t inst_block(const InstStride &is) { return is.n ? blockIdx.x / (uint32_t)is.n : blockIdx.x; }    // block of its instance
+__device__ inline uint32_t inst_blocks(const InstStride &is) { return is.n ? gridDim.x / (uint32_t)is.n : gridDim.x; }    // an instance's
+// The strides of this block's instance, for inst_ptr().
+__device__ inline InstStride at_instance(const InstStride &is)
+{
+    const int64_t k = inst_index(is);
+    return InstStride{is.ws * k, is.buf * k, is.n};
+}
 template <typename T>
-__device__ inline T *inst_ptr(T *p, int64_t stride)
+__device__ inline T *inst_ptr(T *p, int64_t bytes)
 {
     // (pointer arithmetic, not integer arithmetic: the result is still known to point to global memory, so loads
     // through it are global loads and not the slower flat ones)
-    return p ? (T *)((char *)const_cast<typename std::remove_const<T>::type *>(p) + (int64_t)blockIdx.z * stride) : p;   // null stays null
+    return p ? (T *)((char *)const_cast<typename std::remove_const<T>::type *>(p) + bytes) : p;   // null stays null
 }
 constexpr int MAX_INSTANCES = 64;
 
@@ -119,6 +132,11 @@ struct CompStride {
     int64_t xr;    // staged remote rows
     int64_t out;   // the output matrix
 };
+__device__ inline CompStride at_instance(const CompStride &cs)
+{
+    const int64_t k = blockIdx.z;
+    return CompStride{cs.adj * k, cs.x * k, cs.xr * k, cs.out * k};
+}
 struct CompInst {
     int32_t n = 1;
     CompStride cs = {0, 0, 0, 0};
@@ -202,7 +220,22 @@ __host__ inline int open_workspace(csgs_workspace *d, int64_t n_nodes, int64_t n
     return out->bytes * (size_t)n_inst <= d->bytes ? CSGS_OK : CSGS_EWORKSPACE;
 }
 
-__host__ inline InstStride inst_stride(const Workspace &w) { return InstStride{(int64_t)w.bytes, w.buf_stride}; }
+__host__ inline InstStride inst_stride(const Workspace &w) { return InstStride{(int64_t)w.bytes, w.buf_stride, 0}; }
+// Grid of `blocks` blocks per instance, the instances in turn.  For kernels whose blocks wait for nobody or for lower blocks of their instance only
+// (those were dispatched before them): not for resident grids, see below.  An odd number of instances would spread
+// over the XCDs either way.  (us, eight instances of 380 K edges, one after the other / in turn: marking pass of the adjacency 25.4 / 22.2, candidate
+// sums 41 / 38.5, emission 21.5 / 18.8, draws 15.0 / 13.5, compaction 12.7 / 11, a three-layer step 829 / 777.)
+struct InstGrid {
+    dim3 grid;
+    InstStride is;
+};
+__host__ inline InstGrid inst_grid(const Workspace &w, int64_t blocks, int threads)
+{
+    InstStride is = inst_stride(w);
+    if (w.n_inst % 2 || blocks * w.n_inst * threads > 0x7FFFFFFFll) return InstGrid{dim3((unsigned)blocks, 1, (unsigned)w.n_inst), is};
+    is.n = w.n_inst;
+    return InstGrid{dim3((unsigned)(blocks * w.n_inst)), is};
+}
 
 // Grid of a kernel whose blocks wait for each other and stride over a tile count known only on
 // the device: resident_grid(per_cu) blocks of 256 threads, per_cu per compute unit.  Such a kernel

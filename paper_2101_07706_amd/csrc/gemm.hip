@@ -90,6 +90,7 @@ __global__ __launch_bounds__(256, RT * NT >= 6 ? 2 : (RT * NT >= 4 ? 3 : 4)) voi
     double *__restrict__ partial, int M_bound, int N, int K_bound, const int32_t *__restrict__ rows_dev, int tiles_n, int n_tiles,
     int n_blocks, CompStride cs)
 {
+    cs = at_instance(cs);
     constexpr bool DW = MODE == MODE_DW, B_KMAJOR = MODE == MODE_DZ;
     constexpr int BM = 16 * RT, BN = 16 * NT;
     A = inst_ptr(A, cs.x); C = inst_ptr(C, cs.out); rows_dev = inst_ptr(rows_dev, cs.adj);   // B (the weights) is shared

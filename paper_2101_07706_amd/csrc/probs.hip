@@ -45,6 +45,7 @@ __global__ __launch_bounds__(256) void row_prefix(const int64_t *__restrict__ ro
                                                   int64_t *__restrict__ meta, int64_t edge_cap,
                                                   int2 *__restrict__ bound_note, int32_t *__restrict__ status, InstStride is)
 {
+    is = at_instance(is);
     bound_note = inst_ptr(bound_note, is.ws);
     S = inst_ptr(S, is.buf); nS_dev = inst_ptr(nS_dev, is.buf); status = inst_ptr(status, is.buf);
     epoch = inst_ptr(epoch, is.ws); ts_mem = inst_ptr(ts_mem, is.ws); eoff = inst_ptr(eoff, is.ws);
@@ -123,6 +124,8 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
                                                   const int2 *__restrict__ bound_note,
                                                   uint64_t *__restrict__ epoch, int32_t *__restrict__ status, Stage stg, InstStride is)
 {
+    is = at_instance(is);
+    const uint32_t blk = inst_block(is), n_blk = inst_blocks(is);
     constexpr int ITEMS = EDGE_TILE / 256;
     constexpr int BINS = SUB_MAX / WAVE;          // groups per lane of the counting sort
     static_assert(SUB_MAX % WAVE == 0 && EDGE_TILE <= 0xFFFF, "groups of a chunk");
@@ -133,7 +136,7 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
     wtable = inst_ptr(wtable, is.ws); tileflag = inst_ptr(tileflag, is.ws); bound_note = inst_ptr(bound_note, is.ws);
     stg.e = inst_ptr(stg.e, is.ws); stg.off = inst_ptr(stg.off, is.ws);
     status = inst_ptr(status, is.buf); epoch = inst_ptr(epoch, is.ws);
-    ChunkRows rows = chunk_rows(bound_note, blockIdx.x, (int64_t)blockIdx.x + 1);   // (the grid stays within the notes; on its way beside the counts)
+    ChunkRows rows = chunk_rows(bound_note, blk, (int64_t)blk + 1);   // (the grid stays within the notes; on its way beside the counts)
     const int32_t nS = (int32_t)meta[META_ROWS];
     const double scale = ldexp(1.0, shift_for_rows(shift_base, nS));
     const int64_t E = meta[META_EDGES];
@@ -145,17 +148,17 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
     const int lane = lane_id();
     const int wave = (int)(threadIdx.x >> 6);
 
-    if (blockIdx.x == 0) clear_group_sums(stg, is.ws);
-    if (blockIdx.x == 0 && threadIdx.x == 0 && meta[META_EDGES_TRUE] > edge_cap) atomicOr(status, CSGS_ST_EDGE_OVERFLOW);
+    if (blk == 0) clear_group_sums(stg, is.ws);
+    if (blk == 0 && threadIdx.x == 0 && meta[META_EDGES_TRUE] > edge_cap) atomicOr(status, CSGS_ST_EDGE_OVERFLOW);
     bool bad = false;
-    for (int64_t t = blockIdx.x; t < n_chunks; t += gridDim.x) {
+    for (int64_t t = blk; t < n_chunks; t += n_blk) {
         const int64_t c0 = t * EDGE_TILE;
         const int64_t c1 = (c0 + EDGE_TILE < E) ? c0 + EDGE_TILE : E;
         const bool staged = t < n_staged;
         if (staged)
             for (int i = threadIdx.x; i < SUB_MAX; i += blockDim.x) hist[i] = 0u;   // (its last readers are a barrier behind)
         const int32_t len = (int32_t)(c1 - c0);
-        if (t != blockIdx.x) rows = chunk_rows(bound_note, t, t + 1);
+        if (t != blk) rows = chunk_rows(bound_note, t, t + 1);
         (void)map_edges(map, eoff, rowstart, nS, c0, len, rows, first_rows(eoff, rowstart, nS, rows));   // (starts and ends with a barrier)
         const EdgeWords words = edge_words(map);
         // All of a thread's edges go through each step together -- their addresses, then their columns and
@@ -279,6 +282,8 @@ __global__ __launch_bounds__(WIDE_BLOCK) void scan_wide(const int32_t *__restric
                                                         const int2 *__restrict__ bound_note, uint64_t *__restrict__ epoch,
                                                         int32_t *__restrict__ status, Stage stg, InstStride is)
 {
+    is = at_instance(is);
+    const uint32_t blk = inst_block(is), n_blk = inst_blocks(is);
     constexpr int STEPS = WIDE_EDGES / WIDE_STEP, BINS = WIDE_BINS / WIDE_BLOCK;   // bins per thread
     __shared__ union {
         EdgeMap<WIDE_STEP> map;
@@ -304,10 +309,10 @@ __global__ __launch_bounds__(WIDE_BLOCK) void scan_wide(const int32_t *__restric
         tileflag[c >> 3] = 1;         // same values from every writer
         epoch[EPOCH_ADDED] = call;
     };
-    if (blockIdx.x == 0) clear_group_sums(stg, is.ws);
-    if (blockIdx.x == 0 && tid == 0 && meta[META_EDGES_TRUE] > edge_cap) atomicOr(status, CSGS_ST_EDGE_OVERFLOW);
+    if (blk == 0) clear_group_sums(stg, is.ws);
+    if (blk == 0 && tid == 0 && meta[META_EDGES_TRUE] > edge_cap) atomicOr(status, CSGS_ST_EDGE_OVERFLOW);
     bool bad = false;
-    for (int64_t run = blockIdx.x; run < n_runs; run += gridDim.x) {
+    for (int64_t run = blk; run < n_runs; run += n_blk) {
         const bool staged = run < n_staged;
         for (int i = tid; i < stg.bins; i += WIDE_BLOCK) hist[i] = 0u;   // (its last readers are a barrier behind)
         // Which rows, and where they start, is asked for for all steps at once; columns and values of a step travel while the next one
@@ -560,6 +565,8 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, PACK ? 8 : 1) void cand_partials(u
                                                      unsigned long long *__restrict__ partial,
                                                      uint64_t *__restrict__ gtot, int32_t *__restrict__ status, InstStride is)
 {
+    is = at_instance(is);
+    const uint32_t blk = inst_block(is);
     constexpr int WAVES = CAND_PART_BLOCK / WAVE, W = TILES * CAND_WORDS / WAVES;   // words per wavefront
     __shared__ uint64_t lds[WAVES][3];
     __shared__ unsigned long long acc[CAND_TILE];
@@ -575,14 +582,14 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, PACK ? 8 : 1) void cand_partials(u
     // blocks in the order of their tiles: blocks_below of TILES tiles, max_split per tile that meets the local range, TILES again
     const int64_t tile0 = stg.lo / CAND_TILE;
     int64_t t0, t1;
-    const int32_t b = (int32_t)blockIdx.x - blocks_below;
+    const int32_t b = (int32_t)blk - blocks_below;
     const int32_t own_blocks = stg.tiles * stg.max_split;   // at most SPLIT_BLOCKS
     const bool own = b >= 0 && b < own_blocks;
     const uint32_t per_step = stg.adjacent ? (uint32_t)stg.max_split : (uint32_t)stg.tiles;
     const uint32_t step_own = own ? (uint32_t)b / per_step : 0u, rest_own = own ? (uint32_t)b % per_step : 0u;
     const uint32_t tile_own = stg.adjacent ? step_own : rest_own, round_own = stg.adjacent ? rest_own : step_own;
     if (b < 0) {
-        t0 = (int64_t)blockIdx.x * TILES;
+        t0 = (int64_t)blk * TILES;
         t1 = t0 + TILES;
         if (stg.tiles > 0 && t1 > tile0) t1 = tile0;
     } else if (own) {
@@ -764,6 +771,8 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, 8) void bin_sums(uint64_t *__restr
                                                                const uint64_t *__restrict__ epoch, unsigned long long *__restrict__ partial, uint64_t *__restrict__ gtot,
                                                                int32_t *__restrict__ status, InstStride is)
 {
+    is = at_instance(is);
+    const uint32_t blk = inst_block(is);
     constexpr int WAVES = CAND_PART_BLOCK / WAVE, U = 4;   // entries on their way per lane
     __shared__ unsigned long long acc[WIDE_IDS];
     __shared__ __attribute__((aligned(8))) uint32_t s_bits[WIDE_IDS / 32];   // ids with a weight
@@ -776,12 +785,12 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, 8) void bin_sums(uint64_t *__restr
     const int tid = (int)threadIdx.x, lane = lane_id(), wave = tid >> 6;
     // blocks in the order of their bins, max_split for each of the local tiles (see cand_partials)
     const int32_t own_blocks = stg.tiles * stg.max_split;
-    const int32_t b = (int32_t)blockIdx.x - stg.below;
+    const int32_t b = (int32_t)blk - stg.below;
     const bool own = b >= 0 && b < own_blocks;
     const uint32_t per_step = stg.adjacent ? (uint32_t)stg.max_split : (uint32_t)stg.tiles;
     const uint32_t step_own = own ? (uint32_t)b / per_step : 0u, rest_own = own ? (uint32_t)b % per_step : 0u;
     const uint32_t tile_own = stg.adjacent ? step_own : rest_own, round_own = stg.adjacent ? rest_own : step_own;
-    const int32_t bin = b < 0 ? (int32_t)blockIdx.x : (own ? stg.below + (int32_t)tile_own : stg.below + stg.tiles + (b - own_blocks));
+    const int32_t bin = b < 0 ? (int32_t)blk : (own ? stg.below + (int32_t)tile_own : stg.below + stg.tiles + (b - own_blocks));
     const int64_t most = stg.chunks / WIDE_CHUNKS;   // runs that the hand-over array holds, at least one
     const uint16_t *__restrict__ off = stg.off + bin;
     uint32_t beg, end;
@@ -804,7 +813,7 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, 8) void bin_sums(uint64_t *__restr
     const int64_t tile0 = stg.lo / CAND_TILE, local_end = tile0 + stg.tiles;
     int64_t t0, t1;
     if (b < 0) {
-        t0 = (int64_t)blockIdx.x * CAND_PART_TILES;
+        t0 = (int64_t)blk * CAND_PART_TILES;
         t1 = t0 + CAND_PART_TILES;
         if (stg.tiles > 0 && t1 > tile0) t1 = tile0;
     } else if (own) {
@@ -969,6 +978,8 @@ __global__ __launch_bounds__(256) void cand_emit(uint64_t *__restrict__ wtable, 
                                                  int32_t *__restrict__ cand_id, uint64_t *__restrict__ cand_w,
                                                  uint64_t *__restrict__ cdf, float *__restrict__ q, int64_t cap, InstStride is)
 {
+    is = at_instance(is);
+    const uint32_t blk = inst_block(is);
     __shared__ uint32_t s_cnt[4];
     constexpr int TILES = PACKED ? 4 : 1, WORDS = CAND_WORDS / 4;
     __shared__ uint32_t s_id[4][PACKED ? 1 : CAND_TILE / 4];    // the tile's candidates, packed: ids ...
@@ -982,7 +993,7 @@ __global__ __launch_bounds__(256) void cand_emit(uint64_t *__restrict__ wtable, 
     __shared__ uint64_t s_red[4][6];
     const int lane = lane_id();
     const int wave = (int)(threadIdx.x >> 6);
-    const int64_t t = (int64_t)blockIdx.x * TILES;   // the block's first tile
+    const int64_t t = (int64_t)blk * TILES;   // the block's first tile
     const int64_t g = t / 64, n_groups = (n_tiles + 63) / 64;
     // Loads are issued in the order flags, prefix inputs, accumulators, and consumed only after
     // all are in flight, so the tile's own data travels while the prefix is being summed.
@@ -1298,8 +1309,6 @@ static int build_probs_impl(const csgs_graph *g, const int32_t *S, int32_t nS, c
     }
     ws->has_next = 0;
     const RowOffsets &rows = w.rows[ws->rows_buf & 1];
-    const unsigned nz = (unsigned)w.n_inst;
-    const InstStride is = inst_stride(w);
     // The number of edges is known on the device only: rows of the graph's mean degree are a guess that hubs can exceed many
     // times over.  What depends on the number is decided on the device, and there are never fewer blocks than the device
     // holds (those without a chunk leave at once) unless the workspace describes fewer chunks.  With several instances the
@@ -1353,32 +1362,35 @@ static int build_probs_impl(const csgs_graph *g, const int32_t *S, int32_t nS, c
         if (runs < 256 && w.n_inst == 1) runs = 256;
         if (runs > SCAN_GRID / 4) runs = SCAN_GRID / 4;
         if (runs > (w.chunk_cap + WIDE_CHUNKS - 1) / WIDE_CHUNKS) runs = (w.chunk_cap + WIDE_CHUNKS - 1) / WIDE_CHUNKS;
-        CSGS_LAUNCH(K_SCAN_EDGES, scan_wide, dim3((unsigned)runs, 1, nz), dim3(WIDE_BLOCK), st, g->colidx, g->val, g->n_nodes, g->nnz, shift_base,
-                    rows.meta, w.chunk_cap * EDGE_TILE, rows.eoff, rows.rowstart, w.wtable, w.tileflag, rows.bound_note, w.epoch, status, stg, is);
+        const InstGrid ig = inst_grid(w, runs, WIDE_BLOCK);
+        CSGS_LAUNCH(K_SCAN_EDGES, scan_wide, ig.grid, dim3(WIDE_BLOCK), st, g->colidx, g->val, g->n_nodes, g->nnz, shift_base,
+                    rows.meta, w.chunk_cap * EDGE_TILE, rows.eoff, rows.rowstart, w.wtable, w.tileflag, rows.bound_note, w.epoch, status, stg, ig.is);
     } else {
-        CSGS_LAUNCH(K_SCAN_EDGES, scan_edges, dim3((unsigned)chunks, 1, nz), dim3(256), st, g->colidx, g->val,
+        const InstGrid ig = inst_grid(w, chunks, 256);
+        CSGS_LAUNCH(K_SCAN_EDGES, scan_edges, ig.grid, dim3(256), st, g->colidx, g->val,
                     g->n_nodes, g->nnz, shift_base, rows.meta, w.chunk_cap * EDGE_TILE, rows.eoff, rows.rowstart, w.wtable,
-                    w.tileflag, rows.bound_note, w.epoch, status, stg, is);
+                    w.tileflag, rows.bound_note, w.epoch, status, stg, ig.is);
     }
     CSGS_LAUNCH_CHECK();
-    const dim3 part_grid((unsigned)part_blocks, 1, nz);
+    const InstGrid part = inst_grid(w, part_blocks, CAND_PART_BLOCK);
 #define CSGS_CAND_PARTIALS(TILES, PACK)                                                                                                       \
-    CSGS_LAUNCH(K_CAND_PARTIALS, (cand_partials<TILES, PACK>), part_grid, dim3(CAND_PART_BLOCK), st, w.wtable, w.tileflag, n_words, g->n_nodes, \
+    CSGS_LAUNCH(K_CAND_PARTIALS, (cand_partials<TILES, PACK>), part.grid, dim3(CAND_PART_BLOCK), st, w.wtable, w.tileflag, n_words, g->n_nodes, \
                 w.n_tiles, g->local_lo, g->local_hi, rows.meta, stg, (int32_t)(tiles ? below : part_blocks), w.epoch,                   \
-                (unsigned long long *)w.partial, w.gtot, status, is)
+                (unsigned long long *)w.partial, w.gtot, status, part.is)
     const bool packed = wide || w.n_tiles * w.n_inst >= CAND_PACKED_FROM;   // (then `per` is CAND_PART_TILES)
     if (wide)
-        CSGS_LAUNCH(K_CAND_PARTIALS, bin_sums, part_grid, dim3(CAND_PART_BLOCK), st, w.wtable, w.tileflag, n_words, g->n_nodes, w.n_tiles, g->local_lo,
-                    g->local_hi, rows.meta, stg, w.epoch, (unsigned long long *)w.partial, w.gtot, status, is);
+        CSGS_LAUNCH(K_CAND_PARTIALS, bin_sums, part.grid, dim3(CAND_PART_BLOCK), st, w.wtable, w.tileflag, n_words, g->n_nodes, w.n_tiles, g->local_lo,
+                    g->local_hi, rows.meta, stg, w.epoch, (unsigned long long *)w.partial, w.gtot, status, part.is);
     else if (packed) CSGS_CAND_PARTIALS(CAND_PART_TILES, true);
     else if (per == 1) CSGS_CAND_PARTIALS(1, false);
     else CSGS_CAND_PARTIALS(CAND_PART_TILES, false);
 #undef CSGS_CAND_PARTIALS
     CSGS_LAUNCH_CHECK();
+    const InstGrid emit = inst_grid(w, packed ? (w.n_tiles + 3) / 4 : w.n_tiles, 256);
 #define CSGS_CAND_EMIT(PACKED)                                                                                                              \
-    CSGS_LAUNCH(K_CAND_EMIT, cand_emit<PACKED>, dim3((unsigned)(PACKED ? (w.n_tiles + 3) / 4 : w.n_tiles), 1, nz), dim3(256), st, w.wtable, \
+    CSGS_LAUNCH(K_CAND_EMIT, cand_emit<PACKED>, emit.grid, dim3(256), st, w.wtable, \
                 w.tileflag, n_words, g->n_nodes, w.n_tiles, g->local_lo, g->local_hi, pol, w.partial, w.gtot, rows.meta, shift_base, w.epoch, \
-                stats, status, cand_id, cand_w, cdf, q, cap, is)
+                stats, status, cand_id, cand_w, cdf, q, cap, emit.is)
     if (packed) CSGS_CAND_EMIT(true); else CSGS_CAND_EMIT(false);
 #undef CSGS_CAND_EMIT
     CSGS_LAUNCH_CHECK();

@@ -63,6 +63,8 @@ __global__ __launch_bounds__(DRAW_BLOCK) void draw(const uint64_t *__restrict__ 
                                                    uint64_t *__restrict__ epoch, uint64_t *__restrict__ rank,
                                                    uint64_t *__restrict__ member, int64_t n_nodes, InstStride is)
 {
+    is = at_instance(is);
+    const uint32_t blk = inst_block(is), n_blk = inst_blocks(is);
     __shared__ uint64_t top[TOP];
     cdf = inst_ptr(cdf, is.buf); stats = inst_ptr(stats, is.buf);
     hit = inst_ptr(hit, is.ws); cbitmap0 = inst_ptr(cbitmap0, is.ws); cbitmap1 = inst_ptr(cbitmap1, is.ws); epoch = inst_ptr(epoch, is.ws); rank = inst_ptr(rank, is.ws);
@@ -71,19 +73,19 @@ __global__ __launch_bounds__(DRAW_BLOCK) void draw(const uint64_t *__restrict__ 
     // entries could look current, so both tables are wiped once every 2^32 calls (the compaction kernel that
     // follows writes the new entries)
     if ((call_number(epoch) & 0xFFFFFFFFull) == 0) {
-        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_nodes; i += (int64_t)gridDim.x * blockDim.x) {
+        for (int64_t i = (int64_t)blk * blockDim.x + threadIdx.x; i < n_nodes; i += (int64_t)n_blk * blockDim.x) {
             rank[i] = 0ull;
             if (i < (n_nodes + 31) / 32) member[i] = 0ull;
         }
     }
     if (iter_dev) iter = *iter_dev;
-    iter += blockIdx.z;   // consecutive instances are consecutive iterations
+    iter += inst_index(is);   // consecutive instances are consecutive iterations
     const uint32_t iter_lo = (uint32_t)iter, iter_hi = (uint32_t)(iter >> 32);
     int64_t n = stats->n_cand;
     if (n > cand_cap) n = cand_cap;
     const uint64_t turn = epoch[EPOCH_BITMAP_NEXT] & 1ull;
     uint64_t *__restrict__ cbitmap = turn ? cbitmap1 : cbitmap0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {   // (nobody reads these words in this kernel)
+    if (blk == 0 && threadIdx.x == 0) {   // (nobody reads these words in this kernel)
         epoch[EPOCH_DRAW] = call_number(epoch);
         epoch[EPOCH_BITMAP_CUR] = turn;
         epoch[EPOCH_BITMAP_USED + turn] = (uint64_t)(n > 0 ? (n + 63) / 64 : 0);
@@ -96,7 +98,7 @@ __global__ __launch_bounds__(DRAW_BLOCK) void draw(const uint64_t *__restrict__ 
     const int64_t n_top = n / stride;  // number of complete strides
     for (int64_t i = threadIdx.x; i < n_top; i += blockDim.x) top[i] = cdf[(i + 1) * stride - 1];
     __syncthreads();
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t t = (int64_t)blk * blockDim.x + threadIdx.x;
     if (t >= B) return;
     const uint64_t r = philox_word((uint32_t)t, layer, iter_lo, iter_hi, seed_lo, seed_hi);
     const uint64_t u = __umul64hi(r, total);
@@ -196,6 +198,8 @@ __global__ __launch_bounds__(256) void hits(const int32_t *__restrict__ cand_id,
                                             double *__restrict__ pdbl, int32_t *__restrict__ n_next,
                                             uint64_t *__restrict__ ts_mem, int32_t *__restrict__ status, InstStride is)
 {
+    is = at_instance(is);
+    const uint32_t blk = inst_block(is), n_blk = inst_blocks(is);
     constexpr int SUB = 64;   // words listed at a time: four threads of 16 bits each per word
     __shared__ uint16_t s_list[SUB * 64];   // drawn positions of those words, ascending
     __shared__ uint32_t s_cnt[4], s_before[4];
@@ -218,15 +222,15 @@ __global__ __launch_bounds__(256) void hits(const int32_t *__restrict__ cand_id,
     if (n < 0) n = 0;
     const double total = (double)stats->total;   // = cdf[n - 1]
     const int64_t n_words = (n + 63) / 64;
-    if (blockIdx.x == 0 && tid == 0) {   // last kernel of the draw (nobody reads these words in this kernel)
+    if (blk == 0 && tid == 0) {   // last kernel of the draw (nobody reads these words in this kernel)
         epoch[EPOCH_CALLS] = call;
         epoch[EPOCH_BITMAP_NEXT] = turn ^ 1ull;
         if (n_words == 0) *n_next = 0;
     }
-    for (int64_t i = (int64_t)blockIdx.x * 256 + tid; i < old_words; i += (int64_t)gridDim.x * 256) old_bits[i] = 0ull;
-    int64_t wpb = ((n_words + gridDim.x - 1) / gridDim.x + 1) / 2 * 2;   // even
+    for (int64_t i = (int64_t)blk * 256 + tid; i < old_words; i += (int64_t)n_blk * 256) old_bits[i] = 0ull;
+    int64_t wpb = ((n_words + n_blk - 1) / n_blk + 1) / 2 * 2;   // even
     if (wpb < HIT_MIN_WORDS) wpb = HIT_MIN_WORDS;
-    const int64_t w0 = (int64_t)blockIdx.x * wpb, w1 = w0 + wpb < n_words ? w0 + wpb : n_words;
+    const int64_t w0 = (int64_t)blk * wpb, w1 = w0 + wpb < n_words ? w0 + wpb : n_words;
     if (w0 >= n_words) return;
     const uint64_t rank_tag = (call & 0xFFFFFFFFull) << 32;
     uint64_t word = w0 + (tid >> 2) < w1 ? bits[w0 + (tid >> 2)] : 0ull;
@@ -254,8 +258,8 @@ __global__ __launch_bounds__(256) void hits(const int32_t *__restrict__ cand_id,
         // (a count and one in the bits above it, so that no sum of these is ever taken for a tag)
         const unsigned long long local[1] = {(1ull << 52) + s_before[0] + s_before[1] + s_before[2] + s_before[3]};
         unsigned long long excl[1];
-        lookback_publish<1>(ts, tag, blockIdx.x, local);
-        lookback_resolve<1>(ts, tag, blockIdx.x, (n_words + wpb - 1) / wpb, local, excl, s_lb, status);
+        lookback_publish<1>(ts, tag, blk, local);
+        lookback_resolve<1>(ts, tag, blk, (n_words + wpb - 1) / wpb, local, excl, s_lb, status);
         before = (uint32_t)excl[0];   // (positions: below 2^31)
     }
     for (int64_t ws = w0; ws < w1; ws += SUB) {
@@ -490,25 +494,26 @@ __device__ inline void adj_values(const AdjChunk &s, const AdjGraph &g, const in
 __device__ inline bool adj_leading_blocks(RemoteArgs &rem, NextRows &nxt, const uint64_t *__restrict__ epoch, int32_t *__restrict__ status,
                                           const InstStride &is)
 {
+    const uint32_t blk = inst_block(is);
     // The first rem.blocks split the node set into local and remote (what csgs_remote_count does); they wait for nobody
     // and nobody waits for them.
-    if ((int32_t)blockIdx.x < rem.blocks) {
+    if ((int32_t)blk < rem.blocks) {
         rem.S_next = inst_ptr(rem.S_next, is.buf); rem.n_next = inst_ptr(rem.n_next, is.buf);
         rem.remote_total = inst_ptr(rem.remote_total, is.buf); rem.per_part = inst_ptr(rem.per_part, is.buf);
         rem.src_row = inst_ptr(rem.src_row, is.buf); rem.remote_ids = inst_ptr(rem.remote_ids, is.buf);
-        remote_count_body(rem, (int32_t)blockIdx.x, rem.blocks);
+        remote_count_body(rem, (int32_t)blk, rem.blocks);
         return true;
     }
     // The next nxt.blocks lay out the rows of the new node set.  They wait only for each other (lower tiles, dispatched
     // before them); their flags are tagged with the draw's call number, so the counter that a call's last kernel
     // advances does not matter.
-    if ((int32_t)blockIdx.x < rem.blocks + nxt.blocks) {
+    if ((int32_t)blk < rem.blocks + nxt.blocks) {
         nxt.S_next = inst_ptr(nxt.S_next, is.buf); nxt.n_next = inst_ptr(nxt.n_next, is.buf);
         nxt.ts_mem = inst_ptr(nxt.ts_mem, is.ws); nxt.eoff = inst_ptr(nxt.eoff, is.ws);
         nxt.rowstart = inst_ptr(nxt.rowstart, is.ws); nxt.meta = inst_ptr(nxt.meta, is.ws);
         nxt.bound_note = inst_ptr(nxt.bound_note, is.ws);
         const int32_t n = resolve_count(nxt.bound, nxt.n_next);
-        const int64_t t = (int64_t)blockIdx.x - rem.blocks, n_tiles = row_tiles(n);
+        const int64_t t = (int64_t)blk - rem.blocks, n_tiles = row_tiles(n);
         if (t < n_tiles) {
             const TileState<1> rts(nxt.ts_mem, nxt.ts_tiles, wait_limit(epoch));
             row_prefix_tile(nxt.rowptr, nxt.n_nodes, nxt.S_next, n, t, n_tiles, rts, call_tag(epoch[EPOCH_DRAW], SLOT_ROWS_NEXT),
@@ -538,14 +543,16 @@ __global__ __launch_bounds__(256) void adj_mark(AdjGraph g, const int64_t *__res
                                                 uint64_t *__restrict__ kept, int64_t kept_chunks, int32_t *__restrict__ adj_rowptr,
                                                 int32_t *__restrict__ status, RemoteArgs rem, NextRows nxt, InstStride is)
 {
+    is = at_instance(is);
+    const uint32_t blk = inst_block(is), n_blk = inst_blocks(is);
     epoch = inst_ptr(epoch, is.ws); status = inst_ptr(status, is.buf);
     if (adj_leading_blocks(rem, nxt, epoch, status, is)) return;
     meta = inst_ptr(meta, is.ws); g.eoff = inst_ptr(g.eoff, is.ws); g.rowstart = inst_ptr(g.rowstart, is.ws);
     g.rank = inst_ptr(g.rank, is.ws); g.member = inst_ptr(g.member, is.ws); g.pdbl = inst_ptr(g.pdbl, is.ws);
     bound_note = inst_ptr(bound_note, is.ws); chunk_cnt = inst_ptr(chunk_cnt, is.ws); kept = inst_ptr(kept, is.ws);
     adj_rowptr = inst_ptr(adj_rowptr, is.buf);
-    const int64_t bid = (int64_t)blockIdx.x - rem.blocks - nxt.blocks;
-    const int64_t n_bids = (int64_t)gridDim.x - rem.blocks - nxt.blocks;
+    const int64_t bid = (int64_t)blk - rem.blocks - nxt.blocks;
+    const int64_t n_bids = (int64_t)n_blk - rem.blocks - nxt.blocks;
     ChunkRows rows = chunk_rows(bound_note, bid, bid + 1);   // (the grid stays within the notes; on its way beside the counts)
     __shared__ AdjChunk s;
     const uint64_t rank_tag = (epoch[EPOCH_DRAW] & 0xFFFFFFFFull) << 32;
@@ -585,6 +592,8 @@ __global__ __launch_bounds__(256) void adj_place(AdjGraph g, const int64_t *__re
                                                  int32_t *__restrict__ adj_col, float *__restrict__ adj_val, int64_t adj_cap,
                                                  int64_t *__restrict__ adj_nnz, int32_t *__restrict__ status, InstStride is)
 {
+    is = at_instance(is);
+    const uint32_t blk = inst_block(is), n_blk = inst_blocks(is);
     __shared__ uint32_t s_scan[17];
     __shared__ uint32_t s_cnt[256], s_base[256];
     __shared__ ChunkRows s_rows[256];
@@ -605,19 +614,19 @@ __global__ __launch_bounds__(256) void adj_place(AdjGraph g, const int64_t *__re
     int64_t n_chunks = (E + EDGE_TILE - 1) / EDGE_TILE;
     const bool overflow = n_chunks > chunk_cap;   // the workspace cannot describe this many chunks: report, emit nothing
     if (overflow) { E = 0; n_chunks = 0; }
-    if (blockIdx.x == 0 && tid == 0) {
+    if (blk == 0 && tid == 0) {
         epoch[EPOCH_CALLS] += 1ull;   // last kernel of the call; no block of this kernel or of the marking pass reads the counter
         if (overflow) atomicOr(status, CSGS_ST_EDGE_OVERFLOW);
         if (n_chunks == 0) *adj_nnz = 0;
     }
     if (n_chunks == 0) {
-        if (blockIdx.x == 0)
+        if (blk == 0)
             for (int32_t a = tid; a <= nS; a += 256) adj_rowptr[a] = 0;
         return;
     }
-    int64_t per = (n_chunks + gridDim.x - 1) / gridDim.x;
+    int64_t per = (n_chunks + n_blk - 1) / n_blk;
     if (per < ADJ_PLACE_MIN) per = ADJ_PLACE_MIN;
-    const int64_t t0 = (int64_t)blockIdx.x * per, t1 = t0 + per < n_chunks ? t0 + per : n_chunks;
+    const int64_t t0 = (int64_t)blk * per, t1 = t0 + per < n_chunks ? t0 + per : n_chunks;
     if (t0 >= n_chunks) return;
     constexpr uint32_t CNT = 0x7FFFFFFFu;
     uint64_t base = 0;   // kept edges before chunk t0 (then before the chunks at hand)
@@ -701,6 +710,7 @@ __global__ __launch_bounds__(256) void adj_once(AdjGraph g, const int64_t *__res
                                                 float *__restrict__ adj_val, int64_t adj_cap, int64_t *__restrict__ adj_nnz,
                                                 int32_t *__restrict__ status, RemoteArgs rem, NextRows nxt, InstStride is)
 {
+    is = at_instance(is);
     epoch = inst_ptr(epoch, is.ws); status = inst_ptr(status, is.buf);
     if (adj_leading_blocks(rem, nxt, epoch, status, is)) return;
     meta = inst_ptr(meta, is.ws); g.eoff = inst_ptr(g.eoff, is.ws); g.rowstart = inst_ptr(g.rowstart, is.ws);
@@ -796,17 +806,17 @@ extern "C" int csgs_draw_nodes(int64_t n_nodes, const int32_t *cand_id, const ui
     hipStream_t st = (hipStream_t)stream;
     if (cand_cap > n_nodes) cand_cap = n_nodes;  // there are never more candidates than nodes
 
-    const unsigned nz = (unsigned)w.n_inst;
-    const InstStride is = inst_stride(w);
-    CSGS_LAUNCH(K_DRAW, draw, dim3((unsigned)((B + DRAW_BLOCK - 1) / DRAW_BLOCK), 1, nz), dim3(DRAW_BLOCK), st, cdf, stats,
+    const InstGrid dg = inst_grid(w, ((int64_t)B + DRAW_BLOCK - 1) / DRAW_BLOCK, DRAW_BLOCK);
+    CSGS_LAUNCH(K_DRAW, draw, dg.grid, dim3(DRAW_BLOCK), st, cdf, stats,
                 cand_cap, B, (uint32_t)seed, (uint32_t)(seed >> 32), iter, iter_dev, layer, w.hit, w.cbitmap[0], w.cbitmap[1], w.epoch, w.rank,
-                w.member, n_nodes, is);
+                w.member, n_nodes, dg.is);
     CSGS_LAUNCH_CHECK();
     const int64_t cap_words = (cand_cap + 63) / 64;
     const int64_t hit_blocks = (cap_words + HIT_MIN_WORDS - 1) / HIT_MIN_WORDS;
-    CSGS_LAUNCH(K_HITS, hits, dim3((unsigned)(hit_blocks < HIT_GRID ? hit_blocks : HIT_GRID), 1, nz), dim3(256), st, cand_id,
+    const InstGrid hg = inst_grid(w, hit_blocks < HIT_GRID ? hit_blocks : HIT_GRID, 256);
+    CSGS_LAUNCH(K_HITS, hits, hg.grid, dim3(256), st, cand_id,
                 cdf, stats, cand_cap, n_nodes, B, w.epoch, w.hit, w.cbitmap[0], w.cbitmap[1], w.rank, w.member, S_next, mult, p_incl,
-                w.pdbl, n_next, w.hit_ts, status, is);
+                w.pdbl, n_next, w.hit_ts, status, hg.is);
     CSGS_LAUNCH_CHECK();
     ws->has_draw = 1;
     ws->draw_B = B;
@@ -858,23 +868,21 @@ static int sampled_adjacency_impl(const csgs_graph *g, const int32_t *rows, int3
         const int64_t cap = (w.chunk_cap + chunks_each - 1) / chunks_each;
         return (unsigned)(n < cap ? n : cap);
     };
-    const unsigned nz = (unsigned)w.n_inst;
-    const InstStride is = inst_stride(w);
     const AdjGraph ag{g->colidx, g->val, g->n_nodes, g->nnz, cur.eoff, cur.rowstart, w.rank, w.member, w.pdbl};
     if (expected * w.n_inst <= (w.n_inst == 1 ? ADJ_ONCE_MAX : ADJ_ONCE_MAX_EACH)) {
-        const dim3 grid_once(blocks(resident_grid(2), 1) + (unsigned)(rem.blocks + nxt.blocks), 1, nz);
+        const dim3 grid_once(blocks(resident_grid(2), 1) + (unsigned)(rem.blocks + nxt.blocks), 1, (unsigned)w.n_inst);   // (its blocks wait for each other: an instance after the other)
         CSGS_LAUNCH(K_ADJ_ONCE, adj_once, grid_once, dim3(256), st, ag, cur.meta, w.epoch, w.adj_ts, w.chunk_cap, cur.bound_note,
-                    adj_rowptr, adj_col, adj_val, adj_cap, adj_nnz, status, rem, nxt, is);
+                    adj_rowptr, adj_col, adj_val, adj_cap, adj_nnz, status, rem, nxt, inst_stride(w));
         CSGS_LAUNCH_CHECK();
         return CSGS_OK;
     }
     const unsigned mark = blocks(ADJ_MARK_GRID, 1), place = blocks(ADJ_PLACE_GRID, ADJ_PLACE_MIN);
-    const dim3 grid(mark + (unsigned)(rem.blocks + nxt.blocks), 1, nz);
-    CSGS_LAUNCH(K_ADJ_MARK, adj_mark, grid, dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.bound_note, w.adj_cnt, w.stage,
-                w.stage_chunks, adj_rowptr, status, rem, nxt, is);
+    const InstGrid mg = inst_grid(w, mark + (int64_t)(rem.blocks + nxt.blocks), 256), pg = inst_grid(w, place, 256);
+    CSGS_LAUNCH(K_ADJ_MARK, adj_mark, mg.grid, dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.bound_note, w.adj_cnt, w.stage,
+                w.stage_chunks, adj_rowptr, status, rem, nxt, mg.is);
     CSGS_LAUNCH_CHECK();
-    CSGS_LAUNCH(K_ADJ_PLACE, adj_place, dim3(place, 1, nz), dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.bound_note, w.adj_cnt,
-                w.stage, w.stage_chunks, adj_rowptr, adj_col, adj_val, adj_cap, adj_nnz, status, is);
+    CSGS_LAUNCH(K_ADJ_PLACE, adj_place, pg.grid, dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.bound_note, w.adj_cnt,
+                w.stage, w.stage_chunks, adj_rowptr, adj_col, adj_val, adj_cap, adj_nnz, status, pg.is);
     CSGS_LAUNCH_CHECK();
     return CSGS_OK;
 }
