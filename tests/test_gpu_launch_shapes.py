@@ -604,3 +604,32 @@ def test_aggregate_gradient_one_launch(dev, nS, n_cols, most, hub):
         got.append(dH.cpu().numpy())
     chain.assert_close(got[0], oracle.aggregate_grad(rp, col, val, n_cols, dZ, H), chain.RTOL, chain.ATOL, "dH")
     np.testing.assert_array_equal(got[0], got[1])
+
+
+# Where the last chunk of edges ends: rows without edges behind the last one that has some, in its tile of rows and in tiles of their own, before the first
+# one, none at all; edges that end on a chunk's boundary, one short of it and one beyond; the adjacency in one pass and in two.
+@pytest.mark.parametrize("before,with_edges,degree,behind", [(0, 500, 3, 20), (0, 1024, 1, 3000), (3, 341, 3, 3000), (1030, 41, 25, 2000), (0, 1, 2047, 1500), (2100, 5, 1, 0),
+                                                             (0, 9000, 80, 2500), (40, 8192, 80, 0)])
+def test_rows_without_edges_around_the_last_chunk(dev, before, with_edges, degree, behind):
+    from paper_2101_07706_amd import csgs, pipeline
+    rng = np.random.default_rng(before + with_edges)
+    n, B = before + with_edges + behind + 900, 400
+    deg = np.zeros(n, np.int64)
+    deg[before:before + with_edges] = degree
+    rowptr = np.zeros(n + 1, np.int64)
+    np.cumsum(deg, out=rowptr[1:])
+    col = np.concatenate([np.sort(rng.choice(n, d, replace=False)) for d in deg[deg > 0]]).astype(np.int32)
+    g = synth.Graph(n, rowptr, col, (rng.random(len(col)) / degree).astype(np.float32), synth.partition_bounds(n, 3), 0, 1.0)
+    S = np.arange(before + with_edges + behind, dtype=np.int32)
+    dg, Sd = pipeline.DeviceGraph(g, dev), torch.from_numpy(S).to(dev)
+    ws, lb = pipeline.Workspace(n, len(S), B, g.nnz, dev), pipeline.LayerBuffers(len(S), B, n, g.nnz, 3, dev)
+    lb.adj_rowptr.fill_(-7)
+    pipeline.sample_step(dg, ws, Sd, 4.0, B, 5, 3, 0, lb)
+    want = oracle.build_probs(g, S, 4.0)
+    got = oracle.sample_layer(g, S, want, B, 5, 3, 0)
+    n_c, m, nnz = len(want.cand_id), got.n_next, got.adj_nnz
+    assert int(lb.status.item()) == 0 and int(lb.n_next.item()) == m and int(lb.adj_nnz.item()) == nnz
+    np.testing.assert_array_equal(lb.cand_id[:n_c].cpu().numpy(), want.cand_id)
+    np.testing.assert_array_equal(lb.cdf[:n_c].cpu().numpy().view(np.uint64), want.cdf)
+    np.testing.assert_array_equal(lb.adj_rowptr[:len(S) + 1].cpu().numpy(), got.adj_rowptr)
+    np.testing.assert_array_equal(lb.adj_col[:nnz].cpu().numpy(), got.adj_col)
