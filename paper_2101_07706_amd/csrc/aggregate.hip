@@ -32,14 +32,13 @@ __global__ __launch_bounds__(AGG_BLOCK) void aggregate_k(const int32_t *__restri
                                                          const float *__restrict__ mask, int64_t ldm,
                                                          int32_t n_slices, int32_t tr, CompStride cs)
 {
-    cs = at_instance(cs);
     __shared__ WaveStage<tile_rows(G)> stage[AGG_WAVES];
     __shared__ double heads[AGG_WAVES][WAVE * V], carries[AGG_WAVES][2 * G * V];
     const int32_t slice = (int32_t)(blockIdx.x % (unsigned)n_slices);
     const int64_t block_row0 = (int64_t)(blockIdx.x / (unsigned)n_slices) * (AGG_WAVES * tr);
-    adj_rowptr = inst_ptr(adj_rowptr, cs.adj); adj_col = inst_ptr(adj_col, cs.adj); adj_val = inst_ptr(adj_val, cs.adj);
-    nS_dev = inst_ptr(nS_dev, cs.adj); n_cols_p = inst_ptr(n_cols_p, cs.adj); src_row = inst_ptr(src_row, cs.adj);
-    Xl = inst_ptr(Xl, cs.x); Xr = inst_ptr(Xr, cs.xr); Z = inst_ptr(Z, cs.out);
+    adj_rowptr = comp_ptr(adj_rowptr, cs.adj); adj_col = comp_ptr(adj_col, cs.adj); adj_val = comp_ptr(adj_val, cs.adj);
+    nS_dev = comp_ptr(nS_dev, cs.adj); n_cols_p = comp_ptr(n_cols_p, cs.adj); src_row = comp_ptr(src_row, cs.adj);
+    Xl = comp_ptr(Xl, cs.x); Xr = comp_ptr(Xr, cs.xr); Z = comp_ptr(Z, cs.out);
     // the two counts that may live on the device are asked for together; a count that is not given is read from a
     // stand-in address and dropped
     const int32_t nS_raw = *(nS_dev ? nS_dev : adj_rowptr);
@@ -610,9 +609,8 @@ __global__ __launch_bounds__(256) void gather_rows_k(const U *__restrict__ X, in
                                                      const int64_t *__restrict__ n_dev, U *__restrict__ out,
                                                      int64_t ldo, CompStride cs)
 {
-    cs = at_instance(cs);
     constexpr int32_t SIZE = (int32_t)sizeof(U);
-    X = inst_ptr(X, cs.x); ids = inst_ptr(ids, cs.adj); n_dev = inst_ptr(n_dev, cs.adj); out = inst_ptr(out, cs.out);
+    X = comp_ptr(X, cs.x); ids = comp_ptr(ids, cs.adj); n_dev = comp_ptr(n_dev, cs.adj); out = comp_ptr(out, cs.out);
     int64_t n = cap;
     if (n_dev) {
         const int64_t d = *n_dev;

@@ -132,10 +132,11 @@ struct CompStride {
     int64_t xr;    // staged remote rows
     int64_t out;   // the output matrix
 };
-__device__ inline CompStride at_instance(const CompStride &cs)
+// A pointer of this block's instance; the compute kernels take an instance after the other.
+template <typename T>
+__device__ inline T *comp_ptr(T *p, int64_t stride)
 {
-    const int64_t k = blockIdx.z;
-    return CompStride{cs.adj * k, cs.x * k, cs.xr * k, cs.out * k};
+    return p ? (T *)((char *)const_cast<typename std::remove_const<T>::type *>(p) + (int64_t)blockIdx.z * stride) : p;
 }
 struct CompInst {
     int32_t n = 1;

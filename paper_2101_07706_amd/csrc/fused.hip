@@ -38,7 +38,6 @@ __global__ __launch_bounds__(AGG_BLOCK, 3) void layer_forward_k(const int32_t *_
                                                                 float *__restrict__ H, int64_t ldh,
                                                                 float *__restrict__ Zout, int64_t ldz, CompStride cs, int64_t z_stride)
 {
-    cs = at_instance(cs);
     constexpr int V = KP / WAVE;
     constexpr int G = WAVE;
     constexpr int TR = tile_rows(G);
@@ -54,9 +53,9 @@ __global__ __launch_bounds__(AGG_BLOCK, 3) void layer_forward_k(const int32_t *_
     double *part = reinterpret_cast<double *>(work);
 
     const int64_t block_row0 = (int64_t)blockIdx.x * FUSED_ROWS;
-    adj_rowptr = inst_ptr(adj_rowptr, cs.adj); adj_col = inst_ptr(adj_col, cs.adj); adj_val = inst_ptr(adj_val, cs.adj);
-    nS_dev = inst_ptr(nS_dev, cs.adj); n_cols_p = inst_ptr(n_cols_p, cs.adj); src_row = inst_ptr(src_row, cs.adj);
-    Xl = inst_ptr(Xl, cs.x); Xr = inst_ptr(Xr, cs.xr); H = inst_ptr(H, cs.out); Zout = inst_ptr(Zout, z_stride * blockIdx.z);
+    adj_rowptr = comp_ptr(adj_rowptr, cs.adj); adj_col = comp_ptr(adj_col, cs.adj); adj_val = comp_ptr(adj_val, cs.adj);
+    nS_dev = comp_ptr(nS_dev, cs.adj); n_cols_p = comp_ptr(n_cols_p, cs.adj); src_row = comp_ptr(src_row, cs.adj);
+    Xl = comp_ptr(Xl, cs.x); Xr = comp_ptr(Xr, cs.xr); H = comp_ptr(H, cs.out); Zout = comp_ptr(Zout, z_stride);
     const int32_t nS_raw = *(nS_dev ? nS_dev : adj_rowptr);
     const int32_t n_cols_raw = *(n_cols_p ? n_cols_p : adj_rowptr);
     const int32_t nS = !nS_dev ? nS_bound : (nS_raw < 0 ? 0 : (nS_raw < nS_bound ? nS_raw : nS_bound));

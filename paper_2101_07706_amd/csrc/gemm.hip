@@ -90,10 +90,9 @@ __global__ __launch_bounds__(256, RT * NT >= 6 ? 2 : (RT * NT >= 4 ? 3 : 4)) voi
     double *__restrict__ partial, int M_bound, int N, int K_bound, const int32_t *__restrict__ rows_dev, int tiles_n, int n_tiles,
     int n_blocks, CompStride cs)
 {
-    cs = at_instance(cs);
     constexpr bool DW = MODE == MODE_DW, B_KMAJOR = MODE == MODE_DZ;
     constexpr int BM = 16 * RT, BN = 16 * NT;
-    A = inst_ptr(A, cs.x); C = inst_ptr(C, cs.out); rows_dev = inst_ptr(rows_dev, cs.adj);   // B (the weights) is shared
+    A = comp_ptr(A, cs.x); C = comp_ptr(C, cs.out); rows_dev = comp_ptr(rows_dev, cs.adj);   // B (the weights) is shared
     const int lane = (int)(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int grp = lane >> 4, l16 = lane & 15;
     // XCD-aware tile order: hardware deals consecutive block ids round-robin to the 8 XCDs
