@@ -406,29 +406,57 @@ __global__ __launch_bounds__(256) void adjT_order(const int32_t *__restrict__ co
 }
 
 // The same in one launch for few entries: a block owns consecutive columns and looks at the columns of all entries itself (4 bytes each, from the
-// L2s), so that nothing has to be cleared, counted with atomics or waited for between launches.  It keeps its columns' entries in LDS,
-// an entry's place being the number of earlier entries of its column (entries of a row ascend, so earlier ones have smaller rows), and
-// finds an entry's row in the row pointers.  Where a block's entries do not fit, it takes the entries LIST at a time.
-// (us, five launches / this: 4096 rows of 6.2 K entries 16 / 7, 8192 rows of 21 K entries with columns of up to 306 27 / 15; reading a column's entries one
-// after the other for the places made that 25.)
-constexpr int ONE_BLOCK = 1024, ONE_GRID = 256, ONE_LIST = 8192;
-constexpr int64_t ONE_ENTRIES = 1ll << 19;   // most (the caller's bound): every block reads them all
-constexpr int32_t ONE_COLS = 65536;          // most columns
+// L2s), so that nothing has to be cleared, counted with atomics or waited for between launches.  Its wavefronts take consecutive shares of the
+// entries (ascending entries have ascending rows): each counts those of the block's columns by column and lists them in LDS, in order, so that after
+// one prefix over columns and wavefronts an entry's place is the next one of its wavefront and column -- linear in the entries, however
+// long a column is.  Wavefronts of a block whose lists outgrow LDS read their shares again.  An entry's row is searched for in the row pointers.
+// Bound by latency up to 20 K entries, from 100 K on by the instructions that look at every entry in every block.  (us of csgs_aggregate_grad with 8
+// features, several launches / this: 2 K entries of 8192 columns 22 / 13.5, 20 K 22 / 15.5, 131 K 36.6 / 32; 20 K and a column of 257
+// 31 / 19, of 2049 79 / 33, of 8192 248 / 67, of 60 K 1704 / 423; comparing the entries of a column with each other for their places made those
+// 23, 107, 391 and 6740.)
+constexpr int ONE_BLOCK = 1024, ONE_WAVES = ONE_BLOCK / WAVE, ONE_GRID = 256;
+constexpr int ONE_CHUNKS = 192;   // pieces of 64 entries that LDS holds; a wavefront chains as many as it needs
+constexpr int32_t ONE_COLS = 65536;   // most columns
 constexpr int ONE_OWN = ONE_COLS / ONE_GRID;
-static_assert(ONE_OWN <= 4 * WAVE, "columns of a block: four per lane");
+// Most entries, as the caller bounds them (the spare room of its arrays costs nothing).  With arrays that are full (us as above): 262 K entries of 256 columns
+// 684 / 159, of 8192 54.7 / 53.5, of 65536 59.6 / 51.3; 520 K 1299 / 287, 104 / 97 and 88.5 / 96; 1.04 M 2107 / 483, 160 / 181, 148 / 180.  More columns
+// than ONE_WIDE hold few entries each, which the several launches order well.
+constexpr int64_t ONE_ENTRIES = 1ll << 19, ONE_ENTRIES_WIDE = 3ll << 17;
+constexpr int32_t ONE_WIDE = 8192;
+static_assert(ONE_OWN == 256 && ONE_ENTRIES <= 1 << 24, "an entry and its column in 32 bits");
+
+// The row of an entry: last r with adj_rowptr[r] <= e, by eighths (the loads of a round together).  nS > 0.
+__device__ inline int32_t entry_row(const int32_t *__restrict__ adj_rowptr, int32_t nS, int32_t e)
+{
+    int32_t lo = 0, hi = nS;   // adj_rowptr[lo] <= e < adj_rowptr[hi]
+    while (hi - lo > 1) {
+        const int32_t span = hi - lo;
+        int32_t p[7];
+#pragma unroll
+        for (int k = 0; k < 7; ++k) p[k] = adj_rowptr[lo + (int32_t)((int64_t)span * (k + 1) / 8)];
+        int below = 0;
+#pragma unroll
+        for (int k = 0; k < 7; ++k) below += p[k] <= e ? 1 : 0;
+        const int32_t new_lo = lo + (int32_t)((int64_t)span * below / 8);
+        hi = below < 7 ? lo + (int32_t)((int64_t)span * (below + 1) / 8) : hi;
+        lo = new_lo;
+    }
+    return lo;
+}
 
 __global__ __launch_bounds__(ONE_BLOCK) void adjT_one(const int32_t *__restrict__ adj_rowptr, const int32_t *__restrict__ adj_col,
                                                       const float *__restrict__ adj_val, int32_t nS_bound, const int32_t *__restrict__ nS_dev,
                                                       int32_t n_cols_bound, const int32_t *__restrict__ n_cols_dev, int64_t cap,
                                                       int32_t *__restrict__ colptr, int32_t *__restrict__ rowT, float *__restrict__ valT)
 {
-    constexpr int U = 8;   // entries on their way per thread
-    __shared__ int32_t l_e[ONE_LIST], g_e[ONE_LIST];   // entries of my columns, in any order; grouped by column
-    __shared__ uint16_t l_c[ONE_LIST];                 // their columns
-    __shared__ int32_t cnt[ONE_OWN], pre[ONE_OWN], fill[ONE_OWN], done[ONE_OWN];
-    __shared__ int32_t n_list, s_before[ONE_BLOCK / WAVE], s_base;
+    constexpr int U = 8;                                 // entries on their way per lane
+    __shared__ uint32_t l_e[ONE_CHUNKS * WAVE];          // an entry (from the first one) << 8 | its column (from the block's first)
+    __shared__ uint16_t l_next[ONE_CHUNKS];              // the wavefront's piece after this one
+    __shared__ int32_t l_s[ONE_CHUNKS * WAVE];           // the entries in their places
+    __shared__ int32_t at[ONE_WAVES][ONE_OWN];           // entries of a wavefront's share by column, then their next place
+    __shared__ int32_t n_pieces, s_before[ONE_WAVES], s_own[ONE_OWN / WAVE];   // of entries: before the block's columns, by wavefront; in 64 of them
     const int32_t nS = resolve_count(nS_bound, nS_dev), n_cols = resolve_count(n_cols_bound, n_cols_dev);
-    const int tid = (int)threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
+    const int tid = (int)threadIdx.x, lane = tid & (WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t own = (n_cols + ONE_GRID - 1) / ONE_GRID;   // at most ONE_OWN
     const int32_t c0 = (int32_t)blockIdx.x * own, c1 = c0 + own < n_cols ? c0 + own : n_cols;
     if (c0 >= n_cols) {
@@ -439,134 +467,146 @@ __global__ __launch_bounds__(ONE_BLOCK) void adjT_one(const int32_t *__restrict_
     int32_t e_beg = nS > 0 ? adj_rowptr[0] : 0, e_end = nS > 0 ? adj_rowptr[nS] : 0;
     if (e_beg < 0) e_beg = 0;
     if (e_end > cap) e_end = (int32_t)cap;
-    for (int i = tid; i < ONE_OWN; i += ONE_BLOCK) { cnt[i] = 0; done[i] = 0; }
-    if (tid == 0) n_list = 0;
+    if (e_end < e_beg) e_end = e_beg;
+    for (int i = tid; i < ONE_WAVES * ONE_OWN; i += ONE_BLOCK) (&at[0][0])[i] = 0;
+    if (tid == 0) n_pieces = ONE_WAVES;   // a wavefront's first piece is its own
     __syncthreads();
-    // counts of my columns, entries of the columns before them
-    int32_t before = 0;
-    for (int64_t e0 = (int64_t)e_beg + tid; e0 < e_end; e0 += U * ONE_BLOCK) {
-        int32_t c[U];
+    // the wavefront's share (blocks begin at different ones, so that they don't ask the same pieces of an L2 for the same lines at once)
+    const int part = (wave + (int)blockIdx.x) % ONE_WAVES;
+    const int32_t share = (e_end - e_beg + ONE_BLOCK - 1) / ONE_BLOCK * WAVE;
+    const int32_t w0 = e_beg + part * share < e_end ? e_beg + part * share : e_end, w1 = w0 + share < e_end ? w0 + share : e_end;
+    const uint64_t lanes_below = (1ull << lane) - 1ull;
+    const uint32_t n_mine = (uint32_t)(c1 - c0);
+    int32_t before = 0, n_listed = 0, piece = part, used = 0;   // entries of columns before the block's (lane by lane); of its own, listed
+    bool listed = true;
+    int32_t c[U], next_c[U];
+    auto wide = [&](int32_t e) {   // (entries start anywhere)
 #pragma unroll
-        for (int u = 0; u < U; ++u) c[u] = adj_col[e0 + u * ONE_BLOCK < e_end ? e0 + u * ONE_BLOCK : e0];
+        for (int u = 0; u < U; u += 4) {
+            const u32x4 v = load_global<u32x4, 4>(adj_col + e + u);
+            next_c[u] = (int32_t)v.x; next_c[u + 1] = (int32_t)v.y; next_c[u + 2] = (int32_t)v.z; next_c[u + 3] = (int32_t)v.w;
+        }
+    };
+    for (int32_t from = w0;; from += U * WAVE) {   // asks for the entries from here on, looks at the ones before; a lane's U lie side by side
+        const int32_t e = from + lane * U;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (e0 + u * ONE_BLOCK >= e_end || c[u] < 0) continue;
-            before += c[u] < c0 ? 1 : 0;
-            if (c[u] < c0 || c[u] >= c1) continue;
-            atomicAdd(&cnt[c[u] - c0], 1);
-            const int32_t at = atomicAdd(&n_list, 1);
-            if (at < ONE_LIST) {
-                l_e[at] = (int32_t)(e0 + u * ONE_BLOCK);
-                l_c[at] = (uint16_t)(c[u] - c0);
+        for (int u = 0; u < U; ++u) c[u] = next_c[u];
+        if (from + U * WAVE <= w1) {
+            wide(e);
+        } else if (from < w1) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) next_c[u] = -1;   // (a negative column is nobody's)
+            if (e + U <= w1) wide(e);
+            else
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (e + u < w1) next_c[u] = adj_col[e + u];
+        }
+        if (from > w0) {
+            uint32_t mine = 0;   // which of the lane's entries are of the block's columns
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                before += (uint32_t)c[u] < (uint32_t)c0 ? 1 : 0;
+                mine |= (uint32_t)(c[u] - c0) < n_mine ? 1u << u : 0u;
+            }
+            if (__any(mine)) {
+                const int32_t n = __popc(mine), incl = wave_inclusive_scan<int32_t>(n), total = __builtin_amdgcn_readlane(incl, WAVE - 1);
+                const int32_t fresh = (used + total - 1) / WAVE;   // pieces begun
+                int32_t next = piece, i = used + incl - n;
+                if (listed && fresh) {
+                    if (lane == 0) next = atomicAdd(&n_pieces, fresh);
+                    next = __builtin_amdgcn_readfirstlane(next);
+                    listed = next + fresh <= ONE_CHUNKS;
+                    if (listed && lane < fresh) l_next[lane ? next + lane - 1 : piece] = (uint16_t)(next + lane);
+                }
+                for (uint32_t m = mine; m; m &= m - 1u, ++i) {
+                    const int u = __ffs((int)m) - 1;
+                    int32_t d = c[0];
+#pragma unroll
+                    for (int k = 1; k < U; ++k) d = u == k ? c[k] : d;
+                    d -= c0;
+                    atomicAdd(&at[part][d], 1);
+                    if (listed) l_e[i < WAVE ? piece * WAVE + i : next * WAVE + i - WAVE] = (uint32_t)(e - U * WAVE + u - e_beg) << 8 | (uint32_t)d;
+                }
+                used += total - fresh * WAVE;
+                piece = fresh ? next + fresh - 1 : piece;
+                n_listed += total;
             }
         }
+        if (from >= w1) break;
     }
     before = wave_sum(before);
     if (lane == 0) s_before[wave] = before;
     __syncthreads();
-    const int32_t n_own = n_list;   // entries of my columns
-    auto group = [&](bool first) {   // wavefront 0: pre = exclusive prefix of cnt (first: and the column offsets)
-        int32_t v[4], sum = 0;
+    // a thread per column: where it begins, and each share's entries of it
+    int32_t n_col[ONE_WAVES], sum = 0, end = 0;
+    if (tid < ONE_OWN) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            v[k] = lane * 4 + k < ONE_OWN ? cnt[lane * 4 + k] : 0;
-            sum += v[k];
+        for (int w = 0; w < ONE_WAVES; ++w) {
+            n_col[w] = at[w][tid];
+            sum += n_col[w];
         }
-        int32_t ex = wave_inclusive_scan<int32_t>(sum) - sum;
-        int32_t base = 0;
-        if (first) {
-            base = lane < ONE_BLOCK / WAVE ? s_before[lane] : 0;
-            base = wave_sum(base);
-            if (lane == 0) s_base = base;
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int32_t i = lane * 4 + k;
-            if (i < ONE_OWN) {
-                pre[i] = ex;
-                fill[i] = 0;
-                if (first && c0 + i < c1) colptr[c0 + i] = base + ex;
-            }
-            ex += v[k];
-        }
-        if (first && c1 == n_cols && lane == WAVE - 1) colptr[n_cols] = base + ex;
-    };
-    if (wave == 0) group(true);
-    __syncthreads();
-    const int32_t base = s_base;
-    const bool fits = n_own <= ONE_LIST;
-    // where a column's entries begin in the lists (colptr again, for the windows below, whose counts replace cnt and pre)
-    int32_t *__restrict__ const first = fits ? pre : done;
-    if (!fits) {
-        for (int i = tid; i < ONE_OWN; i += ONE_BLOCK) done[i] = pre[i];
-        __syncthreads();
+        end = wave_inclusive_scan<int32_t>(sum);
+        if (lane == WAVE - 1) s_own[wave] = end;
     }
-    for (int64_t w0 = e_beg; w0 < e_end; w0 += ONE_LIST) {
-        int32_t n = n_own;
-        if (!fits) {   // the entries of my columns among the next ONE_LIST
-            for (int i = tid; i < ONE_OWN; i += ONE_BLOCK) cnt[i] = 0;
-            if (tid == 0) n_list = 0;
-            __syncthreads();
-            const int64_t w1 = w0 + ONE_LIST < e_end ? w0 + ONE_LIST : e_end;
-            for (int64_t e = w0 + tid; e < w1; e += ONE_BLOCK) {
-                const int32_t c = adj_col[e];
-                if (c < c0 || c >= c1) continue;
-                atomicAdd(&cnt[c - c0], 1);
-                const int32_t at = atomicAdd(&n_list, 1);   // < ONE_LIST
-                l_e[at] = (int32_t)e;
-                l_c[at] = (uint16_t)(c - c0);
-            }
-            __syncthreads();
-            n = n_list;
-            if (wave == 0) group(false);
-            __syncthreads();
+    __syncthreads();
+    const int32_t base = wave_sum(lane < ONE_WAVES ? s_before[lane] : 0), n_own = wave_sum(lane < ONE_OWN / WAVE ? s_own[lane] : 0);
+    if (tid < ONE_OWN) {
+        end += base + wave_sum(lane < wave ? s_own[lane] : 0);
+        int32_t place = end - sum;
+        if (tid < c1 - c0) colptr[c0 + tid] = place;
+        if (tid == c1 - c0 - 1 && c1 == n_cols) colptr[n_cols] = end;
+#pragma unroll
+        for (int w = 0; w < ONE_WAVES; ++w) {
+            at[w][tid] = place;
+            place += n_col[w];
         }
-        for (int32_t i = tid; i < n; i += ONE_BLOCK) g_e[pre[l_c[i]] + atomicAdd(&fill[l_c[i]], 1)] = l_e[i];
+    }
+    __syncthreads();
+    // places of a wavefront's next 64 entries (lanes that `have` one), in order: lanes of the same column find each other bit by bit
+    const int bits = own > 1 ? 32 - __clz(own - 1) : 0;
+    auto place = [&](bool have, int32_t d) {
+        uint64_t same = __ballot(have);
+        for (int b = 0; b < bits; ++b) {
+            const uint64_t set = __ballot((d >> b) & 1);
+            same &= (d >> b) & 1 ? set : ~set;
+        }
+        const int32_t rank = __popcll(same & lanes_below);
+        int32_t p = 0;
+        if (have && rank == 0) p = atomicAdd(&at[part][d], __popcll(same));
+        __builtin_amdgcn_wave_barrier();   // (the wavefront's next 64 come after these)
+        return __shfl(p, have ? __ffsll((long long)same) - 1 : lane, WAVE) + rank;
+    };
+    auto put = [&](int32_t p, int32_t row, float v) {
+        if (p < cap) {
+            rowT[p] = row;
+            valT[p] = v;
+        }
+    };
+    if (n_pieces <= ONE_CHUNKS) {   // (so all wavefronts have listed theirs)
+        for (int32_t left = n_listed, piece = part; left > 0; left -= WAVE) {
+            const bool have = lane < left;
+            const uint32_t v = have ? l_e[piece * WAVE + lane] : 0u;
+            if (left > WAVE) piece = l_next[piece];
+            const int32_t p = place(have, (int32_t)(v & 255u)) - base;
+            if (have) l_s[p] = e_beg + (int32_t)(v >> 8);   // p < n_own <= listed entries
+        }
         __syncthreads();
-        for (int32_t i = tid; i < n; i += ONE_BLOCK) {
-            const int32_t e = l_e[i], c = l_c[i], beg = pre[c], len = cnt[c];
+        // a thread per place (few threads search where there are few entries)
+        for (int32_t i = tid; i < n_own; i += ONE_BLOCK) {
+            const int32_t e = l_s[i];
             const float v = adj_val[e];
-            // the row: last r with adj_rowptr[r] <= e, by eighths
-            int32_t lo = 0, hi = nS;   // adj_rowptr[lo] <= e < adj_rowptr[hi]
-            while (hi - lo > 1) {
-                const int32_t span = hi - lo;
-                int32_t p[7];
-#pragma unroll
-                for (int k = 0; k < 7; ++k) p[k] = adj_rowptr[lo + (int32_t)((int64_t)span * (k + 1) / 8)];
-                int below = 0;
-#pragma unroll
-                for (int k = 0; k < 7; ++k) below += p[k] <= e ? 1 : 0;
-                const int32_t new_lo = lo + (int32_t)((int64_t)span * below / 8);
-                hi = below < 7 ? lo + (int32_t)((int64_t)span * (below + 1) / 8) : hi;
-                lo = new_lo;
-                if (hi <= lo) break;
-            }
-            int32_t place = 0;
-            int32_t k0 = 0;
-            for (; k0 + 16 <= len; k0 += 16) {   // sixteen reads on their way
-                int32_t o[16];
-#pragma unroll
-                for (int k = 0; k < 16; ++k) o[k] = g_e[beg + k0 + k];
-#pragma unroll
-                for (int k = 0; k < 16; ++k) place += o[k] < e ? 1 : 0;
-            }
-            for (; k0 < len; k0 += 4) {   // (past the column's end its last entry again, dropped)
-                int32_t o[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) o[k] = g_e[beg + (k0 + k < len ? k0 + k : len - 1)];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) place += k0 + k < len && o[k] < e ? 1 : 0;
-            }
-            const int64_t at = (int64_t)base + first[c] + place;
-            if (at < cap) {
-                rowT[at] = lo;
-                valT[at] = v;
-            }
+            put(base + i, entry_row(adj_rowptr, nS, e), v);
         }
-        if (fits) break;
-        __syncthreads();
-        for (int i = tid; i < ONE_OWN; i += ONE_BLOCK) done[i] += cnt[i];
-        __syncthreads();
+        return;
+    }
+    for (int32_t e0 = w0; e0 < w1; e0 += WAVE) {
+        const int32_t e = e0 + lane < w1 ? e0 + lane : w1 - 1, d = adj_col[e] - c0;
+        const bool have = e0 + lane < w1 && (uint32_t)d < n_mine;
+        if (!__any(have)) continue;
+        const float v = adj_val[e];
+        const int32_t p = place(have, d);
+        if (have) put(p, entry_row(adj_rowptr, nS, e), v);
     }
 }
 
@@ -730,7 +770,7 @@ extern "C" int csgs_aggregate_grad(const int32_t *adj_rowptr, const int32_t *adj
     const GradScratch g = carve_grad(scratch, n_cols, adj_cap);
     if (scratch_bytes < g.bytes) return CSGS_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
-    if (adj_cap <= ONE_ENTRIES && n_cols <= ONE_COLS) {
+    if (adj_cap <= (n_cols <= ONE_WIDE ? ONE_ENTRIES : ONE_ENTRIES_WIDE) && n_cols <= ONE_COLS) {
         CSGS_LAUNCH(K_ADJT_ORDER, adjT_one, dim3(ONE_GRID), dim3(ONE_BLOCK), st, adj_rowptr, adj_col, adj_val, nS, nS_dev, n_cols, n_cols_dev, adj_cap,
                     g.colptr, g.rowT, g.valT);
         CSGS_LAUNCH_CHECK();

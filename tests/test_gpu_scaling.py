@@ -150,6 +150,35 @@ def test_gradient_with_many_columns(dev):
     assert us[1] < 60.0 * us[0]
 
 
+# The transpose in one launch beside the several launches of larger arrays (the same entries with more room behind them): never much
+# dearer, with few entries, a column that thousands of rows share, several of those in one block, full arrays of many columns.
+@pytest.mark.parametrize("nS,n_cols,entries,longest", [(8192, 8192, 20_000, 0), (16_384, 8192, 20_000, 1000), (16_384, 8192, 20_000, 8000), (65_536, 8192, 20_000, 60_000),
+                                                       (65_536, 300, 60_000, 0), (16_384, 4, 50_000, 0), (65_536, 65_536, 390_000, 0), (65_536, 8192, 520_000, 0)])
+def test_gradient_in_one_launch(dev, nS, n_cols, entries, longest):
+    from paper_2101_07706_amd import csgs
+    print(f"[aggregate grad] {entries} entries of {n_cols} columns, one of {longest}", flush=True)
+    F, more, us, got = 8, (1 << 19) + 1, [], []
+    gen = torch.Generator(device=dev).manual_seed(nS + longest)
+    key = torch.randint(0, nS * n_cols, (entries,), generator=gen, device=dev)
+    key = torch.unique(torch.cat([key, torch.randperm(nS, generator=gen, device=dev)[:longest] * n_cols + 5 % n_cols]))
+    nnz, row = key.numel(), key // n_cols
+    rp = torch.zeros(nS + 1, dtype=torch.int64, device=dev)
+    rp[1:] = torch.cumsum(torch.bincount(row, minlength=nS), 0)
+    rp, col, val = rp.to(torch.int32), torch.zeros(more, dtype=torch.int32, device=dev), torch.rand(more, generator=gen, device=dev)
+    col[:nnz] = (key % n_cols).to(torch.int32)
+    dZ, dH = torch.randn((nS, F), generator=gen, device=dev), torch.empty((n_cols, F), device=dev)
+    for cap in (nnz, more):
+        scratch = torch.empty(csgs.csgs_aggregate_grad_scratch_bytes(n_cols, cap) // 8 + 32, dtype=torch.int64, device=dev)
+        us.append(_least_us(lambda: csgs.csgs_aggregate_grad(rp, col[:cap], val[:cap], None, dZ, None, dH, scratch),
+                            ("fill_zero", "adjT_count", "adjT_prefix", "adjT_fill", "adjT_order"), 4))
+        got.append(dH.cpu().numpy())
+    np.testing.assert_array_equal(got[0], got[1])   # the same transpose, summed by the same kernel
+    chain.assert_close(got[0], oracle.aggregate_grad(rp.cpu().numpy(), col[:nnz].cpu().numpy(), val[:nnz].cpu().numpy(), n_cols, dZ.cpu().numpy(), None),
+                       chain.RTOL, chain.ATOL, "dH")
+    print(f"[aggregate grad] one launch {us[0]:.1f} us, several {us[1]:.1f} us")
+    assert us[0] < 1.2 * us[1]
+
+
 # Rows a little longer than those that a wavefront walks through: a tenth more edges, not half as much time again.  (2000 rows with
 # F = 481: four rows a tile.)  A block of few rows: twice the edges in no more time, since all its wavefronts take part.
 @pytest.mark.parametrize("fused,F,bf16,n_rows,short,longer", [(True, 128, False, 2048, 60, 66), (True, 128, False, 16_384, 60, 66), (False, 100, True, 65_536, 120, 132),
