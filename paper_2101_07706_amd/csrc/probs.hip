@@ -285,7 +285,7 @@ __global__ __launch_bounds__(WIDE_BLOCK) void scan_wide(const int32_t *__restric
     is = at_instance(is);
     const uint32_t blk = inst_block(is), n_blk = inst_blocks(is);
     constexpr int STEPS = WIDE_EDGES / WIDE_STEP, BINS = WIDE_BINS / WIDE_BLOCK;   // bins per thread
-    __shared__ union {
+    __shared__ __attribute__((aligned(16))) union {   // (e is read two at a time)
         EdgeMap<WIDE_STEP> map;
         unsigned long long e[WIDE_EDGES];
     } u;

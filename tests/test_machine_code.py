@@ -204,3 +204,13 @@ def test_rows_claim_no_more_than_an_element(tmp_path):
             assert align <= element, f"{name}: {line}"
         seen[name] = len(loads)
     assert len(seen) == 9, seen
+
+
+# The wide weight scan copies its sorted entries out of LDS two at a time, 16 bytes: the array says that it lies on such a piece, and does not
+# leave that to where the compiler happens to put it.
+def test_sorted_entries_are_aligned_for_their_copy():
+    ir = subprocess.run(["hipcc", "--offload-arch=gfx950", "--cuda-device-only", "-O3", "-std=c++17", "-S", "-emit-llvm", "-Xclang", "-disable-llvm-passes", "-o", "-",
+                         "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC, os.path.join(build.CSRC, "probs.hip")],
+                        stdout=subprocess.PIPE, text=True, check=True).stdout
+    align = re.findall(r"^@_ZZN4csgs9scan_wide\w+E1u = [^\n]*addrspace\(3\)[^\n]*align (\d+)", ir, re.M)
+    assert len(align) == 1 and int(align[0]) >= 16, align
