@@ -261,8 +261,7 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
 // The weight scan of a launch with many edges: every edge is handed over, so that none costs a scattered atomic.  A block sorts
 // WIDE_EDGES edges at a time by the bin of their target -- the ids of one block of the candidate sums: a local tile, or four tiles
 // elsewhere -- by a counting sort in LDS, and writes them out as one run.  The more edges at a time, the longer a bin's group in the run,
-// which the sums read piece by piece.  What an entry does not hold (weights from WIDE_WEIGHTS on), bins outside the
-// local range that take more than WIDE_BIN_MAX of a run (their block would walk alone through what belongs to many), and runs
+// which the sums read piece by piece.  What an entry does not hold (weights from WIDE_WEIGHTS on), crowded bins (below) and runs
 // beyond the hand-over array go through the atomics.
 constexpr int WIDE_CHUNKS = 16;                            // chunks of EDGE_TILE edges a run holds
 constexpr int WIDE_EDGES = WIDE_CHUNKS * EDGE_TILE;
@@ -272,7 +271,15 @@ constexpr int WIDE_BINS = 4096;
 constexpr int WIDE_STRIDE = WIDE_CHUNKS * SUB_STRIDE;      // entries per run of the groups' begins
 constexpr int WIDE_IDS = CAND_TILE * 4;                    // most ids of a bin
 constexpr unsigned long long WIDE_WEIGHTS = 1ull << 52;
-constexpr uint32_t WIDE_BIN_MAX = WIDE_EDGES / 8;
+// A bin outside the local range is crowded, and its edges of a run go through the atomics, from this many edges over all runs, runs taken as alike: one
+// block adds a bin up, at 0.4 ns an edge where runs are few and their groups long, at up to 1.4 where they are many.  Unless more of a run's bins are: then
+// their blocks have enough company, and the atomics would cost as much.  (us of csgs_build_probs, narrow form / an eighth of a run as
+// the line / this; 2.4 M nodes, a fifth of the edges remote.  204 runs: no bin crowded 88 / 72 / 73, one with 1 % of the edges 87 / 112 / 73, 5 % 86 / 307 / 78, 10 % 85 / 548 /
+// 84, 12 % 86 / 640 / 87, ids by degree 370 / 119 / 99.  436 runs: 153 / 106 / 108, 5 % 150 / 353 / 117, 12 % 144 / 714 / 136.  Eight
+// instances of 24 runs: 126 / 90 / 90, 2 % 124 / 93 / 93, 5 % 122 / 111 / 110, 12 % 120 / 162 / 119.  Dearer for it than the narrow form, whose atomics
+// travel beside its loads: all remote edges in a bin or eight, 204 runs 80 / 93 and 180 / 95 to 97, 436 runs 136 / 151 and 218 / 154.)
+constexpr uint32_t WIDE_CROWD = 8192, WIDE_CROWD_FEW = 16384, WIDE_CROWD_RUN = 32;   // the latter: of a run at least
+constexpr int WIDE_FEW_RUNS = WAVE, WIDE_CROWDED = 32;                             // most crowded bins of a run
 static_assert(WIDE_BINS + 1 <= WIDE_STRIDE && WIDE_EDGES <= 0xFFFF && WIDE_STEP / WAVE <= WAVE, "runs of the wide form");
 
 __global__ __launch_bounds__(WIDE_BLOCK) void scan_wide(const int32_t *__restrict__ colidx, const float *__restrict__ val, int64_t n_nodes,
@@ -291,6 +298,7 @@ __global__ __launch_bounds__(WIDE_BLOCK) void scan_wide(const int32_t *__restric
     } u;
     __shared__ uint32_t hist[WIDE_BINS];
     __shared__ uint32_t s_scan[17];
+    __shared__ int32_t n_crowded;
     meta = inst_ptr(meta, is.ws); eoff = inst_ptr(eoff, is.ws); rowstart = inst_ptr(rowstart, is.ws);
     wtable = inst_ptr(wtable, is.ws); tileflag = inst_ptr(tileflag, is.ws); bound_note = inst_ptr(bound_note, is.ws);
     stg.e = inst_ptr(stg.e, is.ws); stg.off = inst_ptr(stg.off, is.ws);
@@ -300,6 +308,8 @@ __global__ __launch_bounds__(WIDE_BLOCK) void scan_wide(const int32_t *__restric
     const int64_t E = meta[META_EDGES];
     const int64_t n_chunks = (E + EDGE_TILE - 1) / EDGE_TILE, n_runs = (E + WIDE_EDGES - 1) / WIDE_EDGES;
     const int64_t n_staged = stg.chunks / WIDE_CHUNKS;
+    uint32_t crowd = n_runs > WIDE_CROWD ? 0u : (n_runs > WIDE_FEW_RUNS ? WIDE_CROWD : WIDE_CROWD_FEW) / (uint32_t)(n_runs > 0 ? n_runs : 1);
+    if (crowd < WIDE_CROWD_RUN) crowd = WIDE_CROWD_RUN;
     const unsigned long long call = call_number(epoch);
     const int32_t tile0 = stg.tiles ? stg.lo / CAND_TILE : 0x7FFFFFFF, tile1 = stg.tiles ? tile0 + stg.tiles : 0x7FFFFFFF;
     const int32_t past = stg.below + stg.tiles - tile1 / 4;   // of a tile past the local ones: its bin minus a quarter of it
@@ -315,6 +325,7 @@ __global__ __launch_bounds__(WIDE_BLOCK) void scan_wide(const int32_t *__restric
     for (int64_t run = blk; run < n_runs; run += n_blk) {
         const bool staged = run < n_staged;
         for (int i = tid; i < stg.bins; i += WIDE_BLOCK) hist[i] = 0u;   // (its last readers are a barrier behind)
+        if (tid == 0) n_crowded = 0;
         // Which rows, and where they start, is asked for for all steps at once; columns and values of a step travel while the next one
         // is mapped.
         ChunkRows rows[STEPS];
@@ -372,27 +383,31 @@ __global__ __launch_bounds__(WIDE_BLOCK) void scan_wide(const int32_t *__restric
         }
         if (staged) {
             __syncthreads();
-            // counts -> begin of every group; a bin with too many keeps an empty group and the top bit
+            // counts -> begin of every group; a crowded bin keeps an empty group and the top bit.  Both ways at once: with
+            // the crowded bins' edges, and (upper half) without
             uint32_t cnt[BINS], sum = 0;
             bool heavy[BINS];
 #pragma unroll
             for (int i = 0; i < BINS; ++i) {
                 const int b = tid * BINS + i;
-                const uint32_t n = b < stg.bins ? hist[b] : 0u;
-                heavy[i] = n > WIDE_BIN_MAX && (b < stg.below || b >= stg.below + stg.tiles);
-                cnt[i] = heavy[i] ? 0u : n;
-                sum += cnt[i];
+                cnt[i] = b < stg.bins ? hist[b] : 0u;
+                heavy[i] = cnt[i] > crowd && (uint32_t)(b - stg.below) >= (uint32_t)stg.tiles;
+                if (heavy[i]) atomicAdd(&n_crowded, 1);
+                sum += cnt[i] | (heavy[i] ? 0u : cnt[i] << 16);
             }
             uint32_t n_handed;
             uint32_t ex = block_exclusive_scan<uint32_t>(sum, s_scan, &n_handed);
+            const bool few_crowded = n_crowded <= WIDE_CROWDED;   // (complete since the scan's barriers)
+            ex = few_crowded ? ex >> 16 : ex & 0xFFFFu;
+            n_handed = few_crowded ? n_handed >> 16 : n_handed & 0xFFFFu;
 #pragma unroll
             for (int i = 0; i < BINS; ++i) {
                 const int b = tid * BINS + i;
                 if (b < stg.bins) {
-                    hist[b] = ex | (heavy[i] ? 0x80000000u : 0u);
+                    hist[b] = ex | (heavy[i] && few_crowded ? 0x80000000u : 0u);
                     stg.off[run * WIDE_STRIDE + b] = (uint16_t)ex;
                 }
-                ex += cnt[i];
+                ex += heavy[i] && few_crowded ? 0u : cnt[i];
             }
             if (tid == 0) {
                 stg.off[run * WIDE_STRIDE + stg.bins] = (uint16_t)n_handed;
