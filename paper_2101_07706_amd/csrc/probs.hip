@@ -70,6 +70,7 @@ struct Stage {
     int32_t n_inst;     // instances of the launch
     int32_t min_chunks; // chunks over all instances from which edges are handed over (0: whatever a chunk holds)
     int32_t below, bins; // wide form (scan_wide): bins before the local tiles, bins in all
+    int32_t runs;       // most runs that are not whole ones (0: all are)
     unsigned long long *part;        // [tiles * max_split * CAND_TILE] sums of all but a tile's last block
     unsigned long long *part_flag;   // [tiles * max_split] tag of the call that left them
     uint64_t *gtot;     // [gtot_words] sums per group of tiles: the scan clears them for the candidate sums
@@ -280,8 +281,23 @@ constexpr unsigned long long WIDE_WEIGHTS = 1ull << 52;
 // travel beside its loads: all remote edges in a bin or eight, 204 runs 80 / 93 and 180 / 95 to 97, 436 runs 136 / 151 and 218 / 154.)
 constexpr uint32_t WIDE_CROWD = 8192, WIDE_CROWD_FEW = 16384, WIDE_CROWD_RUN = 32;   // the latter: of a run at least
 constexpr int WIDE_FEW_RUNS = WAVE, WIDE_CROWDED = 32;                             // most crowded bins of a run
-static_assert(WIDE_BINS + 1 <= WIDE_STRIDE && WIDE_EDGES <= 0xFFFF && WIDE_STEP / WAVE <= WAVE, "runs of the wide form");
+constexpr int WIDE_STEP_CHUNKS = WIDE_STEP / EDGE_TILE;
+// Steps of a run: four, with one instance no more than leave no more runs than there are compute units, each of which a run's block fills (us of
+// csgs_build_probs with room for 65536 rows of 51 edges, whole runs / this: 1024 rows 42 / 34, 8192 57 / 48, 32768 65 / 59).
+__device__ inline int run_steps_log2(int64_t n_chunks, const Stage &stg)
+{
+    const int64_t two = (int64_t)stg.runs * WIDE_STEP_CHUNKS * 2;   // chunks that runs of two steps hold
+    return n_chunks > two ? 2 : (n_chunks > two / 2 ? 1 : 0);
+}
+__device__ inline int64_t run_count(int64_t n_chunks, const Stage &stg)
+{
+    const int steps = run_steps_log2(n_chunks, stg);
+    return (n_chunks + (WIDE_STEP_CHUNKS << steps) - 1) / WIDE_STEP_CHUNKS >> steps;
+}
+static_assert(WIDE_CHUNKS == WIDE_STEP_CHUNKS * 4, "steps of a run");
+static_assert(WIDE_STEP % EDGE_TILE == 0 && WIDE_BINS + 1 <= WIDE_STRIDE && WIDE_EDGES <= 0xFFFF && WIDE_STEP / WAVE <= WAVE, "runs of the wide form");
 
+template <bool WHOLE>   // runs of WIDE_CHUNKS chunks, whatever there is
 __global__ __launch_bounds__(WIDE_BLOCK) void scan_wide(const int32_t *__restrict__ colidx, const float *__restrict__ val, int64_t n_nodes,
                                                         int64_t nnz, int32_t shift_base, const int64_t *__restrict__ meta, int64_t edge_cap,
                                                         const int64_t *__restrict__ eoff, const int64_t *__restrict__ rowstart,
@@ -306,8 +322,9 @@ __global__ __launch_bounds__(WIDE_BLOCK) void scan_wide(const int32_t *__restric
     const int32_t nS = (int32_t)meta[META_ROWS];
     const double scale = ldexp(1.0, shift_for_rows(shift_base, nS));
     const int64_t E = meta[META_EDGES];
-    const int64_t n_chunks = (E + EDGE_TILE - 1) / EDGE_TILE, n_runs = (E + WIDE_EDGES - 1) / WIDE_EDGES;
-    const int64_t n_staged = stg.chunks / WIDE_CHUNKS;
+    const int64_t n_chunks = (E + EDGE_TILE - 1) / EDGE_TILE;
+    const int32_t steps = WHOLE ? STEPS : 1 << run_steps_log2(n_chunks, stg), per_run = steps * WIDE_STEP_CHUNKS;
+    const int64_t n_runs = WHOLE ? (n_chunks + WIDE_CHUNKS - 1) / WIDE_CHUNKS : run_count(n_chunks, stg), n_staged = stg.chunks / WIDE_CHUNKS;
     uint32_t crowd = n_runs > WIDE_CROWD ? 0u : (n_runs > WIDE_FEW_RUNS ? WIDE_CROWD : WIDE_CROWD_FEW) / (uint32_t)(n_runs > 0 ? n_runs : 1);
     if (crowd < WIDE_CROWD_RUN) crowd = WIDE_CROWD_RUN;
     const unsigned long long call = call_number(epoch);
@@ -332,8 +349,8 @@ __global__ __launch_bounds__(WIDE_BLOCK) void scan_wide(const int32_t *__restric
         RowEdges mine[STEPS];
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
-            const int64_t t0 = run * WIDE_CHUNKS + s * (WIDE_STEP / EDGE_TILE), t1 = t0 + WIDE_STEP / EDGE_TILE;
-            rows[s] = t0 < n_chunks ? chunk_rows(bound_note, t0, t1 < n_chunks ? t1 : n_chunks) : ChunkRows{0, 0};
+            const int64_t t0 = run * per_run + s * WIDE_STEP_CHUNKS, t1 = t0 + WIDE_STEP_CHUNKS;
+            rows[s] = s < steps && t0 < n_chunks ? chunk_rows(bound_note, t0, t1 < n_chunks ? t1 : n_chunks) : ChunkRows{0, 0};
         }
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) mine[s] = first_rows(eoff, rowstart, nS, rows[s]);
@@ -342,7 +359,8 @@ __global__ __launch_bounds__(WIDE_BLOCK) void scan_wide(const int32_t *__restric
         uint32_t live = 0;
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
-            const int64_t c0 = run * WIDE_EDGES + (int64_t)s * WIDE_STEP, left = E - c0;
+            if (s >= steps) continue;
+            const int64_t c0 = run * per_run * EDGE_TILE + (int64_t)s * WIDE_STEP, left = E - c0;
             const int32_t len = left <= 0 ? 0 : (left < WIDE_STEP ? (int32_t)left : WIDE_STEP);
             (void)map_edges(u.map, eoff, rowstart, nS, c0, len, rows[s], mine[s]);
             const EdgeWords words = edge_words(u.map);
@@ -447,8 +465,11 @@ constexpr int32_t HAND_OVER_MIN_CHUNKS = 160;
 // nodes, 150 local tiles: 1664 chunks 64 / 67, 2496 chunks 74 / 69, eight instances of 208 chunks 95 / 88, of 312 chunks 105 / 93, of 372 chunks 124 / 90, one of 6.6 K
 // chunks 139 / 96; 200 K nodes: eight of 197 chunks 57 / 66, of 394 chunks 75 / 70).  Where the local range is too wide for the narrow form's hand-over, which then
 // sends every edge through atomics, it pays much earlier (2 M nodes, 489 local tiles: 605 chunks 60 / 59, 1210 chunks 87 / 70, 3632 chunks 198 / 101).  With
-// few bins their blocks leave compute units idle (30 K nodes, eight of 394 chunks: 73 / 82).
+// few bins their blocks leave compute units idle (30 K nodes, eight of 394 chunks: 73 / 82).  Beyond the hand-over array, whose other runs go through atomics, it is
+// level on large graphs (2.4 M nodes, one edge in five remote: 9 M edges 196 / 160, 13 M 366 / 364, 20 M 668 / 630; 9.8 M nodes: 9 M 243 / 256, 11 M 329 / 311, 13 M
+// 415 / 480, 20 M 727 / 732).
 constexpr int64_t WIDE_MIN_CHUNKS = 2400, WIDE_MIN_CHUNKS_NARROW_OFF = 700;   // expected, over all instances
+constexpr int64_t WIDE_RUNS = 256;                                            // of one instance: a run's block fills a compute unit
 constexpr int64_t WIDE_MIN_BINS = 256;                                        // outside the local range, over all instances
 // A tile's sums are split over several blocks while each block has this many edges left and the launch has SPLIT_BLOCKS
 // of them at most, two per compute unit: a narrow local range has few tiles (29 tiles, 1 M edges: 31 us with a block
@@ -781,6 +802,7 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, PACK ? 8 : 1) void cand_partials(u
 // the entries -- and by how many blocks a compute unit holds, so the first are asked for before anything else is known; before that, by vector
 // instructions: 55 us for eight instances of 380 K edges with all eight wavefronts looking at every id, 41 with a bit per touched id.  (cand_partials
 // after the narrow scan: 52; with the scan, 47 and 25.)
+template <bool WHOLE>   // as in scan_wide
 __global__ __launch_bounds__(CAND_PART_BLOCK, 8) void bin_sums(uint64_t *__restrict__ wtable, uint8_t *__restrict__ tileflag, int64_t n_words, int64_t n_nodes,
                                                                int64_t n_tiles, int32_t lo, int32_t hi, const int64_t *__restrict__ meta, Stage stg,
                                                                const uint64_t *__restrict__ epoch, unsigned long long *__restrict__ partial, uint64_t *__restrict__ gtot,
@@ -819,9 +841,10 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, 8) void bin_sums(uint64_t *__restr
     int readers = own ? WAVES : CAND_PART_TILES;
     extents(lane * readers + wave);
     const unsigned long long call = call_number(epoch), tag = call_tag(call, SLOT_CAND);
-    int64_t n_runs = 0;
+    int64_t n_chunks = 0, n_runs = 0;
     if (epoch[EPOCH_HANDED] == call) {
-        n_runs = (meta[META_EDGES] + WIDE_EDGES - 1) / WIDE_EDGES;
+        n_chunks = (meta[META_EDGES] + EDGE_TILE - 1) / EDGE_TILE;
+        n_runs = WHOLE ? (n_chunks + WIDE_CHUNKS - 1) / WIDE_CHUNKS : run_count(n_chunks, stg);
         if (n_runs > most) n_runs = most;
     }
     const bool table = epoch[EPOCH_ADDED] == call;   // something went through the table of accumulators
@@ -843,7 +866,7 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, 8) void bin_sums(uint64_t *__restr
     // the last `split` of a local tile's blocks share its sums, the others leave
     uint32_t split = 1;
     if (own && n_runs) {
-        const int64_t want = n_runs * (WIDE_CHUNKS * EDGE_TILE / SPLIT_MIN_EDGES) / stg.tiles;
+        const int64_t want = (WHOLE ? n_runs * WIDE_CHUNKS : n_chunks) * EDGE_TILE / SPLIT_MIN_EDGES / stg.tiles;
         split = (uint32_t)(want < n_runs ? want : n_runs);
         if (split > (uint32_t)stg.max_split) split = (uint32_t)stg.max_split;
         if (split < 1u) split = 1u;
@@ -973,7 +996,7 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, 8) void bin_sums(uint64_t *__restr
     publish_tile(tile, sum, partial, gtot);
 }
 
-// Two kinds.  With PACKED a block takes four tiles that cand_partials has packed: where there are many tiles (several instances) the kernel is bound by
+// Two kinds.  With PACKED a block takes four tiles (or two) that cand_partials has packed: where there are many tiles (several instances) the kernel is bound by
 // vector instructions, and what they cost for the sums before a block, for the totals and for every 64-id word is then spent
 // once for four tiles and on the candidates alone, while cand_partials takes longer (us per launch, cand_partials + this kernel, words / packed: 8 x 2392
 // tiles with 65 candidates each 32 + 44 / 37 + 15, with 361 each 36 + 86 / 59 + 48; 1 x 9568 with 65 19 + 26 / 22 + 10, with 258 21 + 37 / 29 + 20; 8 x 1024
@@ -981,8 +1004,11 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, 8) void bin_sums(uint64_t *__restr
 // packed (1 x 2392 tiles with 65 each 8.1 + 11.2 / 9.7 + 5.4, 1 x 4784 12.9 + 15.5 / 15.2 + 7.2), many by words (1 x 2392 with 361 8.1 + 13.8 / 11.8 + 14.0,
 // 1 x 1100 6.8 + 10.1 / 9.1 + 12.8).  From the line on no call was found that words serve better.
 // (cand_partials at eight wavefronts per SIMD keeps two registers of the packing kind in scratch memory: its figures hold that.)
+// After the wide scan of one instance two tiles a block: its local tiles are full and four of them many passes, one a block many blocks where there are many tiles
+// (us, one / two / four: 2392 tiles, 710 K candidates 9.8 / 10.7 / 16.5, 213 K 7.0 / 9.4 / 14.6, 700 5.1 / 3.9 / 3.9; 9571 tiles, 772 K 19.8 / 12.8 / 17).
+constexpr int EMIT_ONE = 2;
 constexpr int64_t CAND_PACKED_FROM = 8192;   // tiles over all instances
-template <bool PACKED>
+template <bool PACKED, int TILES>
 __global__ __launch_bounds__(256) void cand_emit(uint64_t *__restrict__ wtable, uint8_t *__restrict__ tileflag,
                                                  int64_t n_words, int64_t n_nodes, int64_t n_tiles, int32_t lo,
                                                  int32_t hi, SkewPolicy pol, const uint64_t *__restrict__ partial,
@@ -996,7 +1022,8 @@ __global__ __launch_bounds__(256) void cand_emit(uint64_t *__restrict__ wtable, 
     is = at_instance(is);
     const uint32_t blk = inst_block(is);
     __shared__ uint32_t s_cnt[4];
-    constexpr int TILES = PACKED ? 4 : 1, WORDS = CAND_WORDS / 4;
+    static_assert(PACKED ? TILES <= 4 : TILES == 1, "a wavefront per packed tile");
+    constexpr int WORDS = CAND_WORDS / 4;
     __shared__ uint32_t s_id[4][PACKED ? 1 : CAND_TILE / 4];    // the tile's candidates, packed: ids ...
     __shared__ uint64_t s_wt[4][PACKED ? 1 : CAND_TILE / 4];    // ... and fixed-point weights, per wavefront in id order
     __shared__ uint16_t s_at[4][PACKED ? CAND_TILE : 1];        // PACKED: places of a tile's candidates in it, in id order
@@ -1016,7 +1043,7 @@ __global__ __launch_bounds__(256) void cand_emit(uint64_t *__restrict__ wtable, 
     const int64_t bits_at = t * (CAND_TILE / 16) + threadIdx.x;   // PACKED: a lane holds the bits of 16 ids
     uint32_t bits = 0;
     if (PACKED) {
-        if (bits_at < n_words * 4) bits = reinterpret_cast<const uint16_t *>(tileflag)[bits_at];
+        if (wave < TILES && bits_at < n_words * 4) bits = reinterpret_cast<const uint16_t *>(tileflag)[bits_at];
     } else {
 #pragma unroll
         for (int k = 0; k < WORDS; ++k) {
@@ -1370,7 +1397,8 @@ static int build_probs_impl(const csgs_graph *g, const int32_t *S, int32_t nS, c
                       (below + rest) * w.n_inst >= WIDE_MIN_BINS &&
                       fmin(mean, (double)w.chunk_cap) * w.n_inst >= (double)(tiles ? WIDE_MIN_CHUNKS : WIDE_MIN_CHUNKS_NARROW_OFF);
     const Stage stg{w.stage, w.stage_off, w.stage_chunks, range_ok ? g->local_lo : 0, range_ok ? g->local_hi : 0, tiles, (int32_t)split,
-                    adjacent ? 1 : 0, w.n_inst, min_chunks, (int32_t)(tiles ? below : rest), (int32_t)(below + tiles + rest), (unsigned long long *)w.split_sum, (unsigned long long *)w.split_flag,
+                    adjacent ? 1 : 0, w.n_inst, min_chunks, (int32_t)(tiles ? below : rest), (int32_t)(below + tiles + rest),
+                    (int32_t)(w.n_inst == 1 ? (w.stage_chunks / WIDE_CHUNKS < WIDE_RUNS ? w.stage_chunks / WIDE_CHUNKS : WIDE_RUNS) : 0), (unsigned long long *)w.split_sum, (unsigned long long *)w.split_flag,
                     w.gtot, (w.n_tiles + 63) / 64 * 4};
     if (wide) {
         int64_t runs = (int64_t)(guess < 1e9 ? guess : 1e9) / WIDE_CHUNKS + 1;
@@ -1378,8 +1406,11 @@ static int build_probs_impl(const csgs_graph *g, const int32_t *S, int32_t nS, c
         if (runs > SCAN_GRID / 4) runs = SCAN_GRID / 4;
         if (runs > (w.chunk_cap + WIDE_CHUNKS - 1) / WIDE_CHUNKS) runs = (w.chunk_cap + WIDE_CHUNKS - 1) / WIDE_CHUNKS;
         const InstGrid ig = inst_grid(w, runs, WIDE_BLOCK);
-        CSGS_LAUNCH(K_SCAN_EDGES, scan_wide, ig.grid, dim3(WIDE_BLOCK), st, g->colidx, g->val, g->n_nodes, g->nnz, shift_base,
-                    rows.meta, w.chunk_cap * EDGE_TILE, rows.eoff, rows.rowstart, w.wtable, w.tileflag, rows.bound_note, w.epoch, status, stg, ig.is);
+#define CSGS_SCAN_WIDE(WHOLE)                                                                                                                    \
+    CSGS_LAUNCH(K_SCAN_EDGES, scan_wide<WHOLE>, ig.grid, dim3(WIDE_BLOCK), st, g->colidx, g->val, g->n_nodes, g->nnz, shift_base, rows.meta, \
+                w.chunk_cap * EDGE_TILE, rows.eoff, rows.rowstart, w.wtable, w.tileflag, rows.bound_note, w.epoch, status, stg, ig.is)
+        if (stg.runs) CSGS_SCAN_WIDE(false); else CSGS_SCAN_WIDE(true);
+#undef CSGS_SCAN_WIDE
     } else {
         const InstGrid ig = inst_grid(w, chunks, 256);
         CSGS_LAUNCH(K_SCAN_EDGES, scan_edges, ig.grid, dim3(256), st, g->colidx, g->val,
@@ -1393,20 +1424,24 @@ static int build_probs_impl(const csgs_graph *g, const int32_t *S, int32_t nS, c
                 w.n_tiles, g->local_lo, g->local_hi, rows.meta, stg, (int32_t)(tiles ? below : part_blocks), w.epoch,                   \
                 (unsigned long long *)w.partial, w.gtot, status, part.is)
     const bool packed = wide || w.n_tiles * w.n_inst >= CAND_PACKED_FROM;   // (then `per` is CAND_PART_TILES)
-    if (wide)
-        CSGS_LAUNCH(K_CAND_PARTIALS, bin_sums, part.grid, dim3(CAND_PART_BLOCK), st, w.wtable, w.tileflag, n_words, g->n_nodes, w.n_tiles, g->local_lo,
-                    g->local_hi, rows.meta, stg, w.epoch, (unsigned long long *)w.partial, w.gtot, status, part.is);
+#define CSGS_BIN_SUMS(WHOLE)                                                                                                                  \
+    CSGS_LAUNCH(K_CAND_PARTIALS, bin_sums<WHOLE>, part.grid, dim3(CAND_PART_BLOCK), st, w.wtable, w.tileflag, n_words, g->n_nodes, w.n_tiles, \
+                g->local_lo, g->local_hi, rows.meta, stg, w.epoch, (unsigned long long *)w.partial, w.gtot, status, part.is)
+    if (wide && stg.runs) CSGS_BIN_SUMS(false);
+    else if (wide) CSGS_BIN_SUMS(true);
     else if (packed) CSGS_CAND_PARTIALS(CAND_PART_TILES, true);
     else if (per == 1) CSGS_CAND_PARTIALS(1, false);
     else CSGS_CAND_PARTIALS(CAND_PART_TILES, false);
 #undef CSGS_CAND_PARTIALS
+#undef CSGS_BIN_SUMS
     CSGS_LAUNCH_CHECK();
-    const InstGrid emit = inst_grid(w, packed ? (w.n_tiles + 3) / 4 : w.n_tiles, 256);
-#define CSGS_CAND_EMIT(PACKED)                                                                                                              \
-    CSGS_LAUNCH(K_CAND_EMIT, cand_emit<PACKED>, emit.grid, dim3(256), st, w.wtable, \
+    const int64_t emit_tiles = !packed ? 1 : (wide && w.n_inst == 1 ? EMIT_ONE : 4);
+    const InstGrid emit = inst_grid(w, (w.n_tiles + emit_tiles - 1) / emit_tiles, 256);
+#define CSGS_CAND_EMIT(PACKED, TILES)                                                                                                       \
+    CSGS_LAUNCH(K_CAND_EMIT, (cand_emit<PACKED, TILES>), emit.grid, dim3(256), st, w.wtable, \
                 w.tileflag, n_words, g->n_nodes, w.n_tiles, g->local_lo, g->local_hi, pol, w.partial, w.gtot, rows.meta, shift_base, w.epoch, \
                 stats, status, cand_id, cand_w, cdf, q, cap, emit.is)
-    if (packed) CSGS_CAND_EMIT(true); else CSGS_CAND_EMIT(false);
+    if (emit_tiles == 4) CSGS_CAND_EMIT(true, 4); else if (packed) CSGS_CAND_EMIT(true, EMIT_ONE); else CSGS_CAND_EMIT(false, 1);
 #undef CSGS_CAND_EMIT
     CSGS_LAUNCH_CHECK();
     return CSGS_OK;

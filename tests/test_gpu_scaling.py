@@ -272,30 +272,40 @@ def test_weight_scan_by_local_share(dev, P, n_rows, shares, timed):
         assert us[0] < 1.2 * us[1]
 
 
-# Many edges, sorted by the block that sums their targets: some of them crowded into few blocks' ids outside the local range.  Level with the form that
-# sends the remote ones through atomics.
-@pytest.mark.parametrize("share,bins", [(0.0, 1), (0.02, 1), (0.05, 1), (0.12, 1), (0.1, 8), (0.18, 64)])
-def test_weight_scan_of_crowded_targets(dev, share, bins):
+def _scan_modes(dev, share, bins, n_rows, counts, kernels, limit):
+    """csgs_build_probs for the first counts[i] of n_rows rows (8 edges each; 1.4 M nodes, one in eight local, four edges in five to those,
+    `share` of all to the ids of `bins` blocks of the sums elsewhere): as the library chooses, against the form that sends remote edges through atomics."""
     from paper_2101_07706_amd import csgs, pipeline
     rng = np.random.default_rng(bins + int(100 * share))
-    n, P, degree, n_rows, at = 1_400_000, 8, 8, 400_000, 146 * 4096
+    n, P, degree, at = 1_400_000, 8, 8, 146 * 4096
     kind, ids = rng.random((n, degree)), lambda lo, hi: rng.integers(lo, hi, (n, degree))
     col = np.where(kind < 0.8, ids(0, n // P), np.where(kind > 1 - share, ids(at, at + 4096 * bins), ids(n // P, n)))
     col.sort(axis=1)
     g = synth.Graph(n, np.arange(n + 1, dtype=np.int64) * degree, col.reshape(-1).astype(np.int32), np.full(n * degree, 1.0 / degree, np.float32), synth.partition_bounds(n, P), 0, 1.0)
-    S = np.sort(rng.permutation(n)[:n_rows]).astype(np.int32)
+    S = rng.permutation(n)[:n_rows].astype(np.int32)
     dg, Sd = pipeline.DeviceGraph(g, dev), torch.from_numpy(S).to(dev)
-    want = oracle.build_probs(g, S, 4.0)
-    n_c, us = len(want.cand_id), {}
-    for mode in (0, 2):
-        print(f"[scan] {share:.0%} of the edges in {bins} blocks' ids, mode {mode}", flush=True)
-        ws, lb = pipeline.Workspace(n, n_rows, 1, g.nnz, dev, scan_mode=mode), pipeline.LayerBuffers(n_rows, 1, n, 1, 8, dev)
-        us[mode] = _least_us(lambda: csgs.csgs_build_probs(dg.c, Sd, 4.0, lb.cand_id, lb.cand_w, lb.cdf, None, lb.stats, ws.desc, lb.status),
-                             ("scan_edges", "cand_partials"))
-        assert int(lb.status.item()) == 0 and int(lb.stats_host().n_cand) == n_c
-        np.testing.assert_array_equal(lb.cand_id[:n_c].cpu().numpy(), want.cand_id)
-        np.testing.assert_array_equal(lb.cand_w[:n_c].cpu().numpy().view(np.uint64), want.cand_w)
-        np.testing.assert_array_equal(lb.cdf[:n_c].cpu().numpy().view(np.uint64), want.cdf)
-        assert int(torch.count_nonzero(ws.buf[:chain.csgs_clean_words(n)]).item()) == 0, "workspace not restored"
-    print(f"[scan] {share:.0%} in {bins}: mode 0 {us[0]:.1f} us, mode 2 {us[2]:.1f} us")
-    assert us[0] < 1.25 * us[2]
+    for count in counts:
+        want = oracle.build_probs(g, S[:count], 4.0)
+        n_c, us, rows = len(want.cand_id), {}, torch.tensor([count], dtype=torch.int32, device=dev)
+        for mode in (0, 2):
+            print(f"[scan] {share:.0%} of the edges in {bins} blocks' ids, {count} rows, mode {mode}", flush=True)
+            ws, lb = pipeline.Workspace(n, n_rows, 1, g.nnz, dev, scan_mode=mode), pipeline.LayerBuffers(n_rows, 1, n, 1, 8, dev)
+            us[mode] = _least_us(lambda: csgs.csgs_build_probs(dg.c, Sd, 4.0, lb.cand_id, lb.cand_w, lb.cdf, None, lb.stats, ws.desc, lb.status, nS_dev=rows), kernels)
+            assert int(lb.status.item()) == 0 and int(lb.stats_host().n_cand) == n_c
+            np.testing.assert_array_equal(lb.cand_id[:n_c].cpu().numpy(), want.cand_id)
+            np.testing.assert_array_equal(lb.cand_w[:n_c].cpu().numpy().view(np.uint64), want.cand_w)
+            np.testing.assert_array_equal(lb.cdf[:n_c].cpu().numpy().view(np.uint64), want.cdf)
+            assert int(torch.count_nonzero(ws.buf[:chain.csgs_clean_words(n)]).item()) == 0, "workspace not restored"
+        print(f"[scan] {share:.0%} in {bins}, {count} rows: mode 0 {us[0]:.1f} us, mode 2 {us[2]:.1f} us")
+        assert us[0] < limit * us[2]
+
+
+# Many edges, sorted by the block that sums their targets: some of them crowded into few blocks' ids outside the local range.
+@pytest.mark.parametrize("share,bins", [(0.0, 1), (0.02, 1), (0.05, 1), (0.12, 1), (0.1, 8), (0.18, 64)])
+def test_weight_scan_of_crowded_targets(dev, share, bins):
+    _scan_modes(dev, share, bins, 400_000, [400_000], ("scan_edges", "cand_partials"), 1.25)
+
+
+# Room for many rows, of which the device has few: runs of one, two and four steps, a last run that is short.
+def test_weight_scan_of_few_of_many_rows(dev):
+    _scan_modes(dev, 0.0, 1, 400_000, [40, 3000, 50_000, 131_072, 131_200, 200_000, 262_300], ("scan_edges", "cand_partials", "cand_emit"), 1.2)
