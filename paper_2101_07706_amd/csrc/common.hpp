@@ -99,22 +99,23 @@ struct Workspace {
 // Several independent instances of a call run in the same launches, and every per-instance pointer moves by that
 // instance's stride in bytes -- `ws` for what lives in the workspace (instance k's workspace follows instance
 // k - 1's), `buf` for the caller's arrays.  The graph is shared.  With one instance nothing moves.
-// Two orders of the blocks: instance after instance (n = 0: blockIdx.z selects it), or the instances in turn (n of them: block b
-// of instance k is blockIdx.x = b * n + k).  The hardware deals consecutive blocks round-robin to the 8 XCDs, so in turn an
-// instance's blocks stay on one XCD of eight instances, two of four, four of two, and so do the tables
-// they look things up in, which one L2 then holds (see inst_grid).
+// Blocks come instance after instance (blockIdx.z selects it), or the instances in turn (inst_grid() below).
 struct InstStride {
     int64_t ws, buf;
-    int32_t n;
+    int32_t n;   // instances of a one-dimensional grid; 0: blockIdx.z is the instance
 };
-__device__ inline uint32_t inst_index(const InstStride &is) { return is.n ? blockIdx.x % (uint32_t)is.n : blockIdx.z; }
-__device__ inline uint32_t inst_block(const InstStride &is) { return is.n ? blockIdx.x / (uint32_t)is.n : blockIdx.x; }    // block of its instance
-__device__ inline uint32_t inst_blocks(const InstStride &is) { return is.n ? gridDim.x / (uint32_t)is.n : gridDim.x; }    // an instance's
-// The strides of this block's instance, for inst_ptr().
-__device__ inline InstStride at_instance(const InstStride &is)
+// The strides of instance k, for inst_ptr().
+__device__ inline InstStride at_instance(const InstStride &is, int64_t k) { return InstStride{is.ws * k, is.buf * k, is.n}; }
+__device__ inline InstStride at_instance(const InstStride &is) { return at_instance(is, blockIdx.z); }
+// Instance of this block, its number among the instance's, and how many those are.
+struct InstBlock {
+    uint32_t k, block, blocks;
+};
+__device__ inline InstBlock inst_block(const InstStride &is, bool in_turn)
 {
-    const int64_t k = inst_index(is);
-    return InstStride{is.ws * k, is.buf * k, is.n};
+    if (!is.n) return InstBlock{blockIdx.z, blockIdx.x, gridDim.x};
+    const uint32_t n = (uint32_t)is.n, each = gridDim.x / n;
+    return in_turn ? InstBlock{blockIdx.x % n, blockIdx.x / n, each} : InstBlock{blockIdx.x / each, blockIdx.x % each, each};
 }
 template <typename T>
 __device__ inline T *inst_ptr(T *p, int64_t bytes)
@@ -222,10 +223,14 @@ __host__ inline int open_workspace(csgs_workspace *d, int64_t n_nodes, int64_t n
 }
 
 __host__ inline InstStride inst_stride(const Workspace &w) { return InstStride{(int64_t)w.bytes, w.buf_stride, 0}; }
-// Grid of `blocks` blocks per instance, the instances in turn.  For kernels whose blocks wait for nobody or for lower blocks of their instance only
-// (those were dispatched before them): not for resident grids, see below.  An odd number of instances would spread
-// over the XCDs either way.  (us, eight instances of 380 K edges, one after the other / in turn: marking pass of the adjacency 25.4 / 22.2, candidate
-// sums 41 / 38.5, emission 21.5 / 18.8, draws 15.0 / 13.5, compaction 12.7 / 11, a three-layer step 829 / 777.)
+// Grid of `blocks` blocks per instance for kernels that take the instances in turn: block b of instance k is the (b n + k)-th of all.  The hardware deals
+// consecutive blocks round-robin to the 8 XCDs, so an instance's blocks stay on one XCD of eight instances, two of four, four of two, and so do the tables they look
+// things up in, which one L2 then holds.  A launch then lasts as long as its largest instance on its part of the device; kernels whose work follows
+// from the rows' edges do so only where those are about even, as the weight scan has noted (the note is the same for all blocks of a launch).  Only for kernels whose blocks wait for nobody or for lower blocks of their
+// instance (those were dispatched before them): not for resident grids, see below.  An odd number of instances would spread over the XCDs either way.
+// (us per launch, after each other / in turn, eight instances of 8192 rows of 51 edges: marking pass of the adjacency 26.9 / 22.8, emission 24.4 / 19.6, draws 15.8 / 13.2,
+// compaction 12.4 / 10.4, candidate sums 39.2 / 38.5, sampling of a layer 163 / 148; two instances 86 / 85, four 119 / 111, six 138 / 129, sixteen 299 / 273.  One instance of
+// 32768 rows and seven of 2048 in turn 274, after each other 168, as noted 170; the weight scan wins 0.4 us and the placing pass nothing: after each other.)
 struct InstGrid {
     dim3 grid;
     InstStride is;
@@ -237,6 +242,7 @@ __host__ inline InstGrid inst_grid(const Workspace &w, int64_t blocks, int threa
     is.n = w.n_inst;
     return InstGrid{dim3((unsigned)(blocks * w.n_inst)), is};
 }
+__host__ inline dim3 each_instance(const Workspace &w, int64_t blocks) { return dim3((unsigned)blocks, 1, (unsigned)w.n_inst); }
 
 // Grid of a kernel whose blocks wait for each other and stride over a tile count known only on
 // the device: resident_grid(per_cu) blocks of 256 threads, per_cu per compute unit.  Such a kernel
@@ -246,7 +252,7 @@ __host__ inline InstGrid inst_grid(const Workspace &w, int64_t blocks, int threa
 // adjacency filter (17 KB of LDS) runs 2 blocks per unit, so four call sequences on four workspaces
 // can be in flight on one device within the 2048 threads and 160 KB of a compute unit.  That is the
 // documented limit.
-// With several instances per call (blockIdx.z) the grid is that many times as large, but blocks
+// With several instances per call (blockIdx.z) the grid of such a kernel is that many times as large, but blocks
 // wait only for blocks of their own instance and the hardware hands out a grid's blocks in
 // ascending x, then y, then z: an instance is dispatched completely before the next one starts, a
 // completely dispatched instance finishes by itself and frees its places, and at most one instance

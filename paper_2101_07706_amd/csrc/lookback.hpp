@@ -55,7 +55,8 @@ constexpr int EPOCH_BITMAP_NEXT = 3, EPOCH_BITMAP_CUR = 4;
 constexpr int EPOCH_BITMAP_USED = 5;   // [2] words of each bitmap that its latest draw may have set
 constexpr int EPOCH_HANDED = 7;        // value of (calls + 1) during the latest weight scan that handed edges over
 constexpr int EPOCH_ADDED = 8;         // the same of the latest wide scan that added to the table of accumulators
-static_assert(EPOCH_BITMAP_USED + 2 <= EPOCH_HANDED && EPOCH_ADDED < EPOCH_WORDS, "epoch words");
+constexpr int EPOCH_EVEN = 9;          // of the first instance: whether the rows of the latest weight scan have about as many edges in every instance
+static_assert(EPOCH_BITMAP_USED + 2 <= EPOCH_HANDED && EPOCH_EVEN < EPOCH_WORDS, "epoch words");
 // one tag space per scan-state region, so the kernels of one call never mistake each other's flags
 enum TagSlot { SLOT_ROWS = 1, SLOT_CAND = 2, SLOT_HITS = 3, SLOT_ADJ = 4, SLOT_ROWS_NEXT = 5 };
 

@@ -76,6 +76,15 @@ struct Stage {
     uint64_t *gtot;     // [gtot_words] sums per group of tiles: the scan clears them for the candidate sums
     int64_t gtot_words;
 };
+// By the first wavefront of a scan: whether no instance's rows have more than 5 / 4 of the mean's edges.  `meta` and `epoch`: the first instance's.
+__device__ inline void note_even_edges(int32_t n_inst, int64_t ws_stride, const int64_t *__restrict__ meta, uint64_t *__restrict__ epoch)
+{
+    static_assert(MAX_INSTANCES <= WAVE, "a lane per instance");
+    const int lane = lane_id();
+    const uint64_t mine = lane < n_inst ? (uint64_t)inst_ptr(meta, ws_stride * lane)[META_EDGES] : 0ull;
+    const bool uneven = __any(mine * 4 * (uint64_t)n_inst > wave_sum(mine) * 5);
+    if (lane == 0) epoch[EPOCH_EVEN] = uneven ? 0ull : 1ull;
+}
 // By the first block of a scan
 __device__ inline void clear_group_sums(const Stage &stg, int64_t ws_stride)
 {
@@ -125,8 +134,9 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
                                                   const int2 *__restrict__ bound_note,
                                                   uint64_t *__restrict__ epoch, int32_t *__restrict__ status, Stage stg, InstStride is)
 {
+    if (stg.n_inst > 1 && blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x < WAVE) note_even_edges(stg.n_inst, is.ws, meta, epoch);
     is = at_instance(is);
-    const uint32_t blk = inst_block(is), n_blk = inst_blocks(is);
+    const uint32_t blk = blockIdx.x, n_blk = gridDim.x;
     constexpr int ITEMS = EDGE_TILE / 256;
     constexpr int BINS = SUB_MAX / WAVE;          // groups per lane of the counting sort
     static_assert(SUB_MAX % WAVE == 0 && EDGE_TILE <= 0xFFFF, "groups of a chunk");
@@ -305,8 +315,9 @@ __global__ __launch_bounds__(WIDE_BLOCK) void scan_wide(const int32_t *__restric
                                                         const int2 *__restrict__ bound_note, uint64_t *__restrict__ epoch,
                                                         int32_t *__restrict__ status, Stage stg, InstStride is)
 {
+    if (stg.n_inst > 1 && blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x < WAVE) note_even_edges(stg.n_inst, is.ws, meta, epoch);
     is = at_instance(is);
-    const uint32_t blk = inst_block(is), n_blk = inst_blocks(is);
+    const uint32_t blk = blockIdx.x, n_blk = gridDim.x;
     constexpr int STEPS = WIDE_EDGES / WIDE_STEP, BINS = WIDE_BINS / WIDE_BLOCK;   // bins per thread
     __shared__ __attribute__((aligned(16))) union {   // (e is read two at a time)
         EdgeMap<WIDE_STEP> map;
@@ -601,8 +612,9 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, PACK ? 8 : 1) void cand_partials(u
                                                      unsigned long long *__restrict__ partial,
                                                      uint64_t *__restrict__ gtot, int32_t *__restrict__ status, InstStride is)
 {
-    is = at_instance(is);
-    const uint32_t blk = inst_block(is);
+    const InstBlock ib = inst_block(is, epoch[EPOCH_EVEN] != 0);
+    is = at_instance(is, ib.k);
+    const uint32_t blk = ib.block;
     constexpr int WAVES = CAND_PART_BLOCK / WAVE, W = TILES * CAND_WORDS / WAVES;   // words per wavefront
     __shared__ uint64_t lds[WAVES][3];
     __shared__ unsigned long long acc[CAND_TILE];
@@ -808,8 +820,9 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, 8) void bin_sums(uint64_t *__restr
                                                                const uint64_t *__restrict__ epoch, unsigned long long *__restrict__ partial, uint64_t *__restrict__ gtot,
                                                                int32_t *__restrict__ status, InstStride is)
 {
-    is = at_instance(is);
-    const uint32_t blk = inst_block(is);
+    const InstBlock ib = inst_block(is, epoch[EPOCH_EVEN] != 0);
+    is = at_instance(is, ib.k);
+    const uint32_t blk = ib.block;
     constexpr int WAVES = CAND_PART_BLOCK / WAVE, U = 4;   // entries on their way per lane
     __shared__ unsigned long long acc[WIDE_IDS];
     __shared__ __attribute__((aligned(8))) uint32_t s_bits[WIDE_IDS / 32];   // ids with a weight
@@ -1019,8 +1032,9 @@ __global__ __launch_bounds__(256) void cand_emit(uint64_t *__restrict__ wtable, 
                                                  int32_t *__restrict__ cand_id, uint64_t *__restrict__ cand_w,
                                                  uint64_t *__restrict__ cdf, float *__restrict__ q, int64_t cap, InstStride is)
 {
-    is = at_instance(is);
-    const uint32_t blk = inst_block(is);
+    const InstBlock ib = inst_block(is, epoch[EPOCH_EVEN] != 0);
+    is = at_instance(is, ib.k);
+    const uint32_t blk = ib.block;
     __shared__ uint32_t s_cnt[4];
     static_assert(PACKED ? TILES <= 4 : TILES == 1, "a wavefront per packed tile");
     constexpr int WORDS = CAND_WORDS / 4;
@@ -1400,22 +1414,21 @@ static int build_probs_impl(const csgs_graph *g, const int32_t *S, int32_t nS, c
                     adjacent ? 1 : 0, w.n_inst, min_chunks, (int32_t)(tiles ? below : rest), (int32_t)(below + tiles + rest),
                     (int32_t)(w.n_inst == 1 ? (w.stage_chunks / WIDE_CHUNKS < WIDE_RUNS ? w.stage_chunks / WIDE_CHUNKS : WIDE_RUNS) : 0), (unsigned long long *)w.split_sum, (unsigned long long *)w.split_flag,
                     w.gtot, (w.n_tiles + 63) / 64 * 4};
+    const InstStride is = inst_stride(w);
     if (wide) {
         int64_t runs = (int64_t)(guess < 1e9 ? guess : 1e9) / WIDE_CHUNKS + 1;
         if (runs < 256 && w.n_inst == 1) runs = 256;
         if (runs > SCAN_GRID / 4) runs = SCAN_GRID / 4;
         if (runs > (w.chunk_cap + WIDE_CHUNKS - 1) / WIDE_CHUNKS) runs = (w.chunk_cap + WIDE_CHUNKS - 1) / WIDE_CHUNKS;
-        const InstGrid ig = inst_grid(w, runs, WIDE_BLOCK);
 #define CSGS_SCAN_WIDE(WHOLE)                                                                                                                    \
-    CSGS_LAUNCH(K_SCAN_EDGES, scan_wide<WHOLE>, ig.grid, dim3(WIDE_BLOCK), st, g->colidx, g->val, g->n_nodes, g->nnz, shift_base, rows.meta, \
-                w.chunk_cap * EDGE_TILE, rows.eoff, rows.rowstart, w.wtable, w.tileflag, rows.bound_note, w.epoch, status, stg, ig.is)
+    CSGS_LAUNCH(K_SCAN_EDGES, scan_wide<WHOLE>, each_instance(w, runs), dim3(WIDE_BLOCK), st, g->colidx, g->val, g->n_nodes, g->nnz, shift_base, rows.meta, \
+                w.chunk_cap * EDGE_TILE, rows.eoff, rows.rowstart, w.wtable, w.tileflag, rows.bound_note, w.epoch, status, stg, is)
         if (stg.runs) CSGS_SCAN_WIDE(false); else CSGS_SCAN_WIDE(true);
 #undef CSGS_SCAN_WIDE
     } else {
-        const InstGrid ig = inst_grid(w, chunks, 256);
-        CSGS_LAUNCH(K_SCAN_EDGES, scan_edges, ig.grid, dim3(256), st, g->colidx, g->val,
+        CSGS_LAUNCH(K_SCAN_EDGES, scan_edges, each_instance(w, chunks), dim3(256), st, g->colidx, g->val,
                     g->n_nodes, g->nnz, shift_base, rows.meta, w.chunk_cap * EDGE_TILE, rows.eoff, rows.rowstart, w.wtable,
-                    w.tileflag, rows.bound_note, w.epoch, status, stg, ig.is);
+                    w.tileflag, rows.bound_note, w.epoch, status, stg, is);
     }
     CSGS_LAUNCH_CHECK();
     const InstGrid part = inst_grid(w, part_blocks, CAND_PART_BLOCK);

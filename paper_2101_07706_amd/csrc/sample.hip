@@ -63,8 +63,9 @@ __global__ __launch_bounds__(DRAW_BLOCK) void draw(const uint64_t *__restrict__ 
                                                    uint64_t *__restrict__ epoch, uint64_t *__restrict__ rank,
                                                    uint64_t *__restrict__ member, int64_t n_nodes, InstStride is)
 {
-    is = at_instance(is);
-    const uint32_t blk = inst_block(is), n_blk = inst_blocks(is);
+    const InstBlock ib = inst_block(is, true);   // (as many draws for every instance)
+    is = at_instance(is, ib.k);
+    const uint32_t blk = ib.block, n_blk = ib.blocks;
     __shared__ uint64_t top[TOP];
     cdf = inst_ptr(cdf, is.buf); stats = inst_ptr(stats, is.buf);
     hit = inst_ptr(hit, is.ws); cbitmap0 = inst_ptr(cbitmap0, is.ws); cbitmap1 = inst_ptr(cbitmap1, is.ws); epoch = inst_ptr(epoch, is.ws); rank = inst_ptr(rank, is.ws);
@@ -79,7 +80,7 @@ __global__ __launch_bounds__(DRAW_BLOCK) void draw(const uint64_t *__restrict__ 
         }
     }
     if (iter_dev) iter = *iter_dev;
-    iter += inst_index(is);   // consecutive instances are consecutive iterations
+    iter += ib.k;   // consecutive instances are consecutive iterations
     const uint32_t iter_lo = (uint32_t)iter, iter_hi = (uint32_t)(iter >> 32);
     int64_t n = stats->n_cand;
     if (n > cand_cap) n = cand_cap;
@@ -198,8 +199,9 @@ __global__ __launch_bounds__(256) void hits(const int32_t *__restrict__ cand_id,
                                             double *__restrict__ pdbl, int32_t *__restrict__ n_next,
                                             uint64_t *__restrict__ ts_mem, int32_t *__restrict__ status, InstStride is)
 {
-    is = at_instance(is);
-    const uint32_t blk = inst_block(is), n_blk = inst_blocks(is);
+    const InstBlock ib = inst_block(is, epoch[EPOCH_EVEN] != 0);
+    is = at_instance(is, ib.k);
+    const uint32_t blk = ib.block, n_blk = ib.blocks;
     constexpr int SUB = 64;   // words listed at a time: four threads of 16 bits each per word
     __shared__ uint16_t s_list[SUB * 64];   // drawn positions of those words, ascending
     __shared__ uint32_t s_cnt[4], s_before[4];
@@ -492,9 +494,8 @@ __device__ inline void adj_values(const AdjChunk &s, const AdjGraph &g, const in
 // The leading blocks of an adjacency kernel do two other things that need only the new node set, complete since the
 // previous kernel, so that a layer step is that many launches shorter.  Returns true for such a block.
 __device__ inline bool adj_leading_blocks(RemoteArgs &rem, NextRows &nxt, const uint64_t *__restrict__ epoch, int32_t *__restrict__ status,
-                                          const InstStride &is)
+                                          const InstStride &is, uint32_t blk)
 {
-    const uint32_t blk = inst_block(is);
     // The first rem.blocks split the node set into local and remote (what csgs_remote_count does); they wait for nobody
     // and nobody waits for them.
     if ((int32_t)blk < rem.blocks) {
@@ -543,10 +544,11 @@ __global__ __launch_bounds__(256) void adj_mark(AdjGraph g, const int64_t *__res
                                                 uint64_t *__restrict__ kept, int64_t kept_chunks, int32_t *__restrict__ adj_rowptr,
                                                 int32_t *__restrict__ status, RemoteArgs rem, NextRows nxt, InstStride is)
 {
-    is = at_instance(is);
-    const uint32_t blk = inst_block(is), n_blk = inst_blocks(is);
+    const InstBlock ib = inst_block(is, epoch[EPOCH_EVEN] != 0);
+    is = at_instance(is, ib.k);
+    const uint32_t blk = ib.block, n_blk = ib.blocks;
     epoch = inst_ptr(epoch, is.ws); status = inst_ptr(status, is.buf);
-    if (adj_leading_blocks(rem, nxt, epoch, status, is)) return;
+    if (adj_leading_blocks(rem, nxt, epoch, status, is, blk)) return;
     meta = inst_ptr(meta, is.ws); g.eoff = inst_ptr(g.eoff, is.ws); g.rowstart = inst_ptr(g.rowstart, is.ws);
     g.rank = inst_ptr(g.rank, is.ws); g.member = inst_ptr(g.member, is.ws); g.pdbl = inst_ptr(g.pdbl, is.ws);
     bound_note = inst_ptr(bound_note, is.ws); chunk_cnt = inst_ptr(chunk_cnt, is.ws); kept = inst_ptr(kept, is.ws);
@@ -593,7 +595,7 @@ __global__ __launch_bounds__(256) void adj_place(AdjGraph g, const int64_t *__re
                                                  int64_t *__restrict__ adj_nnz, int32_t *__restrict__ status, InstStride is)
 {
     is = at_instance(is);
-    const uint32_t blk = inst_block(is), n_blk = inst_blocks(is);
+    const uint32_t blk = blockIdx.x, n_blk = gridDim.x;
     __shared__ uint32_t s_scan[17];
     __shared__ uint32_t s_cnt[256], s_base[256];
     __shared__ ChunkRows s_rows[256];
@@ -712,7 +714,7 @@ __global__ __launch_bounds__(256) void adj_once(AdjGraph g, const int64_t *__res
 {
     is = at_instance(is);
     epoch = inst_ptr(epoch, is.ws); status = inst_ptr(status, is.buf);
-    if (adj_leading_blocks(rem, nxt, epoch, status, is)) return;
+    if (adj_leading_blocks(rem, nxt, epoch, status, is, blockIdx.x)) return;
     meta = inst_ptr(meta, is.ws); g.eoff = inst_ptr(g.eoff, is.ws); g.rowstart = inst_ptr(g.rowstart, is.ws);
     g.rank = inst_ptr(g.rank, is.ws); g.member = inst_ptr(g.member, is.ws); g.pdbl = inst_ptr(g.pdbl, is.ws);
     ts_mem = inst_ptr(ts_mem, is.ws); bound_note = inst_ptr(bound_note, is.ws);
@@ -877,12 +879,12 @@ static int sampled_adjacency_impl(const csgs_graph *g, const int32_t *rows, int3
         return CSGS_OK;
     }
     const unsigned mark = blocks(ADJ_MARK_GRID, 1), place = blocks(ADJ_PLACE_GRID, ADJ_PLACE_MIN);
-    const InstGrid mg = inst_grid(w, mark + (int64_t)(rem.blocks + nxt.blocks), 256), pg = inst_grid(w, place, 256);
+    const InstGrid mg = inst_grid(w, mark + (int64_t)(rem.blocks + nxt.blocks), 256);
     CSGS_LAUNCH(K_ADJ_MARK, adj_mark, mg.grid, dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.bound_note, w.adj_cnt, w.stage,
                 w.stage_chunks, adj_rowptr, status, rem, nxt, mg.is);
     CSGS_LAUNCH_CHECK();
-    CSGS_LAUNCH(K_ADJ_PLACE, adj_place, pg.grid, dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.bound_note, w.adj_cnt,
-                w.stage, w.stage_chunks, adj_rowptr, adj_col, adj_val, adj_cap, adj_nnz, status, pg.is);
+    CSGS_LAUNCH(K_ADJ_PLACE, adj_place, each_instance(w, place), dim3(256), st, ag, cur.meta, w.epoch, w.chunk_cap, cur.bound_note, w.adj_cnt,
+                w.stage, w.stage_chunks, adj_rowptr, adj_col, adj_val, adj_cap, adj_nnz, status, inst_stride(w));
     CSGS_LAUNCH_CHECK();
     return CSGS_OK;
 }

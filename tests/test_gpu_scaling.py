@@ -309,3 +309,34 @@ def test_weight_scan_of_crowded_targets(dev, share, bins):
 # Room for many rows, of which the device has few: runs of one, two and four steps, a last run that is short.
 def test_weight_scan_of_few_of_many_rows(dev):
     _scan_modes(dev, 0.0, 1, 400_000, [40, 3000, 50_000, 131_072, 131_200, 200_000, 262_300], ("scan_edges", "cand_partials", "cand_emit"), 1.2)
+
+
+# Several instances of which one has most of the rows, beside as many rows shared out evenly: the device works on the large one as a whole.
+def test_uneven_instances(dev):
+    from paper_2101_07706_amd import csgs, pipeline
+    rng = np.random.default_rng(3)
+    n, P, degree, B, K, nS = 400_000, 8, 40, 4096, 8, 32_768
+    col = np.where(rng.random((n, degree)) < 0.8, rng.integers(0, n // P, (n, degree)), rng.integers(n // P, n, (n, degree)))
+    col.sort(axis=1)
+    g = synth.Graph(n, np.arange(n + 1, dtype=np.int64) * degree, col.reshape(-1).astype(np.int32), np.full(n * degree, 1.0 / degree, np.float32), synth.partition_bounds(n, P), 0, 1.0)
+    dg, us = pipeline.DeviceGraph(g, dev), []
+    lb = pipeline.LayerBuffers(nS, B, n, 64 * B, P, dev, n_inst=K)
+    ws = pipeline.Workspace(n, nS, B, 2 * degree * nS, dev, n_inst=K, inst_stride=lb.stride)
+    S = [rng.permutation(n)[:nS].astype(np.int32) for _ in range(K)]
+    for counts in ([(nS + 7 * 2048) // K] * K, [2048] * 3 + [nS] + [2048] * 4):
+        print(f"[instances] {counts} rows", flush=True)
+        for k in range(K):
+            lb.inst(k).S0.copy_(torch.from_numpy(S[k]).to(dev))
+            lb.inst(k).q.view(torch.int32)[0] = counts[k]   # (a word of the instance's that the step leaves alone)
+        us.append(_least_us(lambda: pipeline.sample_step(dg, ws, lb.S0, 4.0, B, 5, 3, 0, lb, want_q=False, nS_dev=lb.q.view(torch.int32)[:1]),
+                            ("scan_edges", "cand_partials", "cand_emit", "draw", "hits", "adj_mark", "adj_place")))
+        for k in (0, 3):
+            want, one = oracle.build_probs(g, S[k][:counts[k]], 4.0), lb.inst(k)
+            step = oracle.sample_layer(g, S[k][:counts[k]], want, B, 5, 3 + k, 0)
+            m, nnz = step.n_next, step.adj_nnz
+            assert int(one.status.item()) == 0 and int(one.n_next.item()) == m and int(one.adj_nnz.item()) == nnz
+            np.testing.assert_array_equal(one.S_next[:m].cpu().numpy(), step.S_next)
+            np.testing.assert_array_equal(one.adj_rowptr[:counts[k] + 1].cpu().numpy(), step.adj_rowptr)
+            np.testing.assert_array_equal(one.adj_col[:nnz].cpu().numpy(), step.adj_col)
+    print(f"[instances] even {us[0]:.1f} us, uneven {us[1]:.1f} us")
+    assert us[1] < 1.5 * us[0]
