@@ -33,9 +33,10 @@
  *     csgs_workspace_init().  Every call leaves it ready for the next.  Calls that share one
  *     workspace must be ordered on one stream.  Calls on DIFFERENT workspaces may run side by
  *     side on different streams; at most four such call sequences per device at a time (one
- *     kernel holds all its blocks resident while they wait for each other, and four of them
- *     fit a compute unit together; a sequence that processes several instances per call, see
- *     csgs_workspace, counts once: its instances are dispatched one after the other).
+ *     kernel, in which up to half a million edges are filtered in one pass, holds all its blocks
+ *     resident while they wait for each other, a quarter of what the device holds; a sequence
+ *     that processes several instances per call, see csgs_workspace, counts once: that kernel's
+ *     instances are dispatched one after the other).
  *   - Replay.  Nothing a kernel needs to tell one call from the next is fixed at launch time
  *     (the call counter behind the inter-block flags lives in the workspace and is advanced by
  *     the kernels), and no entry point records a memset.  A sequence of calls captured into a

@@ -245,13 +245,13 @@ __host__ inline InstGrid inst_grid(const Workspace &w, int64_t blocks, int threa
 __host__ inline dim3 each_instance(const Workspace &w, int64_t blocks) { return dim3((unsigned)blocks, 1, (unsigned)w.n_inst); }
 
 // Grid of a kernel whose blocks wait for each other and stride over a tile count known only on
-// the device: resident_grid(per_cu) blocks of 256 threads, per_cu per compute unit.  Such a kernel
-// must have all its blocks resident at once.  Alone on the device that is certain (registers and
-// LDS allow several times as many).  Beside kernels of other streams it still holds as long as the
-// waiting kernels in flight fit together, because every other kernel drains by itself: the one-pass
-// adjacency filter (17 KB of LDS) runs 2 blocks per unit, so four call sequences on four workspaces
-// can be in flight on one device within the 2048 threads and 160 KB of a compute unit.  That is the
-// documented limit.
+// the device: of the blocks of 256 threads that a compute unit holds (by threads, registers and LDS),
+// resident_grid(per_cu), a share.  Such a kernel must have all its blocks resident at once.  Alone on the device that is
+// certain.  Beside kernels of other streams it still holds as long as the waiting kernels in flight fit
+// together, because every other kernel drains by itself: the one-pass adjacency filter (72 registers, 13 KB of LDS:
+// seven blocks per unit) launches a quarter of what the device holds, so CALL_SEQUENCES on as many workspaces
+// can be in flight on one device.  That is the documented limit.
+constexpr int CALL_SEQUENCES = 4;
 // With several instances per call (blockIdx.z) the grid of such a kernel is that many times as large, but blocks
 // wait only for blocks of their own instance and the hardware hands out a grid's blocks in
 // ascending x, then y, then z: an instance is dispatched completely before the next one starts, a

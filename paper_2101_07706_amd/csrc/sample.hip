@@ -531,10 +531,12 @@ __device__ inline bool adj_leading_blocks(RemoteArgs &rem, NextRows &nxt, const 
 // 54 / 90, eight mini-batches of 380 K 35 / 41, 957 K 15 / 22; level at 413 K (16 / 15); beyond the 8 Mi edges whose kept ones
 // the first pass can leave, where the second looks up the rest again: 16.7 M 300 / 340, 33 M 645 / 720, 125 M 2310 / 3500.  The first
 // pass is bound by its random lookups in the membership words (100 G edges/s).
-// Most chunks (of all instances of a launch, as expected from the mean degree) for the one pass: 2 K edges 10.5 against 14
-// us, 52 K 10.1 / 13.8, 80 K 13.4 / 14.4 (with rows searched for edge by edge; without, a three-layer step of 8192 rows and 420 K edges a layer 271 / 276, a
-// two-layer step of 1 M edges a layer 212 / 204).  With several instances the line is where it was measured for them.
-constexpr int ADJ_ONCE_MAX = 640, ADJ_ONCE_MAX_EACH = 256;
+// Most chunks (of all instances of a launch, as expected from the mean degree with a quarter to spare) for the one pass: with one instance while
+// every chunk has a block of its own.  (us of csgs_build_probs and csgs_sample_layer, 1 K to 65 K draws, two passes / one.  200 K nodes: 2 K edges 50 to
+// 100 / 48 to 90, 259 K 58 to 99 / 57 to 93, 408 K 63 to 104 / 61 to 97; 2.4 M nodes: 259 K 64 to 77 / 63 to 75, 408 K 66 to 79 / 64 to 76; beyond a chunk per block
+// level or dearer.  Rows of hubs that hold many times what the mean expects are dearer in one pass, whose blocks a compute unit holds
+// fewer of: 1.4 M edges where 0.4 M are expected 136 / 148, 4.4 M 284 / 324.)  With several instances the line is where it was measured for them.
+constexpr int ADJ_ONCE_MAX = 560, ADJ_ONCE_MAX_EACH = 256;
 constexpr int ADJ_MARK_GRID = 2048;    // eight blocks per compute unit, by threads
 constexpr int ADJ_PLACE_GRID = 512;
 constexpr int ADJ_PLACE_MIN = 4;       // chunks a block of the placing pass takes at least: one per wavefront
@@ -705,8 +707,10 @@ __global__ __launch_bounds__(256) void adj_place(AdjGraph g, const int64_t *__re
 }
 
 // One pass: a block publishes its chunk's count and waits for the earlier chunks' before it places anything.  All blocks
-// are resident; block b takes chunks b, b + grid, ... in ascending order.
-__global__ __launch_bounds__(256) void adj_once(AdjGraph g, const int64_t *__restrict__ meta, uint64_t *__restrict__ epoch,
+// are resident; block b takes chunks b, b + grid, ... in ascending order.  Its registers decide how many blocks a compute unit holds (eight
+// would need scratch memory: 0.5 us more a launch), a quarter of those is a call's (see resident_grid).
+constexpr int ADJ_ONCE_BLOCKS = 7;   // per compute unit
+__global__ __launch_bounds__(256, ADJ_ONCE_BLOCKS) void adj_once(AdjGraph g, const int64_t *__restrict__ meta, uint64_t *__restrict__ epoch,
                                                 uint64_t *__restrict__ ts_mem, int64_t chunk_cap, const int2 *__restrict__ bound_note,
                                                 int32_t *__restrict__ adj_rowptr, int32_t *__restrict__ adj_col,
                                                 float *__restrict__ adj_val, int64_t adj_cap, int64_t *__restrict__ adj_nnz,
@@ -872,7 +876,7 @@ static int sampled_adjacency_impl(const csgs_graph *g, const int32_t *rows, int3
     };
     const AdjGraph ag{g->colidx, g->val, g->n_nodes, g->nnz, cur.eoff, cur.rowstart, w.rank, w.member, w.pdbl};
     if (expected * w.n_inst <= (w.n_inst == 1 ? ADJ_ONCE_MAX : ADJ_ONCE_MAX_EACH)) {
-        const dim3 grid_once(blocks(resident_grid(2), 1) + (unsigned)(rem.blocks + nxt.blocks), 1, (unsigned)w.n_inst);   // (its blocks wait for each other: an instance after the other)
+        const dim3 grid_once(blocks(resident_grid(ADJ_ONCE_BLOCKS) / CALL_SEQUENCES, 1) + (unsigned)(rem.blocks + nxt.blocks), 1, (unsigned)w.n_inst);   // (its blocks wait for each other: an instance after the other)
         CSGS_LAUNCH(K_ADJ_ONCE, adj_once, grid_once, dim3(256), st, ag, cur.meta, w.epoch, w.adj_ts, w.chunk_cap, cur.bound_note,
                     adj_rowptr, adj_col, adj_val, adj_cap, adj_nnz, status, rem, nxt, inst_stride(w));
         CSGS_LAUNCH_CHECK();

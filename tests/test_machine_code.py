@@ -214,3 +214,28 @@ def test_sorted_entries_are_aligned_for_their_copy():
                         stdout=subprocess.PIPE, text=True, check=True).stdout
     align = re.findall(r"^@_ZZN4csgs9scan_wideILb[01]E\w+E1u = [^\n]*addrspace\(3\)[^\n]*align (\d+)", ir, re.M)
     assert len(align) == 2 and min(map(int, align)) >= 16, align
+
+
+# Four call sequences may be in flight on a device, and the one-pass adjacency launches a quarter of as many blocks as the source says a compute unit
+# holds, which wait for each other: by its registers (512 a lane on each of four units, in pieces of 8) and its LDS (160 KB) a unit holds them.
+def test_waiting_blocks_fit_together(tmp_path):
+    if not os.path.exists(READELF):
+        pytest.skip("no llvm-readelf")
+    with open(os.path.join(build.CSRC, "sample.hip")) as f:
+        src = f.read()
+    blocks = int(re.search(r"constexpr int ADJ_ONCE_BLOCKS = (\d+);", src).group(1))
+    assert "blocks(resident_grid(ADJ_ONCE_BLOCKS) / CALL_SEQUENCES, 1)" in src
+    seen = 0
+    for j, obj in enumerate(_code_objects()):
+        path = tmp_path / f"{j}.elf"
+        path.write_bytes(obj)
+        notes = subprocess.run([READELF, "--notes", str(path)], stdout=subprocess.PIPE, text=True, check=True).stdout
+        for kernel in re.split(r"\n  - \.", notes):
+            name = re.search(r"\.name: +(\S+)", kernel)
+            if not name or "8adj_once" not in name.group(1):
+                continue
+            lds, regs = (int(re.search(rf"\.{key}: +(\d+)", kernel).group(1)) for key in ("group_segment_fixed_size", "vgpr_count"))
+            seen += 1
+            assert 512 // (-(-regs // 8) * 8) >= blocks, f"{regs} registers"
+            assert blocks * lds <= 160 << 10, f"{lds} bytes of LDS"
+    assert seen == 1
