@@ -945,7 +945,9 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, 8) void bin_sums(uint64_t *__restr
         if (tid < share) ok = wait_tag(&stg.part_flag[first + tid * next], tag, wait_limit(epoch));
         if (!ok) atomicOr(status, CSGS_ST_INTERNAL);
         __syncthreads();
-        for (int i = tid; i < CAND_TILE; i += CAND_PART_BLOCK) {
+        // (ids past the last node stay without a weight whatever a share holds that was not waited for: the weights go to the table side by side)
+        const int n_ids = n_nodes - t0 * CAND_TILE < CAND_TILE ? (int)(n_nodes - t0 * CAND_TILE) : CAND_TILE;
+        for (int i = tid; i < n_ids; i += CAND_PART_BLOCK) {
             unsigned long long v = acc[i];
             for (int k = 0; k < share; ++k) v += ld_relaxed(&stg.part[(first + k * next) * CAND_TILE + i]);
             acc[i] = v;

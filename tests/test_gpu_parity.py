@@ -1269,9 +1269,10 @@ def test_layer_gemm_gradients(dev, M, K, N):
         assert bool(torch.isnan(dZ[m:]).all())
 
 
+@pytest.mark.parametrize("spare", [5, 1 << 19])   # entries past the last one: the transpose in one launch, and in several
 @pytest.mark.parametrize("nS,nc,F,maxdeg,relu", [(1, 1, 4, 1, False), (300, 257, 64, 9, True), (2048, 1500, 256, 40, True),
                                                  (500, 64, 100, 64, False), (3000, 3000, 33, 6, True)])
-def test_aggregate_gradient(dev, nS, nc, F, maxdeg, relu):
+def test_aggregate_gradient(dev, nS, nc, F, maxdeg, relu, spare):
     from paper_2101_07706_amd import csgs
     rng = np.random.default_rng(nS + nc + F)
     deg = rng.integers(0, min(maxdeg, nc) + 1, nS)
@@ -1283,7 +1284,7 @@ def test_aggregate_gradient(dev, nS, nc, F, maxdeg, relu):
     val = rng.standard_normal(len(col)).astype(np.float32)
     dZ = rng.standard_normal((nS, F)).astype(np.float32)
     Hp = rng.standard_normal((nc, F)).astype(np.float32)
-    cap = max(len(col), 1) + 5
+    cap = max(len(col), 1) + spare
     rpd, cold, vald = torch.from_numpy(rp).to(dev), torch.zeros(cap, dtype=torch.int32, device=dev), torch.zeros(cap, device=dev)
     cold[:len(col)] = torch.from_numpy(col).to(dev)
     vald[:len(col)] = torch.from_numpy(val).to(dev)
@@ -1498,3 +1499,53 @@ def test_failed_waits_end_normally_and_are_reported(dev, scan_mode):
     csgs.csgs_workspace_init(ws.desc)            # also puts the built-in limit back
     assert run(9) == [0, 0]
     check_exact(9)
+
+
+def test_failed_waits_of_the_scan_of_many_edges(dev):
+    """The same for the form that sorts every edge by the block that sums its target, on many rows, whose row pass waits, and on a thousand
+    rows that hold as many edges, where it is the blocks that share a local tile's sums.  The local range ends in a partial tile."""
+    from paper_2101_07706_amd import csgs, pipeline
+    rng = np.random.default_rng(5)
+    n, P, n_rows, hubs, B = 1_400_000, 8, 400_000, 1000, 2000
+    S = rng.permutation(n)[:n_rows].astype(np.int32)
+    deg = np.full(n, 6)
+    deg[S[:hubs]] = 3000
+    rowptr = np.zeros(n + 1, np.int64)
+    np.cumsum(deg, out=rowptr[1:])
+    bounds = synth.partition_bounds(n, P)
+    col = np.where(rng.random(int(rowptr[-1])) < 0.8, rng.integers(bounds[P - 1], n, int(rowptr[-1])), rng.integers(0, n, int(rowptr[-1])))
+    col = col[np.argsort(np.repeat(np.arange(n, dtype=np.int64), deg) * n + col, kind="stable")].astype(np.int32)
+    g = synth.Graph(n, rowptr, col, (1.0 / np.repeat(deg, deg)).astype(np.float32), bounds, P - 1, 1.0)
+    dg, Sd = pipeline.DeviceGraph(g, dev), torch.from_numpy(S).to(dev)
+    ws, lb = pipeline.Workspace(n, n_rows, B, g.nnz, dev), pipeline.LayerBuffers(n_rows, B, n, 1_000_000, P, dev)
+    wants = {c: oracle.build_probs(g, S[:c], 4.0) for c in (hubs, n_rows)}
+
+    def run(count):
+        lb.status.zero_()
+        pipeline.sample_step(dg, ws, Sd, 4.0, B, 7, 0, 0, lb, nS_dev=torch.tensor([count], dtype=torch.int32, device=dev))
+        torch.cuda.synchronize()
+        return int(lb.status.item())
+
+    def check_exact(count):
+        want, n_c = wants[count], len(wants[count].cand_id)
+        step = oracle.sample_layer(g, S[:count], want, B, 7, 0, 0)
+        np.testing.assert_array_equal(lb.cand_id[:n_c].cpu().numpy(), want.cand_id)
+        np.testing.assert_array_equal(lb.cdf[:n_c].cpu().numpy().view(np.uint64), want.cdf)
+        assert int(lb.n_next.item()) == step.n_next
+        np.testing.assert_array_equal(lb.adj_rowptr[:count + 1].cpu().numpy(), step.adj_rowptr)
+
+    for count in (n_rows, hubs):
+        print(f"[waits] {count} rows", flush=True)
+        assert run(count) == 0
+        check_exact(count)
+        csgs.csgs_workspace_wait_limit(ws.desc, 0)
+        seen = 0
+        for _ in range(3):
+            seen |= run(count)            # must return: that is the test
+            csgs.csgs_workspace_init(ws.desc)
+            csgs.csgs_workspace_wait_limit(ws.desc, 0)
+        say(f"[waits] {count} rows, status bits seen with a poll limit of zero: {seen:#x}")
+        assert seen & csgs.ST_INTERNAL, "no wait gave up although none may poll"
+        csgs.csgs_workspace_init(ws.desc)
+        assert run(count) == 0
+        check_exact(count)
