@@ -221,9 +221,11 @@ def test_weight_scan_hand_over(dev, n_nodes, degree, n_rows, lo, hi, skew):
 
 
 # Column counts around what one block of the transpose orders (16), what one takes of its prefix (2048) and several of those;
-# fewer columns on the device than the bound; columns around the 64 entries that one wavefront orders
+# fewer columns on the device than the bound; columns around the 64 entries that one wavefront orders.  (With that many entries to spare several
+# launches transpose, else one.)
+@pytest.mark.parametrize("spare", [3, 1 << 19])
 @pytest.mark.parametrize("bound,n_cols", [(15, 15), (17, 16), (17, 17), (2047, 2047), (2049, 2048), (2049, 2049), (10_300, 10_241), (9000, 100), (50, 0)])
-def test_aggregate_gradient_columns(dev, bound, n_cols):
+def test_aggregate_gradient_columns(dev, bound, n_cols, spare):
     from paper_2101_07706_amd import csgs
     rng = np.random.default_rng(bound + n_cols)
     nS, F = 700, 20
@@ -238,7 +240,7 @@ def test_aggregate_gradient_columns(dev, bound, n_cols):
     val = rng.standard_normal(len(col)).astype(np.float32)
     dZ, Hp = rng.standard_normal((nS, F)).astype(np.float32), rng.standard_normal((bound, F)).astype(np.float32)
     t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
-    cap = len(col) + 3
+    cap = len(col) + spare
     cold, vald = torch.zeros(cap, dtype=torch.int32, device=dev), torch.zeros(cap, dtype=torch.float32, device=dev)
     cold[:len(col)], vald[:len(col)] = t(col.astype(np.int32)), t(val)
     dH = torch.full((bound, F), float("nan"), dtype=torch.float32, device=dev)

@@ -311,6 +311,11 @@ def test_weight_scan_of_few_of_many_rows(dev):
     _scan_modes(dev, 0.0, 1, 400_000, [40, 3000, 50_000, 131_072, 131_200, 200_000, 262_300], ("scan_edges", "cand_partials", "cand_emit"), 1.2)
 
 
+# More edges than are handed over (8 Mi), just and by a quarter: whole runs go through the atomics, into the sums of the others.
+def test_weight_scan_beyond_the_hand_over(dev):
+    _scan_modes(dev, 0.05, 1, 1_310_000, [1_050_000, 1_310_000], ("scan_edges", "cand_partials", "cand_emit"), 1.3)
+
+
 # Several instances of which one has most of the rows, beside as many rows shared out evenly: the device works on the large one as a whole.
 def test_uneven_instances(dev):
     from paper_2101_07706_amd import csgs, pipeline
