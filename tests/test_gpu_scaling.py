@@ -311,6 +311,38 @@ def test_weight_scan_of_few_of_many_rows(dev):
     _scan_modes(dev, 0.0, 1, 400_000, [40, 3000, 50_000, 131_072, 131_200, 200_000, 262_300], ("scan_edges", "cand_partials", "cand_emit"), 1.2)
 
 
+# Thousands of rows without edges before, between and behind the ones that have some, by both forms of the weight scan: little dearer than the rows with
+# edges alone, and the same candidates and entries.
+@pytest.mark.parametrize("n,k,degree,first,limit", [(200_000, 10_000, 20, 190_000, 4.0), (200_000, 10_000, 20, 0, 4.0), (1_000_000, 50_000, 1, None, 5.0),
+                                                    (1_400_000, 100_000, 32, 1_300_000, 2.0)])
+def test_scan_of_rows_without_edges(dev, n, k, degree, first, limit):
+    from paper_2101_07706_amd import csgs, pipeline
+    rng = np.random.default_rng(n + k)
+    B, us = 500, []
+    with_edges = np.arange(first, first + k) if first is not None else np.sort(rng.permutation(n)[:k])
+    deg = np.zeros(n, np.int64)
+    deg[with_edges] = degree
+    rowptr = np.zeros(n + 1, np.int64)
+    np.cumsum(deg, out=rowptr[1:])
+    col = np.sort(rng.integers(0, n, (k, degree)), axis=1).reshape(-1).astype(np.int32)
+    g = synth.Graph(n, rowptr, col, np.full(k * degree, 1.0 / degree, np.float32), synth.partition_bounds(n, 8), 0, 1.0)
+    dg = pipeline.DeviceGraph(g, dev)
+    ws, lb = pipeline.Workspace(n, n, B, g.nnz, dev), pipeline.LayerBuffers(n, B, n, g.nnz, 8, dev)
+    for S in (with_edges.astype(np.int32), np.arange(n, dtype=np.int32)):
+        print(f"[scan] {len(S)} rows, {k} with {degree} edges", flush=True)
+        Sd = torch.from_numpy(S).to(dev)
+        us.append(_least_us(lambda: pipeline.sample_step(dg, ws, Sd, 4.0, B, 5, 3, 0, lb), ("scan_edges",)))
+        want = oracle.build_probs(g, S, 4.0)
+        step, n_c = oracle.sample_layer(g, S, want, B, 5, 3, 0), len(want.cand_id)
+        assert int(lb.status.item()) == 0 and int(lb.n_next.item()) == step.n_next and int(lb.adj_nnz.item()) == step.adj_nnz
+        np.testing.assert_array_equal(lb.cand_id[:n_c].cpu().numpy(), want.cand_id)
+        np.testing.assert_array_equal(lb.cdf[:n_c].cpu().numpy().view(np.uint64), want.cdf)
+        np.testing.assert_array_equal(lb.adj_rowptr[:len(S) + 1].cpu().numpy(), step.adj_rowptr)
+        np.testing.assert_array_equal(lb.adj_col[:step.adj_nnz].cpu().numpy(), step.adj_col)
+    print(f"[scan] alone {us[0]:.1f} us, among the others {us[1]:.1f} us")
+    assert us[1] < limit * us[0]
+
+
 # More edges than are handed over (8 Mi), just and by a quarter: whole runs go through the atomics, into the sums of the others.
 def test_weight_scan_beyond_the_hand_over(dev):
     _scan_modes(dev, 0.05, 1, 1_310_000, [1_050_000, 1_310_000], ("scan_edges", "cand_partials", "cand_emit"), 1.3)
