@@ -117,6 +117,13 @@ __device__ inline InstBlock inst_block(const InstStride &is, bool in_turn)
     const uint32_t n = (uint32_t)is.n, each = gridDim.x / n;
     return in_turn ? InstBlock{blockIdx.x % n, blockIdx.x / n, each} : InstBlock{blockIdx.x / each, blockIdx.x % each, each};
 }
+// In turn as well, but moved on by one with every turn, so that no XCD is an instance's own.
+__device__ inline InstBlock inst_block_spread(const InstStride &is)
+{
+    if (!is.n) return InstBlock{blockIdx.z, blockIdx.x, gridDim.x};
+    const uint32_t n = (uint32_t)is.n, b = blockIdx.x / n;
+    return InstBlock{(blockIdx.x + b) % n, b, gridDim.x / n};
+}
 template <typename T>
 __device__ inline T *inst_ptr(T *p, int64_t bytes)
 {
@@ -230,7 +237,9 @@ __host__ inline InstStride inst_stride(const Workspace &w) { return InstStride{(
 // instance (those were dispatched before them): not for resident grids, see below.  An odd number of instances would spread over the XCDs either way.
 // (us per launch, after each other / in turn, eight instances of 8192 rows of 51 edges: marking pass of the adjacency 26.9 / 22.8, emission 24.4 / 19.6, draws 15.8 / 13.2,
 // compaction 12.4 / 10.4, candidate sums 39.2 / 38.5, sampling of a layer 163 / 148; two instances 86 / 85, four 119 / 111, six 138 / 129, sixteen 299 / 273.  One instance of
-// 32768 rows and seven of 2048 in turn 274, after each other 168, as noted 170; the weight scan wins 0.4 us and the placing pass nothing: after each other.)
+// 32768 rows and seven of 2048 in turn 274, after each other 168, as noted 174.  The placing pass wins nothing and goes after each other.  The weight scan looks nothing up
+// and its blocks fill a compute unit: level alone, 1 to 2 % of a step with another stream's products beside it (bench, eight instances: 81.5 after each other, 79.6 in turn), so
+// inst_block_spread(), which costs 60 for 43 with one instance of 32768 rows and seven of 8192 and is level with 2048; in turn 78.)
 struct InstGrid {
     dim3 grid;
     InstStride is;

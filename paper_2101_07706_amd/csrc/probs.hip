@@ -135,8 +135,9 @@ __global__ __launch_bounds__(256) void scan_edges(const int32_t *__restrict__ co
                                                   uint64_t *__restrict__ epoch, int32_t *__restrict__ status, Stage stg, InstStride is)
 {
     if (stg.n_inst > 1 && blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x < WAVE) note_even_edges(stg.n_inst, is.ws, meta, epoch);
-    is = at_instance(is);
-    const uint32_t blk = blockIdx.x, n_blk = gridDim.x;
+    const InstBlock ib = inst_block_spread(is);
+    is = at_instance(is, ib.k);
+    const uint32_t blk = ib.block, n_blk = ib.blocks;
     constexpr int ITEMS = EDGE_TILE / 256;
     constexpr int BINS = SUB_MAX / WAVE;          // groups per lane of the counting sort
     static_assert(SUB_MAX % WAVE == 0 && EDGE_TILE <= 0xFFFF, "groups of a chunk");
@@ -285,15 +286,15 @@ constexpr unsigned long long WIDE_WEIGHTS = 1ull << 52;
 // A bin outside the local range is crowded, and its edges of a run go through the atomics, from this many edges over all runs, runs taken as alike: one
 // block adds a bin up, at 0.4 ns an edge where runs are few and their groups long, at up to 1.4 where they are many.  Unless more of a run's bins are: then
 // their blocks have enough company, and the atomics would cost as much.  (us of csgs_build_probs, narrow form / an eighth of a run as
-// the line / this; 2.4 M nodes, a fifth of the edges remote.  204 runs: no bin crowded 88 / 72 / 73, one with 1 % of the edges 87 / 112 / 73, 5 % 86 / 307 / 78, 10 % 85 / 548 /
-// 84, 12 % 86 / 640 / 87, ids by degree 370 / 119 / 99.  436 runs: 153 / 106 / 108, 5 % 150 / 353 / 117, 12 % 144 / 714 / 136.  Eight
-// instances of 24 runs: 126 / 90 / 90, 2 % 124 / 93 / 93, 5 % 122 / 111 / 110, 12 % 120 / 162 / 119.  Dearer for it than the narrow form, whose atomics
-// travel beside its loads: all remote edges in a bin or eight, 204 runs 80 / 93 and 180 / 95 to 97, 436 runs 136 / 151 and 218 / 154.)
+// the line / this; 2.4 M nodes, a fifth of the edges remote.  204 runs: no bin crowded 88 / 72 / 65, one with 1 % of the edges 87 / 112 / 66, 5 % 86 / 307 / 70, 10 % 85 / 548 /
+// 76, 12 % 86 / 640 / 79, ids by degree 370 / 119 / 89 (7 of it by the emission's two tiles a block).  436 runs: 153 / 106 / 101, 5 % 150 / 353 / 111, 12 % 144 / 714 / 128.  Eight
+// instances of 24 runs: 126 / 90 / 90, 2 % 124 / 93 / 93, 5 % 122 / 111 / 108, 12 % 120 / 162 / 117.  Dearer for it than the narrow form, whose atomics
+// travel beside its loads: all remote edges in a bin or eight, 204 runs 80 / 93 and 180 / 88, 436 runs 134 / 151 and 218 / 145.)
 constexpr uint32_t WIDE_CROWD = 8192, WIDE_CROWD_FEW = 16384, WIDE_CROWD_RUN = 32;   // the latter: of a run at least
 constexpr int WIDE_FEW_RUNS = WAVE, WIDE_CROWDED = 32;                             // most crowded bins of a run
 constexpr int WIDE_STEP_CHUNKS = WIDE_STEP / EDGE_TILE;
 // Steps of a run: four, with one instance no more than leave no more runs than there are compute units, each of which a run's block fills (us of
-// csgs_build_probs with room for 65536 rows of 51 edges, whole runs / this: 1024 rows 42 / 34, 8192 57 / 48, 32768 65 / 59).
+// csgs_build_probs with room for 65536 rows of 51 edges, whole runs / this: 1024 rows 42 / 34, 8192 57 / 48, 32768 65 / 59; with the emission's two tiles a block 32, 41, 52).
 __device__ inline int run_steps_log2(int64_t n_chunks, const Stage &stg)
 {
     const int64_t two = (int64_t)stg.runs * WIDE_STEP_CHUNKS * 2;   // chunks that runs of two steps hold
@@ -316,8 +317,9 @@ __global__ __launch_bounds__(WIDE_BLOCK) void scan_wide(const int32_t *__restric
                                                         int32_t *__restrict__ status, Stage stg, InstStride is)
 {
     if (stg.n_inst > 1 && blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x < WAVE) note_even_edges(stg.n_inst, is.ws, meta, epoch);
-    is = at_instance(is);
-    const uint32_t blk = blockIdx.x, n_blk = gridDim.x;
+    const InstBlock ib = inst_block_spread(is);
+    is = at_instance(is, ib.k);
+    const uint32_t blk = ib.block, n_blk = ib.blocks;
     constexpr int STEPS = WIDE_EDGES / WIDE_STEP, BINS = WIDE_BINS / WIDE_BLOCK;   // bins per thread
     __shared__ __attribute__((aligned(16))) union {   // (e is read two at a time)
         EdgeMap<WIDE_STEP> map;
@@ -1416,21 +1418,22 @@ static int build_probs_impl(const csgs_graph *g, const int32_t *S, int32_t nS, c
                     adjacent ? 1 : 0, w.n_inst, min_chunks, (int32_t)(tiles ? below : rest), (int32_t)(below + tiles + rest),
                     (int32_t)(w.n_inst == 1 ? (w.stage_chunks / WIDE_CHUNKS < WIDE_RUNS ? w.stage_chunks / WIDE_CHUNKS : WIDE_RUNS) : 0), (unsigned long long *)w.split_sum, (unsigned long long *)w.split_flag,
                     w.gtot, (w.n_tiles + 63) / 64 * 4};
-    const InstStride is = inst_stride(w);
     if (wide) {
         int64_t runs = (int64_t)(guess < 1e9 ? guess : 1e9) / WIDE_CHUNKS + 1;
         if (runs < 256 && w.n_inst == 1) runs = 256;
         if (runs > SCAN_GRID / 4) runs = SCAN_GRID / 4;
         if (runs > (w.chunk_cap + WIDE_CHUNKS - 1) / WIDE_CHUNKS) runs = (w.chunk_cap + WIDE_CHUNKS - 1) / WIDE_CHUNKS;
+        const InstGrid ig = inst_grid(w, runs, WIDE_BLOCK);
 #define CSGS_SCAN_WIDE(WHOLE)                                                                                                                    \
-    CSGS_LAUNCH(K_SCAN_EDGES, scan_wide<WHOLE>, each_instance(w, runs), dim3(WIDE_BLOCK), st, g->colidx, g->val, g->n_nodes, g->nnz, shift_base, rows.meta, \
-                w.chunk_cap * EDGE_TILE, rows.eoff, rows.rowstart, w.wtable, w.tileflag, rows.bound_note, w.epoch, status, stg, is)
+    CSGS_LAUNCH(K_SCAN_EDGES, scan_wide<WHOLE>, ig.grid, dim3(WIDE_BLOCK), st, g->colidx, g->val, g->n_nodes, g->nnz, shift_base, rows.meta, \
+                w.chunk_cap * EDGE_TILE, rows.eoff, rows.rowstart, w.wtable, w.tileflag, rows.bound_note, w.epoch, status, stg, ig.is)
         if (stg.runs) CSGS_SCAN_WIDE(false); else CSGS_SCAN_WIDE(true);
 #undef CSGS_SCAN_WIDE
     } else {
-        CSGS_LAUNCH(K_SCAN_EDGES, scan_edges, each_instance(w, chunks), dim3(256), st, g->colidx, g->val,
+        const InstGrid ig = inst_grid(w, chunks, 256);
+        CSGS_LAUNCH(K_SCAN_EDGES, scan_edges, ig.grid, dim3(256), st, g->colidx, g->val,
                     g->n_nodes, g->nnz, shift_base, rows.meta, w.chunk_cap * EDGE_TILE, rows.eoff, rows.rowstart, w.wtable,
-                    w.tileflag, rows.bound_note, w.epoch, status, stg, is);
+                    w.tileflag, rows.bound_note, w.epoch, status, stg, ig.is);
     }
     CSGS_LAUNCH_CHECK();
     const InstGrid part = inst_grid(w, part_blocks, CAND_PART_BLOCK);
