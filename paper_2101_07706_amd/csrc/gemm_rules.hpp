@@ -41,6 +41,57 @@ inline Shape pick_shape(int64_t M, int64_t N, int64_t n_inst, bool b_kmajor)
 // A row of a matrix this long could put a lane's offset beyond 32 bits
 inline bool far_apart(int64_t lda, int64_t ldb) { return lda >= (1 << 24) || ldb >= (1 << 24); }
 
+// ---- the products on the integer matrix cores (digits.hip)
+constexpr int DIGIT_CHUNK = 64, DIGIT_WAVES = 8;
+constexpr int digit_rows(int kc) { return kc == 1 ? 128 : kc == 2 ? 64 : kc <= 4 ? 32 : 16; }   // of a step
+
+struct DigitsPlan {
+    bool use;
+    int kc;              // chunks of k that the kernel is made for
+    int cgs, wcs, rgs;   // blocks over the columns, wavefronts of a block side by side over its columns, blocks over the rows
+    int64_t few;         // no more rows than these on the device: in double
+};
+
+// Microseconds of a product [M x K] [K x N] in double: what the fullest compute unit multiplies and stores, and a launch (131072 rows, us, expected:
+// 64 x 256 79, 79; 100 x 256 112, 112; 256 x 256 252, 257; 256 x 47 52, 52; 8192 rows 256 x 256 19.5, 18.9; 4096 rows 512 x 512 34, 34)
+inline double double_us(int64_t M, int64_t N, int64_t K, int64_t n_inst, bool b_kmajor)
+{
+    const Shape s = pick_shape(M, N, n_inst, b_kmajor);
+    const int64_t tiles = ((M + 16 * s.rt - 1) / (16 * s.rt)) * ((N + 16 * s.nt - 1) / (16 * s.nt));
+    const int64_t per_cu = ((tiles + 3) / 4 * n_inst + CUS - 1) / CUS;
+    return 3.0 + (double)per_cu * s.rt * s.nt * ((double)((K + 3) / 4) * 0.029 * s.cost + 0.13);
+}
+
+// The digits' form where it is the quicker by 5 %.  Its time is 13 us (16 with the most digits of B to cut first) and for each step of
+// the block with the most of them what `step` says.  Measured against that, us, double / digits (expected): 131072 rows, 256 x 256
+// 252 / 126 (127), 256 x 128 128 / 79 (80), 256 x 64 66 / 65 (64), 100 x 256 112 / 79 (82), 512 x 128 250 / 134 (134), 64 x 256 79 / 59 (62); 16384 rows
+// 256 x 256 35 / 29 (30), 8192 rows 19.5 / 21.8 (23), 4096 rows 512 x 512 34 / 28 (29).
+inline DigitsPlan digits_plan(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc, int64_t n_inst, bool b_kmajor)
+{
+    DigitsPlan d{false, 0, 0, 0, 0, 0};
+    constexpr int64_t FAR = 1 << 20;   // (a lane's offsets have 32 bits)
+    if (K < 16 || K > 512 || N < 16 || N > 4096 || lda >= FAR || ldb >= FAR || ldc >= FAR || (N > K ? N : K) * ldb >= (1 << 29)) return d;
+    const int chunks = (int)((K + DIGIT_CHUNK - 1) / DIGIT_CHUNK);
+    d.kc = chunks > 5 ? 8 : chunks;
+    const int nt = d.kc > 4 ? 1 : 2, tiles = (int)((N + 16 * nt - 1) / (16 * nt));
+    d.cgs = (tiles + DIGIT_WAVES - 1) / DIGIT_WAVES;
+    d.wcs = (tiles + d.cgs - 1) / d.cgs;
+    const int64_t rs = digit_rows(d.kc), steps = (M + rs - 1) / rs * n_inst;
+    int64_t rgs = d.cgs <= CUS / 8 ? CUS / 8 / d.cgs * 8 : 8;   // a block per compute unit, those over the same rows on one XCD
+    if (rgs > steps) rgs = steps;
+    d.rgs = (int)rgs;
+    const int64_t turns = (steps + rgs - 1) / rgs;
+    if (turns >= 65536) return d;   // (the list of a block's outputs counts its steps in 16 bits)
+    // us of a step with columns for up to two, four and eight wavefronts
+    static constexpr double step[9][3] = {{}, {4.0, 6.6, 11.7}, {3.3, 5.0, 8.4}, {2.9, 3.7, 6.1}, {3.1, 4.2, 7.0}, {2.4, 2.4, 3.0}, {}, {}, {3.0, 3.0, 3.8}};
+    const double one = step[d.kc][d.wcs <= 2 ? 0 : d.wcs <= 4 ? 1 : 2], start = d.kc == 4 && d.wcs > 4 ? 16.0 : 13.0;
+    d.use = start + one * (double)turns < 0.95 * double_us(M, N, K, n_inst, b_kmajor);
+    // the rows on the device that are done in double before the digits are cut: three quarters of what takes as long (smaller tiles there)
+    const double rate = (double_us(M, N, K, n_inst, b_kmajor) - 3.0) / (double)(M * n_inst), mine = one / (double)(rs * rgs);
+    d.few = rate > mine ? (int64_t)(0.75 * (start - 3.0) / (rate - mine)) : 0;
+    return d;
+}
+
 // Parts of the reduction dimension for dW = Z^T G with `rows` rows that the caller's scratch has room for
 inline int dw_max_parts(int rows, int64_t K, int64_t N)
 {

@@ -1,0 +1,150 @@
+"""The layer products on the integer matrix cores against 64-bit sums: ends of tiles, chunks and steps, what has to be summed again in double,
+counts on the device, instances, rows that start anywhere."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+# reduction, columns and rows (the smallest counts that the rule takes are somewhat lower): every kernel there is, columns for one to eight wavefronts
+# and more than one block, last chunks of 1 to 64 k, rows that are no whole step
+SHAPES = [(64, 256, 131_069), (62, 507, 131_072), (128, 128, 100_003), (100, 256, 65_533), (101, 505, 65_533), (192, 250, 30_577), (131, 512, 40_011),
+          (256, 256, 20_399), (255, 101, 60_005), (256, 60, 250_001), (300, 127, 60_001), (257, 256, 30_001), (320, 513, 14_200), (512, 512, 4_095),
+          (385, 126, 54_001), (450, 70, 90_000)]
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    return torch.device("cuda:0")
+
+
+def product(what, A, W, out, **kw):
+    from paper_2101_07706_amd import csgs
+    (csgs.csgs_layer_gemm if what == "H" else csgs.csgs_layer_gemm_grad_z)(A, W, out, **kw)
+    torch.cuda.synchronize()
+
+
+def check(got, A, B):
+    """One rounding to float (2^-24) and what the digits leave out, which is six standard deviations at 2^-22 of an output; beside it, for outputs
+    summed in double, 2^-52 of the summands each, and the least float."""
+    A, B = A.double(), B.double()
+    want = A @ B
+    bound = (2.0 ** -24 + 2.0 ** -22) * want.abs() + A.shape[1] * 2.0 ** -52 * (A.abs() @ B.abs()) + 2.0 ** -150
+    d = (got.double() - want).abs()
+    assert bool((d <= bound).all()), float((d / bound).nan_to_num().max())
+    return float(d.norm()) / float(want.norm())
+
+
+def operands(dev, what, K, N, M, seed, pad=0):
+    g = torch.Generator(device=dev).manual_seed(seed)
+
+    def matrix(r, c, x):
+        t = torch.full((r, c + pad), float("nan"), device=dev)[:, :c] if pad else torch.empty((r, c), device=dev)
+        t.copy_(x)
+        return t
+    A = torch.randn((M, K), generator=g, device=dev).clamp_min_(-0.5) * torch.randn((M, 1), generator=g, device=dev).exp_()
+    W = torch.randn((K, N) if what == "H" else (N, K), generator=g, device=dev)
+    return matrix(M, K, A), matrix(*W.shape, W), torch.full((M + 1, N + 3), float("nan"), device=dev)
+
+
+@pytest.mark.parametrize("what", ["H", "dZ"])
+@pytest.mark.parametrize("K,N,M", SHAPES)
+def test_digit_products(dev, what, K, N, M):
+    print(f"[digits] {what} {M} x {K} x {N}", flush=True)
+    A, W, out = operands(dev, what, K, N, M, M + K + N, pad=M % 4)
+    product(what, A, W, out[:M, :N])
+    # a float's rounding is off by 2^-24 / sqrt(3) = 2^-24.8 of its unit, and the unit by 2^-0.4 of the value on average
+    assert check(out[:M, :N], A, W if what == "H" else W.t().contiguous()) < 2.0 ** -25
+    assert bool(torch.isnan(out[M:]).all()) and bool(torch.isnan(out[:, N:]).all()), "wrote outside"
+
+
+# Row counts on the device: none, few (summed in double), half of a step, all
+@pytest.mark.parametrize("what", ["H", "dZ"])
+@pytest.mark.parametrize("m", [0, 1, 777, 5_000, 40_009, 65_536, 70_000])
+def test_digit_products_device_count(dev, what, m):
+    K, N, M = 256, 100, 65_536
+    print(f"[digits] {what} {m} of {M}", flush=True)
+    A, W, out = operands(dev, what, K, N, M, m)
+    n = min(m, M)
+    A[n:] = float("nan")
+    product(what, A, W, out[:M, :N], M_dev=torch.tensor([m], dtype=torch.int32, device=dev))
+    if n:
+        check(out[:n, :N], A[:n], W if what == "H" else W.t().contiguous())
+    assert bool(torch.isnan(out[n:]).all()) and bool(torch.isnan(out[:, N:]).all()), "wrote outside"
+
+
+def test_digit_products_instances(dev):
+    from paper_2101_07706_amd import csgs
+    K, N, M, n_inst = 100, 256, 8_000, 8
+    counts = [8_000, 0, 1, 7_999, 4_033, 8_000, 16, 6_000]
+    print("[digits] instances", flush=True)
+    A, W, _ = operands(dev, "H", K, N, M * n_inst, 3)
+    A = A.reshape(n_inst, M, K)
+    M_dev = torch.zeros((n_inst, 64), dtype=torch.int32, device=dev)
+    M_dev[:, 0] = torch.tensor(counts, dtype=torch.int32)
+    out = torch.full((n_inst, M, N), float("nan"), device=dev)
+    nb = lambda t: t.stride(0) * t.element_size()
+    csgs.csgs_layer_gemm(A[0], W, out[0], M_dev=M_dev[0, :1], inst=csgs.InstStrides(n_inst, 0, nb(M_dev), nb(A), 0, nb(out)))
+    torch.cuda.synchronize()
+    for k, n in enumerate(counts):
+        if n:
+            check(out[k, :n], A[k, :n], W)
+        assert bool(torch.isnan(out[k, n:]).all()), "wrote outside"
+
+
+# What the digits do not hold: outputs that all but cancel (some, and so many that a block cannot list them), rows and columns of zeros, of numbers
+# beyond the exponents that are used, of one large number among small ones
+@pytest.mark.parametrize("what", ["H", "dZ"])
+@pytest.mark.parametrize("kind", ["cancel", "cancel_all", "zeros", "tiny", "huge", "spread"])
+def test_digit_products_hard(dev, what, kind):
+    K, N, M = 256, 256, 32_000
+    print(f"[digits] {what} {kind}", flush=True)
+    A, W, out = operands(dev, what, K, N, M, 5)
+    B = W if what == "H" else W.t()
+    if kind == "cancel":            # two halves that cancel but for their last bits, in one row in seven
+        A[::7, 1::2] = -A[::7, ::2]
+        B[1::2] = B[::2] * (1 + 2.0 ** -18)
+    elif kind == "cancel_all":
+        A[:, 1::2] = -A[:, ::2]
+        B[1::2] = B[::2] * (1 + 2.0 ** -18)
+    elif kind == "zeros":
+        A[5::9], B[:, 3::5] = 0, 0
+    elif kind == "tiny":
+        A[::3] *= 2.0 ** -100
+        B[:, 7] *= 2.0 ** -95
+    elif kind == "huge":
+        A[::3] *= 2.0 ** 90
+        A[1] *= 2.0 ** 105
+        B[:, 9] *= 2.0 ** 10
+    else:                           # one feature a million times the others, with weights as much smaller
+        A[:, 17] *= 2.0 ** 20
+        B[17] *= 2.0 ** -20
+        A[::2, 17] = 0
+    product(what, A, W, out[:M, :N])
+    check(out[:M, :N], A, B.contiguous())
+    if kind == "zeros":
+        assert bool((out[5:M:9, :N] == 0).all()) and bool((out[:M, 3:N:5] == 0).all())
+
+
+@pytest.mark.parametrize("what", ["H", "dZ"])
+def test_digit_products_infinite(dev, what):
+    K, N, M = 256, 256, 32_000
+    print(f"[digits] {what} infinite", flush=True)
+    A, W, out = operands(dev, what, K, N, M, 6)
+    B = W if what == "H" else W.t()
+    A[100, 3], A[101, 255], A[31_999, 0], A[7] = float("inf"), float("nan"), float("-inf"), 0
+    B[5, 40] = float("inf")
+    product(what, A, W, out[:M, :N])
+    want = (A.double() @ B.double().contiguous()).float()
+    got = out[:M, :N]
+    assert bool((torch.isnan(got) == torch.isnan(want)).all())
+    odd = ~torch.isfinite(want)
+    assert bool((got[odd & ~torch.isnan(want)] == want[odd & ~torch.isnan(want)]).all())
+    rows = torch.ones(M, dtype=torch.bool, device=dev)
+    rows[[100, 101, 31_999]] = False
+    cols = torch.ones(N, dtype=torch.bool, device=dev)
+    cols[40] = False
+    check(got[rows][:, cols], A[rows], B[:, cols].contiguous())

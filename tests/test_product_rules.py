@@ -1,6 +1,8 @@
 """The sizes of the product tests against the rule that picks the tiles: every kernel there is must be among them."""
 import subprocess
 
+import numpy as np
+
 import pytest
 
 pytest.importorskip("torch")
@@ -53,3 +55,40 @@ def test_weight_gradient_runs_every_tile(ask):
     got = ask([("dW", M, K, N) for M, K, N in GRAD_W_SIZES])
     assert {(rt, nt) for rt, nt, _ in got} == {(2, 2), (2, 4), (2, 3), (1, 4), (1, 2), (2, 1), (1, 1)}
     assert any(p == 1 for _, _, p in got) and any(p > 1 for _, _, p in got)
+
+
+ASK_DIGITS = """
+#include <cstdio>
+#include "gemm_rules.hpp"
+int main()
+{
+    long M, K, N, n;
+    int z;
+    while (scanf("%ld %ld %ld %ld %d", &M, &K, &N, &n, &z) == 5) {
+        const csgs::DigitsPlan d = csgs::digits_plan(M, N, K, K, z ? K : N, N, n, z);
+        printf("%d %d %d %d %d %lld\\n", d.use, d.kc, d.cgs, d.wcs, d.rgs, (long long)d.few);
+    }
+}
+"""
+
+
+def test_digit_products_run_every_kernel(tmp_path):
+    from test_gpu_digits import SHAPES
+    (tmp_path / "ask.cpp").write_text(ASK_DIGITS)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", build.CSRC, "-o", str(tmp_path / "ask"), str(tmp_path / "ask.cpp")], check=True)
+
+    def ask(sizes):
+        out = subprocess.run([str(tmp_path / "ask")], input="\n".join(" ".join(map(str, s)) for s in sizes), stdout=subprocess.PIPE, text=True, check=True)
+        return [tuple(map(int, line.split())) for line in out.stdout.splitlines()]
+    got = ask([(M, K, N, 1, z) for K, N, M in SHAPES for z in (0, 1)] + [(65_536, 256, 100, 1, 0), (8_000, 100, 256, 8, 0), (32_000, 256, 256, 1, 0)])
+    assert all(use for use, *_ in got), got
+    assert {kc for _, kc, *_ in got} == {1, 2, 3, 4, 5, 8}
+    assert {w for _, _, _, w, *_ in got} >= {2, 4, 8} and any(c > 1 for _, _, c, *_ in got)
+    # every step of rows has a block, every column a wavefront, and few enough rows on the device are done in double
+    rng = np.random.default_rng(0)
+    sizes = [(int(2 ** rng.uniform(4, 21)), int(rng.integers(1, 700)), int(rng.integers(1, 700)), int(rng.choice([1, 2, 8])), int(rng.integers(2)))
+             for _ in range(2000)]
+    for (M, K, N, n, _), (use, kc, cgs, wcs, rgs, few) in zip(sizes, ask(sizes)):
+        if use:
+            cols = 16 if kc > 4 else 32
+            assert 64 * kc >= K and cgs * wcs * cols >= N > (cgs - 1) * wcs * cols and wcs <= 8 and 1 <= rgs and 0 < few < M * n
