@@ -282,6 +282,7 @@ constexpr int WIDE_STEP = WIDE_BLOCK * 4;                  // mapped at a time
 constexpr int WIDE_BINS = 4096;
 constexpr int WIDE_STRIDE = WIDE_CHUNKS * SUB_STRIDE;      // entries per run of the groups' begins
 constexpr int WIDE_IDS = CAND_TILE * 4;                    // most ids of a bin
+constexpr int64_t BIN_FEW = 800;                            // expected edges per bin up to which a bin of several instances is one wavefront's
 constexpr unsigned long long WIDE_WEIGHTS = 1ull << 52;
 // A bin outside the local range is crowded, and its edges of a run go through the atomics, from this many edges over all runs, runs taken as alike: one
 // block adds a bin up, at 0.4 ns an edge where runs are few and their groups long, at up to 1.4 where they are many.  Unless more of a run's bins are: then
@@ -595,12 +596,15 @@ __device__ inline void sum_handed_over(unsigned long long *acc, const Stage &stg
 // Lane i < 3 of a wavefront holds sum i of tile t in `mine`: left for cand_emit, and added to the sums of its group of 64 tiles, which the weight scan
 // has cleared.  Nobody waits (with a last tile that waited for the others' flags and added them up: 59 against 55 us for an earlier bin_sums over eight instances,
 // 1 % of the smallest step).
+__device__ inline void publish_sum(int64_t t, int which, unsigned long long mine, unsigned long long *__restrict__ partial, uint64_t *__restrict__ gtot)
+{
+    partial[t * 4 + which] = mine;
+    if (mine) (void)__hip_atomic_fetch_add((unsigned long long *)&gtot[t / LB_GROUP * 4 + which], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 __device__ inline void publish_tile(int64_t t, unsigned long long mine, unsigned long long *__restrict__ partial, uint64_t *__restrict__ gtot)
 {
     const int lane = lane_id();
-    if (lane >= 3) return;
-    partial[t * 4 + lane] = mine;
-    if (mine) (void)__hip_atomic_fetch_add((unsigned long long *)&gtot[t / LB_GROUP * 4 + lane], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane < 3) publish_sum(t, lane, mine, partial, gtot);
 }
 
 // PACK: the tiles are also put into the form that the packing kind of cand_emit reads, each tile's weights side by side at the start of its piece
@@ -816,7 +820,15 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, PACK ? 8 : 1) void cand_partials(u
 // the entries -- and by how many blocks a compute unit holds, so the first are asked for before anything else is known; before that, by vector
 // instructions: 55 us for eight instances of 380 K edges with all eight wavefronts looking at every id, 41 with a bit per touched id.  (cand_partials
 // after the narrow scan: 52; with the scan, 47 and 25.)
-template <bool WHOLE>   // as in scan_wide
+// FEW, several instances with up to BIN_FEW expected edges a bin and local tiles that take their share of them: a bin that is no local tile is one
+// wavefront's if it has up to 512 entries.  The wavefront sets a bit for every id that an entry names, and an id's sum stands at the number of bits before it, so
+// 512 sums do for 4096 ids, eight bins fit where one did, nothing waits at a barrier, and the sums are packed as they stand.  What holds more, or was met
+// through the table, is the block's afterwards, one bin after the other.  Eight instances of 380 K edges, 136 entries a bin: 39 -> 24 us (a block of 512
+// threads and 33 KB for each of 4488 bins took five and a half rounds).  The line: with scan, sums and emission of eight instances of 342 K edges, 822 expected
+// a bin, 20 / 50 / 80 / 100 % of them remote, blocks 82 / 84 / 82 / 83 us, wavefronts 74 / 77 / 102 / 104; without local tiles, 433 to 822 entries in
+// every bin, 120 and 109 against 134 and 157.  (Bins of up to 2048 entries by a wavefront in several passes over them: 73 / 78 / 92 / 94, but 1 % of a step more
+// where there are few; four wavefronts with room for 1024 sums each 76 / 79 / 85 / 88.)
+template <bool WHOLE, bool FEW>   // WHOLE: as in scan_wide; FEW: a wavefront for each bin that is no local tile
 __global__ __launch_bounds__(CAND_PART_BLOCK, 8) void bin_sums(uint64_t *__restrict__ wtable, uint8_t *__restrict__ tileflag, int64_t n_words, int64_t n_nodes,
                                                                int64_t n_tiles, int32_t lo, int32_t hi, const int64_t *__restrict__ meta, Stage stg,
                                                                const uint64_t *__restrict__ epoch, unsigned long long *__restrict__ partial, uint64_t *__restrict__ gtot,
@@ -829,188 +841,320 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, 8) void bin_sums(uint64_t *__restr
     __shared__ unsigned long long acc[WIDE_IDS];
     __shared__ __attribute__((aligned(8))) uint32_t s_bits[WIDE_IDS / 32];   // ids with a weight
     __shared__ uint64_t lds[WAVES][3];
+    __shared__ __attribute__((aligned(8))) uint32_t few_bits[FEW ? WAVES : 1][WIDE_IDS / 32];
+    __shared__ int32_t crowded[WAVES], n_crowded;
     wtable = inst_ptr(wtable, is.ws); tileflag = inst_ptr(tileflag, is.ws); epoch = inst_ptr(epoch, is.ws);
     partial = inst_ptr(partial, is.ws); gtot = inst_ptr(gtot, is.ws);
     status = inst_ptr(status, is.buf); meta = inst_ptr(meta, is.ws);
     stg.e = inst_ptr(stg.e, is.ws); stg.off = inst_ptr(stg.off, is.ws);
     stg.part = inst_ptr(stg.part, is.ws); stg.part_flag = inst_ptr(stg.part_flag, is.ws);
     const int tid = (int)threadIdx.x, lane = lane_id(), wave = tid >> 6;
-    // blocks in the order of their bins, max_split for each of the local tiles (see cand_partials)
+    // blocks in the order of their bins, max_split for each of the local tiles (see cand_partials); FEW: the local tiles' before the others
     const int32_t own_blocks = stg.tiles * stg.max_split;
-    const int32_t b = (int32_t)blk - stg.below;
-    const bool own = b >= 0 && b < own_blocks;
-    const uint32_t per_step = stg.adjacent ? (uint32_t)stg.max_split : (uint32_t)stg.tiles;
-    const uint32_t step_own = own ? (uint32_t)b / per_step : 0u, rest_own = own ? (uint32_t)b % per_step : 0u;
-    const uint32_t tile_own = stg.adjacent ? step_own : rest_own, round_own = stg.adjacent ? rest_own : step_own;
-    const int32_t bin = b < 0 ? (int32_t)blk : (own ? stg.below + (int32_t)tile_own : stg.below + stg.tiles + (b - own_blocks));
-    const int64_t most = stg.chunks / WIDE_CHUNKS;   // runs that the hand-over array holds, at least one
-    const uint16_t *__restrict__ off = stg.off + bin;
-    uint32_t beg, end;
-    auto extents = [&](int64_t run) {   // where the bin's group lies in a run
-        const uint16_t *p = off + (run < most ? run : 0) * WIDE_STRIDE;
-        beg = p[0];
-        end = p[1];
+    auto whole_block = [&](int32_t b) {
+        const bool own = b >= 0 && b < own_blocks;
+        const uint32_t per_step = stg.adjacent ? (uint32_t)stg.max_split : (uint32_t)stg.tiles;
+        const uint32_t step_own = own ? (uint32_t)b / per_step : 0u, rest_own = own ? (uint32_t)b % per_step : 0u;
+        const uint32_t tile_own = stg.adjacent ? step_own : rest_own, round_own = stg.adjacent ? rest_own : step_own;
+        const int32_t bin = b < 0 ? stg.below + b : (own ? stg.below + (int32_t)tile_own : stg.below + stg.tiles + (b - own_blocks));
+        const int64_t most = stg.chunks / WIDE_CHUNKS;   // runs that the hand-over array holds, at least one
+        const uint16_t *__restrict__ off = stg.off + bin;
+        uint32_t beg, end;
+        auto extents = [&](int64_t run) {   // where the bin's group lies in a run
+            const uint16_t *p = off + (run < most ? run : 0) * WIDE_STRIDE;
+            beg = p[0];
+            end = p[1];
+        };
+        // share s takes the runs s, s + split, ...; of those, the first `readers` wavefronts one after the other (a bin's groups are
+        // short: where there are few runs, fewer wavefronts have fewer instructions to issue)
+        int readers = own ? WAVES : CAND_PART_TILES;
+        extents(lane * readers + wave);
+        const unsigned long long call = call_number(epoch), tag = call_tag(call, SLOT_CAND);
+        int64_t n_chunks = 0, n_runs = 0;
+        if (epoch[EPOCH_HANDED] == call) {
+            n_chunks = (meta[META_EDGES] + EDGE_TILE - 1) / EDGE_TILE;
+            n_runs = WHOLE ? (n_chunks + WIDE_CHUNKS - 1) / WIDE_CHUNKS : run_count(n_chunks, stg);
+            if (n_runs > most) n_runs = most;
+        }
+        const bool table = epoch[EPOCH_ADDED] == call;   // something went through the table of accumulators
+        const int64_t tile0 = stg.lo / CAND_TILE, local_end = tile0 + stg.tiles;
+        int64_t t0, t1;
+        if (b < 0) {
+            t0 = (int64_t)(stg.below + b) * CAND_PART_TILES;
+            t1 = t0 + CAND_PART_TILES;
+            if (stg.tiles > 0 && t1 > tile0) t1 = tile0;
+        } else if (own) {
+            t0 = tile0 + tile_own;
+            t1 = t0 + 1;
+        } else {
+            t0 = (local_end / CAND_PART_TILES + (b - own_blocks)) * CAND_PART_TILES;
+            t1 = t0 + CAND_PART_TILES;
+            if (t0 < local_end) t0 = local_end;
+        }
+        if (t1 > n_tiles) t1 = n_tiles;
+        // the last `split` of a local tile's blocks share its sums, the others leave
+        uint32_t split = 1;
+        if (own && n_runs) {
+            const int64_t want = (WHOLE ? n_runs * WIDE_CHUNKS : n_chunks) * EDGE_TILE / SPLIT_MIN_EDGES / stg.tiles;
+            split = (uint32_t)(want < n_runs ? want : n_runs);
+            if (split > (uint32_t)stg.max_split) split = (uint32_t)stg.max_split;
+            if (split < 1u) split = 1u;
+        }
+        const int share = own ? (int)round_own - (stg.max_split - (int)split) : 0;
+        if (t0 >= t1 || share < 0) return;   // the whole block
+        const uint32_t ids = own ? CAND_TILE : WIDE_IDS;
+        for (uint32_t i = tid; i < ids; i += CAND_PART_BLOCK) acc[i] = 0ull;
+        for (uint32_t i = tid; i < ids / 32; i += CAND_PART_BLOCK) s_bits[i] = 0u;
+        __syncthreads();
+        const bool sparse = !own && n_runs <= CAND_PART_TILES * WAVE;   // few entries: their bits are set one by one, else from the sums
+        if (split > 1 || (!own && !sparse)) {
+            readers = WAVES;
+            extents((int64_t)(lane * readers + wave) * split + share);
+        }
+        for (int64_t r0 = 0; r0 * split + share < n_runs && wave < readers; r0 += readers * WAVE) {
+            const int64_t run = (r0 + lane * readers + wave) * split + share;
+            // entry j of the sequence belongs to the first lane whose running count exceeds j
+            const int32_t n = run < n_runs && beg <= end && end <= WIDE_EDGES ? (int32_t)(end - beg) : 0;
+            const int32_t incl = wave_inclusive_scan<int32_t>(n);
+            const int32_t total = __builtin_amdgcn_readlane(incl, WAVE - 1);
+            const int32_t first = (int32_t)(run * WIDE_EDGES) + (int32_t)beg - (incl - n);   // it is entry first + j (at most STAGE_EDGES_MAX)
+            extents((r0 + readers * WAVE + lane * readers + wave) * split + share);
+            auto entry = [&](int32_t j) {
+                int lo_l = 0, hi_l = WAVE - 1;
+    #pragma unroll
+                for (int it = 0; it < 6; ++it) {
+                    const int mid = (lo_l + hi_l) >> 1;
+                    if (__shfl(incl, mid, WAVE) > j) hi_l = mid; else lo_l = mid + 1;
+                }
+                const int32_t pos = __shfl(first, lo_l, WAVE) + j;
+                return stg.e[j < total ? pos : 0];   // (unconditional; entry 0 stands in past the end)
+            };
+            auto take = [&](int32_t j, uint64_t v) {
+                if (j >= total) return;
+                const uint32_t at = (uint32_t)v & (ids - 1u);
+                atomicAdd(&acc[at], (unsigned long long)(v / WIDE_IDS));
+                if (sparse) atomicOr(&s_bits[at >> 5], 1u << (at & 31));
+            };
+            for (int32_t j0 = 0; j0 < total; j0 += U * WAVE) {
+                if (total - j0 <= WAVE) {
+                    take(j0 + lane, entry(j0 + lane));
+                    break;
+                }
+                uint64_t v[U];
+    #pragma unroll
+                for (int u = 0; u < U; ++u) v[u] = entry(j0 + u * WAVE + lane);
+    #pragma unroll
+                for (int u = 0; u < U; ++u) take(j0 + u * WAVE + lane, v[u]);
+            }
+        }
+        __syncthreads();
+        if (own && share != (int)split - 1) {   // left for the block of the last share
+            for (int i = tid; i < CAND_TILE; i += CAND_PART_BLOCK) st_relaxed(&stg.part[(int64_t)b * CAND_TILE + i], acc[i]);
+            wait_memory_ops();
+            __syncthreads();
+            if (tid == 0) st_relaxed(&stg.part_flag[b], tag);
+            return;
+        }
+        if (split > 1) {   // (the other shares' blocks were dispatched before and wait for nobody)
+            const int64_t next = stg.adjacent ? 1 : stg.tiles, first = b - share * next;
+            bool ok = true;
+            if (tid < share) ok = wait_tag(&stg.part_flag[first + tid * next], tag, wait_limit(epoch));
+            if (!ok) atomicOr(status, CSGS_ST_INTERNAL);
+            __syncthreads();
+            // (ids past the last node stay without a weight whatever a share holds that was not waited for: the weights go to the table side by side)
+            const int n_ids = n_nodes - t0 * CAND_TILE < CAND_TILE ? (int)(n_nodes - t0 * CAND_TILE) : CAND_TILE;
+            for (int i = tid; i < n_ids; i += CAND_PART_BLOCK) {
+                unsigned long long v = acc[i];
+                for (int k = 0; k < share; ++k) v += ld_relaxed(&stg.part[(first + k * next) * CAND_TILE + i]);
+                acc[i] = v;
+            }
+            __syncthreads();
+        }
+        if (!sparse) {
+            for (uint32_t i = tid; i < ids; i += CAND_PART_BLOCK) {
+                const uint64_t word = __ballot(acc[i] != 0);
+                if (lane == 0) reinterpret_cast<uint64_t *>(s_bits)[i >> 6] = word;
+            }
+            __syncthreads();
+        }
+        if (table) {   // what came through the table joins the sums, and the table is clean
+            for (uint32_t i = tid; i < ids; i += CAND_PART_BLOCK) {
+                const int64_t id = (own ? t0 : t0 / CAND_PART_TILES * CAND_PART_TILES) * CAND_TILE + i;
+                if (id < t0 * CAND_TILE || id >= t1 * CAND_TILE || id >= n_nodes || !tileflag[id >> 3]) continue;
+                const uint64_t more = wtable[id];
+                if (!more) continue;
+                wtable[id] = 0ull;
+                acc[i] += more;
+                atomicOr(&s_bits[i >> 5], 1u << (i & 31));
+            }
+            __syncthreads();
+        }
+        // Lane l looks at 16 ids of the wavefront's tile; a local tile is shared by all wavefronts, eight lanes' ids each.  The tile's weights go side by
+        // side to the start of its piece of the table, and a bit per id in place of the groups' flags.
+        if (!own && wave >= CAND_PART_TILES) return;
+        const int64_t tile = own ? t0 : t0 / CAND_PART_TILES * CAND_PART_TILES + wave;
+        if (tile < t0 || tile >= t1) return;   // (the whole wavefront; of a local tile, none)
+        const uint32_t base = own ? 0u : (uint32_t)wave * CAND_TILE, tile_id = (uint32_t)tile * CAND_TILE;   // (ids: below 2^31 + 1024)
+        const uint32_t piece = reinterpret_cast<const uint16_t *>(s_bits)[base / 16 + lane];
+        const uint32_t cnt = (uint32_t)__popc(piece), incl = wave_inclusive_scan<uint32_t>(cnt), n_t = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1);
+        const bool mine = !own || lane >> 3 == wave;
+        const int64_t at16 = (int64_t)tile_id / 16 + lane;
+        if (mine && at16 < n_words * 4 && (piece || table)) reinterpret_cast<uint16_t *>(tileflag)[at16] = (uint16_t)piece;
+        const uint32_t id0 = tile_id + lane * 16;
+        uint32_t put = tile_id + incl - cnt, n_local = 0;
+        uint64_t wl = 0, wa = 0;
+        for (uint32_t bits = mine ? piece : 0u; bits; bits &= bits - 1u) {
+            const uint32_t k = (uint32_t)__ffs((int)bits) - 1u;
+            const uint64_t v = acc[base + lane * 16 + k];
+            wtable[put++] = v;
+            const bool local = (int64_t)(id0 + k) >= lo && (int64_t)(id0 + k) < hi;
+            wa += v;
+            wl += local ? v : 0ull;
+            n_local += local ? 1u : 0u;
+        }
+        wl = wave_sum(wl); wa = wave_sum(wa);
+        n_local = wave_sum(n_local);
+        if (own) {
+            if (lane == 0) { lds[wave][0] = n_local; lds[wave][1] = wl; lds[wave][2] = wa - wl; }
+            __syncthreads();   // (all wavefronts of a local tile's block come here)
+            if (wave) return;
+        }
+        unsigned long long sum = lane == 0 ? (uint64_t)n_t << 32 | (own ? 0u : n_local) : (lane == 1 ? wl : wa - wl);
+        if (own && lane < 3) {
+            sum = lane == 0 ? (uint64_t)n_t << 32 : 0ull;
+            for (int i = 0; i < WAVES; ++i) sum += lds[i][lane];
+        }
+        publish_tile(tile, sum, partial, gtot);
     };
-    // share s takes the runs s, s + split, ...; of those, the first `readers` wavefronts one after the other (a bin's groups are
-    // short: where there are few runs, fewer wavefronts have fewer instructions to issue)
-    int readers = own ? WAVES : CAND_PART_TILES;
-    extents(lane * readers + wave);
-    const unsigned long long call = call_number(epoch), tag = call_tag(call, SLOT_CAND);
-    int64_t n_chunks = 0, n_runs = 0;
-    if (epoch[EPOCH_HANDED] == call) {
-        n_chunks = (meta[META_EDGES] + EDGE_TILE - 1) / EDGE_TILE;
-        n_runs = WHOLE ? (n_chunks + WIDE_CHUNKS - 1) / WIDE_CHUNKS : run_count(n_chunks, stg);
-        if (n_runs > most) n_runs = most;
-    }
-    const bool table = epoch[EPOCH_ADDED] == call;   // something went through the table of accumulators
-    const int64_t tile0 = stg.lo / CAND_TILE, local_end = tile0 + stg.tiles;
-    int64_t t0, t1;
-    if (b < 0) {
-        t0 = (int64_t)blk * CAND_PART_TILES;
-        t1 = t0 + CAND_PART_TILES;
-        if (stg.tiles > 0 && t1 > tile0) t1 = tile0;
-    } else if (own) {
-        t0 = tile0 + tile_own;
-        t1 = t0 + 1;
+    if constexpr (!FEW) {
+        whole_block((int32_t)blk - stg.below);
     } else {
-        t0 = (local_end / CAND_PART_TILES + (b - own_blocks)) * CAND_PART_TILES;
-        t1 = t0 + CAND_PART_TILES;
-        if (t0 < local_end) t0 = local_end;
-    }
-    if (t1 > n_tiles) t1 = n_tiles;
-    // the last `split` of a local tile's blocks share its sums, the others leave
-    uint32_t split = 1;
-    if (own && n_runs) {
-        const int64_t want = (WHOLE ? n_runs * WIDE_CHUNKS : n_chunks) * EDGE_TILE / SPLIT_MIN_EDGES / stg.tiles;
-        split = (uint32_t)(want < n_runs ? want : n_runs);
-        if (split > (uint32_t)stg.max_split) split = (uint32_t)stg.max_split;
-        if (split < 1u) split = 1u;
-    }
-    const int share = own ? (int)round_own - (stg.max_split - (int)split) : 0;
-    if (t0 >= t1 || share < 0) return;   // the whole block
-    const uint32_t ids = own ? CAND_TILE : WIDE_IDS;
-    for (uint32_t i = tid; i < ids; i += CAND_PART_BLOCK) acc[i] = 0ull;
-    for (uint32_t i = tid; i < ids / 32; i += CAND_PART_BLOCK) s_bits[i] = 0u;
-    __syncthreads();
-    const bool sparse = !own && n_runs <= CAND_PART_TILES * WAVE;   // few entries: their bits are set one by one, else from the sums
-    if (split > 1 || (!own && !sparse)) {
-        readers = WAVES;
-        extents((int64_t)(lane * readers + wave) * split + share);
-    }
-    for (int64_t r0 = 0; r0 * split + share < n_runs && wave < readers; r0 += readers * WAVE) {
-        const int64_t run = (r0 + lane * readers + wave) * split + share;
-        // entry j of the sequence belongs to the first lane whose running count exceeds j
-        const int32_t n = run < n_runs && beg <= end && end <= WIDE_EDGES ? (int32_t)(end - beg) : 0;
+        if ((int32_t)blk < own_blocks) {
+            whole_block((int32_t)blk);
+            return;
+        }
+        const int32_t others = stg.bins - stg.tiles, nth = ((int32_t)blk - own_blocks) * WAVES + wave;
+        const int32_t bin = nth < stg.below ? nth : nth + stg.tiles;
+        const bool mine = nth < others;
+        uint32_t beg = 0, end = 0;
+        {
+            const int64_t most = stg.chunks / WIDE_CHUNKS;
+            const uint16_t *p = stg.off + (mine ? bin : 0) + (lane < most ? lane : 0) * WIDE_STRIDE;
+            beg = p[0];
+            end = p[1];
+        }
+        const unsigned long long call = call_number(epoch);
+        int64_t n_runs = 0;
+        if (epoch[EPOCH_HANDED] == call) {
+            n_runs = ((meta[META_EDGES] + EDGE_TILE - 1) / EDGE_TILE + WIDE_CHUNKS - 1) / WIDE_CHUNKS;
+            const int64_t most = stg.chunks / WIDE_CHUNKS;
+            if (n_runs > most) n_runs = most;
+        }
+        const int64_t tile0 = stg.lo / CAND_TILE, local_end = tile0 + stg.tiles;
+        int64_t first_tile, t0, t1;
+        if (nth < stg.below) {
+            first_tile = t0 = (int64_t)nth * CAND_PART_TILES;
+            t1 = t0 + CAND_PART_TILES;
+            if (stg.tiles > 0 && t1 > tile0) t1 = tile0;
+        } else {
+            first_tile = t0 = (local_end / CAND_PART_TILES + (nth - stg.below)) * CAND_PART_TILES;
+            t1 = t0 + CAND_PART_TILES;
+            if (t0 < local_end) t0 = local_end;
+        }
+        if (t1 > n_tiles) t1 = n_tiles;
+        if (tid == 0) n_crowded = 0;
+        __syncthreads();
+        constexpr int MOST = WIDE_IDS / WAVES;   // sums that a wavefront has room for
+        const int64_t word = first_tile * CAND_WORDS + lane;   // this lane's 64 ids
+        bool wave_does = mine && t0 < t1;
+        if (wave_does && epoch[EPOCH_ADDED] == call)   // something went through the table of accumulators: of this bin?
+            wave_does = !__any(first_tile + (lane >> 4) >= t0 && first_tile + (lane >> 4) < t1 && word < n_words && reinterpret_cast<const uint64_t *>(tileflag)[word < n_words ? word : 0] != 0ull);
+        const int32_t n = lane < n_runs && beg <= end && end <= WIDE_EDGES ? (int32_t)(end - beg) : 0;
         const int32_t incl = wave_inclusive_scan<int32_t>(n);
         const int32_t total = __builtin_amdgcn_readlane(incl, WAVE - 1);
-        const int32_t first = (int32_t)(run * WIDE_EDGES) + (int32_t)beg - (incl - n);   // it is entry first + j (at most STAGE_EDGES_MAX)
-        extents((r0 + readers * WAVE + lane * readers + wave) * split + share);
-        auto entry = [&](int32_t j) {
-            int lo_l = 0, hi_l = WAVE - 1;
+        if (mine && t0 < t1 && (!wave_does || total > MOST || n_runs > WAVE)) {   // the whole block's, afterwards
+            if (lane == 0) crowded[atomicAdd(&n_crowded, 1)] = nth < stg.below ? nth - stg.below : own_blocks + (nth - stg.below);
+            wave_does = false;
+        }
+        if (wave_does) {
+            uint32_t *const bits = few_bits[FEW ? wave : 0];
+            unsigned long long *const sum = acc + wave * MOST;
+            reinterpret_cast<uint64_t *>(bits)[lane] = 0ull;
+            // entry j of the sequence belongs to the first lane whose running count exceeds j
+            const int32_t first = lane * WIDE_EDGES + (int32_t)beg - (incl - n);
+            auto entry = [&](int32_t j) {
+                int lo_l = 0, hi_l = WAVE - 1;
 #pragma unroll
-            for (int it = 0; it < 6; ++it) {
-                const int mid = (lo_l + hi_l) >> 1;
-                if (__shfl(incl, mid, WAVE) > j) hi_l = mid; else lo_l = mid + 1;
+                for (int it = 0; it < 6; ++it) {
+                    const int mid = (lo_l + hi_l) >> 1;
+                    if (__shfl(incl, mid, WAVE) > j) hi_l = mid; else lo_l = mid + 1;
+                }
+                const int32_t pos = __shfl(first, lo_l, WAVE) + j;
+                return stg.e[j < total ? pos : 0];
+            };
+            uint64_t v[MOST / WAVE];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = entry(u * WAVE + lane);
+            if (total > U * WAVE) {
+#pragma unroll
+                for (int u = U; u < MOST / WAVE; ++u) v[u] = entry(u * WAVE + lane);
+            } else {
+#pragma unroll
+                for (int u = U; u < MOST / WAVE; ++u) v[u] = 0ull;
             }
-            const int32_t pos = __shfl(first, lo_l, WAVE) + j;
-            return stg.e[j < total ? pos : 0];   // (unconditional; entry 0 stands in past the end)
-        };
-        auto take = [&](int32_t j, uint64_t v) {
-            if (j >= total) return;
-            const uint32_t at = (uint32_t)v & (ids - 1u);
-            atomicAdd(&acc[at], (unsigned long long)(v / WIDE_IDS));
-            if (sparse) atomicOr(&s_bits[at >> 5], 1u << (at & 31));
-        };
-        for (int32_t j0 = 0; j0 < total; j0 += U * WAVE) {
-            if (total - j0 <= WAVE) {
-                take(j0 + lane, entry(j0 + lane));
-                break;
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int u = 0; u < MOST / WAVE; ++u) {
+                const uint32_t at = (uint32_t)v[u] & (WIDE_IDS - 1u);
+                if (u * WAVE + lane < total) atomicOr(&bits[at >> 5], 1u << (at & 31));
             }
-            uint64_t v[U];
+            __builtin_amdgcn_wave_barrier();
+            // a sum for every id that an entry names, in the order of the ids
+            const uint64_t here = reinterpret_cast<const uint64_t *>(bits)[lane];
+            const uint32_t cnt = (uint32_t)__popcll(here), upto = wave_inclusive_scan<uint32_t>(cnt), before = upto - cnt;
+            const int32_t ids = (int32_t)__builtin_amdgcn_readlane((int)upto, WAVE - 1);
+            for (int32_t i = lane; i < ids; i += WAVE) sum[i] = 0ull;
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-            for (int u = 0; u < U; ++u) v[u] = entry(j0 + u * WAVE + lane);
-#pragma unroll
-            for (int u = 0; u < U; ++u) take(j0 + u * WAVE + lane, v[u]);
-        }
-    }
-    __syncthreads();
-    if (own && share != (int)split - 1) {   // left for the block of the last share
-        for (int i = tid; i < CAND_TILE; i += CAND_PART_BLOCK) st_relaxed(&stg.part[(int64_t)b * CAND_TILE + i], acc[i]);
-        wait_memory_ops();
-        __syncthreads();
-        if (tid == 0) st_relaxed(&stg.part_flag[b], tag);
-        return;
-    }
-    if (split > 1) {   // (the other shares' blocks were dispatched before and wait for nobody)
-        const int64_t next = stg.adjacent ? 1 : stg.tiles, first = b - share * next;
-        bool ok = true;
-        if (tid < share) ok = wait_tag(&stg.part_flag[first + tid * next], tag, wait_limit(epoch));
-        if (!ok) atomicOr(status, CSGS_ST_INTERNAL);
-        __syncthreads();
-        // (ids past the last node stay without a weight whatever a share holds that was not waited for: the weights go to the table side by side)
-        const int n_ids = n_nodes - t0 * CAND_TILE < CAND_TILE ? (int)(n_nodes - t0 * CAND_TILE) : CAND_TILE;
-        for (int i = tid; i < n_ids; i += CAND_PART_BLOCK) {
-            unsigned long long v = acc[i];
-            for (int k = 0; k < share; ++k) v += ld_relaxed(&stg.part[(first + k * next) * CAND_TILE + i]);
-            acc[i] = v;
-        }
-        __syncthreads();
-    }
-    if (!sparse) {
-        for (uint32_t i = tid; i < ids; i += CAND_PART_BLOCK) {
-            const uint64_t word = __ballot(acc[i] != 0);
-            if (lane == 0) reinterpret_cast<uint64_t *>(s_bits)[i >> 6] = word;
-        }
-        __syncthreads();
-    }
-    if (table) {   // what came through the table joins the sums, and the table is clean
-        for (uint32_t i = tid; i < ids; i += CAND_PART_BLOCK) {
-            const int64_t id = (own ? t0 : t0 / CAND_PART_TILES * CAND_PART_TILES) * CAND_TILE + i;
-            if (id < t0 * CAND_TILE || id >= t1 * CAND_TILE || id >= n_nodes || !tileflag[id >> 3]) continue;
-            const uint64_t more = wtable[id];
-            if (!more) continue;
-            wtable[id] = 0ull;
-            acc[i] += more;
-            atomicOr(&s_bits[i >> 5], 1u << (i & 31));
+            for (int u = 0; u < MOST / WAVE; ++u) {
+                if (u >= U && total <= U * WAVE) break;
+                const uint32_t at = (uint32_t)v[u] & (WIDE_IDS - 1u);
+                const uint32_t rank = (uint32_t)__shfl((int)before, (int)(at >> 6), WAVE);
+                const uint64_t w = (uint64_t)(uint32_t)__shfl((int)(uint32_t)here, (int)(at >> 6), WAVE) |
+                                   (uint64_t)(uint32_t)__shfl((int)(uint32_t)(here >> 32), (int)(at >> 6), WAVE) << 32;
+                if (u * WAVE + lane < total)
+                    atomicAdd(&sum[rank + (uint32_t)__popcll(w & ((1ull << (at & 63u)) - 1ull))], (unsigned long long)(v[u] / WIDE_IDS));
+            }
+            __builtin_amdgcn_wave_barrier();
+            // out, each tile's to the start of its piece of the table; 16 lanes hold a tile
+            const int64_t tile = first_tile + (lane >> 4);
+            const uint32_t tile_id = (uint32_t)tile * CAND_TILE, tile_before = (uint32_t)__shfl((int)before, lane & 48, WAVE);
+            if (here) reinterpret_cast<uint64_t *>(tileflag)[word] = here;
+            uint32_t put = tile_id + before - tile_before, rank = before, n_local = 0;
+            uint64_t wl = 0, wa = 0;
+            for (uint64_t left = here; left; left &= left - 1ull) {
+                const int64_t id = word * 64 + (__ffsll((unsigned long long)left) - 1);
+                const uint64_t w = sum[rank++];
+                wtable[put++] = w;
+                const bool local = id >= lo && id < hi;
+                wa += w;
+                wl += local ? w : 0ull;
+                n_local += local ? 1u : 0u;
+            }
+            uint64_t counts = (uint64_t)cnt << 32 | n_local;
+#define CSGS_ROW_SUM(CTRL) (counts += dpp_move_t<uint64_t, CTRL, 0xF>(counts), wl += dpp_move_t<uint64_t, CTRL, 0xF>(wl), wa += dpp_move_t<uint64_t, CTRL, 0xF>(wa))
+            CSGS_ROW_SUM(0x128); CSGS_ROW_SUM(0x124); CSGS_ROW_SUM(0x122); CSGS_ROW_SUM(0x121);   // row_ror: 16 lanes' sums, to all of them
+#undef CSGS_ROW_SUM
+            const int of = lane & 15;
+            if (of < 3 && tile >= t0 && tile < t1) publish_sum(tile, of, of == 0 ? counts : (of == 1 ? wl : wa - wl), partial, gtot);
         }
         __syncthreads();
+        const int32_t many = n_crowded;
+        for (int32_t i = 0; i < many; ++i) {
+            whole_block(crowded[i]);
+            __syncthreads();
+        }
     }
-    // Lane l looks at 16 ids of the wavefront's tile; a local tile is shared by all wavefronts, eight lanes' ids each.  The tile's weights go side by
-    // side to the start of its piece of the table, and a bit per id in place of the groups' flags.
-    if (!own && wave >= CAND_PART_TILES) return;
-    const int64_t tile = own ? t0 : t0 / CAND_PART_TILES * CAND_PART_TILES + wave;
-    if (tile < t0 || tile >= t1) return;   // (the whole wavefront; of a local tile, none)
-    const uint32_t base = own ? 0u : (uint32_t)wave * CAND_TILE, tile_id = (uint32_t)tile * CAND_TILE;   // (ids: below 2^31 + 1024)
-    const uint32_t piece = reinterpret_cast<const uint16_t *>(s_bits)[base / 16 + lane];
-    const uint32_t cnt = (uint32_t)__popc(piece), incl = wave_inclusive_scan<uint32_t>(cnt), n_t = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1);
-    const bool mine = !own || lane >> 3 == wave;
-    const int64_t at16 = (int64_t)tile_id / 16 + lane;
-    if (mine && at16 < n_words * 4 && (piece || table)) reinterpret_cast<uint16_t *>(tileflag)[at16] = (uint16_t)piece;
-    const uint32_t id0 = tile_id + lane * 16;
-    uint32_t put = tile_id + incl - cnt, n_local = 0;
-    uint64_t wl = 0, wa = 0;
-    for (uint32_t bits = mine ? piece : 0u; bits; bits &= bits - 1u) {
-        const uint32_t k = (uint32_t)__ffs((int)bits) - 1u;
-        const uint64_t v = acc[base + lane * 16 + k];
-        wtable[put++] = v;
-        const bool local = (int64_t)(id0 + k) >= lo && (int64_t)(id0 + k) < hi;
-        wa += v;
-        wl += local ? v : 0ull;
-        n_local += local ? 1u : 0u;
-    }
-    wl = wave_sum(wl); wa = wave_sum(wa);
-    n_local = wave_sum(n_local);
-    if (own) {
-        if (lane == 0) { lds[wave][0] = n_local; lds[wave][1] = wl; lds[wave][2] = wa - wl; }
-        __syncthreads();   // (all wavefronts of a local tile's block come here)
-        if (wave) return;
-    }
-    unsigned long long sum = lane == 0 ? (uint64_t)n_t << 32 | (own ? 0u : n_local) : (lane == 1 ? wl : wa - wl);
-    if (own && lane < 3) {
-        sum = lane == 0 ? (uint64_t)n_t << 32 : 0ull;
-        for (int i = 0; i < WAVES; ++i) sum += lds[i][lane];
-    }
-    publish_tile(tile, sum, partial, gtot);
 }
 
 // Two kinds.  With PACKED a block takes four tiles (or two) that cand_partials has packed: where there are many tiles (several instances) the kernel is bound by
@@ -1436,17 +1580,20 @@ static int build_probs_impl(const csgs_graph *g, const int32_t *S, int32_t nS, c
                     w.tileflag, rows.bound_note, w.epoch, status, stg, ig.is);
     }
     CSGS_LAUNCH_CHECK();
-    const InstGrid part = inst_grid(w, part_blocks, CAND_PART_BLOCK);
+    const int64_t others = below + rest;
+    const bool few = wide && !stg.runs && tiles && fmin(mean, (double)w.chunk_cap) * EDGE_TILE <= (double)(BIN_FEW * others);
+    const InstGrid part = inst_grid(w, few ? tiles * split + (others + CAND_PART_BLOCK / WAVE - 1) / (CAND_PART_BLOCK / WAVE) : part_blocks, CAND_PART_BLOCK);
 #define CSGS_CAND_PARTIALS(TILES, PACK)                                                                                                       \
     CSGS_LAUNCH(K_CAND_PARTIALS, (cand_partials<TILES, PACK>), part.grid, dim3(CAND_PART_BLOCK), st, w.wtable, w.tileflag, n_words, g->n_nodes, \
                 w.n_tiles, g->local_lo, g->local_hi, rows.meta, stg, (int32_t)(tiles ? below : part_blocks), w.epoch,                   \
                 (unsigned long long *)w.partial, w.gtot, status, part.is)
     const bool packed = wide || w.n_tiles * w.n_inst >= CAND_PACKED_FROM;   // (then `per` is CAND_PART_TILES)
-#define CSGS_BIN_SUMS(WHOLE)                                                                                                                  \
-    CSGS_LAUNCH(K_CAND_PARTIALS, bin_sums<WHOLE>, part.grid, dim3(CAND_PART_BLOCK), st, w.wtable, w.tileflag, n_words, g->n_nodes, w.n_tiles, \
+#define CSGS_BIN_SUMS(WHOLE, FEW)                                                                                                             \
+    CSGS_LAUNCH(K_CAND_PARTIALS, (bin_sums<WHOLE, FEW>), part.grid, dim3(CAND_PART_BLOCK), st, w.wtable, w.tileflag, n_words, g->n_nodes, w.n_tiles, \
                 g->local_lo, g->local_hi, rows.meta, stg, w.epoch, (unsigned long long *)w.partial, w.gtot, status, part.is)
-    if (wide && stg.runs) CSGS_BIN_SUMS(false);
-    else if (wide) CSGS_BIN_SUMS(true);
+    if (wide && stg.runs) CSGS_BIN_SUMS(false, false);
+    else if (few) CSGS_BIN_SUMS(true, true);
+    else if (wide) CSGS_BIN_SUMS(true, false);
     else if (packed) CSGS_CAND_PARTIALS(CAND_PART_TILES, true);
     else if (per == 1) CSGS_CAND_PARTIALS(1, false);
     else CSGS_CAND_PARTIALS(CAND_PART_TILES, false);

@@ -582,6 +582,46 @@ def test_weight_scan_of_many_edges(dev, n, lo, hi, n_rows, degree, remote_ids, c
     assert int(torch.count_nonzero(ws.buf.view(K, -1)[:, :csgs.csgs_workspace_clean_bytes(n) // 8]).item()) == 0
 
 
+# The same with few edges to a bin, whose sums are one wavefront's: bins with none, with more than it has room for (the block's), with more than the scan
+# hands over (through the table), bins cut by the local range
+@pytest.mark.parametrize("lo,hi,local,hot", [(0, 106_000, 0.8, 0.0), (700_300, 806_001, 0.7, 0.02), (1_790_001, 1_900_001, 0.7, 0.25), (700_300, 806_001, 0.1, 0.0)])
+def test_weight_scan_of_few_edges_a_bin(dev, lo, hi, local, hot):
+    from paper_2101_07706_amd import csgs, pipeline
+    rng = np.random.default_rng(lo + 1)
+    n, n_rows, degree, K, base = 1_900_001, 9000, 38, 8, 50_000
+    print(f"[few edges a bin] local {lo}..{hi}, {hot} of the others in 4096 ids", flush=True)
+    shape = (base, degree)
+    remote = (hi + rng.integers(0, n - hi + lo, shape)) % n
+    remote = np.where(rng.random(shape) < hot, 409_600 + rng.integers(0, 4096, shape), remote)
+    col = np.where(rng.random(shape) < local, rng.integers(lo, hi, shape), remote).astype(np.int32)
+    col[:, 0] = np.where(rng.random(base) < 0.1, 1_200_000 + rng.integers(0, 3, base), col[:, 0])   # (few ids with many edges)
+    col.sort(axis=1)
+    rows = -(-n // base)
+    col = np.tile(col, (rows, 1))[:n]
+    val = np.tile(rng.random(shape).astype(np.float32) / degree, (rows, 1))[:n]
+    g = synth.Graph(n, np.arange(n + 1, dtype=np.int64) * degree, col.reshape(-1), val.reshape(-1), np.array([0, lo, hi, n], np.int32) if lo else np.array([0, hi, n], np.int32),
+                    1 if lo else 0, 1.0)
+    dg = pipeline.DeviceGraph(g, dev)
+    lb = pipeline.LayerBuffers(n_rows, 1, n, 1, dg.n_parts, dev, n_inst=K)
+    ws = pipeline.Workspace(n, n_rows, 1, g.nnz, dev, n_inst=K, inst_stride=lb.stride)
+    S = [np.sort(rng.choice(n, n_rows, replace=False)).astype(np.int32) for _ in range(K)]
+    counts = [n_rows] * (K - 1) + [n_rows // 30]
+    for k in range(K):
+        lb.inst(k).S0.copy_(torch.from_numpy(S[k]).to(dev))
+        lb.inst(k).n_next.fill_(counts[k])
+    for again in range(2):
+        csgs.csgs_build_probs(dg.c, lb.S0[:n_rows], 4.0, lb.cand_id, lb.cand_w, lb.cdf, lb.q, lb.stats, ws.desc, lb.status, nS_dev=lb.n_next)
+        torch.cuda.synchronize()
+    for k in (0, 5, K - 1):
+        want, b = oracle.build_probs(g, S[k][:counts[k]], 4.0), lb.inst(k)
+        n_c = len(want.cand_id)
+        assert int(b.status.item()) == 0 and b.stats_host().n_cand == n_c and b.stats_host().n_local == int(((want.cand_id >= lo) & (want.cand_id < hi)).sum())
+        np.testing.assert_array_equal(b.cand_id[:n_c].cpu().numpy(), want.cand_id)
+        np.testing.assert_array_equal(b.cand_w[:n_c].cpu().numpy().view(np.uint64), want.cand_w)
+        np.testing.assert_array_equal(b.cdf[:n_c].cpu().numpy().view(np.uint64), want.cdf)
+    assert int(torch.count_nonzero(ws.buf.view(K, -1)[:, :csgs.csgs_workspace_clean_bytes(n) // 8]).item()) == 0
+
+
 # The transpose in one launch: a column that holds more entries than a block's lists, row pointers that start inside the arrays, empty rows, the most
 # columns it takes and one more (several launches), two calls bit for bit.
 @pytest.mark.parametrize("nS,n_cols,most,hub", [(20_000, 700, 6, True), (20_000, 65_536, 6, False), (20_000, 65_537, 6, False), (3, 1, 1, True), (700, 256, 300, True), (1, 257, 200, False)])
