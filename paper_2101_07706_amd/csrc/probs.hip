@@ -1274,24 +1274,37 @@ __global__ __launch_bounds__(256) void cand_emit(uint64_t *__restrict__ wtable, 
         c2 = c1 + s_cnt[2];
         n_t = c2 + s_cnt[3];
     };
-    uint32_t id = 0;
-    uint64_t wi = 0;
-    auto fetch = [&](uint32_t i) {   // candidate i < n_t of the block
-        const int src = i < c0 ? 0 : (i < c1 ? 1 : (i < c2 ? 2 : 3));
-        const uint32_t k = i - (src == 0 ? 0u : (src == 1 ? c0 : (src == 2 ? c1 : c2)));
-        if (PACKED) {
-            const uint32_t first = ((uint32_t)t + src) * CAND_TILE;
-            id = first + s_at[src][k];
-            wi = wtable[first + k];
-            wtable[first + k] = 0ull;   // back to the clean state
-        } else {
-            id = s_id[src][k];
-            wi = s_wt[src][k];
+    // A pass takes ROWS times 256 candidates, a wavefront up to ROWS rows of 64 that lie one after the other (as many for each wavefront as the pass needs).
+    // Four where the tiles are few and full: one distribution of 65 536 rows 66.8 -> 65.0 us.  In their registers fewer blocks fit, so one where there are
+    // many (step of eight mini-batches 662 -> 669 with four, level with two) and where the list lies in LDS.
+    constexpr int ROWS = PACKED && TILES == EMIT_ONE ? 4 : 1;
+    uint32_t id[ROWS];
+    uint64_t wi[ROWS];
+    auto rows_of = [&](uint32_t base) { return n_t - base > 256u * (ROWS - 1) ? (uint32_t)ROWS : (n_t - base + 255u) / 256u; };
+    auto place = [&](uint32_t base, uint32_t rows, int r) { return base + ((uint32_t)wave * rows + (uint32_t)r) * WAVE + (uint32_t)lane; };
+    auto fetch = [&](uint32_t base) {   // candidates of the block, the last one in the place of those that do not exist
+        const uint32_t rows = rows_of(base);
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            if ((uint32_t)r >= rows) break;
+            const uint32_t at = place(base, rows, r), i = at < n_t ? at : n_t - 1u;
+            if (ROWS == 1 && at >= n_t) break;   // (one row: nothing waits for this load before it is used)
+            const int src = i < c0 ? 0 : (i < c1 ? 1 : (i < c2 ? 2 : 3));
+            const uint32_t k = i - (src == 0 ? 0u : (src == 1 ? c0 : (src == 2 ? c1 : c2)));
+            if (PACKED) {
+                const uint32_t first = ((uint32_t)t + src) * CAND_TILE;
+                id[r] = first + s_at[src][k];
+                wi[r] = wtable[first + k];
+                if (ROWS == 1) wtable[first + k] = 0ull;   // back to the clean state
+            } else {
+                id[r] = s_id[src][k];
+                wi[r] = s_wt[src][k];
+            }
         }
     };
     if (PACKED) {   // the first pass' weights are asked for before the sums are put together
         counts();
-        if (threadIdx.x < n_t) fetch(threadIdx.x);
+        if (n_t) fetch(0);
     }
     {   // lanes 0 .. 5 add up one of the six sums each; the others get them by lane broadcast (not every lane all 24 terms)
         const uint64_t mine = lane < 6 ? s_red[0][lane] + s_red[1][lane] + s_red[2][lane] + s_red[3][lane] : 0ull;
@@ -1334,29 +1347,39 @@ __global__ __launch_bounds__(256) void cand_emit(uint64_t *__restrict__ wtable, 
     const uint32_t lo_u = lo > 0 ? (uint32_t)lo : 0u, hi_u = hi > 0 ? (uint32_t)hi : 0u;
     const int64_t base_cnt = (int64_t)(pre[0] >> 32);
     uint64_t run_w = pre[1] * m_local + pre[2] * m_remote;   // skewed weight before the packed candidate at pass_base
-    for (uint32_t pass_base = 0; pass_base < n_t; pass_base += 256u) {
-        const uint32_t i = pass_base + threadIdx.x;
-        const bool have = i < n_t;
-        const bool wave_has = pass_base + (uint32_t)wave * WAVE < n_t;   // the same for the whole wavefront
-        uint64_t wsk = 0, incl = 0;
-        if (have && (!PACKED || pass_base)) fetch(i);
-        if (wave_has) {
-            if (have) wsk = wi * ((id >= lo_u && id < hi_u) ? m_local : m_remote);
-            incl = wave_inclusive_scan(wsk);
-            if (lane == WAVE - 1) s_w[wave] = incl;
-        } else if (lane == WAVE - 1) {
-            s_w[wave] = 0ull;
+    for (uint32_t pass_base = 0; pass_base < n_t; pass_base += ROWS * 256u) {
+        const uint32_t rows = rows_of(pass_base);
+        if (!PACKED || pass_base) fetch(pass_base);
+        uint64_t wsk[ROWS], incl[ROWS], sum = 0;   // sum: of this wavefront's candidates
+        if (place(pass_base, rows, 0) - (uint32_t)lane < n_t) {   // (the whole wavefront)
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                if ((uint32_t)r >= rows) break;
+                const uint32_t i = place(pass_base, rows, r);
+                wsk[r] = i < n_t ? wi[r] * ((id[r] >= lo_u && id[r] < hi_u) ? m_local : m_remote) : 0ull;
+                incl[r] = sum + wave_inclusive_scan(wsk[r]);
+                sum = ROWS == 1 ? incl[r] : __shfl(incl[r], WAVE - 1, WAVE);
+            }
         }
+        if (lane == WAVE - 1) s_w[wave] = sum;
         __syncthreads();
         uint64_t before = run_w;
         for (int w2 = 0; w2 < wave; ++w2) before += s_w[w2];
-        if (have) {
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            if ((uint32_t)r >= rows) break;
+            const uint32_t i = place(pass_base, rows, r);
+            if (i >= n_t) break;
+            if (PACKED && ROWS > 1) {   // back to the clean state, now that all weights of the pass are on their way
+                const int src = i < c0 ? 0 : (i < c1 ? 1 : (i < c2 ? 2 : 3));
+                wtable[((uint32_t)t + src) * CAND_TILE + i - (src == 0 ? 0u : (src == 1 ? c0 : (src == 2 ? c1 : c2)))] = 0ull;
+            }
             const int64_t pos = base_cnt + i;
             if (pos < cap) {
-                cand_id[pos] = (int32_t)id;
-                cand_w[pos] = wi;
-                cdf[pos] = before + incl;
-                if (q) q[pos] = (float)((double)wsk / total_d);
+                cand_id[pos] = (int32_t)id[r];
+                cand_w[pos] = wi[r];
+                cdf[pos] = before + incl[r];
+                if (q) q[pos] = (float)((double)wsk[r] / total_d);
             }
         }
         run_w += s_w[0] + s_w[1] + s_w[2] + s_w[3];
