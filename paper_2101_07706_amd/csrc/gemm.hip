@@ -27,6 +27,9 @@
 // 8192 x 256 x 256 25 -> 20, 8192 x 256 x 47 12.2 -> 7.7, 2048 x 602 x 256 27 -> 15.5, 1024 x 256 x 256 9.5 -> 5.9,
 // 131072 x 256 x 256 278 -> 262, odd sizes (20000 x 301 x 201) 85 -> 53.
 //
+// Large Z W and G W^T leave these kernels for sums of 8-bit digits on the integer matrix cores, where digits_plan (gemm_rules.hpp)
+// expects those to be done first: digits.hip, 131072 x 256 x 256 252 -> 126 us.  The figures above are for these kernels.
+//
 // Block ids are remapped so that consecutive tiles (same rows of Z, neighbouring column tiles)
 // land on the same XCD and share its L2.
 #include <type_traits>
