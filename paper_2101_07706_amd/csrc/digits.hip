@@ -500,8 +500,9 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
             const int inst = step % n_inst, s0 = step / n_inst * RS;
             const int32_t *rd = rows_of(inst);
             if (!multiplies) break;
+            const int end = NT * row_tiles(resolve_count(M_bound, rd) - s0, RS);   // (a tile that starts past the last row would read before the matrix)
 #pragma unroll 1
-            for (int ti = wr * NT; ti < TILES * NT; ti += ti % NT == NT - 1 ? (wrs - 1) * NT + 1 : 1)
+            for (int ti = wr * NT; ti < end; ti += ti % NT == NT - 1 ? (wrs - 1) * NT + 1 : 1)
                 if (n0 + 16 * (ti % NT) < N)
                     product_tile<MODE, 1, 1, TAIL_32, uint32_t>((const float *)((const char *)A + inst * cs.x), here(lda), here(Bm), here(ldb),
                                                                 (float *)((char *)C + inst * cs.out), here(ldc), nullptr, here(M_bound), here(N),

@@ -45,6 +45,9 @@ inline bool far_apart(int64_t lda, int64_t ldb) { return lda >= (1 << 24) || ldb
 constexpr int DIGIT_CHUNK = 64, DIGIT_WAVES = 8;
 constexpr int digit_rows(int kc) { return kc == 1 ? 128 : kc == 2 ? 64 : kc <= 4 ? 32 : 16; }   // of a step
 
+// Tiles of 16 rows that hold one of the `left` rows from a step's first one to the last there is
+constexpr int row_tiles(int64_t left, int rows_of_step) { return left <= 0 ? 0 : (int)(((left < rows_of_step ? left : rows_of_step) + 15) / 16); }
+
 struct DigitsPlan {
     bool use;
     int kc;              // chunks of k that the kernel is made for

@@ -129,6 +129,25 @@ def test_digit_products_hard(dev, what, kind):
         assert bool((out[5:M:9, :N] == 0).all()) and bool((out[:M, 3:N:5] == 0).all())
 
 
+# More outputs that are small against row and column than a block lists, where the last step lacks whole tiles of rows: one feature 300 times the others
+# that no weight looks at, one output in fifty
+@pytest.mark.parametrize("what", ["H", "dZ"])
+@pytest.mark.parametrize("counted", [False, True])
+@pytest.mark.parametrize("K,M", [(256, 65_537), (128, 100_003), (64, 131_069)])
+def test_digit_products_many_listed(dev, what, counted, K, M):
+    N = 256
+    print(f"[digits] {what} {M} x {K} x {N} many small, counted {counted}", flush=True)
+    A, W, out = operands(dev, what, K, N, M, 7)
+    B = W if what == "H" else W.t()
+    A[:, 5] *= 300
+    B[5] = 0
+    m = M - 40 if counted else M
+    kw = dict(M_dev=torch.tensor([m], dtype=torch.int32, device=dev)) if counted else {}
+    product(what, A, W, out[:M, :N], **kw)
+    check(out[:m, :N], A[:m], B.contiguous())
+    assert bool(torch.isnan(out[m:]).all()) and bool(torch.isnan(out[:, N:]).all()), "wrote outside"
+
+
 @pytest.mark.parametrize("what", ["H", "dZ"])
 def test_digit_products_infinite(dev, what):
     K, N, M = 256, 256, 32_000

@@ -92,3 +92,25 @@ def test_digit_products_run_every_kernel(tmp_path):
         if use:
             cols = 16 if kc > 4 else 32
             assert 64 * kc >= K and cgs * wcs * cols >= N > (cgs - 1) * wcs * cols and wcs <= 8 and 1 <= rgs and 0 < few < M * n
+
+
+ASK_TILES = """
+#include <cstdio>
+#include "gemm_rules.hpp"
+int main()
+{
+    for (int kc : {1, 2, 3, 4, 5, 8})
+        for (long M = 1; M < 600; ++M)
+            for (long s0 = 0; s0 < M + 2 * csgs::digit_rows(kc); s0 += csgs::digit_rows(kc))
+                printf("%d %ld %ld %d\\n", csgs::digit_rows(kc), M, s0, csgs::row_tiles(M - s0, csgs::digit_rows(kc)));
+}
+"""
+
+
+def test_step_has_no_tile_past_the_last_row(tmp_path):
+    """The row offset of a tile's lanes is formed from its first row before that is compared with the count: it has to exist."""
+    (tmp_path / "ask.cpp").write_text(ASK_TILES)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", build.CSRC, "-o", str(tmp_path / "ask"), str(tmp_path / "ask.cpp")], check=True)
+    out = subprocess.run([str(tmp_path / "ask")], stdout=subprocess.PIPE, text=True, check=True).stdout
+    for rs, M, s0, tiles in np.array(out.split(), dtype=np.int64).reshape(-1, 4):
+        assert tiles == len([m0 for m0 in range(s0, s0 + rs, 16) if m0 < M])
