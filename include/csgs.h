@@ -330,13 +330,10 @@ int csgs_aggregate(const int32_t *adj_rowptr, const int32_t *adj_col, const floa
 int csgs_gather_rows(const void *X, int64_t ld, int64_t rows, int32_t F, int dtype, const int32_t *ids,
                      int64_t cap, const int64_t *n_dev, void *out, int64_t ldo, void *stream);
 
-/* H [M x Nout] = Z [M x K] W [K x Nout], all row-major fp32 (Eq. 1), summed on the matrix cores and
- * rounded to float once.  Small calls: operands widened to double, sums in double.  Large ones: operands
- * as 40-bit numbers against their row's (column's) largest, exact sums of their digits; outputs that come
- * out small against row and column are summed in double, so that none is off by more than 2^-22 of itself
- * (six standard deviations) beside the rounding, and over a matrix the two forms are equally far from 64-bit
- * sums.  The form follows from the sizes, the number of instances and the rows on the device, so equal rows
- * in calls of other sizes may differ in the last bit.
+/* H [M x Nout] = Z [M x K] W [K x Nout], all row-major fp32 (Eq. 1).  Operands are widened to
+ * double, products accumulate in double on the matrix cores, one rounding to float.  (Large calls
+ * reach the same bits by exact sums of the operands' digits; where such a sum does not decide the
+ * float, the output is summed in double.)  A row of H depends on its row of Z and on W alone.
  * With M_dev (device) only the first min(*M_dev, M) rows of H are computed and written; Z must
  * still be M rows of readable memory -- rows beyond the count may be read, whatever they hold
  * reaches no row that is written.
@@ -415,8 +412,8 @@ int csgs_layer_forward_n(const csgs_inst_strides *inst /*host*/, const int32_t *
  *     dW      = Z^T G                                  csgs_layer_gemm_grad_w
  *     dZ      = G W^T                                  csgs_layer_gemm_grad_z
  *     dH_prev = (P~^T dZ) .* [H_prev > 0]              csgs_aggregate_grad   (sigma = ReLU)
- * Same conventions as the forward calls: row-major fp32, double accumulation (the products as
- * csgs_layer_gemm; dW always in double), one rounding to float, M / nS / n_cols with nullable *_dev counterparts.
+ * Same conventions as the forward calls: row-major fp32, double accumulation (fp64 matrix cores
+ * for the two products, dZ of large calls as csgs_layer_gemm), one rounding to float, M / nS / n_cols with nullable *_dev counterparts.
  *
  * csgs_layer_gemm_grad_w: Z [M x K], G [M x Nout] -> dW [K x Nout].  The sum over the M rows is
  *   split into parts that are added in a fixed order; `scratch` (device, 8-byte aligned) holds the

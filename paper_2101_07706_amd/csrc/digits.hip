@@ -1,34 +1,43 @@
 // The layer products on the integer matrix cores, for calls large enough (`digits_plan`).
 //
 // A number x of a row is taken as the integer round(x 2^39 / R), R a power of two above the row's largest magnitude, in five signed 8-bit digits,
-// most significant first: x = R sum_i d_i 2^(-7 - 8 i).  A column of B likewise.  Fifteen of the products of a digit of A by a digit of B, those with
-// i + j <= 4, go through v_mfma_i32_16x16x64_i8 into five 32-bit sums, one for each i + j: exact, whatever the order.  Five conversions and four FMAs
-// put them together in double, and one rounding gives the float.
+// most significant first: x = R sum_i d_i 2^(-7 - 8 i).  A column of B likewise.  Nineteen of the products of a digit of A by a digit of B, those with
+// i + j <= 5, go through v_mfma_i32_16x16x64_i8 into six 32-bit sums, one for each i + j: exact, whatever the order.  Conversions and FMAs
+// put them together in double.
 //
-// What is left out: a rounding of 2^-40 R per number, and the four products of i + j = 5.  Together an output is off by 2^-40.5 sqrt(K) R_A R_B (one
-// standard deviation; R_A, R_B of its row and column).  That is nothing beside the rounding to float unless the output is small against
-// its row and column: one that comes out below 2^-16 sqrt(K) R_A R_B (one in four thousand of what a layer sees) is summed again in double, so that no
-// output is off by more than 2^-22 of itself (six standard deviations) beside its rounding.  Rows and columns that hold an infinity, a NaN or nothing but
-// numbers beyond 2^-90 .. 2^100 are computed in double, and so is a tile with many such outputs, and everything of a block that has too many to list.
-// Against 64 bits over 64 .. 131072 rows and 41 .. 512 columns both forms are off by the same 2.53e-8 (2-norm) and 5.96e-8 (largest, of the
-// larger of value and root mean square).
+// The result is the double form's (product_tile), bit for bit, whatever the operands: beside each sum stands the most that it and the double form's sum can
+// be apart, and where the floats at both ends of that differ the output is summed again in the double form's own order (product_at).  No average enters
+// into it.  In units of 2^-46 R_A R_B an output may be off by
+//  * the products that are left out: 2^-9 times the digits 2 .. 4 of the column, their magnitudes added up, for i + j = 6, and 2^-9 K for i + j > 6;
+//  * 128 for a number that the digits round, which those of at least 2^-16 R are not (counted by row and by column);
+//  * 2^-7 times the column's magnitudes, each as often as the double form rounds after it (v_mfma_f64_16x16x4 is four FMAs in ascending k, each rounded to
+//    nearest), with R_A in the place of the row's, for what that form's sum is off, and 1/8 of that for the roundings here;
+//  * 1 for what is cut off below.
+// Together about 2^-38 R_A R_B for 256 k.  Of normal numbers by uniform weights one output in 6800 is summed again with 64 k, one in 3200 with 256, one in 1400 with
+// 512; of features whose scales are log-normal (sigma 1.5) one in 750 with 256.  Rows and columns that hold an infinity, a NaN or nothing but numbers
+// beyond 2^-90 .. 2^100, rows so small that results may be denormal and tiles with many such outputs are computed in double, and everything of a
+// block that has too many to list.
+// (Fifteen products, those with i + j <= 4, and a bound for roundings that are independent of each other, 126 us where this takes 148: off by 2^-19 where values
+// repeat along k.)
 //
-// Why: the instruction does 4.7 POP/s here, 60 times what v_mfma_f64_16x16x4_f64 does, so fifteen products are a quarter of the time; what counts
-// then is the vector ALU, at ten instructions to cut a number and thirteen to put an output together.
+// Why: the instruction does 4.7 POP/s here, 60 times what v_mfma_f64_16x16x4_f64 does, so nineteen products are a third of the time; what counts
+// beside them is the vector ALU, at eleven instructions to cut a number and twenty to put an output together.
 //  * A block holds the digits of B for its columns in registers (all K, 16 NT columns a wavefront) and walks down the rows of A.  Every number
 //    of A is cut once per block, by the wavefront that loaded it (whole rows side by side, so that loads are whole lines and a row's maximum is
-//    known at once), and its digits go to LDS, from where all wavefronts read them.  The last digits of B, which one product in fifteen takes, wait in
+//    known at once), and its digits go to LDS, from where all wavefronts read them.  The last digits of B, which two products in nineteen take, wait in
 //    LDS too: with them in registers two wavefronts per SIMD do not fit.
 //  * Two buffers of rows, one barrier per step.  Half of the wavefronts (one on every SIMD) cut the next step's rows before they multiply, half
 //    afterwards, so that the one's vector instructions run beside the other's matrix instructions.
 //  * The order of the k within a chunk of 64 is free as long as A and B agree; k = 16 s + 4 g + j for byte 4 s + j of lane group g lets a lane write
 //    the digits of the four consecutive k it loaded as one word, and 16 bytes of room after 16 rows spread those words over the banks.
-// Measured before / now, us: 131072 rows 256 -> 256 252 / 126, 100 -> 256 112 / 79, 65 536 rows 512 -> 256 248 / 129, 58 624 rows 256 -> 256 131 / 72,
-// 4096 rows 512 -> 512 35 / 28.  A step of 32 rows by 256 columns takes 7 us, of which the matrix instructions 3.4; the rest is the
+//  * All of a tile's outputs are put together before the first is stored: each is a chain of ten instructions (131072 x 256 x 256 with a row's two outputs
+//    at a time 191 against 184).  Registers are full: one value more and the loop waits for a reload behind the loads of A (211 against 191).
+// Measured in double / now, us: 131072 rows 256 -> 256 252 / 148, 128 -> 256 135 / 86, 64 -> 256 79 / 60, 65 536 rows 512 -> 128 126 / 90.
+// A step of 32 rows by 256 columns takes 8 us, of which the matrix instructions 4.4; the rest is the
 // wavefronts' own chain (read, multiply, put together, cut, write).
 // Tried: digits of B in LDS and every wavefront for itself (64 columns each: A is cut, and read in pieces of 16 bytes, once per 64 columns)
-// 165 .. 195 us for 131072 x 256 x 256; 16 wavefronts of 16 columns 167 (A's digits are read from LDS twice as often); the outputs that are
-// summed again summed at once 236 (the block waits for them at its next barrier).
+// 165 .. 195 us for 131072 x 256 x 256 with fifteen products, where this form took 126; 16 wavefronts of 16 columns 167 (A's digits are read from LDS twice as often); the
+// outputs that are summed again summed at once 236 (the block waits for them at its next barrier).
 #include "common.hpp"
 #include "gemm_rules.hpp"
 #include "product_tile.hpp"
@@ -40,8 +49,8 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
 
-constexpr int DIGITS = 5, CHUNK = DIGIT_CHUNK, WPB = DIGIT_WAVES;
-constexpr int LIST = 512, TILE_LIST = 32;   // outputs of a block, and of a tile, that are summed again one by one
+constexpr int DIGITS = 5, SUMS = 6, CHUNK = DIGIT_CHUNK, WPB = DIGIT_WAVES;
+constexpr int LIST = 512, TILE_LIST = 16;   // outputs of a block, and of a tile of 16 x 16, that are summed again by themselves
 constexpr int E_MIN = -90, E_MAX = 100, E_ZERO = -1000, E_BAD = 1000;   // exponents that are used, and what stands for a row of zeros or one that is not
 
 // floor(x + 1/2), one instruction
@@ -100,14 +109,21 @@ struct Largest {
 __device__ inline int exponent_of(uint32_t bits) { return bits ? (int)((bits + 0x20000u) >> 23) - 126 : 0; }
 __device__ inline bool unusable(uint32_t bits) { return bits && (bits >= 0x7F800000u || exponent_of(bits) < E_MIN || exponent_of(bits) > E_MAX); }
 __device__ inline float scale_of(int e) { return __int_as_float((127 + 31 - e) << 23); }
-
-// A value the wavefront shares, as of here: what follows from it is not computed ahead, outside a loop, and kept in registers
-template <typename T>
-__device__ inline T here(T x)
+// least magnitude of three (a NaN counts for nothing)
+__device__ inline float least_of(float x, float y, float z)
 {
-    asm volatile("" : "+s"(x));
-    return x;
+    float r;
+    asm("v_min3_f32 %0, |%1|, |%2|, |%3|" : "=v"(r) : "v"(x), "v"(y), "v"(z));
+    return r;
 }
+// the least magnitude whose last bit the digits hold
+__device__ inline float least_whole(int e) { return __int_as_float((127 - 16 + e) << 23); }
+
+// Of a row of A: its exponent, and what its outputs may be off by for its numbers that the digits only round
+struct Row {
+    int e;
+    float off;
+};
 
 // The maximum over L lanes side by side, to all of them; for a whole wavefront as values that it shares
 template <int L, int R>
@@ -153,7 +169,7 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
     constexpr int GS = 272, CS = 4 * GS, PS = KC * CS, TSZ = DIGITS * PS;   // bytes: 16 rows of a lane group, chunk, plane of digits, tile of 16 rows
     __shared__ __align__(16) char digits[2][TILES * TSZ];
     __shared__ __align__(16) char last_digits[WPB * KC * NT * 1024];   // of B, which only one product takes
-    __shared__ int row_e[2][RS];
+    __shared__ Row row_of_a[2][RS];
     __shared__ uint32_t again_list[LIST];
     __shared__ int again_count;
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -169,15 +185,17 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
     const int steps_inst = (M_bound + RS - 1) / RS, total = steps_inst * n_inst;
 
     // ---- rows of A: quad i of this lane
-    const int lrow = wave * RW + (QPR == 2 ? 0 : lane / LPR), kquad = lane % LPR;
-    auto row_of = [&](int i) { return lrow + (QPR == 2 ? i >> 1 : i * (64 / LPR)); };
-    auto quad_of = [&](int i) { return kquad + (QPR == 2 ? 64 * (i & 1) : 0); };
+    auto row_at = [&](int l, int i) { return wave * RW + (QPR == 2 ? i >> 1 : l / LPR + i * (64 / LPR)); };
+    auto quad_at = [&](int l, int i) { return l % LPR + (QPR == 2 ? 64 * (i & 1) : 0); };
     auto place = [&](int step, int &inst, int &m0) {   // the instances in turn
         inst = n_inst == 1 ? 0 : step % n_inst;
         m0 = (n_inst == 1 ? step : step / n_inst) * RS;
     };
     auto load_a = [&](int step, float (&x)[4 * QUADS]) {
         int inst, m0;
+        const int l = here_v(lane);
+        auto row_of = [&](int i) { return row_at(l, i); };
+        auto quad_of = [&](int i) { return quad_at(l, i); };
         place(step < total ? step : total - 1, inst, m0);
         const char *pa = (const char *)(A + (int64_t)m0 * lda) + inst * cs.x;
 #pragma unroll
@@ -190,6 +208,9 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
     };
     // the rows' exponents and digits into buffer `buf`
     auto put_a = [&](int buf, float (&x)[4 * QUADS]) {
+        const int l = here_v(lane);
+        auto row_of = [&](int i) { return row_at(l, i); };
+        auto quad_of = [&](int i) { return quad_at(l, i); };
         if (K & 3) {   // the piece that holds the last k was read further to the left
 #pragma unroll
             for (int i = 0; i < QUADS; ++i) {
@@ -204,6 +225,7 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
         {
             constexpr int ROWS = QUADS / QPR;
             uint32_t b[ROWS];
+            float least[ROWS];
 #pragma unroll
             for (int i = 0; i < ROWS; ++i) {
                 Largest m;
@@ -215,10 +237,34 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
 #pragma unroll
             for (int i = 0; i < ROWS; ++i) {
                 const int e = exponent_of(b[i]);
-                row_e[buf][row_of(QPR * i)] = b[i] == 0 ? E_ZERO : unusable(b[i]) ? E_BAD : e;
+                least[i] = least_whole(e);
 #pragma unroll
                 for (int j = 0; j < QPR; ++j) sc[QPR * i + j] = scale_of(e);
             }
+            // numbers that the digits only round, few as they are
+            bool some = false;
+            int rounded[ROWS];
+#pragma unroll
+            for (int i = 0; i < ROWS; ++i) {
+                rounded[i] = 0;
+                float m = least_of(x[4 * QPR * i], x[4 * QPR * i + 1], least_of(x[4 * QPR * i + 2], x[4 * QPR * i + 3], INFINITY));
+                if (QPR == 2) m = least_of(x[8 * i + 4], x[8 * i + 5], least_of(x[8 * i + 6], x[8 * i + 7], m));
+                some |= m < least[i];
+            }
+            if (__any(some)) {
+#pragma unroll
+                for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4 * QPR; ++j) {
+                        const float v = x[4 * QPR * i + j];
+                        uint64_t w = __ballot(v != 0.f && fabsf(v) < least[i] && 4 * quad_of(QPR * i + j / 4) < K);
+                        if (LPR < 64) w = w >> (l & (64 - LPR)) & ((1ull << (LPR & 63)) - 1);
+                        rounded[i] += __popcll(w);
+                    }
+            }
+#pragma unroll
+            for (int i = 0; i < ROWS; ++i)
+                row_of_a[buf][row_of(QPR * i)] = Row{b[i] == 0 ? E_ZERO : unusable(b[i]) ? E_BAD : exponent_of(b[i]), 132.f * (float)rounded[i]};
         }
         int d[DIGITS][QUADS];
         cut<QUADS>(x, [&](int q) { return sc[q]; }, d);
@@ -259,8 +305,9 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
     // ---- this wavefront's columns of B: digits of k = 64 c + 16 s + 4 grp + j, columns n0 + NT l16 + t
     i32x4 w[KC][NT][DIGITS - 1];
     char *const last_w = last_digits + (wave * KC * NT) * 1024 + lane * 16;
-    int ce[NT];
-    bool col_zero[NT], any_bad;
+    bool any_bad;
+    int col_e[NT], row_lim;   // exponent of a column's unit, 2^-46 R_A R_B
+    float col_off;            // what an output may be off by in that unit, beside its row's share
     {
         // (a lane's offsets lie below 2^32, and what lies beyond the last k reads the last k)
         const uint32_t ldb4 = (uint32_t)ldb * 4;
@@ -337,45 +384,97 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
                 for (int j = 0; j < 16; ++j) y[c][0][j] = left ? y[c][NT - 1][j] : y[c][0][j];
         }
         Largest m[NT];
+        float later[NT], least[NT];   // sum of the magnitudes, each times the additions that follow on it in the double form; least magnitude
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            later[t] = 0.f;
+            least[t] = INFINITY;
+        }
 #pragma unroll
         for (int c = 0; c < KC; ++c)
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
+            for (int t = 0; t < NT; ++t) {
+                end_b(c, y[c][t]);
 #pragma unroll
-                for (int j = 0; j < 16; j += 2) m[t].take(y[c][t][j], y[c][t][j + 1]);
+                for (int h = 0; h < 16; h += 8) {   // 32 k, which that form takes together; those of a last piece come first
+                    const int k0 = c * CHUNK + 4 * h;
+                    float part = 0.f;
+#pragma unroll
+                    for (int j = h; j < h + 8; j += 2) {
+                        m[t].take(y[c][t][j], y[c][t][j + 1]);
+                        part += fabsf(y[c][t][j]) + fabsf(y[c][t][j + 1]);
+                        least[t] = least_of(y[c][t][j], y[c][t][j + 1], least[t]);
+                    }
+                    later[t] = __builtin_fmaf(part, (float)(k0 + 32 <= K ? (K & ~31) - k0 : K), later[t]);
+                }
+            }
         float sc[NT];
-        bool un = false;
+        bool un = false, some = false;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             uint32_t b = m[t].bits(), o = (uint32_t)__shfl_xor((int)b, 16);
             b = b > o ? b : o;
             o = (uint32_t)__shfl_xor((int)b, 32);
             b = b > o ? b : o;
-            ce[t] = exponent_of(b) - 46;
-            sc[t] = scale_of(exponent_of(b));
-            col_zero[t] = b == 0;
+            const int e = exponent_of(b);
+            sc[t] = scale_of(e);
+            col_e[t] = b == 0 ? E_ZERO : e - 46;
             un |= unusable(b);
+            some |= least[t] < least_whole(e);
+            least[t] = least_whole(e);
         }
+        // bad: a column that the digits do not hold; lim: rows below this may give denormal floats, which round elsewhere
         any_bad = __any(un);
+        int el = 0;
 #pragma unroll
-        for (int c = 0; c < KC; ++c)
+        for (int t = 0; t < NT; ++t) el = col_e[t] != E_ZERO && col_e[t] < el ? col_e[t] : el;
 #pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                end_b(c, y[c][t]);
+        for (int o = 1; o < 16; o *= 2) {
+            const int x = __shfl_xor(el, o);
+            el = x < el ? x : el;
+        }
+        row_lim = __builtin_amdgcn_readfirstlane(-149 - el);
+        col_off = 0.f;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            uint32_t dropped = 0;
+            int rounded = 0;   // numbers that the digits only round
+            if (__any(some)) {
+#pragma unroll
+                for (int c = 0; c < KC; ++c)
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) rounded += y[c][t][j] != 0.f && fabsf(y[c][t][j]) < least[t];
+            }
+#pragma unroll
+            for (int c = 0; c < KC; ++c) {
                 i32x4 d[DIGITS];
                 cut<4>(y[c][t], [&](int) { return sc[t]; }, d);
 #pragma unroll
-                for (int p = 0; p < DIGITS - 1; ++p) w[c][t][p] = d[p];
+                for (int p = 2; p < DIGITS; ++p)
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) dropped = __builtin_amdgcn_sad_u8((uint32_t)d[p][s] ^ 0x80808080u, 0x80808080u, dropped);
+#pragma unroll
+                for (int p = 0; p < DIGITS - 1; ++p) {
+                    asm volatile("" : "+v"(d[p]));   // (now: left for later, what they are put together from would not fit the registers)
+                    w[c][t][p] = d[p];
+                }
                 *reinterpret_cast<i32x4 *>(last_w + (c * NT + t) * 1024) = d[DIGITS - 1];
                 __builtin_amdgcn_sched_barrier(0);
             }
+            const float r = __int_as_float((127 - (col_e[t] + 46)) << 23);   // 1 / R
+            float off = (float)dropped * 0x1p-9f + later[t] * (0x1.001p-7f + 0x1p-10f) * r + 132.f * (float)rounded;
+            off += __shfl_xor(off, 16);
+            off += __shfl_xor(off, 32);
+            off = col_e[t] == E_ZERO ? 0.f : off;
+            col_off = off > col_off ? off : col_off;
+        }
+        col_off = (col_off + 1.f + (float)K * 0x1.1p-9f) * 1.0001f;
     }
     if (tid == 0) again_count = 0;
     put_a(0, x0);
     load_a(rg + rgs, x0);
     __syncthreads();
 
-    const double small = 1073741824.0 * sqrt((double)K);   // 2^-16 sqrt(K) R_A R_B in units of the last sum
     int buf = 0;
     uint32_t code = 0;   // names the step in the list
 #pragma unroll 1
@@ -385,7 +484,7 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
         const int32_t *rd = rows_of(inst);
         const int M = resolve_count(M_bound, rd);
         char *pc = (char *)(C + (int64_t)s0 * ldc + n0) + inst * cs.out;
-        if (wave >= WPB / 2) {
+        if (wave >= WPB / 2 && step + rgs < total) {
             put_a(buf ^ 1, x0);
             load_a(step + 2 * rgs, x0);
         }
@@ -394,7 +493,7 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
             for (int ti = wr; ti < TILES; ti += wrs) {
                 const int m0 = s0 + 16 * ti;
                 const char *ap = digits[buf] + ti * TSZ + grp * GS + l16 * 16;
-                const int re0 = row_e[buf][16 * ti + l16];
+                const int re0 = row_of_a[buf][16 * ti + l16].e;
                 if (m0 >= M) break;
                 // what is listed here is done again in double when all steps are through
                 auto list = [&](int n) {
@@ -406,16 +505,16 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
                     const int at = list(1);
                     if (lane == 0 && at < LIST) again_list[at] = 0x80000000u | code | (uint32_t)((16 * ti) << 8 | wc * 16 * NT);
                 };
-                if (any_bad || __any(re0 == E_BAD && m0 + l16 < M)) {
+                if (any_bad || __any((re0 == E_BAD || (re0 < row_lim && re0 != E_ZERO)) && m0 + l16 < M)) {
                     list_tile();
                 } else {
-                    i32x4 acc[NT][DIGITS], a[3], wl[NT];
+                    i32x4 acc[NT][SUMS], a[3], wl[NT];
 #pragma unroll
                     for (int t = 0; t < NT; ++t)
 #pragma unroll
-                        for (int s = 0; s < DIGITS; ++s) acc[t][s] = i32x4{0, 0, 0, 0};
+                        for (int s = 0; s < SUMS; ++s) acc[t][s] = i32x4{0, 0, 0, 0};
                     // A's planes in an order in which two of them take longer than a read from LDS
-                    constexpr int order[DIGITS] = {1, 4, 0, 3, 2};
+                    constexpr int order[DIGITS] = {3, 1, 4, 0, 2};
                     auto read_a = [&](int i) { return *reinterpret_cast<const i32x4 *>(ap + (i / DIGITS) * CS + order[i % DIGITS] * PS); };
                     a[0] = read_a(0);
                     a[1] = read_a(1);
@@ -427,7 +526,7 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
                             for (int t = 0; t < NT; ++t) wl[t] = *reinterpret_cast<const i32x4 *>(last_w + (c * NT + t) * 1024);
                         if (i + 2 < KC * DIGITS) a[(i + 2) % 3] = read_a(i + 2);
 #pragma unroll
-                        for (int p = 0; s + p < DIGITS; ++p)
+                        for (int p = 0; p < DIGITS && s + p < SUMS; ++p)
 #pragma unroll
                             for (int t = 0; t < NT; ++t)
                                 acc[t][s + p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i % 3], p < DIGITS - 1 ? w[c][t][p < DIGITS - 1 ? p : 0] : wl[t], acc[t][s + p], 0, 0, 0);
@@ -436,38 +535,51 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
                     uint32_t at = ((uint32_t)(16 * ti + 4 * grp) * (uint32_t)ldc + (uint32_t)(NT * l16)) * 4;
                     const int left = N - n0 - NT * l16;
                     uint64_t low[4][NT], any = 0;
+                    float v[4][NT];   // (all of them before the first is stored: each is a chain of ten instructions)
+                    Row r[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) r[i] = row_of_a[buf][16 * ti + 4 * grp + i];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const int re = row_e[buf][16 * ti + 4 * grp + i];
-                        float v[NT];
+                        const double off = (double)(r[i].off + col_off);
 #pragma unroll
                         for (int t = 0; t < NT; ++t) {
-                            double d = (double)acc[t][0][i];
-#pragma unroll
-                            for (int s = 1; s < DIGITS; ++s) d = __builtin_fma(d, 256.0, (double)acc[t][s][i]);
-                            v[t] = (float)__builtin_amdgcn_ldexp(d, re + ce[t]);
-                            low[i][t] = __ballot(fabs(d) < small);
+                            // (within 32 bits for K up to 512: the first digit's magnitude is at most 127; of the last sum only what a unit holds)
+                            double d = (double)(int)(((uint32_t)acc[t][0][i] << 8) + (uint32_t)acc[t][1][i]);
+                            d = __builtin_fma(d, 256.0, (double)acc[t][2][i]);
+                            d = __builtin_fma(d, 256.0, (double)acc[t][3][i]);
+                            d = __builtin_fma(d, 256.0, (double)(acc[t][4][i] + (acc[t][5][i] >> 8)));
+                            const float most = (float)(d + off);
+                            low[i][t] = __ballot(__float_as_int(most) != __float_as_int((float)(d - off)));
+                            v[i][t] = __builtin_ldexpf(most, r[i].e + col_e[t]);
                             any |= low[i][t];
                         }
-                        if (m0 + 4 * grp + i < M) {
-                            float *p = reinterpret_cast<float *>(pc + (int64_t)i * ldc * 4 + at);
-                            if (left >= NT) store_floats<NT>(p, v);
-                            else if (NT == 2 && left == 1) *p = v[0];
-                        }
+                    }
+                    float *p = reinterpret_cast<float *>(pc + at);
+                    if (m0 + 16 <= M && n0 + 16 * NT <= N) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i, p += ldc) store_floats<NT>(p, v[i]);
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i, p += ldc)
+                            if (m0 + 4 * grp + i < M) {
+                                if (left >= NT) store_floats<NT>(p, v[i]);
+                                else if (NT == 2 && left == 1) *p = v[i][0];
+                            }
                     }
                     if (any) {
                         int count = 0;
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
                             const int ro = 16 * ti + 4 * grp + i;
-                            const bool row_ok = s0 + ro < M && row_e[buf][ro] != E_ZERO;
+                            const bool row_ok = s0 + ro < M && r[i].e != E_ZERO;
 #pragma unroll
                             for (int t = 0; t < NT; ++t) {
-                                low[i][t] &= __ballot(row_ok && t < left && !col_zero[t]);
+                                low[i][t] &= __ballot(row_ok && t < left && col_e[t] != E_ZERO);
                                 count += __popcll(low[i][t]);
                             }
                         }
-                        if (count > TILE_LIST) {
+                        if (count > TILE_LIST * NT) {
                             list_tile();
                         } else if (count > 0) {
                             int at0 = list(count);
@@ -485,7 +597,7 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
                 }
             }
         }
-        if (wave < WPB / 2) {
+        if (wave < WPB / 2 && step + rgs < total) {
             put_a(buf ^ 1, x0);
             load_a(step + 2 * rgs, x0);
         }
@@ -510,38 +622,23 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
         }
         return;
     }
-    // tiles, and outputs that came out small against their row's and column's maxima: four at a time
+    // tiles, and outputs by themselves, up to sixteen at a time
+    const int each = count < 16 * WPB ? (count + WPB - 1) / WPB : 16;
 #pragma unroll 1
-    for (int s = 4 * wave; s < count; s += 4 * WPB) {
-        const uint32_t what = again_list[s + grp < count ? s + grp : count - 1];
-        const bool is = s + grp < count && !(what >> 31);
+    for (int s = each * wave; s < count; s += each * WPB) {
+        const int some = count - s < each ? count - s : each;
+        const uint32_t what = again_list[s + (l16 < some ? l16 : some - 1)];
         const int st = (int)(what >> 15 & 0xFFFF) * rgs + rg, in = st % n_inst;
         const int64_t m = st / n_inst * RS + (int)((what >> 8) & 127);
         const int n = cg * wcs * 16 * NT + (int)(what & 255);
-        const float *pa = (const float *)((const char *)A + in * cs.x) + m * lda;
-        const float *pb = MODE == MODE_DZ ? Bm + (int64_t)n * ldb : Bm + n;
-        const int64_t bs = MODE == MODE_DZ ? 1 : ldb;
-        double sum = 0.0;
-        for (int k0 = l16; k0 < K; k0 += 256) {
-            float va[16], vb[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int k = k0 + 16 * u < K ? k0 + 16 * u : K - 1;
-                va[u] = pa[k];
-                vb[u] = pb[k * bs];
-            }
-#pragma unroll
-            for (int u = 0; u < 16; ++u) sum = __builtin_fma((double)va[u], k0 + 16 * u < K ? (double)vb[u] : 0.0, sum);
-        }
-#pragma unroll
-        for (int o = 8; o; o >>= 1) sum += __shfl_xor(sum, o);
-        if (l16 == 0 && is) ((float *)((char *)C + in * cs.out))[m * ldc + n] = (float)sum;
-        const int tiles = __popcll(__ballot(l16 == 0 && s + grp < count && what >> 31));
+        const float sum = product_at<MODE, 4>((const float *)((const char *)A + in * cs.x) + m * lda, Bm, MODE == MODE_DZ ? (uint32_t)n * (uint32_t)(ldb * 4) : (uint32_t)n * 4, ldb, K);
+        if (grp == (l16 & 3) && l16 < some && !(what >> 31)) ((float *)((char *)C + in * cs.out))[m * ldc + n] = sum;
+        uint64_t tiles = __ballot(lane < some && what >> 31);
 #pragma unroll 1
-        for (int g = 0; tiles && g < 4 * NT; ++g) {
-            const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)what, 16 * (g / NT));
-            const int nt = cg * wcs * 16 * NT + (int)(w & 255) + 16 * (g % NT);
-            if (s + g / NT >= count || !(w >> 31) || nt >= N) continue;
+        for (int g = 0; tiles; tiles &= g == NT - 1 ? tiles - 1 : ~0ull, g = g == NT - 1 ? 0 : g + 1) {
+            const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)what, __ffsll((unsigned long long)tiles) - 1);
+            const int nt = cg * wcs * 16 * NT + (int)(w & 255) + 16 * g;
+            if (nt >= N) continue;
             const int sg = (int)(w >> 15 & 0xFFFF) * rgs + rg, ig = sg % n_inst;
             const int32_t *rd = rows_of(ig);
             product_tile<MODE, 1, 1, TAIL_32, uint32_t>((const float *)((const char *)A + ig * cs.x), here(lda), here(Bm), here(ldb),

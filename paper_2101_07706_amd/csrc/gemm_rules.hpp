@@ -65,10 +65,10 @@ inline double double_us(int64_t M, int64_t N, int64_t K, int64_t n_inst, bool b_
     return 3.0 + (double)per_cu * s.rt * s.nt * ((double)((K + 3) / 4) * 0.029 * s.cost + 0.13);
 }
 
-// The digits' form where it is the quicker by 5 %.  Its time is 13 us (16 with the most digits of B to cut first) and for each step of
+// The digits' form where it is the quicker by 5 %.  Its time is what `begin` says (digits of B to cut, outputs to sum again) and for each step of
 // the block with the most of them what `step` says.  Measured against that, us, double / digits (expected): 131072 rows, 256 x 256
-// 252 / 126 (127), 256 x 128 128 / 79 (80), 256 x 64 66 / 65 (64), 100 x 256 112 / 79 (82), 512 x 128 250 / 134 (134), 64 x 256 79 / 59 (62); 16384 rows
-// 256 x 256 35 / 29 (30), 8192 rows 19.5 / 21.8 (23), 4096 rows 512 x 512 34 / 28 (29).
+// 252 / 148 (149), 256 x 128 128 / 97 (95), 128 x 256 135 / 86 (91), 64 x 256 79 / 60 (62); 65536 rows 512 x 128 126 / 90 (90), 192 x 256 99 / 69 (70);
+// 16384 rows 256 x 256 36 / 36 (37), 128 x 256 21 / 22 (23).  Columns for one or two wavefronts: never (131072 rows, 256 x 64 66 / 78, 524288 rows, 64 x 64 79 / 85).
 inline DigitsPlan digits_plan(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc, int64_t n_inst, bool b_kmajor)
 {
     DigitsPlan d{false, 0, 0, 0, 0, 0};
@@ -85,9 +85,11 @@ inline DigitsPlan digits_plan(int64_t M, int64_t N, int64_t K, int64_t lda, int6
     d.rgs = (int)rgs;
     const int64_t turns = (steps + rgs - 1) / rgs;
     if (turns >= 65536) return d;   // (the list of a block's outputs counts its steps in 16 bits)
-    // us of a step with columns for up to two, four and eight wavefronts
-    static constexpr double step[9][3] = {{}, {4.0, 6.6, 11.7}, {3.3, 5.0, 8.4}, {2.9, 3.7, 6.1}, {3.1, 4.2, 7.0}, {2.4, 2.4, 3.0}, {}, {}, {3.0, 3.0, 3.8}};
-    const double one = step[d.kc][d.wcs <= 2 ? 0 : d.wcs <= 4 ? 1 : 2], start = d.kc == 4 && d.wcs > 4 ? 16.0 : 13.0;
+    if (d.wcs <= 2) return d;
+    // us before the first step, and of a step, with columns for up to four and for eight wavefronts
+    static constexpr double begin[9][2] = {{}, {11, 9.5}, {14.5, 13}, {15.5, 16}, {19.5, 21}, {12.5, 13.5}, {}, {}, {18.5, 22.5}};
+    static constexpr double step[9][2] = {{}, {7.5, 13.2}, {5.4, 9.8}, {4.3, 6.7}, {4.7, 8.0}, {2.9, 3.6}, {}, {}, {3.5, 4.2}};
+    const double one = step[d.kc][d.wcs > 4], start = begin[d.kc][d.wcs > 4];
     d.use = start + one * (double)turns < 0.95 * double_us(M, N, K, n_inst, b_kmajor);
     // the rows on the device that are done in double before the digits are cut: three quarters of what takes as long (smaller tiles there)
     const double rate = (double_us(M, N, K, n_inst, b_kmajor) - 3.0) / (double)(M * n_inst), mine = one / (double)(rs * rgs);

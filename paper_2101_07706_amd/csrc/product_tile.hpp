@@ -16,6 +16,21 @@ enum { MODE_FWD = 0, MODE_DZ = 1, MODE_DW = 2 };
 // MFMA steps (of four k) that a kernel has for the K % 32 k behind the whole chunks
 enum { TAIL_NONE = 0, TAIL_8 = 2, TAIL_32 = 8 };
 
+// A value the wavefront shares, as of here: what follows from it is not computed ahead, outside a loop, and kept in registers
+template <typename T>
+__device__ inline T here(T x)
+{
+    asm volatile("" : "+s"(x));
+    return x;
+}
+
+template <typename T>
+__device__ inline T here_v(T x)   // the same for a lane's own
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 // N consecutive floats at a byte offset from an address the whole wavefront shares.  Four bytes of alignment are
 // enough for any width of global load on this part.
 template <int N, typename OFF>
@@ -284,6 +299,58 @@ __device__ inline __attribute__((always_inline)) void product_tile(
             }
         }
     }
+}
+
+// Sixteen outputs that lie anywhere, summed in the order of product_tile: lane l gives the row (pa) and the column's offset in B (ob, bytes) of output l % 16, and its
+// sum is the result in lane 16 (l % 4) + l (l < 16): of four small tiles (v_mfma_f64_4x4x4, which adds like the large one) the diagonals.
+// CHUNKS of 32 k are on their way at once.
+template <int MODE, int CHUNKS>
+__device__ inline float product_at(const float *pa, const float *Bm, uint32_t ob, int64_t ldb, int K)
+{
+    const int lane = (int)(threadIdx.x & 63), grp = lane >> 4, l16 = lane & 15;
+    const int64_t bs = MODE == MODE_DZ ? 4 : ldb * 4;   // bytes from one k to the next
+    const uint32_t og = ob + (uint32_t)(8 * grp) * (uint32_t)bs;
+    double acc = 0.0;
+    auto step = [&](float a, float b) { acc = __builtin_amdgcn_mfma_f64_4x4x4f64((double)a, (double)b, acc, 0, 0, 0); };
+    const int kt = K & ~31;
+    struct Set {
+        float a[8], b[8];
+    };
+    auto load = [&](Set &x, int c) {   // (beyond the last chunk that one again)
+        c = c < kt ? c : kt - 32;
+        const char *ca = (const char *)(pa + 8 * grp) + (int64_t)c * 4, *cb = (const char *)here(Bm) + c * here(bs);
+        load_floats<4>(ca, 0, x.a);
+        load_floats<4>(ca, 16, x.a + 4);
+        if constexpr (MODE == MODE_DZ) {
+            load_floats<4>(cb, og, x.b);
+            load_floats<4>(cb + 16, og, x.b + 4);
+        } else {
+#pragma unroll
+            for (int s = 0; s < 8; ++s, cb += bs) load_floats<1>(cb, og, &x.b[s]);
+        }
+    };
+    Set x[CHUNKS];
+    if (kt) {
+#pragma unroll
+        for (int u = 0; u < CHUNKS; ++u) load(x[u], 32 * u);
+    }
+    for (int k0 = kt; k0 < K; k0 += 4) {
+        const int k = k0 + grp < K ? k0 + grp : K - 1;
+        float a = pa[k], b;
+        load_floats<1>((const char *)Bm, ob + (uint32_t)k * (uint32_t)bs, &b);
+        step(k0 + grp < K ? a : 0.f, k0 + grp < K ? b : 0.f);
+    }
+#pragma unroll 1
+    for (int c = 0; c < kt; c += 32 * CHUNKS) {
+#pragma unroll
+        for (int u = 0; u < CHUNKS; ++u) {
+            if (c + 32 * u >= kt) break;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) step(x[u].a[s], x[u].b[s]);
+            load(x[u], c + 32 * (CHUNKS + u));
+        }
+    }
+    return (float)acc;
 }
 
 }  // namespace csgs

@@ -7,11 +7,11 @@ torch = pytest.importorskip("torch")
 
 pytestmark = pytest.mark.gpu
 
-# reduction, columns and rows (the smallest counts that the rule takes are somewhat lower): every kernel there is, columns for one to eight wavefronts
+# reduction, columns and rows (the smallest counts that the rule takes are somewhat lower): every kernel there is, columns for four to eight wavefronts
 # and more than one block, last chunks of 1 to 64 k, rows that are no whole step
 SHAPES = [(64, 256, 131_069), (62, 507, 131_072), (128, 128, 100_003), (100, 256, 65_533), (101, 505, 65_533), (192, 250, 30_577), (131, 512, 40_011),
-          (256, 256, 20_399), (255, 101, 60_005), (256, 60, 250_001), (300, 127, 60_001), (257, 256, 30_001), (320, 513, 14_200), (512, 512, 4_095),
-          (385, 126, 54_001), (450, 70, 90_000)]
+          (256, 256, 28_399), (255, 101, 60_005), (256, 120, 90_001), (300, 127, 60_001), (257, 256, 60_001), (320, 510, 30_200), (512, 512, 8_191),
+          (385, 126, 54_001), (450, 118, 90_000)]
 
 
 @pytest.fixture(scope="module")
@@ -167,3 +167,65 @@ def test_digit_products_infinite(dev, what):
     cols = torch.ones(N, dtype=torch.bool, device=dev)
     cols[40] = False
     check(got[rows][:, cols], A[rows], B[:, cols].contiguous())
+
+
+def in_double(what, A, W, N):
+    """The same rows in calls of few, which are summed in double whatever they hold."""
+    out = torch.empty((A.shape[0], N), device=A.device)
+    for i in range(0, A.shape[0], 512):
+        product(what, A[i:i + 512], W, out[i:i + 512])
+    return out
+
+
+def same_bits(got, want):
+    return bool(((got.contiguous().view(torch.int32) == want.view(torch.int32)) | (torch.isnan(got) & torch.isnan(want))).all())
+
+
+# What a row gives depends on neither the other rows nor their number nor the form that these choose: both give the same bits
+@pytest.mark.parametrize("what", ["H", "dZ"])
+@pytest.mark.parametrize("K,N,M", SHAPES)
+def test_digit_products_equal_double(dev, what, K, N, M):
+    print(f"[digits] {what} {M} x {K} x {N} in both forms", flush=True)
+    A, W, out = operands(dev, what, K, N, M, M + K, pad=M % 3)
+    product(what, A, W, out[:M, :N])
+    assert same_bits(out[:M, :N], in_double(what, A, W, N))
+
+
+def hard(kind, A, B):
+    """Operands that leave the digits little: A [M x K], B [K x N] are changed."""
+    M, K = A.shape
+    if kind == "repeated":            # equal values along k, whose roundings all point one way, and that all but cancel
+        A.copy_(A[:, :1].expand(M, K).contiguous())
+        B[::2] = B[:1].clone()
+        B[1::2] = -B[:1] * (1 + 2.0 ** -18)
+    elif kind == "one among many":    # the same in 2^-8 of the largest
+        A.copy_(A[:, :1].expand(M, K).contiguous() * 2.0 ** -8)
+        A[:, 3] *= 250
+        B[::2] = B[:1].clone()
+        B[1::2] = -B[:1] * (1 + 2.0 ** -10)
+        B[3] = 0
+    elif kind == "scales":            # features of very different size
+        A *= torch.randn(K, generator=torch.Generator(device=A.device).manual_seed(1), device=A.device).mul_(4).exp_()
+    elif kind == "weights of other scales":
+        B *= torch.randn((K, 1), generator=torch.Generator(device=A.device).manual_seed(2), device=A.device).mul_(4).exp_()
+    elif kind == "half way":          # sums that lie half way between two floats, or next to it
+        A.copy_(torch.randint(-4096, 4096, A.shape, generator=torch.Generator(device=A.device).manual_seed(3), device=A.device).float())
+        B.copy_(torch.randint(-4096, 4096, B.shape, generator=torch.Generator(device=A.device).manual_seed(4), device=A.device).float())
+    elif kind == "sparse":
+        A *= (torch.rand(A.shape, generator=torch.Generator(device=A.device).manual_seed(5), device=A.device) < 0.02)
+        B *= (torch.rand(B.shape, generator=torch.Generator(device=A.device).manual_seed(6), device=A.device) < 0.1)
+    elif kind == "least floats":      # results among the denormal numbers
+        A *= 2.0 ** -75
+        B *= 2.0 ** -70
+
+
+@pytest.mark.parametrize("what", ["H", "dZ"])
+@pytest.mark.parametrize("kind", ["repeated", "one among many", "scales", "weights of other scales", "half way", "sparse", "least floats"])
+@pytest.mark.parametrize("K,N,M", [(64, 256, 131_069), (256, 256, 32_033), (512, 512, 8_191)])
+def test_digit_products_equal_double_hard(dev, what, kind, K, N, M):
+    print(f"[digits] {what} {M} x {K} x {N} {kind} in both forms", flush=True)
+    A, W, out = operands(dev, what, K, N, M, K)
+    hard(kind, A, W if what == "H" else W.t())
+    product(what, A, W, out[:M, :N])
+    assert same_bits(out[:M, :N], in_double(what, A, W, N))
+    assert bool(torch.isnan(out[M:]).all()) and bool(torch.isnan(out[:, N:]).all()), "wrote outside"
