@@ -48,6 +48,14 @@ constexpr int digit_rows(int kc) { return kc == 1 ? 128 : kc == 2 ? 64 : kc <= 4
 // Tiles of 16 rows that hold one of the `left` rows from a step's first one to the last there is
 constexpr int row_tiles(int64_t left, int rows_of_step) { return left <= 0 ? 0 : (int)(((left < rows_of_step ? left : rows_of_step) + 15) / 16); }
 
+// What a block sums again in double.  A wavefront lists the outputs of a tile by themselves up to so many per 16 columns; of more, the tile: an output on its own reads
+// a line of B for every k, and that many take as long as the tile.
+constexpr int digit_tile_list(int kc) { return kc > 4 ? 8 : 4; }
+// Most that a step lists, a tile taken as the outputs that would have stood in its place; and the room: the list is worked off when a step might find too little.  That
+// costs the digits of B once more, 10 to 20 us, so there is room for 1024 (131072 x 256 x 256, one output in 750: once in 90 steps).
+constexpr int digit_step_list(int kc) { return digit_rows(kc) / 16 * DIGIT_WAVES * digit_tile_list(kc) * (kc > 4 ? 1 : 2); }
+constexpr int digit_list(int kc) { return kc == 1 ? 2048 : 1024; }
+
 struct DigitsPlan {
     bool use;
     int kc;              // chunks of k that the kernel is made for

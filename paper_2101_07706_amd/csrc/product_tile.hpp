@@ -71,10 +71,11 @@ __device__ inline void store_floats(float *p, const float *v)
 template <int MODE, int RT, int NT, int TAIL, typename OFF>
 __device__ inline __attribute__((always_inline)) void product_tile(
     const float *__restrict__ A, int64_t lda, const float *__restrict__ Bm, int64_t ldb, float *__restrict__ C, int64_t ldc,
-    double *__restrict__ partial, int M_bound, int N, int K_bound, const int32_t *__restrict__ rows_dev, int m0, int n0)
+    double *__restrict__ partial, int M_bound, int N, int K_bound, const int32_t *__restrict__ rows_dev, int m0, int n0,
+    const int lane = (int)(threadIdx.x & 63))
 {
     constexpr bool DW = MODE == MODE_DW, B_KMAJOR = MODE == MODE_DZ;
-    const int lane = (int)(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int grp = lane >> 4, l16 = lane & 15;
     const int m_dev = (!DW && rows_dev) ? *rows_dev : M_bound;
     const int K = DW ? __builtin_amdgcn_readfirstlane(resolve_count(K_bound, rows_dev)) : K_bound;
@@ -305,9 +306,9 @@ __device__ inline __attribute__((always_inline)) void product_tile(
 // sum is the result in lane 16 (l % 4) + l (l < 16): of four small tiles (v_mfma_f64_4x4x4, which adds like the large one) the diagonals.
 // CHUNKS of 32 k are on their way at once.
 template <int MODE, int CHUNKS>
-__device__ inline float product_at(const float *pa, const float *Bm, uint32_t ob, int64_t ldb, int K)
+__device__ inline float product_at(const float *pa, const float *Bm, uint32_t ob, int64_t ldb, int K, int lane)
 {
-    const int lane = (int)(threadIdx.x & 63), grp = lane >> 4, l16 = lane & 15;
+    const int grp = lane >> 4, l16 = lane & 15;
     const int64_t bs = MODE == MODE_DZ ? 4 : ldb * 4;   // bytes from one k to the next
     const uint32_t og = ob + (uint32_t)(8 * grp) * (uint32_t)bs;
     double acc = 0.0;

@@ -229,3 +229,20 @@ def test_digit_products_equal_double_hard(dev, what, kind, K, N, M):
     product(what, A, W, out[:M, :N])
     assert same_bits(out[:M, :N], in_double(what, A, W, N))
     assert bool(torch.isnan(out[M:]).all()) and bool(torch.isnan(out[:, N:]).all()), "wrote outside"
+
+
+# More to sum again than the list holds: worked off several times, then so much that the rest is done in double (from the first row on, from the middle on, in no step)
+@pytest.mark.parametrize("what", ["H", "dZ"])
+@pytest.mark.parametrize("dense_from", [0, 300_007, None])
+@pytest.mark.parametrize("K,N,M", [(100, 256, 600_005), (260, 130, 400_009)])
+def test_digit_products_list_worked_off(dev, what, dense_from, K, N, M):
+    print(f"[digits] {what} {M} x {K} x {N} many listed, all from {dense_from}", flush=True)
+    A, W, out = operands(dev, what, K, N, M, 11)
+    B = W if what == "H" else W.t()
+    A *= torch.randn(K, generator=torch.Generator(device=dev).manual_seed(7), device=dev).mul_(1.5).exp_()
+    if dense_from is not None:
+        A[dense_from:, 5] *= 3000
+        B[5] = 0
+    product(what, A, W, out[:M, :N])
+    assert same_bits(out[:M, :N], in_double(what, A, W, N))
+    assert bool(torch.isnan(out[M:]).all()) and bool(torch.isnan(out[:, N:]).all()), "wrote outside"

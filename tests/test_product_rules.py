@@ -114,3 +114,28 @@ def test_step_has_no_tile_past_the_last_row(tmp_path):
     out = subprocess.run([str(tmp_path / "ask")], stdout=subprocess.PIPE, text=True, check=True).stdout
     for rs, M, s0, tiles in np.array(out.split(), dtype=np.int64).reshape(-1, 4):
         assert tiles == len([m0 for m0 in range(s0, s0 + rs, 16) if m0 < M])
+
+
+ASK_LIST = """
+#include <cstdio>
+#include "gemm_rules.hpp"
+int main()
+{
+    for (int kc : {1, 2, 3, 4, 5, 8})
+        printf("%d %d %d %d %d\\n", kc, csgs::digit_rows(kc), csgs::digit_tile_list(kc), csgs::digit_step_list(kc), csgs::digit_list(kc));
+}
+"""
+
+
+def test_list_has_room_for_a_step(tmp_path):
+    """What a block sums again: whatever the operands, a step finds room for all that it lists, however many steps a call has, in the LDS there is."""
+    (tmp_path / "ask.cpp").write_text(ASK_LIST)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", build.CSRC, "-o", str(tmp_path / "ask"), str(tmp_path / "ask.cpp")], check=True)
+    out = subprocess.run([str(tmp_path / "ask")], stdout=subprocess.PIPE, text=True, check=True).stdout
+    for kc, rows, tile, step, room in np.array(out.split(), dtype=np.int64).reshape(-1, 5):
+        nt = 1 if kc > 4 else 2
+        assert step == rows // 16 * 8 * nt * tile     # every wavefront, each of its tiles
+        # it is worked off after a step that left less than the next may take, and in one with more than half of that in every step so far
+        assert 2 * step <= room < 2 ** 15 and tile <= 16
+        lds = 2 * rows // 16 * 5 * kc * 1088 + 8 * kc * nt * 1024 + 2 * rows * 8 + 4 * room + 16
+        assert lds <= 160 * 1024
