@@ -179,6 +179,7 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
     __shared__ uint32_t again_list[LIST];
     __shared__ uint32_t again;     // entries, and in the upper half the outputs that they stand for
     __shared__ int again_full[2];   // by the step's buffer
+    __shared__ int step_end[64];    // of each instance, behind its last step
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, grp = lane >> 4;
     // blocks over the same rows lie on one XCD and share what they read
@@ -189,14 +190,19 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
     const int n0 = (cg * wcs + wc) * 16 * NT;
     const bool multiplies = wr < wrs && n0 < N;
     const int kq = K - 4;
-    const int steps_inst = (M_bound + RS - 1) / RS, total = steps_inst * n_inst;
+    int total;   // steps there are
+    auto rows_of = [&](int inst) { return rows_dev ? (const int32_t *)((const char *)rows_dev + inst * cs.adj) : nullptr; };
 
     // ---- rows of A: quad i of this lane
     auto row_at = [&](int l, int i) { return wave * RW + (QPR == 2 ? i >> 1 : l / LPR + i * (64 / LPR)); };
     auto quad_at = [&](int l, int i) { return l % LPR + (QPR == 2 ? 64 * (i & 1) : 0); };
-    auto place = [&](int step, int &inst, int &m0) {   // the instances in turn
-        inst = n_inst == 1 ? 0 : step % n_inst;
-        m0 = (n_inst == 1 ? step : step / n_inst) * RS;
+    auto place = [&](int step, int &inst, int &m0) {   // one instance after the other
+        inst = 0;
+        m0 = step * RS;
+        if (n_inst == 1) return;
+        const int end = step_end[here_v(lane)];
+        inst = __popcll(__ballot(end <= step));
+        m0 = (step - (inst ? __builtin_amdgcn_readlane(end, inst - 1) : 0)) * RS;
     };
     auto load_a = [&](int step, float (&x)[4 * QUADS]) {
         int inst, m0;
@@ -285,14 +291,10 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
             }
         }
     };
-    float x0[4 * QUADS];
-    int step = rg;
-    load_a(step, x0);
-
     // ---- few rows on the device of the many there is room for: in double, the tiles dealt to all wavefronts
-    auto rows_of = [&](int inst) { return rows_dev ? (const int32_t *)((const char *)rows_dev + inst * cs.adj) : nullptr; };
+    const int my_rows = lane < n_inst ? resolve_count(M_bound, rows_of(lane)) : 0;   // of instance `lane`
     if (rows_dev) {
-        int64_t rows = lane < n_inst ? resolve_count(M_bound, rows_of(lane)) : 0;
+        int64_t rows = my_rows;
 #pragma unroll
         for (int o = 32; o; o >>= 1) rows += __shfl_xor(rows, o);
         if ((int64_t)__builtin_amdgcn_readfirstlane((int)(rows > few)) == 0) {
@@ -309,6 +311,17 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
             return;
         }
     }
+    // The steps that hold a row; no other is read.  (us, every step there is room for / these: 131072 x 256 x 256 with 16 384 rows 69 / 40, 65 536 rows 108 / 88, 131072 x 100 x 256
+    // with 32 768 rows 47 / 37; eight instances of up to 16 384 rows, 2000 in each 66 / 38 (in double 46), 0 .. 16 384 x 100 x 256 88 / 53 (70).)
+    {
+        const int incl = wave_inclusive_scan<int32_t>((my_rows + RS - 1) / RS);
+        total = __builtin_amdgcn_readlane(incl, 63);
+        step_end[lane] = incl;   // (every wavefront writes the same and reads what it wrote)
+    }
+    if (rg >= total) return;
+    float x0[4 * QUADS];
+    int step = rg;
+    load_a(step, x0);
 
     uint32_t code = 0;   // names the step in the list
 #pragma unroll 1
@@ -484,7 +497,7 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
             }
             col_off = (col_off + 1.f + (float)ks * 0x1.1p-9f) * 1.0001f;
         }
-        if (tid == 0) {
+        if (wave == 0 && lane == 0) {
             const int none = here_v(0);   // (a constant would be kept, and spilled, outside the loop)
             again = (uint32_t)none;
             again_full[0] = again_full[1] = none;
@@ -639,8 +652,15 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
         for (int s = wave; s < count; s += 16 * WPB) {
             const int there = (count - s + WPB - 1) / WPB, some = there < 16 ? there : 16;
             const uint32_t what = again_list[s + WPB * (l16 < some ? l16 : some - 1)];
-            const int st = (int)(what >> 15 & 0xFFFF) * rgs + rg, in = st % n_inst;
-            const int64_t m = st / n_inst * RS + (int)((what >> 8) & 127);
+            const int st = (int)(what >> 15 & 0xFFFF) * rgs + rg;
+            int in = 0, before = 0;   // instance, and the steps before its first
+            if (n_inst > 1)
+#pragma unroll 1
+                for (int e = step_end[0]; e <= st; e = step_end[in]) {
+                    before = e;
+                    ++in;
+                }
+            const int64_t m = (st - before) * RS + (int)((what >> 8) & 127);
             const int n = cg * wcs * 16 * NT + (int)(what & 255);
             if (__any(!(what >> 31))) {
                 const float sum = product_at<MODE, 4>((const float *)((const char *)A + in * cs.x) + m * lda, Bm, MODE == MODE_DZ ? (uint32_t)n * (uint32_t)(ldb * 4) : (uint32_t)n * 4, ldb, K, l);
@@ -652,11 +672,12 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
                 const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)what, __ffsll((unsigned long long)tiles) - 1);
                 const int nt = cg * wcs * 16 * NT + (int)(w & 255) + 16 * g;
                 if (nt >= N) continue;
-                const int sg = (int)(w >> 15 & 0xFFFF) * rgs + rg, ig = sg % n_inst;
+                int ig, mg;
+                place((int)(w >> 15 & 0xFFFF) * rgs + rg, ig, mg);
                 const int32_t *rd = rows_of(ig);
                 product_tile<MODE, 1, 1, TAIL_32, uint32_t>((const float *)((const char *)A + ig * cs.x), here(lda), here(Bm), here(ldb),
                                                             (float *)((char *)C + ig * cs.out), here(ldc), nullptr, here(M_bound), here(N),
-                                                            here(K), rd, sg / n_inst * RS + (int)((w >> 8) & 127), nt, l);
+                                                            here(K), rd, mg + (int)((w >> 8) & 127), nt, l);
             }
         }
         if (step >= total) return;
@@ -679,7 +700,7 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
         auto tile = [&](auto tail) {
             product_tile<MODE, RT, 4, decltype(tail)::value, uint32_t>((const float *)((const char *)A + inst * cs.x), here(lda), here(Bm), here(ldb),
                                                                        (float *)((char *)C + inst * cs.out), here(ldc), nullptr, here(M_bound),
-                                                                       here(n_end), here(K), rd, m0, n_first + t % tn * 64);
+                                                                       here(n_end), here(K), rd, m0, n_first + t % tn * 64, lane);
         };
         if (K % 32 == 0) tile(std::integral_constant<int, TAIL_NONE>());
         else if (K % 32 <= 8) tile(std::integral_constant<int, TAIL_8>());

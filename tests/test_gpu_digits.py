@@ -246,3 +246,31 @@ def test_digit_products_list_worked_off(dev, what, dense_from, K, N, M):
     product(what, A, W, out[:M, :N])
     assert same_bits(out[:M, :N], in_double(what, A, W, N))
     assert bool(torch.isnan(out[M:]).all()) and bool(torch.isnan(out[:, N:]).all()), "wrote outside"
+
+
+# Steps are counted over the rows that there are: instances of any number of rows one after the other, their outputs listed, rows beyond the counts of any value
+@pytest.mark.parametrize("counts", [[16_000, 0, 33, 9_000, 16_000, 1, 0, 12_345], [0, 0, 0, 16_000], [16_000, 15_999, 0], [2_100] * 64])
+@pytest.mark.parametrize("hard_values", [False, True])
+@pytest.mark.parametrize("K", [100, 256])
+def test_digit_products_steps_of_instances(dev, counts, hard_values, K):
+    from paper_2101_07706_amd import csgs
+    N, M, n_inst = 256, max(counts) if len(counts) == 64 else 16_000, len(counts)
+    print(f"[digits] {n_inst} instances of {M} x {K} x {N}, hard {hard_values}", flush=True)
+    A, W, _ = operands(dev, "H", K, N, M * n_inst, 13)
+    A *= torch.randn(K, generator=torch.Generator(device=dev).manual_seed(8), device=dev).mul_(1.5).exp_()
+    if hard_values:
+        A[M // 2:, 5] *= 300
+        W[5] = 0
+    A = A.reshape(n_inst, M, K)
+    M_dev = torch.zeros((n_inst, 64), dtype=torch.int32, device=dev)
+    M_dev[:, 0] = torch.tensor(counts, dtype=torch.int32)
+    for k, n in enumerate(counts):
+        A[k, n:] = float("nan")
+    out = torch.full((n_inst, M, N), float("nan"), device=dev)
+    nb = lambda t: t.stride(0) * t.element_size()
+    csgs.csgs_layer_gemm(A[0], W, out[0], M_dev=M_dev[0, :1], inst=csgs.InstStrides(n_inst, 0, nb(M_dev), nb(A), 0, nb(out)))
+    torch.cuda.synchronize()
+    for k, n in enumerate(counts):
+        if n:
+            assert same_bits(out[k, :n], in_double("H", A[k, :n], W, N)), k
+        assert bool(torch.isnan(out[k, n:]).all()), "wrote outside"
