@@ -282,7 +282,8 @@ constexpr int WIDE_STEP = WIDE_BLOCK * 4;                  // mapped at a time
 constexpr int WIDE_BINS = 4096;
 constexpr int WIDE_STRIDE = WIDE_CHUNKS * SUB_STRIDE;      // entries per run of the groups' begins
 constexpr int WIDE_IDS = CAND_TILE * 4;                    // most ids of a bin
-constexpr int64_t BIN_FEW = 800;                            // expected edges per bin up to which a bin of several instances is one wavefront's
+constexpr int64_t BIN_FEW = 800;                            // expected edges per bin up to which a bin of several instances may be one wavefront's
+constexpr int32_t BIN_ONE_WAVE = 490;                       // entries per bin outside the local range up to which it is
 constexpr unsigned long long WIDE_WEIGHTS = 1ull << 52;
 // A bin outside the local range is crowded, and its edges of a run go through the atomics, from this many edges over all runs, runs taken as alike: one
 // block adds a bin up, at 0.4 ns an edge where runs are few and their groups long, at up to 1.4 where they are many.  Unless more of a run's bins are: then
@@ -823,11 +824,14 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, PACK ? 8 : 1) void cand_partials(u
 // FEW, several instances with up to BIN_FEW expected edges a bin and local tiles that take their share of them: a bin that is no local tile is one
 // wavefront's if it has up to 512 entries.  The wavefront sets a bit for every id that an entry names, and an id's sum stands at the number of bits before it, so
 // 512 sums do for 4096 ids, eight bins fit where one did, nothing waits at a barrier, and the sums are packed as they stand.  What holds more, or was met
-// through the table, is the block's afterwards, one bin after the other.  Eight instances of 380 K edges, 136 entries a bin: 39 -> 24 us (a block of 512
-// threads and 33 KB for each of 4488 bins took five and a half rounds).  The line: with scan, sums and emission of eight instances of 342 K edges, 822 expected
-// a bin, 20 / 50 / 80 / 100 % of them remote, blocks 82 / 84 / 82 / 83 us, wavefronts 74 / 77 / 102 / 104; without local tiles, 433 to 822 entries in
-// every bin, 120 and 109 against 134 and 157.  (Bins of up to 2048 entries by a wavefront in several passes over them: 73 / 78 / 92 / 94, but 1 % of a step more
-// where there are few; four wavefronts with room for 1024 sums each 76 / 79 / 85 / 88.)
+// through the table, is the block's afterwards, one bin after the other; a block's bins lie far apart, as crowded ones lie side by side where ids follow the degree.  Eight
+// instances of 380 K edges, 136 entries a bin: 39 -> 24 us (a block of 512 threads and 33 KB for each of 4488 bins took five and a half rounds).
+// How many entries the local tiles take is known here only: with more than BIN_ONE_WAVE a bin left for the others these go one by one over the blocks that
+// the device holds.  With scan, sums and emission of eight instances of 418 K edges, 745 a bin, 20 / 50 / 65 / 70 / 80 / 100 % of them remote, us:
+//   a block per bin 91 / 92 / 92 / 93 / 93 / 90, wavefronts whatever they find 78 / 79 / 92 / 109 / 111 / 108, this 77 / 78 / 93 / 98 / 98 / 94
+//   the remote ids by degree (density x^-2/3) 91 / 91 / 92 / 93 / 94 / 115, 118 / 155 / 175 / 180 / 191 / 210, 79 / 89 / 97 / 99 / 109 / 132
+// (With blocks for every bin launched 83 at 20 %, as those that leave come in rounds too; bins of up to 2048 entries by a wavefront in several passes, or four wavefronts
+// with room for 1024 sums each, cost the first column 1 to 3 us.)
 template <bool WHOLE, bool FEW>   // WHOLE: as in scan_wide; FEW: a wavefront for each bin that is no local tile
 __global__ __launch_bounds__(CAND_PART_BLOCK, 8) void bin_sums(uint64_t *__restrict__ wtable, uint8_t *__restrict__ tileflag, int64_t n_words, int64_t n_nodes,
                                                                int64_t n_tiles, int32_t lo, int32_t hi, const int64_t *__restrict__ meta, Stage stg,
@@ -842,7 +846,7 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, 8) void bin_sums(uint64_t *__restr
     __shared__ __attribute__((aligned(8))) uint32_t s_bits[WIDE_IDS / 32];   // ids with a weight
     __shared__ uint64_t lds[WAVES][3];
     __shared__ __attribute__((aligned(8))) uint32_t few_bits[FEW ? WAVES : 1][WIDE_IDS / 32];
-    __shared__ int32_t crowded[WAVES], n_crowded;
+    __shared__ int32_t crowded[WAVES], n_crowded, many_elsewhere;
     wtable = inst_ptr(wtable, is.ws); tileflag = inst_ptr(tileflag, is.ws); epoch = inst_ptr(epoch, is.ws);
     partial = inst_ptr(partial, is.ws); gtot = inst_ptr(gtot, is.ws);
     status = inst_ptr(status, is.buf); meta = inst_ptr(meta, is.ws);
@@ -1033,15 +1037,18 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, 8) void bin_sums(uint64_t *__restr
             whole_block((int32_t)blk);
             return;
         }
-        const int32_t others = stg.bins - stg.tiles, nth = ((int32_t)blk - own_blocks) * WAVES + wave;
+        const int32_t others = stg.bins - stg.tiles, groups = (others + WAVES - 1) / WAVES;
+        const int32_t nth = (int32_t)blk - own_blocks < groups ? wave * groups + (int32_t)blk - own_blocks : others;
         const int32_t bin = nth < stg.below ? nth : nth + stg.tiles;
         const bool mine = nth < others;
         uint32_t beg = 0, end = 0;
+        int32_t elsewhere = 0;   // entries of this lane's run that no local tile takes
         {
             const int64_t most = stg.chunks / WIDE_CHUNKS;
-            const uint16_t *p = stg.off + (mine ? bin : 0) + (lane < most ? lane : 0) * WIDE_STRIDE;
+            const uint16_t *run = stg.off + (lane < most ? lane : 0) * WIDE_STRIDE, *p = run + (mine ? bin : 0);
             beg = p[0];
             end = p[1];
+            if (wave == 0) elsewhere = (int32_t)run[stg.bins] - ((int32_t)run[stg.below + stg.tiles] - (int32_t)run[stg.below]);
         }
         const unsigned long long call = call_number(epoch);
         int64_t n_runs = 0;
@@ -1050,6 +1057,22 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, 8) void bin_sums(uint64_t *__restr
             const int64_t most = stg.chunks / WIDE_CHUNKS;
             if (n_runs > most) n_runs = most;
         }
+        if (wave == 0) {
+            elsewhere = wave_sum<int32_t>(lane < n_runs ? elsewhere : 0);
+            if (lane == 0) {
+                many_elsewhere = n_runs > WAVE || elsewhere > BIN_ONE_WAVE * others;   // (the same for all blocks)
+                n_crowded = 0;
+            }
+        }
+        __syncthreads();
+        if (many_elsewhere) {
+            for (int32_t i = (int32_t)blk - own_blocks; i < others; i += (int32_t)ib.blocks - own_blocks) {
+                whole_block(i < stg.below ? i - stg.below : own_blocks + (i - stg.below));
+                __syncthreads();
+            }
+            return;
+        }
+        if ((int32_t)blk - own_blocks >= groups) return;
         const int64_t tile0 = stg.lo / CAND_TILE, local_end = tile0 + stg.tiles;
         int64_t first_tile, t0, t1;
         if (nth < stg.below) {
@@ -1062,8 +1085,6 @@ __global__ __launch_bounds__(CAND_PART_BLOCK, 8) void bin_sums(uint64_t *__restr
             if (t0 < local_end) t0 = local_end;
         }
         if (t1 > n_tiles) t1 = n_tiles;
-        if (tid == 0) n_crowded = 0;
-        __syncthreads();
         constexpr int MOST = WIDE_IDS / WAVES;   // sums that a wavefront has room for
         const int64_t word = first_tile * CAND_WORDS + lane;   // this lane's 64 ids
         bool wave_does = mine && t0 < t1;
@@ -1605,7 +1626,11 @@ static int build_probs_impl(const csgs_graph *g, const int32_t *S, int32_t nS, c
     CSGS_LAUNCH_CHECK();
     const int64_t others = below + rest;
     const bool few = wide && !stg.runs && tiles && fmin(mean, (double)w.chunk_cap) * EDGE_TILE <= (double)(BIN_FEW * others);
-    const InstGrid part = inst_grid(w, few ? tiles * split + (others + CAND_PART_BLOCK / WAVE - 1) / (CAND_PART_BLOCK / WAVE) : part_blocks, CAND_PART_BLOCK);
+    // FEW: a wavefront for every other bin, and, should they be taken one by one, as many blocks as the device holds (else these leave at once)
+    constexpr int64_t FEW_BINS = CAND_PART_BLOCK / WAVE, FEW_BLOCKS = SCAN_GRID / 2;
+    int64_t few_blocks = (others + FEW_BINS - 1) / FEW_BINS;
+    if (few_blocks < FEW_BLOCKS / w.n_inst) few_blocks = FEW_BLOCKS / w.n_inst < others ? FEW_BLOCKS / w.n_inst : others;
+    const InstGrid part = inst_grid(w, few ? tiles * split + few_blocks : part_blocks, CAND_PART_BLOCK);
 #define CSGS_CAND_PARTIALS(TILES, PACK)                                                                                                       \
     CSGS_LAUNCH(K_CAND_PARTIALS, (cand_partials<TILES, PACK>), part.grid, dim3(CAND_PART_BLOCK), st, w.wtable, w.tileflag, n_words, g->n_nodes, \
                 w.n_tiles, g->local_lo, g->local_hi, rows.meta, stg, (int32_t)(tiles ? below : part_blocks), w.epoch,                   \

@@ -583,8 +583,9 @@ def test_weight_scan_of_many_edges(dev, n, lo, hi, n_rows, degree, remote_ids, c
 
 
 # The same with few edges to a bin, whose sums are one wavefront's: bins with none, with more than it has room for (the block's), with more than the scan
-# hands over (through the table), bins cut by the local range
-@pytest.mark.parametrize("lo,hi,local,hot", [(0, 106_000, 0.8, 0.0), (700_300, 806_001, 0.7, 0.02), (1_790_001, 1_900_001, 0.7, 0.25), (700_300, 806_001, 0.1, 0.0)])
+# hands over (through the table), bins cut by the local range; as many entries outside the local range as decide whether wavefronts or blocks take them
+@pytest.mark.parametrize("lo,hi,local,hot", [(0, 106_000, 0.8, 0.0), (700_300, 806_001, 0.7, 0.02), (1_790_001, 1_900_001, 0.7, 0.25), (700_300, 806_001, 0.1, 0.0),
+                                             (700_300, 806_001, 0.39, 0.0), (0, 106_000, 0.33, 0.0), (1_790_001, 1_900_001, 0.39, 0.3)])
 def test_weight_scan_of_few_edges_a_bin(dev, lo, hi, local, hot):
     from paper_2101_07706_amd import csgs, pipeline
     rng = np.random.default_rng(lo + 1)
