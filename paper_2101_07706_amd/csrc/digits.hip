@@ -718,8 +718,8 @@ void launch_digits(const DigitsPlan &d, const float *A, int64_t lda, const float
                 ci.n, ci.cs)
 #define CSGS_DIGITS(KC, NT)                                         \
     do {                                                            \
-        if (MODE == MODE_FWD) CSGS_DIGITS_AS(K_GEMM, KC, NT);       \
-        else CSGS_DIGITS_AS(K_GEMM_DZ, KC, NT);                     \
+        if (MODE == MODE_FWD) CSGS_DIGITS_AS(K_GEMM_DIGITS, KC, NT); \
+        else CSGS_DIGITS_AS(K_GEMM_DZ_DIGITS, KC, NT);              \
     } while (0)
     if (d.kc == 1) CSGS_DIGITS(1, 2);
     else if (d.kc == 2) CSGS_DIGITS(2, 2);

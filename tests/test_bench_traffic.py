@@ -1,4 +1,4 @@
-"""bench.py reports measured memory traffic only from a summary taken on the kernels that it times."""
+"""bench.py reports measured memory traffic only from a summary taken on the kernels that it times, and every kernel against the peak of what it issues."""
 import bench
 
 TABLE = """HBM traffic per kernel launch, workload 'w', 8 mini-batches per launch
@@ -30,3 +30,10 @@ def test_hash_sees_code_and_not_comments(tmp_path):
     assert bench.kernel_sources_hash(str(tmp_path)) == first
     a.write_text("int f() { return 2; }")
     assert bench.kernel_sources_hash(str(tmp_path)) != first
+
+
+def test_products_are_held_against_their_own_instruction():
+    k = dict(TFLOPs=50.0, flop_per_launch=1e9, avg_us=20.0)
+    double, digits, fused = (bench.roofline_of({n: k}, n, (None, ""), 8) for n in ("layer_gemm", "layer_gemm_digits", "layer_forward"))
+    assert double["peak"] == fused["peak"] == bench.MFMA_F64_PEAK_TFLOPS and digits["peak"] == bench.MFMA_I8_PEAK_TOPS / 19
+    assert digits["frac"] < digits["frac_of_fp64_matrix_peak"] == double["frac"]
