@@ -192,13 +192,14 @@ class Workload:
         """Under which name the library times the product of layer l as the timed schedule launches it: its sizes decide which kernel it is."""
         if l not in self.product_names:
             torch, csgs, nb = self.torch, self.csgs, lambda t: t.stride(0) * t.element_size()
-            nS, W = self.Sd[0].numel() if l == 0 else self.B, self.Wd[self.M - 1 - l]
+            nS, W, lb = self.Sd[0].numel() if l == 0 else self.B, self.Wd[self.M - 1 - l], self.lb_sets[0][max(l - 1, 0)]
+            M_dev = lb.n_next if l else None
             csgs.csgs_profile_enable(True)
             if self.batch_compute:
                 Z, H = self.ZsK[l], self.HsK[l]
-                csgs.csgs_layer_gemm(Z[0, :nS], W, H[0, :nS], inst=csgs.InstStrides(self.n_inst, 0, 0, nb(Z), 0, nb(H)))
+                csgs.csgs_layer_gemm(Z[0, :nS], W, H[0, :nS], M_dev=M_dev, inst=csgs.InstStrides(self.n_inst, 0, lb.stride, nb(Z), 0, nb(H)))
             else:
-                csgs.csgs_layer_gemm(self.Zs[l][:nS], W, self.Hs[l][:nS])
+                csgs.csgs_layer_gemm(self.Zs[l][:nS], W, self.Hs[l][:nS], M_dev=M_dev)
             torch.cuda.synchronize()
             csgs.csgs_profile_enable(False)
             self.product_names[l], = csgs.csgs_profile_collect()

@@ -264,6 +264,19 @@ __global__ __launch_bounds__(64 * WPB, 1) void gemm_digits_k(
                 if (QPR == 2) m = least_of(x[8 * i + 4], x[8 * i + 5], least_of(x[8 * i + 6], x[8 * i + 7], m));
                 some |= m < least[i];
             }
+            if (__any(some)) {   // (zeros count for nothing: twice the bits less one is largest for them)
+                some = false;
+#pragma unroll
+                for (int i = 0; i < ROWS; ++i) {
+                    uint32_t m = ~0u;
+#pragma unroll
+                    for (int j = 0; j < 4 * QPR; ++j) {
+                        const uint32_t v = (uint32_t)__float_as_int(x[4 * QPR * i + j]) * 2u - 1u;
+                        m = m < v ? m : v;
+                    }
+                    some |= m < (uint32_t)__float_as_int(least[i]) * 2u - 1u;
+                }
+            }
             if (__any(some)) {
 #pragma unroll
                 for (int i = 0; i < ROWS; ++i)

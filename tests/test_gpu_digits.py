@@ -28,11 +28,10 @@ def product(what, A, W, out, **kw):
 
 
 def check(got, A, B):
-    """One rounding to float (2^-24) and what the digits leave out, which is six standard deviations at 2^-22 of an output; beside it, for outputs
-    summed in double, 2^-52 of the summands each, and the least float."""
+    """One rounding to float (2^-24), whichever form sums; beside it 2^-52 of the summands each for the sums in double, here and there, and the least float."""
     A, B = A.double(), B.double()
     want = A @ B
-    bound = (2.0 ** -24 + 2.0 ** -22) * want.abs() + A.shape[1] * 2.0 ** -52 * (A.abs() @ B.abs()) + 2.0 ** -150
+    bound = 2.0 ** -24 * want.abs() + A.shape[1] * 2.0 ** -52 * (A.abs() @ B.abs()) + 2.0 ** -150
     d = (got.double() - want).abs()
     assert bool((d <= bound).all()), float((d / bound).nan_to_num().max())
     return float(d.norm()) / float(want.norm())
@@ -95,8 +94,8 @@ def test_digit_products_instances(dev):
         assert bool(torch.isnan(out[k, n:]).all()), "wrote outside"
 
 
-# What the digits do not hold: outputs that all but cancel (some, and so many that a block cannot list them), rows and columns of zeros, of numbers
-# beyond the exponents that are used, of one large number among small ones
+# What the digits do not hold: outputs that all but cancel (in some rows, and in all, where whole tiles are summed again and blocks go on in double), rows and
+# columns of zeros, of numbers beyond the exponents that are used, of one large number among small ones
 @pytest.mark.parametrize("what", ["H", "dZ"])
 @pytest.mark.parametrize("kind", ["cancel", "cancel_all", "zeros", "tiny", "huge", "spread"])
 def test_digit_products_hard(dev, what, kind):
@@ -129,8 +128,8 @@ def test_digit_products_hard(dev, what, kind):
         assert bool((out[5:M:9, :N] == 0).all()) and bool((out[:M, 3:N:5] == 0).all())
 
 
-# More outputs that are small against row and column than a block lists, where the last step lacks whole tiles of rows: one feature 300 times the others
-# that no weight looks at, one output in fifty
+# So many outputs that are small against row and column that blocks go on in double, where the last step lacks whole tiles of rows: one feature 300 times the
+# others that no weight looks at, one output in fifty
 @pytest.mark.parametrize("what", ["H", "dZ"])
 @pytest.mark.parametrize("counted", [False, True])
 @pytest.mark.parametrize("K,M", [(256, 65_537), (128, 100_003), (64, 131_069)])
@@ -233,8 +232,8 @@ def test_digit_products_equal_double_hard(dev, what, kind, K, N, M):
 
 # More to sum again than the list holds: worked off several times, then so much that the rest is done in double (from the first row on, from the middle on, in no step)
 @pytest.mark.parametrize("what", ["H", "dZ"])
-@pytest.mark.parametrize("dense_from", [0, 300_007, None])
-@pytest.mark.parametrize("K,N,M", [(100, 256, 600_005), (260, 130, 400_009)])
+@pytest.mark.parametrize("dense_from", [0, 100_007, None])
+@pytest.mark.parametrize("K,N,M", [(100, 256, 600_005), (260, 256, 200_009)])
 def test_digit_products_list_worked_off(dev, what, dense_from, K, N, M):
     print(f"[digits] {what} {M} x {K} x {N} many listed, all from {dense_from}", flush=True)
     A, W, out = operands(dev, what, K, N, M, 11)
@@ -249,12 +248,12 @@ def test_digit_products_list_worked_off(dev, what, dense_from, K, N, M):
 
 
 # Steps are counted over the rows that there are: instances of any number of rows one after the other, their outputs listed, rows beyond the counts of any value
-@pytest.mark.parametrize("counts", [[16_000, 0, 33, 9_000, 16_000, 1, 0, 12_345], [0, 0, 0, 16_000], [16_000, 15_999, 0], [2_100] * 64])
+@pytest.mark.parametrize("counts", [[16_000, 0, 33, 9_000, 16_000, 1, 0, 12_345], [0, 0, 0, 16_000], [27_000, 26_999, 0], [2_100] * 64])
 @pytest.mark.parametrize("hard_values", [False, True])
 @pytest.mark.parametrize("K", [100, 256])
 def test_digit_products_steps_of_instances(dev, counts, hard_values, K):
     from paper_2101_07706_amd import csgs
-    N, M, n_inst = 256, max(counts) if len(counts) == 64 else 16_000, len(counts)
+    N, M, n_inst = 256, max(counts), len(counts)
     print(f"[digits] {n_inst} instances of {M} x {K} x {N}, hard {hard_values}", flush=True)
     A, W, _ = operands(dev, "H", K, N, M * n_inst, 13)
     A *= torch.randn(K, generator=torch.Generator(device=dev).manual_seed(8), device=dev).mul_(1.5).exp_()

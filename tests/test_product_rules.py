@@ -139,3 +139,18 @@ def test_list_has_room_for_a_step(tmp_path):
         assert 2 * step <= room < 2 ** 15 and tile <= 16
         lds = 2 * rows // 16 * 5 * kc * 1088 + 8 * kc * nt * 1024 + 2 * rows * 8 + 4 * room + 16
         assert lds <= 160 * 1024
+
+
+def test_digit_forms_are_compared_with_calls_in_double(tmp_path):
+    """The products that the tests compare go by digits, and the calls of 512 rows that they are compared with never do."""
+    from test_gpu_digits import SHAPES
+    (tmp_path / "ask.cpp").write_text(ASK_DIGITS)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", build.CSRC, "-o", str(tmp_path / "ask"), str(tmp_path / "ask.cpp")], check=True)
+    by_digits = [(M, K, N, 1, z) for K, N, M in SHAPES + [(64, 256, 131_069), (256, 256, 32_033), (512, 512, 8_191), (256, 256, 65_537), (128, 256, 100_003), (100, 256, 600_005),
+                                                         (260, 256, 200_009)] for z in (0, 1)]
+    by_digits += [(M, K, 256, n, 0) for K in (100, 256) for M, n in ((16_000, 8), (16_000, 4), (27_000, 3), (2_100, 64))]
+    in_double = [(512, K, N, 1, z) for K in range(16, 513, 3) for N in (16, 100, 256, 512, 700) for z in (0, 1)]
+    sent = "\n".join(" ".join(map(str, s)) for s in by_digits + in_double)
+    out = subprocess.run([str(tmp_path / "ask")], input=sent, stdout=subprocess.PIPE, text=True, check=True).stdout
+    use = [int(line.split()[0]) for line in out.splitlines()]
+    assert use == [1] * len(by_digits) + [0] * len(in_double), [s for s, u in zip(by_digits + in_double, use) if u != (s in by_digits)]
