@@ -33,9 +33,9 @@
 //  * All of a tile's outputs are put together before the first is stored: each is a chain of ten instructions (131072 x 256 x 256 with a row's two outputs
 //    at a time 191 against 184).  Registers are full: one value more and the loop waits for a reload behind the loads of A (211 against 191).
 // Measured in double / now, us: 131072 rows 256 -> 256 252 / 148, 128 -> 256 135 / 86, 64 -> 256 79 / 60, 65 536 rows 512 -> 128 126 / 90.
-// Operands that leave the digits little, in double / now, us: scales of features by exp(1.5 g) 131072 x 256 x 256 255 / 181, 2449029 x 100 x 256 2160 / 1905, 65536 x 512 x 128
-// 124 / 119; one feature 300 times the others that no weight looks at (one output in 57) 250 / 287, 2160 / 2286, 124 / 167; infinities everywhere 252 / 281, 2156 / 2274, 124 / 163
-// (normal numbers 255 / 146, 2160 / 1530, 126 / 89).  (A list of 512 outputs, and everything of a block that lists more again: 650, 6490, 305, and 6020 for the normal numbers
+// Operands that leave the digits little, in double / now, us: scales of features by exp(1.5 g) 131072 x 256 x 256 255 / 183, 2449029 x 100 x 256 2160 / 1915, 65536 x 512 x 128
+// 124 / 120; one feature 300 times the others that no weight looks at (one output in 57) 250 / 287, 2160 / 2286, 124 / 167; infinities everywhere 252 / 281, 2156 / 2274, 124 / 163
+// (normal numbers 255 / 148, 2160 / 1475, 126 / 90).  (A list of 512 outputs, and everything of a block that lists more again: 650, 6490, 305, and 6020 for the normal numbers
 // of 2449029 rows; a list that is worked off by itself, 16 outputs of a tile of 16 x 16 before all of it is summed again: 501, 4440, 366.)
 // A step of 32 rows by 256 columns takes 8 us, of which the matrix instructions 4.4; the rest is the
 // wavefronts' own chain (read, multiply, put together, cut, write).
